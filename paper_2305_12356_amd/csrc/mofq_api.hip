@@ -105,7 +105,7 @@ WOnlyWs carve_w_only(void* ws, int64_t units, int n_cand, int gran, int n_clip) 
     w.err[i] = c.take<double>(units);
   }
   w.energy = c.take<double>(units);
-  w.decide_part = c.take<double>(static_cast<size_t>(MOFQ_MAX_CANDIDATES + 1) * kDecideBlocks);
+  w.decide_part = c.take<double>(kDecidePart);
   if (gran == MOFQ_PER_TENSOR) {
     w.absmax_part = c.take<float>(kTensorBlocks);
     w.energy_part = c.take<double>(kTensorBlocks);
@@ -324,10 +324,9 @@ int wo_output_score(const mofq_tensor_t* w, const mofq_tensor_t* x, const int32_
       e.scale[0] = a.wrec.scale[c];
       e.clip[0] = a.wrec.clip[c];
       e.err[0] = a.wrec.err[c];
-      e.result = nullptr;
       e.out.codes = a.wg[c];
       e.as_bf16_values = 1;
-      if ((rc = launch_emit(e, st))) return rc;
+      if ((rc = launch_emit(&e, 1, 0, st))) return rc;
     }
     g.q[c].kind = WA_GRID_BF16;
     g.q[c].x = x->data;          // the unquantized input, scale 1
@@ -428,10 +427,9 @@ int wa_score(const mofq_tensor_t* w, const mofq_tensor_t* x, const int32_t* cand
       e.scale[0] = rec.scale[slot];
       e.clip[0] = rec.clip[slot];
       e.err[0] = rec.err[slot];
-      e.result = nullptr;
       e.out.codes = which ? a.wq[f] : a.xq[f];
       e.as_bf16_values = (f == 1 && !fp8_unit);
-      if ((rc = launch_emit(e, st))) return rc;
+      if ((rc = launch_emit(&e, 1, 0, st))) return rc;
     }
     WaProduct& q = g.q[n_q++];
     q.kind = f == 0 ? WA_INT8 : (fp8_unit ? WA_FP8 : WA_GRID_BF16);
@@ -469,9 +467,8 @@ int select_wa_general(const mofq_tensor_t* w, const mofq_tensor_t* x, const int3
   d.n_cand = n_candidates;
   for (int c = 0; c < n_candidates; ++c) d.err[c] = candidates[c] == MOFQ_INT8 ? a.part[0] : a.part[1];
   d.energy = a.part[2];
-  d.result = result;
-  if ((rc = launch_decide(d, st))) return rc;
-  // second quantize_layer call of Algorithm 1: W and X in the chosen format
+  // second quantize_layer call of Algorithm 1: W and X in the chosen format (each launch takes the
+  // select from the tile partials; W's leaves the record)
   for (int which = 0; which < 2; ++which) {
     const mofq_tensor_t* t = which ? w : x;
     const mofq_qout_t* o = which ? w_out : x_out;
@@ -492,9 +489,10 @@ int select_wa_general(const mofq_tensor_t* w, const mofq_tensor_t* x, const int3
       e.clip[c] = rec.clip[c];
       e.err[c] = rec.err[c];
     }
-    e.result = result;
+    e.decide = d;
+    e.decide.result = which ? result : nullptr;
     e.out = *o;
-    if ((rc = launch_emit(e, st))) return rc;
+    if ((rc = launch_emit(&e, 1, 0, st))) return rc;
   }
   return MOFQ_OK;
 }
@@ -753,7 +751,6 @@ int select_w_only(const mofq_tensor_t* w, const int32_t* candidates, int n_candi
   d.energy = s.energy;
   d.part = s.decide_part;
   d.result = result;
-  if ((rc = launch_decide(d, st))) return rc;
   EmitParams e{};
   e.w = w->data;
   e.dtype = w->dtype;
@@ -770,9 +767,9 @@ int select_w_only(const mofq_tensor_t* w, const int32_t* candidates, int n_candi
     e.clip[c] = s.clip[c];
     e.err[c] = s.err[c];
   }
-  e.result = result;
+  e.decide = d;
   e.out = *w_out;
-  return launch_emit(e, st);
+  return launch_emit(&e, 1, 0, st);
 }
 
 }  // namespace
@@ -870,16 +867,14 @@ int mofq_quantize(const mofq_tensor_t* t, int32_t format, const mofq_scale_cfg_t
   if (!ws || ws_bytes < w.bytes || !aligned16(ws)) return MOFQ_ERR_WORKSPACE;
   hipStream_t st = static_cast<hipStream_t>(stream);
   if ((rc = sweep_candidates(t, &format, 1, cfg, w, st))) return rc;
-  if (tensor_err) {
-    DecideParams d{};
-    d.units = units;
-    d.n_cand = 1;
-    d.err[0] = w.err[0];
-    d.part = w.decide_part;
-    d.tensor_err_out = tensor_err;
-    if ((rc = launch_decide(d, st))) return rc;
-  }
   EmitParams e{};
+  if (tensor_err) {
+    e.decide.units = units;
+    e.decide.n_cand = 1;
+    e.decide.err[0] = w.err[0];
+    e.decide.part = w.decide_part;
+    e.decide.tensor_err_out = tensor_err;
+  }
   e.w = t->data;
   e.dtype = t->dtype;
   e.rows = t->rows;
@@ -893,9 +888,8 @@ int mofq_quantize(const mofq_tensor_t* t, int32_t format, const mofq_scale_cfg_t
   e.scale[0] = w.scale[0];
   e.clip[0] = w.clip[0];
   e.err[0] = w.err[0];
-  e.result = nullptr;
   e.out = *out;
-  return launch_emit(e, st);
+  return launch_emit(&e, 1, 0, st);
 }
 
 int mofq_score(const mofq_tensor_t* w, const mofq_tensor_t* x, int32_t format, int32_t metric,
@@ -962,7 +956,7 @@ int mofq_score(const mofq_tensor_t* w, const mofq_tensor_t* x, int32_t format, i
 
 namespace {
 
-// A batch of mofq_select_layers ends at kFinishBatch tensors or once it holds 2 MB of input per
+// A batch of mofq_select_layers ends at kEmitBatch tensors or once it holds 2 MB of input per
 // compute unit.  The batch is the unit of overlap (its select and emission run beside the next
 // batch's searches) and of search grouping (its tensors of one row length share a launch), so
 // it should span the same-length tensors of a transformer block; past that, larger batches
@@ -975,7 +969,7 @@ int batch_length(int n_layers, const mofq_tensor_t* w, int i0, int cus) {
   const int64_t batch_bytes = static_cast<int64_t>(cus) * (int64_t{2} << 20);
   int64_t bytes = 0;
   int nb = 0;
-  for (; i0 + nb < n_layers && nb < kFinishBatch; ++nb) {
+  for (; i0 + nb < n_layers && nb < kEmitBatch; ++nb) {
     const int64_t b = w[i0 + nb].rows * w[i0 + nb].cols * (w[i0 + nb].dtype == MOFQ_F32 ? 4 : 2);
     if (nb > 0 && bytes + b > batch_bytes) break;
     bytes += b;
@@ -1014,7 +1008,7 @@ int mofq_select_layers_search_groups(int32_t n_layers, const mofq_tensor_t* w, c
   const int cus = compute_units();
   for (int i0 = 0, nb = 0; i0 < n_layers; i0 += nb) {
     nb = batch_length(n_layers, w, i0, cus);
-    int first[kFinishBatch];
+    int first[kEmitBatch];
     plan_search_groups(w + i0, nb, candidates, n_candidates, first);
     for (int j = 0; j < nb; ++j) group_first[i0 + j] = i0 + first[j];
   }
@@ -1072,6 +1066,7 @@ int mofq_select_layers_timed(int32_t n_layers, const mofq_tensor_t* w, const int
   const int cus = compute_units();
   int emit_cap = sw.two ? 2 * cus : 0;
 
+  // everything after the search of tensor i: reduce + select, codes and per-unit outputs
   auto emit_params = [&](int i, const WOnlyWs& s) {
     EmitParams e{};
     e.w = w[i].data;
@@ -1083,32 +1078,34 @@ int mofq_select_layers_timed(int32_t n_layers, const mofq_tensor_t* w, const int
     e.group = w_cfg->group_size;
     e.scale_f16_out = w_cfg->scale_dtype == MOFQ_F16;
     e.n_cand = n_candidates;
+    DecideParams& d = e.decide;
+    d.units = mofq_num_units(w[i].rows, w[i].cols, w_cfg->gran, w_cfg->group_size);
+    d.n_cand = n_candidates;
     for (int c = 0; c < n_candidates; ++c) {
       e.fmt[c] = candidates[c];
       e.scale[c] = s.scale[c];
       e.clip[c] = s.clip[c];
       e.err[c] = s.err[c];
+      d.err[c] = s.err[c];
     }
-    e.result = &results[i];
+    d.energy = s.energy;
+    d.part = s.decide_part;
+    d.result = &results[i];
     e.out = w_out[i];
-    e.max_blocks = emit_cap;
     return e;
   };
 
   char* base = static_cast<char*>(ws);
   for (int i0 = 0, nb = 0; i0 < n_layers; i0 += nb) {
     nb = batch_length(n_layers, w, i0, cus);
-    WOnlyWs slot[kFinishBatch];
-    FinishParams fin[kFinishBatch];
-    DecideParams big[kFinishBatch];
-    int n_fin = 0, fin_of[kFinishBatch], n_big = 0, big_of[kFinishBatch];
+    WOnlyWs slot[kEmitBatch];
     // 1. the searches, back to back; the tensors of one row length share a launch
     for (int j = 0; j < nb; ++j) {
       const int64_t units = mofq_num_units(w[i0 + j].rows, w[i0 + j].cols, w_cfg->gran, w_cfg->group_size);
       slot[j] = carve_w_only(base, units, n_candidates, w_cfg->gran, w_cfg->n_clip);
       base += slot[j].bytes;
     }
-    int first[kFinishBatch];
+    int first[kEmitBatch];
     plan_search_groups(w + i0, nb, candidates, n_candidates, first);
     const bool one_launch = one_sweep_launch(candidates, n_candidates);
     for (int j = 0; j < nb; ++j) {
@@ -1134,50 +1131,18 @@ int mofq_select_layers_timed(int32_t n_layers, const mofq_tensor_t* w, const int
       }
       if (ev_end && hipEventRecord(static_cast<hipEvent_t>(ev_end[i0 + last]), st) != hipSuccess) return join(MOFQ_ERR_HIP);
     }
-    for (int j = 0; j < nb; ++j) {
-      const int i = i0 + j;
-      const int64_t units = mofq_num_units(w[i].rows, w[i].cols, w_cfg->gran, w_cfg->group_size);
-      DecideParams d{};
-      d.units = units;
-      d.n_cand = n_candidates;
-      for (int c = 0; c < n_candidates; ++c) d.err[c] = slot[j].err[c];
-      d.energy = slot[j].energy;
-      d.part = slot[j].decide_part;
-      d.result = &results[i];
-      if (units <= kFinishMaxUnits) {
-        FinishParams& f = fin[n_fin];
-        f = FinishParams{};
-        f.d = d;
-        f.scale_f16_out = w_cfg->scale_dtype == MOFQ_F16;
-        for (int c = 0; c < n_candidates; ++c) { f.scale[c] = slot[j].scale[c]; f.clip[c] = slot[j].clip[c]; }
-        f.out_scales = w_out[i].scales;
-        f.out_clip = w_out[i].clip_idx;
-        f.out_unit_err = w_out[i].unit_err;
-        fin_of[n_fin++] = j;
-      } else {
-        // many units (group-wise scales): the two-stage reduce and the per-unit kernel of the
-        // single-tensor path, after the batch's searches
-        big[n_big] = d;
-        big_of[n_big++] = j;
-      }
-    }
     if (i0 + nb >= n_layers) emit_cap = 0;   // nothing runs beside the last batch's emission
-    // 2. on the second stream, once the batch's searches are done: reduce + select + per-unit
-    //    outputs of the batch in one launch, then the codes of the winners.  The next batch's
-    //    searches follow on the caller's stream meanwhile; every tensor has its own workspace.
+    // 2. on the second stream, once the batch's searches are done: reduce + select, the codes of
+    //    the winners and the per-unit outputs, one launch for the tensors of one dtype.  The next
+    //    batch's searches follow on the caller's stream meanwhile; every tensor has its own
+    //    workspace.
     if ((rc = sw.fork())) return join(rc);
-    if (n_fin && (rc = launch_finish_batch(fin, n_fin, st2))) return join(rc);
-    for (int q = 0; q < n_fin; ++q) {
-      const int j = fin_of[q];
-      EmitParams e = emit_params(i0 + j, slot[j]);
-      e.out.scales = nullptr;
-      e.out.clip_idx = nullptr;
-      e.out.unit_err = nullptr;
-      if ((rc = launch_emit(e, st2))) return join(rc);
-    }
-    for (int q = 0; q < n_big; ++q) {
-      if ((rc = launch_decide(big[q], st2))) return join(rc);
-      if ((rc = launch_emit(emit_params(i0 + big_of[q], slot[big_of[q]]), st2))) return join(rc);
+    for (int dtype : {MOFQ_F32, MOFQ_F16, MOFQ_BF16}) {
+      EmitParams e[kEmitBatch];
+      int n = 0;
+      for (int j = 0; j < nb; ++j)
+        if (w[i0 + j].dtype == dtype) e[n++] = emit_params(i0 + j, slot[j]);
+      if (n && (rc = launch_emit(e, n, emit_cap, st2))) return join(rc);
     }
   }
   return join(MOFQ_OK);
@@ -1223,8 +1188,7 @@ int mofq_select_calibrated(const mofq_tensor_t* x, const int32_t* candidates, in
   for (int c = 0; c < n_candidates; ++c) d.err[c] = s.err[c];
   d.energy = s.energy;
   d.result = result;
-  if ((rc = launch_decide(d, st))) return rc;
-  if (!x_out) return MOFQ_OK;
+  if (!x_out) return launch_decide(d, st);
   EmitParams e{};
   e.w = x->data;
   e.dtype = x->dtype;
@@ -1240,9 +1204,9 @@ int mofq_select_calibrated(const mofq_tensor_t* x, const int32_t* candidates, in
     e.clip[c] = s.clip[c];
     e.err[c] = s.err[c];
   }
-  e.result = result;
+  e.decide = d;
   e.out = *x_out;
-  return launch_emit(e, st);
+  return launch_emit(&e, 1, 0, st);
 }
 
 size_t mofq_select_units_workspace_bytes(const mofq_tensor_t* w, int32_t n_candidates,
@@ -1269,9 +1233,8 @@ int mofq_select_units(const mofq_tensor_t* w, const int32_t* candidates, int32_t
   const WOnlyWs s = carve_w_only(ws, units, n_candidates, w_cfg->gran, w_cfg->n_clip);
   const size_t need = mofq_select_units_workspace_bytes(w, n_candidates, w_cfg);
   if (!ws || !need || ws_bytes < need || !aligned16(ws)) return MOFQ_ERR_WORKSPACE;
-  double* picked = reinterpret_cast<double*>(static_cast<char*>(ws) + s.bytes);
   if ((rc = sweep_candidates(w, candidates, n_candidates, w_cfg, s, st))) return rc;
-  // the layer-wise view, as mofq_select_layer reports it
+  // the layer-wise view, as mofq_select_layer reports it, and the sum of the per-unit minima
   DecideParams d{};
   d.units = units;
   d.n_cand = n_candidates;
@@ -1279,22 +1242,7 @@ int mofq_select_units(const mofq_tensor_t* w, const int32_t* candidates, int32_t
   d.energy = s.energy;
   d.part = s.decide_part;
   d.result = result;
-  if ((rc = launch_decide(d, st))) return rc;
-  // per unit
-  PickUnitsParams pk{};
-  pk.units = units;
-  pk.n_cand = n_candidates;
-  for (int c = 0; c < n_candidates; ++c) pk.err[c] = s.err[c];
-  pk.unit_fmt = unit_format;
-  pk.picked_err = picked;
-  if ((rc = launch_pick_units(pk, st))) return rc;
-  DecideParams m{};
-  m.units = units;
-  m.n_cand = 1;
-  m.err[0] = picked;
-  m.part = s.decide_part;
-  m.tensor_err_out = mixed_err;
-  if ((rc = launch_decide(m, st))) return rc;
+  d.mixed_out = mixed_err;
   EmitParams e{};
   e.w = w->data;
   e.dtype = w->dtype;
@@ -1311,10 +1259,10 @@ int mofq_select_units(const mofq_tensor_t* w, const int32_t* candidates, int32_t
     e.clip[c] = s.clip[c];
     e.err[c] = s.err[c];
   }
-  e.result = nullptr;
+  e.decide = d;
   e.unit_fmt = unit_format;
   e.out = *w_out;
-  return launch_emit(e, st);
+  return launch_emit(&e, 1, 0, st);
 }
 
 int mofq_select_layer(const mofq_tensor_t* w, const mofq_tensor_t* x, const int32_t* candidates,
@@ -1420,7 +1368,6 @@ int mofq_select_layer_timed(const mofq_tensor_t* w, const mofq_tensor_t* x,
     for (int c = 0; c < n_candidates; ++c) d.err[c] = a.part[c];
     d.energy = a.part[2];
     d.result = result;
-    if ((rc = launch_decide(d, st))) return rc;
     // second quantize_layer call of Algorithm 1: W in the chosen format
     EmitParams e{};
     e.w = w->data;
@@ -1438,9 +1385,9 @@ int mofq_select_layer_timed(const mofq_tensor_t* w, const mofq_tensor_t* x,
       e.clip[c] = a.wrec.clip[c];
       e.err[c] = a.wrec.err[c];
     }
-    e.result = result;
+    e.decide = d;
     e.out = *w_out;
-    return launch_emit(e, st);
+    return launch_emit(&e, 1, 0, st);
   }
   if (metric != MOFQ_ERR_LAYER_OUTPUT && metric != MOFQ_ERR_LAYER_OUTPUT_FP8_UNIT)
     return MOFQ_ERR_INVALID_ARG;

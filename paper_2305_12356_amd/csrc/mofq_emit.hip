@@ -1,7 +1,9 @@
 // Tensor-level reduce + format select (Algorithm 1's strict-less rule), and the
 // second quantize_layer call of Algorithm 1: emit the codes of the winning format
-// with the scales the search chose.  Both read the decision from device memory,
+// with the scales the search chose.  The decision never leaves device memory,
 // so a whole model can be processed without a host synchronisation.
+#include <algorithm>
+
 #include "mofq_device.h"
 #include "mofq_internal.h"
 
@@ -9,130 +11,176 @@ namespace mofq {
 
 namespace {
 
-// ---- decide ---------------------------------------------------------------------
+// ---- tensor-level reduce + select ---------------------------------------------------
 
-constexpr int kDecideThreads = 1024;
+constexpr int kThreads = 256;
+constexpr int kNW = kThreads / 64;
 
-// Sum of v[0..n) over the block in a fixed order (thread-strided partials, then
-// wave sums, then the waves in order); the result is valid on thread 0.
-MOFQ_DEV double block_sum(const double* v, int64_t n, double* s_red, int64_t step = 1) {
+// Sums over the units are taken in two stages of a fixed shape, so that a result depends on the
+// number of values alone and not on the launch: consecutive chunks of values (one workgroup each),
+// then the chunk sums.  Up to kDirectUnits values there is one stage: reading 8 KB per candidate
+// in every emitting workgroup costs less than one more launch (2.5 us of host time, about 2 us on
+// the device); beyond, the first stage leaves at most kDecideBlocks values.
+constexpr int64_t kDirectUnits = 1024;
+int64_t partial_chunks(int64_t n) {
+  return n <= kDirectUnits ? 0 : std::min<int64_t>(kDecideBlocks, (n + kDirectUnits - 1) / kDirectUnits);
+}
+
+// every candidate's error, the energy, the sum of the smallest error of every unit
+constexpr int kEnergy = MOFQ_MAX_CANDIDATES, kMixed = kEnergy + 1, kSums = kMixed + 1;
+
+struct SumArrays {
+  const double* v[kSums];   // nullptr: not asked for; v[kMixed] is only read in the last stage
+  int32_t n_cand;
+  int32_t mixed;            // form the per-unit minimum over the candidates' arrays
+};
+
+// Sums over the workgroup in a fixed order (thread-strided partials, wave sums, then the waves
+// in order); every thread gets all of them.
+MOFQ_DEV void block_sums(const SumArrays& a, int64_t lo, int64_t n, double (&out)[kSums], double (&s_red)[kSums][kNW]) {
   const int tid = threadIdx.x;
-  double t = 0.0;
-  for (int64_t i = tid; i < n; i += kDecideThreads) t += v[i * step];
-  t = wave_sum(t);
-  __syncthreads();
-  if ((tid & 63) == 0) s_red[tid >> 6] = t;
-  __syncthreads();
-  double r = 0.0;
-  if (tid == 0)
-    for (int w = 0; w < kDecideThreads / 64; ++w) r += s_red[w];
-  return r;
-}
-
-// First stage for tensors with many units: workgroup b adds units [b*chunk, (b+1)*chunk)
-// of every candidate (and of the energies) in the same fixed order; the decide kernel
-// then adds the kDecideBlocks partials.
-struct PartialArgs {
-  DecideParams p;
-  int64_t chunk;
-};
-__global__ __launch_bounds__(kDecideThreads) void decide_partial_kernel(const PartialArgs a) {
-  __shared__ double s_red[kDecideThreads / 64];
-  const DecideParams& p = a.p;
-  const int64_t lo = static_cast<int64_t>(blockIdx.x) * a.chunk;
-  int64_t n = p.units - lo;
-  n = n < 0 ? 0 : (n < a.chunk ? n : a.chunk);
+  double t[kSums];
 #pragma unroll
-  for (int c = 0; c <= MOFQ_MAX_CANDIDATES; ++c) {
-    const double* v = (c < MOFQ_MAX_CANDIDATES) ? (c < p.n_cand ? p.err[c] : nullptr) : p.energy;
-    if (!v) continue;    // uniform
-    const double t = block_sum(v + lo, n, s_red);
-    if (threadIdx.x == 0) p.part[c * kDecideBlocks + blockIdx.x] = t;
+  for (int c = 0; c < kSums; ++c) t[c] = 0.0;
+  for (int64_t i = tid; i < n; i += kThreads) {
+    // Algorithm 1's rule for one unit: start at infinity, list order, strictly smaller wins
+    double min_err = __builtin_inf(), picked = 0.0;
+#pragma unroll
+    for (int c = 0; c < kSums; ++c)
+      if (a.v[c]) {   // uniform
+        const double e = a.v[c][lo + i];
+        t[c] += e;
+        if (c < MOFQ_MAX_CANDIDATES) {
+          if (c == 0 || e < min_err) picked = e;
+          if (e < min_err) min_err = e;
+        }
+      }
+    if (a.mixed) t[kMixed] += picked;
   }
-}
-
-// Fixed-order sums of the unit errors, Algorithm 1's select, result record.  Returns the
-// chosen index on thread 0.
-MOFQ_DEV int decide_body(const DecideParams& p, double* s_red);
-
-struct FinishBatchArgs {
-  FinishParams p[kFinishBatch];
-};
-__global__ __launch_bounds__(kDecideThreads) void finish_batch_kernel(const FinishBatchArgs a) {
-  __shared__ double s_red[kDecideThreads / 64];
-  __shared__ int s_best;
-  const FinishParams& p = a.p[blockIdx.x];
-  const int b = decide_body(p.d, s_red);
-  if (threadIdx.x == 0) s_best = (b < 0 || b >= p.d.n_cand) ? 0 : b;   // no candidate beat infinity: keep the first
-  __syncthreads();
-  const int best = s_best;
-  for (int64_t u = threadIdx.x; u < p.d.units; u += kDecideThreads) {
-    const float s = p.scale[best][u];
-    if (p.out_scales) {
-      if (p.scale_f16_out)
-        static_cast<uint16_t*>(p.out_scales)[u] = __half_as_ushort(__float2half_rn(s));  // exact: s is an fp16 value
-      else
-        static_cast<float*>(p.out_scales)[u] = s;
+  __syncthreads();   // s_red is free again
+#pragma unroll
+  for (int c = 0; c < kSums; ++c)
+    if (a.v[c] || (c == kMixed && a.mixed)) {
+      t[c] = wave_sum(t[c]);
+      if ((tid & 63) == 0) s_red[c][tid >> 6] = t[c];
     }
-    if (p.out_clip) p.out_clip[u] = p.clip[best][u];
-    if (p.out_unit_err) p.out_unit_err[u] = p.d.err[best][u];
+  __syncthreads();
+#pragma unroll
+  for (int c = 0; c < kSums; ++c) {
+    double r = 0.0;
+    if (a.v[c] || (c == kMixed && a.mixed)) {
+#pragma unroll
+      for (int w = 0; w < kNW; ++w) r += s_red[c][w];
+    }
+    out[c] = r;
   }
 }
 
-__global__ __launch_bounds__(kDecideThreads) void decide_kernel(const DecideParams p) {
-  __shared__ double s_red[kDecideThreads / 64];
-  decide_body(p, s_red);
+// First stage for the tensors of a launch: workgroup b of a tensor adds its b-th chunk.
+struct PartialTensor {
+  SumArrays a;
+  double* part;             // [kSums][kDecideBlocks]
+  int64_t n, chunk;
+  int32_t first_block;
+};
+struct PartialArgs {
+  PartialTensor t[kEmitBatch];
+  int32_t n;
+};
+static_assert(sizeof(PartialArgs) <= 4096, "kernel arguments");
+__global__ __launch_bounds__(kThreads) void decide_partial_kernel(const PartialArgs args) {
+  __shared__ double s_red[kSums][kNW];
+  int k = 0;
+  while (k + 1 < args.n && static_cast<int>(blockIdx.x) >= args.t[k + 1].first_block) ++k;   // uniform
+  const PartialTensor& t = args.t[k];
+  const int b = static_cast<int>(blockIdx.x) - t.first_block;
+  const int64_t lo = b * t.chunk;
+  const int64_t n = (t.n - lo) < t.chunk ? (t.n - lo) : t.chunk;
+  double sum[kSums];
+  block_sums(t.a, lo, n, sum, s_red);
+  if (threadIdx.x == 0) {
+#pragma unroll
+    for (int c = 0; c < kSums; ++c) t.part[c * kDecideBlocks + b] = sum[c];
+  }
 }
 
-MOFQ_DEV int decide_body(const DecideParams& p, double* s_red) {
-  double err[MOFQ_MAX_CANDIDATES];
+// The last stage's input and where the outcome goes.
+struct Decision {
+  SumArrays a;
+  int32_t n;                 // values per array
+  mofq_result_t* result;     // each optional
+  double* tensor_err_out;
+  double* energy_out;
+  double* mixed_out;
+};
+
+// Last stage and Algorithm 1's select: min_error starts at infinity, candidates in list order, a
+// candidate wins only if strictly smaller; the first one where none is below infinity
+// (non-finite input), in the record and in what is emitted.  Every workgroup that needs the choice
+// calls it; `write`: leave the record too.
+MOFQ_DEV int decide(const Decision& d, bool write, double (&s_red)[kSums][kNW]) {
+  SumArrays a = d.a;
+  if (!write) {
+    a.v[kEnergy] = nullptr;
+    a.v[kMixed] = nullptr;
+    a.mixed = 0;
+  }
+  double sum[kSums];
+  block_sums(a, 0, d.n, sum, s_red);
+  double min_err = __builtin_inf();
+  int best = 0;
 #pragma unroll
   for (int c = 0; c < MOFQ_MAX_CANDIDATES; ++c)
-    err[c] = (c < p.n_cand) ? block_sum(p.err[c], p.units, s_red) : 0.0;
-  const double energy = p.energy ? block_sum(p.energy, p.units, s_red) : 0.0;
-  int best = -1;
-  if (threadIdx.x == 0) {
-    // Algorithm 1: min_error starts at infinity, candidates in list order, a
-    // candidate wins only if strictly smaller.
-    double min_err = __builtin_inf();
+    if (c < a.n_cand && sum[c] < min_err) { min_err = sum[c]; best = c; }
+  if (write && threadIdx.x == 0) {
+    if (d.result) {
+      d.result->best = best;
+      d.result->n = a.n_cand;
 #pragma unroll
-    for (int c = 0; c < MOFQ_MAX_CANDIDATES; ++c)
-      if (c < p.n_cand && err[c] < min_err) { min_err = err[c]; best = c; }
-    if (p.result) {
-      // no candidate below infinity (non-finite input): the first candidate, which is also what
-      // the emission falls back to, so record and codes agree
-      p.result->best = best < 0 ? 0 : best;
-      p.result->n = p.n_cand;
-#pragma unroll
-      for (int c = 0; c < MOFQ_MAX_CANDIDATES; ++c) p.result->err[c] = (c < p.n_cand) ? err[c] : 0.0;
-      p.result->ref_energy = energy;
+      for (int c = 0; c < MOFQ_MAX_CANDIDATES; ++c) d.result->err[c] = (c < a.n_cand) ? sum[c] : 0.0;
+      d.result->ref_energy = sum[kEnergy];
     }
-    if (p.tensor_err_out) *p.tensor_err_out = err[0];
-    if (p.energy_out) *p.energy_out = energy;
+    if (d.tensor_err_out) *d.tensor_err_out = sum[0];
+    if (d.energy_out) *d.energy_out = sum[kEnergy];
+    if (d.mixed_out) *d.mixed_out = sum[kMixed];
   }
-  return best;
+  return __builtin_amdgcn_readfirstlane(best);
+}
+
+__global__ __launch_bounds__(kThreads) void decide_kernel(const Decision d) {
+  __shared__ double s_red[kSums][kNW];
+  decide(d, true, s_red);
 }
 
 // The weight-activation path after the matrix kernels of a group of layers, one workgroup per
 // layer: select from the per-tile partials, then the one-unit outputs of the chosen format
 // for X and W.
-struct WaFinishArgs {
-  WaFinishParams p[kWaGroup];
+struct WaFinishLayer {
+  Decision d;
+  int32_t fmt_slot[MOFQ_MAX_CANDIDATES];
+  WaFinishTensor t[2];
 };
-__global__ __launch_bounds__(kDecideThreads) void wa_finish_kernel(const WaFinishArgs args) {
-  __shared__ double s_red[kDecideThreads / 64];
-  __shared__ int s_best;
-  const WaFinishParams& a = args.p[blockIdx.x];
-  const int b = decide_body(a.d, s_red);
-  if (threadIdx.x == 0) s_best = (b < 0 || b >= a.d.n_cand) ? 0 : b;   // no candidate beat infinity: keep the first
-  __syncthreads();
-  const int f = a.fmt_slot[s_best];
+struct WaFinishArgs {
+  WaFinishLayer p[kWaGroup];
+};
+static_assert(sizeof(WaFinishArgs) <= 4096, "kernel arguments");
+__global__ __launch_bounds__(kThreads) void wa_finish_kernel(const WaFinishArgs args) {
+  __shared__ double s_red[kSums][kNW];
+  const WaFinishLayer& l = args.p[blockIdx.x];
+  const int f = l.fmt_slot[decide(l.d, true, s_red)];
 #pragma unroll
   for (int which = 0; which < 2; ++which) {
-    const WaFinishTensor& t = a.t[which];
+    const WaFinishTensor& t = l.t[which];
     if (t.n_segments < 1) continue;   // uniform
     double e = 0.0;
-    if (t.out_unit_err) e = block_sum(t.sse_part + f, t.n_segments, s_red, 2);
+    if (t.out_unit_err) {
+      for (int i = threadIdx.x; i < t.n_segments; i += kThreads) e += t.sse_part[2 * i + f];
+      e = wave_sum(e);
+      __syncthreads();
+      if ((threadIdx.x & 63) == 0) s_red[0][threadIdx.x >> 6] = e;
+      __syncthreads();
+      e = (s_red[0][0] + s_red[0][1]) + (s_red[0][2] + s_red[0][3]);
+    }
     if (threadIdx.x == 0) {
       if (t.out_unit_err) *t.out_unit_err = e;
       if (t.out_scales) *static_cast<float*>(t.out_scales) = t.scale[f];
@@ -177,6 +225,13 @@ __global__ __launch_bounds__(256) void wa_copy_kernel(const WaCopyArgs a) {
 }
 
 // ---- emit -------------------------------------------------------------------------
+//
+// One launch for up to kEmitBatch tensors does all that follows the search: the select (from the
+// unit errors or their chunk sums, redone by every workgroup), the winner's codes and its
+// per-unit outputs.  Bound by memory: 2 (4) bytes read and half a byte (one) written per element.
+// A workgroup walks segments of consecutive 8-element chunks, so that row, column and unit of a
+// chunk follow from one division per segment and a 32-bit multiplication per chunk (a 64-bit
+// division per chunk costs more instructions than its quantization).
 
 // Codes of 8 scaled elements.  4-bit: one word, element 2j in the low nibble of byte j;
 // 8-bit: two words, one byte per element.  The FP formats use the gfx950 pack-convert
@@ -222,156 +277,192 @@ MOFQ_DEV void encode8(const float (&v)[8], float inv_s, uint32_t (&words)[2]) {
   }
 }
 
-struct EmitArgs {
+struct EmitTensor {
   const void* w;
-  int64_t rows, cols, ld;
-  int64_t units;
-  int32_t gran, group;
-  int32_t scale_f16_out;
-  int32_t n_cand;
-  int32_t fmt[MOFQ_MAX_CANDIDATES];
+  int64_t ld, cols, n_chunks;
+  uint32_t cpr, magic;       // 8-element chunks per row; row_of()
+  int32_t seg_chunks, n_seg; // chunks per segment
+  int32_t first_block;
+  int32_t gran, group_shift;
   const float* scale[MOFQ_MAX_CANDIDATES];
   const int32_t* clip[MOFQ_MAX_CANDIDATES];
   const double* err[MOFQ_MAX_CANDIDATES];
-  const mofq_result_t* result;
-  const uint8_t* unit_fmt;  // per-unit candidate index, or nullptr (then the tensor-level choice)
+  Decision d;                // d.n = 0: candidate 0
+  uint8_t* unit_fmt;         // PER_UNIT: index of each unit's candidate
   mofq_qout_t out;
-  int32_t as_bf16_values;   // write dequantised grid values (bf16, unscaled) instead of codes
+};
+struct EmitArgs {
+  EmitTensor t[kEmitBatch];
+  int32_t n;
+  int32_t n_cand;
+  int32_t fmt[MOFQ_MAX_CANDIDATES];
+  int32_t scale_f16_out;
+  int32_t as_bf16_values;   // write grid values (bf16, unscaled) instead of codes
 };
 
-MOFQ_DEV int chosen(const EmitArgs& a) {
-  int best = a.result ? a.result->best : 0;
-  if (best < 0 || best >= a.n_cand) best = 0;   // no candidate beat infinity: keep the first
-  return __builtin_amdgcn_readfirstlane(best);
+// row, counted from the segment's first, of the chunk `off` chunks behind that row's start
+MOFQ_DEV uint32_t row_of(const EmitTensor& t, uint32_t off) {
+  if (t.magic) return __umulhi(off, t.magic);         // off * cpr < 2^32: exact
+  if (t.cpr == 1) return off;
+  return off >= t.cpr ? 1u : 0u;                      // rows longer than a segment
+}
+
+template <int FMT> MOFQ_DEV uint32_t grid_pair_bf16(float t0, float t1) {
+  // grid values have at most 7 significant bits: exact in bf16 (top half of fp32)
+  return (f2u(Codec<FMT>::grid(t0)) >> 16) | (f2u(Codec<FMT>::grid(t1)) & 0xFFFF0000u);
 }
 
 // One 8-element chunk: quantize with the unit's scale and store.
-template <typename In>
-MOFQ_DEV void emit_chunk(const EmitArgs& a, int best, int64_t cpr, int64_t c, const float (&v)[8]) {
-  const int64_t row = c / cpr, col = (c - row * cpr) * 8;
-  int64_t unit = 0;
-  if (a.gran == MOFQ_PER_CHANNEL) unit = row;
-  else if (a.gran == MOFQ_PER_GROUP) unit = row * (a.cols / a.group) + col / a.group;
-  if (a.unit_fmt) {
-    best = a.unit_fmt[unit];
-    if (best >= a.n_cand) best = 0;
-  }
-  const int fmt = a.fmt[best];
-  const float inv_s = 1.0f / a.scale[best][unit];
-  uint32_t words[2];
-  switch (fmt) {
-    case MOFQ_INT4: encode8<MOFQ_INT4>(v, inv_s, words); break;
-    case MOFQ_FP4_E2M1: encode8<MOFQ_FP4_E2M1>(v, inv_s, words); break;
-    case MOFQ_INT8: encode8<MOFQ_INT8>(v, inv_s, words); break;
-    case MOFQ_FP4_E2M1_IEEE: encode8<MOFQ_FP4_E2M1_IEEE>(v, inv_s, words); break;
-    case MOFQ_FP8_E5M2: encode8<MOFQ_FP8_E5M2>(v, inv_s, words); break;
-    default: encode8<MOFQ_FP8_E4M3>(v, inv_s, words); break;
-  }
-  const int64_t e0 = row * a.cols + col;   // dense output rows
+template <int FMT>
+MOFQ_DEV void emit_chunk(const EmitArgs& a, void* codes, int64_t e8, const float (&v)[8], float inv_s) {
   if (a.as_bf16_values) {
-    // grid values have at most 7 significant bits: exact in bf16 (top half of fp32)
     u32x4 o;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      float g0, g1;
-      switch (fmt) {
-        case MOFQ_INT4: g0 = Codec<MOFQ_INT4>::grid(v[2 * i] * inv_s); g1 = Codec<MOFQ_INT4>::grid(v[2 * i + 1] * inv_s); break;
-        case MOFQ_FP4_E2M1: g0 = Codec<MOFQ_FP4_E2M1>::grid(v[2 * i] * inv_s); g1 = Codec<MOFQ_FP4_E2M1>::grid(v[2 * i + 1] * inv_s); break;
-        case MOFQ_INT8: g0 = Codec<MOFQ_INT8>::grid(v[2 * i] * inv_s); g1 = Codec<MOFQ_INT8>::grid(v[2 * i + 1] * inv_s); break;
-        case MOFQ_FP4_E2M1_IEEE: g0 = Codec<MOFQ_FP4_E2M1_IEEE>::grid(v[2 * i] * inv_s); g1 = Codec<MOFQ_FP4_E2M1_IEEE>::grid(v[2 * i + 1] * inv_s); break;
-        case MOFQ_FP8_E5M2: g0 = Codec<MOFQ_FP8_E5M2>::grid(v[2 * i] * inv_s); g1 = Codec<MOFQ_FP8_E5M2>::grid(v[2 * i + 1] * inv_s); break;
-        default: g0 = Codec<MOFQ_FP8_E4M3>::grid(v[2 * i] * inv_s); g1 = Codec<MOFQ_FP8_E4M3>::grid(v[2 * i + 1] * inv_s); break;
-      }
-      o[i] = (f2u(g0) >> 16) | (f2u(g1) & 0xFFFF0000u);
-    }
-    reinterpret_cast<u32x4*>(a.out.codes)[e0 / 8] = o;
-  } else if (fmt == MOFQ_INT4 || fmt == MOFQ_FP4_E2M1 || fmt == MOFQ_FP4_E2M1_IEEE) {
-    static_cast<uint32_t*>(a.out.codes)[e0 / 8] = words[0];
+    for (int i = 0; i < 4; ++i) o[i] = grid_pair_bf16<FMT>(v[2 * i] * inv_s, v[2 * i + 1] * inv_s);
+    static_cast<u32x4*>(codes)[e8] = o;
+    return;
+  }
+  uint32_t words[2];
+  encode8<FMT>(v, inv_s, words);
+  if constexpr (Codec<FMT>::BITS == 4) {
+    static_cast<uint32_t*>(codes)[e8] = words[0];
   } else {
     u32x2 o;
     o[0] = words[0];
     o[1] = words[1];
-    reinterpret_cast<u32x2*>(a.out.codes)[e0 / 8] = o;
+    static_cast<u32x2*>(codes)[e8] = o;
   }
 }
 
-// Grid-stride over 8-element chunks, kEmitUnroll chunks per thread and iteration so that
-// several 16-byte loads are in flight per lane (the pass is HBM-bound).
-constexpr int kEmitUnroll = 4;
-template <typename In>
-__global__ __launch_bounds__(256) void emit_codes_kernel(const EmitArgs a) {
+constexpr int kEmitUnroll = 4;   // chunks per thread and iteration: 16-byte loads in flight per lane
+// PER_UNIT: every unit takes its own best candidate (its index goes to unit_fmt), else the tensor's.
+template <typename In, bool PER_UNIT>
+__global__ __launch_bounds__(kThreads) void emit_kernel(const EmitArgs a) {
   using L = Load8<In>;
-  const int best = chosen(a);
-  const int64_t cpr = a.cols / 8;
-  const int64_t n_chunks = a.rows * cpr;
-  const int64_t stride = static_cast<int64_t>(gridDim.x) * 256;
-  int64_t c = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x;
-  for (; c + (kEmitUnroll - 1) * stride < n_chunks; c += kEmitUnroll * stride) {
-    float v[kEmitUnroll][8];
-#pragma unroll
-    for (int u = 0; u < kEmitUnroll; ++u) {
-      const int64_t cu = c + u * stride;
-      const int64_t row = cu / cpr, col = (cu - row * cpr) * 8;
-      L::load(static_cast<const typename L::elem*>(a.w) + row * a.ld + col, v[u]);
-    }
-#pragma unroll
-    for (int u = 0; u < kEmitUnroll; ++u) emit_chunk<In>(a, best, cpr, c + u * stride, v[u]);
-  }
-  for (; c < n_chunks; c += stride) {
-    float v[8];
-    const int64_t row = c / cpr, col = (c - row * cpr) * 8;
-    L::load(static_cast<const typename L::elem*>(a.w) + row * a.ld + col, v);
-    emit_chunk<In>(a, best, cpr, c, v);
-  }
-}
+  __shared__ double s_red[kSums][kNW];
+  int k = 0;
+  while (k + 1 < a.n && static_cast<int>(blockIdx.x) >= a.t[k + 1].first_block) ++k;   // uniform
+  const EmitTensor& t = a.t[k];
+  const int b = static_cast<int>(blockIdx.x) - t.first_block;
+  const int nb = (k + 1 < a.n ? a.t[k + 1].first_block : static_cast<int>(gridDim.x)) - t.first_block;
+  const int best = t.d.n > 0 ? decide(t.d, b == 0, s_red) : 0;
+  const bool units_out = PER_UNIT || t.out.scales || t.out.clip_idx || t.out.unit_err;
+  const uint32_t group_mask = (1u << t.group_shift) - 1u;
+  const int64_t units_per_row = t.gran == MOFQ_PER_GROUP ? t.cols >> t.group_shift : 1;
 
-__global__ __launch_bounds__(256) void emit_units_kernel(const EmitArgs a) {
-  int best = chosen(a);
-  const int64_t u = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x;
-  if (u >= a.units) return;
-  if (a.unit_fmt) {
-    best = a.unit_fmt[u];
-    if (best >= a.n_cand) best = 0;
-  }
-  const float s = a.scale[best][u];
-  if (a.out.scales) {
-    if (a.scale_f16_out)
-      static_cast<uint16_t*>(a.out.scales)[u] = __half_as_ushort(__float2half_rn(s));  // exact: s is an fp16 value
-    else
-      static_cast<float*>(a.out.scales)[u] = s;
-  }
-  if (a.out.clip_idx) a.out.clip_idx[u] = a.clip[best][u];
-  if (a.out.unit_err) a.out.unit_err[u] = a.err[best][u];
-}
-
-__global__ __launch_bounds__(256) void pick_units_kernel(const PickUnitsParams p) {
-  const int64_t u = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x;
-  if (u >= p.units) return;
-  // Algorithm 1's rule for one unit: start at infinity, list order, strictly smaller wins
-  double min_err = __builtin_inf();
-  int best = 0;
+  for (int seg = b; seg < t.n_seg; seg += nb) {
+    const int64_t c0 = static_cast<int64_t>(seg) * t.seg_chunks;
+    const int64_t row0 = c0 / t.cpr;
+    const uint32_t off0 = static_cast<uint32_t>(c0 - row0 * t.cpr);
+    const int n = static_cast<int>((t.n_chunks - c0) < t.seg_chunks ? (t.n_chunks - c0) : t.seg_chunks);
+    for (int l0 = threadIdx.x; l0 < n; l0 += kThreads * kEmitUnroll) {
+      float v[kEmitUnroll][8];
+      int64_t row[kEmitUnroll];
+      uint32_t col[kEmitUnroll];
 #pragma unroll
-  for (int c = 0; c < MOFQ_MAX_CANDIDATES; ++c)
-    if (c < p.n_cand) {
-      const double e = p.err[c][u];
-      if (e < min_err) { min_err = e; best = c; }
+      for (int u = 0; u < kEmitUnroll; ++u) {
+        const int l = l0 + u * kThreads < n ? l0 + u * kThreads : l0;   // past the end: the first again, not stored
+        const uint32_t off = off0 + static_cast<uint32_t>(l);
+        const uint32_t q = row_of(t, off);
+        row[u] = row0 + q;
+        col[u] = (off - q * t.cpr) * 8;
+        L::load(static_cast<const typename L::elem*>(t.w) + row[u] * t.ld + col[u], v[u]);
+      }
+#pragma unroll
+      for (int u = 0; u < kEmitUnroll; ++u) {
+        if (l0 + u * kThreads >= n) continue;
+        int64_t unit = 0;
+        bool first = row[u] == 0 && col[u] == 0;      // does the chunk open its unit?
+        if (t.gran == MOFQ_PER_CHANNEL) { unit = row[u]; first = col[u] == 0; }
+        else if (t.gran == MOFQ_PER_GROUP) { unit = row[u] * units_per_row + (col[u] >> t.group_shift); first = (col[u] & group_mask) == 0; }
+        int c = best;
+        if constexpr (PER_UNIT) {
+          // Algorithm 1's rule for one unit: start at infinity, list order, strictly smaller wins
+          double min_err = __builtin_inf();
+          c = 0;
+#pragma unroll
+          for (int i = 0; i < MOFQ_MAX_CANDIDATES; ++i)
+            if (i < a.n_cand) {
+              const double e = t.err[i][unit];
+              if (e < min_err) { min_err = e; c = i; }
+            }
+        }
+        const float s = t.scale[c][unit];
+        const float inv_s = 1.0f / s;
+        const int64_t e8 = c0 + l0 + u * kThreads;    // dense output rows
+        switch (a.fmt[c]) {
+          case MOFQ_INT4: emit_chunk<MOFQ_INT4>(a, t.out.codes, e8, v[u], inv_s); break;
+          case MOFQ_FP4_E2M1: emit_chunk<MOFQ_FP4_E2M1>(a, t.out.codes, e8, v[u], inv_s); break;
+          case MOFQ_INT8: emit_chunk<MOFQ_INT8>(a, t.out.codes, e8, v[u], inv_s); break;
+          case MOFQ_FP4_E2M1_IEEE: emit_chunk<MOFQ_FP4_E2M1_IEEE>(a, t.out.codes, e8, v[u], inv_s); break;
+          case MOFQ_FP8_E5M2: emit_chunk<MOFQ_FP8_E5M2>(a, t.out.codes, e8, v[u], inv_s); break;
+          default: emit_chunk<MOFQ_FP8_E4M3>(a, t.out.codes, e8, v[u], inv_s); break;
+        }
+        if (units_out && first) {
+          if constexpr (PER_UNIT) t.unit_fmt[unit] = static_cast<uint8_t>(c);
+          if (t.out.scales) {
+            if (a.scale_f16_out)
+              static_cast<uint16_t*>(t.out.scales)[unit] = __half_as_ushort(__float2half_rn(s));  // exact: s is an fp16 value
+            else
+              static_cast<float*>(t.out.scales)[unit] = s;
+          }
+          if (t.out.clip_idx) t.out.clip_idx[unit] = t.clip[c][unit];
+          if (t.out.unit_err) t.out.unit_err[unit] = t.err[c][unit];
+        }
+      }
     }
-  p.unit_fmt[u] = static_cast<uint8_t>(best);
-  p.picked_err[u] = p.err[best][u];
+  }
 }
 
 }  // namespace
 
-int launch_finish_batch(const FinishParams* p, int n, hipStream_t st) {
-  if (!p || n < 1 || n > kFinishBatch) return MOFQ_ERR_INVALID_ARG;
-  FinishBatchArgs a{};
-  for (int i = 0; i < n; ++i) {
-    if (p[i].d.units < 1 || p[i].d.units > kFinishMaxUnits) return MOFQ_ERR_INVALID_ARG;
-    a.p[i] = p[i];
+namespace {
+
+// The last stage's view of a reduce; `partial`: a first stage has left its chunk sums in p.part.
+Decision decision(const DecideParams& p, bool partial) {
+  Decision d{};
+  d.a.n_cand = p.n_cand;
+  for (int c = 0; c < p.n_cand; ++c) d.a.v[c] = partial ? p.part + c * kDecideBlocks : p.err[c];
+  if (p.energy) d.a.v[kEnergy] = partial ? p.part + kEnergy * kDecideBlocks : p.energy;
+  if (p.mixed_out) {
+    if (partial) d.a.v[kMixed] = p.part + kMixed * kDecideBlocks;
+    else d.a.mixed = 1;
   }
-  hipLaunchKernelGGL(finish_batch_kernel, dim3(static_cast<unsigned>(n)), dim3(kDecideThreads), 0, st, a);
+  d.n = static_cast<int32_t>(partial ? partial_chunks(p.units) : p.units);
+  d.result = p.result;
+  d.tensor_err_out = p.tensor_err_out;
+  d.energy_out = p.energy_out;
+  d.mixed_out = p.mixed_out;
+  return d;
+}
+
+bool two_stages(const DecideParams& p) { return p.part && partial_chunks(p.units) > 0; }
+
+// First stages of the reduces that have one, in one launch.
+int launch_partial(const DecideParams* const* p, int n, hipStream_t st) {
+  PartialArgs a{};
+  int blocks = 0;
+  for (int i = 0; i < n; ++i) {
+    if (!two_stages(*p[i])) continue;
+    PartialTensor& t = a.t[a.n++];
+    t.a.n_cand = p[i]->n_cand;
+    for (int c = 0; c < p[i]->n_cand; ++c) t.a.v[c] = p[i]->err[c];
+    t.a.v[kEnergy] = p[i]->energy;
+    t.a.mixed = p[i]->mixed_out != nullptr;
+    t.part = p[i]->part;
+    t.n = p[i]->units;
+    const int64_t nc = partial_chunks(t.n);
+    t.chunk = (t.n + nc - 1) / nc;
+    t.first_block = blocks;
+    // every chunk sum is written, also where rounding the chunk up leaves the last ones empty
+    blocks += static_cast<int>(nc);
+  }
+  if (!a.n) return MOFQ_OK;
+  hipLaunchKernelGGL(decide_partial_kernel, dim3(static_cast<unsigned>(blocks)), dim3(kThreads), 0, st, a);
   return hip_status(hipGetLastError());
 }
+
+}  // namespace
 
 int launch_wa_finish(const WaFinishParams* p, int n, hipStream_t st) {
   if (!p || n < 1 || n > kWaGroup) return MOFQ_ERR_INVALID_ARG;
@@ -379,11 +470,15 @@ int launch_wa_finish(const WaFinishParams* p, int n, hipStream_t st) {
   for (int i = 0; i < n; ++i) {
     const DecideParams& d = p[i].d;
     if (d.units < 1 || d.n_cand < 1 || d.n_cand > MOFQ_MAX_CANDIDATES || !d.result) return MOFQ_ERR_INVALID_ARG;
-    for (int c = 0; c < d.n_cand; ++c)
+    for (int c = 0; c < d.n_cand; ++c) {
       if (!d.err[c] || p[i].fmt_slot[c] < 0 || p[i].fmt_slot[c] > 1) return MOFQ_ERR_INVALID_ARG;
-    a.p[i] = p[i];
+      a.p[i].fmt_slot[c] = p[i].fmt_slot[c];
+    }
+    a.p[i].d = decision(d, false);
+    a.p[i].t[0] = p[i].t[0];
+    a.p[i].t[1] = p[i].t[1];
   }
-  hipLaunchKernelGGL(wa_finish_kernel, dim3(static_cast<unsigned>(n)), dim3(kDecideThreads), 0, st, a);
+  hipLaunchKernelGGL(wa_finish_kernel, dim3(static_cast<unsigned>(n)), dim3(kThreads), 0, st, a);
   return hip_status(hipGetLastError());
 }
 
@@ -417,64 +512,83 @@ int launch_wa_copy(const WaCopyParams* p, int n, hipStream_t st) {
   return hip_status(hipGetLastError());
 }
 
-int launch_pick_units(const PickUnitsParams& p, hipStream_t st) {
-  if (p.units <= 0 || p.n_cand < 1 || p.n_cand > MOFQ_MAX_CANDIDATES) return MOFQ_ERR_INVALID_ARG;
-  hipLaunchKernelGGL(pick_units_kernel, dim3(static_cast<unsigned>((p.units + 255) / 256)), dim3(256), 0, st, p);
-  return hip_status(hipGetLastError());
-}
-
 int launch_decide(const DecideParams& p, hipStream_t st) {
-  if (p.part && p.units > 16 * 1024) {
-    PartialArgs a{p, (p.units + kDecideBlocks - 1) / kDecideBlocks};
-    hipLaunchKernelGGL(decide_partial_kernel, dim3(kDecideBlocks), dim3(kDecideThreads), 0, st, a);
-    DecideParams d = p;
-    d.units = kDecideBlocks;
-    for (int c = 0; c < MOFQ_MAX_CANDIDATES; ++c) d.err[c] = c < p.n_cand ? p.part + c * kDecideBlocks : nullptr;
-    d.energy = p.energy ? p.part + MOFQ_MAX_CANDIDATES * kDecideBlocks : nullptr;
-    hipLaunchKernelGGL(decide_kernel, dim3(1), dim3(kDecideThreads), 0, st, d);
-    return hip_status(hipGetLastError());
-  }
-  hipLaunchKernelGGL(decide_kernel, dim3(1), dim3(kDecideThreads), 0, st, p);
+  if (p.units < 1 || p.units > (int64_t{1} << 31) * (two_stages(p) ? kDirectUnits : 1) - 1) return MOFQ_ERR_INVALID_ARG;
+  const DecideParams* list[1] = {&p};
+  const int rc = launch_partial(list, 1, st);
+  if (rc != MOFQ_OK) return rc;
+  hipLaunchKernelGGL(decide_kernel, dim3(1), dim3(kThreads), 0, st, decision(p, two_stages(p)));
   return hip_status(hipGetLastError());
 }
 
-int launch_emit(const EmitParams& p, hipStream_t st) {
+int launch_emit(const EmitParams* p, int n, int max_blocks, hipStream_t st) {
+  if (!p || n < 1 || n > kEmitBatch) return MOFQ_ERR_INVALID_ARG;
+  static_assert(sizeof(EmitArgs) <= 4096, "kernel arguments");
   EmitArgs a{};
-  a.w = p.w;
-  a.rows = p.rows;
-  a.cols = p.cols;
-  a.ld = p.ld;
-  a.gran = p.gran;
-  a.group = p.group;
-  a.scale_f16_out = p.scale_f16_out;
-  a.n_cand = p.n_cand;
-  for (int c = 0; c < MOFQ_MAX_CANDIDATES; ++c) {
-    a.fmt[c] = p.fmt[c];
-    a.scale[c] = p.scale[c];
-    a.clip[c] = p.clip[c];
-    a.err[c] = p.err[c];
-  }
-  a.result = p.result;
-  a.unit_fmt = p.unit_fmt;
-  a.out = p.out;
-  a.as_bf16_values = p.as_bf16_values;
-  a.units = mofq_num_units(p.rows, p.cols, p.gran, p.group);
-  if (a.units <= 0) return MOFQ_ERR_INVALID_ARG;
-  const int64_t n_chunks = p.rows * (p.cols / 8);
-  // full occupancy (8 workgroups of 256 on each of 256 compute units), several chunks per thread
-  const int64_t cap = p.max_blocks > 0 ? p.max_blocks : 256 * 8;
-  const unsigned blocks = static_cast<unsigned>(
-      std::max<int64_t>(1, std::min<int64_t>((n_chunks + 256 * kEmitUnroll - 1) / (256 * kEmitUnroll), cap)));
-  if (p.out.codes) {
-    switch (p.dtype) {
-      case MOFQ_F32: hipLaunchKernelGGL(emit_codes_kernel<F32>, dim3(blocks), dim3(256), 0, st, a); break;
-      case MOFQ_F16: hipLaunchKernelGGL(emit_codes_kernel<F16>, dim3(blocks), dim3(256), 0, st, a); break;
-      case MOFQ_BF16: hipLaunchKernelGGL(emit_codes_kernel<BF16>, dim3(blocks), dim3(256), 0, st, a); break;
-      default: return MOFQ_ERR_INVALID_ARG;
+  const DecideParams* dec[kEmitBatch];
+  int n_dec = 0;
+  // Segments of 256 to 2048 chunks: the largest that still give 2048 workgroups (8 on each of
+  // 256 compute units).
+  int64_t total_chunks = 0, total_seg = 0;
+  for (int i = 0; i < n; ++i) total_chunks += p[i].rows * (p[i].cols / 8);
+  const int64_t per_thread = std::min<int64_t>(8, std::max<int64_t>(1, total_chunks / (2048 * kThreads)));
+  a.n = n;
+  a.n_cand = p[0].n_cand;
+  a.scale_f16_out = p[0].scale_f16_out;
+  a.as_bf16_values = p[0].as_bf16_values;
+  for (int c = 0; c < MOFQ_MAX_CANDIDATES; ++c) a.fmt[c] = p[0].fmt[c];
+  for (int i = 0; i < n; ++i) {
+    const EmitParams& q = p[i];
+    if (q.dtype != p[0].dtype || q.n_cand != a.n_cand || q.scale_f16_out != a.scale_f16_out || q.as_bf16_values != a.as_bf16_values || (q.unit_fmt != nullptr) != (p[0].unit_fmt != nullptr) ||
+        q.rows < 1 || q.cols < 8 || q.cols % 8 != 0 || !q.out.codes || q.n_cand < 1 || q.n_cand > MOFQ_MAX_CANDIDATES)
+      return MOFQ_ERR_INVALID_ARG;
+    EmitTensor& t = a.t[i];
+    if (q.cols / 8 >= (int64_t{1} << 32) - 4096) return MOFQ_ERR_UNSUPPORTED;
+    t.w = q.w;
+    t.ld = q.ld;
+    t.cols = q.cols;
+    t.cpr = static_cast<uint32_t>(q.cols / 8);
+    t.n_chunks = q.rows * t.cpr;
+    // exact while off * cpr < 2^32, off < cpr + 2048; longer rows span a segment
+    t.magic = (t.cpr > 1 && t.cpr < 32768) ? static_cast<uint32_t>((uint64_t{1} << 32) / t.cpr + 1) : 0;
+    t.seg_chunks = static_cast<int32_t>(per_thread * kThreads);
+    const int64_t n_seg = (t.n_chunks + t.seg_chunks - 1) / t.seg_chunks;
+    if (n_seg >= (int64_t{1} << 31)) return MOFQ_ERR_UNSUPPORTED;
+    t.n_seg = static_cast<int32_t>(n_seg);
+    total_seg += n_seg;
+    t.gran = q.gran;
+    if (q.gran == MOFQ_PER_GROUP) {
+      if (q.group < 8 || (q.group & (q.group - 1)) != 0) return MOFQ_ERR_UNSUPPORTED;
+      while ((1 << t.group_shift) < q.group) ++t.group_shift;
     }
+    for (int c = 0; c < q.n_cand; ++c) { t.scale[c] = q.scale[c]; t.clip[c] = q.clip[c]; t.err[c] = q.err[c]; }
+    if (q.decide.units > 0) {
+      t.d = decision(q.decide, two_stages(q.decide));
+      dec[n_dec++] = &q.decide;
+    }
+    t.unit_fmt = q.unit_fmt;
+    t.out = q.out;
   }
-  if (p.out.scales || p.out.clip_idx || p.out.unit_err)
-    hipLaunchKernelGGL(emit_units_kernel, dim3(static_cast<unsigned>((a.units + 255) / 256)), dim3(256), 0, st, a);
+  int rc = n_dec ? launch_partial(dec, n_dec, st) : static_cast<int>(MOFQ_OK);
+  if (rc != MOFQ_OK) return rc;
+  const int64_t cap = max_blocks > 0 ? max_blocks : (int64_t{1} << 30);
+  int64_t blocks = 0;
+  for (int i = 0; i < n; ++i) {
+    a.t[i].first_block = static_cast<int32_t>(blocks);
+    blocks += total_seg <= cap ? a.t[i].n_seg : std::max<int64_t>(1, a.t[i].n_seg * cap / total_seg);
+  }
+  const dim3 grid(static_cast<unsigned>(blocks));
+  const bool per_unit = p[0].unit_fmt != nullptr;
+#define MOFQ_EMIT(IN)                                                                                  \
+  if (per_unit) hipLaunchKernelGGL((emit_kernel<IN, true>), grid, dim3(kThreads), 0, st, a);            \
+  else hipLaunchKernelGGL((emit_kernel<IN, false>), grid, dim3(kThreads), 0, st, a);
+  switch (p[0].dtype) {
+    case MOFQ_F32: MOFQ_EMIT(F32) break;
+    case MOFQ_F16: MOFQ_EMIT(F16) break;
+    case MOFQ_BF16: MOFQ_EMIT(BF16) break;
+    default: return MOFQ_ERR_INVALID_ARG;
+  }
+#undef MOFQ_EMIT
   return hip_status(hipGetLastError());
 }
 

@@ -73,17 +73,18 @@ struct DecideParams {
   int32_t n_cand;
   const double* err[MOFQ_MAX_CANDIDATES];
   const double* energy;          // [units] or nullptr
-  mofq_result_t* result;         // device
+  mofq_result_t* result;         // device, optional
   double* tensor_err_out;        // optional: err of candidate 0 (device) or nullptr
   double* energy_out;            // optional (device) or nullptr
-  double* part;                  // optional scratch, (MOFQ_MAX_CANDIDATES + 1) * kDecideBlocks doubles:
-                                 // with it, many units are first reduced by kDecideBlocks workgroups
+  double* mixed_out;             // optional (device): sum over the units of the smallest candidate's error
+  double* part;                  // optional scratch of kDecidePart doubles: with it, many units are
+                                 // first reduced by up to kDecideBlocks workgroups
 };
 constexpr int kDecideBlocks = 256;
+constexpr int kDecidePart = (MOFQ_MAX_CANDIDATES + 2) * kDecideBlocks;
 int launch_decide(const DecideParams& p, hipStream_t stream);
 
-// Emit codes and per-unit outputs for the format chosen in *result (or slot 0 if
-// result is null).
+// Codes and per-unit outputs of up to kEmitBatch tensors of one dtype and candidate list.
 struct EmitParams {
   const void* w;
   int32_t dtype;
@@ -95,41 +96,14 @@ struct EmitParams {
   const float* scale[MOFQ_MAX_CANDIDATES];
   const int32_t* clip[MOFQ_MAX_CANDIDATES];
   const double* err[MOFQ_MAX_CANDIDATES];
-  const mofq_result_t* result;   // device, may be nullptr (then candidate 0)
-  const uint8_t* unit_fmt;       // device [units] or nullptr: candidate index per unit (overrides result)
+  DecideParams decide;           // units > 0: the launch takes this reduce + select too and emits its choice; else candidate 0
+  uint8_t* unit_fmt;             // device [units] or nullptr: every unit takes its own best candidate, whose index goes here
   mofq_qout_t out;
-  int32_t as_bf16_values;        // 8-bit formats: out.codes receives the grid values as bf16
-  int32_t max_blocks;            // 0: fill the device; else a cap for emission that runs beside other kernels
+  int32_t as_bf16_values;        // out.codes receives the grid values as bf16
 };
-int launch_emit(const EmitParams& p, hipStream_t stream);
-
-// Tensor-level reduce + select + the per-unit outputs of the winner for several tensors in
-// one launch (one workgroup per tensor): the small dependent steps between the search and
-// the code emission, batched so that a model-wide pass does not pay their latency per
-// tensor.  Every tensor must have at most kFinishMaxUnits units.
-struct FinishParams {
-  DecideParams d;
-  int32_t scale_f16_out;
-  const float* scale[MOFQ_MAX_CANDIDATES];
-  const int32_t* clip[MOFQ_MAX_CANDIDATES];
-  void* out_scales;          // may be nullptr
-  int32_t* out_clip;         // may be nullptr
-  double* out_unit_err;      // may be nullptr
-};
-constexpr int kFinishBatch = 12;
-constexpr int64_t kFinishMaxUnits = 16 * 1024;
-int launch_finish_batch(const FinishParams* p, int n, hipStream_t stream);
-
-// Per unit: the first candidate with the strictly smallest error; writes its index and
-// its error.
-struct PickUnitsParams {
-  int64_t units;
-  int32_t n_cand;
-  const double* err[MOFQ_MAX_CANDIDATES];
-  uint8_t* unit_fmt;     // [units]
-  double* picked_err;    // [units]
-};
-int launch_pick_units(const PickUnitsParams& p, hipStream_t stream);
+constexpr int kEmitBatch = 12;
+// max_blocks: 0, or a cap on the workgroups for emission that runs beside other kernels
+int launch_emit(const EmitParams* p, int n, int max_blocks, hipStream_t stream);
 
 // Layer-output error of one linear layer: partial sums per 128x128 output tile.
 // A null xi/wi (or xf/wf) pair skips that format.
