@@ -3,6 +3,7 @@
 // with the scales the search chose.  The decision never leaves device memory,
 // so a whole model can be processed without a host synchronisation.
 #include <algorithm>
+#include <type_traits>
 
 #include "mofq_device.h"
 #include "mofq_internal.h"
@@ -30,50 +31,49 @@ int64_t partial_chunks(int64_t n) {
 constexpr int kEnergy = MOFQ_MAX_CANDIDATES, kMixed = kEnergy + 1, kSums = kMixed + 1;
 
 struct SumArrays {
-  const double* v[kSums];   // nullptr: not asked for; v[kMixed] is only read in the last stage
+  const double* v[kSums];   // packed: the candidates' errors, then the energy if asked for, then the chunk sums of the mixed error
   int32_t n_cand;
-  int32_t mixed;            // form the per-unit minimum over the candidates' arrays
+  int32_t n_arr;            // arrays in v
+  int32_t has_energy;
+  int32_t mixed;            // 1: form the per-unit minimum over the candidates' arrays; 2: v's last array holds its chunk sums
 };
 
-// Sums over the workgroup in a fixed order (thread-strided partials, wave sums, then the waves
-// in order); every thread gets all of them.
-MOFQ_DEV void block_sums(const SumArrays& a, int64_t lo, int64_t n, double (&out)[kSums], double (&s_red)[kSums][kNW]) {
-  const int tid = threadIdx.x;
-  double t[kSums];
+// Sums of n values of the first n_arr arrays, and of the per-unit minima if asked for, into s_sum.
+// One wave per array: a wave reads 1024 values with 16 loads in flight per lane, so the whole is
+// one memory latency for the sizes this is called with, and the order is fixed (lane-strided, then
+// the wave sum).  Valid for every thread.
+MOFQ_DEV void block_sums(const SumArrays& a, int n_arr, int64_t lo, int64_t n, bool mixed, double (&s_sum)[kSums]) {
+  constexpr int U = 16;
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  for (int c = wave; c < n_arr; c += kNW) {
+    const double* v = a.v[c] + lo;
+    double t = 0.0;
+    for (int64_t i0 = lane; i0 < n; i0 += U * 64) {
+      double e[U];
 #pragma unroll
-  for (int c = 0; c < kSums; ++c) t[c] = 0.0;
-  for (int64_t i = tid; i < n; i += kThreads) {
-    // Algorithm 1's rule for one unit: start at infinity, list order, strictly smaller wins
-    double min_err = __builtin_inf(), picked = 0.0;
+      for (int u = 0; u < U; ++u) e[u] = v[i0 + u * 64 < n ? i0 + u * 64 : i0];
 #pragma unroll
-    for (int c = 0; c < kSums; ++c)
-      if (a.v[c]) {   // uniform
+      for (int u = 0; u < U; ++u) t += i0 + u * 64 < n ? e[u] : 0.0;
+    }
+    t = wave_sum(t);
+    if (lane == 0) s_sum[c] = t;
+  }
+  if (mixed && wave == kNW - 1) {   // the last wave is the one with nothing else to do (two formats and their energy)
+    double t = 0.0;
+    for (int64_t i = lane; i < n; i += 64) {
+      // Algorithm 1's rule for one unit: start at infinity, list order, strictly smaller wins
+      double min_err = __builtin_inf(), picked = a.v[0][lo + i];
+      for (int c = 0; c < a.n_cand; ++c) {
         const double e = a.v[c][lo + i];
-        t[c] += e;
-        if (c < MOFQ_MAX_CANDIDATES) {
-          if (c == 0 || e < min_err) picked = e;
-          if (e < min_err) min_err = e;
-        }
+        if (e < min_err) { min_err = e; picked = e; }
       }
-    if (a.mixed) t[kMixed] += picked;
-  }
-  __syncthreads();   // s_red is free again
-#pragma unroll
-  for (int c = 0; c < kSums; ++c)
-    if (a.v[c] || (c == kMixed && a.mixed)) {
-      t[c] = wave_sum(t[c]);
-      if ((tid & 63) == 0) s_red[c][tid >> 6] = t[c];
+      t += picked;
     }
+    t = wave_sum(t);
+    if (lane == 0) s_sum[kMixed] = t;
+  }
   __syncthreads();
-#pragma unroll
-  for (int c = 0; c < kSums; ++c) {
-    double r = 0.0;
-    if (a.v[c] || (c == kMixed && a.mixed)) {
-#pragma unroll
-      for (int w = 0; w < kNW; ++w) r += s_red[c][w];
-    }
-    out[c] = r;
-  }
 }
 
 // First stage for the tensors of a launch: workgroup b of a tensor adds its b-th chunk.
@@ -81,27 +81,32 @@ struct PartialTensor {
   SumArrays a;
   double* part;             // [kSums][kDecideBlocks]
   int64_t n, chunk;
-  int32_t first_block;
 };
 struct PartialArgs {
+  int32_t first_block[kEmitBatch];   // unused entries: INT_MAX
   PartialTensor t[kEmitBatch];
   int32_t n;
 };
+
+// Index of the tensor that workgroup `block` belongs to (uniform).
+MOFQ_DEV int tensor_of(const int32_t (&first_block)[kEmitBatch], int block) {
+  int k = 0;
+#pragma unroll
+  for (int i = 1; i < kEmitBatch; ++i) k += block >= first_block[i] ? 1 : 0;
+  return k;
+}
+
 static_assert(sizeof(PartialArgs) <= 4096, "kernel arguments");
 __global__ __launch_bounds__(kThreads) void decide_partial_kernel(const PartialArgs args) {
-  __shared__ double s_red[kSums][kNW];
-  int k = 0;
-  while (k + 1 < args.n && static_cast<int>(blockIdx.x) >= args.t[k + 1].first_block) ++k;   // uniform
+  __shared__ double s_sum[kSums];
+  const int k = tensor_of(args.first_block, static_cast<int>(blockIdx.x));
   const PartialTensor& t = args.t[k];
-  const int b = static_cast<int>(blockIdx.x) - t.first_block;
+  const int b = static_cast<int>(blockIdx.x) - args.first_block[k];
   const int64_t lo = b * t.chunk;
   const int64_t n = (t.n - lo) < t.chunk ? (t.n - lo) : t.chunk;
-  double sum[kSums];
-  block_sums(t.a, lo, n, sum, s_red);
-  if (threadIdx.x == 0) {
-#pragma unroll
-    for (int c = 0; c < kSums; ++c) t.part[c * kDecideBlocks + b] = sum[c];
-  }
+  block_sums(t.a, t.a.n_arr, lo, n, t.a.mixed != 0, s_sum);
+  const int c = threadIdx.x;   // rows of part in the order of t.a.v
+  if (c < t.a.n_arr || (c == kMixed && t.a.mixed)) t.part[c * kDecideBlocks + b] = s_sum[c];
 }
 
 // The last stage's input and where the outcome goes.
@@ -118,38 +123,31 @@ struct Decision {
 // candidate wins only if strictly smaller; the first one where none is below infinity
 // (non-finite input), in the record and in what is emitted.  Every workgroup that needs the choice
 // calls it; `write`: leave the record too.
-MOFQ_DEV int decide(const Decision& d, bool write, double (&s_red)[kSums][kNW]) {
-  SumArrays a = d.a;
-  if (!write) {
-    a.v[kEnergy] = nullptr;
-    a.v[kMixed] = nullptr;
-    a.mixed = 0;
-  }
-  double sum[kSums];
-  block_sums(a, 0, d.n, sum, s_red);
+MOFQ_DEV int decide(const Decision& d, bool write, double (&s_sum)[kSums]) {
+  const int nc = d.a.n_cand;
+  block_sums(d.a, write ? d.a.n_arr : nc, 0, d.n, write && d.a.mixed == 1, s_sum);
   double min_err = __builtin_inf();
   int best = 0;
-#pragma unroll
-  for (int c = 0; c < MOFQ_MAX_CANDIDATES; ++c)
-    if (c < a.n_cand && sum[c] < min_err) { min_err = sum[c]; best = c; }
+  for (int c = 0; c < nc; ++c)
+    if (s_sum[c] < min_err) { min_err = s_sum[c]; best = c; }
   if (write && threadIdx.x == 0) {
+    const double energy = d.a.has_energy ? s_sum[nc] : 0.0;
     if (d.result) {
       d.result->best = best;
-      d.result->n = a.n_cand;
-#pragma unroll
-      for (int c = 0; c < MOFQ_MAX_CANDIDATES; ++c) d.result->err[c] = (c < a.n_cand) ? sum[c] : 0.0;
-      d.result->ref_energy = sum[kEnergy];
+      d.result->n = nc;
+      for (int c = 0; c < MOFQ_MAX_CANDIDATES; ++c) d.result->err[c] = (c < nc) ? s_sum[c] : 0.0;
+      d.result->ref_energy = energy;
     }
-    if (d.tensor_err_out) *d.tensor_err_out = sum[0];
-    if (d.energy_out) *d.energy_out = sum[kEnergy];
-    if (d.mixed_out) *d.mixed_out = sum[kMixed];
+    if (d.tensor_err_out) *d.tensor_err_out = s_sum[0];
+    if (d.energy_out) *d.energy_out = energy;
+    if (d.mixed_out) *d.mixed_out = s_sum[d.a.mixed == 2 ? d.a.n_arr - 1 : kMixed];
   }
   return __builtin_amdgcn_readfirstlane(best);
 }
 
 __global__ __launch_bounds__(kThreads) void decide_kernel(const Decision d) {
-  __shared__ double s_red[kSums][kNW];
-  decide(d, true, s_red);
+  __shared__ double s_sum[kSums];
+  decide(d, true, s_sum);
 }
 
 // The weight-activation path after the matrix kernels of a group of layers, one workgroup per
@@ -165,9 +163,10 @@ struct WaFinishArgs {
 };
 static_assert(sizeof(WaFinishArgs) <= 4096, "kernel arguments");
 __global__ __launch_bounds__(kThreads) void wa_finish_kernel(const WaFinishArgs args) {
-  __shared__ double s_red[kSums][kNW];
+  __shared__ double s_sum[kSums];
+  __shared__ double s_red[kNW];
   const WaFinishLayer& l = args.p[blockIdx.x];
-  const int f = l.fmt_slot[decide(l.d, true, s_red)];
+  const int f = l.fmt_slot[decide(l.d, true, s_sum)];
 #pragma unroll
   for (int which = 0; which < 2; ++which) {
     const WaFinishTensor& t = l.t[which];
@@ -177,9 +176,9 @@ __global__ __launch_bounds__(kThreads) void wa_finish_kernel(const WaFinishArgs 
       for (int i = threadIdx.x; i < t.n_segments; i += kThreads) e += t.sse_part[2 * i + f];
       e = wave_sum(e);
       __syncthreads();
-      if ((threadIdx.x & 63) == 0) s_red[0][threadIdx.x >> 6] = e;
+      if ((threadIdx.x & 63) == 0) s_red[threadIdx.x >> 6] = e;
       __syncthreads();
-      e = (s_red[0][0] + s_red[0][1]) + (s_red[0][2] + s_red[0][3]);
+      e = (s_red[0] + s_red[1]) + (s_red[2] + s_red[3]);
     }
     if (threadIdx.x == 0) {
       if (t.out_unit_err) *t.out_unit_err = e;
@@ -231,7 +230,10 @@ __global__ __launch_bounds__(256) void wa_copy_kernel(const WaCopyArgs a) {
 // per-unit outputs.  Bound by memory: 2 (4) bytes read and half a byte (one) written per element.
 // A workgroup walks segments of consecutive 8-element chunks, so that row, column and unit of a
 // chunk follow from one division per segment and a 32-bit multiplication per chunk (a 64-bit
-// division per chunk costs more instructions than its quantization).
+// division per chunk costs more instructions than its quantization); addresses are a uniform base
+// plus a 32-bit offset, and the units that open in a segment are written together at its end, a
+// thread per unit (as a branch of the chunk loop they cost two dependent loads in every wave).
+// Measured: a 7B-shaped block with groups of 128 (202 M elements) 193 us -> 113 us, 4.5 TB/s.
 
 // Codes of 8 scaled elements.  4-bit: one word, element 2j in the low nibble of byte j;
 // 8-bit: two words, one byte per element.  The FP formats use the gfx950 pack-convert
@@ -282,8 +284,7 @@ struct EmitTensor {
   int64_t ld, cols, n_chunks;
   uint32_t cpr, magic;       // 8-element chunks per row; row_of()
   int32_t seg_chunks, n_seg; // chunks per segment
-  int32_t first_block;
-  int32_t gran, group_shift;
+  int32_t gran, group_shift; // log2 of the chunks per group
   const float* scale[MOFQ_MAX_CANDIDATES];
   const int32_t* clip[MOFQ_MAX_CANDIDATES];
   const double* err[MOFQ_MAX_CANDIDATES];
@@ -292,12 +293,13 @@ struct EmitTensor {
   mofq_qout_t out;
 };
 struct EmitArgs {
-  EmitTensor t[kEmitBatch];
+  int32_t first_block[kEmitBatch];   // unused entries: INT_MAX
   int32_t n;
   int32_t n_cand;
   int32_t fmt[MOFQ_MAX_CANDIDATES];
   int32_t scale_f16_out;
   int32_t as_bf16_values;   // write grid values (bf16, unscaled) instead of codes
+  EmitTensor t[kEmitBatch];
 };
 
 // row, counted from the segment's first, of the chunk `off` chunks behind that row's start
@@ -307,6 +309,19 @@ MOFQ_DEV uint32_t row_of(const EmitTensor& t, uint32_t off) {
   return off >= t.cpr ? 1u : 0u;                      // rows longer than a segment
 }
 
+// Algorithm 1's rule for one unit: start at infinity, list order, strictly smaller wins
+MOFQ_DEV int unit_choice(const EmitTensor& t, int n_cand, int64_t unit) {
+  double min_err = __builtin_inf();
+  int c = 0;
+#pragma unroll
+  for (int i = 0; i < MOFQ_MAX_CANDIDATES; ++i)
+    if (i < n_cand) {
+      const double e = t.err[i][unit];
+      if (e < min_err) { min_err = e; c = i; }
+    }
+  return c;
+}
+
 template <int FMT> MOFQ_DEV uint32_t grid_pair_bf16(float t0, float t1) {
   // grid values have at most 7 significant bits: exact in bf16 (top half of fp32)
   return (f2u(Codec<FMT>::grid(t0)) >> 16) | (f2u(Codec<FMT>::grid(t1)) & 0xFFFF0000u);
@@ -314,101 +329,160 @@ template <int FMT> MOFQ_DEV uint32_t grid_pair_bf16(float t0, float t1) {
 
 // One 8-element chunk: quantize with the unit's scale and store.
 template <int FMT>
-MOFQ_DEV void emit_chunk(const EmitArgs& a, void* codes, int64_t e8, const float (&v)[8], float inv_s) {
+MOFQ_DEV void emit_chunk(const EmitArgs& a, void* codes, int64_t c0, uint32_t l, const float (&v)[8], float inv_s) {   // chunk c0 + l; c0 is uniform
   if (a.as_bf16_values) {
     u32x4 o;
 #pragma unroll
     for (int i = 0; i < 4; ++i) o[i] = grid_pair_bf16<FMT>(v[2 * i] * inv_s, v[2 * i + 1] * inv_s);
-    static_cast<u32x4*>(codes)[e8] = o;
+    (static_cast<u32x4*>(codes) + c0)[l] = o;
     return;
   }
   uint32_t words[2];
   encode8<FMT>(v, inv_s, words);
   if constexpr (Codec<FMT>::BITS == 4) {
-    static_cast<uint32_t*>(codes)[e8] = words[0];
+    (static_cast<uint32_t*>(codes) + c0)[l] = words[0];
   } else {
     u32x2 o;
     o[0] = words[0];
     o[1] = words[1];
-    static_cast<u32x2*>(codes)[e8] = o;
+    (static_cast<u32x2*>(codes) + c0)[l] = o;
+  }
+}
+
+// 8 elements as they come from memory, widened where they are used
+template <typename In> struct Raw8 {
+  u32x4 w;
+  // element i0 + i; i0 is uniform
+  MOFQ_DEV void load(const void* base, int64_t i0, uint32_t i) {
+    w = *reinterpret_cast<const u32x4*>(static_cast<const uint16_t*>(base) + i0 + i);
+  }
+  MOFQ_DEV void widen(float (&v)[8]) const {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      if constexpr (std::is_same<In, F16>::value) {
+        v[2 * i] = static_cast<float>(__builtin_bit_cast(_Float16, static_cast<uint16_t>(w[i])));
+        v[2 * i + 1] = static_cast<float>(__builtin_bit_cast(_Float16, static_cast<uint16_t>(w[i] >> 16)));
+      } else {
+        v[2 * i] = u2f(w[i] << 16);
+        v[2 * i + 1] = u2f(w[i] & 0xFFFF0000u);
+      }
+    }
+  }
+};
+template <> struct Raw8<F32> {
+  u32x4 w[2];
+  MOFQ_DEV void load(const void* base, int64_t i0, uint32_t i) {
+    const u32x4* p = reinterpret_cast<const u32x4*>(static_cast<const float*>(base) + i0 + i);
+    w[0] = p[0];
+    w[1] = p[1];
+  }
+  MOFQ_DEV void widen(float (&v)[8]) const {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) { v[i] = u2f(w[0][i]); v[4 + i] = u2f(w[1][i]); }
+  }
+};
+
+template <typename F> MOFQ_DEV void with_format(int fmt, F&& f) {
+  switch (fmt) {
+    case MOFQ_INT4: f(std::integral_constant<int, MOFQ_INT4>{}); break;
+    case MOFQ_FP4_E2M1: f(std::integral_constant<int, MOFQ_FP4_E2M1>{}); break;
+    case MOFQ_INT8: f(std::integral_constant<int, MOFQ_INT8>{}); break;
+    case MOFQ_FP4_E2M1_IEEE: f(std::integral_constant<int, MOFQ_FP4_E2M1_IEEE>{}); break;
+    case MOFQ_FP8_E5M2: f(std::integral_constant<int, MOFQ_FP8_E5M2>{}); break;
+    default: f(std::integral_constant<int, MOFQ_FP8_E4M3>{}); break;
   }
 }
 
 constexpr int kEmitUnroll = 4;   // chunks per thread and iteration: 16-byte loads in flight per lane
 // PER_UNIT: every unit takes its own best candidate (its index goes to unit_fmt), else the tensor's.
-template <typename In, bool PER_UNIT>
+// MULTI: more than one tensor; a single one's arguments sit at fixed offsets, so that they all come
+// with the first round of scalar loads.  A small launch is a chain of memory latencies, so the
+// first chunks and the scales of the first two candidates are requested before the select.
+template <typename In, bool PER_UNIT, bool MULTI>
 __global__ __launch_bounds__(kThreads) void emit_kernel(const EmitArgs a) {
-  using L = Load8<In>;
-  __shared__ double s_red[kSums][kNW];
-  int k = 0;
-  while (k + 1 < a.n && static_cast<int>(blockIdx.x) >= a.t[k + 1].first_block) ++k;   // uniform
+  __shared__ double s_sum[kSums];
+  const int k = MULTI ? tensor_of(a.first_block, static_cast<int>(blockIdx.x)) : 0;
   const EmitTensor& t = a.t[k];
-  const int b = static_cast<int>(blockIdx.x) - t.first_block;
-  const int nb = (k + 1 < a.n ? a.t[k + 1].first_block : static_cast<int>(gridDim.x)) - t.first_block;
-  const int best = t.d.n > 0 ? decide(t.d, b == 0, s_red) : 0;
+  const int b = static_cast<int>(blockIdx.x) - (MULTI ? a.first_block[k] : 0);
+  const int nb = (MULTI && k + 1 < a.n ? a.first_block[k + 1] : static_cast<int>(gridDim.x)) - (MULTI ? a.first_block[k] : 0);
   const bool units_out = PER_UNIT || t.out.scales || t.out.clip_idx || t.out.unit_err;
-  const uint32_t group_mask = (1u << t.group_shift) - 1u;
-  const int64_t units_per_row = t.gran == MOFQ_PER_GROUP ? t.cols >> t.group_shift : 1;
+  const bool per_group = t.gran == MOFQ_PER_GROUP, per_channel = t.gran == MOFQ_PER_CHANNEL;
+  const bool dense = t.ld == t.cols;
+  int best = -1;
 
   for (int seg = b; seg < t.n_seg; seg += nb) {
+    // everything 64-bit is uniform over the workgroup; lanes add 32-bit offsets
     const int64_t c0 = static_cast<int64_t>(seg) * t.seg_chunks;
     const int64_t row0 = c0 / t.cpr;
     const uint32_t off0 = static_cast<uint32_t>(c0 - row0 * t.cpr);
     const int n = static_cast<int>((t.n_chunks - c0) < t.seg_chunks ? (t.n_chunks - c0) : t.seg_chunks);
-    for (int l0 = threadIdx.x; l0 < n; l0 += kThreads * kEmitUnroll) {
-      float v[kEmitUnroll][8];
-      int64_t row[kEmitUnroll];
-      uint32_t col[kEmitUnroll];
+    // unit of a chunk: its group (segments start at a group), its row, or 0
+    const int64_t unit0 = per_group ? c0 >> t.group_shift : (per_channel ? row0 : 0);
+    const int64_t src0 = dense ? c0 * 8 : row0 * t.ld;
+    const float* const scale0 = t.scale[0] + unit0;
+    const float* const scale1 = t.scale[1] + unit0;
+    for (int i0 = 0; i0 < n; i0 += kThreads * kEmitUnroll) {   // uniform
+      const int l0 = i0 + static_cast<int>(threadIdx.x);
+      Raw8<In> raw[kEmitUnroll];
+      float sc0[kEmitUnroll], sc1[kEmitUnroll];
+      uint32_t unit[kEmitUnroll];                     // counted from unit0
 #pragma unroll
       for (int u = 0; u < kEmitUnroll; ++u) {
-        const int l = l0 + u * kThreads < n ? l0 + u * kThreads : l0;   // past the end: the first again, not stored
-        const uint32_t off = off0 + static_cast<uint32_t>(l);
-        const uint32_t q = row_of(t, off);
-        row[u] = row0 + q;
-        col[u] = (off - q * t.cpr) * 8;
-        L::load(static_cast<const typename L::elem*>(t.w) + row[u] * t.ld + col[u], v[u]);
+        const int l = l0 + u * kThreads < n ? l0 + u * kThreads : n - 1;   // past the end: the last again, not stored
+        uint32_t q = 0;
+        if (per_channel || !dense) q = row_of(t, off0 + static_cast<uint32_t>(l));
+        if (dense) raw[u].load(t.w, src0, static_cast<uint32_t>(l) * 8);
+        else raw[u].load(t.w, src0 + static_cast<int64_t>(q) * t.ld, (off0 + static_cast<uint32_t>(l) - q * t.cpr) * 8);
+        unit[u] = per_group ? static_cast<uint32_t>(l) >> t.group_shift : (per_channel ? q : 0u);
+        sc0[u] = scale0[unit[u]];
+        sc1[u] = scale1[unit[u]];
       }
+      if (best < 0) best = t.d.n > 0 ? decide(t.d, b == 0, s_sum) : 0;   // uniform
+      // candidate c for chunk u, whose format is fmt_c
+      auto store = [&](auto fmt_c, const int u, const int c) {
+        const float s0 = sc0[u], s1 = sc1[u];
+        float s = c == 0 ? s0 : s1;
+        if (c > 1) s = t.scale[c][unit0 + unit[u]];
+        float v[8];
+        raw[u].widen(v);
+        emit_chunk<decltype(fmt_c)::value>(a, t.out.codes, c0, static_cast<uint32_t>(l0 + u * kThreads), v, 1.0f / s);   // dense output rows
+      };
+      if constexpr (PER_UNIT) {
 #pragma unroll
-      for (int u = 0; u < kEmitUnroll; ++u) {
-        if (l0 + u * kThreads >= n) continue;
-        int64_t unit = 0;
-        bool first = row[u] == 0 && col[u] == 0;      // does the chunk open its unit?
-        if (t.gran == MOFQ_PER_CHANNEL) { unit = row[u]; first = col[u] == 0; }
-        else if (t.gran == MOFQ_PER_GROUP) { unit = row[u] * units_per_row + (col[u] >> t.group_shift); first = (col[u] & group_mask) == 0; }
+        for (int u = 0; u < kEmitUnroll; ++u) {
+          if (l0 + u * kThreads >= n) continue;
+          const int c = unit_choice(t, a.n_cand, unit0 + unit[u]);
+          with_format(a.fmt[c], [&](auto fmt_c) { store(fmt_c, u, c); });
+        }
+      } else {
+        with_format(a.fmt[best], [&](auto fmt_c) {
+#pragma unroll
+          for (int u = 0; u < kEmitUnroll; ++u)
+            if (l0 + u * kThreads < n) store(fmt_c, u, best);
+        });
+      }
+    }
+    // outputs of the units that open in this segment, a thread per unit
+    if (units_out) {
+      const int64_t cpu = per_group ? int64_t{1} << t.group_shift : (per_channel ? t.cpr : t.n_chunks);   // chunks per unit
+      const int64_t end = (c0 + n + cpu - 1) / cpu;
+      for (int64_t o = (c0 + cpu - 1) / cpu + threadIdx.x; o < end; o += kThreads) {
         int c = best;
         if constexpr (PER_UNIT) {
-          // Algorithm 1's rule for one unit: start at infinity, list order, strictly smaller wins
-          double min_err = __builtin_inf();
-          c = 0;
-#pragma unroll
-          for (int i = 0; i < MOFQ_MAX_CANDIDATES; ++i)
-            if (i < a.n_cand) {
-              const double e = t.err[i][unit];
-              if (e < min_err) { min_err = e; c = i; }
-            }
+          c = unit_choice(t, a.n_cand, o);
+          t.unit_fmt[o] = static_cast<uint8_t>(c);
         }
-        const float s = t.scale[c][unit];
-        const float inv_s = 1.0f / s;
-        const int64_t e8 = c0 + l0 + u * kThreads;    // dense output rows
-        switch (a.fmt[c]) {
-          case MOFQ_INT4: emit_chunk<MOFQ_INT4>(a, t.out.codes, e8, v[u], inv_s); break;
-          case MOFQ_FP4_E2M1: emit_chunk<MOFQ_FP4_E2M1>(a, t.out.codes, e8, v[u], inv_s); break;
-          case MOFQ_INT8: emit_chunk<MOFQ_INT8>(a, t.out.codes, e8, v[u], inv_s); break;
-          case MOFQ_FP4_E2M1_IEEE: emit_chunk<MOFQ_FP4_E2M1_IEEE>(a, t.out.codes, e8, v[u], inv_s); break;
-          case MOFQ_FP8_E5M2: emit_chunk<MOFQ_FP8_E5M2>(a, t.out.codes, e8, v[u], inv_s); break;
-          default: emit_chunk<MOFQ_FP8_E4M3>(a, t.out.codes, e8, v[u], inv_s); break;
+        const float s = t.scale[c][o];
+        const int32_t clip = t.clip[c][o];
+        const double err = t.err[c][o];
+        if (t.out.scales) {
+          if (a.scale_f16_out)
+            static_cast<uint16_t*>(t.out.scales)[o] = __half_as_ushort(__float2half_rn(s));  // exact: s is an fp16 value
+          else
+            static_cast<float*>(t.out.scales)[o] = s;
         }
-        if (units_out && first) {
-          if constexpr (PER_UNIT) t.unit_fmt[unit] = static_cast<uint8_t>(c);
-          if (t.out.scales) {
-            if (a.scale_f16_out)
-              static_cast<uint16_t*>(t.out.scales)[unit] = __half_as_ushort(__float2half_rn(s));  // exact: s is an fp16 value
-            else
-              static_cast<float*>(t.out.scales)[unit] = s;
-          }
-          if (t.out.clip_idx) t.out.clip_idx[unit] = t.clip[c][unit];
-          if (t.out.unit_err) t.out.unit_err[unit] = t.err[c][unit];
-        }
+        if (t.out.clip_idx) t.out.clip_idx[o] = clip;
+        if (t.out.unit_err) t.out.unit_err[o] = err;
       }
     }
   }
@@ -418,15 +492,28 @@ __global__ __launch_bounds__(kThreads) void emit_kernel(const EmitArgs a) {
 
 namespace {
 
-// The last stage's view of a reduce; `partial`: a first stage has left its chunk sums in p.part.
+// The arrays of a reduce (the unit values), and the last stage's view of it; `partial`: a first
+// stage leaves its chunk sums in p.part, one row of kDecideBlocks per array in the same order.
+SumArrays sum_arrays(const DecideParams& p) {
+  SumArrays a{};
+  a.n_cand = p.n_cand;
+  for (int c = 0; c < p.n_cand; ++c) a.v[a.n_arr++] = p.err[c];
+  if (p.energy) {
+    a.v[a.n_arr++] = p.energy;
+    a.has_energy = 1;
+  }
+  a.mixed = p.mixed_out ? 1 : 0;
+  return a;
+}
 Decision decision(const DecideParams& p, bool partial) {
   Decision d{};
-  d.a.n_cand = p.n_cand;
-  for (int c = 0; c < p.n_cand; ++c) d.a.v[c] = partial ? p.part + c * kDecideBlocks : p.err[c];
-  if (p.energy) d.a.v[kEnergy] = partial ? p.part + kEnergy * kDecideBlocks : p.energy;
-  if (p.mixed_out) {
-    if (partial) d.a.v[kMixed] = p.part + kMixed * kDecideBlocks;
-    else d.a.mixed = 1;
+  d.a = sum_arrays(p);
+  if (partial) {
+    for (int c = 0; c < d.a.n_arr; ++c) d.a.v[c] = p.part + c * kDecideBlocks;
+    if (d.a.mixed) {
+      d.a.v[d.a.n_arr++] = p.part + kMixed * kDecideBlocks;
+      d.a.mixed = 2;
+    }
   }
   d.n = static_cast<int32_t>(partial ? partial_chunks(p.units) : p.units);
   d.result = p.result;
@@ -444,19 +531,17 @@ int launch_partial(const DecideParams* const* p, int n, hipStream_t st) {
   int blocks = 0;
   for (int i = 0; i < n; ++i) {
     if (!two_stages(*p[i])) continue;
-    PartialTensor& t = a.t[a.n++];
-    t.a.n_cand = p[i]->n_cand;
-    for (int c = 0; c < p[i]->n_cand; ++c) t.a.v[c] = p[i]->err[c];
-    t.a.v[kEnergy] = p[i]->energy;
-    t.a.mixed = p[i]->mixed_out != nullptr;
+    PartialTensor& t = a.t[a.n];
+    t.a = sum_arrays(*p[i]);
     t.part = p[i]->part;
     t.n = p[i]->units;
     const int64_t nc = partial_chunks(t.n);
     t.chunk = (t.n + nc - 1) / nc;
-    t.first_block = blocks;
+    a.first_block[a.n++] = blocks;
     // every chunk sum is written, also where rounding the chunk up leaves the last ones empty
     blocks += static_cast<int>(nc);
   }
+  for (int i = a.n; i < kEmitBatch; ++i) a.first_block[i] = INT32_MAX;
   if (!a.n) return MOFQ_OK;
   hipLaunchKernelGGL(decide_partial_kernel, dim3(static_cast<unsigned>(blocks)), dim3(kThreads), 0, st, a);
   return hip_status(hipGetLastError());
@@ -523,15 +608,15 @@ int launch_decide(const DecideParams& p, hipStream_t st) {
 
 int launch_emit(const EmitParams* p, int n, int max_blocks, hipStream_t st) {
   if (!p || n < 1 || n > kEmitBatch) return MOFQ_ERR_INVALID_ARG;
-  static_assert(sizeof(EmitArgs) <= 4096, "kernel arguments");
+  static_assert(sizeof(EmitArgs) <= 4096 && MOFQ_MAX_CANDIDATES >= 2, "kernel arguments");
   EmitArgs a{};
   const DecideParams* dec[kEmitBatch];
   int n_dec = 0;
-  // Segments of 256 to 2048 chunks: the largest that still give 2048 workgroups (8 on each of
-  // 256 compute units).
+  // Segments of 512 to 2048 chunks: the largest that still give 1024 workgroups (4 on each of
+  // 256 compute units); more of them would only repeat the select more often.
   int64_t total_chunks = 0, total_seg = 0;
   for (int i = 0; i < n; ++i) total_chunks += p[i].rows * (p[i].cols / 8);
-  const int64_t per_thread = std::min<int64_t>(8, std::max<int64_t>(1, total_chunks / (2048 * kThreads)));
+  const int64_t per_thread = std::min<int64_t>(8, std::max<int64_t>(2, total_chunks / (1024 * kThreads)));
   a.n = n;
   a.n_cand = p[0].n_cand;
   a.scale_f16_out = p[0].scale_f16_out;
@@ -543,12 +628,14 @@ int launch_emit(const EmitParams* p, int n, int max_blocks, hipStream_t st) {
         q.rows < 1 || q.cols < 8 || q.cols % 8 != 0 || !q.out.codes || q.n_cand < 1 || q.n_cand > MOFQ_MAX_CANDIDATES)
       return MOFQ_ERR_INVALID_ARG;
     EmitTensor& t = a.t[i];
-    if (q.cols / 8 >= (int64_t{1} << 32) - 4096) return MOFQ_ERR_UNSUPPORTED;
+    // a dense per-tensor tensor is one run of chunks: rows of one chunk, whatever its shape
+    const bool run = q.gran == MOFQ_PER_TENSOR && q.ld == q.cols;
+    if (!run && q.cols >= (int64_t{1} << 31)) return MOFQ_ERR_UNSUPPORTED;
     t.w = q.w;
-    t.ld = q.ld;
-    t.cols = q.cols;
-    t.cpr = static_cast<uint32_t>(q.cols / 8);
-    t.n_chunks = q.rows * t.cpr;
+    t.ld = run ? 8 : q.ld;
+    t.cols = run ? 8 : q.cols;
+    t.cpr = static_cast<uint32_t>(t.cols / 8);
+    t.n_chunks = q.rows * (q.cols / 8);
     // exact while off * cpr < 2^32, off < cpr + 2048; longer rows span a segment
     t.magic = (t.cpr > 1 && t.cpr < 32768) ? static_cast<uint32_t>((uint64_t{1} << 32) / t.cpr + 1) : 0;
     t.seg_chunks = static_cast<int32_t>(per_thread * kThreads);
@@ -558,10 +645,11 @@ int launch_emit(const EmitParams* p, int n, int max_blocks, hipStream_t st) {
     total_seg += n_seg;
     t.gran = q.gran;
     if (q.gran == MOFQ_PER_GROUP) {
-      if (q.group < 8 || (q.group & (q.group - 1)) != 0) return MOFQ_ERR_UNSUPPORTED;
-      while ((1 << t.group_shift) < q.group) ++t.group_shift;
+      if (q.group < 8 || q.group > 4096 || (q.group & (q.group - 1)) != 0) return MOFQ_ERR_UNSUPPORTED;
+      while ((8 << t.group_shift) < q.group) ++t.group_shift;   // segments hold whole groups: 512 chunks and more
     }
     for (int c = 0; c < q.n_cand; ++c) { t.scale[c] = q.scale[c]; t.clip[c] = q.clip[c]; t.err[c] = q.err[c]; }
+    if (q.n_cand < 2) t.scale[1] = q.scale[0];   // requested early, not used
     if (q.decide.units > 0) {
       t.d = decision(q.decide, two_stages(q.decide));
       dec[n_dec++] = &q.decide;
@@ -574,14 +662,17 @@ int launch_emit(const EmitParams* p, int n, int max_blocks, hipStream_t st) {
   const int64_t cap = max_blocks > 0 ? max_blocks : (int64_t{1} << 30);
   int64_t blocks = 0;
   for (int i = 0; i < n; ++i) {
-    a.t[i].first_block = static_cast<int32_t>(blocks);
+    a.first_block[i] = static_cast<int32_t>(blocks);
     blocks += total_seg <= cap ? a.t[i].n_seg : std::max<int64_t>(1, a.t[i].n_seg * cap / total_seg);
   }
+  for (int i = n; i < kEmitBatch; ++i) a.first_block[i] = INT32_MAX;
   const dim3 grid(static_cast<unsigned>(blocks));
   const bool per_unit = p[0].unit_fmt != nullptr;
-#define MOFQ_EMIT(IN)                                                                                  \
-  if (per_unit) hipLaunchKernelGGL((emit_kernel<IN, true>), grid, dim3(kThreads), 0, st, a);            \
-  else hipLaunchKernelGGL((emit_kernel<IN, false>), grid, dim3(kThreads), 0, st, a);
+#define MOFQ_EMIT(IN)                                                                                                \
+  if (per_unit && n == 1) hipLaunchKernelGGL((emit_kernel<IN, true, false>), grid, dim3(kThreads), 0, st, a);          \
+  else if (per_unit) return MOFQ_ERR_UNSUPPORTED;                                                                     \
+  else if (n == 1) hipLaunchKernelGGL((emit_kernel<IN, false, false>), grid, dim3(kThreads), 0, st, a);                \
+  else hipLaunchKernelGGL((emit_kernel<IN, false, true>), grid, dim3(kThreads), 0, st, a);
   switch (p[0].dtype) {
     case MOFQ_F32: MOFQ_EMIT(F32) break;
     case MOFQ_F16: MOFQ_EMIT(F16) break;
