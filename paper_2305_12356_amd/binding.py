@@ -133,13 +133,16 @@ _DTYPES = {torch.float32: F32, torch.float16: F16, torch.bfloat16: BF16}
 
 
 def tensor_desc(t: torch.Tensor) -> TensorDesc:
-    if t.dim() != 2 or t.stride(1) != 1:
+    strides = t.stride()
+    if len(strides) != 2 or strides[1] != 1:
         raise ValueError("expected a 2-D tensor with contiguous rows")
-    if t.dtype not in _DTYPES:
+    dtype = _DTYPES.get(t.dtype)
+    if dtype is None:
         raise ValueError(f"unsupported dtype {t.dtype}")
     if not t.is_cuda:
         raise ValueError("the library works on device memory only")
-    return TensorDesc(t.data_ptr(), _DTYPES[t.dtype], t.shape[0], t.shape[1], t.stride(0))
+    rows, cols = t.shape
+    return TensorDesc(t.data_ptr(), dtype, rows, cols, strides[0])
 
 
 class Cfg:
@@ -158,13 +161,15 @@ class Cfg:
 
 
 def _ptr(t: Optional[torch.Tensor]):
-    return None if t is None else C.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()
 
 
-def _stream_handle(stream) -> C.c_void_p:
+def _stream_handle(stream) -> int:
     if stream is None:
-        stream = torch.cuda.current_stream()
-    return C.c_void_p(stream.cuda_stream)
+        # the handle itself: torch.cuda.current_stream() builds a Stream object around it first,
+        # 3 us of a single-layer call's 12
+        return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+    return stream.cuda_stream
 
 
 @dataclass
@@ -206,7 +211,7 @@ def quantize(t: torch.Tensor, fmt: int, cfg: Cfg, out: QBuffers,
     td = tensor_desc(t)
     oc = out.c()
     rc = _lib.mofq_quantize(C.byref(td), fmt, C.byref(cfg.c), C.byref(oc), _ptr(tensor_err),
-                            _ptr(ws), ws.numel() * ws.element_size(), _stream_handle(stream))
+                            _ptr(ws), ws.nbytes, _stream_handle(stream))
     if rc != 0:
         raise MofqError(rc, "mofq_quantize")
 
@@ -218,7 +223,7 @@ def score(w: torch.Tensor, x: Optional[torch.Tensor], fmt: int, metric: int, cfg
     wd = tensor_desc(w)
     xd = tensor_desc(x) if x is not None else None
     rc = _lib.mofq_score(C.byref(wd), C.byref(xd) if xd else None, fmt, metric, C.byref(cfg.c),
-                         _ptr(err), _ptr(ref_energy), _ptr(ws), ws.numel() * ws.element_size(),
+                         _ptr(err), _ptr(ref_energy), _ptr(ws), ws.nbytes,
                          _stream_handle(stream))
     if rc != 0:
         raise MofqError(rc, "mofq_score")
@@ -248,7 +253,7 @@ def select_layer(w: torch.Tensor, x: Optional[torch.Tensor], candidates: Sequenc
     xoc = x_out.c() if x_out is not None else None
     args = (C.byref(wd), C.byref(xd) if xd else None, cand, len(candidates), metric,
             C.byref(cfg.c), C.byref(woc), C.byref(xoc) if xoc else None, _ptr(result), _ptr(ws),
-            ws.numel() * ws.element_size(), _stream_handle(stream))
+            ws.nbytes, _stream_handle(stream))
     if ev_begin is None and ev_end is None:
         rc = _lib.mofq_select_layer(*args)
     else:
@@ -288,7 +293,7 @@ def select_units(w: torch.Tensor, candidates: Sequence[int], cfg: Cfg, w_out: QB
     woc = w_out.c()
     rc = _lib.mofq_select_units(C.byref(wd), cand, len(candidates), C.byref(cfg.c), C.byref(woc),
                                 _ptr(unit_format), _ptr(result), _ptr(mixed_err), _ptr(ws),
-                                ws.numel() * ws.element_size(), _stream_handle(stream))
+                                ws.nbytes, _stream_handle(stream))
     if rc != 0:
         raise MofqError(rc, "mofq_select_units")
 
@@ -296,7 +301,7 @@ def select_units(w: torch.Tensor, candidates: Sequence[int], cfg: Cfg, w_out: QB
 def calibrate_absmax(x: torch.Tensor, absmax: torch.Tensor, ws: torch.Tensor, stream=None) -> None:
     """mofq_calibrate_absmax: absmax (device float32 scalar) = max(absmax, max|x|); enqueue."""
     xd = tensor_desc(x)
-    rc = _lib.mofq_calibrate_absmax(C.byref(xd), _ptr(absmax), _ptr(ws), ws.numel() * ws.element_size(),
+    rc = _lib.mofq_calibrate_absmax(C.byref(xd), _ptr(absmax), _ptr(ws), ws.nbytes,
                                     _stream_handle(stream))
     if rc != 0:
         raise MofqError(rc, "mofq_calibrate_absmax")
@@ -311,7 +316,7 @@ def select_calibrated(x: torch.Tensor, candidates: Sequence[int], absmax: torch.
     xoc = x_out.c() if x_out is not None else None
     rc = _lib.mofq_select_calibrated(C.byref(xd), cand, len(candidates), _ptr(absmax),
                                      C.byref(xoc) if xoc else None, _ptr(result), _ptr(ws),
-                                     ws.numel() * ws.element_size(), _stream_handle(stream))
+                                     ws.nbytes, _stream_handle(stream))
     if rc != 0:
         raise MofqError(rc, "mofq_select_calibrated")
 
@@ -350,9 +355,9 @@ def select_layers(batch: LayerBatch, candidates: Sequence[int], cfg: Cfg, result
     ev_begin of a launch's first tensor and ev_end of its last are recorded, the others are
     left alone (LayerBatch.search_groups tells which)."""
     cand = (C.c_int32 * len(candidates))(*candidates)
-    side = C.c_void_p(side_stream.cuda_stream) if side_stream is not None else C.c_void_p(0)
+    side = side_stream.cuda_stream if side_stream is not None else None
     args = (batch.n, batch.w, cand, len(candidates), C.byref(cfg.c), batch.out, _ptr(results), _ptr(ws),
-            ws.numel() * ws.element_size(), _stream_handle(stream), side)
+            ws.nbytes, _stream_handle(stream), side)
     if ev_begin is None:
         rc = _lib.mofq_select_layers(*args)
     else:
@@ -390,7 +395,7 @@ def select_layers_wa(batch: WaLayerBatch, candidates: Sequence[int], metric: int
     layer's matrix kernel): the weight-activation select of every layer of the batch; enqueue."""
     cand = (C.c_int32 * len(candidates))(*candidates)
     args = (batch.n, batch.w, batch.x, cand, len(candidates), metric, C.byref(cfg.c), batch.w_out, batch.x_out,
-            _ptr(results), _ptr(ws), ws.numel() * ws.element_size(), _stream_handle(stream))
+            _ptr(results), _ptr(ws), ws.nbytes, _stream_handle(stream))
     if ev_begin is None:
         rc = _lib.mofq_select_layers_wa(*args)
     else:
@@ -408,7 +413,7 @@ def device_ceiling(kind: int, scratch: torch.Tensor, iters: int, stream=None) ->
     """mofq_device_ceiling: enqueue one rate-measuring micro-kernel (or `iters` plain copies of
     half of `scratch`); returns the work of the launch (bytes or operations)."""
     work = C.c_double(0.0)
-    rc = _lib.mofq_device_ceiling(kind, _ptr(scratch), scratch.numel() * scratch.element_size(), iters,
+    rc = _lib.mofq_device_ceiling(kind, _ptr(scratch), scratch.nbytes, iters,
                                   C.byref(work), _stream_handle(stream))
     if rc != 0:
         raise MofqError(rc, "mofq_device_ceiling")

@@ -109,7 +109,7 @@ WOnlyWs carve_w_only(void* ws, int64_t units, int n_cand, int gran, int n_clip) 
   if (gran == MOFQ_PER_TENSOR) {
     w.absmax_part = c.take<float>(kTensorBlocks);
     w.energy_part = c.take<double>(kTensorBlocks);
-    w.sse_part = c.take<double>(static_cast<size_t>(kTensorBlocks) * kMaxFmt * n_clip);
+    w.sse_part = c.take<double>(static_cast<size_t>(kTensorBlocks) * std::max<int>(kMaxFmt * n_clip, MOFQ_MAX_CANDIDATES));
   }
   w.bytes = (c.off + kAlign - 1) / kAlign * kAlign;
   return w;
@@ -165,7 +165,7 @@ bool one_sweep_launch(const int32_t* cand, int n_cand) {
 
 int sweep_candidates(const mofq_tensor_t* t, const int32_t* cand, int n_cand,
                      const mofq_scale_cfg_t* cfg, const WOnlyWs& w, hipStream_t st,
-                     const float* ext_absmax = nullptr, const SweepEmit* em = nullptr) {
+                     const SweepEmit* em = nullptr) {
   int c0 = 0;
   while (c0 < n_cand) {
     // two different formats share one launch (one read of the tensor); a repeated
@@ -174,7 +174,6 @@ int sweep_candidates(const mofq_tensor_t* t, const int32_t* cand, int n_cand,
     SweepParams p{};
     int rc = sweep_params(t, cand, c0, n, cfg, w, &p);
     if (rc != MOFQ_OK) return rc;
-    p.ext_absmax = ext_absmax;
     if (em) {
       if (n != 2) return MOFQ_ERR_INVALID_ARG;
       p.emit_i8 = em->i8;
@@ -190,6 +189,27 @@ int sweep_candidates(const mofq_tensor_t* t, const int32_t* cand, int n_cand,
     c0 += n;
   }
   return MOFQ_OK;
+}
+
+// One tensor with one scale and one clip ratio: the passes of mofq_tensor.hip.
+bool one_scale(const mofq_scale_cfg_t* cfg) { return cfg->gran == MOFQ_PER_TENSOR && cfg->n_clip == 1; }
+
+TensorParams tensor_params(const mofq_tensor_t* t, const int32_t* cand, int n_cand, const mofq_scale_cfg_t* cfg,
+                           const WOnlyWs& w) {
+  TensorParams p{};
+  p.w = t->data;
+  p.dtype = t->dtype;
+  p.rows = t->rows;
+  p.cols = t->cols;
+  p.ld = t->ld;
+  p.ratio = cfg->clip_ratios[0];
+  p.scale_f16 = cfg->scale_dtype == MOFQ_F16;
+  p.n_cand = n_cand;
+  for (int c = 0; c < n_cand; ++c) p.fmt[c] = cand[c];
+  p.absmax_part = w.absmax_part;
+  p.sse = w.sse_part;
+  p.energy = w.energy_part;
+  return p;
 }
 
 int check_candidates(const int32_t* cand, int n) {
@@ -307,7 +327,7 @@ int wo_output_score(const mofq_tensor_t* w, const mofq_tensor_t* x, const int32_
   // holds each row in registers and writes both candidates' grid values itself.
   const bool fused = n_cand == 2 && paired(cand[0], cand[1]) && w_cfg->gran == MOFQ_PER_CHANNEL && w_cfg->n_clip == 1;
   const SweepEmit em{nullptr, nullptr, 0, {a.wg[0], a.wg[1]}};
-  if ((rc = sweep_candidates(w, cand, n_cand, w_cfg, a.wrec, st, nullptr, fused ? &em : nullptr))) return rc;
+  if ((rc = sweep_candidates(w, cand, n_cand, w_cfg, a.wrec, st, fused ? &em : nullptr))) return rc;
   WaGemmParams g{};
   for (int c = 0; c < n_cand; ++c) {
     if (!fused) {
@@ -400,8 +420,8 @@ int wa_score(const mofq_tensor_t* w, const mofq_tensor_t* x, const int32_t* cand
     both = (cand[0] == MOFQ_INT8 && cand[1] == MOFQ_FP8_E4M3) || (cand[0] == MOFQ_FP8_E4M3 && cand[1] == MOFQ_INT8);
   const bool fused_x = both, fused_w = both && w_cfg->gran == MOFQ_PER_TENSOR;
   const SweepEmit ex{a.xq[0], a.xq[1], fp8_unit ? 0 : 1, {nullptr, nullptr}}, ew{a.wq[0], a.wq[1], fp8_unit ? 0 : 1, {nullptr, nullptr}};
-  if ((rc = sweep_candidates(x, cand, n_cand, &xc, a.xrec, st, nullptr, fused_x ? &ex : nullptr))) return rc;
-  if ((rc = sweep_candidates(w, cand, n_cand, w_cfg, a.wrec, st, nullptr, fused_w ? &ew : nullptr))) return rc;
+  if ((rc = sweep_candidates(x, cand, n_cand, &xc, a.xrec, st, fused_x ? &ex : nullptr))) return rc;
+  if ((rc = sweep_candidates(w, cand, n_cand, w_cfg, a.wrec, st, fused_w ? &ew : nullptr))) return rc;
   WaGemmParams g{};
   int n_q = 0;
   for (int f = 0; f < 2; ++f) {
@@ -742,6 +762,13 @@ int select_w_only(const mofq_tensor_t* w, const int32_t* candidates, int n_candi
   const WOnlyWs s = carve_w_only(ws, units, n_candidates, w_cfg->gran, w_cfg->n_clip);
   if (!ws || ws_bytes < s.bytes || !aligned16(ws)) return MOFQ_ERR_WORKSPACE;
   if (ev0 && hipEventRecord(ev0, st) != hipSuccess) return MOFQ_ERR_HIP;
+  if (one_scale(w_cfg)) {
+    TensorParams p = tensor_params(w, candidates, n_candidates, w_cfg, s);
+    p.out = *w_out;
+    p.result = result;
+    if ((rc = launch_tensor_select(p, st))) return rc;
+    return ev1 && hipEventRecord(ev1, st) != hipSuccess ? MOFQ_ERR_HIP : MOFQ_OK;
+  }
   if ((rc = sweep_candidates(w, candidates, n_candidates, w_cfg, s, st))) return rc;
   if (ev1 && hipEventRecord(ev1, st) != hipSuccess) return MOFQ_ERR_HIP;
   DecideParams d{};
@@ -866,6 +893,12 @@ int mofq_quantize(const mofq_tensor_t* t, int32_t format, const mofq_scale_cfg_t
   const WOnlyWs w = carve_w_only(ws, units, 1, cfg->gran, cfg->n_clip);
   if (!ws || ws_bytes < w.bytes || !aligned16(ws)) return MOFQ_ERR_WORKSPACE;
   hipStream_t st = static_cast<hipStream_t>(stream);
+  if (one_scale(cfg)) {
+    TensorParams p = tensor_params(t, &format, 1, cfg, w);
+    p.out = *out;
+    p.tensor_err = tensor_err;
+    return launch_tensor_quantize(p, st);
+  }
   if ((rc = sweep_candidates(t, &format, 1, cfg, w, st))) return rc;
   EmitParams e{};
   if (tensor_err) {
@@ -1099,9 +1132,11 @@ int mofq_select_layers_timed(int32_t n_layers, const mofq_tensor_t* w, const int
   for (int i0 = 0, nb = 0; i0 < n_layers; i0 += nb) {
     nb = batch_length(n_layers, w, i0, cus);
     WOnlyWs slot[kEmitBatch];
+    char* slot_base[kEmitBatch];
     // 1. the searches, back to back; the tensors of one row length share a launch
     for (int j = 0; j < nb; ++j) {
       const int64_t units = mofq_num_units(w[i0 + j].rows, w[i0 + j].cols, w_cfg->gran, w_cfg->group_size);
+      slot_base[j] = base;
       slot[j] = carve_w_only(base, units, n_candidates, w_cfg->gran, w_cfg->n_clip);
       base += slot[j].bytes;
     }
@@ -1123,6 +1158,13 @@ int mofq_select_layers_timed(int32_t n_layers, const mofq_tensor_t* w, const int
           last = k;
         }
       if (ev_begin && hipEventRecord(static_cast<hipEvent_t>(ev_begin[i0 + j]), st) != hipSuccess) return join(MOFQ_ERR_HIP);
+      if (one_scale(w_cfg)) {
+        // one scale per tensor: nothing to share, the whole of mofq_select_layer per tensor
+        for (int k = j; k <= last; ++k)
+          if (first[k] == j &&
+              (rc = select_w_only(&w[i0 + k], candidates, n_candidates, w_cfg, &w_out[i0 + k], &results[i0 + k], slot_base[k], slot[k].bytes, st, nullptr, nullptr)))
+            return join(rc);
+      } else
       if (g > 1) {
         if (!one_launch) return join(MOFQ_ERR_INVALID_ARG);   // cannot happen: see plan_search_groups
         if ((rc = launch_sweep_group(sp, g, st))) return join(rc);
@@ -1136,6 +1178,7 @@ int mofq_select_layers_timed(int32_t n_layers, const mofq_tensor_t* w, const int
     //    the winners and the per-unit outputs, one launch for the tensors of one dtype.  The next
     //    batch's searches follow on the caller's stream meanwhile; every tensor has its own
     //    workspace.
+    if (one_scale(w_cfg)) continue;
     if ((rc = sw.fork())) return join(rc);
     for (int dtype : {MOFQ_F32, MOFQ_F16, MOFQ_BF16}) {
       EmitParams e[kEmitBatch];
@@ -1157,15 +1200,9 @@ int mofq_calibrate_absmax(const mofq_tensor_t* x, float* absmax, void* ws, size_
   if ((rc = check_cfg(x, &cfg))) return rc;
   const WOnlyWs s = carve_w_only(ws, 1, 1, MOFQ_PER_TENSOR, 1);
   if (!ws || ws_bytes < s.bytes || !aligned16(ws)) return MOFQ_ERR_WORKSPACE;
-  SweepParams p{};
-  p.w = x->data;
-  p.dtype = x->dtype;
-  p.rows = x->rows;
-  p.cols = x->cols;
-  p.ld = x->ld;
-  p.absmax_part = s.absmax_part;
-  p.energy_part = s.energy_part;
-  return launch_running_absmax(p, absmax, static_cast<hipStream_t>(stream));
+  TensorParams p = tensor_params(x, nullptr, 0, &cfg, s);
+  p.running = absmax;
+  return launch_running_absmax(p, static_cast<hipStream_t>(stream));
 }
 
 int mofq_select_calibrated(const mofq_tensor_t* x, const int32_t* candidates, int32_t n_candidates,
@@ -1181,32 +1218,11 @@ int mofq_select_calibrated(const mofq_tensor_t* x, const int32_t* candidates, in
   hipStream_t st = static_cast<hipStream_t>(stream);
   const WOnlyWs s = carve_w_only(ws, 1, n_candidates, MOFQ_PER_TENSOR, 1);
   if (!ws || ws_bytes < s.bytes || !aligned16(ws)) return MOFQ_ERR_WORKSPACE;
-  if ((rc = sweep_candidates(x, candidates, n_candidates, &cfg, s, st, absmax))) return rc;
-  DecideParams d{};
-  d.units = 1;
-  d.n_cand = n_candidates;
-  for (int c = 0; c < n_candidates; ++c) d.err[c] = s.err[c];
-  d.energy = s.energy;
-  d.result = result;
-  if (!x_out) return launch_decide(d, st);
-  EmitParams e{};
-  e.w = x->data;
-  e.dtype = x->dtype;
-  e.rows = x->rows;
-  e.cols = x->cols;
-  e.ld = x->ld;
-  e.gran = MOFQ_PER_TENSOR;
-  e.group = 0;
-  e.n_cand = n_candidates;
-  for (int c = 0; c < n_candidates; ++c) {
-    e.fmt[c] = candidates[c];
-    e.scale[c] = s.scale[c];
-    e.clip[c] = s.clip[c];
-    e.err[c] = s.err[c];
-  }
-  e.decide = d;
-  e.out = *x_out;
-  return launch_emit(&e, 1, 0, st);
+  TensorParams p = tensor_params(x, candidates, n_candidates, &cfg, s);
+  p.ext_absmax = absmax;
+  if (x_out) p.out = *x_out;
+  p.result = result;
+  return launch_tensor_select(p, st);
 }
 
 size_t mofq_select_units_workspace_bytes(const mofq_tensor_t* w, int32_t n_candidates,

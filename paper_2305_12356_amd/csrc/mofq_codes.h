@@ -1,0 +1,159 @@
+// Device helpers shared by the kernels that score and write codes: grid values and codes through the
+// gfx950 pack-convert instructions, elements kept as they come from memory.
+#pragma once
+#include <type_traits>
+
+#include "mofq_device.h"
+
+namespace mofq {
+
+namespace {
+
+// ---- grid value of a scaled element, two elements at a time ---------------------
+//
+// FP formats use the gfx950 pack-convert instructions (round to nearest even,
+// subnormals, saturation); they agree with Codec<>::mag / code on every finite fp32
+// bit pattern (checked exhaustively on the part), and cost about half the vector
+// cycles of the add/subtract-constant form.
+typedef float f32x2 __attribute__((ext_vector_type(2)));
+
+// `carry` is the register the fp4 encode merges its byte into; its other bytes are
+// never read, so it is simply handed from call to call (no clearing instruction).
+template <int FMT> MOFQ_DEV f32x2 grid2(float t0, float t1, uint32_t& carry) {
+  f32x2 g;
+  if constexpr (FMT == MOFQ_FP4_E2M1) {
+    carry = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(carry, t0, t1, 1.0f, 0);
+    g = __builtin_amdgcn_cvt_scalef32_pk_f32_fp4(carry, 1.0f, 0);
+  } else if constexpr (FMT == MOFQ_FP4_E2M1_IEEE) {
+    // the same grid below 3: clamp, then the same convert
+    carry = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(carry, med3(t0, -3.0f, 3.0f), med3(t1, -3.0f, 3.0f), 1.0f, 0);
+    g = __builtin_amdgcn_cvt_scalef32_pk_f32_fp4(carry, 1.0f, 0);
+  } else if constexpr (FMT == MOFQ_FP8_E4M3) {
+    const int p = __builtin_amdgcn_cvt_pk_fp8_f32(med3(t0, -448.0f, 448.0f), med3(t1, -448.0f, 448.0f), 0, false);
+    g = __builtin_amdgcn_cvt_pk_f32_fp8(p, false);
+  } else {
+    g[0] = Codec<FMT>::grid(t0);
+    g[1] = Codec<FMT>::grid(t1);
+  }
+  return g;
+}
+
+// Squared error of two elements, the residual and its square in fp64.
+template <int FMT> MOFQ_DEV void score2_f64(double& acc, float x0, float x1, float inv_s, double sd, uint32_t& carry) {
+  const f32x2 g = grid2<FMT>(x0 * inv_s, x1 * inv_s, carry);
+  const double d0 = __builtin_fma(-static_cast<double>(g[0]), sd, static_cast<double>(x0));
+  const double d1 = __builtin_fma(-static_cast<double>(g[1]), sd, static_cast<double>(x1));
+  acc = __builtin_fma(d0, d0, acc);
+  acc = __builtin_fma(d1, d1, acc);
+}
+
+// Codes of 8 scaled elements.  4-bit: one word, element 2j in the low nibble of byte j;
+// 8-bit: two words, one byte per element.  The FP formats use the gfx950 pack-convert
+// instructions (round to nearest even, subnormals kept, saturating; the E4M3 convert
+// needs its input clamped to +-448 first), which agree with Codec<>::code on every
+// finite fp32 bit pattern.
+template <int FMT>
+MOFQ_DEV void encode8(const float (&v)[8], float inv_s, uint32_t (&words)[2]) {
+  if constexpr (FMT == MOFQ_FP4_E2M1) {
+    uint32_t w = 0;
+    w = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(w, v[0] * inv_s, v[1] * inv_s, 1.0f, 0);
+    w = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(w, v[2] * inv_s, v[3] * inv_s, 1.0f, 1);
+    w = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(w, v[4] * inv_s, v[5] * inv_s, 1.0f, 2);
+    w = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(w, v[6] * inv_s, v[7] * inv_s, 1.0f, 3);
+    words[0] = w;
+    words[1] = 0;
+  } else if constexpr (FMT == MOFQ_FP8_E4M3) {
+    float t[8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) t[i] = med3(v[i] * inv_s, -448.0f, 448.0f);
+    int w0 = 0, w1 = 0;
+    w0 = __builtin_amdgcn_cvt_pk_fp8_f32(t[0], t[1], w0, false);
+    w0 = __builtin_amdgcn_cvt_pk_fp8_f32(t[2], t[3], w0, true);
+    w1 = __builtin_amdgcn_cvt_pk_fp8_f32(t[4], t[5], w1, false);
+    w1 = __builtin_amdgcn_cvt_pk_fp8_f32(t[6], t[7], w1, true);
+    words[0] = static_cast<uint32_t>(w0);
+    words[1] = static_cast<uint32_t>(w1);
+  } else if constexpr (FMT == MOFQ_INT4 || FMT == MOFQ_INT8) {
+    // Clamping before rounding gives the same integer (the bounds are integers); adding 1.5 * 2^23
+    // rounds to nearest even and leaves the two's-complement integer in the low bits.
+    constexpr float lo = FMT == MOFQ_INT4 ? -8.0f : -128.0f, hi = FMT == MOFQ_INT4 ? 7.0f : 127.0f;
+    uint32_t y[8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) y[i] = f2u(med3(v[i] * inv_s, lo, hi) + 12582912.0f);
+    if constexpr (FMT == MOFQ_INT4) {
+      uint32_t b[4];   // two codes in the low byte
+#pragma unroll
+      for (int i = 0; i < 4; ++i) b[i] = (y[2 * i] & 0xFu) | ((y[2 * i + 1] << 4) & ~0xFu);
+      words[0] = __builtin_amdgcn_perm(__builtin_amdgcn_perm(b[3], b[2], 0x0C0C0400u), __builtin_amdgcn_perm(b[1], b[0], 0x0C0C0400u), 0x05040100u);
+      words[1] = 0;
+    } else {
+#pragma unroll
+      for (int i = 0; i < 2; ++i)
+        words[i] = __builtin_amdgcn_perm(__builtin_amdgcn_perm(y[4 * i + 3], y[4 * i + 2], 0x0C0C0400u),
+                                         __builtin_amdgcn_perm(y[4 * i + 1], y[4 * i], 0x0C0C0400u), 0x05040100u);
+    }
+  } else if constexpr (Codec<FMT>::BITS == 4) {
+    uint32_t w = 0;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) w |= Codec<FMT>::code(v[i] * inv_s) << (4 * i);
+    words[0] = w;
+    words[1] = 0;
+  } else {
+    uint32_t w0 = 0, w1 = 0;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      w0 |= Codec<FMT>::code(v[i] * inv_s) << (8 * i);
+      w1 |= Codec<FMT>::code(v[4 + i] * inv_s) << (8 * i);
+    }
+    words[0] = w0;
+    words[1] = w1;
+  }
+}
+
+// 8 elements as they come from memory, widened where they are used
+template <typename In> struct Raw8 {
+  u32x4 w;
+  // element i0 + i; i0 is uniform
+  MOFQ_DEV void load(const void* base, int64_t i0, uint32_t i) {
+    w = *reinterpret_cast<const u32x4*>(static_cast<const uint16_t*>(base) + i0 + i);
+  }
+  MOFQ_DEV void widen(float (&v)[8]) const {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      if constexpr (std::is_same<In, F16>::value) {
+        v[2 * i] = static_cast<float>(__builtin_bit_cast(_Float16, static_cast<uint16_t>(w[i])));
+        v[2 * i + 1] = static_cast<float>(__builtin_bit_cast(_Float16, static_cast<uint16_t>(w[i] >> 16)));
+      } else {
+        v[2 * i] = u2f(w[i] << 16);
+        v[2 * i + 1] = u2f(w[i] & 0xFFFF0000u);
+      }
+    }
+  }
+};
+template <> struct Raw8<F32> {
+  u32x4 w[2];
+  MOFQ_DEV void load(const void* base, int64_t i0, uint32_t i) {
+    const u32x4* p = reinterpret_cast<const u32x4*>(static_cast<const float*>(base) + i0 + i);
+    w[0] = p[0];
+    w[1] = p[1];
+  }
+  MOFQ_DEV void widen(float (&v)[8]) const {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) { v[i] = u2f(w[0][i]); v[4 + i] = u2f(w[1][i]); }
+  }
+};
+
+template <typename F> MOFQ_DEV void with_format(int fmt, F&& f) {
+  switch (fmt) {
+    case MOFQ_INT4: f(std::integral_constant<int, MOFQ_INT4>{}); break;
+    case MOFQ_FP4_E2M1: f(std::integral_constant<int, MOFQ_FP4_E2M1>{}); break;
+    case MOFQ_INT8: f(std::integral_constant<int, MOFQ_INT8>{}); break;
+    case MOFQ_FP4_E2M1_IEEE: f(std::integral_constant<int, MOFQ_FP4_E2M1_IEEE>{}); break;
+    case MOFQ_FP8_E5M2: f(std::integral_constant<int, MOFQ_FP8_E5M2>{}); break;
+    default: f(std::integral_constant<int, MOFQ_FP8_E4M3>{}); break;
+  }
+}
+
+}  // namespace
+
+}  // namespace mofq

@@ -3,9 +3,8 @@
 // with the scales the search chose.  The decision never leaves device memory,
 // so a whole model can be processed without a host synchronisation.
 #include <algorithm>
-#include <type_traits>
 
-#include "mofq_device.h"
+#include "mofq_codes.h"
 #include "mofq_internal.h"
 
 namespace mofq {
@@ -235,50 +234,6 @@ __global__ __launch_bounds__(256) void wa_copy_kernel(const WaCopyArgs a) {
 // thread per unit (as a branch of the chunk loop they cost two dependent loads in every wave).
 // Measured: a 7B-shaped block with groups of 128 (202 M elements) 193 us -> 113 us, 4.5 TB/s.
 
-// Codes of 8 scaled elements.  4-bit: one word, element 2j in the low nibble of byte j;
-// 8-bit: two words, one byte per element.  The FP formats use the gfx950 pack-convert
-// instructions (round to nearest even, subnormals kept, saturating; the E4M3 convert
-// needs its input clamped to +-448 first), which agree with Codec<>::code on every
-// finite fp32 bit pattern.
-template <int FMT>
-MOFQ_DEV void encode8(const float (&v)[8], float inv_s, uint32_t (&words)[2]) {
-  if constexpr (FMT == MOFQ_FP4_E2M1) {
-    uint32_t w = 0;
-    w = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(w, v[0] * inv_s, v[1] * inv_s, 1.0f, 0);
-    w = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(w, v[2] * inv_s, v[3] * inv_s, 1.0f, 1);
-    w = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(w, v[4] * inv_s, v[5] * inv_s, 1.0f, 2);
-    w = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(w, v[6] * inv_s, v[7] * inv_s, 1.0f, 3);
-    words[0] = w;
-    words[1] = 0;
-  } else if constexpr (FMT == MOFQ_FP8_E4M3) {
-    float t[8];
-#pragma unroll
-    for (int i = 0; i < 8; ++i) t[i] = med3(v[i] * inv_s, -448.0f, 448.0f);
-    int w0 = 0, w1 = 0;
-    w0 = __builtin_amdgcn_cvt_pk_fp8_f32(t[0], t[1], w0, false);
-    w0 = __builtin_amdgcn_cvt_pk_fp8_f32(t[2], t[3], w0, true);
-    w1 = __builtin_amdgcn_cvt_pk_fp8_f32(t[4], t[5], w1, false);
-    w1 = __builtin_amdgcn_cvt_pk_fp8_f32(t[6], t[7], w1, true);
-    words[0] = static_cast<uint32_t>(w0);
-    words[1] = static_cast<uint32_t>(w1);
-  } else if constexpr (Codec<FMT>::BITS == 4) {
-    uint32_t w = 0;
-#pragma unroll
-    for (int i = 0; i < 8; ++i) w |= Codec<FMT>::code(v[i] * inv_s) << (4 * i);
-    words[0] = w;
-    words[1] = 0;
-  } else {
-    uint32_t w0 = 0, w1 = 0;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      w0 |= Codec<FMT>::code(v[i] * inv_s) << (8 * i);
-      w1 |= Codec<FMT>::code(v[4 + i] * inv_s) << (8 * i);
-    }
-    words[0] = w0;
-    words[1] = w1;
-  }
-}
-
 struct EmitTensor {
   const void* w;
   int64_t ld, cols, n_chunks;
@@ -346,50 +301,6 @@ MOFQ_DEV void emit_chunk(const EmitArgs& a, void* codes, int64_t c0, uint32_t l,
     o[0] = words[0];
     o[1] = words[1];
     (static_cast<u32x2*>(codes) + c0)[l] = o;
-  }
-}
-
-// 8 elements as they come from memory, widened where they are used
-template <typename In> struct Raw8 {
-  u32x4 w;
-  // element i0 + i; i0 is uniform
-  MOFQ_DEV void load(const void* base, int64_t i0, uint32_t i) {
-    w = *reinterpret_cast<const u32x4*>(static_cast<const uint16_t*>(base) + i0 + i);
-  }
-  MOFQ_DEV void widen(float (&v)[8]) const {
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      if constexpr (std::is_same<In, F16>::value) {
-        v[2 * i] = static_cast<float>(__builtin_bit_cast(_Float16, static_cast<uint16_t>(w[i])));
-        v[2 * i + 1] = static_cast<float>(__builtin_bit_cast(_Float16, static_cast<uint16_t>(w[i] >> 16)));
-      } else {
-        v[2 * i] = u2f(w[i] << 16);
-        v[2 * i + 1] = u2f(w[i] & 0xFFFF0000u);
-      }
-    }
-  }
-};
-template <> struct Raw8<F32> {
-  u32x4 w[2];
-  MOFQ_DEV void load(const void* base, int64_t i0, uint32_t i) {
-    const u32x4* p = reinterpret_cast<const u32x4*>(static_cast<const float*>(base) + i0 + i);
-    w[0] = p[0];
-    w[1] = p[1];
-  }
-  MOFQ_DEV void widen(float (&v)[8]) const {
-#pragma unroll
-    for (int i = 0; i < 4; ++i) { v[i] = u2f(w[0][i]); v[4 + i] = u2f(w[1][i]); }
-  }
-};
-
-template <typename F> MOFQ_DEV void with_format(int fmt, F&& f) {
-  switch (fmt) {
-    case MOFQ_INT4: f(std::integral_constant<int, MOFQ_INT4>{}); break;
-    case MOFQ_FP4_E2M1: f(std::integral_constant<int, MOFQ_FP4_E2M1>{}); break;
-    case MOFQ_INT8: f(std::integral_constant<int, MOFQ_INT8>{}); break;
-    case MOFQ_FP4_E2M1_IEEE: f(std::integral_constant<int, MOFQ_FP4_E2M1_IEEE>{}); break;
-    case MOFQ_FP8_E5M2: f(std::integral_constant<int, MOFQ_FP8_E5M2>{}); break;
-    default: f(std::integral_constant<int, MOFQ_FP8_E4M3>{}); break;
   }
 }
 

@@ -36,7 +36,6 @@ struct SweepParams {
   float* absmax_part;     // [kTensorBlocks]
   double* sse_part;       // [kTensorBlocks][n_fmt][n_clip]
   double* energy_part;    // [kTensorBlocks]
-  const float* ext_absmax;  // device, one value, or nullptr: use this magnitude instead of the tensor's own
   // per-tensor (INT8, FP8-E4M3) pair with one clip ratio only: the scoring pass also writes
   // the quantized tensor in both formats (dense rows), saving two further reads of the input
   uint8_t* emit_i8;         // int8 codes, or nullptr
@@ -49,9 +48,30 @@ struct SweepParams {
 
 constexpr int kTensorBlocks = 1024;  // partial results of per-tensor passes
 
-// max|x| of a tensor folded into a running maximum: *running = max(*running, max|x|).
-// `absmax_part` / `energy_part` are scratch of kTensorBlocks entries.
-int launch_running_absmax(const SweepParams& p, float* running, hipStream_t stream);
+// Per-tensor scales with one clip ratio (mofq_tensor.hip).
+struct TensorParams {
+  const void* w;
+  int32_t dtype;
+  int64_t rows, cols, ld;
+  float ratio;
+  int32_t scale_f16;
+  int32_t n_cand;
+  int32_t fmt[MOFQ_MAX_CANDIDATES];
+  const float* ext_absmax;       // device, one value, or nullptr: use this magnitude instead of the tensor's own
+  float* running;                // device, one value (launch_running_absmax only)
+  float* absmax_part;            // scratch, [kTensorBlocks]
+  double* sse;                   // scratch, [MOFQ_MAX_CANDIDATES][kTensorBlocks]
+  double* energy;                // scratch, [kTensorBlocks]
+  mofq_qout_t out;               // members may be nullptr
+  mofq_result_t* result;         // optional
+  double* tensor_err;            // optional (launch_tensor_quantize)
+};
+// *running = max(*running, max|x|).
+int launch_running_absmax(const TensorParams& p, hipStream_t stream);
+// Algorithm 1's select among n_cand formats, the record and the winner's outputs.
+int launch_tensor_select(const TensorParams& p, hipStream_t stream);
+// Codes, scale and error in the one format fmt[0].
+int launch_tensor_quantize(const TensorParams& p, hipStream_t stream);
 
 // Enqueue the scale search.  Returns a mofq_status_t.
 int launch_sweep(const SweepParams& p, hipStream_t stream);

@@ -12,7 +12,7 @@
 // 100-candidate search the kernel is bound by the vector units, not by HBM.
 #include <type_traits>
 
-#include "mofq_device.h"
+#include "mofq_codes.h"
 #include "mofq_internal.h"
 
 namespace mofq {
@@ -31,7 +31,6 @@ struct SweepArgs {
   double* sse_part;
   double* energy_part;
   int32_t n_blocks;  // per-tensor: blocks of the partial passes
-  const float* ext_absmax;   // per-tensor: calibrated magnitude replacing the tensor's own, or nullptr
   int32_t k0;                // per-tensor: first clip candidate of this scoring pass
   uint8_t* emit_i8;          // per-tensor 8-bit pair: also write the codes (see SweepParams)
   void* emit_f8;
@@ -57,35 +56,6 @@ MOFQ_DEV void accumulate(double& acc, float x, double xd, float inv_s, double sd
   }
 }
 
-// ---- grid value of a scaled element, two elements at a time ---------------------
-//
-// FP formats use the gfx950 pack-convert instructions (round to nearest even,
-// subnormals, saturation); they agree with Codec<>::mag / code on every finite fp32
-// bit pattern (checked exhaustively on the part), and cost about half the vector
-// cycles of the add/subtract-constant form.
-typedef float f32x2 __attribute__((ext_vector_type(2)));
-
-// `carry` is the register the fp4 encode merges its byte into; its other bytes are
-// never read, so it is simply handed from call to call (no clearing instruction).
-template <int FMT> MOFQ_DEV f32x2 grid2(float t0, float t1, uint32_t& carry) {
-  f32x2 g;
-  if constexpr (FMT == MOFQ_FP4_E2M1) {
-    carry = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(carry, t0, t1, 1.0f, 0);
-    g = __builtin_amdgcn_cvt_scalef32_pk_f32_fp4(carry, 1.0f, 0);
-  } else if constexpr (FMT == MOFQ_FP4_E2M1_IEEE) {
-    // the same grid below 3: clamp, then the same convert
-    carry = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(carry, med3(t0, -3.0f, 3.0f), med3(t1, -3.0f, 3.0f), 1.0f, 0);
-    g = __builtin_amdgcn_cvt_scalef32_pk_f32_fp4(carry, 1.0f, 0);
-  } else if constexpr (FMT == MOFQ_FP8_E4M3) {
-    const int p = __builtin_amdgcn_cvt_pk_fp8_f32(med3(t0, -448.0f, 448.0f), med3(t1, -448.0f, 448.0f), 0, false);
-    g = __builtin_amdgcn_cvt_pk_f32_fp8(p, false);
-  } else {
-    g[0] = Codec<FMT>::grid(t0);
-    g[1] = Codec<FMT>::grid(t1);
-  }
-  return g;
-}
-
 // Phase 1 of the search: squared error of two elements in fp32 (fused residual and
 // accumulation, relative error of a unit's sum below 60 * 2^-24).
 template <int FMT> MOFQ_DEV void score2_f32(float& acc, float x0, float x1, float inv_s, float s, uint32_t& carry) {
@@ -94,15 +64,6 @@ template <int FMT> MOFQ_DEV void score2_f32(float& acc, float x0, float x1, floa
   const float d1 = __builtin_fmaf(-g[1], s, x1);
   acc = __builtin_fmaf(d0, d0, acc);
   acc = __builtin_fmaf(d1, d1, acc);
-}
-
-// Phase 2: the same two elements with the residual and its square in fp64.
-template <int FMT> MOFQ_DEV void score2_f64(double& acc, float x0, float x1, float inv_s, double sd, uint32_t& carry) {
-  const f32x2 g = grid2<FMT>(x0 * inv_s, x1 * inv_s, carry);
-  const double d0 = __builtin_fma(-static_cast<double>(g[0]), sd, static_cast<double>(x0));
-  const double d1 = __builtin_fma(-static_cast<double>(g[1]), sd, static_cast<double>(x1));
-  acc = __builtin_fma(d0, d0, acc);
-  acc = __builtin_fma(d1, d1, acc);
 }
 
 // Sum over the wave in six DPP steps; the total is valid in lanes 48..63 only.
@@ -672,7 +633,6 @@ __global__ __launch_bounds__(256) void tensor_absmax_kernel(const SweepArgs a) {
 constexpr int kTensorMaxClip = 8;
 
 MOFQ_DEV float tensor_absmax(const SweepArgs& a, float* s_tmp) {
-  if (a.ext_absmax) return *a.ext_absmax;   // uniform over the grid
   const int tid = threadIdx.x;
   float m = 0.0f;
   for (int i = tid; i < a.n_blocks; i += 256) m = __builtin_fmaxf(m, a.absmax_part[i]);
@@ -874,21 +834,6 @@ __global__ __launch_bounds__(256) void tensor_finalize_kernel(const SweepArgs a)
   }
 }
 
-// *dst = max(*dst, max of the partials): one workgroup.
-__global__ __launch_bounds__(256) void absmax_fold_kernel(const float* part, int n, float* dst) {
-  __shared__ float s_tmp[4];
-  const int tid = threadIdx.x;
-  float m = 0.0f;
-  for (int i = tid; i < n; i += 256) m = __builtin_fmaxf(m, part[i]);
-  m = wave_max(m);
-  if ((tid & 63) == 0) s_tmp[tid >> 6] = m;
-  __syncthreads();
-  if (tid == 0) {
-    m = __builtin_fmaxf(__builtin_fmaxf(s_tmp[0], s_tmp[1]), __builtin_fmaxf(s_tmp[2], s_tmp[3]));
-    *dst = __builtin_fmaxf(*dst, m);
-  }
-}
-
 // ---- dispatch ---------------------------------------------------------------------
 
 inline int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
@@ -1011,7 +956,6 @@ int launch_sweep(const SweepParams& p, hipStream_t st) {
   a.absmax_part = p.absmax_part;
   a.sse_part = p.sse_part;
   a.energy_part = p.energy_part;
-  a.ext_absmax = (p.gran == MOFQ_PER_TENSOR) ? p.ext_absmax : nullptr;
   if (p.emit_i8 || p.emit_f8) {
     if (p.gran != MOFQ_PER_TENSOR) return MOFQ_ERR_UNSUPPORTED;
     a.emit_i8 = p.emit_i8;
@@ -1045,27 +989,6 @@ int launch_sweep_group(const SweepParams* p, int n, hipStream_t st) {
     if (rc != MOFQ_OK) return rc;
   }
   return MOFQ_OK;
-}
-
-int launch_running_absmax(const SweepParams& p, float* running, hipStream_t st) {
-  if (!running || !p.absmax_part || !p.energy_part) return MOFQ_ERR_INVALID_ARG;
-  SweepArgs a{};
-  a.w = p.w;
-  a.rows = p.rows;
-  a.cols = p.cols;
-  a.ld = p.ld;
-  a.absmax_part = p.absmax_part;
-  a.energy_part = p.energy_part;
-  const int64_t n_chunks = a.rows * (a.cols / 8);
-  a.n_blocks = static_cast<int32_t>(std::min<int64_t>(kTensorBlocks, ceil_div(n_chunks, 256)));
-  switch (p.dtype) {
-    case MOFQ_F32: hipLaunchKernelGGL((tensor_absmax_kernel<F32>), dim3(a.n_blocks), dim3(256), 0, st, a); break;
-    case MOFQ_F16: hipLaunchKernelGGL((tensor_absmax_kernel<F16>), dim3(a.n_blocks), dim3(256), 0, st, a); break;
-    case MOFQ_BF16: hipLaunchKernelGGL((tensor_absmax_kernel<BF16>), dim3(a.n_blocks), dim3(256), 0, st, a); break;
-    default: return MOFQ_ERR_INVALID_ARG;
-  }
-  hipLaunchKernelGGL(absmax_fold_kernel, dim3(1), dim3(256), 0, st, a.absmax_part, a.n_blocks, running);
-  return hip_status(hipGetLastError());
 }
 
 }  // namespace mofq
