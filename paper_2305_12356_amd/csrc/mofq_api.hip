@@ -93,6 +93,8 @@ struct WOnlyWs {
   double* sse_part;
   double* energy_part;
   double* decide_part;
+  uint8_t* tag;          // per-channel searches that write codes ahead
+  double* tally;
   size_t bytes;
 };
 
@@ -106,6 +108,10 @@ WOnlyWs carve_w_only(void* ws, int64_t units, int n_cand, int gran, int n_clip) 
   }
   w.energy = c.take<double>(units);
   w.decide_part = c.take<double>(kDecidePart);
+  if (gran == MOFQ_PER_CHANNEL) {
+    w.tag = c.take<uint8_t>(units);
+    w.tally = c.take<double>(kTallies * kTallyStride);
+  }
   if (gran == MOFQ_PER_TENSOR) {
     w.absmax_part = c.take<float>(kTensorBlocks);
     w.energy_part = c.take<double>(kTensorBlocks);
@@ -127,7 +133,7 @@ struct SweepEmit {
 // Parameters of the launch that scores candidates c0 .. c0 + n - 1 (n = 2: a pair of different
 // formats that share one read of the tensor).  A launch takes at most kMaxFmt formats.
 int sweep_params(const mofq_tensor_t* t, const int32_t* cand, int c0, int n,
-                 const mofq_scale_cfg_t* cfg, const WOnlyWs& w, SweepParams* out) {
+                 const mofq_scale_cfg_t* cfg, const WOnlyWs& w, void* ahead_codes, SweepParams* out) {
   if (n < 1 || n > kMaxFmt || c0 < 0 || c0 + n > MOFQ_MAX_CANDIDATES) return MOFQ_ERR_INVALID_ARG;
   SweepParams p{};
   p.w = t->data;
@@ -154,6 +160,12 @@ int sweep_params(const mofq_tensor_t* t, const int32_t* cand, int c0, int n,
   p.absmax_part = w.absmax_part;
   p.sse_part = w.sse_part;
   p.energy_part = w.energy_part;
+  if (ahead_codes) {
+    p.ahead.codes = ahead_codes;
+    p.ahead.tag = w.tag;
+    p.ahead.tally = w.tally;
+    for (int f = 0; f < n; ++f) p.ahead.cand_of[f] = slot[f];
+  }
   *out = p;
   return MOFQ_OK;
 }
@@ -163,16 +175,26 @@ bool one_sweep_launch(const int32_t* cand, int n_cand) {
   return n_cand == 1 || (n_cand == 2 && paired(cand[0], cand[1]));
 }
 
+// Whether the search of these tensors (one launch) should write codes ahead (AheadCodes): it saves
+// the second read of the input and costs a launch of 2 us for the tallies plus the rows done twice, so
+// it pays from about 100 MB on (64 MB: even).
+constexpr int64_t kAheadBytes = int64_t{128} << 20;
+bool codes_ahead(const mofq_tensor_t* t, const int32_t* cand, int n_cand, const mofq_scale_cfg_t* cfg, int64_t launch_bytes) {
+  return cfg->gran == MOFQ_PER_CHANNEL && cfg->n_clip == 1 && one_sweep_launch(cand, n_cand) && launch_bytes >= kAheadBytes &&
+         t->cols < (int64_t{1} << 31);
+}
+int64_t tensor_bytes(const mofq_tensor_t* t) { return t->rows * t->cols * (t->dtype == MOFQ_F32 ? 4 : 2); }
+
 int sweep_candidates(const mofq_tensor_t* t, const int32_t* cand, int n_cand,
                      const mofq_scale_cfg_t* cfg, const WOnlyWs& w, hipStream_t st,
-                     const SweepEmit* em = nullptr) {
+                     const SweepEmit* em = nullptr, void* ahead_codes = nullptr) {
   int c0 = 0;
   while (c0 < n_cand) {
     // two different formats share one launch (one read of the tensor); a repeated
     // format is scored on its own
     const int n = (c0 + 1 < n_cand && paired(cand[c0], cand[c0 + 1])) ? 2 : 1;
     SweepParams p{};
-    int rc = sweep_params(t, cand, c0, n, cfg, w, &p);
+    int rc = sweep_params(t, cand, c0, n, cfg, w, ahead_codes, &p);
     if (rc != MOFQ_OK) return rc;
     if (em) {
       if (n != 2) return MOFQ_ERR_INVALID_ARG;
@@ -769,7 +791,9 @@ int select_w_only(const mofq_tensor_t* w, const int32_t* candidates, int n_candi
     if ((rc = launch_tensor_select(p, st))) return rc;
     return ev1 && hipEventRecord(ev1, st) != hipSuccess ? MOFQ_ERR_HIP : MOFQ_OK;
   }
-  if ((rc = sweep_candidates(w, candidates, n_candidates, w_cfg, s, st))) return rc;
+  const bool ahead = codes_ahead(w, candidates, n_candidates, w_cfg, tensor_bytes(w));
+  if (ahead && (rc = launch_clear(&s.tally, 1, st))) return rc;
+  if ((rc = sweep_candidates(w, candidates, n_candidates, w_cfg, s, st, nullptr, ahead ? w_out->codes : nullptr))) return rc;
   if (ev1 && hipEventRecord(ev1, st) != hipSuccess) return MOFQ_ERR_HIP;
   DecideParams d{};
   d.units = units;
@@ -795,8 +819,9 @@ int select_w_only(const mofq_tensor_t* w, const int32_t* candidates, int n_candi
     e.err[c] = s.err[c];
   }
   e.decide = d;
+  e.tag = ahead ? s.tag : nullptr;
   e.out = *w_out;
-  return launch_emit(&e, 1, 0, st);
+  return ahead ? launch_fixup(&e, 1, 0, st) : launch_emit(&e, 1, 0, st);
 }
 
 }  // namespace
@@ -899,7 +924,8 @@ int mofq_quantize(const mofq_tensor_t* t, int32_t format, const mofq_scale_cfg_t
     p.tensor_err = tensor_err;
     return launch_tensor_quantize(p, st);
   }
-  if ((rc = sweep_candidates(t, &format, 1, cfg, w, st))) return rc;
+  const bool ahead = codes_ahead(t, &format, 1, cfg, tensor_bytes(t));
+  if ((rc = sweep_candidates(t, &format, 1, cfg, w, st, nullptr, ahead ? out->codes : nullptr))) return rc;
   EmitParams e{};
   if (tensor_err) {
     e.decide.units = units;
@@ -921,8 +947,9 @@ int mofq_quantize(const mofq_tensor_t* t, int32_t format, const mofq_scale_cfg_t
   e.scale[0] = w.scale[0];
   e.clip[0] = w.clip[0];
   e.err[0] = w.err[0];
+  e.tag = ahead ? w.tag : nullptr;
   e.out = *out;
-  return launch_emit(&e, 1, 0, st);
+  return ahead ? launch_fixup(&e, 1, 0, st) : launch_emit(&e, 1, 0, st);
 }
 
 int mofq_score(const mofq_tensor_t* w, const mofq_tensor_t* x, int32_t format, int32_t metric,
@@ -1143,6 +1170,17 @@ int mofq_select_layers_timed(int32_t n_layers, const mofq_tensor_t* w, const int
     int first[kEmitBatch];
     plan_search_groups(w + i0, nb, candidates, n_candidates, first);
     const bool one_launch = one_sweep_launch(candidates, n_candidates);
+    bool ahead[kEmitBatch];
+    double* tally[kEmitBatch];
+    int n_ahead = 0;
+    for (int j = 0; j < nb; ++j) {
+      int64_t bytes = 0;   // of tensor j's launch
+      for (int k = 0; k < nb; ++k)
+        if (first[k] == first[j]) bytes += tensor_bytes(&w[i0 + k]);
+      ahead[j] = codes_ahead(&w[i0 + j], candidates, n_candidates, w_cfg, bytes);
+      if (ahead[j]) tally[n_ahead++] = slot[j].tally;
+    }
+    if (n_ahead && (rc = launch_clear(tally, n_ahead, st))) return join(rc);
     for (int j = 0; j < nb; ++j) {
       if (first[j] != j) continue;
       // A launch over several tensors exists only where the whole candidate list is one
@@ -1152,7 +1190,7 @@ int mofq_select_layers_timed(int32_t n_layers, const mofq_tensor_t* w, const int
       int g = 0, last = j;
       for (int k = j; k < nb; ++k)
         if (first[k] == j) {
-          if (one_launch && (rc = sweep_params(&w[i0 + k], candidates, 0, n_candidates, w_cfg, slot[k], &sp[g])))
+          if (one_launch && (rc = sweep_params(&w[i0 + k], candidates, 0, n_candidates, w_cfg, slot[k], ahead[k] ? w_out[i0 + k].codes : nullptr, &sp[g])))
             return join(rc);
           ++g;
           last = k;
@@ -1169,7 +1207,8 @@ int mofq_select_layers_timed(int32_t n_layers, const mofq_tensor_t* w, const int
         if (!one_launch) return join(MOFQ_ERR_INVALID_ARG);   // cannot happen: see plan_search_groups
         if ((rc = launch_sweep_group(sp, g, st))) return join(rc);
       } else {
-        if ((rc = sweep_candidates(&w[i0 + j], candidates, n_candidates, w_cfg, slot[j], st))) return join(rc);
+        if ((rc = sweep_candidates(&w[i0 + j], candidates, n_candidates, w_cfg, slot[j], st, nullptr, ahead[j] ? w_out[i0 + j].codes : nullptr)))
+          return join(rc);
       }
       if (ev_end && hipEventRecord(static_cast<hipEvent_t>(ev_end[i0 + last]), st) != hipSuccess) return join(MOFQ_ERR_HIP);
     }
@@ -1181,10 +1220,15 @@ int mofq_select_layers_timed(int32_t n_layers, const mofq_tensor_t* w, const int
     if (one_scale(w_cfg)) continue;
     if ((rc = sw.fork())) return join(rc);
     for (int dtype : {MOFQ_F32, MOFQ_F16, MOFQ_BF16}) {
-      EmitParams e[kEmitBatch];
-      int n = 0;
+      EmitParams e[kEmitBatch], f[kEmitBatch];
+      int n = 0, m = 0;
       for (int j = 0; j < nb; ++j)
-        if (w[i0 + j].dtype == dtype) e[n++] = emit_params(i0 + j, slot[j]);
+        if (w[i0 + j].dtype == dtype) {
+          EmitParams& q = ahead[j] ? f[m++] : e[n++];
+          q = emit_params(i0 + j, slot[j]);
+          if (ahead[j]) q.tag = slot[j].tag;
+        }
+      if (m && (rc = launch_fixup(f, m, emit_cap, st2))) return join(rc);
       if (n && (rc = launch_emit(e, n, emit_cap, st2))) return join(rc);
     }
   }

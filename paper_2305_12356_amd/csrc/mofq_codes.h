@@ -4,6 +4,7 @@
 #include <type_traits>
 
 #include "mofq_device.h"
+#include "mofq_internal.h"
 
 namespace mofq {
 
@@ -110,6 +111,14 @@ MOFQ_DEV void encode8(const float (&v)[8], float inv_s, uint32_t (&words)[2]) {
   }
 }
 
+// What the finished rows of a tensor favour (AheadCodes).  Workgroup ids go round the XCDs; workgroup
+// scope keeps the addition in the XCD's own L2.  Stale or missed values only cost a row done twice.
+MOFQ_DEV double* tally_of(const AheadCodes& a) { return a.tally + (blockIdx.x % kTallies) * kTallyStride; }
+MOFQ_DEV double tally_read(const AheadCodes& a) { return __hip_atomic_load(tally_of(a), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP); }
+// one row in 16 is enough to tell
+MOFQ_DEV bool tally_adds() { return (blockIdx.x / kTallies) % 16 == 0; }
+MOFQ_DEV void tally_add(const AheadCodes& a, double d) { __hip_atomic_fetch_add(tally_of(a), d, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP); }
+
 // 8 elements as they come from memory, widened where they are used
 template <typename In> struct Raw8 {
   u32x4 w;
@@ -117,6 +126,8 @@ template <typename In> struct Raw8 {
   MOFQ_DEV void load(const void* base, int64_t i0, uint32_t i) {
     w = *reinterpret_cast<const u32x4*>(static_cast<const uint16_t*>(base) + i0 + i);
   }
+  MOFQ_DEV void clear() { w = u32x4{0u, 0u, 0u, 0u}; }
+  MOFQ_DEV void opaque() { asm volatile("" : "+v"(w)); }   // what was computed from it is not kept for later uses
   MOFQ_DEV void widen(float (&v)[8]) const {
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
@@ -137,6 +148,8 @@ template <> struct Raw8<F32> {
     w[0] = p[0];
     w[1] = p[1];
   }
+  MOFQ_DEV void clear() { w[0] = w[1] = u32x4{0u, 0u, 0u, 0u}; }
+  MOFQ_DEV void opaque() { asm volatile("" : "+v"(w[0]), "+v"(w[1])); }
   MOFQ_DEV void widen(float (&v)[8]) const {
 #pragma unroll
     for (int i = 0; i < 4; ++i) { v[i] = u2f(w[0][i]); v[4 + i] = u2f(w[1][i]); }

@@ -244,6 +244,7 @@ struct EmitTensor {
   const int32_t* clip[MOFQ_MAX_CANDIDATES];
   const double* err[MOFQ_MAX_CANDIDATES];
   Decision d;                // d.n = 0: candidate 0
+  const uint8_t* tag;        // fixup_kernel: [rows]
   uint8_t* unit_fmt;         // PER_UNIT: index of each unit's candidate
   mofq_qout_t out;
 };
@@ -399,6 +400,75 @@ __global__ __launch_bounds__(kThreads) void emit_kernel(const EmitArgs a) {
   }
 }
 
+// After searches that wrote codes ahead (AheadCodes): select, per-unit outputs, and the codes of the
+// rows that hold another candidate's.  A workgroup takes kFixRows rows at a time: a thread per row for
+// the outputs, then all threads for one row to be done again after the other.
+constexpr int kFixRows = 16;
+template <typename In>
+__global__ __launch_bounds__(kThreads) void fixup_kernel(const EmitArgs a) {
+  __shared__ double s_sum[kSums];
+  __shared__ int s_redo[kFixRows];
+  const int k = tensor_of(a.first_block, static_cast<int>(blockIdx.x));
+  const EmitTensor& t = a.t[k];
+  const int b = static_cast<int>(blockIdx.x) - a.first_block[k];
+  const int nb = (k + 1 < a.n ? a.first_block[k + 1] : static_cast<int>(gridDim.x)) - a.first_block[k];
+  const int64_t rows = t.n_chunks / t.cpr;
+  const int tid = threadIdx.x;
+  const int best = t.d.n > 0 ? decide(t.d, b == 0, s_sum) : 0;   // uniform
+  for (int64_t r0 = static_cast<int64_t>(b) * kFixRows; r0 < rows; r0 += static_cast<int64_t>(nb) * kFixRows) {
+    if (tid < kFixRows) {
+      const int64_t o = r0 + tid;
+      int redo = 0;
+      if (o < rows) {
+        redo = t.tag[o] != best;
+        const float s = t.scale[best][o];
+        const int32_t clip = t.clip[best][o];
+        const double err = t.err[best][o];
+        if (t.out.scales) {
+          if (a.scale_f16_out)
+            static_cast<uint16_t*>(t.out.scales)[o] = __half_as_ushort(__float2half_rn(s));  // exact: s is an fp16 value
+          else
+            static_cast<float*>(t.out.scales)[o] = s;
+        }
+        if (t.out.clip_idx) t.out.clip_idx[o] = clip;
+        if (t.out.unit_err) t.out.unit_err[o] = err;
+      }
+      s_redo[tid] = redo;
+    }
+    __syncthreads();
+    for (int i = 0; i < kFixRows; ++i) {
+      if (!s_redo[i]) continue;   // uniform
+      const int64_t row = r0 + i;
+      const float inv_s = 1.0f / t.scale[best][row];
+      const int cpr = static_cast<int>(t.cpr);
+      with_format(a.fmt[best], [&](auto fmt_c) {
+        for (int l0 = tid; l0 < cpr; l0 += kThreads * kEmitUnroll) {
+          Raw8<In> raw[kEmitUnroll];
+#pragma unroll
+          for (int u = 0; u < kEmitUnroll; ++u)
+            raw[u].load(t.w, row * t.ld, static_cast<uint32_t>(l0 + u * kThreads < cpr ? l0 + u * kThreads : l0) * 8);
+#pragma unroll
+          for (int u = 0; u < kEmitUnroll; ++u)
+            if (l0 + u * kThreads < cpr) {
+              float v[8];
+              raw[u].widen(v);
+              emit_chunk<decltype(fmt_c)::value>(a, t.out.codes, row * t.cpr, static_cast<uint32_t>(l0 + u * kThreads), v, inv_s);
+            }
+        }
+      });
+    }
+    __syncthreads();   // s_redo is free again
+  }
+}
+
+struct ClearArgs {
+  double* p[kEmitBatch];
+  int32_t n;
+};
+__global__ __launch_bounds__(kTallies * kTallyStride) void clear_kernel(const ClearArgs a) {   // a workgroup per tally
+  a.p[blockIdx.x][threadIdx.x] = 0.0;
+}
+
 }  // namespace
 
 namespace {
@@ -517,15 +587,19 @@ int launch_decide(const DecideParams& p, hipStream_t st) {
   return hip_status(hipGetLastError());
 }
 
-int launch_emit(const EmitParams* p, int n, int max_blocks, hipStream_t st) {
+namespace {
+
+// Kernel arguments of an emission (segments and everything else but the workgroups), and the first
+// stages of its reduces.
+int prepare_emit(const EmitParams* p, int n, EmitArgs& a, hipStream_t st) {
   if (!p || n < 1 || n > kEmitBatch) return MOFQ_ERR_INVALID_ARG;
   static_assert(sizeof(EmitArgs) <= 4096 && MOFQ_MAX_CANDIDATES >= 2, "kernel arguments");
-  EmitArgs a{};
+  a = EmitArgs{};
   const DecideParams* dec[kEmitBatch];
   int n_dec = 0;
   // Segments of 512 to 2048 chunks: the largest that still give 1024 workgroups (4 on each of
   // 256 compute units); more of them would only repeat the select more often.
-  int64_t total_chunks = 0, total_seg = 0;
+  int64_t total_chunks = 0;
   for (int i = 0; i < n; ++i) total_chunks += p[i].rows * (p[i].cols / 8);
   const int64_t per_thread = std::min<int64_t>(8, std::max<int64_t>(2, total_chunks / (1024 * kThreads)));
   a.n = n;
@@ -553,7 +627,6 @@ int launch_emit(const EmitParams* p, int n, int max_blocks, hipStream_t st) {
     const int64_t n_seg = (t.n_chunks + t.seg_chunks - 1) / t.seg_chunks;
     if (n_seg >= (int64_t{1} << 31)) return MOFQ_ERR_UNSUPPORTED;
     t.n_seg = static_cast<int32_t>(n_seg);
-    total_seg += n_seg;
     t.gran = q.gran;
     if (q.gran == MOFQ_PER_GROUP) {
       if (q.group < 8 || q.group > 4096 || (q.group & (q.group - 1)) != 0) return MOFQ_ERR_UNSUPPORTED;
@@ -565,19 +638,34 @@ int launch_emit(const EmitParams* p, int n, int max_blocks, hipStream_t st) {
       t.d = decision(q.decide, two_stages(q.decide));
       dec[n_dec++] = &q.decide;
     }
+    t.tag = q.tag;
     t.unit_fmt = q.unit_fmt;
     t.out = q.out;
   }
-  int rc = n_dec ? launch_partial(dec, n_dec, st) : static_cast<int>(MOFQ_OK);
-  if (rc != MOFQ_OK) return rc;
-  const int64_t cap = max_blocks > 0 ? max_blocks : (int64_t{1} << 30);
-  int64_t blocks = 0;
-  for (int i = 0; i < n; ++i) {
-    a.first_block[i] = static_cast<int32_t>(blocks);
-    blocks += total_seg <= cap ? a.t[i].n_seg : std::max<int64_t>(1, a.t[i].n_seg * cap / total_seg);
-  }
   for (int i = n; i < kEmitBatch; ++i) a.first_block[i] = INT32_MAX;
-  const dim3 grid(static_cast<unsigned>(blocks));
+  return n_dec ? launch_partial(dec, n_dec, st) : static_cast<int>(MOFQ_OK);
+}
+
+// Workgroups: `want` per tensor, or their share of `cap` where they exceed it; returns the total.
+unsigned deal_blocks(EmitArgs& a, const int64_t* want, int64_t cap) {
+  int64_t total = 0, blocks = 0;
+  for (int i = 0; i < a.n; ++i) total += want[i];
+  for (int i = 0; i < a.n; ++i) {
+    a.first_block[i] = static_cast<int32_t>(blocks);
+    blocks += total <= cap ? want[i] : std::max<int64_t>(1, want[i] * cap / total);
+  }
+  return static_cast<unsigned>(blocks);
+}
+
+}  // namespace
+
+int launch_emit(const EmitParams* p, int n, int max_blocks, hipStream_t st) {
+  EmitArgs a;
+  const int rc = prepare_emit(p, n, a, st);
+  if (rc != MOFQ_OK) return rc;
+  int64_t want[kEmitBatch];
+  for (int i = 0; i < n; ++i) want[i] = a.t[i].n_seg;
+  const dim3 grid(deal_blocks(a, want, max_blocks > 0 ? max_blocks : int64_t{1} << 30));
   const bool per_unit = p[0].unit_fmt != nullptr;
 #define MOFQ_EMIT(IN)                                                                                                \
   if (per_unit && n == 1) hipLaunchKernelGGL((emit_kernel<IN, true, false>), grid, dim3(kThreads), 0, st, a);          \
@@ -591,6 +679,33 @@ int launch_emit(const EmitParams* p, int n, int max_blocks, hipStream_t st) {
     default: return MOFQ_ERR_INVALID_ARG;
   }
 #undef MOFQ_EMIT
+  return hip_status(hipGetLastError());
+}
+
+int launch_fixup(const EmitParams* p, int n, int max_blocks, hipStream_t st) {
+  for (int i = 0; i < n; ++i)
+    if (!p[i].tag || p[i].gran != MOFQ_PER_CHANNEL || p[i].unit_fmt || p[i].as_bf16_values) return MOFQ_ERR_INVALID_ARG;
+  EmitArgs a;
+  const int rc = prepare_emit(p, n, a, st);
+  if (rc != MOFQ_OK) return rc;
+  int64_t want[kEmitBatch];
+  for (int i = 0; i < n; ++i) want[i] = (p[i].rows + kFixRows - 1) / kFixRows;
+  const dim3 grid(deal_blocks(a, want, max_blocks > 0 ? max_blocks : 256 * 8));
+  switch (p[0].dtype) {
+    case MOFQ_F32: hipLaunchKernelGGL(fixup_kernel<F32>, grid, dim3(kThreads), 0, st, a); break;
+    case MOFQ_F16: hipLaunchKernelGGL(fixup_kernel<F16>, grid, dim3(kThreads), 0, st, a); break;
+    case MOFQ_BF16: hipLaunchKernelGGL(fixup_kernel<BF16>, grid, dim3(kThreads), 0, st, a); break;
+    default: return MOFQ_ERR_INVALID_ARG;
+  }
+  return hip_status(hipGetLastError());
+}
+
+int launch_clear(double* const* p, int n, hipStream_t st) {
+  if (!p || n < 1 || n > kEmitBatch) return MOFQ_ERR_INVALID_ARG;
+  ClearArgs a{};
+  a.n = n;
+  for (int i = 0; i < n; ++i) a.p[i] = p[i];
+  hipLaunchKernelGGL(clear_kernel, dim3(static_cast<unsigned>(n)), dim3(kTallies * kTallyStride), 0, st, a);
   return hip_status(hipGetLastError());
 }
 

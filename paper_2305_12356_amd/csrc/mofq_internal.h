@@ -21,6 +21,22 @@ struct UnitRecords {
   double* energy;  // sum x^2 per unit
 };
 
+// Codes written by the search itself (per-channel scales, one launch for the whole candidate list):
+// every row is emitted while it is at hand, in the format that the tensor's rows favour so far, so
+// that the tensor is read once; rows whose format turns out not to be the tensor's choice are
+// emitted again afterwards (launch_fixup).  What is favoured is a sum over finished rows that
+// workgroups read and add to as they come: it decides how many rows are done twice, never the result.
+// There is one sum per XCD, so that adding stays inside its L2 (an addition to one place of the whole
+// device takes some 70 ns and they queue up: 16384 rows took 1.4 ms instead of 0.25).
+struct AheadCodes {
+  void* codes;              // nullptr: not asked for
+  uint8_t* tag;             // [rows]: candidate whose codes the row holds
+  double* tally;            // [kTallies * kTallyStride]: sums of (error in slot 0 - error in slot 1); zero before the launch
+  int32_t cand_of[kMaxFmt]; // launch slot -> candidate index
+};
+
+constexpr int kTallies = 8, kTallyStride = 16;   // one per XCD, 128 bytes apart
+
 struct SweepParams {
   const void* w;
   int32_t dtype;
@@ -44,6 +60,7 @@ struct SweepParams {
   // per-channel pair of two different formats (bf16 input) with one clip ratio only: the pass
   // also writes the grid values of format slot f as bf16, dense [rows][cols], to emit_grid[f]
   void* emit_grid[kMaxFmt];
+  AheadCodes ahead;
 };
 
 constexpr int kTensorBlocks = 1024;  // partial results of per-tensor passes
@@ -117,11 +134,17 @@ struct EmitParams {
   const int32_t* clip[MOFQ_MAX_CANDIDATES];
   const double* err[MOFQ_MAX_CANDIDATES];
   DecideParams decide;           // units > 0: the launch takes this reduce + select too and emits its choice; else candidate 0
+  const uint8_t* tag;            // launch_fixup: [rows], as the search left it
   uint8_t* unit_fmt;             // device [units] or nullptr: every unit takes its own best candidate, whose index goes here
   mofq_qout_t out;
   int32_t as_bf16_values;        // out.codes receives the grid values as bf16
 };
 constexpr int kEmitBatch = 12;
+// The same after searches that wrote codes ahead (per-channel scales): per-unit outputs, and the codes
+// of the rows whose `tag` is not the choice.
+int launch_fixup(const EmitParams* p, int n, int max_blocks, hipStream_t stream);
+// Clears the tallies of such searches.
+int launch_clear(double* const* p, int n, hipStream_t stream);
 // max_blocks: 0, or a cap on the workgroups for emission that runs beside other kernels
 int launch_emit(const EmitParams* p, int n, int max_blocks, hipStream_t stream);
 

@@ -36,6 +36,7 @@ struct SweepArgs {
   void* emit_f8;
   int32_t emit_f8_as_bf16;
   uint16_t* emit_grid[kMaxFmt];   // per-channel single-candidate pair: grid values as bf16 (see SweepParams)
+  AheadCodes ahead;
   float clip[MOFQ_MAX_CLIP];
 };
 
@@ -274,48 +275,51 @@ __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(CH <= 4
 }
 
 // ------------------------------------------------------------------------------
-// Per-channel with a single candidate (absmax scale, no search): a memory-bound pass.
-// Same register-resident row, but no candidate tables and two barriers in all; not
-// held to the register budget of the search kernel.
-// ------------------------------------------------------------------------------
-#ifndef K1_WAVES
-#define K1_WAVES 4
-#endif
+// Per-channel with a single candidate (absmax scale, no search): a memory-bound pass, one workgroup
+// per row, two barriers.  The row stays in registers as it came from memory and is widened anew
+// in each of the three steps (magnitude and energy, errors, codes): left alone, the compiler
+// keeps the fp64 image of the whole row across the barrier (128 registers and spills for 4 chunks
+// per thread, 72 without).
+//
 // GRID: the pass also writes the grid values of both formats as bf16 (dense rows), the operands
 // of the weight-only layer-output products, so that they cost no further read of the tensor.
+// With a.ahead the row's codes leave from the same registers.
+// ------------------------------------------------------------------------------
 template <typename In, int FA, int FB, int THREADS, int CH, bool GRID = false>
-__global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(GRID ? 2 : K1_WAVES))) void sweep_channel_single_kernel(const SweepArgs a) {
-  using L = Load8<In>;
+__global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(GRID ? 2 : 4))) void sweep_channel_single_kernel(const SweepArgs a) {
   constexpr int NF = (FB >= 0) ? 2 : 1;
   constexpr int FBX = (FB >= 0) ? FB : FA;
   constexpr int NW = THREADS / 64;
-  constexpr int NE = CH * 8;
   __shared__ float s_wmax[NW];
   __shared__ double s_wen[NW];
   __shared__ double s_acc[2][NW];
+  __shared__ double s_tally;
 
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int64_t row = blockIdx.x;
-  const typename L::elem* src = static_cast<const typename L::elem*>(a.w) + row * a.ld;
+  // read at the start, so that its latency is hidden (it may miss the rows of the last microseconds), and
+  // by one thread: waves that read it at different times could disagree
+  double tally = 0.0;
+  if (NF == 2 && a.ahead.codes && tid == 0) tally = tally_read(a.ahead);
 
-  float x[NE];
+  const int cpr = static_cast<int>(a.cols / 8);
+  Raw8<In> raw[CH];   // chunk j: the row's chunk j * THREADS + tid; zeros past the row's end add nothing
+#pragma unroll
+  for (int j = 0; j < CH; ++j) {
+    const int c = j * THREADS + tid;
+    raw[j].load(a.w, row * a.ld, static_cast<uint32_t>(c < cpr ? c : 0) * 8);
+    if (c >= cpr) raw[j].clear();
+  }
   float amax = 0.0f;
   double en = 0.0;
 #pragma unroll
   for (int j = 0; j < CH; ++j) {
-    const int64_t c0 = (static_cast<int64_t>(j) * THREADS + tid) * 8;
     float v[8];
-    if (c0 < a.cols) {
-      L::load(src + c0, v);
-    } else {
-#pragma unroll
-      for (int i = 0; i < 8; ++i) v[i] = 0.0f;   // zeros past the row's end add nothing
-    }
+    raw[j].widen(v);
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
-      x[j * 8 + i] = v[i];
       amax = __builtin_fmaxf(amax, __builtin_fabsf(v[i]));
       const double xd = static_cast<double>(v[i]);
       en = __builtin_fma(xd, xd, en);
@@ -338,12 +342,15 @@ __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(GRID ? 
   uint32_t carry = 0;
 #pragma unroll
   for (int j = 0; j < CH; ++j) {
+    raw[j].opaque();
+    float v[8];
+    raw[j].widen(v);
     if constexpr (GRID) {
       // grid values have at most 7 significant bits: exact in bf16 (the top half of an fp32)
       u32x4 ga, gb;
 #pragma unroll
       for (int i = 0; i < 8; i += 2) {
-        const float x0 = x[j * 8 + i], x1 = x[j * 8 + i + 1];
+        const float x0 = v[i], x1 = v[i + 1];
         const f32x2 qa = grid2<FA>(x0 * iA, x1 * iA, carry);
         const f32x2 qb = grid2<FBX>(x0 * iB, x1 * iB, carry);
         ga[i >> 1] = (f2u(qa[0]) >> 16) | (f2u(qa[1]) & 0xFFFF0000u);
@@ -357,23 +364,23 @@ __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(GRID ? 
         accB = __builtin_fma(b0, b0, accB);
         accB = __builtin_fma(b1, b1, accB);
       }
-      const int64_t c0 = (static_cast<int64_t>(j) * THREADS + tid) * 8;
-      if (c0 < a.cols) {
-        const int64_t e8 = (row * a.cols + c0) / 8;
-        reinterpret_cast<u32x4*>(a.emit_grid[0])[e8] = ga;
-        reinterpret_cast<u32x4*>(a.emit_grid[1])[e8] = gb;
+      const int c = j * THREADS + tid;
+      if (c < cpr) {
+        reinterpret_cast<u32x4*>(a.emit_grid[0])[row * cpr + c] = ga;
+        reinterpret_cast<u32x4*>(a.emit_grid[1])[row * cpr + c] = gb;
       }
     } else {
 #pragma unroll
       for (int i = 0; i < 8; i += 2) {
-        score2_f64<FA>(accA, x[j * 8 + i], x[j * 8 + i + 1], iA, sAd, carry);
-        if constexpr (NF == 2) score2_f64<FBX>(accB, x[j * 8 + i], x[j * 8 + i + 1], iB, sBd, carry);
+        score2_f64<FA>(accA, v[i], v[i + 1], iA, sAd, carry);
+        if constexpr (NF == 2) score2_f64<FBX>(accB, v[i], v[i + 1], iB, sBd, carry);
       }
     }
   }
   accA = wave_sum(accA);
   if constexpr (NF == 2) accB = wave_sum(accB);
   if (lane == 0) { s_acc[0][wave] = accA; s_acc[1][wave] = accB; }
+  if (tid == 0) s_tally = tally;
   __syncthreads();
   if (tid < NF) {
     double t = 0.0;
@@ -383,6 +390,41 @@ __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(GRID ? 
     a.rec.clip[tid][row] = 0;
     a.rec.err[tid][row] = t;
     if (tid == 0 && a.rec.energy) a.rec.energy[row] = en;
+  }
+  if (!GRID && a.ahead.codes) {   // uniform
+    int slot = 0;
+    if constexpr (NF == 2) {
+      double d = 0.0;
+#pragma unroll
+      for (int w = 0; w < NW; ++w) d += s_acc[0][w] - s_acc[1][w];
+      slot = __builtin_amdgcn_readfirstlane(s_tally + d > 0.0 ? 1 : 0);
+      if (tid == 0 && tally_adds()) tally_add(a.ahead, d);
+    }
+    if (tid == 0) a.ahead.tag[row] = static_cast<uint8_t>(a.ahead.cand_of[slot]);
+    auto codes = [&](auto fmt_c, float inv) {
+      constexpr int FMT = decltype(fmt_c)::value;
+#pragma unroll
+      for (int j = 0; j < CH; ++j) {
+        const int c = j * THREADS + tid;
+        raw[j].opaque();
+        float v[8];
+        raw[j].widen(v);
+        uint32_t words[2];
+        encode8<FMT>(v, inv, words);
+        if (c < cpr) {
+          if constexpr (Codec<FMT>::BITS == 4) {
+            (static_cast<uint32_t*>(a.ahead.codes) + row * cpr)[c] = words[0];
+          } else {
+            u32x2 o;
+            o[0] = words[0];
+            o[1] = words[1];
+            (static_cast<u32x2*>(a.ahead.codes) + row * cpr)[c] = o;
+          }
+        }
+      }
+    };
+    if (slot == 0) codes(std::integral_constant<int, FA>{}, iA);
+    else codes(std::integral_constant<int, FBX>{}, iB);
   }
 }
 
@@ -966,6 +1008,10 @@ int launch_sweep(const SweepParams& p, hipStream_t st) {
     if (p.gran != MOFQ_PER_CHANNEL || p.n_clip != 1 || p.n_fmt != 2) return MOFQ_ERR_UNSUPPORTED;
     a.emit_grid[0] = static_cast<uint16_t*>(p.emit_grid[0]);
     a.emit_grid[1] = static_cast<uint16_t*>(p.emit_grid[1]);
+  }
+  if (p.ahead.codes) {
+    if (p.gran != MOFQ_PER_CHANNEL || p.n_clip != 1 || !p.ahead.tag || (p.n_fmt == 2 && !p.ahead.tally)) return MOFQ_ERR_UNSUPPORTED;
+    a.ahead = p.ahead;
   }
   a.units = mofq_num_units(p.rows, p.cols, p.gran, p.group);
   for (int k = 0; k < p.n_clip; ++k) a.clip[k] = p.clip[k];

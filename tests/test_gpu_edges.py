@@ -1,0 +1,52 @@
+"""Sizes at the edges of the launch rules and tiles: where a pass changes its shape (one launch or
+several, one or two stages of a sum, codes from the search or after it) and where a segment, a
+row or a unit ends inside a workgroup's piece.  Against the CPU oracle."""
+import pytest
+import torch
+
+import mofq_inputs as mi
+from oracle import mofq_oracle as orc
+from tests.test_gpu_w_only import check_tensor, mq  # noqa: F401
+
+pytestmark = pytest.mark.gpu
+
+DEV = "cuda:0"
+PAIR4, PAIR8 = [orc.INT4, orc.FP4_E2M1], [orc.FP8_E4M3, orc.INT8]
+
+
+def _strided(rows, cols, pad, seed, dtype):
+    w = mi.llama_like_weight(rows, cols + pad, seed=seed, dtype=dtype, device=DEV, outlier_frac=2e-3)
+    return w[:, :cols]
+
+
+# one launch up to 65536 elements, then three; one chunk; rows that lie apart
+@pytest.mark.parametrize("rows,cols,pad", [(1, 8, 0), (8, 8192, 0), (8, 8200, 0), (3, 1000, 8), (67, 1000, 24), (1025, 2056, 0)])
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+def test_per_tensor_passes(mq, rows, cols, pad, dtype):  # noqa: F811
+    w = _strided(rows, cols, pad, rows + cols, dtype)
+    check_tensor(mq, w, PAIR8, orc.PER_TENSOR, mi.clip_ratios(1), f16=rows == 67, label="tensor-edge")
+    check_tensor(mq, w, PAIR4 + [orc.FP4_E2M1_IEEE], orc.PER_TENSOR, mi.clip_ratios(1), label="tensor-edge-4")
+
+
+# rows of one chunk; units on both sides of the one-stage limit; segments that end inside rows and groups
+@pytest.mark.parametrize("rows,cols,pad,group", [(700, 8, 0, 0), (1024, 40, 0, 0), (1025, 264, 8, 0), (5, 32768, 0, 0),
+                                                 (33, 4128, 32, 32), (9, 16640, 0, 256), (70, 640, 64, 64)])
+def test_emission_segments(mq, rows, cols, pad, group):  # noqa: F811
+    w = _strided(rows, cols, pad, rows + cols, torch.float16)
+    gran = orc.PER_GROUP if group else orc.PER_CHANNEL
+    check_tensor(mq, w, PAIR4, gran, mi.clip_ratios(1), group, bool(group), label="emit-edge")
+    check_tensor(mq, w, PAIR8, gran, mi.clip_ratios(3), group, False, label="emit-edge-8")
+
+
+# inputs large enough that the search writes the codes itself; the first and last rows favour the format
+# that the tensor as a whole does not take, so rows are done twice
+@pytest.mark.parametrize("dtype,rows,cols,pad,cands,f16", [
+    (torch.float32, 4100, 8192, 0, PAIR4, False), (torch.bfloat16, 3001, 23008, 32, PAIR8, True),
+    (torch.float16, 16400, 4104, 0, [orc.FP4_E2M1, orc.INT4], False)])
+def test_codes_written_by_the_single_candidate_search(mq, dtype, rows, cols, pad, cands, f16):  # noqa: F811
+    w = _strided(rows, cols, pad, rows, dtype)
+    g = torch.Generator(device=DEV).manual_seed(rows)
+    for r in (slice(0, 40), slice(rows - 9, rows)):      # small integers: exact in the integer format
+        w[r] = torch.randint(-7, 8, w[r].shape, generator=g, device=DEV).to(dtype)
+        w[r, 5] = 7.0
+    check_tensor(mq, w, cands, orc.PER_CHANNEL, mi.clip_ratios(1), f16=f16, label="ahead-single")
