@@ -175,13 +175,25 @@ bool one_sweep_launch(const int32_t* cand, int n_cand) {
   return n_cand == 1 || (n_cand == 2 && paired(cand[0], cand[1]));
 }
 
-// Whether the search of these tensors (one launch) should write codes ahead (AheadCodes): it saves
-// the second read of the input and costs a launch of 2 us for the tallies plus the rows done twice, so
-// it pays from about 100 MB on (64 MB: even).
+// Whether the search of these tensors (one launch) should write codes ahead (AheadCodes).  One clip
+// ratio: it saves the second read of the input and costs a launch of 2 us for the tallies plus the
+// rows done twice, so it pays from about 100 MB on (64 MB: even).  Histogram search: from a few times
+// as many rows as are resident at once, so that most of them find a tally.
 constexpr int64_t kAheadBytes = int64_t{128} << 20;
-bool codes_ahead(const mofq_tensor_t* t, const int32_t* cand, int n_cand, const mofq_scale_cfg_t* cfg, int64_t launch_bytes) {
-  return cfg->gran == MOFQ_PER_CHANNEL && cfg->n_clip == 1 && one_sweep_launch(cand, n_cand) && launch_bytes >= kAheadBytes &&
-         t->cols < (int64_t{1} << 31);
+constexpr int64_t kAheadRows = 8192;
+bool codes_ahead(const mofq_tensor_t* t, const int32_t* cand, int n_cand, const mofq_scale_cfg_t* cfg, int64_t launch_bytes, int64_t launch_rows) {
+  if (cfg->gran != MOFQ_PER_CHANNEL || !one_sweep_launch(cand, n_cand)) return false;
+  if (cfg->n_clip == 1) return launch_bytes >= kAheadBytes && t->cols < (int64_t{1} << 31);
+  if (launch_rows < kAheadRows) return false;
+  SweepParams p{};
+  p.dtype = t->dtype;
+  p.cols = t->cols;
+  p.gran = cfg->gran;
+  p.n_clip = cfg->n_clip;
+  std::memcpy(p.clip, cfg->clip_ratios, sizeof(float) * cfg->n_clip);
+  p.n_fmt = n_cand;
+  for (int c = 0; c < n_cand; ++c) p.fmt[c] = cand[c];
+  return sweep_by_histogram(p);
 }
 int64_t tensor_bytes(const mofq_tensor_t* t) { return t->rows * t->cols * (t->dtype == MOFQ_F32 ? 4 : 2); }
 
@@ -791,7 +803,7 @@ int select_w_only(const mofq_tensor_t* w, const int32_t* candidates, int n_candi
     if ((rc = launch_tensor_select(p, st))) return rc;
     return ev1 && hipEventRecord(ev1, st) != hipSuccess ? MOFQ_ERR_HIP : MOFQ_OK;
   }
-  const bool ahead = codes_ahead(w, candidates, n_candidates, w_cfg, tensor_bytes(w));
+  const bool ahead = codes_ahead(w, candidates, n_candidates, w_cfg, tensor_bytes(w), w->rows);
   if (ahead && (rc = launch_clear(&s.tally, 1, st))) return rc;
   if ((rc = sweep_candidates(w, candidates, n_candidates, w_cfg, s, st, nullptr, ahead ? w_out->codes : nullptr))) return rc;
   if (ev1 && hipEventRecord(ev1, st) != hipSuccess) return MOFQ_ERR_HIP;
@@ -924,7 +936,8 @@ int mofq_quantize(const mofq_tensor_t* t, int32_t format, const mofq_scale_cfg_t
     p.tensor_err = tensor_err;
     return launch_tensor_quantize(p, st);
   }
-  const bool ahead = codes_ahead(t, &format, 1, cfg, tensor_bytes(t));
+  const bool ahead = codes_ahead(t, &format, 1, cfg, tensor_bytes(t), t->rows);
+  if (ahead && (rc = launch_clear(&w.tally, 1, st))) return rc;
   if ((rc = sweep_candidates(t, &format, 1, cfg, w, st, nullptr, ahead ? out->codes : nullptr))) return rc;
   EmitParams e{};
   if (tensor_err) {
@@ -1174,10 +1187,10 @@ int mofq_select_layers_timed(int32_t n_layers, const mofq_tensor_t* w, const int
     double* tally[kEmitBatch];
     int n_ahead = 0;
     for (int j = 0; j < nb; ++j) {
-      int64_t bytes = 0;   // of tensor j's launch
+      int64_t bytes = 0, rows = 0;   // of tensor j's launch
       for (int k = 0; k < nb; ++k)
-        if (first[k] == first[j]) bytes += tensor_bytes(&w[i0 + k]);
-      ahead[j] = codes_ahead(&w[i0 + j], candidates, n_candidates, w_cfg, bytes);
+        if (first[k] == first[j]) { bytes += tensor_bytes(&w[i0 + k]); rows += w[i0 + k].rows; }
+      ahead[j] = codes_ahead(&w[i0 + j], candidates, n_candidates, w_cfg, bytes, rows);
       if (ahead[j]) tally[n_ahead++] = slot[j].tally;
     }
     if (n_ahead && (rc = launch_clear(tally, n_ahead, st))) return join(rc);

@@ -95,6 +95,8 @@ int launch_sweep(const SweepParams& p, hipStream_t stream);
 // Sort-based search for per-channel 4-bit searches on 16-bit inputs; returns
 // MOFQ_ERR_UNSUPPORTED (nothing enqueued) outside that domain.
 int launch_sweep_sorted(const SweepParams& p, hipStream_t stream);
+// Whether that search takes the histogram kernel (which can write codes ahead).
+bool sweep_by_histogram(const SweepParams& p);
 // The same for up to kSweepGroupMax tensors of one row length, dtype and configuration in one
 // launch (MOFQ_ERR_UNSUPPORTED, nothing enqueued, if they differ or are outside the domain).
 constexpr int kSweepGroupMax = 8;

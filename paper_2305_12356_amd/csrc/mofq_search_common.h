@@ -5,7 +5,7 @@
 #include <cmath>
 #include <type_traits>
 
-#include "mofq_device.h"
+#include "mofq_codes.h"
 #include "mofq_internal.h"
 
 namespace mofq {
@@ -16,6 +16,7 @@ struct SortedTensor {
   const void* w;
   int64_t ld;
   UnitRecords rec;
+  AheadCodes ahead;   // histogram kernel only
 };
 struct SortedArgs {
   SortedTensor t[kSweepGroupMax];
@@ -28,6 +29,7 @@ struct SortedArgs {
   // for b = 0..6.  Entry 7 is INT4's extra boundary (|t| below it: a negative element stays on -7)
   // with the weights of the step from 7 to 8; unused (zero weights) for E2M1.
   float thr[2][8];
+  float thr_est[2][8];   // histogram kernel: a shade below thr (see threshold_pattern)
   double dgd[2][8];   // m_b - m_{b+1};  entry 7: 8 - 7
   int32_t dg2q[2][8]; // 4 (m_b^2 - m_{b+1}^2): an integer for every 4-bit format;  entry 7: 4 (64 - 49)
   float g_last[2];    // m_7
@@ -42,7 +44,6 @@ int launch_sweep_hist(const SweepParams& p, const SortedArgs& a, int64_t total_r
 
 namespace {
 
-typedef float f32x2 __attribute__((ext_vector_type(2)));
 typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
 
 // ---- sort keys ------------------------------------------------------------------------

@@ -1010,7 +1010,7 @@ int launch_sweep(const SweepParams& p, hipStream_t st) {
     a.emit_grid[1] = static_cast<uint16_t*>(p.emit_grid[1]);
   }
   if (p.ahead.codes) {
-    if (p.gran != MOFQ_PER_CHANNEL || p.n_clip != 1 || !p.ahead.tag || (p.n_fmt == 2 && !p.ahead.tally)) return MOFQ_ERR_UNSUPPORTED;
+    if (p.gran != MOFQ_PER_CHANNEL || p.n_clip != 1 || !p.ahead.tag || !p.ahead.tally) return MOFQ_ERR_UNSUPPORTED;
     a.ahead = p.ahead;
   }
   a.units = mofq_num_units(p.rows, p.cols, p.gran, p.group);

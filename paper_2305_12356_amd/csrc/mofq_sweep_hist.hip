@@ -10,8 +10,7 @@
 // counts the elements per pattern (16-bit counters, two per word, LDS adds), forms count and
 // magnitude-sum prefixes over groups of 8 patterns (a group shares its exponent, so its elements'
 // magnitudes are v0 + i ulp and its sum is v0 C + ulp sum i c_i, exact in fp64), finds H from
-// an fp32 estimate proven with two exact decisions (a pattern-space binary search where the
-// estimate is off), and reads count and sum up to H from the group
+// an fp32 estimate and one exact decision, and reads count and sum up to H from the group
 // prefix and one 16-byte read of the group's counters.  Only the patterns between the smallest
 // threshold and the row's largest magnitude get a counter: elements below every threshold sit on
 // level 0 for every candidate and drop out of both level sums.  How many patterns that is
@@ -19,8 +18,12 @@
 // sorting kernel where it would not fit.  INT4's negative elements beyond its extra boundary
 // are counted in a second, short histogram over the top of the range.
 //
+// Where the counted patterns span few enough binades, sums of magnitudes are 32-bit integers in units
+// of the first counted pattern's ulp (exact, and a third of the instructions of fp64 sums); else fp64.
+//
 // Filter, shortlist and exact fp64 re-score are those of the sorting kernel; the re-score reads
-// the row again.
+// the row again.  With AheadCodes the row's codes are written at the end, from a further read that
+// comes from L2.
 #include "mofq_search_common.h"
 
 namespace mofq {
@@ -32,17 +35,15 @@ MOFQ_DEV uint32_t dot2(uint32_t a, uint32_t b, uint32_t c) {   // a.lo b.lo + a.
   return __builtin_amdgcn_udot2(__builtin_bit_cast(u16x2, a), __builtin_bit_cast(u16x2, b), c, false);
 }
 
-MOFQ_DEV int med3i(int x, int lo, int hi) { return x < lo ? lo : (x > hi ? hi : x); }   // x clamped to [lo, hi]
-
-// bit pattern of x >= 0 rounded toward zero to the input type; largest finite pattern
+// bit pattern of x >= 0 rounded toward zero to the input type
 template <typename In> MOFQ_DEV uint32_t pattern_rtz(float x);
 template <> MOFQ_DEV uint32_t pattern_rtz<F16>(float x) {
-  return __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_pkrtz(x, 0.0f)) & 0xFFFFu;
+  return __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_pkrtz(x, 0.0f));   // the high half is +0
 }
 template <> MOFQ_DEV uint32_t pattern_rtz<BF16>(float x) { return f2u(x) >> 16; }
 template <typename In> struct Pattern;
-template <> struct Pattern<F16> { static constexpr int MAX_FINITE = 0x7BFF; };
-template <> struct Pattern<BF16> { static constexpr int MAX_FINITE = 0x7F7F; };
+template <> struct Pattern<F16> { static constexpr int MANT = 10; };
+template <> struct Pattern<BF16> { static constexpr int MANT = 7; };
 
 // Lexicographic minimum of (value, index) over the wave by data-parallel-primitive moves: the
 // smallest value (no NaN among the inputs), then the smallest index among the lanes that hold it.
@@ -65,128 +66,139 @@ MOFQ_DEV void wave_argmin_dpp(double& v, int& idx) {
 }
 
 
+// ---- prefixes -----------------------------------------------------------------------------
+// Exclusive prefix of count and magnitude sum per group of 8 counters, one record per group, the
+// totals in record ng.  A group's patterns share the exponent: pattern lo + 8 g + i has the magnitude
+// (m + i) << shift in units of the ulp of pattern lo (Narrow) or v0 + i ulp (Wide).
+struct Narrow {
+  using sum_t = uint32_t;
+  uint32_t sum, word;   // word: count (16 bits) | m (11) | shift (5)
+};
+struct Wide {
+  using sum_t = double;
+  double sum;
+  uint32_t cnt, unused;
+};
+
+// m and shift of the group at pattern p (subnormals: the first normal binade's ulp, no leading bit)
+template <typename In> MOFQ_DEV void mant_shift(uint32_t p, int e_lo, uint32_t& m, uint32_t& shift) {
+  constexpr int MANT = Pattern<In>::MANT;
+  const int e = static_cast<int>(p >> MANT);
+  m = (p & ((1u << MANT) - 1u)) | (static_cast<uint32_t>(e > 0 ? 1 : 0) << MANT);
+  shift = static_cast<uint32_t>((e > 1 ? e : 1) - e_lo);
+}
+template <typename In> MOFQ_DEV int exponent_of(int p) { const int e = p >> Pattern<In>::MANT; return e > 1 ? e : 1; }
+
+// count and index-weighted count of eight counters, two per word
+MOFQ_DEV void count8(const u32x4 w, uint32_t& c, uint32_t& wsum) {
+  c = 0;
+  wsum = 0;
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    c = dot2(w[j], 0x00010001u, c);
+    wsum = dot2(w[j], static_cast<uint32_t>(2 * j) | (static_cast<uint32_t>(2 * j + 1) << 16), wsum);
+  }
+}
+
 // Count and magnitude sum of the elements in the histogram's first n1 counters, 0 <= n1 <= nbin:
-// the exclusive prefixes of group n1 / 8 plus the first n1 % 8 counters of that group (n1 = nbin
-// reads the 16 bytes after the counters, which are inside the workgroup's LDS, and masks them all).
-// hist: counters, two per word; cntp / sump: exclusive prefixes per group of 8 counters;
+// the record of group n1 / 8 plus the first n1 % 8 counters of that group (n1 = nbin reads the 16
+// bytes after the counters, which are inside the workgroup's LDS, and masks them all).
 // keep[c]: masks of the first c of a group's eight counters (a table in LDS: one read instead of
 // sixteen compare-and-select instructions).
 template <typename In>
-MOFQ_DEV void hist_prefix(const uint32_t* hist, const uint16_t* cntp, const double* sump, const u32x4* keep, int lo,
-                          int n1, uint32_t& C, double& S) {
-  const int g = n1 >> 3;
-  const u32x4 w = *reinterpret_cast<const u32x4*>(hist + 4 * g);
+MOFQ_DEV void hist_prefix(const uint32_t* hist, const Narrow* rec, const u32x4* keep, int, uint32_t n1, uint32_t& C, uint32_t& S) {
+  const u32x4 w = *reinterpret_cast<const u32x4*>(hist + 4 * (n1 >> 3));
   const u32x4 m = keep[n1 & 7];   // 16-bit masks, two per word
-  uint32_t cin = 0, win = 0;
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const uint32_t v = w[i] & m[i];
-    cin = dot2(v, 0x00010001u, cin);
-    win = dot2(v, static_cast<uint32_t>(2 * i) | (static_cast<uint32_t>(2 * i + 1) << 16), win);
-  }
+  const Narrow r = rec[n1 >> 3];
+  uint32_t cin, win;
+  count8(w & m, cin, win);
+  S = r.sum + ((__umul24((r.word >> 16) & 0x7FFu, cin) + win) << (r.word >> 27));
+  C = (r.word & 0xFFFFu) + cin;
+}
+template <typename In>
+MOFQ_DEV void hist_prefix(const uint32_t* hist, const Wide* rec, const u32x4* keep, int lo, uint32_t n1, uint32_t& C, double& S) {
+  const int g = static_cast<int>(n1 >> 3);
+  const u32x4 w = *reinterpret_cast<const u32x4*>(hist + 4 * g);
+  const u32x4 m = keep[n1 & 7];
+  uint32_t cin, win;
+  count8(w & m, cin, win);
   const float v0 = bits_to_float<In>(static_cast<uint32_t>(lo + 8 * g));
   const float ulp = bits_to_float<In>(static_cast<uint32_t>(lo + 8 * g + 1)) - v0;   // exact
-  double s = sump[g];
+  double s = rec[g].sum;
   s = __builtin_fma(static_cast<double>(v0), static_cast<double>(cin), s);
-  s = __builtin_fma(static_cast<double>(ulp), static_cast<double>(win), s);
-  C = cntp[g] + cin;
-  S = s;
+  S = __builtin_fma(static_cast<double>(ulp), static_cast<double>(win), s);
+  C = rec[g].cnt + cin;
 }
 
-// Exclusive prefixes of count and magnitude sum per group of 8 bins; the totals in entry ng.
-// Thread t takes the groups [t gp, (t + 1) gp), gp <= GPMAX.  Called by all threads.
-template <typename In, int THREADS, int GPMAX>
-MOFQ_DEV void hist_group_prefixes(const uint32_t* hist, uint16_t* cntp, double* sump, int lo, int ng, int gp,
-                                  uint32_t* s_wc, double* s_ws) {
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  uint32_t c8[GPMAX];
-  double s8[GPMAX];
+// One group's own count and sum, and its record.
+template <typename In> MOFQ_DEV void group_sum(const Narrow*, u32x4 w, int lo, int g, uint32_t& c, uint32_t& s, uint32_t& aux) {
+  uint32_t wsum, m, shift;
+  count8(w, c, wsum);
+  mant_shift<In>(static_cast<uint32_t>(lo + 8 * g), exponent_of<In>(lo), m, shift);
+  s = (__umul24(m, c) + wsum) << shift;
+  aux = (m << 16) | (shift << 27);
+}
+template <typename In> MOFQ_DEV void group_sum(const Wide*, u32x4 w, int lo, int g, uint32_t& c, double& s, uint32_t& aux) {
+  uint32_t wsum;
+  count8(w, c, wsum);
+  const float v0 = bits_to_float<In>(static_cast<uint32_t>(lo + 8 * g));
+  const float ulp = bits_to_float<In>(static_cast<uint32_t>(lo + 8 * g + 1)) - v0;
+  s = __builtin_fma(static_cast<double>(ulp), static_cast<double>(wsum), static_cast<double>(v0) * static_cast<double>(c));
+  aux = 0;
+}
+MOFQ_DEV Narrow make_record(const Narrow*, uint32_t c, uint32_t s, uint32_t aux) { return Narrow{s, c | aux}; }
+MOFQ_DEV Wide make_record(const Wide*, uint32_t c, double s, uint32_t) { return Wide{s, c, 0}; }
+MOFQ_DEV uint32_t record_count(const Narrow& r) { return r.word & 0xFFFFu; }
+MOFQ_DEV uint32_t record_count(const Wide& r) { return r.cnt; }
+MOFQ_DEV uint32_t wave_excl_scan(uint32_t v, uint32_t& total) { return wave_excl_scan_u32(v, total); }
+MOFQ_DEV double wave_excl_scan(double v, double& total) { return wave_excl_scan_f64(v, total); }
+
+// The records of all groups: lane `id` of `lanes` takes the groups [id gp, (id + 1) gp), gp <= GPMAX.
+// NW > 1: by all threads of the workgroup (three barriers); NW = 1: by one wave alone, without
+// barriers, for a short histogram: the caller's next barrier publishes the result.
+template <typename In, int NW, int GPMAX, typename Rec>
+MOFQ_DEV void hist_records(const uint32_t* hist, Rec* rec, int lo, int ng, uint32_t* s_wc, typename Rec::sum_t* s_ws) {
+  using sum_t = typename Rec::sum_t;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int id = NW > 1 ? tid : lane;
+  const int gp = (ng + NW * 64 - 1) / (NW * 64);
+  uint32_t c8[GPMAX], aux[GPMAX];
+  sum_t s8[GPMAX];
   uint32_t ct = 0;
-  double st = 0.0;
+  sum_t st = 0;
 #pragma unroll
   for (int i = 0; i < GPMAX; ++i) {
-    const int g = tid * gp + i;
+    const int g = id * gp + i;
     c8[i] = 0;
-    s8[i] = 0.0;
+    s8[i] = 0;
+    aux[i] = 0;
     if (i < gp && g < ng) {
-      const u32x4 w = *reinterpret_cast<const u32x4*>(hist + 4 * g);
-      uint32_t c = 0, wsum = 0;
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        c = dot2(w[j], 0x00010001u, c);
-        wsum = dot2(w[j], static_cast<uint32_t>(2 * j) | (static_cast<uint32_t>(2 * j + 1) << 16), wsum);
-      }
-      const float v0 = bits_to_float<In>(static_cast<uint32_t>(lo + 8 * g));
-      const float ulp = bits_to_float<In>(static_cast<uint32_t>(lo + 8 * g + 1)) - v0;
-      c8[i] = c;
-      s8[i] = __builtin_fma(static_cast<double>(ulp), static_cast<double>(wsum), static_cast<double>(v0) * static_cast<double>(c));
-      ct += c;
+      group_sum<In>(rec, *reinterpret_cast<const u32x4*>(hist + 4 * g), lo, g, c8[i], s8[i], aux[i]);
+      ct += c8[i];
       st += s8[i];
     }
   }
   uint32_t wct;
-  double wst;
-  uint32_t cb = wave_excl_scan_u32(ct, wct);
-  double sb = wave_excl_scan_f64(st, wst);
-  if (lane == 0) { s_wc[wave] = wct; s_ws[wave] = wst; }
-  __syncthreads();
-  for (int w = 0; w < wave; ++w) { cb += s_wc[w]; sb += s_ws[w]; }
+  sum_t wst;
+  uint32_t cb = wave_excl_scan(ct, wct);
+  sum_t sb = wave_excl_scan(st, wst);
+  if constexpr (NW > 1) {
+    if (lane == 0) { s_wc[wave] = wct; s_ws[wave] = wst; }
+    __syncthreads();
+    for (int w = 0; w < wave; ++w) { cb += s_wc[w]; sb += s_ws[w]; }
+  }
 #pragma unroll
   for (int i = 0; i < GPMAX; ++i) {
-    const int g = tid * gp + i;
-    if (i < gp && g < ng) { cntp[g] = static_cast<uint16_t>(cb); sump[g] = sb; }
+    const int g = id * gp + i;
+    if (i < gp && g < ng) rec[g] = make_record(rec, cb, sb, aux[i]);
     cb += c8[i];
     sb += s8[i];
   }
-  if (tid == THREADS - 1) { cntp[ng] = static_cast<uint16_t>(cb); sump[ng] = sb; }
-  __syncthreads();
+  if (id == NW * 64 - 1) rec[ng] = make_record(rec, cb, sb, 0);
+  if constexpr (NW > 1) __syncthreads();
 }
 
-// The same for a short histogram (at most 64 * GPMAX groups) by one wave alone, without barriers:
-// lane l takes the groups [l gp, (l + 1) gp).  The caller's next barrier publishes the result.
-template <typename In, int GPMAX>
-MOFQ_DEV void hist_group_prefixes_wave(const uint32_t* hist, uint16_t* cntp, double* sump, int lo, int ng, int gp) {
-  const int lane = threadIdx.x & 63;
-  uint32_t c8[GPMAX];
-  double s8[GPMAX];
-  uint32_t ct = 0;
-  double st = 0.0;
-#pragma unroll
-  for (int i = 0; i < GPMAX; ++i) {
-    const int g = lane * gp + i;
-    c8[i] = 0;
-    s8[i] = 0.0;
-    if (i < gp && g < ng) {
-      const u32x4 w = *reinterpret_cast<const u32x4*>(hist + 4 * g);
-      uint32_t c = 0, wsum = 0;
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        c = dot2(w[j], 0x00010001u, c);
-        wsum = dot2(w[j], static_cast<uint32_t>(2 * j) | (static_cast<uint32_t>(2 * j + 1) << 16), wsum);
-      }
-      const float v0 = bits_to_float<In>(static_cast<uint32_t>(lo + 8 * g));
-      const float ulp = bits_to_float<In>(static_cast<uint32_t>(lo + 8 * g + 1)) - v0;
-      c8[i] = c;
-      s8[i] = __builtin_fma(static_cast<double>(ulp), static_cast<double>(wsum), static_cast<double>(v0) * static_cast<double>(c));
-      ct += c;
-      st += s8[i];
-    }
-  }
-  uint32_t wct;
-  double wst;
-  uint32_t cb = wave_excl_scan_u32(ct, wct);
-  double sb = wave_excl_scan_f64(st, wst);
-#pragma unroll
-  for (int i = 0; i < GPMAX; ++i) {
-    const int g = lane * gp + i;
-    if (i < gp && g < ng) { cntp[g] = static_cast<uint16_t>(cb); sump[g] = sb; }
-    cb += c8[i];
-    sb += s8[i];
-  }
-  if (lane == 63) { cntp[ng] = static_cast<uint16_t>(cb); sump[ng] = sb; }
-}
-
-template <typename In, int FA, int FB, int CH>
+template <typename In, int FA, int FB, int CH, typename Rec>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(CH <= 2 ? 5 : (CH <= 6 ? 4 : 3))))
 void sweep_hist_kernel(const SortedArgs a) {
   using L = Load8<In>;
@@ -200,29 +212,31 @@ void sweep_hist_kernel(const SortedArgs a) {
   constexpr bool ANY_TAIL = TAIL_A || TAIL_B;
   constexpr int GPMAX = kHistMaxBins / 8 / THREADS;   // groups per thread at most
 
-  // dynamic LDS: [sump | tsump | hist | thist | cntp | tcntp]
+  using sum_t = typename Rec::sum_t;
+
+  // dynamic LDS: [records | the short histogram's | counters | the short histogram's | 16 bytes]
   extern __shared__ __attribute__((aligned(16))) unsigned char s_dyn[];
   const int nbin = a.nbin, ntbin = ANY_TAIL ? a.ntbin : 0;   // multiples of 8
   const int ng = nbin >> 3, ntg = ntbin >> 3;
-  double* const sump = reinterpret_cast<double*>(s_dyn);
-  double* const tsump = sump + (ng + 1);
-  uint32_t* const hist = reinterpret_cast<uint32_t*>(s_dyn + (((ng + 1) + (ntg + 1)) * 8 + 15) / 16 * 16);
-  uint32_t* const thist = hist + (nbin >> 1);
-  uint16_t* const cntp = reinterpret_cast<uint16_t*>(thist + (ntbin >> 1));   // counts stay below 2^16: a row has at most 24576 elements
-  uint16_t* const tcntp = cntp + (ng + 1);
+  Rec* const rec = reinterpret_cast<Rec*>(s_dyn);
+  Rec* const trec = rec + (ng + 1);
+  uint32_t* const hist = reinterpret_cast<uint32_t*>(s_dyn + (static_cast<size_t>((ng + 1) + (ntg + 1)) * sizeof(Rec) + 15) / 16 * 16);
+  uint32_t* const thist = hist + (nbin >> 1);   // (counts stay below 2^16: a row has at most 24576 elements)
 
   __shared__ float s_scale[NF][MOFQ_MAX_CLIP];
   __shared__ double s_fast[NF][MOFQ_MAX_CLIP];
   __shared__ float s_wmax[NW];
   __shared__ double s_wsum[1][NW];
   __shared__ uint32_t s_wc[NW];
-  __shared__ double s_ws[NW];
+  __shared__ sum_t s_ws[NW];
   __shared__ double s_thr[NF];
   __shared__ int s_direct[NF];   // the winning candidate where no element-wise pass is needed, else -1
   __shared__ uint8_t s_list[MAXL];   // format * MOFQ_MAX_CLIP + candidate
   __shared__ int s_nlist;
   __shared__ double s_p2[NW];
-  // re-scored errors of the shortlist: over the sum prefixes, which are no longer needed by then
+  __shared__ double s_best[NF], s_tally;
+  __shared__ float s_bscale[NF];
+  // re-scored errors of the shortlist: over the records, which are no longer needed by then
   // (the host sizes the dynamic LDS for it)
   double* const s_val = reinterpret_cast<double*>(s_dyn);
   __shared__ __attribute__((aligned(16))) uint32_t s_keep[8][4];
@@ -243,6 +257,11 @@ void sweep_hist_kernel(const SortedArgs a) {
     s_keep[c][i] = (c >= 2 * i + 2) ? 0xFFFFFFFFu : ((c == 2 * i + 1) ? 0x0000FFFFu : 0u);
   }
   const u32x4* const keep = reinterpret_cast<const u32x4*>(&s_keep[0][0]);
+
+  // what the tensor's finished rows favour: read early, by one thread (waves that read it at different
+  // times could disagree)
+  double tally = 0.0;
+  if (NF == 2 && T.ahead.codes && tid == 0) tally = tally_read(T.ahead);
 
   // ---- load the row (it stays in registers until it is counted): absmax, energy; clear the counters ---
   u32x4 rawv[CH];
@@ -336,12 +355,12 @@ void sweep_hist_kernel(const SortedArgs a) {
         if (b2[1] >= 0) count(hist_at, hi16(b2));
         if constexpr (ANY_TAIL) {
           const i16x2 t2 = h2 - tlo2;
-          // halves that are negative elements at or above the short histogram's first pattern
-          const uint32_t q2 = sign_fill2(w) & ~sign_fill2(__builtin_bit_cast(uint32_t, t2));
+          // negative elements at or above the short histogram's first pattern
+          const uint32_t q2 = w & ~__builtin_bit_cast(uint32_t, t2) & 0x80008000u;
           if (q2 != 0) {
             const i16x2 tc2 = __builtin_elementwise_min(t2, tlast2);
-            if (q2 & 0xFFFFu) count(thist_at, lo16(tc2));
-            if (q2 >> 16) count(thist_at, hi16(tc2));
+            if (q2 & 0x8000u) count(thist_at, lo16(tc2));
+            if (q2 >> 31) count(thist_at, hi16(tc2));
           }
         }
       }
@@ -352,13 +371,16 @@ void sweep_hist_kernel(const SortedArgs a) {
   // ---- group prefixes ----------------------------------------------------------------------------
   // (the short histogram by the last wave alone, before the barriers of the long one's prefixes)
   if constexpr (ANY_TAIL)
-    if (wave == NW - 1) hist_group_prefixes_wave<In, kHistMaxTailBins / 8 / 64>(thist, tcntp, tsump, tlo, ntg, (ntg + 63) / 64);
-  hist_group_prefixes<In, THREADS, GPMAX>(hist, cntp, sump, lo, ng, (ng + THREADS - 1) / THREADS, s_wc, s_ws);
-  const uint32_t c_total = cntp[ng];
-  const double s_total = sump[ng];
+    if (wave == NW - 1) hist_records<In, 1, kHistMaxTailBins / 8 / 64>(thist, trec, tlo, ntg, s_wc, s_ws);
+  hist_records<In, NW, GPMAX>(hist, rec, lo, ng, s_wc, s_ws);
+  const uint32_t c_total = record_count(rec[ng]);
+  // sums are in units of this (1 where they are fp64 magnitudes)
+  const float v_lo = bits_to_float<In>(static_cast<uint32_t>(lo));
+  const double sum_unit = std::is_same<Rec, Narrow>::value ? static_cast<double>(bits_to_float<In>(static_cast<uint32_t>(lo) + 1) - v_lo) : 1.0;
+  const double s_total = static_cast<double>(rec[ng].sum);
   // sum |x| enters the rounding bounds only: the counted elements' sum (raised beyond its rounding)
   // plus, for every other element, the magnitude of the first counted pattern, which exceeds its own
-  const double l1 = s_total * (1.0 + 0x1p-40) + static_cast<double>(n) * static_cast<double>(bits_to_float<In>(static_cast<uint32_t>(lo)));
+  const double l1 = sum_unit * s_total * (1.0 + 0x1p-40) + static_cast<double>(n) * static_cast<double>(v_lo);
 
   // ---- level boundaries of every candidate: one lane per candidate, one wave per (format, 64
   // candidates) --------------------------------------------------------------------------------
@@ -368,24 +390,15 @@ void sweep_hist_kernel(const SortedArgs a) {
       constexpr bool TAIL = decltype(tail_tag)::value;
       const float s = s_scale[f][k < K ? k : K - 1];
       const float inv = 1.0f / s;
-      // H = the largest finite pattern h with fl32(v(h) * inv) <= thr.  v(0) = 0 passes.
-      auto threshold_pattern = [&](const float thr) {
-        auto pass = [&](int h) { return scaled<In>(static_cast<uint32_t>(h), inv) <= thr; };
-        // estimate: the pattern of thr * s rounded toward zero, which is H unless a pattern's
-        // value lies in the gap of a few fp32 steps between that product and the real boundary
-        int H = static_cast<int>(pattern_rtz<In>(thr * s));
-        H = H > Pattern<In>::MAX_FINITE - 1 ? Pattern<In>::MAX_FINITE - 1 : H;
-        const bool at = pass(H), above = pass(H + 1);   // both always: a short circuit costs more than it saves
-        if (!(static_cast<int>(at) & static_cast<int>(!above))) {   // (also: no finite pattern fails)
-          int lo_h = 0, hi_h = Pattern<In>::MAX_FINITE;   // pass(lo_h) holds; the answer is in [lo_h, hi_h]
-          while (lo_h < hi_h) {
-            const int mid = (lo_h + hi_h + 1) >> 1;
-            if (pass(mid)) lo_h = mid;
-            else hi_h = mid - 1;
-          }
-          H = lo_h;
-        }
-        return H;
+      // H = the largest finite pattern h with fl32(v(h) * inv) <= thr.  inv and the product are each off
+      // by at most 2^-24, so the decision flips between thr s (1 - 2^-22) and thr s (1 + 2^-22); thr_est is
+      // thr (1 - 2^-21) (to 2^-24), so the pattern of thr_est s rounded toward zero passes, and the
+      // second pattern above it, at least 2^-11 larger, does not: one decision, on the first, tells.
+      // Returns H - first + 1.
+      auto counters_below = [&](const int f_, const int q, const int first) {
+        const int est = static_cast<int>(pattern_rtz<In>(a.thr_est[f_][q] * s));
+        const bool above = scaled<In>(static_cast<uint32_t>(est + 1), inv) <= a.thr[f_][q];
+        return est + (1 - first) + (above ? 1 : 0);
       };
       double ca = 0.0;
       int cb4 = 0;       // 4 sum_b (count up to boundary b) (m_b^2 - m_{b+1}^2): an integer below 2^31
@@ -396,28 +409,33 @@ void sweep_hist_kernel(const SortedArgs a) {
       // one boundary at a time (a rolled loop: unrolled, the eight of them cost some 80 registers)
 #pragma unroll 1
       for (int q = 0; q < 7; ++q) {
-        const int n1 = threshold_pattern(a.thr[f][q]) - lo + 1;
+        const int n1 = counters_below(f, q, lo);
         least = n1 < least ? n1 : least;
         uint32_t C;
-        double S;
-        hist_prefix<In>(hist, cntp, sump, keep, lo, med3i(n1, 0, nbin), C, S);
-        ca = __builtin_fma(S, a.dgd[f][q], ca);
+        sum_t S;
+        hist_prefix<In>(hist, rec, keep, lo, static_cast<uint32_t>(min(max(n1, 0), nbin)), C, S);
+        ca = __builtin_fma(static_cast<double>(S), a.dgd[f][q], ca);
         cb4 = __mul24(static_cast<int>(C), a.dg2q[f][q]) + cb4;
       }
+      double ca_tail = 0.0;
       if constexpr (TAIL) {
         // negative elements with a pattern above H: the short histogram's totals less its prefix
-        const int n1 = threshold_pattern(a.thr[f][7]) - tlo + 1;
+        const int n1 = counters_below(f, 7, tlo);
         least = n1 < least ? n1 : least;
         uint32_t C;
-        double S;
-        hist_prefix<In>(thist, tcntp, tsump, keep, tlo, med3i(n1, 0, ntbin), C, S);
-        ca = __builtin_fma(tsump[ntg] - S, a.dgd[f][7], ca);
-        cb4 = __mul24(static_cast<int>(tcntp[ntg] - C), a.dg2q[f][7]) + cb4;
+        sum_t S;
+        hist_prefix<In>(thist, trec, keep, tlo, static_cast<uint32_t>(min(max(n1, 0), ntbin)), C, S);
+        ca_tail = static_cast<double>(trec[ntg].sum - S) * a.dgd[f][7];
+        if constexpr (std::is_same<Rec, Narrow>::value) {
+          const float v_tlo = bits_to_float<In>(static_cast<uint32_t>(tlo));
+          ca_tail *= static_cast<double>(bits_to_float<In>(static_cast<uint32_t>(tlo) + 1) - v_tlo);
+        }
+        cb4 = __mul24(static_cast<int>(record_count(trec[ntg]) - C), a.dg2q[f][7]) + cb4;
       }
       const bool bad = least < 0;
       if (k < K) {
         const double gl = static_cast<double>(a.g_last[f]);
-        const double A = ca + gl * s_total;
+        const double A = __builtin_fma(sum_unit, ca + gl * s_total, ca_tail);
         const double B = 0.25 * static_cast<double>(cb4) + gl * gl * static_cast<double>(c_total);
         const double sc = static_cast<double>(s);
         const double v = (en - 2.0 * sc * A) + sc * sc * B;   // filtered error
@@ -435,10 +453,12 @@ void sweep_hist_kernel(const SortedArgs a) {
   __syncthreads();
 
   // ---- shortlist.  The rounding bound of the filtered error is the sorting kernel's with the depth
-  // of this kernel's summation trees: a group's sum is exact (products and sum of fewer than 2^27
-  // units of one ulp), a group prefix adds at most GPMAX of them in a thread, 6 levels of the wave
-  // scan and the waves before, and a look-up adds two exact products: fewer than D = 16 roundings,
-  // each of at most u sum|x|, whatever the row's length.
+  // of this kernel's summation trees.  Integer sums are exact, and so is A (an integer below 2^53 in
+  // units of an ulp, but for the addition of the tail): D = 1.  fp64 sums: a group's sum is exact
+  // (products and sum of fewer than 2^27 units of one ulp), a group prefix adds at most GPMAX of them
+  // in a thread, 6 levels of the wave scan and the waves before, and a look-up adds two exact products:
+  // fewer than D = 16 roundings, each of at most u sum|x|, whatever the row's length.
+  constexpr double D = std::is_same<Rec, Narrow>::value ? 1.0 : 16.0;
   for (int f = wave; f < NF; f += NW) {
     double m = __builtin_inf();
     int km = 0;
@@ -460,7 +480,7 @@ void sweep_hist_kernel(const SortedArgs a) {
       cnt += __builtin_popcountll(__ballot(k < K && !(s_fast[f][k < K ? k : 0] > thr)));
     }
     static_assert(GPMAX + 6 + NW + 2 <= 16, "depth of the prefix sums");
-    const double beta = 0x1p-53 * (40.0 * 16 * 2.0 * sm * l1 + (E + 32) * en + 8.0 * sm * sm * gm * gm * nd);
+    const double beta = 0x1p-53 * (40.0 * D * 2.0 * sm * l1 + (E + 32) * en + 8.0 * sm * sm * gm * gm * nd);
     const bool direct = cnt == 1 && beta <= 0x1p-34 * m;   // false for a zero or non-finite error
     if (lane == 0) { s_thr[f] = thr; s_direct[f] = direct ? km : -1; }
   }
@@ -525,22 +545,56 @@ void sweep_hist_kernel(const SortedArgs a) {
     T.rec.clip[f][row] = bk;
     T.rec.err[f][row] = best;
     if (f == 0 && T.rec.energy) T.rec.energy[row] = en;
+    s_best[f] = best;
+    s_bscale[f] = s_scale[f][bk];
+    if (f == 0) s_tally = tally;
   }
+  if (!T.ahead.codes) return;   // uniform
+
+  // ---- the row's codes, in the format that the tensor's rows favour so far ------------------------
+  Raw8<In> codes_in[CH];
+#pragma unroll
+  for (int j = 0; j < CH; ++j) {
+    const int c = j * THREADS + tid;
+    codes_in[j].load(src, 0, static_cast<uint32_t>(c * 8 < n ? c : 0) * 8);
+  }
+  __syncthreads();
+  int slot = 0;
+  if constexpr (NF == 2) {
+    const double d = s_best[0] - s_best[1];
+    slot = __builtin_amdgcn_readfirstlane(s_tally + d > 0.0 ? 1 : 0);
+    if (tid == 0 && tally_adds()) tally_add(T.ahead, d);
+  }
+  if (tid == 0) T.ahead.tag[row] = static_cast<uint8_t>(T.ahead.cand_of[slot]);
+  const float inv = 1.0f / s_bscale[slot];
+  uint32_t* const out = static_cast<uint32_t*>(T.ahead.codes) + row * (a.cols / 8);
+  auto emit = [&](auto fmt_c) {
+#pragma unroll
+    for (int j = 0; j < CH; ++j) {
+      const int c = j * THREADS + tid;
+      float v[8];
+      codes_in[j].widen(v);
+      uint32_t words[2];
+      encode8<decltype(fmt_c)::value>(v, inv, words);
+      if (c * 8 < n) out[c] = words[0];
+    }
+  };
+  if (slot == 0) emit(std::integral_constant<int, FA>{});
+  else emit(std::integral_constant<int, FBX>{});
 }
 
-// The histogram kernel: dynamic LDS for [sum prefixes | counters | count prefixes (16 bits)] of both
-// histograms; the shortlist's re-scored values lie over its start later.
-template <typename In, int FA, int FB>
+// Dynamic LDS: the records and counters of both histograms; the shortlist's re-scored values lie
+// over their start later.
+template <typename In, int FA, int FB, typename Rec>
 int launch_hist_shape(const SortedArgs& a, int64_t total_rows, hipStream_t st) {
   const dim3 grid(static_cast<unsigned>(total_rows));
   const int64_t chunks = a.cols / 8;
   const int ng = a.nbin / 8, ntg = a.ntbin / 8;
-  const size_t lds = std::max<size_t>((static_cast<size_t>((ng + 1) + (ntg + 1)) * 8 + 15) / 16 * 16 + 2 * static_cast<size_t>(a.nbin + a.ntbin) +
-                                          2 * static_cast<size_t>((ng + 1) + (ntg + 1)),
+  const size_t lds = std::max<size_t>((static_cast<size_t>((ng + 1) + (ntg + 1)) * sizeof(Rec) + 15) / 16 * 16 + 2 * static_cast<size_t>(a.nbin + a.ntbin) + 16,
                                       2 * MOFQ_MAX_CLIP * sizeof(double));   // at least the shortlist's values
 #define MOFQ_HIST(CH)                                                                         \
   if (chunks <= 256 * (CH)) {                                                                  \
-    hipLaunchKernelGGL((sweep_hist_kernel<In, FA, FB, CH>), grid, dim3(256), lds, st, a);       \
+    hipLaunchKernelGGL((sweep_hist_kernel<In, FA, FB, CH, Rec>), grid, dim3(256), lds, st, a);  \
     return hip_status(hipGetLastError());                                                      \
   }
   MOFQ_HIST(1)   //  2048 columns
@@ -552,6 +606,16 @@ int launch_hist_shape(const SortedArgs& a, int64_t total_rows, hipStream_t st) {
   return MOFQ_ERR_UNSUPPORTED;
 }
 
+// 32-bit sums where they cannot overflow: the counted patterns reach at most `span` binades above
+// the first one's, so a magnitude is below 2^(MANT + 1 + span) units.
+template <typename In, int FA, int FB>
+int launch_hist_sums(const SortedArgs& a, int64_t total_rows, hipStream_t st) {
+  constexpr int ppb = 1 << Pattern<In>::MANT;
+  const int span = (std::max(a.nbin, a.ntbin) + ppb - 1) / ppb;
+  const bool narrow = span <= 16 && (a.cols << (Pattern<In>::MANT + 1 + span)) < (int64_t{1} << 32);
+  return narrow ? launch_hist_shape<In, FA, FB, Narrow>(a, total_rows, st) : launch_hist_shape<In, FA, FB, Wide>(a, total_rows, st);
+}
+
 }  // namespace
 
 int launch_sweep_hist(const SweepParams& p, const SortedArgs& a, int64_t total_rows, hipStream_t st) {
@@ -559,11 +623,11 @@ int launch_sweep_hist(const SweepParams& p, const SortedArgs& a, int64_t total_r
   const int fa = p.fmt[0], fb = p.n_fmt == 2 ? p.fmt[1] : -1;
   const bool h = p.dtype == MOFQ_F16;
   if (fa == MOFQ_INT4 && fb == MOFQ_FP4_E2M1)
-    return h ? launch_hist_shape<F16, MOFQ_INT4, MOFQ_FP4_E2M1>(a, total_rows, st) : launch_hist_shape<BF16, MOFQ_INT4, MOFQ_FP4_E2M1>(a, total_rows, st);
+    return h ? launch_hist_sums<F16, MOFQ_INT4, MOFQ_FP4_E2M1>(a, total_rows, st) : launch_hist_sums<BF16, MOFQ_INT4, MOFQ_FP4_E2M1>(a, total_rows, st);
   if (fa == MOFQ_INT4 && fb == -1)
-    return h ? launch_hist_shape<F16, MOFQ_INT4, -1>(a, total_rows, st) : launch_hist_shape<BF16, MOFQ_INT4, -1>(a, total_rows, st);
+    return h ? launch_hist_sums<F16, MOFQ_INT4, -1>(a, total_rows, st) : launch_hist_sums<BF16, MOFQ_INT4, -1>(a, total_rows, st);
   if (fa == MOFQ_FP4_E2M1 && fb == -1)
-    return h ? launch_hist_shape<F16, MOFQ_FP4_E2M1, -1>(a, total_rows, st) : launch_hist_shape<BF16, MOFQ_FP4_E2M1, -1>(a, total_rows, st);
+    return h ? launch_hist_sums<F16, MOFQ_FP4_E2M1, -1>(a, total_rows, st) : launch_hist_sums<BF16, MOFQ_FP4_E2M1, -1>(a, total_rows, st);
   return MOFQ_ERR_UNSUPPORTED;
 }
 

@@ -620,12 +620,14 @@ void fill_levels(int fmt, SortedArgs& a, int slot) {
     // tie goes up  -> magnitude <= m_b needs t <  mid -> t <= the float just below mid
     // tie goes down-> magnitude <= m_b needs t <= mid
     a.thr[slot][b] = up_is_even[b] ? std::nextafterf(mid, -INFINITY) : mid;
+    a.thr_est[slot][b] = static_cast<float>(a.thr[slot][b] * (1.0 - 0x1p-21));
     a.dgd[slot][b] = m[b] - m[b + 1];
     a.dg2q[slot][b] = static_cast<int32_t>(4.0 * (m[b] * m[b] - m[b + 1] * m[b + 1]));   // exact
   }
   if (int4) {
     // a negative element stays on -7 while t < 7.5 (the tie goes to the even 8); beyond, it lands on -8
     a.thr[slot][7] = std::nextafterf(7.5f, -INFINITY);
+    a.thr_est[slot][7] = static_cast<float>(a.thr[slot][7] * (1.0 - 0x1p-21));
     a.dgd[slot][7] = m[8] - m[7];
     a.dg2q[slot][7] = static_cast<int32_t>(4.0 * (m[8] * m[8] - m[7] * m[7]));
   }
@@ -698,17 +700,34 @@ void hist_sizes(const SweepParams& p, SortedArgs& a) {
 
 }  // namespace
 
+namespace {
+
+// Whether the configuration of one tensor is in the domain of these kernels.
+bool in_domain(const SweepParams& p) {
+  if (p.gran != MOFQ_PER_CHANNEL || (p.dtype != MOFQ_F16 && p.dtype != MOFQ_BF16)) return false;
+  if (p.n_clip < 8 || p.cols < 1024 || p.cols > 24576) return false;
+  for (int f = 0; f < p.n_fmt; ++f)
+    if (p.fmt[f] != MOFQ_INT4 && p.fmt[f] != MOFQ_FP4_E2M1) return false;
+  return true;
+}
+
+}  // namespace
+
+bool sweep_by_histogram(const SweepParams& p) {
+  if (!in_domain(p)) return false;
+  SortedArgs a{};
+  for (int f = 0; f < p.n_fmt; ++f) fill_levels(p.fmt[f], a, f);
+  hist_sizes(p, a);
+  return a.nbin > 0;
+}
+
 // Returns MOFQ_ERR_UNSUPPORTED when the configuration is outside this kernel's domain
 // (the caller then uses the direct kernel) or the tensors do not share row length, dtype and
 // configuration; nothing has been enqueued in that case.
 int launch_sweep_sorted_group(const SweepParams* ps, int n, hipStream_t st) {
   if (!ps || n < 1 || n > kSweepGroupMax) return MOFQ_ERR_UNSUPPORTED;
   const SweepParams& p = ps[0];
-  if (p.gran != MOFQ_PER_CHANNEL) return MOFQ_ERR_UNSUPPORTED;
-  if (p.dtype != MOFQ_F16 && p.dtype != MOFQ_BF16) return MOFQ_ERR_UNSUPPORTED;
-  if (p.n_clip < 8 || p.cols < 1024 || p.cols > 24576) return MOFQ_ERR_UNSUPPORTED;
-  for (int f = 0; f < p.n_fmt; ++f)
-    if (p.fmt[f] != MOFQ_INT4 && p.fmt[f] != MOFQ_FP4_E2M1) return MOFQ_ERR_UNSUPPORTED;
+  if (!in_domain(p)) return MOFQ_ERR_UNSUPPORTED;
   int64_t total_rows = 0;
   for (int i = 0; i < n; ++i) {
     if (ps[i].rows < 1) return MOFQ_ERR_UNSUPPORTED;
@@ -718,7 +737,8 @@ int launch_sweep_sorted_group(const SweepParams* ps, int n, hipStream_t st) {
   for (int i = 1; i < n; ++i) {
     const SweepParams& q = ps[i];
     if (q.gran != p.gran || q.dtype != p.dtype || q.cols != p.cols ||
-        q.scale_f16 != p.scale_f16 || q.n_clip != p.n_clip || q.n_fmt != p.n_fmt)
+        q.scale_f16 != p.scale_f16 || q.n_clip != p.n_clip || q.n_fmt != p.n_fmt ||
+        (q.ahead.codes != nullptr) != (p.ahead.codes != nullptr))
       return MOFQ_ERR_UNSUPPORTED;
     for (int f = 0; f < p.n_fmt; ++f)
       if (q.fmt[f] != p.fmt[f]) return MOFQ_ERR_UNSUPPORTED;
@@ -733,6 +753,7 @@ int launch_sweep_sorted_group(const SweepParams* ps, int n, hipStream_t st) {
     a.t[i].w = ps[i].w;
     a.t[i].ld = ps[i].ld;
     a.t[i].rec = ps[i].rec;
+    a.t[i].ahead = ps[i].ahead;
     a.row0[i] = row0;
     row0 += static_cast<uint32_t>(ps[i].rows);
   }
@@ -742,6 +763,7 @@ int launch_sweep_sorted_group(const SweepParams* ps, int n, hipStream_t st) {
   for (int k = 0; k < p.n_clip; ++k) a.clip[k] = p.clip[k];
   for (int f = 0; f < p.n_fmt; ++f) fill_levels(p.fmt[f], a, f);
   hist_sizes(p, a);
+  if (p.ahead.codes && (a.nbin <= 0 || !p.ahead.tag || !p.ahead.tally)) return MOFQ_ERR_UNSUPPORTED;
   return p.dtype == MOFQ_F16 ? launch_fmt<F16>(p, a, total_rows, st) : launch_fmt<BF16>(p, a, total_rows, st);
 }
 
