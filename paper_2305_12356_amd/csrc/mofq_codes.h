@@ -111,13 +111,21 @@ MOFQ_DEV void encode8(const float (&v)[8], float inv_s, uint32_t (&words)[2]) {
   }
 }
 
-// What the finished rows of a tensor favour (AheadCodes).  Workgroup ids go round the XCDs; workgroup
-// scope keeps the addition in the XCD's own L2.  Stale or missed values only cost a row done twice.
-MOFQ_DEV double* tally_of(const AheadCodes& a) { return a.tally + (blockIdx.x % kTallies) * kTallyStride; }
-MOFQ_DEV double tally_read(const AheadCodes& a) { return __hip_atomic_load(tally_of(a), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP); }
-// one row in 16 is enough to tell
-MOFQ_DEV bool tally_adds() { return (blockIdx.x / kTallies) % 16 == 0; }
-MOFQ_DEV void tally_add(const AheadCodes& a, double d) { __hip_atomic_fetch_add(tally_of(a), d, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP); }
+// What the finished rows of a tensor favour (AheadCodes): read by one wave (a lane per place; the sum
+// is over the wave), added to by one thread of one row in EVERY.  Workgroup ids go round the XCDs;
+// workgroup scope keeps both in the XCD's own L2.  Stale or missed values only cost a row done twice.
+MOFQ_DEV double tally_read(const AheadCodes& a) {
+  const int lane = threadIdx.x & 63;
+  const double* const t = a.tally + ((blockIdx.x % kXcds) * kTalliesPerXcd + lane) * kTallyStride;
+  return lane < kTalliesPerXcd ? __hip_atomic_load(t, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) : 0.0;
+}
+// (loads queue behind the additions: the shorter a row's work, the fewer of them)
+template <unsigned EVERY> MOFQ_DEV void tally_add(const AheadCodes& a, double d) {
+  const unsigned n = blockIdx.x / kXcds;   // this row's number in its XCD
+  if (n / kTalliesPerXcd % EVERY == 0)
+    __hip_atomic_fetch_add(a.tally + ((blockIdx.x % kXcds) * kTalliesPerXcd + n % kTalliesPerXcd) * kTallyStride, d, __ATOMIC_RELAXED,
+                           __HIP_MEMORY_SCOPE_WORKGROUP);
+}
 
 // 8 elements as they come from memory, widened where they are used
 template <typename In> struct Raw8 {

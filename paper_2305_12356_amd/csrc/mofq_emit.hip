@@ -465,7 +465,7 @@ struct ClearArgs {
   double* p[kEmitBatch];
   int32_t n;
 };
-__global__ __launch_bounds__(kTallies * kTallyStride) void clear_kernel(const ClearArgs a) {   // a workgroup per tally
+__global__ __launch_bounds__(kTallies * kTallyStride) void clear_kernel(const ClearArgs a) {   // a workgroup per tensor
   a.p[blockIdx.x][threadIdx.x] = 0.0;
 }
 

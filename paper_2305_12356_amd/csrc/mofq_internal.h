@@ -26,16 +26,18 @@ struct UnitRecords {
 // that the tensor is read once; rows whose format turns out not to be the tensor's choice are
 // emitted again afterwards (launch_fixup).  What is favoured is a sum over finished rows that
 // workgroups read and add to as they come: it decides how many rows are done twice, never the result.
-// There is one sum per XCD, so that adding stays inside its L2 (an addition to one place of the whole
-// device takes some 70 ns and they queue up: 16384 rows took 1.4 ms instead of 0.25).
+// Every XCD has sums of its own, kTalliesPerXcd of them, so that the traffic stays inside its L2: an
+// addition to one place takes some 70 ns and they queue up, and device-wide ones also slow the loads
+// (16384 rows: 1.4 ms with one place for the device, 0.30 with 16 such places, 0.25 without).
 struct AheadCodes {
   void* codes;              // nullptr: not asked for
   uint8_t* tag;             // [rows]: candidate whose codes the row holds
-  double* tally;            // [kTallies * kTallyStride]: sums of (error in slot 0 - error in slot 1); zero before the launch
+  double* tally;            // [kTallies][kTallyStride]: sums of (error in slot 0 - error in slot 1); zero before the launch
   int32_t cand_of[kMaxFmt]; // launch slot -> candidate index
 };
 
-constexpr int kTallies = 8, kTallyStride = 16;   // one per XCD, 128 bytes apart
+constexpr int kXcds = 8, kTalliesPerXcd = 4, kTallies = kXcds * kTalliesPerXcd;
+constexpr int kTallyStride = 16;   // 128 bytes apart
 
 struct SweepParams {
   const void* w;

@@ -299,10 +299,6 @@ __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(GRID ? 
   const int lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int64_t row = blockIdx.x;
-  // read at the start, so that its latency is hidden (it may miss the rows of the last microseconds), and
-  // by one thread: waves that read it at different times could disagree
-  double tally = 0.0;
-  if (NF == 2 && a.ahead.codes && tid == 0) tally = tally_read(a.ahead);
 
   const int cpr = static_cast<int>(a.cols / 8);
   Raw8<In> raw[CH];   // chunk j: the row's chunk j * THREADS + tid; zeros past the row's end add nothing
@@ -312,6 +308,10 @@ __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(GRID ? 
     raw[j].load(a.w, row * a.ld, static_cast<uint32_t>(c < cpr ? c : 0) * 8);
     if (c >= cpr) raw[j].clear();
   }
+  // read early, so that its latency is hidden (it may miss the rows of the last microseconds), but behind
+  // the row (loads return in order), and by one wave: waves that read it at different times could disagree
+  double tally = 0.0;
+  if (NF == 2 && a.ahead.codes && wave == 0) tally = tally_read(a.ahead);
   float amax = 0.0f;
   double en = 0.0;
 #pragma unroll
@@ -380,7 +380,10 @@ __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(GRID ? 
   accA = wave_sum(accA);
   if constexpr (NF == 2) accB = wave_sum(accB);
   if (lane == 0) { s_acc[0][wave] = accA; s_acc[1][wave] = accB; }
-  if (tid == 0) s_tally = tally;
+  if (NF == 2 && a.ahead.codes && wave == 0) {
+    tally = wave_sum(tally);
+    if (lane == 0) s_tally = tally;
+  }
   __syncthreads();
   if (tid < NF) {
     double t = 0.0;
@@ -398,7 +401,7 @@ __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(GRID ? 
 #pragma unroll
       for (int w = 0; w < NW; ++w) d += s_acc[0][w] - s_acc[1][w];
       slot = __builtin_amdgcn_readfirstlane(s_tally + d > 0.0 ? 1 : 0);
-      if (tid == 0 && tally_adds()) tally_add(a.ahead, d);
+      if (tid == 0) tally_add<16>(a.ahead, d);
     }
     if (tid == 0) a.ahead.tag[row] = static_cast<uint8_t>(a.ahead.cand_of[slot]);
     auto codes = [&](auto fmt_c, float inv) {

@@ -258,11 +258,6 @@ void sweep_hist_kernel(const SortedArgs a) {
   }
   const u32x4* const keep = reinterpret_cast<const u32x4*>(&s_keep[0][0]);
 
-  // what the tensor's finished rows favour: read early, by one thread (waves that read it at different
-  // times could disagree)
-  double tally = 0.0;
-  if (NF == 2 && T.ahead.codes && tid == 0) tally = tally_read(T.ahead);
-
   // ---- load the row (it stays in registers until it is counted): absmax, energy; clear the counters ---
   u32x4 rawv[CH];
   float amax = 0.0f;
@@ -275,6 +270,10 @@ void sweep_hist_kernel(const SortedArgs a) {
     if (c0 < a.cols) raw = *reinterpret_cast<const u32x4*>(src + c0);
     rawv[j] = raw;
   }
+  // what the tensor's finished rows favour: behind the row (loads return in order), by one wave (waves that
+  // read it at different times could disagree)
+  double tally = 0.0;
+  if (NF == 2 && T.ahead.codes && wave == NW - 1) tally = tally_read(T.ahead);
   {
     const u32x4 zero = {0u, 0u, 0u, 0u};
     for (int i = tid; i < ng + ntg; i += THREADS) reinterpret_cast<u32x4*>(hist)[i] = zero;   // hist and thist are adjacent
@@ -547,9 +546,12 @@ void sweep_hist_kernel(const SortedArgs a) {
     if (f == 0 && T.rec.energy) T.rec.energy[row] = en;
     s_best[f] = best;
     s_bscale[f] = s_scale[f][bk];
-    if (f == 0) s_tally = tally;
   }
   if (!T.ahead.codes) return;   // uniform
+  if (NF == 2 && wave == NW - 1) {
+    tally = wave_sum(tally);
+    if (lane == 0) s_tally = tally;
+  }
 
   // ---- the row's codes, in the format that the tensor's rows favour so far ------------------------
   Raw8<In> codes_in[CH];
@@ -563,7 +565,7 @@ void sweep_hist_kernel(const SortedArgs a) {
   if constexpr (NF == 2) {
     const double d = s_best[0] - s_best[1];
     slot = __builtin_amdgcn_readfirstlane(s_tally + d > 0.0 ? 1 : 0);
-    if (tid == 0 && tally_adds()) tally_add(T.ahead, d);
+    if (tid == 0) tally_add<4>(T.ahead, d);
   }
   if (tid == 0) T.ahead.tag[row] = static_cast<uint8_t>(T.ahead.cand_of[slot]);
   const float inv = 1.0f / s_bscale[slot];
