@@ -1,6 +1,6 @@
-// Shared by the two per-channel searches that do not score every (element, candidate) pair
-// (mofq_sweep_sorted.hip: sort the row and search it; mofq_sweep_hist.hip: count the row's bit
-// patterns): their kernel arguments and the device helpers both use.
+// Shared by the per-channel searches that do not score every (element, candidate) pair
+// (mofq_sweep_sorted.hip: sort the row and search it; mofq_sweep_hist.hip and mofq_sweep_bf16.hip: count the
+// row's bit patterns): their kernel arguments and the device helpers they use.
 #pragma once
 #include <cmath>
 #include <type_traits>
@@ -16,7 +16,7 @@ struct SortedTensor {
   const void* w;
   int64_t ld;
   UnitRecords rec;
-  AheadCodes ahead;   // histogram kernel only
+  AheadCodes ahead;   // histogram kernels only
 };
 struct SortedArgs {
   SortedTensor t[kSweepGroupMax];
@@ -41,6 +41,9 @@ constexpr int kHistMaxTailBins = 2048;  // of INT4's negative elements
 
 // The histogram kernel for arguments with nbin > 0 (mofq_sweep_hist.hip).
 int launch_sweep_hist(const SweepParams& p, const SortedArgs& a, int64_t total_rows, hipStream_t st);
+// The one of bf16 rows (mofq_sweep_bf16.hip), and whether these histograms fit it.
+int launch_sweep_bf16(const SweepParams& p, const SortedArgs& a, int64_t total_rows, hipStream_t st);
+bool bf16_search_fits(const SweepParams& p, int nbin, int ntbin);
 
 namespace {
 
@@ -133,6 +136,237 @@ template <int FMT> MOFQ_DEV void rescore2(double& acc, float x0, float x1, float
   const double d1 = __builtin_fma(-static_cast<double>(g[1]), sd, static_cast<double>(x1));
   acc = __builtin_fma(d0, d0, acc);
   acc = __builtin_fma(d1, d1, acc);
+}
+
+
+// bit pattern of x >= 0 rounded toward zero to the input type
+template <typename In> MOFQ_DEV uint32_t pattern_rtz(float x);
+template <> MOFQ_DEV uint32_t pattern_rtz<F16>(float x) {
+  return __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_pkrtz(x, 0.0f));   // the high half is +0
+}
+template <> MOFQ_DEV uint32_t pattern_rtz<BF16>(float x) { return f2u(x) >> 16; }
+template <typename In> struct Pattern;
+template <> struct Pattern<F16> { static constexpr int MANT = 10; };
+template <> struct Pattern<BF16> { static constexpr int MANT = 7; };
+
+// Lexicographic minimum of (value, index) over the wave by data-parallel-primitive moves: the
+// smallest value (no NaN among the inputs), then the smallest index among the lanes that hold it.
+template <int CTRL> MOFQ_DEV int dpp_i32(int x) { return __builtin_amdgcn_update_dpp(0, x, CTRL, 0xF, 0xF, true); }
+MOFQ_DEV void wave_argmin_dpp(double& v, int& idx) {
+  double m = v;
+  m = __builtin_fmin(m, dpp_f64<DPP_QUAD_XOR1>(m));
+  m = __builtin_fmin(m, dpp_f64<DPP_QUAD_XOR2>(m));
+  m = __builtin_fmin(m, dpp_f64<DPP_ROW_HALF_MIRROR>(m));
+  m = __builtin_fmin(m, dpp_f64<DPP_ROW_MIRROR>(m));
+  m = __builtin_fmin(__builtin_fmin(readlane_f64(m, 0), readlane_f64(m, 16)), __builtin_fmin(readlane_f64(m, 32), readlane_f64(m, 48)));
+  int c = (v == m) ? idx : 0x7FFFFFFF;
+  c = min(c, dpp_i32<DPP_QUAD_XOR1>(c));
+  c = min(c, dpp_i32<DPP_QUAD_XOR2>(c));
+  c = min(c, dpp_i32<DPP_ROW_HALF_MIRROR>(c));
+  c = min(c, dpp_i32<DPP_ROW_MIRROR>(c));
+  idx = min(min(__builtin_amdgcn_readlane(c, 0), __builtin_amdgcn_readlane(c, 16)),
+            min(__builtin_amdgcn_readlane(c, 32), __builtin_amdgcn_readlane(c, 48)));
+  v = m;
+}
+
+
+// m and shift of the group at pattern p (subnormals: the first normal binade's ulp, no leading bit)
+template <typename In> MOFQ_DEV void mant_shift(uint32_t p, int e_lo, uint32_t& m, uint32_t& shift) {
+  constexpr int MANT = Pattern<In>::MANT;
+  const int e = static_cast<int>(p >> MANT);
+  m = (p & ((1u << MANT) - 1u)) | (static_cast<uint32_t>(e > 0 ? 1 : 0) << MANT);
+  shift = static_cast<uint32_t>((e > 1 ? e : 1) - e_lo);
+}
+template <typename In> MOFQ_DEV int exponent_of(int p) { const int e = p >> Pattern<In>::MANT; return e > 1 ? e : 1; }
+
+
+// ---- what follows the filtered errors of a row: shortlist, exact re-score, the winners -----------------
+// Shared memory of these steps (the filtered errors are the caller's to fill).
+template <int NF, int NW> struct RowSearch {
+  float scale[NF][MOFQ_MAX_CLIP];
+  double fast[NF][MOFQ_MAX_CLIP];       // filtered errors; NaN: has to be scored exactly
+  double thr[NF], p2[NW], best[NF], tally;
+  float best_scale[NF];
+  int direct[NF];                       // the winning candidate where no element-wise pass is needed, else -1
+  int nlist;
+  uint8_t list[NF * MOFQ_MAX_CLIP];     // format * MOFQ_MAX_CLIP + candidate
+};
+
+// Shortlist margin and rounding bound of the filtered error v = (en - 2 s A) + s^2 B.
+// EXACT_SUMS: A and B are exact but for one addition.  The error of a candidate is at most the energy (0 is a
+// grid value, and clipping moves an element towards itself), so s^2 B <= (|x| + |x - s g|)^2 <= 4 en and
+// 2 s A <= 5 en; en itself comes from a summation tree of depth E + 14, and six operations round on terms
+// of at most 6 en: |v - exact| <= u (E + 48) en =: beta.  The margin 2^-40 en is far above 2 beta.
+// Otherwise prefix sums are off by up to D u sum|x| (fewer than D roundings each): the bound is the sorting
+// kernel's.
+struct FilterBounds {
+  double margin, beta;
+};
+// 8-bit formats: B is exact (an integer below 2^51 in units of the smallest level's square), A takes fewer than
+// 24 roundings on terms of at most 512 sum|x|.
+template <int E, bool EXACT_SUMS, int BITS>
+MOFQ_DEV FilterBounds filter_bounds(double en, double l1, double smax, double gmax, double n) {
+  if constexpr (EXACT_SUMS && BITS == 8) {
+    const double beta = 0x1p-53 * ((E + 48) * en + 48.0 * 512.0 * smax * l1);
+    return {__builtin_fmax(0x1p-40 * en, 4.0 * beta), beta};
+  } else if constexpr (EXACT_SUMS) {
+    return {0x1p-40 * en, 0x1p-53 * (E + 48) * en};
+  } else {
+    constexpr double D = 16.0;
+    const double mag = en + 2.0 * smax * gmax * l1 + smax * smax * gmax * gmax * n;
+    return {0x1p-33 * mag, 0x1p-53 * (40.0 * D * 2.0 * smax * l1 + (E + 32) * en + 8.0 * smax * smax * gmax * gmax * n)};
+  }
+}
+
+// From the filtered errors (published by a barrier) to the winner of each format: rec of the row, and
+// sh.best / sh.best_scale (for the caller to publish).  The row at src is read again where the filter cannot
+// separate the candidates; s_val: MOFQ_MAX_CLIP doubles per format of LDS that is free by then.
+template <typename In, int FA, int FB, int THREADS, int CH, bool EXACT_SUMS>
+MOFQ_DEV void finish_row(RowSearch<(FB >= 0 ? 2 : 1), THREADS / 64>& sh, double* s_val, const uint16_t* src, int n, int K, double en, double l1,
+                         const float (&g_absmax)[2], const UnitRecords& rec, int64_t row) {
+  constexpr int NF = (FB >= 0) ? 2 : 1, FBX = (FB >= 0) ? FB : FA, NW = THREADS / 64, E = CH * 8;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  for (int f = wave; f < NF; f += NW) {
+    double m = __builtin_inf();
+    int km = 0;
+    float smax = 0.0f;
+    for (int k = lane; k < K; k += 64) {
+      const double v = sh.fast[f][k];
+      if (v < m) { m = v; km = k; }
+      smax = __builtin_fmaxf(smax, sh.scale[f][k]);
+    }
+    wave_argmin_dpp(m, km);
+    if constexpr (!EXACT_SUMS || Codec<FA>::BITS == 8) smax = wave_max(smax);
+    const FilterBounds fb = filter_bounds<E, EXACT_SUMS, Codec<FA>::BITS>(en, l1, static_cast<double>(smax), static_cast<double>(g_absmax[f]), static_cast<double>(n));
+    const double thr = m + fb.margin;   // more than twice the bound: both values carry the error
+    int cnt = 0;
+    for (int k0 = 0; k0 < K; k0 += 64) {
+      const int k = k0 + lane;
+      cnt += __builtin_popcountll(__ballot(k < K && !(sh.fast[f][k < K ? k : 0] > thr)));
+    }
+    // a format whose shortlist is one candidate with a provably accurate error is done; false for a zero or
+    // non-finite error
+    const bool direct = cnt == 1 && fb.beta <= 0x1p-34 * m;
+    if (lane == 0) { sh.thr[f] = thr; sh.direct[f] = direct ? km : -1; }
+  }
+  if (tid == 0) sh.nlist = 0;
+  __syncthreads();
+#pragma unroll
+  for (int f = 0; f < NF; ++f)
+    if (sh.direct[f] < 0)   // uniform
+      for (int k = tid; k < K; k += THREADS)
+        if (!(sh.fast[f][k] > sh.thr[f])) sh.list[atomicAdd(&sh.nlist, 1)] = static_cast<uint8_t>(f * MOFQ_MAX_CLIP + k);   // any order
+  __syncthreads();
+  const int n_list = sh.nlist;
+
+  // exact fp64 re-score of the shortlist, element by element
+  uint32_t carry = 0;
+  for (int e = 0; e < n_list; ++e) {
+    const int fk = sh.list[e];
+    const int f = __builtin_amdgcn_readfirstlane(fk / MOFQ_MAX_CLIP);
+    const int k = __builtin_amdgcn_readfirstlane(fk % MOFQ_MAX_CLIP);
+    const float s = sh.scale[f][k], inv = 1.0f / s;
+    const double sd = static_cast<double>(s);
+    double acc = 0.0;
+    auto score = [&](auto fmt_c) {
+#pragma unroll
+      for (int j = 0; j < CH; ++j) {
+        const int c = (j * THREADS + tid) * 8;
+        Raw8<In> raw;
+        raw.clear();                   // padding is zero and scores zero
+        if (c < n) raw.load(src, 0, static_cast<uint32_t>(c));
+        float v[8];
+        raw.widen(v);
+#pragma unroll
+        for (int i = 0; i < 8; i += 2) score2_f64<decltype(fmt_c)::value>(acc, v[i], v[i + 1], inv, sd, carry);
+      }
+    };
+    if (f == 0) score(std::integral_constant<int, FA>{});
+    else score(std::integral_constant<int, FBX>{});
+    acc = wave_sum(acc);
+    if (lane == 0) sh.p2[wave] = acc;
+    __syncthreads();
+    if (tid == 0) {
+      double t = sh.p2[0];
+#pragma unroll
+      for (int w = 1; w < NW; ++w) t += sh.p2[w];
+      s_val[e] = t;
+    }
+    __syncthreads();
+  }
+
+  if (tid < NF) {
+    const int f = tid;
+    double best = __builtin_inf();
+    int bk = sh.direct[f];
+    if (bk >= 0) best = sh.fast[f][bk];
+    for (int e = 0; e < n_list; ++e) {   // smallest error, then smallest index: the first smallest
+      const int fk = sh.list[e];
+      if (fk / MOFQ_MAX_CLIP != f) continue;
+      const int k = fk % MOFQ_MAX_CLIP;
+      if (s_val[e] < best || (s_val[e] == best && k < bk)) { best = s_val[e]; bk = k; }
+    }
+    if (bk < 0) { bk = 0; best = __builtin_nan(""); }   // only on non-finite input
+    rec.scale[f][row] = sh.scale[f][bk];
+    rec.clip[f][row] = bk;
+    rec.err[f][row] = best;
+    if (f == 0 && rec.energy) rec.energy[row] = en;
+    sh.best[f] = best;
+    sh.best_scale[f] = sh.scale[f][bk];
+  }
+}
+
+// The row's codes (AheadCodes) after finish_row, in the format that the tensor's rows favour so far.
+// `tally`: what tally_read gave the last wave.
+template <typename In, int FA, int FB, int THREADS, int CH>
+MOFQ_DEV void emit_row_ahead(RowSearch<(FB >= 0 ? 2 : 1), THREADS / 64>& sh, const AheadCodes& ahead, double tally, const uint16_t* src, int n, int64_t row) {
+  constexpr int NF = (FB >= 0) ? 2 : 1, FBX = (FB >= 0) ? FB : FA, NW = THREADS / 64;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  if (NF == 2 && wave == NW - 1) {
+    tally = wave_sum(tally);
+    if (lane == 0) sh.tally = tally;
+  }
+  Raw8<In> raw[CH];
+#pragma unroll
+  for (int j = 0; j < CH; ++j) {
+    const int c = (j * THREADS + tid) * 8;
+    raw[j].load(src, 0, static_cast<uint32_t>(c < n ? c : 0));
+  }
+  __syncthreads();
+  int slot = 0;
+  if constexpr (NF == 2) {
+    const double d = sh.best[0] - sh.best[1];
+    slot = __builtin_amdgcn_readfirstlane(sh.tally + d > 0.0 ? 1 : 0);
+    if (tid == 0) tally_add<4>(ahead, d);
+  }
+  if (tid == 0) ahead.tag[row] = static_cast<uint8_t>(ahead.cand_of[slot]);
+  const float inv = 1.0f / sh.best_scale[slot];
+  const int64_t row_chunks = row * (n / 8);
+  auto emit = [&](auto fmt_c) {
+    constexpr int FMT = decltype(fmt_c)::value;
+#pragma unroll
+    for (int j = 0; j < CH; ++j) {
+      const int c = j * THREADS + tid;
+      float v[8];
+      raw[j].widen(v);
+      uint32_t words[2];
+      encode8<FMT>(v, inv, words);
+      if (c * 8 < n) {
+        if constexpr (Codec<FMT>::BITS == 4) {
+          (static_cast<uint32_t*>(ahead.codes) + row_chunks)[c] = words[0];
+        } else {
+          u32x2 o;
+          o[0] = words[0];
+          o[1] = words[1];
+          (static_cast<u32x2*>(ahead.codes) + row_chunks)[c] = o;
+        }
+      }
+    }
+  };
+  if (slot == 0) emit(std::integral_constant<int, FA>{});
+  else emit(std::integral_constant<int, FBX>{});
 }
 
 }  // namespace

@@ -1,0 +1,446 @@
+// Per-channel scale search on bf16 rows, 4-bit and 8-bit formats: the histogram search of
+// mofq_sweep_hist.hip with a prefix for every bit pattern.  A bf16 magnitude has 128 patterns per
+// binade, so the patterns between the smallest threshold of any candidate and the row's largest magnitude
+// are few (about 760 for INT4 / E2M1 over ratios in [0.5, 1], about 2600 for E4M3, whose
+// subnormals reach 20 binades down) and the count and the sum of magnitudes of the elements below
+// each of them fit in LDS, packed into 64 bits: count << 48 | sum in units of the first counted
+// pattern's ulp.  Both are exact.  A look-up (candidate, level boundary) is then one threshold decision, one
+// 8-byte read and four integer operations, 13 vector instructions in all against 38 of the group
+// records, which makes the 127 boundaries of an 8-bit format cheap: scoring every (element, candidate)
+// pair takes 4.8 instructions per element, candidate and format (240 000 per wave lane for a row of
+// 5000 elements and 50 candidates; here 3300 look-up instructions and about 800 for the histogram
+// serve all 50).  Bound by vector issue.
+// Measured, layer selection: INT8 against E4M3, 3001 x 5000, 50 ratios 277 -> 67 us (this kernel 56); 4096 x
+// 11008, 100 ratios 1315 -> 133 us; INT4 against E2M1, 1237 x 5000, 100 ratios: 28.2 -> 26.0 us.
+//
+// INT8's levels are spaced evenly; E4M3's evenly inside runs of 8 codes (a binade; the subnormals are the
+// first run): per run the level sums are d sum_i S_i and d^2 sum_i (2 (base + i) + 1) C_i with d the run's
+// spacing.  Boundaries beyond the largest level count everything (threshold infinity) and cancel against the
+// last level's weight.
+#include "mofq_search_common.h"
+
+namespace mofq {
+
+namespace {
+
+constexpr int kThreads = 256, kNW = kThreads / 64;
+constexpr int kMaxBins = 4096, kMaxTailBins = 1024;
+constexpr int kRuns = 16;   // runs of 8 boundaries of an 8-bit format
+
+typedef __attribute__((address_space(3))) uint32_t lds_u32;
+
+// Decision thresholds of the 8-bit formats' boundaries: level magnitude m_b or below <=> t <= thr; est: a
+// shade below (counters_below).  Run r, boundary i between code 8 r + i and the next; ties to the even code.
+struct Boundary {
+  float est, thr;
+};
+struct BoundaryTable {
+  Boundary b[kRuns][8];
+};
+constexpr double kInfinity = __builtin_inf();
+constexpr float prev_float(float x) { return __builtin_bit_cast(float, __builtin_bit_cast(uint32_t, x) - 1u); }   // x > 0
+constexpr Boundary boundary(double mid, bool up_is_even) {
+  const float m = static_cast<float>(mid);   // exact
+  const float thr = up_is_even ? prev_float(m) : m;
+  return Boundary{static_cast<float>(thr * (1.0 - 0x1p-21)), thr};
+}
+constexpr Boundary kBeyond{static_cast<float>(kInfinity), static_cast<float>(kInfinity)};
+constexpr BoundaryTable int8_table() {
+  BoundaryTable t{};
+  for (int r = 0; r < kRuns; ++r)
+    for (int i = 0; i < 8; ++i) {
+      const int b = 8 * r + i;
+      t.b[r][i] = b < 127 ? boundary(b + 0.5, b % 2 == 1) : kBeyond;
+    }
+  return t;
+}
+constexpr double e4m3_mag(int c) {
+  double m = c < 8 ? c : 8 + (c & 7);
+  for (int e = c < 8 ? 0 : (c >> 3) - 1; e < 9; ++e) m *= 0.5;
+  for (int e = 9; e < (c < 8 ? 0 : (c >> 3) - 1); ++e) m *= 2.0;
+  return m;
+}
+constexpr BoundaryTable e4m3_table() {
+  BoundaryTable t{};
+  for (int r = 0; r < kRuns; ++r)
+    for (int i = 0; i < 8; ++i) {
+      const int c = 8 * r + i;
+      t.b[r][i] = c < 126 ? boundary(0.5 * (e4m3_mag(c) + e4m3_mag(c + 1)), c % 2 == 1) : kBeyond;
+    }
+  return t;
+}
+static_assert(e4m3_mag(126) == 448.0 && e4m3_mag(8) == 0x1p-6 && e4m3_mag(1) == 0x1p-9 && e4m3_mag(127) == 480.0, "E4M3 magnitudes");
+__device__ const BoundaryTable kInt8Boundaries = int8_table();
+__device__ const BoundaryTable kE4m3Boundaries = e4m3_table();
+
+template <int FMT> struct Runs;
+template <> struct Runs<MOFQ_INT8> {
+  static constexpr double LAST = 128.0;   // the level after the last run
+  MOFQ_DEV static const BoundaryTable& table() { return kInt8Boundaries; }
+  MOFQ_DEV static double spacing(int) { return 1.0; }
+  MOFQ_DEV static int base(int r) { return 8 * r; }
+};
+template <> struct Runs<MOFQ_FP8_E4M3> {
+  static constexpr double LAST = 512.0;
+  MOFQ_DEV static const BoundaryTable& table() { return kE4m3Boundaries; }
+  MOFQ_DEV static double spacing(int r) { return __builtin_bit_cast(double, static_cast<uint64_t>(1023 - 9 + (r > 0 ? r - 1 : 0)) << 52); }   // 2^(max(r, 1) - 10)
+  MOFQ_DEV static int base(int r) { return r > 0 ? 8 : 0; }
+};
+
+// One counter (16 bits, two per word) of the byte offset 2 b more, b = counter number in the low bits of `b16`.
+MOFQ_DEV void count_at(uint32_t base, uint32_t byte_off, uint32_t parity16) {
+  // 1 or 65536: the shift takes the low five bits of its operand, which is 16 times the counter number
+  __hip_atomic_fetch_add((lds_u32*)static_cast<uintptr_t>(base + byte_off), 1u << (parity16 & 31u), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+}
+
+// Counters of both halves of a word of counter numbers (negative halves: none).
+MOFQ_DEV void count_pair(uint32_t base, i16x2 b2) {
+  const uint32_t off2 = __builtin_bit_cast(uint32_t, b2 << static_cast<short>(1));
+  const uint32_t par2 = __builtin_bit_cast(uint32_t, b2 << static_cast<short>(4));
+  if (b2[0] >= 0) count_at(base, off2 & 0xFFFCu, par2);
+  if (__builtin_bit_cast(int, b2) >= 0) count_at(base, (off2 >> 16) & 0xFFFCu, par2 >> 16);
+}
+
+// Exclusive prefixes over the counters in place of P[0 .. nbin], packed count << 48 | sum.  Thread `id` of
+// NW waves takes the counters [id pp, (id + 1) pp), pp even.  NW > 1: by the whole workgroup, with barriers.
+template <int NW>
+MOFQ_DEV void packed_prefixes(const uint32_t* counters, uint64_t* P, int lo, int nbin, uint64_t* s_wave) {
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int id = NW > 1 ? tid : lane;
+  const int pw = (nbin / 2 + NW * 64 - 1) / (NW * 64);   // words per thread
+  const int e_lo = exponent_of<BF16>(lo);
+  const int w0 = id * pw, w1 = (w0 + pw < nbin / 2) ? w0 + pw : nbin / 2;
+  uint64_t acc = 0;
+  for (int w = w0; w < w1; ++w) {
+    const uint32_t c2 = counters[w];
+    uint32_t m, shift;
+    mant_shift<BF16>(static_cast<uint32_t>(lo + 2 * w), e_lo, m, shift);   // lo is even: both patterns share the exponent
+    P[2 * w] = acc;
+    acc += static_cast<uint64_t>(m << shift) * (c2 & 0xFFFFu) + (static_cast<uint64_t>(c2 & 0xFFFFu) << 48);
+    P[2 * w + 1] = acc;
+    acc += static_cast<uint64_t>((m + 1) << shift) * (c2 >> 16) + (static_cast<uint64_t>(c2 >> 16) << 48);
+  }
+  // exclusive scan over the threads (sums of the two fields do not meet: the sum stays below 2^48)
+  uint64_t inc = acc;
+#pragma unroll
+  for (int d = 1; d < 64; d <<= 1) {
+    const uint64_t o = __shfl_up(inc, d, 64);
+    if (lane >= d) inc += o;
+  }
+  uint64_t base = inc - acc;
+  if constexpr (NW > 1) {
+    if (lane == 63) s_wave[wave] = inc;
+    __syncthreads();
+    for (int w = 0; w < wave; ++w) base += s_wave[w];
+  }
+  for (int w = w0; w < w1; ++w) {
+    P[2 * w] += base;
+    P[2 * w + 1] += base;
+  }
+  if (id == NW * 64 - 1) P[nbin] = base + acc;
+  if constexpr (NW > 1) __syncthreads();
+}
+
+MOFQ_DEV double sum_of(uint64_t p) {   // the low 48 bits
+  return __builtin_fma(static_cast<double>(static_cast<uint32_t>(p >> 32) & 0xFFFFu), 0x1p32, static_cast<double>(static_cast<uint32_t>(p)));
+}
+MOFQ_DEV uint32_t count_of(uint64_t p) { return static_cast<uint32_t>(p >> 48); }
+
+template <int FA, int FB, int CH>
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(CH <= 6 ? 5 : 4)))
+void sweep_bf16_kernel(const SortedArgs a) {
+  constexpr int NF = (FB >= 0) ? 2 : 1;
+  constexpr int FBX = (FB >= 0) ? FB : FA;
+  constexpr bool TAIL_A = Codec<FA>::IS_INT, TAIL_B = (FB >= 0) && Codec<FBX>::IS_INT;   // the level one beyond the positive ones
+  constexpr bool ANY_TAIL = TAIL_A || TAIL_B;
+  constexpr bool EIGHT = Codec<FA>::BITS == 8;
+
+  // dynamic LDS: [counters | of the negative elements | prefixes | of the negative elements]
+  extern __shared__ __attribute__((aligned(16))) unsigned char s_dyn[];
+  const int nbin = a.nbin, ntbin = ANY_TAIL ? a.ntbin : 0;   // multiples of 8
+  uint32_t* const counters = reinterpret_cast<uint32_t*>(s_dyn);
+  uint32_t* const tcounters = counters + nbin / 2;
+  uint64_t* const P = reinterpret_cast<uint64_t*>(tcounters + ntbin / 2);
+  uint64_t* const TP = P + (nbin + 1);
+
+  __shared__ RowSearch<NF, kNW> sh;
+  __shared__ float s_wmax[kNW];
+  __shared__ double s_wsum[kNW];
+  __shared__ uint64_t s_wave[kNW];
+
+  const int tid = threadIdx.x;
+  const int lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  uint32_t tensor = 0;                                                    // wave-uniform
+#pragma unroll
+  for (int i = 1; i < kSweepGroupMax; ++i) tensor += (blockIdx.x >= a.row0[i]);
+  const int64_t row = blockIdx.x - a.row0[tensor];
+  const SortedTensor& T = a.t[tensor];
+  const uint16_t* src = static_cast<const uint16_t*>(T.w) + row * T.ld;
+  const int K = a.n_clip;
+  const int n = static_cast<int>(a.cols);
+
+  // ---- load the row, clear the counters; largest magnitude and energy ------------------------------
+  Raw8<BF16> raw[CH];
+#pragma unroll
+  for (int j = 0; j < CH; ++j) {
+    const int c = (j * kThreads + tid) * 8;
+    raw[j].load(src, 0, static_cast<uint32_t>(c < n ? c : 0));
+    if (c >= n) raw[j].clear();
+  }
+  // what the tensor's finished rows favour: behind the row (loads return in order), by one wave (waves that
+  // read it at different times could disagree)
+  double tally = 0.0;
+  if (NF == 2 && T.ahead.codes && wave == kNW - 1) tally = tally_read(T.ahead);
+  {
+    const u32x4 zero = {0u, 0u, 0u, 0u};
+    for (int i = tid; i < (nbin + ntbin) / 8; i += kThreads) reinterpret_cast<u32x4*>(counters)[i] = zero;
+  }
+  float amax = 0.0f;
+  double en = 0.0;
+#pragma unroll
+  for (int j = 0; j < CH; ++j) {
+    float v[8];
+    raw[j].widen(v);
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      amax = __builtin_fmaxf(amax, __builtin_fabsf(v[i]));
+      const double d = static_cast<double>(v[i]);
+      en = __builtin_fma(d, d, en);
+    }
+  }
+  amax = wave_max(amax);
+  en = wave_sum(en);
+  if (lane == 0) { s_wmax[wave] = amax; s_wsum[wave] = en; }
+  __syncthreads();   // also: the counters are clear
+  amax = s_wmax[0];
+  en = s_wsum[0];
+#pragma unroll
+  for (int w = 1; w < kNW; ++w) {
+    amax = __builtin_fmaxf(amax, s_wmax[w]);
+    en += s_wsum[w];
+  }
+  {   // thread f * MOFQ_MAX_CLIP + k
+    const int f = tid / MOFQ_MAX_CLIP, k = tid % MOFQ_MAX_CLIP;
+    const float qmax = (f == 0) ? Codec<FA>::QMAX : Codec<FBX>::QMAX;
+    if (f < NF && k < K) sh.scale[f][k] = unit_scale(amax, a.clip[k], qmax, a.scale_f16 != 0);
+  }
+  static_assert(2 * MOFQ_MAX_CLIP <= kThreads, "one thread per (format, candidate)");
+
+  // ---- count the nbin patterns up to the largest magnitude's (a non-finite element lands in the last
+  // counter: the row's error is non-finite anyway) ---------------------------------------------------
+  const int hmax = __builtin_amdgcn_readfirstlane(static_cast<int>(pattern_rtz<BF16>(__builtin_fminf(amax, 3.4028234e38f))));   // exact for a finite amax
+  const int lo = (((hmax + 1 - nbin) > 0 ? (hmax + 1 - nbin) : 0) + 7) & ~7;
+  const int tlo = (((hmax + 1 - ntbin) > 0 ? (hmax + 1 - ntbin) : 0) + 7) & ~7;
+  {
+    const i16x2 lo2 = {static_cast<short>(lo), static_cast<short>(lo)};
+    const i16x2 tlo2 = {static_cast<short>(tlo), static_cast<short>(tlo)};
+    const i16x2 last2 = {static_cast<short>(nbin - 1), static_cast<short>(nbin - 1)};
+    const i16x2 tlast2 = {static_cast<short>(ntbin - 1), static_cast<short>(ntbin - 1)};
+    const uint32_t at = static_cast<uint32_t>(reinterpret_cast<uintptr_t>((lds_u32*)counters));
+    const uint32_t tat = static_cast<uint32_t>(reinterpret_cast<uintptr_t>((lds_u32*)tcounters));
+#pragma unroll
+    for (int j = 0; j < CH; ++j)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const uint32_t w = raw[j].w[i];
+        const i16x2 h2 = __builtin_bit_cast(i16x2, w & 0x7FFF7FFFu);
+        // padding (zero) and whatever lies below every threshold has no counter
+        count_pair(at, __builtin_elementwise_min(h2 - lo2, last2));
+        if constexpr (ANY_TAIL) {
+          const i16x2 t2 = h2 - tlo2;
+          // halves that are negative elements at or above the first pattern of theirs
+          const uint32_t q2 = w & ~__builtin_bit_cast(uint32_t, t2) & 0x80008000u;
+          if (q2 != 0) {
+            const i16x2 none = {-1, -1};
+            const uint32_t keep = sign_fill2(q2);
+            const i16x2 b2 = __builtin_elementwise_min(t2, tlast2);
+            count_pair(tat, __builtin_bit_cast(i16x2, (__builtin_bit_cast(uint32_t, b2) & keep) | (__builtin_bit_cast(uint32_t, none) & ~keep)));
+          }
+        }
+      }
+  }
+  __syncthreads();
+
+  if constexpr (ANY_TAIL)
+    if (wave == kNW - 1) packed_prefixes<1>(tcounters, TP, tlo, ntbin, s_wave);
+  packed_prefixes<kNW>(counters, P, lo, nbin, s_wave);
+  const uint64_t total = P[nbin];
+  const float v_lo = bits_to_float<BF16>(static_cast<uint32_t>(lo));
+  const double unit = static_cast<double>(bits_to_float<BF16>(static_cast<uint32_t>(lo) + 1) - v_lo);   // an ulp at lo
+  const double s_total = sum_of(total);
+  const double c_total = static_cast<double>(count_of(total));
+
+  // ---- level boundaries: one lane per candidate; a wave takes (format, 64 candidates, part of the runs) ----
+  {
+    // H = the largest pattern h with fl32(v(h) * inv) <= thr, as in the histogram kernel: the pattern of
+    // est * s rounded toward zero passes, one decision on the next tells.  Returns H - first + 1 as
+    // a number of counters; negative numbers are large ones to the unsigned minimum.
+    auto counters_below = [](float est, float thr, float s, float inv, int first) {
+      const uint32_t x1 = f2u(est * s) + 0x10000u;
+      const bool above = u2f(x1 & 0xFFFF0000u) * inv <= thr;
+      return static_cast<int>(x1 >> 16) - first + (above ? 1 : 0);
+    };
+    const int chunks = (K + 63) >> 6;
+    // few units: the runs of an 8-bit format are dealt to all waves, whose partial sums meet in LDS
+    const int parts = EIGHT ? kNW / (NF * chunks) : 1;   // 4, 2 or 1
+    double A = 0.0, B = 0.0, ca_tail = 0.0;
+    bool bad = false;
+    int cb_tail = 0;
+    auto tail = [&](const int first_level, float est, float thr, float s, float inv) {
+      // negative elements beyond the last positive level's upper boundary sit one level further
+      const int n1 = counters_below(est, thr, s, inv, tlo);
+      bad |= n1 < 0;
+      const uint64_t above = TP[ntbin] - TP[min(static_cast<uint32_t>(n1), static_cast<uint32_t>(ntbin))];
+      const float v_tlo = bits_to_float<BF16>(static_cast<uint32_t>(tlo));
+      ca_tail = sum_of(above) * static_cast<double>(bits_to_float<BF16>(static_cast<uint32_t>(tlo) + 1) - v_tlo);
+      cb_tail = static_cast<int>(count_of(above)) * (2 * first_level + 1);
+    };
+    auto finish = [&](const int f, const int k, float s, double last) {
+      if (k < K) {
+        const double At = __builtin_fma(unit, A + last * s_total, ca_tail);
+        const double Bt = B + static_cast<double>(cb_tail) + last * last * c_total;
+        const double sc = static_cast<double>(s);
+        const double v = (en - 2.0 * sc * At) + sc * sc * Bt;   // filtered error
+        sh.fast[f][k] = bad ? __builtin_nan("") : v;
+      }
+    };
+    auto search8 = [&](auto fmt_c, const int f, const int k, const int part) {
+      constexpr int FMT = decltype(fmt_c)::value;
+      const float s = sh.scale[f][k < K ? k : K - 1];
+      const float inv = 1.0f / s;
+      A = B = ca_tail = 0.0;
+      bad = false;
+      cb_tail = 0;
+      const BoundaryTable& t = Runs<FMT>::table();
+      const int runs = kRuns / parts;
+      for (int r = part * runs; r < (part + 1) * runs; ++r) {
+        uint64_t sums = 0;
+        int ib = 0;
+        const int base2 = 2 * Runs<FMT>::base(r) + 1;
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+          const int n1 = counters_below(t.b[r][i].est, t.b[r][i].thr, s, inv, lo);
+          // the smallest threshold: nothing uncounted above it, and no subnormal product (too coarse an estimate)
+          if (i == 0 && r == 0) bad = n1 < 0 || !(t.b[0][0].est * s >= 0x1p-126f);
+          const uint64_t p = P[min(static_cast<uint32_t>(n1), static_cast<uint32_t>(nbin))];
+          sums += p;      // (the counts overflow out of the word)
+          ib += __mul24(static_cast<int>(count_of(p)), base2 + 2 * i);
+        }
+        const double d = Runs<FMT>::spacing(r);
+        A = __builtin_fma(-d, sum_of(sums), A);
+        B = __builtin_fma(-d * d, static_cast<double>(ib), B);
+      }
+      if constexpr (Codec<FMT>::IS_INT)
+        if (part == 0) tail(127, static_cast<float>((127.5 - 0x1p-17) * (1.0 - 0x1p-21)), static_cast<float>(127.5 - 0x1p-17), s, inv);
+      if (parts == 1) finish(f, k, s, Runs<FMT>::LAST);
+    };
+    auto search4 = [&](auto fmt_c, const int f, const int k) {
+      constexpr int FMT = decltype(fmt_c)::value;
+      const float s = sh.scale[f][k < K ? k : K - 1];
+      const float inv = 1.0f / s;
+      A = B = ca_tail = 0.0;
+      bad = false;
+      cb_tail = 0;
+      int cb4 = 0;       // 4 sum_b (count up to boundary b) (m_b^2 - m_{b+1}^2): an integer below 2^31
+#pragma unroll
+      for (int q = 0; q < 7; ++q) {
+        const int n1 = counters_below(a.thr_est[f][q], a.thr[f][q], s, inv, lo);
+        if (q == 0) bad = n1 < 0;
+        const uint64_t p = P[min(static_cast<uint32_t>(n1), static_cast<uint32_t>(nbin))];
+        A = __builtin_fma(sum_of(p), a.dgd[f][q], A);
+        cb4 = __mul24(static_cast<int>(count_of(p)), a.dg2q[f][q]) + cb4;
+      }
+      B = 0.25 * static_cast<double>(cb4);
+      if constexpr (Codec<FMT>::IS_INT) tail(7, a.thr_est[f][7], a.thr[f][7], s, inv);
+      finish(f, k, s, static_cast<double>(a.g_last[f]));
+    };
+    for (int u = wave; u < NF * chunks * parts; u += kNW) {   // wave-uniform
+      const int part = u % parts, fc = u / parts;
+      const int f = fc / chunks;
+      const int k = (fc - f * chunks) * 64 + lane;
+      if constexpr (EIGHT) {
+        if (f == 0) search8(std::integral_constant<int, FA>{}, f, k, part);
+        else search8(std::integral_constant<int, FBX>{}, f, k, part);
+      } else {
+        if (f == 0) search4(std::integral_constant<int, FA>{}, f, k);
+        else search4(std::integral_constant<int, FBX>{}, f, k);
+      }
+    }
+    if constexpr (EIGHT) {
+      if (parts > 1) {   // one unit per wave: its sums are still in its registers
+        double* const s_part = reinterpret_cast<double*>(P);   // [wave][64][2], over the prefixes
+        __syncthreads();
+        s_part[tid * 2] = A;
+        s_part[tid * 2 + 1] = B;
+        __syncthreads();
+        if (wave % parts == 0) {
+          const int fc = wave / parts, f = fc / chunks;
+          const int k = (fc - f * chunks) * 64 + lane;
+          for (int p = 1; p < parts; ++p) {
+            A += s_part[(tid + 64 * p) * 2];
+            B += s_part[(tid + 64 * p) * 2 + 1];
+          }
+          finish(f, k, sh.scale[f][k < K ? k : K - 1], f == 0 ? Runs<FA>::LAST : Runs<FBX>::LAST);
+        }
+      }
+    }
+  }
+  __syncthreads();
+
+  // ---- winners (the re-scored values lie over the prefixes, which are no longer needed), codes --------
+  finish_row<BF16, FA, FB, kThreads, CH, true>(sh, reinterpret_cast<double*>(P), src, n, K, en, unit * s_total, a.g_absmax, T.rec, row);
+  if (T.ahead.codes) emit_row_ahead<BF16, FA, FB, kThreads, CH>(sh, T.ahead, tally, src, n, row);   // uniform
+}
+
+size_t lds_bytes(const SortedArgs& a) {
+  const size_t prefixes = std::max<size_t>(8 * static_cast<size_t>(a.nbin + 1 + a.ntbin + 1), 2 * MOFQ_MAX_CLIP * sizeof(double));
+  return 2 * static_cast<size_t>(a.nbin + a.ntbin) + prefixes;
+}
+
+template <int FA, int FB>
+int launch_shape(const SortedArgs& a, int64_t total_rows, hipStream_t st) {
+  const dim3 grid(static_cast<unsigned>(total_rows));
+  const int64_t chunks = a.cols / 8;
+#define MOFQ_BF16(CH)                                                                          \
+  if (chunks <= kThreads * (CH)) {                                                              \
+    hipLaunchKernelGGL((sweep_bf16_kernel<FA, FB, CH>), grid, dim3(kThreads), lds_bytes(a), st, a); \
+    return hip_status(hipGetLastError());                                                      \
+  }
+  MOFQ_BF16(1)   //  2048 columns
+  MOFQ_BF16(2)   //  4096
+  MOFQ_BF16(3)   //  6144
+  MOFQ_BF16(4)   //  8192
+  MOFQ_BF16(6)   // 12288
+  MOFQ_BF16(12)  // 24576
+#undef MOFQ_BF16
+  return MOFQ_ERR_UNSUPPORTED;
+}
+
+}  // namespace
+
+// The packed prefixes hold it: sums below 2^45 units (an element is below 2^(8 + binades); eight prefixes
+// are added up in 48 bits); LDS for three workgroups; room for the partial sums of a divided search.
+bool bf16_search_fits(const SweepParams& p, int nbin, int ntbin) {
+  if (p.dtype != MOFQ_BF16 || nbin <= 0 || nbin > kMaxBins || ntbin > kMaxTailBins) return false;
+  const int span = (std::max(nbin, ntbin) + 127) / 128;
+  if ((p.fmt[0] == MOFQ_INT8 || p.fmt[0] == MOFQ_FP8_E4M3) && nbin < 512) return false;
+  return span <= 22 && (p.cols << (8 + span)) <= (int64_t{1} << 45) && p.cols <= 24576;
+}
+
+int launch_sweep_bf16(const SweepParams& p, const SortedArgs& a, int64_t total_rows, hipStream_t st) {
+  if (!bf16_search_fits(p, a.nbin, a.ntbin)) return MOFQ_ERR_UNSUPPORTED;
+  const int fa = p.fmt[0], fb = p.n_fmt == 2 ? p.fmt[1] : -1;
+#define MOFQ_F(A, B) \
+  if (fa == (A) && fb == (B)) return launch_shape<A, B>(a, total_rows, st);
+  MOFQ_F(MOFQ_INT4, MOFQ_FP4_E2M1)
+  MOFQ_F(MOFQ_INT4, -1)
+  MOFQ_F(MOFQ_FP4_E2M1, -1)
+  MOFQ_F(MOFQ_INT8, MOFQ_FP8_E4M3)
+  MOFQ_F(MOFQ_INT8, -1)
+  MOFQ_F(MOFQ_FP8_E4M3, -1)
+#undef MOFQ_F
+  return MOFQ_ERR_UNSUPPORTED;
+}
+
+}  // namespace mofq

@@ -35,37 +35,6 @@ MOFQ_DEV uint32_t dot2(uint32_t a, uint32_t b, uint32_t c) {   // a.lo b.lo + a.
   return __builtin_amdgcn_udot2(__builtin_bit_cast(u16x2, a), __builtin_bit_cast(u16x2, b), c, false);
 }
 
-// bit pattern of x >= 0 rounded toward zero to the input type
-template <typename In> MOFQ_DEV uint32_t pattern_rtz(float x);
-template <> MOFQ_DEV uint32_t pattern_rtz<F16>(float x) {
-  return __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_pkrtz(x, 0.0f));   // the high half is +0
-}
-template <> MOFQ_DEV uint32_t pattern_rtz<BF16>(float x) { return f2u(x) >> 16; }
-template <typename In> struct Pattern;
-template <> struct Pattern<F16> { static constexpr int MANT = 10; };
-template <> struct Pattern<BF16> { static constexpr int MANT = 7; };
-
-// Lexicographic minimum of (value, index) over the wave by data-parallel-primitive moves: the
-// smallest value (no NaN among the inputs), then the smallest index among the lanes that hold it.
-template <int CTRL> MOFQ_DEV int dpp_i32(int x) { return __builtin_amdgcn_update_dpp(0, x, CTRL, 0xF, 0xF, true); }
-MOFQ_DEV void wave_argmin_dpp(double& v, int& idx) {
-  double m = v;
-  m = __builtin_fmin(m, dpp_f64<DPP_QUAD_XOR1>(m));
-  m = __builtin_fmin(m, dpp_f64<DPP_QUAD_XOR2>(m));
-  m = __builtin_fmin(m, dpp_f64<DPP_ROW_HALF_MIRROR>(m));
-  m = __builtin_fmin(m, dpp_f64<DPP_ROW_MIRROR>(m));
-  m = __builtin_fmin(__builtin_fmin(readlane_f64(m, 0), readlane_f64(m, 16)), __builtin_fmin(readlane_f64(m, 32), readlane_f64(m, 48)));
-  int c = (v == m) ? idx : 0x7FFFFFFF;
-  c = min(c, dpp_i32<DPP_QUAD_XOR1>(c));
-  c = min(c, dpp_i32<DPP_QUAD_XOR2>(c));
-  c = min(c, dpp_i32<DPP_ROW_HALF_MIRROR>(c));
-  c = min(c, dpp_i32<DPP_ROW_MIRROR>(c));
-  idx = min(min(__builtin_amdgcn_readlane(c, 0), __builtin_amdgcn_readlane(c, 16)),
-            min(__builtin_amdgcn_readlane(c, 32), __builtin_amdgcn_readlane(c, 48)));
-  v = m;
-}
-
-
 // ---- prefixes -----------------------------------------------------------------------------
 // Exclusive prefix of count and magnitude sum per group of 8 counters, one record per group, the
 // totals in record ng.  A group's patterns share the exponent: pattern lo + 8 g + i has the magnitude
@@ -79,15 +48,6 @@ struct Wide {
   double sum;
   uint32_t cnt, unused;
 };
-
-// m and shift of the group at pattern p (subnormals: the first normal binade's ulp, no leading bit)
-template <typename In> MOFQ_DEV void mant_shift(uint32_t p, int e_lo, uint32_t& m, uint32_t& shift) {
-  constexpr int MANT = Pattern<In>::MANT;
-  const int e = static_cast<int>(p >> MANT);
-  m = (p & ((1u << MANT) - 1u)) | (static_cast<uint32_t>(e > 0 ? 1 : 0) << MANT);
-  shift = static_cast<uint32_t>((e > 1 ? e : 1) - e_lo);
-}
-template <typename In> MOFQ_DEV int exponent_of(int p) { const int e = p >> Pattern<In>::MANT; return e > 1 ? e : 1; }
 
 // count and index-weighted count of eight counters, two per word
 MOFQ_DEV void count8(const u32x4 w, uint32_t& c, uint32_t& wsum) {
@@ -206,8 +166,6 @@ void sweep_hist_kernel(const SortedArgs a) {
   constexpr int NF = (FB >= 0) ? 2 : 1;
   constexpr int FBX = (FB >= 0) ? FB : FA;
   constexpr int NW = THREADS / 64;
-  constexpr int E = CH * 8;            // elements per thread
-  constexpr int MAXL = NF * MOFQ_MAX_CLIP;
   constexpr bool TAIL_A = FA == MOFQ_INT4, TAIL_B = (FB >= 0) && FBX == MOFQ_INT4;
   constexpr bool ANY_TAIL = TAIL_A || TAIL_B;
   constexpr int GPMAX = kHistMaxBins / 8 / THREADS;   // groups per thread at most
@@ -223,22 +181,11 @@ void sweep_hist_kernel(const SortedArgs a) {
   uint32_t* const hist = reinterpret_cast<uint32_t*>(s_dyn + (static_cast<size_t>((ng + 1) + (ntg + 1)) * sizeof(Rec) + 15) / 16 * 16);
   uint32_t* const thist = hist + (nbin >> 1);   // (counts stay below 2^16: a row has at most 24576 elements)
 
-  __shared__ float s_scale[NF][MOFQ_MAX_CLIP];
-  __shared__ double s_fast[NF][MOFQ_MAX_CLIP];
+  __shared__ RowSearch<NF, NW> sh;
   __shared__ float s_wmax[NW];
-  __shared__ double s_wsum[1][NW];
+  __shared__ double s_wsum[NW];
   __shared__ uint32_t s_wc[NW];
   __shared__ sum_t s_ws[NW];
-  __shared__ double s_thr[NF];
-  __shared__ int s_direct[NF];   // the winning candidate where no element-wise pass is needed, else -1
-  __shared__ uint8_t s_list[MAXL];   // format * MOFQ_MAX_CLIP + candidate
-  __shared__ int s_nlist;
-  __shared__ double s_p2[NW];
-  __shared__ double s_best[NF], s_tally;
-  __shared__ float s_bscale[NF];
-  // re-scored errors of the shortlist: over the records, which are no longer needed by then
-  // (the host sizes the dynamic LDS for it)
-  double* const s_val = reinterpret_cast<double*>(s_dyn);
   __shared__ __attribute__((aligned(16))) uint32_t s_keep[8][4];
 
   const int tid = threadIdx.x;
@@ -299,25 +246,25 @@ void sweep_hist_kernel(const SortedArgs a) {
     amax = __builtin_fmaxf(bits_to_float<In>(amax2 & 0xFFFFu), bits_to_float<In>(amax2 >> 16));
   amax = wave_max(amax);
   en = wave_sum(en);
-  if (lane == 0) { s_wmax[wave] = amax; s_wsum[0][wave] = en; }
+  if (lane == 0) { s_wmax[wave] = amax; s_wsum[wave] = en; }
   __syncthreads();   // also: the counters are clear
   amax = s_wmax[0];
-  en = s_wsum[0][0];
+  en = s_wsum[0];
 #pragma unroll
   for (int w = 1; w < NW; ++w) {
     amax = __builtin_fmaxf(amax, s_wmax[w]);
-    en += s_wsum[0][w];
+    en += s_wsum[w];
   }
   if (tid < 2 * MOFQ_MAX_CLIP) {   // thread f * MOFQ_MAX_CLIP + k
     const int f = tid / MOFQ_MAX_CLIP, k = tid % MOFQ_MAX_CLIP;
     const float qmax = (f == 0) ? Codec<FA>::QMAX : Codec<FBX>::QMAX;
-    if (f < NF && k < K) s_scale[f][k] = unit_scale(amax, a.clip[k], qmax, a.scale_f16 != 0);
+    if (f < NF && k < K) sh.scale[f][k] = unit_scale(amax, a.clip[k], qmax, a.scale_f16 != 0);
   }
   static_assert(2 * MOFQ_MAX_CLIP <= THREADS, "one thread per (format, candidate)");
 
   // ---- the histogram covers the nbin patterns up to the largest magnitude's (a non-finite
   // element lands in the last counter: the row's error is non-finite anyway) --------------------
-  const int hmax = static_cast<int>(pattern_rtz<In>(amax < 3.0e38f ? amax : 3.0e38f));   // exact for a finite amax
+  const int hmax = static_cast<int>(pattern_rtz<In>(__builtin_fminf(amax, 3.4028234e38f)));   // exact for a finite amax
   const int lo = (((hmax + 1 - nbin) > 0 ? (hmax + 1 - nbin) : 0) + 7) & ~7;
   const int tlo = (((hmax + 1 - ntbin) > 0 ? (hmax + 1 - ntbin) : 0) + 7) & ~7;
   {
@@ -387,7 +334,7 @@ void sweep_hist_kernel(const SortedArgs a) {
     const int chunks = (K + 63) >> 6;
     auto unit = [&](auto tail_tag, const int f, const int k) {
       constexpr bool TAIL = decltype(tail_tag)::value;
-      const float s = s_scale[f][k < K ? k : K - 1];
+      const float s = sh.scale[f][k < K ? k : K - 1];
       const float inv = 1.0f / s;
       // H = the largest finite pattern h with fl32(v(h) * inv) <= thr.  inv and the product are each off
       // by at most 2^-24, so the decision flips between thr s (1 - 2^-22) and thr s (1 + 2^-22); thr_est is
@@ -402,17 +349,18 @@ void sweep_hist_kernel(const SortedArgs a) {
       double ca = 0.0;
       int cb4 = 0;       // 4 sum_b (count up to boundary b) (m_b^2 - m_{b+1}^2): an integer below 2^31
       // counters at or below H, as a number of counters: H - lo + 1 within [0, nbin].  A threshold
-      // more than one pattern below the histogram's range (least < 0) sends the candidate to the
-      // exact pass: uncounted elements might lie above it.
-      int least = 0;
+      // more than one pattern below the histogram's range sends the candidate to the exact pass:
+      // uncounted elements might lie above it.  The first boundary's is the smallest (and a negative
+      // number is a large one to the unsigned minimum, so addresses stay inside).
+      bool bad = false;
       // one boundary at a time (a rolled loop: unrolled, the eight of them cost some 80 registers)
 #pragma unroll 1
       for (int q = 0; q < 7; ++q) {
         const int n1 = counters_below(f, q, lo);
-        least = n1 < least ? n1 : least;
+        if (q == 0) bad = n1 < 0;
         uint32_t C;
         sum_t S;
-        hist_prefix<In>(hist, rec, keep, lo, static_cast<uint32_t>(min(max(n1, 0), nbin)), C, S);
+        hist_prefix<In>(hist, rec, keep, lo, min(static_cast<uint32_t>(n1), static_cast<uint32_t>(nbin)), C, S);
         ca = __builtin_fma(static_cast<double>(S), a.dgd[f][q], ca);
         cb4 = __mul24(static_cast<int>(C), a.dg2q[f][q]) + cb4;
       }
@@ -420,10 +368,10 @@ void sweep_hist_kernel(const SortedArgs a) {
       if constexpr (TAIL) {
         // negative elements with a pattern above H: the short histogram's totals less its prefix
         const int n1 = counters_below(f, 7, tlo);
-        least = n1 < least ? n1 : least;
+        bad |= n1 < 0;
         uint32_t C;
         sum_t S;
-        hist_prefix<In>(thist, trec, keep, tlo, static_cast<uint32_t>(min(max(n1, 0), ntbin)), C, S);
+        hist_prefix<In>(thist, trec, keep, tlo, min(static_cast<uint32_t>(n1), static_cast<uint32_t>(ntbin)), C, S);
         ca_tail = static_cast<double>(trec[ntg].sum - S) * a.dgd[f][7];
         if constexpr (std::is_same<Rec, Narrow>::value) {
           const float v_tlo = bits_to_float<In>(static_cast<uint32_t>(tlo));
@@ -431,14 +379,13 @@ void sweep_hist_kernel(const SortedArgs a) {
         }
         cb4 = __mul24(static_cast<int>(record_count(trec[ntg]) - C), a.dg2q[f][7]) + cb4;
       }
-      const bool bad = least < 0;
       if (k < K) {
         const double gl = static_cast<double>(a.g_last[f]);
         const double A = __builtin_fma(sum_unit, ca + gl * s_total, ca_tail);
         const double B = 0.25 * static_cast<double>(cb4) + gl * gl * static_cast<double>(c_total);
         const double sc = static_cast<double>(s);
         const double v = (en - 2.0 * sc * A) + sc * sc * B;   // filtered error
-        s_fast[f][k] = bad ? __builtin_nan("") : v;
+        sh.fast[f][k] = bad ? __builtin_nan("") : v;
       }
     };
     for (int u = wave; u < NF * chunks; u += NW) {
@@ -451,138 +398,14 @@ void sweep_hist_kernel(const SortedArgs a) {
   }
   __syncthreads();
 
-  // ---- shortlist.  The rounding bound of the filtered error is the sorting kernel's with the depth
-  // of this kernel's summation trees.  Integer sums are exact, and so is A (an integer below 2^53 in
-  // units of an ulp, but for the addition of the tail): D = 1.  fp64 sums: a group's sum is exact
+  // ---- winners.  With 32-bit sums everything but the energy is exact; fp64 sums: a group's sum is exact
   // (products and sum of fewer than 2^27 units of one ulp), a group prefix adds at most GPMAX of them
   // in a thread, 6 levels of the wave scan and the waves before, and a look-up adds two exact products:
-  // fewer than D = 16 roundings, each of at most u sum|x|, whatever the row's length.
-  constexpr double D = std::is_same<Rec, Narrow>::value ? 1.0 : 16.0;
-  for (int f = wave; f < NF; f += NW) {
-    double m = __builtin_inf();
-    int km = 0;
-    float smax = 0.0f;
-    for (int k = lane; k < K; k += 64) {
-      const double v = s_fast[f][k];
-      if (v < m) { m = v; km = k; }
-      smax = __builtin_fmaxf(smax, s_scale[f][k]);
-    }
-    wave_argmin_dpp(m, km);
-    smax = wave_max(smax);
-    const double sm = static_cast<double>(smax), gm = static_cast<double>(a.g_absmax[f]);
-    const double nd = static_cast<double>(n);
-    const double mag = en + 2.0 * sm * gm * l1 + sm * sm * gm * gm * nd;
-    const double thr = m + 0x1p-33 * mag;   // twice the margin: both values carry the error
-    int cnt = 0;
-    for (int k0 = 0; k0 < K; k0 += 64) {
-      const int k = k0 + lane;
-      cnt += __builtin_popcountll(__ballot(k < K && !(s_fast[f][k < K ? k : 0] > thr)));
-    }
-    static_assert(GPMAX + 6 + NW + 2 <= 16, "depth of the prefix sums");
-    const double beta = 0x1p-53 * (40.0 * D * 2.0 * sm * l1 + (E + 32) * en + 8.0 * sm * sm * gm * gm * nd);
-    const bool direct = cnt == 1 && beta <= 0x1p-34 * m;   // false for a zero or non-finite error
-    if (lane == 0) { s_thr[f] = thr; s_direct[f] = direct ? km : -1; }
-  }
-  if (tid == 0) s_nlist = 0;
-  __syncthreads();
-#pragma unroll
-  for (int f = 0; f < NF; ++f)
-    if (s_direct[f] < 0)   // uniform
-      for (int k = tid; k < K; k += THREADS)
-        if (!(s_fast[f][k] > s_thr[f])) s_list[atomicAdd(&s_nlist, 1)] = static_cast<uint8_t>(f * MOFQ_MAX_CLIP + k);   // any order
-  __syncthreads();
-  const int n_list = s_nlist;
-
-  // ---- exact fp64 re-score of the shortlist, element by element ------------------------------
-  uint32_t carry = 0;
-  for (int e = 0; e < n_list; ++e) {
-    const int fk = s_list[e];
-    const int f = __builtin_amdgcn_readfirstlane(fk / MOFQ_MAX_CLIP);
-    const int k = __builtin_amdgcn_readfirstlane(fk % MOFQ_MAX_CLIP);
-    const float s = s_scale[f][k], inv = 1.0f / s;
-    const double sd = static_cast<double>(s);
-    double acc = 0.0;
-    // the row is read again (it left the registers after the counting; this pass is rare)
-#pragma unroll
-    for (int j = 0; j < CH; ++j) {
-      const int64_t c0 = (static_cast<int64_t>(j) * THREADS + tid) * 8;
-      u32x4 raw = {0u, 0u, 0u, 0u};   // padding is zero and scores zero
-      if (c0 < a.cols) raw = *reinterpret_cast<const u32x4*>(src + c0);
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const float x0 = bits_to_float<In>(raw[i] & 0xFFFFu);
-        const float x1 = bits_to_float<In>(raw[i] >> 16);
-        if (f == 0) rescore2<FA>(acc, x0, x1, inv, sd, carry);
-        else rescore2<FBX>(acc, x0, x1, inv, sd, carry);
-      }
-    }
-    acc = wave_sum(acc);
-    if (lane == 0) s_p2[wave] = acc;
-    __syncthreads();
-    if (tid == 0) {
-      double t = s_p2[0];
-#pragma unroll
-      for (int w = 1; w < NW; ++w) t += s_p2[w];
-      s_val[e] = t;
-    }
-    __syncthreads();
-  }
-
-  if (tid < NF) {
-    const int f = tid;
-    double best = __builtin_inf();
-    int bk = s_direct[f];
-    if (bk >= 0) best = s_fast[f][bk];
-    for (int e = 0; e < n_list; ++e) {   // smallest error, then smallest index: the first smallest
-      const int fk = s_list[e];
-      if (fk / MOFQ_MAX_CLIP != f) continue;
-      const int k = fk % MOFQ_MAX_CLIP;
-      if (s_val[e] < best || (s_val[e] == best && k < bk)) { best = s_val[e]; bk = k; }
-    }
-    if (bk < 0) { bk = 0; best = __builtin_nan(""); }   // only on non-finite input
-    T.rec.scale[f][row] = s_scale[f][bk];
-    T.rec.clip[f][row] = bk;
-    T.rec.err[f][row] = best;
-    if (f == 0 && T.rec.energy) T.rec.energy[row] = en;
-    s_best[f] = best;
-    s_bscale[f] = s_scale[f][bk];
-  }
-  if (!T.ahead.codes) return;   // uniform
-  if (NF == 2 && wave == NW - 1) {
-    tally = wave_sum(tally);
-    if (lane == 0) s_tally = tally;
-  }
-
-  // ---- the row's codes, in the format that the tensor's rows favour so far ------------------------
-  Raw8<In> codes_in[CH];
-#pragma unroll
-  for (int j = 0; j < CH; ++j) {
-    const int c = j * THREADS + tid;
-    codes_in[j].load(src, 0, static_cast<uint32_t>(c * 8 < n ? c : 0) * 8);
-  }
-  __syncthreads();
-  int slot = 0;
-  if constexpr (NF == 2) {
-    const double d = s_best[0] - s_best[1];
-    slot = __builtin_amdgcn_readfirstlane(s_tally + d > 0.0 ? 1 : 0);
-    if (tid == 0) tally_add<4>(T.ahead, d);
-  }
-  if (tid == 0) T.ahead.tag[row] = static_cast<uint8_t>(T.ahead.cand_of[slot]);
-  const float inv = 1.0f / s_bscale[slot];
-  uint32_t* const out = static_cast<uint32_t*>(T.ahead.codes) + row * (a.cols / 8);
-  auto emit = [&](auto fmt_c) {
-#pragma unroll
-    for (int j = 0; j < CH; ++j) {
-      const int c = j * THREADS + tid;
-      float v[8];
-      codes_in[j].widen(v);
-      uint32_t words[2];
-      encode8<decltype(fmt_c)::value>(v, inv, words);
-      if (c * 8 < n) out[c] = words[0];
-    }
-  };
-  if (slot == 0) emit(std::integral_constant<int, FA>{});
-  else emit(std::integral_constant<int, FBX>{});
+  // fewer than 16 roundings, whatever the row's length.  The re-scored values lie over the records,
+  // which are no longer needed (the host sizes the dynamic LDS for it).
+  static_assert(GPMAX + 6 + NW + 2 <= 16, "depth of the prefix sums");
+  finish_row<In, FA, FB, THREADS, CH, std::is_same<Rec, Narrow>::value>(sh, reinterpret_cast<double*>(s_dyn), src, n, K, en, l1, a.g_absmax, T.rec, row);
+  if (T.ahead.codes) emit_row_ahead<In, FA, FB, THREADS, CH>(sh, T.ahead, tally, src, n, row);   // uniform
 }
 
 // Dynamic LDS: the records and counters of both histograms; the shortlist's re-scored values lie
@@ -614,14 +437,16 @@ template <typename In, int FA, int FB>
 int launch_hist_sums(const SortedArgs& a, int64_t total_rows, hipStream_t st) {
   constexpr int ppb = 1 << Pattern<In>::MANT;
   const int span = (std::max(a.nbin, a.ntbin) + ppb - 1) / ppb;
-  const bool narrow = span <= 16 && (a.cols << (Pattern<In>::MANT + 1 + span)) < (int64_t{1} << 32);
-  return narrow ? launch_hist_shape<In, FA, FB, Narrow>(a, total_rows, st) : launch_hist_shape<In, FA, FB, Wide>(a, total_rows, st);
+  if constexpr (std::is_same<In, F16>::value)   // (bf16 rows with so few patterns have their own kernel)
+    if (span <= 16 && (a.cols << (Pattern<In>::MANT + 1 + span)) < (int64_t{1} << 32)) return launch_hist_shape<In, FA, FB, Narrow>(a, total_rows, st);
+  return launch_hist_shape<In, FA, FB, Wide>(a, total_rows, st);
 }
 
 }  // namespace
 
 int launch_sweep_hist(const SweepParams& p, const SortedArgs& a, int64_t total_rows, hipStream_t st) {
   if (a.nbin <= 0 || (p.dtype != MOFQ_F16 && p.dtype != MOFQ_BF16)) return MOFQ_ERR_UNSUPPORTED;
+  if (bf16_search_fits(p, a.nbin, a.ntbin)) return launch_sweep_bf16(p, a, total_rows, st);
   const int fa = p.fmt[0], fb = p.n_fmt == 2 ? p.fmt[1] : -1;
   const bool h = p.dtype == MOFQ_F16;
   if (fa == MOFQ_INT4 && fb == MOFQ_FP4_E2M1)

@@ -597,10 +597,18 @@ __global__ __launch_bounds__(THREADS, (CH <= 4 ? 4 : 2)) void sweep_sorted_kerne
 
 // ---- host: rounding thresholds of the level boundaries ---------------------------------------
 
-// Level magnitudes of a 4-bit format in ascending order, and for each boundary b the largest
+// 4-bit formats: level magnitudes in ascending order, and for each boundary b the largest
 // fp32 t = |x| / s that still lands on magnitude m_b or below.  Rounding is to nearest with ties
 // to the even code, which is symmetric in the sign.
 void fill_levels(int fmt, SortedArgs& a, int slot) {
+  if (fmt == MOFQ_INT8 || fmt == MOFQ_FP8_E4M3) {
+    // the search of bf16 rows has its own tables; here only what sizes the histograms: the smallest threshold,
+    // and the one beyond which a negative element sits one level further
+    a.thr[slot][0] = fmt == MOFQ_INT8 ? 0.5f : 0x1p-10f;
+    a.thr[slot][7] = 127.5f;
+    a.g_absmax[slot] = fmt == MOFQ_INT8 ? 128.0f : 448.0f;
+    return;
+  }
   double m[9];
   bool up_is_even[8];   // at the midpoint between m[b] and m[b+1], does the tie go to m[b+1]?
   const bool int4 = fmt == MOFQ_INT4;
@@ -651,10 +659,13 @@ int launch_shape(const SortedArgs& a, int64_t total_rows, hipStream_t st) {
   return MOFQ_ERR_UNSUPPORTED;
 }
 
+bool eight_bit(const SweepParams& p) { return p.fmt[0] == MOFQ_INT8 || p.fmt[0] == MOFQ_FP8_E4M3; }
+
 template <typename In>
 int launch_fmt(const SweepParams& p, const SortedArgs& a, int64_t total_rows, hipStream_t st) {
   const int fa = p.fmt[0], fb = p.n_fmt == 2 ? p.fmt[1] : -1;
   const bool hist = a.nbin > 0;
+  if (eight_bit(p)) return hist ? launch_sweep_bf16(p, a, total_rows, st) : MOFQ_ERR_UNSUPPORTED;
   if (fa == MOFQ_INT4 && fb == MOFQ_FP4_E2M1)
     return hist ? launch_sweep_hist(p, a, total_rows, st) : launch_shape<In, MOFQ_INT4, MOFQ_FP4_E2M1>(a, total_rows, st);
   if (fa == MOFQ_INT4 && fb == -1)
@@ -689,11 +700,13 @@ void hist_sizes(const SweepParams& p, SortedArgs& a) {
   const int ppb = p.dtype == MOFQ_F16 ? 1024 : 128;
   int nbin = 16, ntbin = 0;
   for (int f = 0; f < p.n_fmt; ++f) {
-    const double qmax = p.fmt[f] == MOFQ_INT4 ? 7.0 : 6.0;
+    const bool integer = p.fmt[f] == MOFQ_INT4 || p.fmt[f] == MOFQ_INT8;
+    const double qmax = p.fmt[f] == MOFQ_INT4 ? 7.0 : (p.fmt[f] == MOFQ_INT8 ? 127.0 : (p.fmt[f] == MOFQ_FP8_E4M3 ? 448.0 : 6.0));
     nbin = std::max(nbin, hist_bins(qmax / (static_cast<double>(a.thr[f][0]) * r_min), ppb));
-    if (p.fmt[f] == MOFQ_INT4) ntbin = std::max(16, hist_bins(qmax / (static_cast<double>(a.thr[f][7]) * r_min), ppb));
+    if (integer) ntbin = std::max(16, hist_bins(qmax / (static_cast<double>(a.thr[f][7]) * r_min), ppb));
   }
   if (nbin > kHistMaxBins || ntbin > kHistMaxTailBins) return;
+  if (eight_bit(p) && !bf16_search_fits(p, nbin, ntbin)) return;
   a.nbin = nbin;
   a.ntbin = ntbin;
 }
@@ -702,10 +715,19 @@ void hist_sizes(const SweepParams& p, SortedArgs& a) {
 
 namespace {
 
+constexpr int64_t kMinPairs8 = 32768;
+
 // Whether the configuration of one tensor is in the domain of these kernels.
 bool in_domain(const SweepParams& p) {
   if (p.gran != MOFQ_PER_CHANNEL || (p.dtype != MOFQ_F16 && p.dtype != MOFQ_BF16)) return false;
   if (p.n_clip < 8 || p.cols < 1024 || p.cols > 24576) return false;
+  if (eight_bit(p)) {
+    // Only bf16 rows have few enough patterns.  The line: 4096 rows, INT8 against E4M3, scored directly / by
+    // histogram: 1024 x 16 ratios 50 / 60 us, 1024 x 32 73 / 63, 4096 x 8 82 / 72, 8192 x 8 135 / 94; one format:
+    // 1024 x 32 42..48 / 42..44, 4096 x 8 52..57 / 50..56.
+    if (p.dtype != MOFQ_BF16 || p.cols * p.n_clip < kMinPairs8) return false;
+    return p.n_fmt == 1 || (p.fmt[0] == MOFQ_INT8 && p.fmt[1] == MOFQ_FP8_E4M3);
+  }
   for (int f = 0; f < p.n_fmt; ++f)
     if (p.fmt[f] != MOFQ_INT4 && p.fmt[f] != MOFQ_FP4_E2M1) return false;
   return true;

@@ -50,3 +50,33 @@ def test_codes_written_by_the_single_candidate_search(mq, dtype, rows, cols, pad
         w[r] = torch.randint(-7, 8, w[r].shape, generator=g, device=DEV).to(dtype)
         w[r, 5] = 7.0
     check_tensor(mq, w, cands, orc.PER_CHANNEL, mi.clip_ratios(1), f16=f16, label="ahead-single")
+
+
+# bf16 rows searched through prefixes per bit pattern: tiles of the row, one and two groups of 64 candidates,
+# one format and two, ratios that stretch the histogram; rows of zeros, of equal elements, of powers of two
+# over the whole range, and rows so small that the scales or the elements are subnormal
+@pytest.mark.parametrize("cols,n_clip,lo_clip,f16", [
+    (1024, 32, 0.5, False), (2048, 16, 0.3, False), (2056, 64, 0.5, True), (4104, 8, 0.9, False), (5000, 50, 0.5, False),
+    (6152, 65, 0.5, False), (8200, 100, 0.25, True), (12296, 20, 0.5, False), (24576, 9, 0.05, False)])
+def test_bf16_pattern_prefixes(mq, cols, n_clip, lo_clip, f16):  # noqa: F811
+    w = _strided(21, cols, 8, cols, torch.bfloat16)
+    g = torch.Generator(device=DEV).manual_seed(cols)
+    w[1] = 0.0
+    w[2] = 0.75
+    w[3] = torch.exp2(torch.randint(-40, 3, (cols,), generator=g, device=DEV).float()).to(torch.bfloat16) * w[3].sign()
+    w[4] *= 1e-36
+    w[5] = (w[5].float() * 2.0 ** -118).to(torch.bfloat16)
+    w[6] = torch.where(w[6] > 0, w[6], -w[6] * 3).to(torch.bfloat16)
+    w[7, 3] = -3.3e38 if not f16 else -6e4
+    ratios = [lo_clip + (1.0 - lo_clip) * (i + 1) / n_clip for i in range(n_clip)]
+    for cands in (PAIR8, [orc.INT8], [orc.FP8_E4M3], PAIR4, [orc.INT4], [orc.FP4_E2M1]):
+        check_tensor(mq, w, cands, orc.PER_CHANNEL, ratios, f16=f16, label="bf16-edge")
+
+
+def test_bf16_search_writes_codes(mq):  # noqa: F811
+    w = _strided(8209, 1048, 8, 3, torch.bfloat16)
+    g = torch.Generator(device=DEV).manual_seed(3)
+    w[:40] = torch.randint(-7, 8, (40, 1048), generator=g, device=DEV).to(torch.bfloat16)
+    w[:40, 5] = 7.0
+    check_tensor(mq, w, PAIR8, orc.PER_CHANNEL, mi.clip_ratios(40), label="bf16-ahead-8")
+    check_tensor(mq, w, PAIR4, orc.PER_CHANNEL, mi.clip_ratios(40), label="bf16-ahead-4")
