@@ -96,7 +96,6 @@ constexpr int CH = ROW_B / 16;                  // chunks per row
 constexpr int STAGE_ROWS = TM + TN;
 constexpr int STAGE = STAGE_ROWS * ROW_B;       // 48 KB
 constexpr int NST = 3;                          // stages resident
-constexpr int AHEAD = NST - 1;                  // stage kt + AHEAD is issued during step kt
 constexpr int DEP = STAGE / 1024 / NW;          // deposits per wave per stage (6)
 MOFQ_DEV constexpr int swz(int row) { return (row >> 1) & (CH - 1); }
 
@@ -104,18 +103,16 @@ MOFQ_DEV constexpr int swz(int row) { return (row >> 1) & (CH - 1); }
 // them at LDS address lds_base + 16*l.  Written as inline assembly so that the compiler
 // does not serialise later LDS reads of OTHER buffers behind the deposit; completion is
 // tracked by hand with s_waitcnt vmcnt (deposits of a wave retire in order).
-MOFQ_DEV void lds_deposit(const char* gsrc, const unsigned char* lds_dst) {
-  const uint32_t lds_addr = static_cast<uint32_t>(reinterpret_cast<uintptr_t>(
-      (__attribute__((address_space(3))) const unsigned char*)lds_dst));
+MOFQ_DEV void lds_deposit(const char* gsrc, uint32_t lds_addr) {
   asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off"
                :
                : "s"(__builtin_amdgcn_readfirstlane(lds_addr)), "v"(gsrc)
                : "memory");   // m0 is not otherwise used by these kernels
 }
 
-// s_waitcnt with only the vector-memory counter constrained (6 bits, split field).
-template <int N> MOFQ_DEV void wait_deposits_but() {
-  __builtin_amdgcn_s_waitcnt((N & 15) | (7 << 4) | (15 << 8) | ((N >> 4) << 14));
+// s_waitcnt: all LDS reads done, at most N vector-memory operations in flight (6 bits, split field).
+template <int N> MOFQ_DEV void wait_deposits_and_reads() {
+  __builtin_amdgcn_s_waitcnt((N & 15) | (7 << 4) | (0 << 8) | ((N >> 4) << 14));
 }
 
 enum : int { K_REF = 100, K_GRID = WA_GRID_BF16, K_I8 = WA_INT8, K_F8 = WA_FP8 };   // K_REF: the 16-bit inputs themselves
@@ -125,6 +122,7 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2, 2)))
   __shared__ __attribute__((aligned(1024))) unsigned char s_buf[NST * STAGE];
   __shared__ double s_red[3][NW];
 
+  const uint32_t lds0 = static_cast<uint32_t>(reinterpret_cast<uintptr_t>((__attribute__((address_space(3))) unsigned char*)s_buf));
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -180,64 +178,64 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2, 2)))
     constexpr int EB = (KIND == K_REF || KIND == K_GRID) ? 2 : 1;   // bytes per element
     constexpr int TK = ROW_B / EB;                                  // K elements per stage
     constexpr int NG = (KIND == K_F8) ? CH / 4 : CH / 2;            // matrix groups per stage (TI*TJ instructions each)
-    constexpr int NF = (KIND == K_F8) ? 2 : 1;                      // 16-byte chunks per fragment
     const char* xb; const char* wb; int64_t xrow, wrow;
     if constexpr (KIND == K_REF) { xb = reinterpret_cast<const char*>(a.x); wb = reinterpret_cast<const char*>(a.w); xrow = a.ldx * 2; wrow = a.ldw * 2; }
-    else { xb = static_cast<const char*>(xq); wb = static_cast<const char*>(wq); xrow = wrow = static_cast<int64_t>(kdim) * EB; }
+    else { xb = static_cast<const char*>(xq); wb = static_cast<const char*>(wq); xrow = wrow = static_cast<int64_t>(static_cast<uint32_t>(kdim) * EB); }
 
     // This lane's global source of each of its wave's deposits at k = 0 (deposit i of a
-    // stage covers chunk slots 64 i .. 64 i + 63 and is issued by wave i % NW).
-    const char* src[DEP];
-#pragma unroll
-    for (int d = 0; d < DEP; ++d) {
-      const int c = (wave + NW * d) * 64 + lane;
-      const int row = c / CH, kc = (c % CH) ^ swz(row);
-      if (row < TM) {
-        int gr = m0 + row;
-        gr = gr < a.M ? gr : a.M - 1;          // rows past the edge repeat the last one (masked later)
-        src[d] = xb + static_cast<int64_t>(gr) * xrow + kc * 16;
-      } else {
-        int gr = n0 + row - TM;
-        gr = gr < a.N ? gr : a.N - 1;
-        src[d] = wb + static_cast<int64_t>(gr) * wrow + kc * 16;
-      }
-    }
+    // stage covers chunk slots 64 i .. 64 i + 63 and is issued by wave i % NW: rows that are multiples of 64
+    // apart, so the lane fetches the same chunk of each).
+    // Rows past the edge repeat the last one (masked later): `more_x`, `more_w` rows exist beyond the lane's first.
+    const int row0 = wave * 8 + (lane >> 3), kc = (lane & 7) ^ swz(row0);
+    const int row_x = m0 + row0 < a.M ? m0 + row0 : a.M - 1, row_w = n0 + row0 < a.N ? n0 + row0 : a.N - 1;
+    const int more_x = a.M - 1 - row_x, more_w = a.N - 1 - row_w;
+    const char* const src_x = xb + static_cast<int64_t>(row_x) * xrow + kc * 16;
+    const char* const src_w = wb + static_cast<int64_t>(row_w) * wrow + kc * 16;
+    auto source = [&](int d) {
+      constexpr int STEP = NW * 8;
+      const bool x = d * STEP < TM;
+      int more = x ? more_x : more_w;
+      asm volatile("" : "+v"(more));   // computed at each use: kept, the DEP sources would take 8 registers more
+      const int e = x ? d * STEP : d * STEP - TM;
+      const uint64_t rows = static_cast<uint32_t>(e < more ? e : more);
+      return (x ? src_x : src_w) + rows * static_cast<uint64_t>(x ? xrow : wrow);
+    };
     // K is a multiple of 64 elements, so the last stage of an 8-bit product may hold only
     // half a row (64 bytes).  Its deposits then fetch the valid half twice (addresses stay
     // inside the row) and the matrix groups of the missing half are skipped.
     const int KT = (kdim + TK - 1) / TK;
     const bool half_tail = (EB == 1) && (kdim % TK) != 0;   // 16-bit stages hold 64 elements: never
-    auto issue = [&](int kt, int lo, int hi) {   // deposits [lo, hi) of stage kt
-      unsigned char* st = s_buf + (kt % NST) * STAGE;
-      const int64_t kb = static_cast<int64_t>(kt) * ROW_B;
-      const bool tail = half_tail && kt == KT - 1;
+    const int back = (EB == 1 && kc >= CH / 2) ? ROW_B / 2 : 0;
+    auto issue = [&](int kt, int buf, int lo, int hi) {   // deposits [lo, hi) of stage kt into the buffer at byte `buf`
+      int64_t kb = static_cast<int64_t>(kt) * ROW_B;
+      if constexpr (EB == 1) kb -= (half_tail && kt == KT - 1) ? back : 0;
 #pragma unroll
       for (int d = 0; d < DEP; ++d)
-        if (d >= lo && d < hi) {
-          const char* g_src = src[d] + kb;
-          if (tail) {
-            const int c = (wave + NW * d) * 64 + lane;
-            if (((c % CH) ^ swz(c / CH)) >= CH / 2) g_src -= ROW_B / 2;
-          }
-          lds_deposit(g_src, st + (wave + NW * d) * 1024);
-        }
+        if (d >= lo && d < hi) lds_deposit(source(d) + kb, lds0 + static_cast<uint32_t>(buf + (wave + NW * d) * 1024));
     };
-    // Fragments of group gi of a stage: f[0 .. TI*NF) = A tiles, f[TI*NF ..) = B tiles.
-    auto load_group = [&](const unsigned char* st, int gi, i32x4 (&f)[(TI + TJ) * NF]) {
-#pragma unroll
-      for (int h = 0; h < NF; ++h) {
-        const int ch = (KIND == K_F8) ? ch_f[2 * gi + h] : ch_k[gi];
-#pragma unroll
-        for (int i = 0; i < TI; ++i) f[i * NF + h] = *reinterpret_cast<const i32x4*>(st + row_a + i * 32 * ROW_B + ch);
-#pragma unroll
-        for (int j = 0; j < TJ; ++j) f[(TI + j) * NF + h] = *reinterpret_cast<const i32x4*>(st + row_b + j * 32 * ROW_B + ch);
+    // Fragments of group gi of a stage: f[0 .. TI) = A tiles, f[TI ..) = B tiles.
+    using frag_t = std::conditional_t<KIND == K_F8, i32x8, i32x4>;
+    auto load_frag = [&](const unsigned char* row, int gi) {
+      if constexpr (KIND == K_F8) {
+        const i32x4 lo = *reinterpret_cast<const i32x4*>(row + ch_f[2 * gi]), hi = *reinterpret_cast<const i32x4*>(row + ch_f[2 * gi + 1]);
+        return __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
+      } else {
+        return *reinterpret_cast<const i32x4*>(row + ch_k[gi]);
       }
+    };
+    auto load_group = [&](const unsigned char* st, int gi, frag_t (&f)[TI + TJ]) {
+#pragma unroll
+      for (int i = 0; i < TI; ++i) f[i] = load_frag(st + row_a + i * 32 * ROW_B, gi);
+#pragma unroll
+      for (int j = 0; j < TJ; ++j) f[TI + j] = load_frag(st + row_b + j * 32 * ROW_B, gi);
     };
     // The matrix instructions of one group, with the deposits [lo, hi) of stage kt_dep
     // spread between them: a wave issues in order, so a burst of deposits (each occupies
     // the texture path for ~18 clocks, and all waves share it) would hold back the
     // matrix instructions behind it while the matrix pipe runs dry.
-    auto run_group = [&](const i32x4 (&f)[(TI + TJ) * NF], bool more, int kt_dep, int lo, int hi) {
+    // `then` (the next group's fragment reads) follows the first instruction: what that one waits for is its own
+    // group's fragments alone.
+    auto run_group = [&](const frag_t (&f)[TI + TJ], auto more_c, int kt_dep, int buf, int lo, int hi, auto then) {
 #pragma unroll
       for (int i = 0; i < TI; ++i)
 #pragma unroll
@@ -245,7 +243,8 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2, 2)))
           {
             const int m = i * TJ + j, n = hi - lo;
             __builtin_amdgcn_sched_barrier(0);
-            if (more) issue(kt_dep, lo + m * n / (TI * TJ), lo + (m + 1) * n / (TI * TJ));
+            if (m == 1) then();
+            if constexpr (decltype(more_c)::value) issue(kt_dep, buf, lo + m * n / (TI * TJ), lo + (m + 1) * n / (TI * TJ));
             __builtin_amdgcn_sched_barrier(0);
           }
           if constexpr (KIND == K_REF || KIND == K_GRID) {
@@ -253,54 +252,64 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2, 2)))
           } else if constexpr (KIND == K_I8) {
             acc[i][j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(f[i], f[TI + j], acc[i][j], 0, 0, 0);
           } else {
-            i32x8 fa, fb;
-#pragma unroll
-            for (int e = 0; e < 4; ++e) { fa[e] = f[i * 2][e]; fa[4 + e] = f[i * 2 + 1][e]; fb[e] = f[(TI + j) * 2][e]; fb[4 + e] = f[(TI + j) * 2 + 1][e]; }
             // format selectors 0 = E4M3 for both operands; block scales 2^0 (exponent byte 127)
-            acc[i][j] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(fa, fb, acc[i][j], 0, 0, 0, 127, 0, 127);
+            acc[i][j] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(f[i], f[TI + j], acc[i][j], 0, 0, 0, 127, 0, 127);
           }
         }
     };
-    // Wait until this wave's deposits of stage kt have landed; those of stage kt+1 (if
-    // there is one) may stay in flight.
-    auto wait_stage = [&](int kt) {
-      if (kt + 1 < KT) wait_deposits_but<DEP>();
-      else wait_deposits_but<0>();
-    };
-
-    // Prologue: AHEAD stages on their way.
-#pragma unroll
-    for (int s = 0; s < AHEAD; ++s)
-      if (s < KT) issue(s, 0, DEP);
-
-    // One K step: the barrier makes stage kt visible to everyone and tells everyone that
-    // stage kt-1 is no longer read, which is the buffer the deposits of stage kt+AHEAD go
-    // to.  Inside the step the fragments of group g+1 are requested before the matrix
+    // One K step.  Its last group is preceded by a barrier that makes stage kt+1 visible to everyone and tells
+    // everyone that stage kt is no longer read (its last fragments are in registers): the fragments of the next step's
+    // first group are requested there, ahead of a whole group of matrix instructions, and the deposits of
+    // stage kt+NST may begin to overwrite stage kt.  So no step starts by waiting for LDS, and up to three
+    // stages are on their way or unread.  Inside the step the fragments of group g+1 are requested before the matrix
     // instructions of group g are issued, and the deposits are spread over the groups so
     // that the texture path works while the matrix cores do.
-    auto step = [&](int kt, auto groups_c) {
+    // (Straight-line code: where the step had branches, the compiler moved matrix instructions down past them.)
+    frag_t f[2][TI + TJ];
+    int b0 = 0, b1 = STAGE, b2 = 2 * STAGE;   // buffers of the stages kt, kt + 1, kt + 2
+    static_assert(NST == 3, "three buffers in turn");
+    auto step = [&](int kt, auto groups_c, auto more2_c, auto more3_c) {   // moreN: there is a stage kt + N
       constexpr int GROUPS = decltype(groups_c)::value;
-      wait_stage(kt);
-      __builtin_amdgcn_s_barrier();
-      asm volatile("" ::: "memory");     // LDS reads below must not move above the barrier
-      const unsigned char* st = s_buf + (kt % NST) * STAGE;
-      const bool more = kt + AHEAD < KT;
-      i32x4 f[2][(TI + TJ) * NF];
-      load_group(st, 0, f[0]);
 #pragma unroll
       for (int gi = 0; gi < GROUPS; ++gi) {
-        if (gi + 1 < GROUPS) load_group(st, gi + 1, f[(gi + 1) & 1]);
-        run_group(f[gi & 1], more, kt + AHEAD, gi * DEP / GROUPS, (gi + 1) * DEP / GROUPS);
+        if (gi + 1 < GROUPS) {
+          run_group(f[gi & 1], more2_c, kt + 2, b2, (gi + 1) * DEP / NG, (gi + 2) * DEP / NG, [&] { load_group(s_buf + b0, gi + 1, f[(gi + 1) & 1]); });
+        } else {
+          // this wave's deposits of stage kt+1 have landed, its fragment reads are done; stage kt+2 may stay in flight
+          wait_deposits_and_reads<decltype(more2_c)::value ? DEP : 0>();
+          __builtin_amdgcn_s_barrier();
+          asm volatile("" ::: "memory");     // LDS reads below must not move above the barrier
+          // (after the last step: whatever the buffer holds, unused; a conditional load would keep f[0] twice)
+          run_group(f[gi & 1], more3_c, kt + 3, b0, 0, DEP / NG, [&] { load_group(s_buf + b1, 0, f[(gi + 1) & 1]); });
+        }
       }
+      const int b = b0;
+      b0 = b1;
+      b1 = b2;
+      b2 = b;
     };
-    const int KT_full = half_tail ? KT - 1 : KT;
-    for (int kt = 0; kt < KT_full; ++kt) step(kt, std::integral_constant<int, NG>{});
-    if constexpr (EB == 1)
-      if (half_tail) step(KT - 1, std::integral_constant<int, NG / 2>{});
-    // All deposits of this product have landed (the last wait allowed none in flight);
-    // the next product's prologue overwrites buffers only after everyone is here.
+    // Prologue: stages 0 and 1, and what a step before the first would have issued of stage 2.
+    issue(0, b0, 0, DEP);
+    if (KT > 1) {
+      issue(1, b1, 0, DEP);
+      wait_deposits_and_reads<DEP>();
+    } else {
+      wait_deposits_and_reads<0>();
+    }
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
+    if (KT > 2) issue(2, b2, 0, DEP / NG);
+    load_group(s_buf, 0, f[0]);
+    using full = std::integral_constant<int, NG>;
+    using yes = std::true_type;
+    using no = std::false_type;
+    for (int kt = 0; kt < KT - 3; ++kt) step(kt, full{}, yes{}, yes{});
+    if (KT > 2) step(KT - 3, full{}, yes{}, no{});
+    if (KT > 1) step(KT - 2, full{}, no{}, no{});
+    if (EB == 1 && half_tail) step(KT - 1, std::integral_constant<int, NG / 2>{}, no{}, no{});
+    else step(KT - 1, full{}, no{}, no{});
+    // The last step's barrier: all deposits of this product have landed and nobody reads them any more, so the
+    // next product's prologue may overwrite the buffers.
   };
 
   // ---- squared differences in fp64.  Accumulator value e of a lane in one 32x32 tile is
