@@ -94,6 +94,9 @@ int launch_tensor_quantize(const TensorParams& p, hipStream_t stream);
 
 // Enqueue the scale search.  Returns a mofq_status_t.
 int launch_sweep(const SweepParams& p, hipStream_t stream);
+// Search for groups of 64 and more (4-bit formats, 16-bit inputs) that does not score every element and candidate;
+// MOFQ_ERR_UNSUPPORTED (nothing enqueued) elsewhere.
+int launch_sweep_group_bits(const SweepParams& p, hipStream_t stream);
 // Sort-based search for per-channel 4-bit searches on 16-bit inputs; returns
 // MOFQ_ERR_UNSUPPORTED (nothing enqueued) outside that domain.
 int launch_sweep_sorted(const SweepParams& p, hipStream_t stream);

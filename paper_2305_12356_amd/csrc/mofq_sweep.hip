@@ -986,7 +986,7 @@ int launch_fmt(const SweepParams& p, const SweepArgs& a, hipStream_t st) {
 
 int launch_sweep(const SweepParams& p, hipStream_t st) {
   {
-    const int rc = launch_sweep_sorted(p, st);
+    const int rc = p.gran == MOFQ_PER_GROUP ? launch_sweep_group_bits(p, st) : launch_sweep_sorted(p, st);
     if (rc != MOFQ_ERR_UNSUPPORTED) return rc;
   }
   SweepArgs a{};

@@ -1,0 +1,451 @@
+// Group-wise scale search for the 4-bit formats on 16-bit weights: Algorithm 1's quantize_layer +
+// compute_error with the tensor-error metric (Section 4.1) per group of consecutive elements (Section 5),
+// over a table of clip ratios.  The formulation is that of the per-channel searches (mofq_sweep_sorted.hip):
+// the error of a candidate follows from the number and the sum of magnitudes of the elements below each of its
+// 7 level boundaries (INT4: 8), and the decision is monotone in the magnitude's bit pattern.  Scoring a group
+// of 128 directly (sweep_group_kernel) costs 9.6 vector instructions per element and candidate for the format
+// pair, 960 wave instructions per group with 50 ratios plus a second pass in fp64; a look-up costs 18,
+// whatever the group's size.
+//
+// One wave takes 64 / LPG groups, LPG = GROUP / 8 lanes each, and shares nothing with other waves:
+//   1. a bit per pattern that occurs, over the patterns between the smallest threshold of any candidate and
+//      the group's largest magnitude (fp16: about 5700 bits, bf16: 720), 32 to an LDS word, beside each word the number
+//      of distinct patterns before it;
+//   2. per distinct pattern the count and the sum of magnitudes (integers, in ulps of the first pattern) of its
+//      elements, and of its negative elements for INT4's extra level; prefix sums of both.  Count and
+//      sum share a word of 32 bits where they fit (those of the negative elements in the upper half of 64), else 64;
+//   3. a lane per candidate: the largest pattern below each boundary (an fp32 estimate and one exact decision), its
+//      rank among the distinct patterns (a population count), count and sum up to it: two LDS reads;
+//   4. the smallest error; where a second candidate is too close, or the error is not provably accurate
+//      (non-finite or nearly exact groups), all candidates of the group are scored element by element in fp64.
+//
+// Bound by vector issue: 1740 instructions per wave of four groups of 128 with 50 ratios (the direct kernel: 4360), 4
+// waves of 10 KB LDS per SIMD.  Measured, fp16 groups of 128, 50 ratios, the seven linears of a 7B block: 2740 us ->
+// 1246 us.
+#include <algorithm>
+#include <cmath>
+
+#include "mofq_search_common.h"
+
+namespace mofq {
+
+namespace {
+
+struct GroupArgs {
+  const void* w;
+  int64_t cols, ld, units;
+  int32_t scale_f16, n_clip;
+  int32_t nbin;                // patterns with a bit, a multiple of 32
+  UnitRecords rec;
+  float clip[MOFQ_MAX_CLIP];
+};
+
+// Level magnitudes m_0 .. m_7 (INT4: and 8 on the negative side), decision thresholds as in fill_levels
+constexpr float below(float x) { return __builtin_bit_cast(float, __builtin_bit_cast(uint32_t, x) - 1u); }   // x > 0
+template <int FMT> struct Levels {
+  static constexpr int N = FMT == MOFQ_INT4 ? 8 : 7;   // boundaries
+  static constexpr float mag(int b) {
+    constexpr float e2m1[8] = {0.0f, 0.5f, 1.0f, 1.5f, 2.0f, 3.0f, 4.0f, 6.0f};
+    return FMT == MOFQ_INT4 ? static_cast<float>(b) : e2m1[b < 8 ? b : 7];
+  }
+  static constexpr float thr(int b) {   // ties to the even code
+    const float mid = 0.5f * (mag(b) + mag(b + 1));
+    return b % 2 == 1 ? below(mid) : mid;
+  }
+  static constexpr float over(int b) { return static_cast<float>(thr(b) * (1.0 + 0x1p-21)); }
+  static constexpr uint32_t step2(int b) { return static_cast<uint32_t>(2.0f * (mag(b + 1) - mag(b))); }   // an integer
+  static constexpr int dg2q(int b) { return static_cast<int>(4.0f * (mag(b) * mag(b) - mag(b + 1) * mag(b + 1))); }
+};
+
+// count << B | sum
+template <bool WIDE> struct Cell {
+  using word = uint32_t;
+  static constexpr int B = 24;
+  MOFQ_DEV static uint32_t sum(word w) { return w & 0xFFFFFFu; }
+  MOFQ_DEV static int count(word w) { return static_cast<int>(w >> 24); }
+};
+template <> struct Cell<true> {
+  using word = uint64_t;
+  static constexpr int B = 48;
+  MOFQ_DEV static uint64_t sum(word w) { return w & 0xFFFFFFFFFFFFull; }
+  MOFQ_DEV static int count(word w) { return static_cast<int>(w >> 48); }
+};
+
+// unit_scale of the search: ratio * absmax over QMAX by one multiplication and Markstein's correction, which is the
+// correctly rounded quotient for 7 and 6 (all mantissas checked) wherever it is at least 2^-126; a non-finite
+// group comes out as 1 and is scored exactly later.
+template <int FMT> MOFQ_DEV float search_scale(float ra, bool f16) {
+  constexpr float d = Codec<FMT>::QMAX, r = 1.0f / d;
+  const float q = ra * r;
+  float s = __builtin_fmaf(__builtin_fmaf(-d, q, ra), r, q);
+  if (f16) s = round_fp16_clamped(s);
+  if (!(s >= 0x1p-126f)) s = 1.0f;
+  return s;
+}
+
+// what a lane of the wave wrote to LDS is there for the others: LDS operations of a wave are in order
+MOFQ_DEV void wave_fence() {
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_wave_barrier();
+}
+
+template <typename T> MOFQ_DEV uint32_t lds_address(T* p) {
+  return static_cast<uint32_t>(reinterpret_cast<uintptr_t>((__attribute__((address_space(3))) T*)p));
+}
+
+// over the LPG adjacent lanes of a group (8, 16 or 32)
+template <int LPG, typename T, typename Op> MOFQ_DEV T group_reduce(T v, Op op) {
+  auto dpp = [](T x, auto ctrl_c) {
+    constexpr int CTRL = decltype(ctrl_c)::value;
+    if constexpr (sizeof(T) == 8) return dpp_f64<CTRL>(x);
+    else if constexpr (std::is_same<T, float>::value) return dpp_f32<CTRL>(x);
+    else return static_cast<T>(dpp_i32<CTRL>(static_cast<int>(x)));
+  };
+  v = op(v, dpp(v, std::integral_constant<int, DPP_QUAD_XOR1>{}));
+  v = op(v, dpp(v, std::integral_constant<int, DPP_QUAD_XOR2>{}));
+  v = op(v, dpp(v, std::integral_constant<int, DPP_ROW_HALF_MIRROR>{}));
+  if constexpr (LPG >= 16) v = op(v, dpp(v, std::integral_constant<int, DPP_ROW_MIRROR>{}));
+  if constexpr (LPG >= 32) v = op(v, __shfl_xor(v, 16, 64));
+  return v;
+}
+// x of the lane that control CTRL names, 0 where there is none or ROW_MASK leaves the row out
+template <int CTRL, int ROW_MASK, typename T> MOFQ_DEV T dpp_or_zero(T x) {
+  auto half = [](uint32_t v) { return static_cast<uint32_t>(__builtin_amdgcn_update_dpp(0, static_cast<int>(v), CTRL, ROW_MASK, 0xf, false)); };
+  if constexpr (sizeof(T) == 4) return static_cast<T>(half(static_cast<uint32_t>(x)));
+  else return static_cast<T>(half(static_cast<uint32_t>(x))) | (static_cast<T>(half(static_cast<uint32_t>(static_cast<uint64_t>(x) >> 32))) << 32);
+}
+// exclusive prefix over the group's lanes
+template <int LPG, typename T> MOFQ_DEV T group_excl(T v, int l) {
+  T inc = v;
+  auto step = [&](auto ctrl_c, int d) {   // row_shr: inside rows of 16 lanes
+    const T o = dpp_or_zero<decltype(ctrl_c)::value, 0xf>(inc);
+    inc += (LPG >= 16 || l >= d) ? o : 0;
+  };
+  step(std::integral_constant<int, 0x111>{}, 1);
+  step(std::integral_constant<int, 0x112>{}, 2);
+  step(std::integral_constant<int, 0x114>{}, 4);
+  if constexpr (LPG >= 16) step(std::integral_constant<int, 0x118>{}, 8);
+  if constexpr (LPG >= 32) inc += dpp_or_zero<0x142, 0xa>(inc);   // row_bcast:15 into rows 1 and 3
+  return inc - v;
+}
+
+// Bytes of a group: bit words and ranks, then the words of the distinct patterns: one array with both
+// halves (narrow with INT4), or an array each.  Pieces of 16 bytes.
+template <int GROUP, bool WIDE, bool TAIL> struct GroupLayout {
+  static constexpr int LPG = GROUP / 8;
+  static constexpr bool JOINED = TAIL && !WIDE;
+  using store = std::conditional_t<WIDE || JOINED, uint64_t, uint32_t>;
+  static constexpr int STRIDE = sizeof(store);
+  static constexpr int CELLS = STRIDE * (GROUP + 16 / STRIDE);   // GROUP + 1 of them are used
+  static constexpr int entries(int nbin) { return ((nbin / 32 + 1 + LPG - 1) / LPG) | 1; }   // per lane; odd: lanes' pieces in different banks
+  static constexpr int table(int nbin) { return (entries(nbin) * LPG * 8 + 15) / 16 * 16; }
+  static constexpr int bytes(int nbin) { return table(nbin) + CELLS * (TAIL && !JOINED ? 2 : 1); }
+};
+
+template <typename In, int FA, int FB, int GROUP, bool WIDE>
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4))) void sweep_group_bits_kernel(const GroupArgs a) {
+  constexpr int NF = (FB >= 0) ? 2 : 1;
+  constexpr int FBX = (FB >= 0) ? FB : FA;
+  constexpr int LPG = GROUP / 8, GPW = 64 / LPG;
+  constexpr bool TAIL = FA == MOFQ_INT4 || FBX == MOFQ_INT4;
+  using Lay = GroupLayout<GROUP, WIDE, TAIL>;
+  using C = Cell<WIDE>;
+  using word = typename C::word;
+  typedef __attribute__((address_space(3))) u32x2 lds_u32x2;
+  typedef __attribute__((address_space(3))) word lds_word;
+
+  extern __shared__ __attribute__((aligned(16))) unsigned char s_dyn[];
+  __shared__ float s_clip[MOFQ_MAX_CLIP];
+  const int K = a.n_clip, nbin = a.nbin;
+  const int lane = threadIdx.x, l = lane % LPG, g = lane / LPG;
+  const int epl = Lay::entries(nbin);
+  unsigned char* const mine = s_dyn + g * Lay::bytes(nbin);
+  u32x2* const tbl = reinterpret_cast<u32x2*>(mine);           // bits, distinct patterns before them
+  using store = typename Lay::store;
+  store* const P = reinterpret_cast<store*>(mine + Lay::table(nbin));
+  store* const PN = P + Lay::CELLS / Lay::STRIDE;   // not where they are joined
+
+  const int64_t gpr = a.cols / GROUP;   // groups per row
+  int64_t unit = static_cast<int64_t>(blockIdx.x) * GPW + g;
+  const bool valid = unit < a.units;
+  if (!valid) unit = a.units - 1;
+  int64_t at0 = unit * GROUP;
+  if (a.ld != a.cols) {   // uniform
+    const int64_t row = unit / gpr;
+    at0 = row * a.ld + (unit - row * gpr) * GROUP;
+  }
+  const uint16_t* const src = static_cast<const uint16_t*>(a.w) + at0 + l * 8;
+  const bool f16 = a.scale_f16 != 0;
+
+  Raw8<In> raw;
+  raw.load(src, 0, 0);
+  for (int k = lane; k < K; k += 64) s_clip[k] = a.clip[k];
+  {
+    const u32x4 zero = {0u, 0u, 0u, 0u};
+    for (int i = l; i < Lay::bytes(nbin) / 16; i += LPG) reinterpret_cast<u32x4*>(mine)[i] = zero;
+  }
+  float x[8], amax = 0.0f;
+  raw.widen(x);
+  double en = 0.0;
+#pragma unroll
+  for (int i = 0; i < 8; ++i) {
+    amax = __builtin_fmaxf(amax, __builtin_fabsf(x[i]));
+    const double xd = static_cast<double>(x[i]);
+    en = __builtin_fma(xd, xd, en);
+  }
+  amax = group_reduce<LPG>(amax, [](float p, float q) { return __builtin_fmaxf(p, q); });
+  en = group_reduce<LPG>(en, [](double p, double q) { return p + q; });
+  // the counted patterns; whatever lies below them is on level 0 for every candidate
+  const int hmax = static_cast<int>(pattern_rtz<In>(__builtin_fminf(amax, 3.4028234e38f)));
+  const int lo = (hmax + 1 - nbin) > 0 ? hmax + 1 - nbin : 0;
+
+  // ---- 1. bits ----------------------------------------------------------------------------------------
+  wave_fence();
+  int at[8];
+#pragma unroll
+  for (int i = 0; i < 8; ++i) {
+    const int h = static_cast<int>((i % 2 == 0 ? raw.w[i / 2] : raw.w[i / 2] >> 16) & 0x7FFFu);
+    at[i] = min(h - lo, nbin - 1);   // (a non-finite element: the group's error is non-finite anyway)
+    if (at[i] >= 0)
+      __hip_atomic_fetch_or(reinterpret_cast<uint32_t*>(tbl + (at[i] >> 5)), 1u << (at[i] & 31), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+  }
+  wave_fence();
+  {
+    uint32_t n = 0;
+    for (int e = 0; e < epl; ++e) n += __builtin_popcount(tbl[l * epl + e][0]);
+    uint32_t base = group_excl<LPG>(n, l);
+    for (int e = 0; e < epl; ++e) {
+      const uint32_t bits = tbl[l * epl + e][0];
+      tbl[l * epl + e][1] = base;
+      base += __builtin_popcount(bits);
+    }
+  }
+  wave_fence();
+  // distinct patterns among the first n
+  const uint32_t tbl_at = lds_address(tbl), p_at = lds_address(P), pn_at = Lay::JOINED ? p_at + 4 : lds_address(PN);
+  auto rank = [&](uint32_t n) {
+    uint32_t e = n >> 5, r;
+    asm("" : "+v"(e));   // a shift-and-add
+    const u32x2 t = *(lds_u32x2*)static_cast<uintptr_t>((e << 3) + tbl_at);
+    asm("v_bcnt_u32_b32 %0, %1, %2" : "=v"(r) : "v"(__builtin_amdgcn_ubfe(t[0], 0u, n)), "v"(t[1]));   // (the width's low 5 bits count)
+    return r;
+  };
+  auto cell = [](uint32_t at, uint32_t r) { return *(lds_word*)static_cast<uintptr_t>(at + r * Lay::STRIDE); };
+
+  // ---- 2. count and sum per distinct pattern, prefixes -----------------------------------------------
+  constexpr int kUlp = std::is_same<In, F16>::value ? 25 : 134;   // exponent field of the pattern whose ulp is 1
+  const int e_lo = exponent_of<In>(lo);
+#pragma unroll
+  for (int i = 0; i < 8; ++i)
+    if (at[i] >= 0) {
+      const uint32_t d = rank(static_cast<uint32_t>(at[i]));
+      const word one = (static_cast<word>(1) << C::B) + static_cast<word>(static_cast<uint32_t>(__builtin_ldexpf(__builtin_fabsf(x[i]), kUlp - e_lo)));
+      const store neg = (f2u(x[i]) >> 31) != 0 ? static_cast<store>(one) : 0;
+      if constexpr (Lay::JOINED) {
+        __hip_atomic_fetch_add(P + d, one | (neg << 32), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+      } else {
+        __hip_atomic_fetch_add(P + d, one, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        if constexpr (TAIL) __hip_atomic_fetch_add(PN + d, neg, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+      }
+    }
+  wave_fence();
+  auto prefix = [&](store* cells) {   // (no carry from one half to the other)
+    store v[8], sum = 0;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) v[i] = cells[l * 8 + i];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      const store c = v[i];
+      v[i] = sum;
+      sum += c;
+    }
+    const store base = group_excl<LPG>(sum, l);
+#pragma unroll
+    for (int i = 0; i < 8; ++i) cells[l * 8 + i] = base + v[i];
+    if (l == LPG - 1) cells[GROUP] = base + sum;
+  };
+  prefix(P);
+  if constexpr (TAIL && !Lay::JOINED) prefix(PN);
+  wave_fence();
+  const word total = cell(p_at, GROUP);
+  const word n_total = TAIL ? cell(pn_at, GROUP) : 0;
+  const float v_lo = bits_to_float<In>(static_cast<uint32_t>(lo));
+  const double minus_2ulp = -2.0 * static_cast<double>(bits_to_float<In>(static_cast<uint32_t>(lo) + 1) - v_lo);   // ulps at lo
+
+  // ---- 3. candidates -----------------------------------------------------------------------------
+  double best[NF], second[NF];
+  int bk[NF];
+  bool bad = false;   // the group has to be scored exactly
+#pragma unroll
+  for (int f = 0; f < NF; ++f) {
+    best[f] = second[f] = __builtin_inf();
+    bk[f] = MOFQ_MAX_CLIP;
+  }
+  auto candidate = [&](auto fmt_c, int k, int f) {
+    constexpr int FMT = decltype(fmt_c)::value;
+    using Lv = Levels<FMT>;
+    const float s = search_scale<FMT>(s_clip[k < K ? k : K - 1] * amax, f16);
+    // 1 / s, correctly rounded (every s in [2^-126, 2^125] checked): the hardware's reciprocal and one Newton step
+    float inv = __builtin_amdgcn_rcpf(s);
+    inv = __builtin_fmaf(__builtin_fmaf(-s, inv, 1.0f), inv, inv);
+    uint32_t r[Lv::N];
+    // The largest pattern at or below the boundary (threshold t s): the pattern of t s (1 + 2^-21) rounded toward
+    // zero or the one before it, as the exact decision on the first tells; patterns above are beyond t s (1 + 2^-22), those
+    // below short of t s (1 - 2^-22), whatever the rounding of 1 / s and of the product.
+#pragma unroll
+    for (int q = 0; q < Lv::N; ++q) {
+      const uint32_t e = pattern_rtz<In>(Lv::over(q) * s);
+      const bool at_most = scaled<In>(e, inv) <= Lv::thr(q);
+      const int n = static_cast<int>(e) - lo + (at_most ? 1 : 0);
+      if (q == 0) bad |= k < K && (n < 0 || !(s <= 0x1p125f));   // the smallest threshold: uncounted elements might lie above it
+      r[q] = rank(min(static_cast<uint32_t>(n), static_cast<uint32_t>(nbin)));
+    }
+    // sums in half levels, and 4 times the sum of squares
+    word A = 0;
+    int b4 = static_cast<int>(4.0f * Lv::mag(7) * Lv::mag(7)) * C::count(total);
+#pragma unroll
+    for (int q = 0; q < 7; ++q) {
+      const word p = cell(p_at, r[q]);
+      if constexpr (WIDE) A += C::sum(p) * Lv::step2(q);
+      else asm("v_mad_u32_u24 %0, %1, %2, %0" : "+v"(A) : "v"(p), "n"(Lv::step2(q)));   // the low 24 bits
+      b4 = __mul24(C::count(p), Lv::dg2q(q)) + b4;
+    }
+    A = static_cast<word>(2.0f * Lv::mag(7)) * C::sum(total) - A;
+    if constexpr (FMT == MOFQ_INT4) {   // negative elements beyond the last boundary sit on -8
+      const word t = n_total - cell(pn_at, r[7]);
+      A += 2 * C::sum(t);
+      b4 = __mul24(C::count(t), 4 * (64 - 49)) + b4;
+    }
+    const double h = 0.5 * static_cast<double>(s);   // (exact: half of the smallest scales is subnormal in fp32)
+    const double v = __builtin_fma(h, __builtin_fma(h, static_cast<double>(b4), static_cast<double>(A) * minus_2ulp), en);
+    if (k < K) {
+      const bool better = v < best[f];
+      const double worse = better ? best[f] : v;
+      second[f] = worse < second[f] ? worse : second[f];
+      bk[f] = better ? k : bk[f];
+      best[f] = better ? v : best[f];
+    }
+  };
+  for (int k0 = 0; k0 < K; k0 += LPG) {
+    candidate(std::integral_constant<int, FA>{}, k0 + l, 0);
+    if constexpr (NF == 2) candidate(std::integral_constant<int, FBX>{}, k0 + l, NF - 1);
+  }
+
+  // ---- 4. winners.  Count and sum are exact and the error takes two roundings (filter_bounds). ---------
+  const bool exact = group_reduce<LPG>(bad ? 1 : 0, [](int p, int q) { return p | q; }) != 0;
+  auto finish = [&](auto fmt_c, int f) {
+    constexpr int FMT = decltype(fmt_c)::value;
+    auto least = [](double p, double q) { return __builtin_fmin(p, q); };
+    const double m = group_reduce<LPG>(best[f], least);
+    int k = group_reduce<LPG>(best[f] == m ? bk[f] : MOFQ_MAX_CLIP, [](int p, int q) { return min(p, q); });
+    const double m2 = group_reduce<LPG>(bk[f] == k ? second[f] : best[f], least);   // candidates of one lane are its own
+    const FilterBounds fb = filter_bounds<GROUP, true, 4>(en, 0.0, 0.0, 0.0, 0.0);
+    double err = m;
+    const bool sure = !exact && m2 > m + fb.margin && fb.beta <= 0x1p-34 * m;   // false for a zero or non-finite error
+    if (__builtin_amdgcn_ballot_w64(!sure && valid) != 0) {
+      raw.load(src, 0, 0);
+      float v[8];
+      raw.widen(v);
+      double eb = __builtin_inf();
+      int ek = -1;
+      uint32_t carry = 0;
+      for (int c = 0; c < K; ++c) {
+        const float s = unit_scale(amax, s_clip[c], Codec<FMT>::QMAX, f16);
+        const float inv = 1.0f / s;
+        const double sd = static_cast<double>(s);
+        double acc = 0.0;
+#pragma unroll
+        for (int i = 0; i < 8; i += 2) score2_f64<FMT>(acc, v[i], v[i + 1], inv, sd, carry);
+        acc = group_reduce<LPG>(acc, [](double p, double q) { return p + q; });
+        if (acc < eb) { eb = acc; ek = c; }
+      }
+      if (!sure) {
+        err = ek < 0 ? __builtin_nan("") : eb;   // only on non-finite input
+        k = ek < 0 ? 0 : ek;
+      }
+    }
+    if (valid && l == 0) {
+      a.rec.scale[f][unit] = unit_scale(amax, s_clip[k], Codec<FMT>::QMAX, f16);
+      a.rec.clip[f][unit] = k;
+      a.rec.err[f][unit] = err;
+    }
+  };
+  finish(std::integral_constant<int, FA>{}, 0);
+  if constexpr (NF == 2) finish(std::integral_constant<int, FBX>{}, NF - 1);
+  if (valid && l == 0 && a.rec.energy) a.rec.energy[unit] = en;
+}
+
+template <typename In, int FA, int FB, int GROUP>
+int launch_size(const GroupArgs& a, hipStream_t st) {
+  constexpr int GPW = 64 / (GROUP / 8), MANT = Pattern<In>::MANT;
+  constexpr bool TAIL = FA == MOFQ_INT4 || FB == MOFQ_INT4;
+  // a magnitude is below 2^(MANT + 1 + span) ulps of the first pattern: sums of a group below 2^24, counts below 2^8
+  const int span = (a.nbin + (1 << MANT) - 1) >> MANT;
+  const dim3 grid(static_cast<unsigned>((a.units + GPW - 1) / GPW));
+  if (GROUP <= 128 && ((GROUP - 1) >> (24 - (MANT + 1 + span))) == 0 && MANT + 1 + span < 24) {
+    const size_t lds = GPW * static_cast<size_t>(GroupLayout<GROUP, false, TAIL>::bytes(a.nbin));
+    hipLaunchKernelGGL((sweep_group_bits_kernel<In, FA, FB, GROUP, false>), grid, dim3(64), lds, st, a);
+  } else {
+    const size_t lds = GPW * static_cast<size_t>(GroupLayout<GROUP, true, TAIL>::bytes(a.nbin));
+    hipLaunchKernelGGL((sweep_group_bits_kernel<In, FA, FB, GROUP, true>), grid, dim3(64), lds, st, a);
+  }
+  return hip_status(hipGetLastError());
+}
+
+template <typename In, int FA, int FB>
+int launch_fmt(const SweepParams& p, const GroupArgs& a, hipStream_t st) {
+  switch (p.group) {
+    case 64: return launch_size<In, FA, FB, 64>(a, st);
+    case 128: return launch_size<In, FA, FB, 128>(a, st);
+    case 256: return launch_size<In, FA, FB, 256>(a, st);
+  }
+  return MOFQ_ERR_UNSUPPORTED;
+}
+
+template <typename In>
+int launch_type(const SweepParams& p, const GroupArgs& a, hipStream_t st) {
+  const int fa = p.fmt[0], fb = p.n_fmt == 2 ? p.fmt[1] : -1;
+  if (fa == MOFQ_INT4 && fb == MOFQ_FP4_E2M1) return launch_fmt<In, MOFQ_INT4, MOFQ_FP4_E2M1>(p, a, st);
+  if (fa == MOFQ_INT4 && fb == -1) return launch_fmt<In, MOFQ_INT4, -1>(p, a, st);
+  if (fa == MOFQ_FP4_E2M1 && fb == -1) return launch_fmt<In, MOFQ_FP4_E2M1, -1>(p, a, st);
+  return MOFQ_ERR_UNSUPPORTED;
+}
+
+// From how many clip ratios on this kernel is the faster one: building the table costs what scoring so many
+// candidates costs.  4096 x 4096 elements, INT4 against E2M1, scored directly / by look-up, us: fp16 groups of 128 with
+// 8 ratios 76 / 76, 12: 92 / 77, 50: 253 / 120; of 64 with 16: 116 / 122, 24: 151 / 138 (a table per
+// group, whatever its size); of 256 (64-bit words) with 16: 110 / 110, 24: 144 / 109; bf16 (a table of an
+// eighth): 64 with 8: 78 / 67, 128 with 8: 74 / 62, 256 with 16: 109 / 99.  One format alone shares the table with none:
+// INT4, groups of 128, fp16 with 16: 67.5 / 65, bf16 with 12: 58 / 53; E2M1 with 12: 59 / 57.
+int min_clip(const SweepParams& p) {
+  const bool f16 = p.dtype == MOFQ_F16;
+  const int pair = p.group == 64 ? (f16 ? 24 : 8) : (p.group == 128 ? (f16 ? 12 : 8) : (f16 ? 18 : 16));
+  return p.n_fmt == 2 ? pair : (p.fmt[0] == MOFQ_INT4 ? pair * 5 / 2 : pair * 4 / 3);
+}
+
+}  // namespace
+
+int launch_sweep_group_bits(const SweepParams& p, hipStream_t st) {
+  if (p.gran != MOFQ_PER_GROUP || (p.dtype != MOFQ_F16 && p.dtype != MOFQ_BF16) || p.n_clip < min_clip(p)) return MOFQ_ERR_UNSUPPORTED;
+  GroupArgs a{};
+  a.w = p.w;
+  a.cols = p.cols;
+  a.ld = p.ld;
+  a.units = mofq_num_units(p.rows, p.cols, p.gran, p.group);
+  if (a.units <= 0) return MOFQ_ERR_INVALID_ARG;
+  a.scale_f16 = p.scale_f16;
+  a.n_clip = p.n_clip;
+  a.rec = p.rec;
+  float r_min = INFINITY;
+  for (int k = 0; k < p.n_clip; ++k) {
+    if (!(p.clip[k] > 0.0f) || !std::isfinite(p.clip[k])) return MOFQ_ERR_UNSUPPORTED;
+    r_min = std::fmin(r_min, p.clip[k]);
+    a.clip[k] = p.clip[k];
+  }
+  const bool e2m1 = p.fmt[0] == MOFQ_FP4_E2M1 || (p.n_fmt == 2 && p.fmt[1] == MOFQ_FP4_E2M1);
+  a.nbin = (hist_bins((e2m1 ? 24.0 : 14.0) / r_min, p.dtype == MOFQ_F16 ? 1024 : 128) + 31) / 32 * 32;
+  if (a.nbin > 8192) return MOFQ_ERR_UNSUPPORTED;   // 2 KB of bits per group
+  return p.dtype == MOFQ_F16 ? launch_type<F16>(p, a, st) : launch_type<BF16>(p, a, st);
+}
+
+}  // namespace mofq

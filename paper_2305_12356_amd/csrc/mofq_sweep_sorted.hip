@@ -675,18 +675,6 @@ int launch_fmt(const SweepParams& p, const SortedArgs& a, int64_t total_rows, hi
   return MOFQ_ERR_UNSUPPORTED;
 }
 
-// How many bit patterns lie between a threshold t = c * amax and amax at most: a pattern is
-// (exponent, mantissa) read as an integer, i.e. PPB * (log2 of the value + a term in [0, 0.0861))
-// up to a constant, so two values a factor 1 / c apart are at most PPB * (log2(1 / c) + 0.0861) + 1
-// patterns apart (fewer among subnormals).  The scale's own roundings move a threshold by less than
-// a pattern; the kernel rounds the first counter's pattern up to a multiple of 8.
-int hist_bins(double ratio_amax_over_threshold, int ppb) {
-  const double lg = std::log2(ratio_amax_over_threshold);
-  const double bins = ppb * ((lg > 0.0 ? lg : 0.0) + 0.09) + 24.0;
-  if (!(bins < 1.0e6)) return 1 << 20;
-  return (static_cast<int>(std::ceil(bins)) + 7) / 8 * 8;
-}
-
 // Sizes of the histograms for this configuration, or 0 where they would not fit (then the
 // sorting kernel runs).  They depend on the formats, the clip ratios and the dtype only.
 void hist_sizes(const SweepParams& p, SortedArgs& a) {

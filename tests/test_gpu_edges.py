@@ -80,3 +80,29 @@ def test_bf16_search_writes_codes(mq):  # noqa: F811
     w[:40, 5] = 7.0
     check_tensor(mq, w, PAIR8, orc.PER_CHANNEL, mi.clip_ratios(40), label="bf16-ahead-8")
     check_tensor(mq, w, PAIR4, orc.PER_CHANNEL, mi.clip_ratios(40), label="bf16-ahead-4")
+
+
+# groups searched through ranks of bit patterns: one and several rounds of candidates, 32- and 64-bit words,
+# rows that lie apart, a last wave that is not full; groups of zeros, of equal or all-negative elements, of
+# powers of two over the whole range, nearly exact ones, with subnormal scales, with one huge element
+@pytest.mark.parametrize("dtype", [torch.float16, torch.bfloat16])
+@pytest.mark.parametrize("group,n_clip,lo_clip,f16,pad", [
+    (64, 24, 0.5, True, 0), (64, 33, 0.2, False, 64), (128, 12, 0.9, False, 0), (128, 50, 0.5, True, 128),
+    (128, 128, 0.02, False, 0), (256, 18, 0.5, True, 0), (256, 45, 0.3, False, 256)])
+def test_group_pattern_ranks(mq, dtype, group, n_clip, lo_clip, f16, pad):  # noqa: F811
+    w = _strided(13, 7 * group, pad, n_clip, dtype)
+    g = torch.Generator(device=DEV).manual_seed(n_clip)
+    v = [w[r, (r % 3) * group:(r % 3 + 1) * group] for r in range(13)]
+    v[0][:] = 0.0
+    v[1][:] = 0.75
+    v[2][:] = -v[2].abs()
+    v[3][:] = torch.exp2(torch.randint(-13, 3, (group,), generator=g, device=DEV).float()).to(dtype)
+    v[4][:] = torch.randint(-7, 8, (group,), generator=g, device=DEV).to(dtype)
+    v[5][:] = v[5] * 2.0 ** -11
+    v[6][:] = (v[6].float() * (2.0 ** -17 if dtype == torch.float16 else 2.0 ** -119)).to(dtype)
+    v[7][3] = -6.0e4
+    v[8][:] = -1.5
+    v[9][5:] = 0.0
+    ratios = [lo_clip + (1.0 - lo_clip) * (i + 1) / n_clip for i in range(n_clip)]
+    for cands in (PAIR4, [orc.INT4], [orc.FP4_E2M1]):
+        check_tensor(mq, w, cands, orc.PER_GROUP, ratios, group, f16, label="group-rank-edge")
