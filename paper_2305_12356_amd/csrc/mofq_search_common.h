@@ -185,11 +185,62 @@ MOFQ_DEV void wave_argmin_dpp(double& v, int& idx) {
 // m and shift of the group at pattern p (subnormals: the first normal binade's ulp, no leading bit)
 template <typename In> MOFQ_DEV void mant_shift(uint32_t p, int e_lo, uint32_t& m, uint32_t& shift) {
   constexpr int MANT = Pattern<In>::MANT;
-  const int e = static_cast<int>(p >> MANT);
-  m = (p & ((1u << MANT) - 1u)) | (static_cast<uint32_t>(e > 0 ? 1 : 0) << MANT);
-  shift = static_cast<uint32_t>((e > 1 ? e : 1) - e_lo);
+  const uint32_t e1 = __builtin_elementwise_sub_sat(p >> MANT, 1u);                   // exponent field less one, 0 for subnormals
+  // mantissa with its leading bit: p - (e1 << MANT) (as a shift and a subtraction it costs one instruction more)
+  asm("v_mad_i32_i24 %0, %1, %2, %3" : "=v"(m) : "v"(e1), "s"(-(1 << MANT)), "v"(p));
+  int first = __builtin_amdgcn_readfirstlane(e_lo - 1);
+  asm("" : "+s"(first));   // opaque: one subtraction
+  shift = e1 - static_cast<uint32_t>(first);
 }
 template <typename In> MOFQ_DEV int exponent_of(int p) { const int e = p >> Pattern<In>::MANT; return e > 1 ? e : 1; }
+
+// ---- counting a row's bit patterns ---------------------------------------------------------------------
+typedef __attribute__((address_space(3))) uint32_t lds_u32;
+typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
+
+// One counter (16 bits, two per word) at LDS byte address base + byte_off (a multiple of 4) more: the low half
+// of the word for an even counter number, else the high half.
+MOFQ_DEV void count_at(uint32_t base, uint32_t byte_off, uint32_t parity16, uint32_t one = 1u) {
+  // 1 or 65536: the shift takes the low five bits of its operand, which is 16 times the counter number
+  __hip_atomic_fetch_add((lds_u32*)static_cast<uintptr_t>(base + byte_off), one << (parity16 & 31u), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+}
+
+// Counters of both halves of a word of counter numbers below 8192 (negative halves: none).
+// `one`: 1 in a register of its own (the half-selecting shift takes no constant).
+MOFQ_DEV void count_pair(uint32_t base, i16x2 b2, uint32_t one) {
+  uint32_t off2 = __builtin_bit_cast(uint32_t, b2 << static_cast<short>(1)) & 0xFFFCFFFCu;
+  uint32_t par2 = __builtin_bit_cast(uint32_t, b2 << static_cast<short>(4));
+  // opaque: the halves are then selected by the instructions that use them instead of masked first
+  asm("" : "+v"(off2), "+v"(par2));
+  if (b2[0] >= 0) count_at(base, off2 & 0xFFFFu, par2, one);
+  if (__builtin_bit_cast(int, b2) >= 0) count_at(base, off2 >> 16, par2 >> 16, one);
+}
+
+// The counters of a row's negative elements at or above pattern tlo, counted apart from the others.  They are
+// few (the boundary lies half way up to the row's largest magnitude), but among the 128 elements of a wave's
+// word there is nearly always one: as a branch of the counting loop they cost every word 15 instructions.
+// So the loop only notes them, 3 instructions per word, and they are read again (they come from
+// L2) once the loop is done: a lane has two at most in most rows.
+// A mask holds the words of four 16-byte chunks: bits 0 and 16 the last word's halves.
+MOFQ_DEV void note_negative(uint32_t& mask, uint32_t w, int tlo) {
+  const unsigned short below = static_cast<unsigned short>(0x8000 + tlo - 1);
+  const u16x2 below2 = {below, below}, one = {1, 1};
+  uint32_t over = __builtin_bit_cast(uint32_t, __builtin_elementwise_sub_sat(__builtin_bit_cast(u16x2, w), below2));   // sign and magnitude as one number
+  asm("" : "+v"(over));   // opaque: else two comparisons and selects
+  mask = (mask << 1) | __builtin_bit_cast(uint32_t, __builtin_elementwise_min(__builtin_bit_cast(u16x2, over), one));
+}
+// chunk0: element number of the lane's first chunk of the mask; its chunks are `stride` elements apart.
+template <int WORDS>
+MOFQ_DEV void count_noted(uint32_t mask, const uint16_t* src, int chunk0, int stride, int tlo, int ntbin, uint32_t at) {
+  while (mask) {
+    const uint32_t bit = 31u - static_cast<uint32_t>(__builtin_clz(mask));
+    mask &= ~(1u << bit);
+    const uint32_t word = (WORDS - 1) - (bit & 15u);
+    const uint32_t e = static_cast<uint32_t>(chunk0) + __umul24(word >> 2, static_cast<uint32_t>(stride)) + 2 * (word & 3u) + (bit >> 4);
+    const int b = min((src[e] & 0x7FFF) - tlo, ntbin - 1);
+    count_at(at, static_cast<uint32_t>(2 * b) & ~3u, static_cast<uint32_t>(b) << 4);
+  }
+}
 
 
 // ---- what follows the filtered errors of a row: shortlist, exact re-score, the winners -----------------

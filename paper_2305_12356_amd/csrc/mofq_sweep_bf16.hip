@@ -27,8 +27,6 @@ constexpr int kThreads = 256, kNW = kThreads / 64;
 constexpr int kMaxBins = 4096, kMaxTailBins = 1024;
 constexpr int kRuns = 16;   // runs of 8 boundaries of an 8-bit format
 
-typedef __attribute__((address_space(3))) uint32_t lds_u32;
-
 // Decision thresholds of the 8-bit formats' boundaries: level magnitude m_b or below <=> t <= thr; est: a
 // shade below (counters_below).  Run r, boundary i between code 8 r + i and the next; ties to the even code.
 struct Boundary {
@@ -86,20 +84,6 @@ template <> struct Runs<MOFQ_FP8_E4M3> {
   MOFQ_DEV static double spacing(int r) { return __builtin_bit_cast(double, static_cast<uint64_t>(1023 - 9 + (r > 0 ? r - 1 : 0)) << 52); }   // 2^(max(r, 1) - 10)
   MOFQ_DEV static int base(int r) { return r > 0 ? 8 : 0; }
 };
-
-// One counter (16 bits, two per word) of the byte offset 2 b more, b = counter number in the low bits of `b16`.
-MOFQ_DEV void count_at(uint32_t base, uint32_t byte_off, uint32_t parity16) {
-  // 1 or 65536: the shift takes the low five bits of its operand, which is 16 times the counter number
-  __hip_atomic_fetch_add((lds_u32*)static_cast<uintptr_t>(base + byte_off), 1u << (parity16 & 31u), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-}
-
-// Counters of both halves of a word of counter numbers (negative halves: none).
-MOFQ_DEV void count_pair(uint32_t base, i16x2 b2) {
-  const uint32_t off2 = __builtin_bit_cast(uint32_t, b2 << static_cast<short>(1));
-  const uint32_t par2 = __builtin_bit_cast(uint32_t, b2 << static_cast<short>(4));
-  if (b2[0] >= 0) count_at(base, off2 & 0xFFFCu, par2);
-  if (__builtin_bit_cast(int, b2) >= 0) count_at(base, (off2 >> 16) & 0xFFFCu, par2 >> 16);
-}
 
 // Exclusive prefixes over the counters in place of P[0 .. nbin], packed count << 48 | sum.  Thread `id` of
 // NW waves takes the counters [id pp, (id + 1) pp), pp even.  NW > 1: by the whole workgroup, with barriers.
@@ -234,31 +218,25 @@ void sweep_bf16_kernel(const SortedArgs a) {
   const int tlo = (((hmax + 1 - ntbin) > 0 ? (hmax + 1 - ntbin) : 0) + 7) & ~7;
   {
     const i16x2 lo2 = {static_cast<short>(lo), static_cast<short>(lo)};
-    const i16x2 tlo2 = {static_cast<short>(tlo), static_cast<short>(tlo)};
     const i16x2 last2 = {static_cast<short>(nbin - 1), static_cast<short>(nbin - 1)};
-    const i16x2 tlast2 = {static_cast<short>(ntbin - 1), static_cast<short>(ntbin - 1)};
     const uint32_t at = static_cast<uint32_t>(reinterpret_cast<uintptr_t>((lds_u32*)counters));
     const uint32_t tat = static_cast<uint32_t>(reinterpret_cast<uintptr_t>((lds_u32*)tcounters));
+    uint32_t one = 1;
+    asm("" : "+v"(one));
 #pragma unroll
-    for (int j = 0; j < CH; ++j)
+    for (int j0 = 0; j0 < CH; j0 += 4) {
+      constexpr int PART = CH < 4 ? CH : 4;
+      uint32_t noted = 0;
 #pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const uint32_t w = raw[j].w[i];
-        const i16x2 h2 = __builtin_bit_cast(i16x2, w & 0x7FFF7FFFu);
-        // padding (zero) and whatever lies below every threshold has no counter
-        count_pair(at, __builtin_elementwise_min(h2 - lo2, last2));
-        if constexpr (ANY_TAIL) {
-          const i16x2 t2 = h2 - tlo2;
-          // halves that are negative elements at or above the first pattern of theirs
-          const uint32_t q2 = w & ~__builtin_bit_cast(uint32_t, t2) & 0x80008000u;
-          if (q2 != 0) {
-            const i16x2 none = {-1, -1};
-            const uint32_t keep = sign_fill2(q2);
-            const i16x2 b2 = __builtin_elementwise_min(t2, tlast2);
-            count_pair(tat, __builtin_bit_cast(i16x2, (__builtin_bit_cast(uint32_t, b2) & keep) | (__builtin_bit_cast(uint32_t, none) & ~keep)));
-          }
+      for (int j = j0; j < j0 + PART; ++j)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const uint32_t w = j < CH ? raw[j].w[i] : 0;
+          if (j < CH) count_pair(at, __builtin_elementwise_min(__builtin_bit_cast(i16x2, w & 0x7FFF7FFFu) - lo2, last2), one);   // padding (zero) and whatever lies below every threshold has no counter
+          if constexpr (ANY_TAIL) note_negative(noted, w, tlo);
         }
-      }
+      if constexpr (ANY_TAIL) count_noted<PART * 4>(noted, src, (j0 * kThreads + tid) * 8, kThreads * 8, tlo, ntbin, tat);
+    }
   }
   __syncthreads();
 

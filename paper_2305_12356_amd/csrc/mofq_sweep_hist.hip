@@ -21,6 +21,12 @@
 // Where the counted patterns span few enough binades, sums of magnitudes are 32-bit integers in units
 // of the first counted pattern's ulp (exact, and a third of the instructions of fp64 sums); else fp64.
 //
+// Bound by vector issue: the vector ALU executes for 95 % of a launch, 1030 instructions per wave on
+// rows of 4096 elements (INT4 / E2M1, 100 ratios): 200 to count, 180 for the prefixes, 310 for the
+// look-ups.  Two blocks of the 65B shape 2295 -> 2222 us, eight of the 7B shape 3094 -> 2957 us with the
+// negative elements' counting behind the loop (note_negative), the halves of a word selected by
+// the instructions that use them (count_pair) and one weighted sum per group (count8).
+//
 // Filter, shortlist and exact fp64 re-score are those of the sorting kernel; the re-score reads
 // the row again.  With AheadCodes the row's codes are written at the end, from a further read that
 // comes from L2.
@@ -30,7 +36,6 @@ namespace mofq {
 
 namespace {
 
-typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
 MOFQ_DEV uint32_t dot2(uint32_t a, uint32_t b, uint32_t c) {   // a.lo b.lo + a.hi b.hi + c
   return __builtin_amdgcn_udot2(__builtin_bit_cast(u16x2, a), __builtin_bit_cast(u16x2, b), c, false);
 }
@@ -49,15 +54,19 @@ struct Wide {
   uint32_t cnt, unused;
 };
 
-// count and index-weighted count of eight counters, two per word
-MOFQ_DEV void count8(const u32x4 w, uint32_t& c, uint32_t& wsum) {
+// count and index-weighted count of eight counters, two per word.  JOINT: rows of up to 4096 elements, whose
+// weighted count stays below 7 * 2^12 < 2^15: one sum with the weights 2^15 + i (two instructions fewer).
+template <bool JOINT> MOFQ_DEV void count8(const u32x4 w, uint32_t& c, uint32_t& wsum) {
+  constexpr uint32_t base = JOINT ? 0x80008000u : 0u;
+  uint32_t s = 0;
   c = 0;
-  wsum = 0;
 #pragma unroll
   for (int j = 0; j < 4; ++j) {
-    c = dot2(w[j], 0x00010001u, c);
-    wsum = dot2(w[j], static_cast<uint32_t>(2 * j) | (static_cast<uint32_t>(2 * j + 1) << 16), wsum);
+    if constexpr (!JOINT) c = dot2(w[j], 0x00010001u, c);
+    s = dot2(w[j], base + (static_cast<uint32_t>(2 * j) | (static_cast<uint32_t>(2 * j + 1) << 16)), s);
   }
+  if constexpr (JOINT) c = s >> 15;
+  wsum = JOINT ? s & 0x7FFFu : s;
 }
 
 // Count and magnitude sum of the elements in the histogram's first n1 counters, 0 <= n1 <= nbin:
@@ -65,23 +74,25 @@ MOFQ_DEV void count8(const u32x4 w, uint32_t& c, uint32_t& wsum) {
 // bytes after the counters, which are inside the workgroup's LDS, and masks them all).
 // keep[c]: masks of the first c of a group's eight counters (a table in LDS: one read instead of
 // sixteen compare-and-select instructions).
-template <typename In>
+template <typename In, bool JOINT>
 MOFQ_DEV void hist_prefix(const uint32_t* hist, const Narrow* rec, const u32x4* keep, int, uint32_t n1, uint32_t& C, uint32_t& S) {
-  const u32x4 w = *reinterpret_cast<const u32x4*>(hist + 4 * (n1 >> 3));
+  uint32_t g = n1 >> 3;
+  asm("" : "+v"(g));   // opaque: both addresses are one shift-add of g (of n1 they would be a shift, a mask and an addition)
+  const u32x4 w = *reinterpret_cast<const u32x4*>(hist + 4 * g);
   const u32x4 m = keep[n1 & 7];   // 16-bit masks, two per word
-  const Narrow r = rec[n1 >> 3];
+  const Narrow r = rec[g];
   uint32_t cin, win;
-  count8(w & m, cin, win);
+  count8<JOINT>(w & m, cin, win);
   S = r.sum + ((__umul24((r.word >> 16) & 0x7FFu, cin) + win) << (r.word >> 27));
   C = (r.word & 0xFFFFu) + cin;
 }
-template <typename In>
+template <typename In, bool JOINT>
 MOFQ_DEV void hist_prefix(const uint32_t* hist, const Wide* rec, const u32x4* keep, int lo, uint32_t n1, uint32_t& C, double& S) {
   const int g = static_cast<int>(n1 >> 3);
   const u32x4 w = *reinterpret_cast<const u32x4*>(hist + 4 * g);
   const u32x4 m = keep[n1 & 7];
   uint32_t cin, win;
-  count8(w & m, cin, win);
+  count8<JOINT>(w & m, cin, win);
   const float v0 = bits_to_float<In>(static_cast<uint32_t>(lo + 8 * g));
   const float ulp = bits_to_float<In>(static_cast<uint32_t>(lo + 8 * g + 1)) - v0;   // exact
   double s = rec[g].sum;
@@ -91,16 +102,16 @@ MOFQ_DEV void hist_prefix(const uint32_t* hist, const Wide* rec, const u32x4* ke
 }
 
 // One group's own count and sum, and its record.
-template <typename In> MOFQ_DEV void group_sum(const Narrow*, u32x4 w, int lo, int g, uint32_t& c, uint32_t& s, uint32_t& aux) {
+template <typename In, bool JOINT> MOFQ_DEV void group_sum(const Narrow*, u32x4 w, int lo, int g, uint32_t& c, uint32_t& s, uint32_t& aux) {
   uint32_t wsum, m, shift;
-  count8(w, c, wsum);
+  count8<JOINT>(w, c, wsum);
   mant_shift<In>(static_cast<uint32_t>(lo + 8 * g), exponent_of<In>(lo), m, shift);
   s = (__umul24(m, c) + wsum) << shift;
   aux = (m << 16) | (shift << 27);
 }
-template <typename In> MOFQ_DEV void group_sum(const Wide*, u32x4 w, int lo, int g, uint32_t& c, double& s, uint32_t& aux) {
+template <typename In, bool JOINT> MOFQ_DEV void group_sum(const Wide*, u32x4 w, int lo, int g, uint32_t& c, double& s, uint32_t& aux) {
   uint32_t wsum;
-  count8(w, c, wsum);
+  count8<JOINT>(w, c, wsum);
   const float v0 = bits_to_float<In>(static_cast<uint32_t>(lo + 8 * g));
   const float ulp = bits_to_float<In>(static_cast<uint32_t>(lo + 8 * g + 1)) - v0;
   s = __builtin_fma(static_cast<double>(ulp), static_cast<double>(wsum), static_cast<double>(v0) * static_cast<double>(c));
@@ -116,7 +127,7 @@ MOFQ_DEV double wave_excl_scan(double v, double& total) { return wave_excl_scan_
 // The records of all groups: lane `id` of `lanes` takes the groups [id gp, (id + 1) gp), gp <= GPMAX.
 // NW > 1: by all threads of the workgroup (three barriers); NW = 1: by one wave alone, without
 // barriers, for a short histogram: the caller's next barrier publishes the result.
-template <typename In, int NW, int GPMAX, typename Rec>
+template <typename In, bool JOINT, int NW, int GPMAX, typename Rec>
 MOFQ_DEV void hist_records(const uint32_t* hist, Rec* rec, int lo, int ng, uint32_t* s_wc, typename Rec::sum_t* s_ws) {
   using sum_t = typename Rec::sum_t;
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -133,7 +144,7 @@ MOFQ_DEV void hist_records(const uint32_t* hist, Rec* rec, int lo, int ng, uint3
     s8[i] = 0;
     aux[i] = 0;
     if (i < gp && g < ng) {
-      group_sum<In>(rec, *reinterpret_cast<const u32x4*>(hist + 4 * g), lo, g, c8[i], s8[i], aux[i]);
+      group_sum<In, JOINT>(rec, *reinterpret_cast<const u32x4*>(hist + 4 * g), lo, g, c8[i], s8[i], aux[i]);
       ct += c8[i];
       st += s8[i];
     }
@@ -170,6 +181,8 @@ void sweep_hist_kernel(const SortedArgs a) {
   constexpr bool ANY_TAIL = TAIL_A || TAIL_B;
   constexpr int GPMAX = kHistMaxBins / 8 / THREADS;   // groups per thread at most
 
+  constexpr bool JOINT = CH <= 2;   // 4096 elements at most
+  static_assert(CH > 2 || CH * THREADS * 8 <= 4096, "count8");
   using sum_t = typename Rec::sum_t;
 
   // dynamic LDS: [records | the short histogram's | counters | the short histogram's | 16 bytes]
@@ -264,52 +277,32 @@ void sweep_hist_kernel(const SortedArgs a) {
 
   // ---- the histogram covers the nbin patterns up to the largest magnitude's (a non-finite
   // element lands in the last counter: the row's error is non-finite anyway) --------------------
-  const int hmax = static_cast<int>(pattern_rtz<In>(__builtin_fminf(amax, 3.4028234e38f)));   // exact for a finite amax
+  const int hmax = __builtin_amdgcn_readfirstlane(static_cast<int>(pattern_rtz<In>(__builtin_fminf(amax, 3.4028234e38f))));   // exact for a finite amax
   const int lo = (((hmax + 1 - nbin) > 0 ? (hmax + 1 - nbin) : 0) + 7) & ~7;
   const int tlo = (((hmax + 1 - ntbin) > 0 ? (hmax + 1 - ntbin) : 0) + 7) & ~7;
   {
     // both halves of a word at once: signed 16-bit differences to the first counted pattern
     // (patterns are below 2^15), clamped to the last counter
     const i16x2 lo2 = {static_cast<short>(lo), static_cast<short>(lo)};
-    const i16x2 tlo2 = {static_cast<short>(tlo), static_cast<short>(tlo)};
     const i16x2 last2 = {static_cast<short>(nbin - 1), static_cast<short>(nbin - 1)};
-    const i16x2 tlast2 = {static_cast<short>(ntbin - 1), static_cast<short>(ntbin - 1)};
-    // Counter b is the low (b even) or high half of word b / 2: add 1 or 65536.  Address and
-    // addend are written out (a shift-add and a mask on the LDS byte address, one 24-bit
-    // multiply-add): left to the compiler the increment costs twice the instructions, and this
-    // loop runs once per element.
-    typedef __attribute__((address_space(3))) uint32_t lds_u32;
     const uint32_t hist_at = static_cast<uint32_t>(reinterpret_cast<uintptr_t>((lds_u32*)hist));     // LDS byte addresses, multiples of 16
     const uint32_t thist_at = static_cast<uint32_t>(reinterpret_cast<uintptr_t>((lds_u32*)thist));
-    auto count = [](uint32_t at, uint32_t ub) {
-      uint32_t one_or_65536;
-      asm("v_mad_u32_u24 %0, %1, %2, 1" : "=v"(one_or_65536) : "v"(ub & 1u), "s"(0xFFFFu));
-      lds_u32* const word = (lds_u32*)static_cast<uintptr_t>(((ub << 1) + at) & ~3u);
-      __hip_atomic_fetch_add(word, one_or_65536, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-    };
-    auto lo16 = [](i16x2 v) { return static_cast<uint32_t>(__builtin_bit_cast(uint32_t, v) & 0xFFFFu); };
-    auto hi16 = [](i16x2 v) { return static_cast<uint32_t>(__builtin_bit_cast(uint32_t, v) >> 16); };
+    uint32_t one = 1;
+    asm("" : "+v"(one));
 #pragma unroll
-    for (int j = 0; j < CH; ++j) {
+    for (int j0 = 0; j0 < CH; j0 += 4) {
+      constexpr int PART = CH < 4 ? CH : 4;
+      uint32_t noted = 0;
 #pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const uint32_t w = rawv[j][i];
-        const i16x2 h2 = __builtin_bit_cast(i16x2, w & 0x7FFF7FFFu);
-        const i16x2 b2 = __builtin_elementwise_min(h2 - lo2, last2);
-        // padding (zero) and whatever lies below every threshold has no counter
-        if (b2[0] >= 0) count(hist_at, lo16(b2));   // non-negative: the 16 bits are the counter's number
-        if (b2[1] >= 0) count(hist_at, hi16(b2));
-        if constexpr (ANY_TAIL) {
-          const i16x2 t2 = h2 - tlo2;
-          // negative elements at or above the short histogram's first pattern
-          const uint32_t q2 = w & ~__builtin_bit_cast(uint32_t, t2) & 0x80008000u;
-          if (q2 != 0) {
-            const i16x2 tc2 = __builtin_elementwise_min(t2, tlast2);
-            if (q2 & 0x8000u) count(thist_at, lo16(tc2));
-            if (q2 >> 31) count(thist_at, hi16(tc2));
-          }
+      for (int j = j0; j < j0 + PART; ++j)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const uint32_t w = j < CH ? rawv[j][i] : 0;
+          // padding (zero) and whatever lies below every threshold has no counter
+          if (j < CH) count_pair(hist_at, __builtin_elementwise_min(__builtin_bit_cast(i16x2, w & 0x7FFF7FFFu) - lo2, last2), one);
+          if constexpr (ANY_TAIL) note_negative(noted, w, tlo);
         }
-      }
+      if constexpr (ANY_TAIL) count_noted<PART * 4>(noted, src, (j0 * THREADS + tid) * 8, THREADS * 8, tlo, ntbin, thist_at);
     }
   }
   __syncthreads();
@@ -317,8 +310,8 @@ void sweep_hist_kernel(const SortedArgs a) {
   // ---- group prefixes ----------------------------------------------------------------------------
   // (the short histogram by the last wave alone, before the barriers of the long one's prefixes)
   if constexpr (ANY_TAIL)
-    if (wave == NW - 1) hist_records<In, 1, kHistMaxTailBins / 8 / 64>(thist, trec, tlo, ntg, s_wc, s_ws);
-  hist_records<In, NW, GPMAX>(hist, rec, lo, ng, s_wc, s_ws);
+    if (wave == NW - 1) hist_records<In, JOINT, 1, kHistMaxTailBins / 8 / 64>(thist, trec, tlo, ntg, s_wc, s_ws);
+  hist_records<In, JOINT, NW, GPMAX>(hist, rec, lo, ng, s_wc, s_ws);
   const uint32_t c_total = record_count(rec[ng]);
   // sums are in units of this (1 where they are fp64 magnitudes)
   const float v_lo = bits_to_float<In>(static_cast<uint32_t>(lo));
@@ -352,15 +345,15 @@ void sweep_hist_kernel(const SortedArgs a) {
       // more than one pattern below the histogram's range sends the candidate to the exact pass:
       // uncounted elements might lie above it.  The first boundary's is the smallest (and a negative
       // number is a large one to the unsigned minimum, so addresses stay inside).
-      bool bad = false;
-      // one boundary at a time (a rolled loop: unrolled, the eight of them cost some 80 registers)
+      int fewest = 0;
+      // one boundary at a time (a rolled loop: unrolled, the eight of them cost some 80 registers), the first last
 #pragma unroll 1
-      for (int q = 0; q < 7; ++q) {
+      for (int q = 6; q >= 0; --q) {
         const int n1 = counters_below(f, q, lo);
-        if (q == 0) bad = n1 < 0;
+        fewest = n1;
         uint32_t C;
         sum_t S;
-        hist_prefix<In>(hist, rec, keep, lo, min(static_cast<uint32_t>(n1), static_cast<uint32_t>(nbin)), C, S);
+        hist_prefix<In, JOINT>(hist, rec, keep, lo, min(static_cast<uint32_t>(n1), static_cast<uint32_t>(nbin)), C, S);
         ca = __builtin_fma(static_cast<double>(S), a.dgd[f][q], ca);
         cb4 = __mul24(static_cast<int>(C), a.dg2q[f][q]) + cb4;
       }
@@ -368,10 +361,10 @@ void sweep_hist_kernel(const SortedArgs a) {
       if constexpr (TAIL) {
         // negative elements with a pattern above H: the short histogram's totals less its prefix
         const int n1 = counters_below(f, 7, tlo);
-        bad |= n1 < 0;
+        fewest = min(fewest, n1);
         uint32_t C;
         sum_t S;
-        hist_prefix<In>(thist, trec, keep, tlo, min(static_cast<uint32_t>(n1), static_cast<uint32_t>(ntbin)), C, S);
+        hist_prefix<In, JOINT>(thist, trec, keep, tlo, min(static_cast<uint32_t>(n1), static_cast<uint32_t>(ntbin)), C, S);
         ca_tail = static_cast<double>(trec[ntg].sum - S) * a.dgd[f][7];
         if constexpr (std::is_same<Rec, Narrow>::value) {
           const float v_tlo = bits_to_float<In>(static_cast<uint32_t>(tlo));
@@ -385,7 +378,7 @@ void sweep_hist_kernel(const SortedArgs a) {
         const double B = 0.25 * static_cast<double>(cb4) + gl * gl * static_cast<double>(c_total);
         const double sc = static_cast<double>(s);
         const double v = (en - 2.0 * sc * A) + sc * sc * B;   // filtered error
-        sh.fast[f][k] = bad ? __builtin_nan("") : v;
+        sh.fast[f][k] = fewest < 0 ? __builtin_nan("") : v;
       }
     };
     for (int u = wave; u < NF * chunks; u += NW) {

@@ -106,3 +106,18 @@ def test_group_pattern_ranks(mq, dtype, group, n_clip, lo_clip, f16, pad):  # no
     ratios = [lo_clip + (1.0 - lo_clip) * (i + 1) / n_clip for i in range(n_clip)]
     for cands in (PAIR4, [orc.INT4], [orc.FP4_E2M1]):
         check_tensor(mq, w, cands, orc.PER_GROUP, ratios, group, f16, label="group-rank-edge")
+
+
+# fp16 rows searched through the histogram: every tile of the row (one to three masks of noted negative
+# elements), all elements in a group's last pattern (the largest weighted count), all of them negative
+@pytest.mark.parametrize("cols", [2048, 4096, 8200, 12296, 24576])
+def test_fp16_histogram_counts(mq, cols):  # noqa: F811
+    w = _strided(7, cols, 8, cols, torch.float16)
+    last = torch.tensor([0x3807], dtype=torch.int16, device=DEV).view(torch.float16)   # pattern 7 modulo 8
+    w[1] = last
+    w[2] = -last
+    w[3] = -w[3].abs()
+    w[4, : cols // 2] = last
+    w[5, cols - 1] = -w[5].abs().max() * 2
+    for cands in (PAIR4, [orc.INT4], [orc.FP4_E2M1]):
+        check_tensor(mq, w, cands, orc.PER_CHANNEL, mi.clip_ratios(100), label="fp16-edge")
