@@ -379,10 +379,13 @@ template <typename In, int FA, int FB, int GROUP>
 int launch_size(const GroupArgs& a, hipStream_t st) {
   constexpr int GPW = 64 / (GROUP / 8), MANT = Pattern<In>::MANT;
   constexpr bool TAIL = FA == MOFQ_INT4 || FB == MOFQ_INT4;
-  // a magnitude is below 2^(MANT + 1 + span) ulps of the first pattern: sums of a group below 2^24, counts below 2^8
-  const int span = (a.nbin + (1 << MANT) - 1) >> MANT;
+  // A magnitude is below 2^bits ulps of the first pattern: an integer of 32 bits, whose sum over a group of 256
+  // fits the wide cell's 48; the narrow cell holds sums below 2^24 and counts below 2^8.  More binades than that are
+  // the direct kernel's (bf16 from ratios below about 2e-6 on; an fp16 table ends at 8).
+  const int bits = MANT + 1 + ((a.nbin + (1 << MANT) - 1) >> MANT);
+  if (bits > 32) return MOFQ_ERR_UNSUPPORTED;
   const dim3 grid(static_cast<unsigned>((a.units + GPW - 1) / GPW));
-  if (GROUP <= 128 && ((GROUP - 1) >> (24 - (MANT + 1 + span))) == 0 && MANT + 1 + span < 24) {
+  if (GROUP <= 128 && bits < 24 && ((GROUP - 1) >> (24 - bits)) == 0) {
     const size_t lds = GPW * static_cast<size_t>(GroupLayout<GROUP, false, TAIL>::bytes(a.nbin));
     hipLaunchKernelGGL((sweep_group_bits_kernel<In, FA, FB, GROUP, false>), grid, dim3(64), lds, st, a);
   } else {

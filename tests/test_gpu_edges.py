@@ -108,6 +108,19 @@ def test_group_pattern_ranks(mq, dtype, group, n_clip, lo_clip, f16, pad):  # no
         check_tensor(mq, w, cands, orc.PER_GROUP, ratios, group, f16, label="group-rank-edge")
 
 
+# ratios so small that a group's largest elements are 2^31 ulps of the first counted pattern and more: the last tables
+# of the rank kernel and, beyond them, the direct kernel (bf16: 128 patterns per binade)
+@pytest.mark.parametrize("lo_clip", [1e-5, 4e-6, 2e-6, 1e-6, 1e-7])
+@pytest.mark.parametrize("group", [64, 128, 256])
+def test_group_tiny_ratios(mq, group, lo_clip):  # noqa: F811
+    w = _strided(9, 4 * group, 0, group, torch.bfloat16)
+    w[2, :group] = 0.75
+    w[3, :group] = -w[3, :group].abs()
+    ratios = [1.0 - 0.5 * i / 44 for i in range(44)] + [lo_clip]
+    for cands in (PAIR4, [orc.INT4], [orc.FP4_E2M1]):
+        check_tensor(mq, w, cands, orc.PER_GROUP, ratios, group, label=f"group-tiny-ratio {lo_clip}")
+
+
 # fp16 rows searched through the histogram: every tile of the row (one to three masks of noted negative
 # elements), all elements in a group's last pattern (the largest weighted count), all of them negative
 @pytest.mark.parametrize("cols", [2048, 4096, 8200, 12296, 24576])
