@@ -308,9 +308,11 @@ MOFQ_DEV void finish_row(RowSearch<(FB >= 0 ? 2 : 1), THREADS / 64>& sh, double*
       const int k = k0 + lane;
       cnt += __builtin_popcountll(__ballot(k < K && !(sh.fast[f][k < K ? k : 0] > thr)));
     }
-    // a format whose shortlist is one candidate with a provably accurate error is done; false for a zero or
-    // non-finite error
-    const bool direct = cnt == 1 && fb.beta <= 0x1p-34 * m;
+    // 4-bit formats: one whose shortlist is one candidate with a provably accurate error is done; false for a zero
+    // or non-finite error.  An 8-bit format's error is some 1e-4 of what its filter cancels, four digits of the
+    // reported error, so its winner is scored element by element too (a pass of 10 instructions per element beside
+    // the 13 per look-up and boundary).
+    const bool direct = Codec<FA>::BITS == 4 && cnt == 1 && fb.beta <= 0x1p-34 * m;
     if (lane == 0) { sh.thr[f] = thr; sh.direct[f] = direct ? km : -1; }
   }
   if (tid == 0) sh.nlist = 0;

@@ -1,11 +1,13 @@
 """Sizes at the edges of the launch rules and tiles: where a pass changes its shape (one launch or
 several, one or two stages of a sum, codes from the search or after it) and where a segment, a
 row or a unit ends inside a workgroup's piece.  Against the CPU oracle."""
+import numpy as np
 import pytest
 import torch
 
 import mofq_inputs as mi
 from oracle import mofq_oracle as orc
+from tests.gpu_util import scales_to_f32, unpack_codes
 from tests.test_gpu_w_only import check_tensor, mq  # noqa: F401
 
 pytestmark = pytest.mark.gpu
@@ -119,6 +121,34 @@ def test_group_tiny_ratios(mq, group, lo_clip):  # noqa: F811
     ratios = [1.0 - 0.5 * i / 44 for i in range(44)] + [lo_clip]
     for cands in (PAIR4, [orc.INT4], [orc.FP4_E2M1]):
         check_tensor(mq, w, cands, orc.PER_GROUP, ratios, group, label=f"group-tiny-ratio {lo_clip}")
+
+
+# The reported unit error is the sum of the squared residuals element by element.  x - g s is one fused operation
+# (2^-53 of it, twice that in the square), a lane adds at most `per_lane` squares, the lanes and waves of a unit
+# are summed in `levels` additions, all terms positive: the sum is within (2 + per_lane + levels) 2^-53 of the exact one.
+@pytest.mark.parametrize("dtype,cols,group,fmts,per_lane,levels", [
+    (torch.bfloat16, 2048, 0, [orc.INT8, orc.FP8_E4M3], 8, 9), (torch.bfloat16, 5000, 0, [orc.INT8, orc.FP8_E4M3], 24, 9),
+    (torch.bfloat16, 24576, 0, [orc.INT8, orc.FP8_E4M3], 96, 9)])
+def test_unit_errors_are_sums_of_residuals(mq, dtype, cols, group, fmts, per_lane, levels):  # noqa: F811
+    rows = 64 if group else 24
+    w = _strided(rows, cols, 0, cols + group, dtype)
+    x = w.double().cpu().numpy().reshape(-1, group or cols)
+    cfg = mq.Cfg(orc.PER_GROUP if group else orc.PER_CHANNEL, mi.clip_ratios(50), group)
+    bits = orc.bits(fmts[0])
+    for cands in ([fmts[0]], [fmts[1]], fmts):
+        out = mq.alloc_qbuffers(rows, cols, bits, cfg, DEV)
+        res = mq.alloc_result(DEV)
+        ws = torch.empty(mq.workspace_bytes(w, None, len(cands), mq.ERR_TENSOR, cfg), dtype=torch.uint8, device=DEV)
+        mq.select_layer(w, None, cands, mq.ERR_TENSOR, cfg, out, None, res, ws)
+        torch.cuda.synchronize()
+        fmt = cands[mq.read_result(res).best]
+        print(f"[case] residual sums {dtype} cols={cols} group={group} cands={cands}", flush=True)
+        g = orc.decode_array(fmt, unpack_codes(out.codes, rows, cols, bits)).astype(np.float64).reshape(x.shape)
+        s = scales_to_f32(out.scales).astype(np.float64)[:, None]
+        d = x.astype(np.longdouble) - (g * s)      # g s is exact in fp64
+        want = (d * d).sum(axis=1)
+        got = out.unit_err.cpu().numpy().astype(np.longdouble)
+        assert np.max(np.abs(got - want) / want) <= (2 + per_lane + levels) * 2.0 ** -53
 
 
 # fp16 rows searched through the histogram: every tile of the row (one to three masks of noted negative
