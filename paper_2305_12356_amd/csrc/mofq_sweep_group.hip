@@ -16,8 +16,9 @@
 //      sum share a word of 32 bits where they fit (those of the negative elements in the upper half of 64), else 64;
 //   3. a lane per candidate: the largest pattern below each boundary (an fp32 estimate and one exact decision), its
 //      rank among the distinct patterns (a population count), count and sum up to it: two LDS reads;
-//   4. the smallest error; where a second candidate is too close, or the error is not provably accurate
-//      (non-finite or nearly exact groups), all candidates of the group are scored element by element in fp64.
+//   4. the smallest error and, for the winner alone, the sum of its residuals element by element: that sum is what
+//      leaves (the difference of sums keeps two digits fewer).  Where a second candidate is too close, or a scale is
+//      out of range (non-finite or nearly exact groups), all candidates of the group are scored that way, in fp64.
 //
 // Bound by vector issue: 1740 instructions per wave of four groups of 128 with 50 ratios (the direct kernel: 4360), 4
 // waves of 10 KB LDS per SIMD.  Measured, fp16 groups of 128, 50 ratios, the seven linears of a 7B block: 2740 us ->
@@ -81,6 +82,13 @@ template <int FMT> MOFQ_DEV float search_scale(float ra, bool f16) {
   if (f16) s = round_fp16_clamped(s);
   if (!(s >= 0x1p-126f)) s = 1.0f;
   return s;
+}
+
+// 1 / s, correctly rounded for s in [2^-126, 2^125] (all of them checked): the hardware's reciprocal and one step of
+// Newton's iteration r + r (1 - s r).  A group with a larger scale is scored exactly, with the division.
+MOFQ_DEV float reciprocal(float s) {
+  const float r = __builtin_amdgcn_rcpf(s);
+  return __builtin_fmaf(__builtin_fmaf(-s, r, 1.0f), r, r);
 }
 
 // what a lane of the wave wrote to LDS is there for the others: LDS operations of a wave are in order
@@ -285,9 +293,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4))) void sw
     constexpr int FMT = decltype(fmt_c)::value;
     using Lv = Levels<FMT>;
     const float s = search_scale<FMT>(s_clip[k < K ? k : K - 1] * amax, f16);
-    // 1 / s, correctly rounded (every s in [2^-126, 2^125] checked): the hardware's reciprocal and one Newton step
-    float inv = __builtin_amdgcn_rcpf(s);
-    inv = __builtin_fmaf(__builtin_fmaf(-s, inv, 1.0f), inv, inv);
+    const float inv = reciprocal(s);
     uint32_t r[Lv::N];
     // The largest pattern at or below the boundary (threshold t s): the pattern of t s (1 + 2^-21) rounded toward
     // zero or the one before it, as the exact decision on the first tells; patterns above are beyond t s (1 + 2^-22), those
@@ -331,43 +337,60 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4))) void sw
     if constexpr (NF == 2) candidate(std::integral_constant<int, FBX>{}, k0 + l, NF - 1);
   }
 
-  // ---- 4. winners.  Count and sum are exact and the error takes two roundings (filter_bounds). ---------
+  // ---- 4. winners.  Count and sum are exact and the error takes two roundings (filter_bounds): a candidate that
+  // is the smallest by more than the margin is the winner, and its own error is then summed element by element, for
+  // en - 2 s A + s^2 B keeps two digits fewer than that sum. -------------------------------------------------
   const bool exact = group_reduce<LPG>(bad ? 1 : 0, [](int p, int q) { return p | q; }) != 0;
-  auto finish = [&](auto fmt_c, int f) {
-    constexpr int FMT = decltype(fmt_c)::value;
+  const double margin = filter_bounds<GROUP, true, 4>(en, 0.0, 0.0, 0.0, 0.0).margin;
+  int win[NF];
+  bool sure[NF];
+#pragma unroll
+  for (int f = 0; f < NF; ++f) {
     auto least = [](double p, double q) { return __builtin_fmin(p, q); };
     const double m = group_reduce<LPG>(best[f], least);
-    int k = group_reduce<LPG>(best[f] == m ? bk[f] : MOFQ_MAX_CLIP, [](int p, int q) { return min(p, q); });
-    const double m2 = group_reduce<LPG>(bk[f] == k ? second[f] : best[f], least);   // candidates of one lane are its own
-    const FilterBounds fb = filter_bounds<GROUP, true, 4>(en, 0.0, 0.0, 0.0, 0.0);
-    double err = m;
-    const bool sure = !exact && m2 > m + fb.margin && fb.beta <= 0x1p-34 * m;   // false for a zero or non-finite error
-    if (__builtin_amdgcn_ballot_w64(!sure && valid) != 0) {
-      raw.load(src, 0, 0);
-      float v[8];
-      raw.widen(v);
+    win[f] = group_reduce<LPG>(best[f] == m ? bk[f] : MOFQ_MAX_CLIP, [](int p, int q) { return min(p, q); });
+    const double m2 = group_reduce<LPG>(bk[f] == win[f] ? second[f] : best[f], least);   // candidates of one lane are its own
+    sure[f] = !exact && m2 > m + margin;   // false for a zero or non-finite error
+  }
+  raw.opaque();
+  raw.widen(x);
+  uint32_t carry = 0;
+  auto residuals = [&](auto fmt_c, float s, float inv) {
+    constexpr int FMT = decltype(fmt_c)::value;
+    const double sd = static_cast<double>(s);
+    double acc = 0.0;
+#pragma unroll
+    for (int i = 0; i < 8; i += 2) score2_f64<FMT>(acc, x[i], x[i + 1], inv, sd, carry);
+    return group_reduce<LPG>(acc, [](double p, double q) { return p + q; });
+  };
+  float s_win[NF];
+  double err[NF];
+  auto winner = [&](auto fmt_c, int f) {
+    win[f] = win[f] < K ? win[f] : 0;   // none on non-finite input
+    s_win[f] = unit_scale(amax, s_clip[win[f]], Codec<decltype(fmt_c)::value>::QMAX, f16);
+    err[f] = residuals(fmt_c, s_win[f], reciprocal(s_win[f]));
+  };
+  winner(std::integral_constant<int, FA>{}, 0);
+  if constexpr (NF == 2) winner(std::integral_constant<int, FBX>{}, NF - 1);
+  auto finish = [&](auto fmt_c, int f) {
+    if (__builtin_amdgcn_ballot_w64(!sure[f] && valid) != 0) {
       double eb = __builtin_inf();
       int ek = -1;
-      uint32_t carry = 0;
       for (int c = 0; c < K; ++c) {
-        const float s = unit_scale(amax, s_clip[c], Codec<FMT>::QMAX, f16);
-        const float inv = 1.0f / s;
-        const double sd = static_cast<double>(s);
-        double acc = 0.0;
-#pragma unroll
-        for (int i = 0; i < 8; i += 2) score2_f64<FMT>(acc, v[i], v[i + 1], inv, sd, carry);
-        acc = group_reduce<LPG>(acc, [](double p, double q) { return p + q; });
-        if (acc < eb) { eb = acc; ek = c; }
+        const float s = unit_scale(amax, s_clip[c], Codec<decltype(fmt_c)::value>::QMAX, f16);
+        const double e = residuals(fmt_c, s, 1.0f / s);
+        if (e < eb) { eb = e; ek = c; }
       }
-      if (!sure) {
-        err = ek < 0 ? __builtin_nan("") : eb;   // only on non-finite input
-        k = ek < 0 ? 0 : ek;
+      if (!sure[f]) {
+        err[f] = ek < 0 ? __builtin_nan("") : eb;   // only on non-finite input
+        win[f] = ek < 0 ? 0 : ek;
+        s_win[f] = unit_scale(amax, s_clip[win[f]], Codec<decltype(fmt_c)::value>::QMAX, f16);
       }
     }
     if (valid && l == 0) {
-      a.rec.scale[f][unit] = unit_scale(amax, s_clip[k], Codec<FMT>::QMAX, f16);
-      a.rec.clip[f][unit] = k;
-      a.rec.err[f][unit] = err;
+      a.rec.scale[f][unit] = s_win[f];
+      a.rec.clip[f][unit] = win[f];
+      a.rec.err[f][unit] = err[f];
     }
   };
   finish(std::integral_constant<int, FA>{}, 0);

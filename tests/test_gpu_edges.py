@@ -128,7 +128,9 @@ def test_group_tiny_ratios(mq, group, lo_clip):  # noqa: F811
 # are summed in `levels` additions, all terms positive: the sum is within (2 + per_lane + levels) 2^-53 of the exact one.
 @pytest.mark.parametrize("dtype,cols,group,fmts,per_lane,levels", [
     (torch.bfloat16, 2048, 0, [orc.INT8, orc.FP8_E4M3], 8, 9), (torch.bfloat16, 5000, 0, [orc.INT8, orc.FP8_E4M3], 24, 9),
-    (torch.bfloat16, 24576, 0, [orc.INT8, orc.FP8_E4M3], 96, 9)])
+    (torch.bfloat16, 24576, 0, [orc.INT8, orc.FP8_E4M3], 96, 9),
+    (torch.bfloat16, 1024, 64, PAIR4, 8, 3), (torch.bfloat16, 1024, 128, PAIR4, 8, 4), (torch.bfloat16, 1024, 256, PAIR4, 8, 5),
+    (torch.float16, 1024, 64, PAIR4, 8, 3), (torch.float16, 1024, 128, PAIR4, 8, 4), (torch.float16, 1024, 256, PAIR4, 8, 5)])
 def test_unit_errors_are_sums_of_residuals(mq, dtype, cols, group, fmts, per_lane, levels):  # noqa: F811
     rows = 64 if group else 24
     w = _strided(rows, cols, 0, cols + group, dtype)
