@@ -264,7 +264,8 @@ size_t mofq_select_layers_workspace_bytes(int32_t n_layers, const mofq_tensor_t*
  * group_first (HOST, n_layers entries) receives, for every tensor, the index of the first
  * tensor of its group.  The _timed variant records ev_begin[] of that first tensor before the
  * group's launch and ev_end[] of the group's last tensor (the largest index) after it, and
- * leaves the other events of the group alone.
+ * leaves the other events of the group alone.  What the events enclose is what those of
+ * mofq_select_layer_timed do.
  */
 int mofq_select_layers_search_groups(int32_t n_layers, const mofq_tensor_t* w, const int32_t* candidates,
                                      int32_t n_candidates, int32_t* group_first);
@@ -357,7 +358,8 @@ int mofq_select_calibrated(const mofq_tensor_t* x, const int32_t* candidates, in
  * be NULL) recorded on `stream` immediately before and after the error-scoring
  * kernels (the scale search for the tensor metric, the matrix products for the
  * layer-output metric), so that a harness can time the dominant kernel inside its
- * own timed region.  Everything else is identical.
+ * own timed region.  Everything else is identical: where a per-channel search writes the
+ * codes as well (one kernel; large tensors), the events enclose that too.
  */
 int mofq_select_layer_timed(const mofq_tensor_t* w, const mofq_tensor_t* x,
                             const int32_t* candidates, int32_t n_candidates, int32_t metric,

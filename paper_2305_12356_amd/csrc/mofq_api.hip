@@ -795,18 +795,21 @@ int select_w_only(const mofq_tensor_t* w, const int32_t* candidates, int n_candi
   const int64_t units = mofq_num_units(w->rows, w->cols, w_cfg->gran, w_cfg->group_size);
   const WOnlyWs s = carve_w_only(ws, units, n_candidates, w_cfg->gran, w_cfg->n_clip);
   if (!ws || ws_bytes < s.bytes || !aligned16(ws)) return MOFQ_ERR_WORKSPACE;
-  if (ev0 && hipEventRecord(ev0, st) != hipSuccess) return MOFQ_ERR_HIP;
+  auto record = [&](hipEvent_t e) { return e && hipEventRecord(e, st) != hipSuccess ? MOFQ_ERR_HIP : MOFQ_OK; };
   if (one_scale(w_cfg)) {
     TensorParams p = tensor_params(w, candidates, n_candidates, w_cfg, s);
     p.out = *w_out;
     p.result = result;
-    if ((rc = launch_tensor_select(p, st))) return rc;
-    return ev1 && hipEventRecord(ev1, st) != hipSuccess ? MOFQ_ERR_HIP : MOFQ_OK;
+    if ((rc = record(ev0))) return rc;
+    if ((rc = launch_tensor_scores(p, st))) return rc;
+    if ((rc = record(ev1))) return rc;
+    return launch_tensor_pick(p, st);
   }
   const bool ahead = codes_ahead(w, candidates, n_candidates, w_cfg, tensor_bytes(w), w->rows);
   if (ahead && (rc = launch_clear(&s.tally, 1, st))) return rc;
+  if ((rc = record(ev0))) return rc;
   if ((rc = sweep_candidates(w, candidates, n_candidates, w_cfg, s, st, nullptr, ahead ? w_out->codes : nullptr))) return rc;
-  if (ev1 && hipEventRecord(ev1, st) != hipSuccess) return MOFQ_ERR_HIP;
+  if ((rc = record(ev1))) return rc;
   DecideParams d{};
   d.units = units;
   d.n_cand = n_candidates;
@@ -1172,11 +1175,9 @@ int mofq_select_layers_timed(int32_t n_layers, const mofq_tensor_t* w, const int
   for (int i0 = 0, nb = 0; i0 < n_layers; i0 += nb) {
     nb = batch_length(n_layers, w, i0, cus);
     WOnlyWs slot[kEmitBatch];
-    char* slot_base[kEmitBatch];
     // 1. the searches, back to back; the tensors of one row length share a launch
     for (int j = 0; j < nb; ++j) {
       const int64_t units = mofq_num_units(w[i0 + j].rows, w[i0 + j].cols, w_cfg->gran, w_cfg->group_size);
-      slot_base[j] = base;
       slot[j] = carve_w_only(base, units, n_candidates, w_cfg->gran, w_cfg->n_clip);
       base += slot[j].bytes;
     }
@@ -1209,14 +1210,21 @@ int mofq_select_layers_timed(int32_t n_layers, const mofq_tensor_t* w, const int
           last = k;
         }
       if (ev_begin && hipEventRecord(static_cast<hipEvent_t>(ev_begin[i0 + j]), st) != hipSuccess) return join(MOFQ_ERR_HIP);
+      // one scale per tensor: nothing to share, the whole of mofq_select_layer per tensor (its codes while its
+      // elements may still be in cache, unless events ask for the scoring alone)
+      auto tensor = [&](int k) {
+        TensorParams p = tensor_params(&w[i0 + k], candidates, n_candidates, w_cfg, slot[k]);
+        p.out = w_out[i0 + k];
+        p.result = &results[i0 + k];
+        return p;
+      };
       if (one_scale(w_cfg)) {
-        // one scale per tensor: nothing to share, the whole of mofq_select_layer per tensor
-        for (int k = j; k <= last; ++k)
-          if (first[k] == j &&
-              (rc = select_w_only(&w[i0 + k], candidates, n_candidates, w_cfg, &w_out[i0 + k], &results[i0 + k], slot_base[k], slot[k].bytes, st, nullptr, nullptr)))
-            return join(rc);
-      } else
-      if (g > 1) {
+        for (int k = j; k <= last; ++k) {
+          if (first[k] != j) continue;
+          if ((rc = launch_tensor_scores(tensor(k), st))) return join(rc);
+          if (!ev_end && (rc = launch_tensor_pick(tensor(k), st))) return join(rc);
+        }
+      } else if (g > 1) {
         if (!one_launch) return join(MOFQ_ERR_INVALID_ARG);   // cannot happen: see plan_search_groups
         if ((rc = launch_sweep_group(sp, g, st))) return join(rc);
       } else {
@@ -1224,6 +1232,9 @@ int mofq_select_layers_timed(int32_t n_layers, const mofq_tensor_t* w, const int
           return join(rc);
       }
       if (ev_end && hipEventRecord(static_cast<hipEvent_t>(ev_end[i0 + last]), st) != hipSuccess) return join(MOFQ_ERR_HIP);
+      if (ev_end && one_scale(w_cfg))
+        for (int k = j; k <= last; ++k)
+          if (first[k] == j && (rc = launch_tensor_pick(tensor(k), st))) return join(rc);
     }
     if (i0 + nb >= n_layers) emit_cap = 0;   // nothing runs beside the last batch's emission
     // 2. on the second stream, once the batch's searches are done: reduce + select, the codes of
@@ -1279,7 +1290,7 @@ int mofq_select_calibrated(const mofq_tensor_t* x, const int32_t* candidates, in
   p.ext_absmax = absmax;
   if (x_out) p.out = *x_out;
   p.result = result;
-  return launch_tensor_select(p, st);
+  return (rc = launch_tensor_scores(p, st)) ? rc : launch_tensor_pick(p, st);
 }
 
 size_t mofq_select_units_workspace_bytes(const mofq_tensor_t* w, int32_t n_candidates,

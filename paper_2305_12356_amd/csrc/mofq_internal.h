@@ -87,8 +87,9 @@ struct TensorParams {
 };
 // *running = max(*running, max|x|).
 int launch_running_absmax(const TensorParams& p, hipStream_t stream);
-// Algorithm 1's select among n_cand formats, the record and the winner's outputs.
-int launch_tensor_select(const TensorParams& p, hipStream_t stream);
+// Errors of n_cand formats; then Algorithm 1's select among them, the record and the winner's outputs.
+int launch_tensor_scores(const TensorParams& p, hipStream_t stream);
+int launch_tensor_pick(const TensorParams& p, hipStream_t stream);
 // Codes, scale and error in the one format fmt[0].
 int launch_tensor_quantize(const TensorParams& p, hipStream_t stream);
 

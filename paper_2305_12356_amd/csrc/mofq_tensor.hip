@@ -396,10 +396,12 @@ template <typename In> int launch_errors(const TensorArgs& a, hipStream_t st) {
   return hip_status(hipGetLastError());
 }
 
-template <typename In> int launch_select(const TensorArgs& a, hipStream_t st) {
-  int rc = MOFQ_OK;
-  if (a.absmax == a.absmax_part && (rc = launch_max<In>(a, st))) return rc;
-  if ((rc = launch_errors<In>(a, st))) return rc;
+template <typename In> int launch_scores(const TensorArgs& a, hipStream_t st) {
+  const int rc = a.absmax == a.absmax_part ? launch_max<In>(a, st) : static_cast<int>(MOFQ_OK);
+  return rc ? rc : launch_errors<In>(a, st);
+}
+
+template <typename In> int launch_pick(const TensorArgs& a, hipStream_t st) {
   hipLaunchKernelGGL((tensor_select_kernel<In>), dim3(a.out.codes ? a.n_blocks : 1), dim3(kThreads), 0, st, a);
   return hip_status(hipGetLastError());
 }
@@ -446,12 +448,26 @@ int launch_running_absmax(const TensorParams& p, hipStream_t st) {
   MOFQ_BY_DTYPE(launch_max)
 }
 
-int launch_tensor_select(const TensorParams& p, hipStream_t st) {
-  TensorArgs a;
-  const int rc = fill(p, &a);
+namespace {
+int fill_select(const TensorParams& p, TensorArgs* a) {
+  const int rc = fill(p, a);
   if (rc) return rc;
-  if (a.n_cand < 1 || !a.sse || !a.energy || !a.absmax || a.running) return MOFQ_ERR_INVALID_ARG;
-  MOFQ_BY_DTYPE(launch_select)
+  return a->n_cand < 1 || !a->sse || !a->energy || !a->absmax || a->running ? MOFQ_ERR_INVALID_ARG : MOFQ_OK;
+}
+}  // namespace
+
+int launch_tensor_scores(const TensorParams& p, hipStream_t st) {
+  TensorArgs a;
+  const int rc = fill_select(p, &a);
+  if (rc) return rc;
+  MOFQ_BY_DTYPE(launch_scores)
+}
+
+int launch_tensor_pick(const TensorParams& p, hipStream_t st) {
+  TensorArgs a;
+  const int rc = fill_select(p, &a);
+  if (rc) return rc;
+  MOFQ_BY_DTYPE(launch_pick)
 }
 
 int launch_tensor_quantize(const TensorParams& p, hipStream_t st) {

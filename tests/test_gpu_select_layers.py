@@ -138,3 +138,44 @@ def test_batched_three_and_four_candidates(mq, cands_name):
         compare_quantized(w32, cands[ref.best], orc.PER_CHANNEL, 0, False, clip, ref.w,
                           unpack_codes(outs[i].codes, *shapes[i], bits), scales_to_f32(outs[i].scales),
                           outs[i].clip_idx.cpu().numpy(), outs[i].unit_err.cpu().numpy())
+
+
+def test_events_enclose_the_scoring_alone(mq):
+    """Per-tensor scales, one ratio: the events of the timed forms lie around the errors, not around the codes
+    (a quarter of the time or more: a pass that reads 2 bytes and writes 1 per element, of three passes)."""
+    ws = [mi.llama_like_weight(16384, 8192, seed=i, dtype=torch.bfloat16, device=DEV) for i in range(2)]
+    cfg = mq.Cfg(mq.PER_TENSOR, mi.clip_ratios(1))
+    cands = [mq.INT8, mq.FP8_E4M3]
+    outs = [mq.alloc_qbuffers(16384, 8192, 8, cfg, DEV) for _ in ws]
+    res = mq.alloc_result(DEV, 2)
+    batch = mq.LayerBatch(ws, outs)
+    scratch = torch.empty(batch.workspace_bytes(2, cfg), dtype=torch.uint8, device=DEV)
+    assert batch.search_groups(cands) == [0, 0]
+    ev = lambda: torch.cuda.Event(enable_timing=True)  # noqa: E731
+
+    def share(call):
+        best = 1.0
+        for _ in range(6):
+            e0, e1, outer0, outer1 = [ev(), ev()], [ev(), ev()], ev(), ev()
+            for e in e0 + e1:
+                e.record()
+            torch.cuda.synchronize()
+            outer0.record()
+            call(e0, e1)
+            outer1.record()
+            torch.cuda.synchronize()
+            best = min(best, e0[0].elapsed_time(e1[-1]) / outer0.elapsed_time(outer1))
+        return best
+
+    one = share(lambda e0, e1: mq.select_layer(ws[0], None, cands, mq.ERR_TENSOR, cfg, outs[0], None, res[0], scratch,
+                                               ev_begin=e0[0], ev_end=e1[-1]))
+    two = share(lambda e0, e1: mq.select_layers(batch, cands, cfg, res, scratch, ev_begin=e0, ev_end=e1))
+    print(f"[case] share of the call inside the events: {one:.3f} {two:.3f}", flush=True)
+    assert 0.1 < one < 0.75 and 0.1 < two < 0.75   # 0.61 and 0.59; 0.9 with the codes inside
+    want = [mq.alloc_qbuffers(16384, 8192, 8, cfg, DEV) for _ in ws]
+    plain = mq.alloc_result(DEV, 2)
+    mq.select_layers(mq.LayerBatch(ws, want), cands, cfg, plain, scratch)
+    torch.cuda.synchronize()
+    assert torch.equal(res, plain)
+    for o, q in zip(outs, want):
+        assert torch.equal(o.codes, q.codes) and torch.equal(o.scales, q.scales) and torch.equal(o.unit_err, q.unit_err)
