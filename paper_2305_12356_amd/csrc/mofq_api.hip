@@ -162,8 +162,8 @@ int sweep_params(const mofq_tensor_t* t, const int32_t* cand, int c0, int n,
   p.energy_part = w.energy_part;
   if (ahead_codes) {
     p.ahead.codes = ahead_codes;
-    p.ahead.tag = w.tag;
-    p.ahead.tally = w.tally;
+    p.ahead.tag = n == 2 ? w.tag : nullptr;
+    p.ahead.tally = n == 2 ? w.tally : nullptr;
     for (int f = 0; f < n; ++f) p.ahead.cand_of[f] = slot[f];
   }
   *out = p;
@@ -806,7 +806,8 @@ int select_w_only(const mofq_tensor_t* w, const int32_t* candidates, int n_candi
     return launch_tensor_pick(p, st);
   }
   const bool ahead = codes_ahead(w, candidates, n_candidates, w_cfg, tensor_bytes(w), w->rows);
-  if (ahead && (rc = launch_clear(&s.tally, 1, st))) return rc;
+  const bool two = n_candidates == 2;   // else the codes written ahead are final: no tallies, no tags
+  if (ahead && two && (rc = launch_clear(&s.tally, 1, st))) return rc;
   if ((rc = record(ev0))) return rc;
   if ((rc = sweep_candidates(w, candidates, n_candidates, w_cfg, s, st, nullptr, ahead ? w_out->codes : nullptr))) return rc;
   if ((rc = record(ev1))) return rc;
@@ -834,7 +835,7 @@ int select_w_only(const mofq_tensor_t* w, const int32_t* candidates, int n_candi
     e.err[c] = s.err[c];
   }
   e.decide = d;
-  e.tag = ahead ? s.tag : nullptr;
+  e.tag = ahead && two ? s.tag : nullptr;
   e.out = *w_out;
   return ahead ? launch_fixup(&e, 1, 0, st) : launch_emit(&e, 1, 0, st);
 }
@@ -940,7 +941,6 @@ int mofq_quantize(const mofq_tensor_t* t, int32_t format, const mofq_scale_cfg_t
     return launch_tensor_quantize(p, st);
   }
   const bool ahead = codes_ahead(t, &format, 1, cfg, tensor_bytes(t), t->rows);
-  if (ahead && (rc = launch_clear(&w.tally, 1, st))) return rc;
   if ((rc = sweep_candidates(t, &format, 1, cfg, w, st, nullptr, ahead ? out->codes : nullptr))) return rc;
   EmitParams e{};
   if (tensor_err) {
@@ -963,7 +963,6 @@ int mofq_quantize(const mofq_tensor_t* t, int32_t format, const mofq_scale_cfg_t
   e.scale[0] = w.scale[0];
   e.clip[0] = w.clip[0];
   e.err[0] = w.err[0];
-  e.tag = ahead ? w.tag : nullptr;
   e.out = *out;
   return ahead ? launch_fixup(&e, 1, 0, st) : launch_emit(&e, 1, 0, st);
 }
@@ -1194,7 +1193,8 @@ int mofq_select_layers_timed(int32_t n_layers, const mofq_tensor_t* w, const int
       ahead[j] = codes_ahead(&w[i0 + j], candidates, n_candidates, w_cfg, bytes, rows);
       if (ahead[j]) tally[n_ahead++] = slot[j].tally;
     }
-    if (n_ahead && (rc = launch_clear(tally, n_ahead, st))) return join(rc);
+    const bool two = n_candidates == 2;   // else the codes written ahead are final
+    if (n_ahead && two && (rc = launch_clear(tally, n_ahead, st))) return join(rc);
     for (int j = 0; j < nb; ++j) {
       if (first[j] != j) continue;
       // A launch over several tensors exists only where the whole candidate list is one
@@ -1250,7 +1250,7 @@ int mofq_select_layers_timed(int32_t n_layers, const mofq_tensor_t* w, const int
         if (w[i0 + j].dtype == dtype) {
           EmitParams& q = ahead[j] ? f[m++] : e[n++];
           q = emit_params(i0 + j, slot[j]);
-          if (ahead[j]) q.tag = slot[j].tag;
+          if (ahead[j] && two) q.tag = slot[j].tag;
         }
       if (m && (rc = launch_fixup(f, m, emit_cap, st2))) return join(rc);
       if (n && (rc = launch_emit(e, n, emit_cap, st2))) return join(rc);

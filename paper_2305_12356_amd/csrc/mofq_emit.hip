@@ -244,7 +244,7 @@ struct EmitTensor {
   const int32_t* clip[MOFQ_MAX_CANDIDATES];
   const double* err[MOFQ_MAX_CANDIDATES];
   Decision d;                // d.n = 0: candidate 0
-  const uint8_t* tag;        // fixup_kernel: [rows]
+  const uint8_t* tag;        // fixup_kernel: [rows], or nullptr: every row holds its final codes
   uint8_t* unit_fmt;         // PER_UNIT: index of each unit's candidate
   mofq_qout_t out;
 };
@@ -420,7 +420,7 @@ __global__ __launch_bounds__(kThreads) void fixup_kernel(const EmitArgs a) {
       const int64_t o = r0 + tid;
       int redo = 0;
       if (o < rows) {
-        redo = t.tag[o] != best;
+        redo = t.tag ? t.tag[o] != best : 0;
         const float s = t.scale[best][o];
         const int32_t clip = t.clip[best][o];
         const double err = t.err[best][o];
@@ -684,7 +684,7 @@ int launch_emit(const EmitParams* p, int n, int max_blocks, hipStream_t st) {
 
 int launch_fixup(const EmitParams* p, int n, int max_blocks, hipStream_t st) {
   for (int i = 0; i < n; ++i)
-    if (!p[i].tag || p[i].gran != MOFQ_PER_CHANNEL || p[i].unit_fmt || p[i].as_bf16_values) return MOFQ_ERR_INVALID_ARG;
+    if ((!p[i].tag && p[i].n_cand > 1) || p[i].gran != MOFQ_PER_CHANNEL || p[i].unit_fmt || p[i].as_bf16_values) return MOFQ_ERR_INVALID_ARG;
   EmitArgs a;
   const int rc = prepare_emit(p, n, a, st);
   if (rc != MOFQ_OK) return rc;

@@ -31,6 +31,7 @@ struct UnitRecords {
 // (16384 rows: 1.4 ms with one place for the device, 0.30 with 16 such places, 0.25 without).
 struct AheadCodes {
   void* codes;              // nullptr: not asked for
+  // two formats only (a single one's codes are final):
   uint8_t* tag;             // [rows]: candidate whose codes the row holds
   double* tally;            // [kTallies][kTallyStride]: sums of (error in slot 0 - error in slot 1); zero before the launch
   int32_t cand_of[kMaxFmt]; // launch slot -> candidate index
@@ -142,7 +143,7 @@ struct EmitParams {
   const int32_t* clip[MOFQ_MAX_CANDIDATES];
   const double* err[MOFQ_MAX_CANDIDATES];
   DecideParams decide;           // units > 0: the launch takes this reduce + select too and emits its choice; else candidate 0
-  const uint8_t* tag;            // launch_fixup: [rows], as the search left it
+  const uint8_t* tag;            // launch_fixup: [rows], as the search left it; nullptr with one candidate
   uint8_t* unit_fmt;             // device [units] or nullptr: every unit takes its own best candidate, whose index goes here
   mofq_qout_t out;
   int32_t as_bf16_values;        // out.codes receives the grid values as bf16

@@ -404,9 +404,11 @@ MOFQ_DEV void emit_row_ahead(RowSearch<(FB >= 0 ? 2 : 1), THREADS / 64>& sh, con
   if constexpr (NF == 2) {
     const double d = sh.best[0] - sh.best[1];
     slot = __builtin_amdgcn_readfirstlane(sh.tally + d > 0.0 ? 1 : 0);
-    if (tid == 0) tally_add<4>(ahead, d);
+    if (tid == 0) {
+      tally_add<4>(ahead, d);
+      ahead.tag[row] = static_cast<uint8_t>(ahead.cand_of[slot]);
+    }
   }
-  if (tid == 0) ahead.tag[row] = static_cast<uint8_t>(ahead.cand_of[slot]);
   const float inv = 1.0f / sh.best_scale[slot];
   const int64_t row_chunks = row * (n / 8);
   auto emit = [&](auto fmt_c) {

@@ -401,9 +401,11 @@ __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(GRID ? 
 #pragma unroll
       for (int w = 0; w < NW; ++w) d += s_acc[0][w] - s_acc[1][w];
       slot = __builtin_amdgcn_readfirstlane(s_tally + d > 0.0 ? 1 : 0);
-      if (tid == 0) tally_add<16>(a.ahead, d);
+      if (tid == 0) {
+        tally_add<16>(a.ahead, d);
+        a.ahead.tag[row] = static_cast<uint8_t>(a.ahead.cand_of[slot]);
+      }
     }
-    if (tid == 0) a.ahead.tag[row] = static_cast<uint8_t>(a.ahead.cand_of[slot]);
     auto codes = [&](auto fmt_c, float inv) {
       constexpr int FMT = decltype(fmt_c)::value;
 #pragma unroll
@@ -1013,7 +1015,7 @@ int launch_sweep(const SweepParams& p, hipStream_t st) {
     a.emit_grid[1] = static_cast<uint16_t*>(p.emit_grid[1]);
   }
   if (p.ahead.codes) {
-    if (p.gran != MOFQ_PER_CHANNEL || p.n_clip != 1 || !p.ahead.tag || !p.ahead.tally) return MOFQ_ERR_UNSUPPORTED;
+    if (p.gran != MOFQ_PER_CHANNEL || p.n_clip != 1 || (p.n_fmt == 2 && (!p.ahead.tag || !p.ahead.tally))) return MOFQ_ERR_UNSUPPORTED;
     a.ahead = p.ahead;
   }
   a.units = mofq_num_units(p.rows, p.cols, p.gran, p.group);
