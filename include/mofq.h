@@ -321,8 +321,8 @@ size_t mofq_select_layers_wa_workspace_bytes(int32_t n_layers, const mofq_tensor
  *                 best = the layer-wise choice, exactly as mofq_select_layer reports.
  *   mixed_err   : device, one double; the tensor error of the mixed assignment (the sum
  *                 of the per-unit minima, never above err[best]).
- * Workspace: mofq_workspace_bytes(w, NULL, n_candidates, MOFQ_ERR_TENSOR, w_cfg) plus
- * 8 bytes per unit, i.e. mofq_select_units_workspace_bytes().
+ * Workspace: mofq_workspace_bytes(w, NULL, n_candidates, MOFQ_ERR_TENSOR, w_cfg), i.e.
+ * mofq_select_units_workspace_bytes() (0 for per-tensor scales, which this call does not take).
  */
 int mofq_select_units(const mofq_tensor_t* w, const int32_t* candidates, int32_t n_candidates,
                       const mofq_scale_cfg_t* w_cfg, const mofq_qout_t* w_out,

@@ -1295,10 +1295,8 @@ int mofq_select_calibrated(const mofq_tensor_t* x, const int32_t* candidates, in
 
 size_t mofq_select_units_workspace_bytes(const mofq_tensor_t* w, int32_t n_candidates,
                                          const mofq_scale_cfg_t* w_cfg) {
-  const size_t base = mofq_workspace_bytes(w, nullptr, n_candidates, MOFQ_ERR_TENSOR, w_cfg);
-  if (!base || w_cfg->gran == MOFQ_PER_TENSOR) return 0;
-  const int64_t units = mofq_num_units(w->rows, w->cols, w_cfg->gran, w_cfg->group_size);
-  return base + (static_cast<size_t>(units) * sizeof(double) + kAlign - 1) / kAlign * kAlign;
+  const size_t bytes = mofq_workspace_bytes(w, nullptr, n_candidates, MOFQ_ERR_TENSOR, w_cfg);
+  return bytes && w_cfg->gran != MOFQ_PER_TENSOR ? bytes : 0;
 }
 
 int mofq_select_units(const mofq_tensor_t* w, const int32_t* candidates, int32_t n_candidates,

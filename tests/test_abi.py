@@ -216,3 +216,12 @@ def test_select_layers_wa_host_side(lib):
     assert L.mofq_select_layers_wa(*args(w=w16)) == -2               # the reference product takes bf16
     no_codes = (lib.QOut * n)(*[lib.QOut(None, 0x3000000, None, None) for _ in range(n)])
     assert L.mofq_select_layers_wa(*args(w_out=no_codes)) == -1
+
+
+def test_units_workspace_is_the_search_records(lib):
+    clip = np.ones(1, dtype=np.float32)
+    w = lib.TensorDesc(0x100000, lib.F16, 4096, 4096, 4096)
+    for gran, group in ((lib.PER_CHANNEL, 0), (lib.PER_GROUP, 128)):
+        cfg = lib.ScaleCfg(gran, group, lib.F32, 1, clip.ctypes.data_as(C.POINTER(C.c_float)))
+        need = lib._lib.mofq_workspace_bytes(C.byref(w), None, 2, lib.ERR_TENSOR, C.byref(cfg))
+        assert lib._lib.mofq_select_units_workspace_bytes(C.byref(w), 2, C.byref(cfg)) == need > 0
