@@ -164,11 +164,16 @@ def _ptr(t: Optional[torch.Tensor]):
     return None if t is None else t.data_ptr()
 
 
+# The current stream's raw handle.  torch.cuda.current_stream() builds a Stream object around it first, 3 us of a
+# single-layer call's 12; the function below it is not public, so a torch without it gets the public way.
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _stream_handle(stream) -> int:
     if stream is None:
-        # the handle itself: torch.cuda.current_stream() builds a Stream object around it first,
-        # 3 us of a single-layer call's 12
-        return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+        if _raw_stream is not None:
+            return _raw_stream(torch.cuda.current_device())
+        stream = torch.cuda.current_stream()
     return stream.cuda_stream
 
 

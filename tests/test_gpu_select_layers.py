@@ -179,3 +179,13 @@ def test_events_enclose_the_scoring_alone(mq):
     assert torch.equal(res, plain)
     for o, q in zip(outs, want):
         assert torch.equal(o.codes, q.codes) and torch.equal(o.scales, q.scales) and torch.equal(o.unit_err, q.unit_err)
+
+
+def test_current_stream_handle(mq, monkeypatch):
+    """The handle that calls without a stream use, by either way to it, on the default stream and another."""
+    for stream in (torch.cuda.default_stream(), torch.cuda.Stream()):
+        with torch.cuda.stream(stream):
+            fast = mq._stream_handle(None)
+            monkeypatch.setattr(mq, "_raw_stream", None)
+            assert mq._stream_handle(None) == fast == stream.cuda_stream
+            monkeypatch.undo()
