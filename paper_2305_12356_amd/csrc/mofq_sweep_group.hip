@@ -437,16 +437,21 @@ int launch_type(const SweepParams& p, const GroupArgs& a, hipStream_t st) {
   return MOFQ_ERR_UNSUPPORTED;
 }
 
-// From how many clip ratios on this kernel is the faster one: building the table costs what scoring so many
-// candidates costs.  4096 x 4096 elements, INT4 against E2M1, scored directly / by look-up, us: fp16 groups of 128 with
-// 8 ratios 76 / 76, 12: 92 / 77, 50: 253 / 120; of 64 with 16: 116 / 122, 24: 151 / 138 (a table per
-// group, whatever its size); of 256 (64-bit words) with 16: 110 / 110, 24: 144 / 109; bf16 (a table of an
-// eighth): 64 with 8: 78 / 67, 128 with 8: 74 / 62, 256 with 16: 109 / 99.  One format alone shares the table with none:
-// INT4, groups of 128, fp16 with 16: 67.5 / 65, bf16 with 12: 58 / 53; E2M1 with 12: 59 / 57.
+// From how many clip ratios on this kernel is the faster one: building the table costs what scoring that many
+// candidates costs.  The pair shares one table and a format alone has it to itself; INT4's takes the negative elements'
+// words as well (E2M1 alone needs neither them nor their prefixes); bf16 has an eighth of fp16's bits to clear and to walk;
+// a group of 64 has a table of its own like any other; one of 256 takes 64-bit words.  Measured at the lines, layer
+// selection, 4096 x 4096 (11008 x 4096 gives the same lines to within three ratios; below 1000 rows launches
+// hide the difference), us, scored directly / by look-up: INT4 and E2M1, fp16: 64, 29 ratios: 161 / 160; 128, 13: 84 / 83; 256, 21: 117 /
+// 114; bf16: 64, 12: 84 / 83; 128, 9: 66 / 65; 256, 18: 103 / 102.  INT4: fp16 64, 80: 183 / 179; 128, 28: 77 / 76; 256, 40: 103 / 102; bf16
+// 64, 21: 68.4 / 67.5; 128, 20: 60.8 / 60.8; 256, 39: 99 / 97.  E2M1: fp16 64, 38: 115 / 113; 128, 20: 68 / 66; 256, 19: 63 / 63; bf16 64, 13: 56.5 /
+// 55.8; 128, 11: 47.6 / 45.7; 256, 16: 55.8 / 55.5.
 int min_clip(const SweepParams& p) {
-  const bool f16 = p.dtype == MOFQ_F16;
-  const int pair = p.group == 64 ? (f16 ? 24 : 8) : (p.group == 128 ? (f16 ? 12 : 8) : (f16 ? 18 : 16));
-  return p.n_fmt == 2 ? pair : (p.fmt[0] == MOFQ_INT4 ? pair * 5 / 2 : pair * 4 / 3);
+  static constexpr int lines[2][3][3] = {   // [fp16, bf16][64, 128, 256][pair, INT4, E2M1]
+      {{29, 80, 38}, {13, 27, 20}, {21, 40, 19}},
+      {{12, 21, 13}, {9, 20, 11}, {18, 39, 16}}};
+  const int which = p.n_fmt == 2 ? 0 : (p.fmt[0] == MOFQ_INT4 ? 1 : 2);
+  return lines[p.dtype == MOFQ_F16 ? 0 : 1][p.group == 64 ? 0 : (p.group == 128 ? 1 : 2)][which];
 }
 
 }  // namespace

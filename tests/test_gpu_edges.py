@@ -90,7 +90,9 @@ def test_bf16_search_writes_codes(mq):  # noqa: F811
 @pytest.mark.parametrize("dtype", [torch.float16, torch.bfloat16])
 @pytest.mark.parametrize("group,n_clip,lo_clip,f16,pad", [
     (64, 24, 0.5, True, 0), (64, 33, 0.2, False, 64), (128, 12, 0.9, False, 0), (128, 50, 0.5, True, 128),
-    (128, 128, 0.02, False, 0), (256, 18, 0.5, True, 0), (256, 45, 0.3, False, 256)])
+    (128, 128, 0.02, False, 0), (256, 18, 0.5, True, 0), (256, 45, 0.3, False, 256),
+    # from these on for every type and list of formats
+    (64, 80, 0.5, True, 64), (128, 27, 0.4, True, 0), (256, 40, 0.6, False, 0)])
 def test_group_pattern_ranks(mq, dtype, group, n_clip, lo_clip, f16, pad):  # noqa: F811
     w = _strided(13, 7 * group, pad, n_clip, dtype)
     g = torch.Generator(device=DEV).manual_seed(n_clip)
