@@ -134,23 +134,6 @@ MOFQ_DEV float wave_sum_f32(float v) {
   return (a + b) + (c + d);
 }
 
-// exact re-score of two elements (same arithmetic as the direct kernel's second phase)
-template <int FMT> MOFQ_DEV void rescore2(double& acc, float x0, float x1, float inv_s, double sd, uint32_t& carry) {
-  f32x2 g;
-  if constexpr (FMT == MOFQ_FP4_E2M1) {
-    carry = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(carry, x0 * inv_s, x1 * inv_s, 1.0f, 0);
-    g = __builtin_amdgcn_cvt_scalef32_pk_f32_fp4(carry, 1.0f, 0);
-  } else {
-    g[0] = Codec<FMT>::grid(x0 * inv_s);
-    g[1] = Codec<FMT>::grid(x1 * inv_s);
-  }
-  const double d0 = __builtin_fma(-static_cast<double>(g[0]), sd, static_cast<double>(x0));
-  const double d1 = __builtin_fma(-static_cast<double>(g[1]), sd, static_cast<double>(x1));
-  acc = __builtin_fma(d0, d0, acc);
-  acc = __builtin_fma(d1, d1, acc);
-}
-
-
 // bit pattern of x >= 0 rounded toward zero to the input type
 template <typename In> MOFQ_DEV uint32_t pattern_rtz(float x);
 template <> MOFQ_DEV uint32_t pattern_rtz<F16>(float x) {

@@ -559,8 +559,8 @@ __global__ __launch_bounds__(THREADS, (CH <= 4 ? 4 : 2)) void sweep_sorted_kerne
         for (int i = 0; i < 4; ++i) {
           const float x0 = (p0 + 2 * i < n) ? bits_to_float<In>(v[i] & 0xFFFFu) : 0.0f;
           const float x1 = (p0 + 2 * i + 1 < n) ? bits_to_float<In>(v[i] >> 16) : 0.0f;
-          if (f == 0) rescore2<FA>(acc, x0, x1, inv, sd, carry);
-          else rescore2<FBX>(acc, x0, x1, inv, sd, carry);
+          if (f == 0) score2_f64<FA>(acc, x0, x1, inv, sd, carry);
+          else score2_f64<FBX>(acc, x0, x1, inv, sd, carry);
         }
       }
     }

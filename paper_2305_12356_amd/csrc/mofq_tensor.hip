@@ -270,8 +270,10 @@ __global__ __launch_bounds__(kThreads) void tensor_unit_kernel(const TensorArgs 
 // Tensors of up to 65536 elements (a few tokens of an activation): one launch.  Every workgroup
 // reads the whole tensor (128 KB at most, from L2) and finds its magnitude; workgroup 0 then sums the
 // error and leaves the outputs of the one unit, workgroup b > 0 writes the b-th eighth of the codes.
-// Two further launches would cost 5 us of host time and as much on the device; the error of
-// 65536 elements takes one workgroup about 4 us.
+// Two further launches cost a call 4.5 us whatever its size (10.0 us among others, 21.8 alone, bf16 E4M3),
+// the error in one workgroup grows with it: 5.5 / 16.5 us for 4096 elements, 7.6 / 20.4 for 65536.  With registers
+// for twice as many chunks 65536 elements take 7.9 / 20.8, 81920 9.2 / 22.2 and 98304 10.4 / 23.3: the lines cross
+// at about 80000, and the larger tile is slower for every smaller call (fp32 rows no longer fit registers at all).
 constexpr int kSmallThreads = 1024, kSmallChunks = 8;
 template <typename In, int FMT>
 __global__ __launch_bounds__(kSmallThreads) void tensor_quant_small_kernel(const TensorArgs a) {
