@@ -703,17 +703,18 @@ void hist_sizes(const SweepParams& p, SortedArgs& a) {
 
 namespace {
 
-constexpr int64_t kMinPairs8 = 32768;
-
 // Whether the configuration of one tensor is in the domain of these kernels.
 bool in_domain(const SweepParams& p) {
   if (p.gran != MOFQ_PER_CHANNEL || (p.dtype != MOFQ_F16 && p.dtype != MOFQ_BF16)) return false;
   if (p.n_clip < 8 || p.cols < 1024 || p.cols > 24576) return false;
   if (eight_bit(p)) {
-    // Only bf16 rows have few enough patterns.  The line: 4096 rows, INT8 against E4M3, scored directly / by
-    // histogram: 1024 x 16 ratios 50 / 60 us, 1024 x 32 73 / 63, 4096 x 8 82 / 72, 8192 x 8 135 / 94; one format:
-    // 1024 x 32 42..48 / 42..44, 4096 x 8 52..57 / 50..56.
-    if (p.dtype != MOFQ_BF16 || p.cols * p.n_clip < kMinPairs8) return false;
+    // Only bf16 rows have few enough patterns. The histogram costs a row much the same whatever the number of
+    // candidates up to 64, scoring them costs their pairs with its elements. Measured at the line, layer selection of
+    // 4096 rows, us, directly / by histogram: the pair, 1024 columns x 36 ratios 72 / 66, 2048 x 18 70 / 69, 4096 x 9
+    // 78 / 80, 5120 x 8 88 / 89; INT8, 1536 x 32 46 / 43, 2048 x 24 45 / 45, 4096 x 14 56 / 56, 5120 x 12 62 / 61;
+    // E4M3, 1536 x 28 50 / 49, 2048 x 22 52 / 50, 4096 x 11 59 / 59, 5120 x 9 63 / 64.
+    const int64_t line = p.n_fmt == 2 ? 36864 : (p.fmt[0] == MOFQ_INT8 ? 53248 : 45056);
+    if (p.dtype != MOFQ_BF16 || p.cols * p.n_clip < line) return false;
     return p.n_fmt == 1 || (p.fmt[0] == MOFQ_INT8 && p.fmt[1] == MOFQ_FP8_E4M3);
   }
   for (int f = 0; f < p.n_fmt; ++f)
