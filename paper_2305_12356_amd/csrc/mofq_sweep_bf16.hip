@@ -8,12 +8,13 @@
 // 8-byte read and four integer operations, 13 vector instructions in all against 38 of the group
 // records, which makes the 127 boundaries of an 8-bit format cheap: scoring every (element, candidate)
 // pair takes 4.8 instructions per element, candidate and format (240 000 per wave lane for a row of
-// 5000 elements and 50 candidates; here 3300 look-up instructions and about 800 for the histogram
-// serve all 50).  Bound by vector issue.
+// 5000 elements and 50 candidates; here a wave issues 2235 instructions in all, in the 4-bit search with
+// 100 candidates 890).  Bound by vector issue and, at 8 bits, by the LDS reads of the look-ups beside it (their
+// bank conflicts take 55 % of the LDS's cycles).
 // The error that leaves for an 8-bit format is the winner's element-wise sum (finish_row): the look-ups
 // choose it, and their difference of large sums would keep four digits fewer (1e-12 instead of 1e-15 on 5000 elements).
-// Measured, layer selection: INT8 against E4M3, 3001 x 5000, 50 ratios 277 -> 69 us (68 without that sum); 4096 x
-// 11008, 100 ratios 1315 -> 133 us; INT4 against E2M1, 1237 x 5000, 100 ratios: 28.2 -> 26.0 us.
+// Measured, layer selection: INT8 against E4M3, 3001 x 5000, 50 ratios 277 -> 69.5 us (68 without that sum; this
+// kernel 58); 4096 x 11008, 100 ratios 1294 -> 141 us; INT4 against E2M1, 1237 x 5000, 100 ratios: 28.2 -> 25.6 us.
 //
 // INT8's levels are spaced evenly; E4M3's evenly inside runs of 8 codes (a binade; the subnormals are the
 // first run): per run the level sums are d sum_i S_i and d^2 sum_i (2 (base + i) + 1) C_i with d the run's

@@ -20,9 +20,9 @@
 //      leaves (the difference of sums keeps two digits fewer).  Where a second candidate is too close, or a scale is
 //      out of range (non-finite or nearly exact groups), all candidates of the group are scored that way, in fp64.
 //
-// Bound by vector issue: 1740 instructions per wave of four groups of 128 with 50 ratios (the direct kernel: 4360), 4
-// waves of 10 KB LDS per SIMD.  Measured, fp16 groups of 128, 50 ratios, the seven linears of a 7B block: 2740 us ->
-// 1246 us.
+// Bound by vector issue: 1878 instructions per wave of four groups of 128 with 50 ratios (130 of them the winners' own
+// sums; the direct kernel: 4360), 4 waves of 10 KB LDS per SIMD.  Measured, layer selection of the seven linears of a
+// 7B block, fp16 groups of 128, 50 ratios: 3003 us -> 1434 us.
 #include <algorithm>
 #include <cmath>
 
@@ -439,13 +439,14 @@ int launch_type(const SweepParams& p, const GroupArgs& a, hipStream_t st) {
 
 // From how many clip ratios on this kernel is the faster one: building the table costs what scoring that many
 // candidates costs.  The pair shares one table and a format alone has it to itself; INT4's takes the negative elements'
-// words as well (E2M1 alone needs neither them nor their prefixes); bf16 has an eighth of fp16's bits to clear and to walk;
-// a group of 64 has a table of its own like any other; one of 256 takes 64-bit words.  Measured at the lines, layer
-// selection, 4096 x 4096 (11008 x 4096 gives the same lines to within three ratios; below 1000 rows launches
-// hide the difference), us, scored directly / by look-up: INT4 and E2M1, fp16: 64, 29 ratios: 161 / 160; 128, 13: 84 / 83; 256, 21: 117 /
-// 114; bf16: 64, 12: 84 / 83; 128, 9: 66 / 65; 256, 18: 103 / 102.  INT4: fp16 64, 80: 183 / 179; 128, 28: 77 / 76; 256, 40: 103 / 102; bf16
-// 64, 21: 68.4 / 67.5; 128, 20: 60.8 / 60.8; 256, 39: 99 / 97.  E2M1: fp16 64, 38: 115 / 113; 128, 20: 68 / 66; 256, 19: 63 / 63; bf16 64, 13: 56.5 /
-// 55.8; 128, 11: 47.6 / 45.7; 256, 16: 55.8 / 55.5.
+// words as well (E2M1 alone needs neither them nor their prefixes); bf16 has an eighth of fp16's bits to clear and to
+// walk; a group of 64 has a table of its own like any other; one of 256 takes 64-bit words.  Measured at the lines,
+// layer selection, 4096 x 4096 (11008 x 4096 gives the same lines to within three ratios; below 1000 rows launches hide
+// the difference), us, scored directly / by look-up: INT4 and E2M1, fp16: 64, 29 ratios: 161 / 160; 128, 13: 84 / 83;
+// 256, 21: 117 / 114; bf16: 64, 12: 84 / 83; 128, 9: 66 / 65; 256, 18: 103 / 102.  INT4: fp16 64, 80: 183 / 179; 128,
+// 28: 77 / 76; 256, 40: 103 / 102; bf16 64, 21: 68.4 / 67.5; 128, 20: 60.8 / 60.8; 256, 39: 99 / 97.  E2M1: fp16 64,
+// 38: 115 / 113; 128, 20: 68 / 66; 256, 19: 63 / 63; bf16 64, 13: 56.5 / 55.8; 128, 11: 47.6 / 45.7; 256, 16: 55.8 /
+// 55.5.
 int min_clip(const SweepParams& p) {
   static constexpr int lines[2][3][3] = {   // [fp16, bf16][64, 128, 256][pair, INT4, E2M1]
       {{29, 80, 38}, {13, 27, 20}, {21, 40, 19}},

@@ -21,9 +21,9 @@
 // Where the counted patterns span few enough binades, sums of magnitudes are 32-bit integers in units
 // of the first counted pattern's ulp (exact, and a third of the instructions of fp64 sums); else fp64.
 //
-// Bound by vector issue: the vector ALU executes for 95 % of a launch, 1030 instructions per wave on
-// rows of 4096 elements (INT4 / E2M1, 100 ratios): 200 to count, 180 for the prefixes, 310 for the
-// look-ups.  Two blocks of the 65B shape 2295 -> 2222 us, eight of the 7B shape 3094 -> 2957 us with the
+// Bound by vector issue: 1008 instructions per wave on rows of 4096 elements (INT4 / E2M1, 100 ratios, codes
+// included): 200 to count, 180 for the prefixes, 310 for the look-ups; they take 611 000 clocks per SIMD of a
+// launch of 38400 rows and 299 us (85 % of it at 2.4 GHz, all but a twentieth at the 2.1 to 2.25 GHz of such a load).  Two blocks of the 65B shape 2295 -> 2222 us, eight of the 7B shape 3094 -> 2957 us with the
 // negative elements' counting behind the loop (note_negative), the halves of a word selected by
 // the instructions that use them (count_pair) and one weighted sum per group (count8).
 //
