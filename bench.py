@@ -47,16 +47,21 @@ MFMA_PEAK = {"bf16": 2500.0, "int8": 5000.0, "fp8": 5000.0}
 # reads every candidate's level counts and sums from its prefixes), so this prices an
 # equivalent rate, reported under its own key, never as a utilisation.
 FLOPS_PER_ELEM_CAND_FMT = 7
-# Counter-derived facts about sweep_hist_kernel on 4096-column rows, measured by rocprofv3 runs
-# of this command (not in the run that prints them): where they come from is printed beside them.
 TAIL_SPREAD = False   # set from --tail-spread
 
+# Counter-derived facts about the search kernels, measured by rocprofv3 runs of this command (not in the run that
+# prints them): where they come from is printed beside them.  sweep_hist_kernel, 4096-column rows: a launch of 8192
+# rows and more also writes the rows' codes (0.5 byte per element).
 SEARCH_KERNEL_COUNTERS = {
     "from": "profiles/w_only_hist_kernel_counters.txt, profiles/w_only_7b_k100_hbm_traffic.txt",
-    "read_per_input_byte": 373087.0 / (46592 * 4096 * 2 / 1024),     # FETCH_SIZE, scaled by a plain copy
-    "write_bytes_per_row": 10192.0 * 1024 / 46592,                   # WRITE_SIZE
-    "valu_instr_per_wave": 1200.0,                                   # SQ_INSTS_VALU / SQ_WAVES, 4096-column instance
+    "read_per_input_byte": 374276.0 / (46592 * 4096 * 2 / 1024),     # FETCH_SIZE, scaled by a plain copy
+    "write_bytes_per_row": 896.0 * 1024 / 4096,                      # WRITE_SIZE: records alone
+    "write_bytes_per_row_with_codes": 104104.0 * 1024 / 46592,
+    "rows_with_codes": 8192,
+    "valu_instr_per_wave": 1008.0,                                   # SQ_INSTS_VALU / SQ_WAVES, 4096-column instance
 }
+# sweep_group_bits_kernel, fp16 groups of 128, 50 ratios: a wave takes four groups
+GROUP_KERNEL_COUNTERS = {"from": "profiles/w4_group128_7b_k50_kernel_stats.txt", "valu_instr_per_wave": 1878.0}
 
 
 def parse():
@@ -65,7 +70,7 @@ def parse():
     ap.add_argument("--steps", type=int, default=8)
     ap.add_argument("--warmup", type=int, default=2)
     ap.add_argument("--model", default="7b", choices=["7b", "65b"],
-                    help="65b = configs[4]: 560 linears, 129.5 GB of fp16 weights resident in HBM")
+                    help="65b: 560 linears, 129.5 GB of fp16 weights resident in HBM")
     ap.add_argument("--workload", default="all",
                     choices=["all", "w4_channel", "w4_group128", "w8a8", "w4a16_output", "k1_hbm", "fp4_variants",
                              "w4_units", "ceilings"])
@@ -80,7 +85,7 @@ def parse():
                     help="w4_channel: no second stream (kernels run one at a time; for counter runs)")
     ap.add_argument("--tail-spread", action="store_true",
                     help="model-shaped sets with a per-layer share of heavy-tail entries (both outcomes of the "
-                         "4-bit select occur) instead of BASELINE.json's 0.05 % in every layer")
+                         "4-bit select occur) instead of 0.05 %% in every layer")
     ap.add_argument("--copy-calibration", action="store_true",
                     help="also run one plain 1 GiB device copy (reference for rocprofv3 byte counters)")
     ap.add_argument("--full-parity", action="store_true",
@@ -201,7 +206,7 @@ def cpu_baseline(weights, outs, clip, cands):
     }
 
 
-# ---- weight-only, tensor error: configs[1], [2], [4] ------------------------------------
+# ---- weight-only, tensor error: per channel and per group ------------------------------------
 
 def make_weights(shapes, dev, dtype=None):
     import torch
@@ -287,10 +292,11 @@ def run_w4(args, shapes, dev, weights, group, model, steps, warmup, ceilings=Non
     roofline = {
         "bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBPS, "unit": "GB/s",
         "frac": achieved / HBM_PEAK_GBPS, "traffic": None,
-        "kernel": (f"sweep_group_kernel<F16, INT4, FP4_E2M1, {GROUP}> on {dom_cols}-column rows" if group else
+        "kernel": (f"sweep_group_bits_kernel<F16, INT4, FP4_E2M1, {GROUP}, 32-bit words> on {dom_cols}-column rows" if group else
                    f"sweep_hist_kernel<F16, INT4, FP4_E2M1> instance for {dom_cols}-column rows"),
-        "limited_by": "vector instruction issue, not bytes: the search evaluates "
-                      f"{n_clip} x {N_FMT} scale candidates per element from LDS and registers",
+        "limited_by": "vector instruction issue, not bytes: " +
+                      (f"per group a table of its bit patterns, then {n_clip} x {N_FMT} candidates x 7 or 8 boundary look-ups" if group else
+                       f"per row a histogram of its bit patterns, then {n_clip} x {N_FMT} candidates x 7 or 8 boundary look-ups"),
         "avg_launch_ms": dom_time / len(dom) * 1e3, "launches": len(dom),
         "algorithmic_bytes_per_launch": alg_bytes_per_launch,
         "algorithmic_bytes_per_elem": 2,
@@ -300,27 +306,29 @@ def run_w4(args, shapes, dev, weights, group, model, steps, warmup, ceilings=Non
             "TFLOPs": dom_elems * n_clip * N_FMT * FLOPS_PER_ELEM_CAND_FMT / dom_time / 1e12,
             "flops_per_elem_cand_fmt": FLOPS_PER_ELEM_CAND_FMT,
             "note": "flop of scoring every element x candidate x format one by one (7 each) over the launch "
-                    "time; the kernel reaches the same result with far fewer instructions (histogram of the "
-                    "row's bit patterns + prefix look-ups), so this is not a fraction of any peak",
+                    "time; the kernel reaches the same result with far fewer instructions (a table of the "
+                    "row's or group's bit patterns + prefix look-ups), so this is not a fraction of any peak",
         },
     }
     if ceilings:
         roofline["frac_of_measured_read"] = achieved / ceilings["read_GBps"]
     if not group and model == "7b" and dom_cols == 4096:
         c = SEARCH_KERNEL_COUNTERS
-        roofline["traffic"] = (alg_bytes_per_launch * c["read_per_input_byte"] +
-                               dom_rows / len(dom) * c["write_bytes_per_row"])
+        written = sum(r * c["write_bytes_per_row_with_codes" if r >= c["rows_with_codes"] else "write_bytes_per_row"] for _, _, r in dom)
+        roofline["traffic"] = alg_bytes_per_launch * c["read_per_input_byte"] + written / len(dom)
         roofline["traffic_from"] = {"file": c["from"], "measured_in_this_run": False,
                                     "how": "rocprofv3 FETCH_SIZE / WRITE_SIZE per row, scaled by a plain copy, "
-                                           "times the rows of this run's average launch"}
-        if ceilings:
-            # what binds the kernel: wave instructions issued per second (4 waves per row, the instruction
-            # count per wave from the counters profile) against the rate of the plain FMA loop of this run
-            rate = c["valu_instr_per_wave"] * 4 * dom_rows / dom_time
-            roofline["vector_issue"] = {"wave_instr_per_s": rate, "ceiling_measured": ceilings["valu_wave_instr_per_s"],
-                                        "frac": rate / ceilings["valu_wave_instr_per_s"],
-                                        "instr_per_wave": c["valu_instr_per_wave"],
-                                        "instr_per_wave_from": {"file": c["from"], "measured_in_this_run": False}}
+                                           "times the rows of this run's launches (codes written by most of them included)"}
+    if ceilings and model == "7b":
+        # what binds the kernel: wave instructions issued per second (4 waves per row or a wave per 4 groups, the
+        # instruction count per wave from the counters profile) against the rate of the plain FMA loop of this run
+        c = GROUP_KERNEL_COUNTERS if group else SEARCH_KERNEL_COUNTERS
+        waves = dom_elems / (4 * GROUP) if group else 4 * dom_rows
+        rate = c["valu_instr_per_wave"] * waves / dom_time
+        roofline["vector_issue"] = {"wave_instr_per_s": rate, "ceiling_measured": ceilings["valu_wave_instr_per_s"],
+                                    "frac": rate / ceilings["valu_wave_instr_per_s"],
+                                    "instr_per_wave": c["valu_instr_per_wave"],
+                                    "instr_per_wave_from": {"file": c["from"], "measured_in_this_run": False}}
 
     res = mq.read_results(results)
     fp_pct = 100.0 * sum(1 for r in res if r.best == 1) / len(res)
@@ -331,12 +339,12 @@ def run_w4(args, shapes, dev, weights, group, model, steps, warmup, ceilings=Non
         "select_time_s": ms_per_step / 1e3,
         "higher_is_better": True, "scaling": "weak", "vs_baseline": None,
         "dtype": "f32 decisions, f64 errors", "data": "synthetic",
-        "config": {"workload": ("configs[2]: LLaMA-7B-shaped fp16 weight set, "
+        "config": {"workload": ("LLaMA-7B-shaped fp16 weight set, "
                                 f"{len(shapes)} linears, {n_elems} weights, 4-bit W-only group-wise "
                                 "(128 along the input dim, fp16 scales), 50 clip ratios in [0.5,1], "
                                 "INT4 vs FP4-E2M1, per-layer select + emit") if group else
-                               (("configs[4]: LLaMA-65B-shaped" if model == "65b" else
-                                 "configs[1]: LLaMA-7B-shaped") + " fp16 weight set, "
+                               (("LLaMA-65B-shaped" if model == "65b" else
+                                 "LLaMA-7B-shaped") + " fp16 weight set, "
                                 f"{len(shapes)} linears, {n_elems} weights, 4-bit W-only per-channel, "
                                 "100 clip ratios in [0.5,1], INT4 vs FP4-E2M1, per-layer select + emit"),
                    "n_clip": n_clip, "formats": ["INT4", "FP4_E2M1"], "fp_percent": fp_pct,
@@ -350,10 +358,10 @@ def run_w4(args, shapes, dev, weights, group, model, steps, warmup, ceilings=Non
     return out
 
 
-# ---- layer-output error: configs[3] and the weight-only variant -------------------------
+# ---- layer-output error: weight-activation and the weight-only variant -------------------------
 
 def run_w8a8(args, shapes, dev, weights, w_only, fp8_unit, steps, warmup, ceilings=None):
-    """configs[3]: per linear, X [2048, in] bf16 with outlier channels, W bf16; per-tensor
+    """W8A8: per linear, X [2048, in] bf16 with outlier channels, W bf16; per-tensor
     INT8 vs FP8-E4M3 for both; layer-output error through the matrix cores; select + emit.
     With w_only: the weight-only select by layer-output error (X stays bf16; W per-channel
     absmax scales, INT4 vs FP4-E2M1)."""
@@ -466,7 +474,7 @@ def run_w8a8(args, shapes, dev, weights, w_only, fp8_unit, steps, warmup, ceilin
         "config": {"workload": (f"weight-only select by layer-output error: {len(shapes)} linears of the LLaMA-7B shape, "
                                 f"X [{TOKENS} x in] bf16 unquantized, W bf16, per-channel absmax scales, "
                                 "INT4 vs FP4-E2M1, per-layer select + emit") if w_only else
-                               (f"configs[3]: {len(shapes)} linears of the LLaMA-7B shape, X [{TOKENS} x in] bf16 "
+                               (f"W8A8: {len(shapes)} linears of the LLaMA-7B shape, X [{TOKENS} x in] bf16 "
                                 "with 6 outlier channels x60, W bf16, per-tensor INT8 vs FP8-E4M3, "
                                 "layer-output error, per-layer select + emit"),
                    "fp8_product": ("E4M3 codes on the fp8 matrix cores, the activation's outlier columns in one K step "
@@ -478,7 +486,7 @@ def run_w8a8(args, shapes, dev, weights, w_only, fp8_unit, steps, warmup, ceilin
 
 
 def run_k1_hbm(args, dev, steps, warmup, ceilings=None):
-    """configs[0]'s recipe at a size that does not fit in the caches: one 16384 x 16384 fp32
+    """The single-candidate case at a size that does not fit in the caches: one 16384 x 16384 fp32
     tensor, per-channel absmax scale (one candidate), INT4 vs FP4-E2M1, select + emit."""
     import torch
 
@@ -507,30 +515,30 @@ def run_k1_hbm(args, dev, steps, warmup, ceilings=None):
     elapsed = time.perf_counter() - t0
     ms_per_step = elapsed / steps * 1e3
     sweep_s = sum(e0.elapsed_time(e1) for e0, e1 in events) * 1e-3 / steps
-    read_bytes = n * n * 4
-    achieved = read_bytes / sweep_s / 1e9
+    alg_bytes = n * n * 4 + n * n // 2      # read once, the codes written by the same kernel
+    achieved = alg_bytes / sweep_s / 1e9
     r = mq.read_result(res)
     roofline = {
         "bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBPS, "unit": "GB/s", "frac": achieved / HBM_PEAK_GBPS,
         # FETCH_SIZE / WRITE_SIZE of this kernel, scaled by a plain copy's
-        "traffic": (1048666 + 3642) * 1024.0,
+        "traffic": (1048932 + 135129) * 1024.0,
         "traffic_from": {"file": "profiles/k1_hbm_fp32_16384_kernel_stats.txt", "measured_in_this_run": False},
         "kernel": "sweep_channel_single_kernel<F32, INT4, FP4_E2M1, 512 threads, 4 chunks>",
-        "note": "algorithmic bytes = 4 B per element read once by the scoring kernel; the emit pass "
-                "(4 B read + 0.5 B written per element) is in ms_per_step but not in this kernel",
+        "note": "algorithmic bytes = 4 B per element read and 0.5 B of codes written, once each, by the scoring kernel; "
+                "the select, the per-channel outputs and the rows that change format follow (rest_ms_per_step)",
         "avg_launch_ms": sweep_s * 1e3, "launches": len(events),
-        "algorithmic_bytes_per_launch": read_bytes,
-        "select_emit_GBps": n * n * 4.5 / (elapsed / steps - sweep_s) / 1e9,
+        "algorithmic_bytes_per_launch": alg_bytes,
+        "rest_ms_per_step": (elapsed / steps - sweep_s) * 1e3,
     }
     if ceilings:
-        roofline["frac_of_measured_read"] = achieved / ceilings["read_GBps"]
+        roofline["frac_of_measured_read"] = n * n * 4 / sweep_s / 1e9 / ceilings["read_GBps"]
     return {
         "metric": "weight-elems x candidates scored/sec (memory-bound case: one scale candidate)",
         "value": n * n * N_FMT / (elapsed / steps), "unit": "elem*cand/s", "n_gpus": 1,
         "steps": steps, "warmup": warmup, "ms_per_step": ms_per_step,
         "higher_is_better": True, "scaling": "weak", "vs_baseline": None,
         "dtype": "f32 decisions, f64 errors", "data": "synthetic",
-        "config": {"workload": "configs[0]'s recipe on a 16384 x 16384 fp32 tensor (1 GiB): N(0, 0.02^2), 0.1 % of "
+        "config": {"workload": "one 16384 x 16384 fp32 tensor (1 GiB): N(0, 0.02^2), 0.1 % of "
                                "entries x10, per-channel absmax scale, INT4 vs FP4-E2M1, tensor error, select + emit",
                    "best": int(r.best), "err": [float(r.err[0]), float(r.err[1])]},
         "roofline": roofline,
@@ -728,7 +736,7 @@ def full_parity(args, dev):
 
 
 def full_parity_wa(args, dev):
-    """Every linear of the listed blocks of the W8A8 workload (configs[3]), block by block through
+    """Every linear of the listed blocks of the W8A8 workload, block by block through
     mofq_select_layers_wa as bench.py times it (one call per block here, one activation per role
     of the block: q/k/v, o, gate/up, down) with both forms of the layer-output
     metric and, whole, through the oracle (fp64 matrix products): both candidates' error sums and
@@ -886,31 +894,31 @@ def main():
         shapes7 = [s for s in shapes7 if s[0] < args.blocks]
     note("7B-shaped fp16 weights")
     weights = make_weights(shapes7, dev)
-    note("configs[1]: per-channel, 100 clip ratios")
+    note("7B-shaped set: per-channel, 100 clip ratios")
     out = run_w4(args, shapes7, dev, weights, False, "7b", args.steps, args.warmup, ceilings,
                  want_cpu=not args.no_cpu_baseline and not args.blocks)
     out["ceilings"] = ceilings
     sec = {}
     few, few_w = max(1, min(args.steps, 3)), max(1, min(args.warmup, 1))
-    note("configs[2]: group 128, 50 clip ratios")
+    note("7B-shaped set: group 128, 50 clip ratios")
     sec["w4_group128"] = brief(run_w4(args, shapes7, dev, weights, True, "7b", few, few_w, ceilings))
     del weights
     torch.cuda.empty_cache()
-    note("configs[0]'s recipe on 1 GiB")
+    note("single candidate, fp32, 1 GiB")
     sec["k1_hbm"] = brief(run_k1_hbm(args, dev, few, few_w, ceilings))
     torch.cuda.empty_cache()
     note("bf16 weights for the layer-output workloads")
     weights = make_weights(shapes7, dev, torch.bfloat16)
-    note("configs[3]: W8A8, int8 and fp8 matrix cores for the quantized products")
+    note("W8A8, int8 and fp8 matrix cores for the quantized products")
     sec["w8a8"] = brief(run_w8a8(args, shapes7, dev, weights, False, True, few, few_w, ceilings))
-    note("configs[3]: W8A8, E4M3 product from grid values on the bf16 matrix cores")
+    note("W8A8, E4M3 product from grid values on the bf16 matrix cores")
     sec["w8a8_exact_e4m3"] = brief(run_w8a8(args, shapes7, dev, weights, False, False, few, few_w, ceilings))
     note("weight-only select by layer-output error")
     sec["w4a16_output"] = brief(run_w8a8(args, shapes7, dev, weights, True, False, few, few_w, ceilings))
     del weights
     torch.cuda.empty_cache()
     if not args.no_65b and not args.blocks:
-        note("configs[4]: 65B-shaped set, 129.5 GB resident")
+        note("65B-shaped set, 129.5 GB resident")
         shapes65 = mi.model_linear_shapes("65b")
         weights = make_weights(shapes65, dev)
         sec["w4_channel_65b"] = brief(run_w4(args, shapes65, dev, weights, False, "65b", 2, 1, ceilings))
