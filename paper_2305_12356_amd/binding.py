@@ -164,15 +164,17 @@ def _ptr(t: Optional[torch.Tensor]):
     return None if t is None else t.data_ptr()
 
 
-# The current stream's raw handle.  torch.cuda.current_stream() builds a Stream object around it first, 3 us of a
-# single-layer call's 12; the function below it is not public, so a torch without it gets the public way.
+# The current stream's raw handle.  torch.cuda.current_stream() builds a Stream object around it first (3 us of a
+# single-layer call's 12) and torch.cuda.current_device() checks for initialisation, which an argument on the device has
+# behind it (0.2 us).  The functions below them are not public, so a torch without them gets the public ones.
 _raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+_device = getattr(torch._C, "_cuda_getDevice", torch.cuda.current_device)
 
 
 def _stream_handle(stream) -> int:
     if stream is None:
         if _raw_stream is not None:
-            return _raw_stream(torch.cuda.current_device())
+            return _raw_stream(_device())
         stream = torch.cuda.current_stream()
     return stream.cuda_stream
 

@@ -186,6 +186,8 @@ def test_current_stream_handle(mq, monkeypatch):
     for stream in (torch.cuda.default_stream(), torch.cuda.Stream()):
         with torch.cuda.stream(stream):
             fast = mq._stream_handle(None)
+            monkeypatch.setattr(mq, "_device", torch.cuda.current_device)
+            assert mq._stream_handle(None) == fast
             monkeypatch.setattr(mq, "_raw_stream", None)
             assert mq._stream_handle(None) == fast == stream.cuda_stream
             monkeypatch.undo()
