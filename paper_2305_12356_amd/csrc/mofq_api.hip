@@ -285,6 +285,8 @@ int check_wa(const mofq_tensor_t* w, const mofq_tensor_t* x, const int32_t* cand
   return MOFQ_OK;
 }
 
+WaPlan wa_plan(const mofq_tensor_t* w, const mofq_tensor_t* x) { return wa_gemm_plan(x->rows, w->rows, w->cols, x->ld, w->ld); }
+
 struct WaWs {
   WOnlyWs xrec, wrec;
   uint8_t* xq[2];   // [0] INT8 codes, [1] E4M3 codes (fp8-unit mode) or bf16 grid values
@@ -307,7 +309,7 @@ WaWs carve_wa(void* ws, const mofq_tensor_t* w, const mofq_tensor_t* x, int n_ca
     a.xq[f] = c.take<uint8_t>(static_cast<size_t>(x->rows) * x->cols * (f ? 2 : 1));
     a.wq[f] = c.take<uint8_t>(static_cast<size_t>(w->rows) * w->cols * (f ? 2 : 1));
   }
-  a.blocks = wa_gemm_blocks(x->rows, w->rows);
+  a.blocks = wa_plan(w, x).blocks;
   for (int i = 0; i < 3; ++i) a.part[i] = c.take<double>(a.blocks);
   a.bytes = off + (c.off + kAlign - 1) / kAlign * kAlign;
   return a;
@@ -347,7 +349,7 @@ WoOutWs carve_wo_output(void* ws, const mofq_tensor_t* w, const mofq_tensor_t* x
   char* base = static_cast<char*>(ws);
   Carver c(base ? base + a.wrec.bytes : nullptr);
   for (int f = 0; f < n_cand; ++f) a.wg[f] = c.take<uint8_t>(static_cast<size_t>(w->rows) * w->cols * 2);
-  a.blocks = wa_gemm_blocks(x->rows, w->rows);
+  a.blocks = wa_plan(w, x).blocks;
   for (int i = 0; i < 3; ++i) a.part[i] = c.take<double>(a.blocks);
   a.bytes = a.wrec.bytes + (c.off + kAlign - 1) / kAlign * kAlign;
   return a;
@@ -584,13 +586,12 @@ struct WaFusedTensorWs {
 struct WaLayerWs {
   WaFusedTensorWs x, w;
   double* part[3];
+  int blocks;     // output tiles: values in each part
   bool fresh_x;   // false: x is the previous layer's (same descriptor, same group)
 };
 
 // The layers are worked off in groups of up to kWaGroup consecutive layers holding up to
-// kWaGroupElems weight elements (a decoder block of the 7B shape is one group): with a second
-// stream a whole group is prepared while the previous group is multiplied, so that the two
-// streams meet once per group and not once per layer.  Returns the number of layers of the
+// kWaGroupElems weight elements (a decoder block of the 7B shape is one group).  Returns the number of layers of the
 // group that starts at i0.
 constexpr int64_t kWaGroupElems = int64_t{1} << 28;
 int wa_group_length(int n_layers, const mofq_tensor_t* w, int i0) {
@@ -642,7 +643,8 @@ size_t carve_wa_group(void* arena, int i0, int n, const mofq_tensor_t* w, const 
         }
       }
     }
-    for (int q = 0; q < 3; ++q) l.part[q] = c.take<double>(wa_gemm_blocks(x[i].rows, w[i].rows));
+    l.blocks = wa_plan(&w[i], &x[i]).blocks;
+    for (int q = 0; q < 3; ++q) l.part[q] = c.take<double>(l.blocks);
     if (out) out[j] = l;
   }
   return (c.off + kAlign - 1) / kAlign * kAlign;
@@ -733,7 +735,7 @@ int select_layers_wa(int n_layers, const mofq_tensor_t* w, const mofq_tensor_t* 
     WaFinishParams f[kWaGroup] = {};
     for (int j = 0; j < n; ++j) {
       const int i = i0 + j;
-      f[j].d.units = wa_gemm_blocks(x[i].rows, w[i].rows);
+      f[j].d.units = l[j].blocks;
       f[j].d.n_cand = n_cand;
       for (int c = 0; c < n_cand; ++c) { f[j].d.err[c] = l[j].part[fmt_slot[c]]; f[j].fmt_slot[c] = fmt_slot[c]; }
       f[j].d.energy = l[j].part[2];

@@ -157,7 +157,7 @@ int launch_clear(double* const* p, int n, hipStream_t stream);
 // max_blocks: 0, or a cap on the workgroups for emission that runs beside other kernels
 int launch_emit(const EmitParams* p, int n, int max_blocks, hipStream_t stream);
 
-// Layer-output error of one linear layer: partial sums per 128x128 output tile.
+// Layer-output error of one linear layer: partial sums per output tile.
 // A null xi/wi (or xf/wf) pair skips that format.
 // One quantized product of the layer-output kernel: sum_i Gx[t,i] * Gw[o,i], scaled by
 // sx * sw[o] in the reduction.  Operand arrays are dense ([M][K] and [N][K]).
@@ -172,7 +172,7 @@ struct WaProduct {
   const void* x; const void* w;
   const float* sx;                 // device, one value; nullptr = 1 (unquantized input)
   const float* sw;                 // device, 1 or N values
-  double* part;                    // [wa_gemm_blocks(M, N)] squared-difference partials
+  double* part;                    // [WaPlan::blocks] squared-difference partials
   // optional second part of the same product (same scales): grid values as bf16, dense
   // [M][kWaSideCols] and [N][kWaSideCols], multiplied on the bf16 matrix cores and added
   const void* xs; const void* ws;
@@ -183,9 +183,15 @@ struct WaGemmParams {
   WaProduct q[2];                  // up to two quantized products (kind WA_NONE = unused)
   int32_t w_per_channel;
   int64_t M, N, K;
-  double* part_p;                  // [wa_gemm_blocks(M, N)] sum of Y^2
+  double* part_p;                  // [WaPlan::blocks] sum of Y^2
 };
-int wa_gemm_blocks(int64_t M, int64_t N);
+// How a layer's products are tiled: by its shape alone (the errors' sums depend on it).
+struct WaPlan {
+  enum : int { kLarge, kWide };
+  int tile;
+  int blocks;              // output tiles
+};
+WaPlan wa_gemm_plan(int64_t M, int64_t N, int64_t K, int64_t ldx, int64_t ldw);
 int launch_wa_gemm(const WaGemmParams& p, hipStream_t stream);
 
 // The fused weight-activation path (both 8-bit formats as candidates, per-tensor scales)

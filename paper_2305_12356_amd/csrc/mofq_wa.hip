@@ -4,7 +4,7 @@
 //     E_f = sum_{t,o} ( Y[t,o] - sx_f * sw_f[o] * (Qx_f Qw_f^T)[t,o] )^2 ,  P = sum Y^2 ,
 //     Y = X W^T .
 //
-// One kernel computes, per 256x128 output tile, the reference product on the bf16
+// One kernel computes, per output tile, the reference product on the bf16
 // matrix cores, then up to two quantized products (for W8A8: the INT8 code product on the
 // int8 matrix cores and the FP8-E4M3 code product), one after the other: each product is a K loop of its own over its own
 // operand arrays, the reference accumulators stay in registers for the whole kernel and
@@ -20,6 +20,11 @@
 // one waits at the stage barrier or for its fragments the other keeps the matrix core
 // busy.  The 256x128 workgroup tile needs 25 % fewer operand bytes per flop than
 // 128x128.
+//
+// What bounds it on full grids: power.  The part holds 1.73 GHz with the matrix cores busy for 0.67 of the clocks
+// (2048 x 11008 x 4096, three bf16 products, 456 us); four waves of 128 x 64, with a quarter less LDS traffic, run at 1.87 GHz
+// and 0.62 and take as long; without the deposits, at 1.89 GHz and 0.72, it takes 387 us.  On small grids: the latency of a
+// step (0.2 us of deposit, barrier and fragment reads with one workgroup on a compute unit).
 //
 // Exactness: bf16 x bf16 products are exact in fp32 and are accumulated in fp32;
 // int8 products are accumulated exactly in int32 (|sum| <= 32768*127*127 < 2^31).
@@ -44,6 +49,7 @@
 //                  hand their grid values over as a second part (QProd::xs / ws): one K step
 //                  on the bf16 matrix cores into the same accumulators, which brings the sum
 //                  to within 4e-7 at full size.
+#include <algorithm>
 #include <type_traits>
 
 #include "mofq_device.h"
@@ -60,29 +66,26 @@ typedef int i32x4 __attribute__((ext_vector_type(4)));
 typedef int i32x8 __attribute__((ext_vector_type(8)));
 
 constexpr int SIDE_K = kWaSideCols;             // K extent of a product's optional second part: one 16-bit stage
-constexpr int TM = 256, TN = 128;               // workgroup tile; 8 waves (two per SIMD), 64 x 64 each
-constexpr int WM = 64, WN = 64;                 // wave tile: 2 x 2 matrix-core tiles of 32 x 32
-constexpr int NW = (TM / WM) * (TN / WN);       // waves per workgroup
-constexpr int TI = WM / 32, TJ = WN / 32;
 
-struct QProd {
-  const void* x; const void* w;                 // dense [M][K], [N][K] in the product's operand type
-  const float* sx; const float* sw;             // scales: sx one value or null (= 1); sw one value or [N]
-  double* part;                                 // [blocks]
-  const void* xs; const void* ws;               // optional second part: bf16 grid values, dense [M][SIDE_K], [N][SIDE_K]
+// The K loops of a tile run one after the other as one sequence of stages, in this order.
+enum : int { SEG_REF = 0, SEG_Q = 1, SEG_SIDE = 2, N_SEG = 5 };   // the reference, then (product, its side part) twice
+struct Segment {
+  const void* x; const void* w;                 // rows of X and W
+  int64_t xrow, wrow;                           // bytes from row to row
+  int32_t stages;                               // 0: not there
+  int32_t half;                                 // the last stage holds half a line per row (8-bit, K % 128 == 64)
 };
 struct GemmArgs {
-  const uint16_t* x; int64_t ldx;               // bf16 [M][K]
-  const uint16_t* w; int64_t ldw;               // bf16 [N][K]
-  QProd q[2];
+  Segment seg[N_SEG];
+  const float* sx[2]; const float* sw[2];       // scales: sx one value or null (= 1); sw one value or [N]
+  double* part[3];                              // [blocks]: errors of the two products (or null), sum of Y^2
   int32_t w_per_channel;
-  int32_t M, N, K;
+  int32_t M, N;
   int32_t tiles_m, tiles_n;
-  double* part_p;                               // [blocks]
 };
 
 // ---- LDS stage ----------------------------------------------------------------------
-// A stage holds one K slab of both operand tiles: 256 rows of X then 128 rows of W, each
+// A stage holds one K slab of both operand tiles: TM rows of X then TN rows of W, each
 // row ROW_B = 128 bytes (64 sixteen-bit or 128 eight-bit elements, one cache line), i.e.
 // 8 chunks of 16 bytes, no padding.  Stages are filled by global_load_lds (each lane of a wave
 // instruction deposits 16 bytes at consecutive LDS addresses), so the layout is chosen
@@ -93,20 +96,24 @@ struct GemmArgs {
 // every 2 rows.
 constexpr int ROW_B = 128;
 constexpr int CH = ROW_B / 16;                  // chunks per row
-constexpr int STAGE_ROWS = TM + TN;
-constexpr int STAGE = STAGE_ROWS * ROW_B;       // 48 KB
 constexpr int NST = 3;                          // stages resident
-constexpr int DEP = STAGE / 1024 / NW;          // deposits per wave per stage (6)
 MOFQ_DEV constexpr int swz(int row) { return (row >> 1) & (CH - 1); }
 
-// One wave instruction: lane l fetches 16 bytes at its own global address and deposits
-// them at LDS address lds_base + 16*l.  Written as inline assembly so that the compiler
+// One wave instruction: lane l fetches 16 bytes at base + its own offset and deposits
+// them at LDS address lds_addr + 16*l.  Written as inline assembly so that the compiler
 // does not serialise later LDS reads of OTHER buffers behind the deposit; completion is
 // tracked by hand with s_waitcnt vmcnt (deposits of a wave retire in order).
-MOFQ_DEV void lds_deposit(const char* gsrc, uint32_t lds_addr) {
+// (64-bit offsets: for row strides beyond 2^32 bytes per tile.)
+MOFQ_DEV void lds_deposit(const char* base, uint64_t off, uint32_t lds_addr) {
   asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off"
                :
-               : "s"(__builtin_amdgcn_readfirstlane(lds_addr)), "v"(gsrc)
+               : "s"(__builtin_amdgcn_readfirstlane(lds_addr)), "v"(base + off)
+               : "memory");
+}
+MOFQ_DEV void lds_deposit(const char* base, uint32_t off, uint32_t lds_addr) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
+               :
+               : "s"(__builtin_amdgcn_readfirstlane(lds_addr)), "v"(off), "s"(base)
                : "memory");   // m0 is not otherwise used by these kernels
 }
 
@@ -117,8 +124,42 @@ template <int N> MOFQ_DEV void wait_deposits_and_reads() {
 
 enum : int { K_REF = 100, K_GRID = WA_GRID_BF16, K_I8 = WA_INT8, K_F8 = WA_FP8 };   // K_REF: the 16-bit inputs themselves
 
-template <int KIND1, int KIND2>
-__global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2, 2))) void wa_gemm_kernel(const GemmArgs a) {
+template <int TM_, int TN_, int WM_, int WN_> struct Tile {
+  static constexpr int TM = TM_, TN = TN_;                  // workgroup tile
+  static constexpr int WM = WM_, WN = WN_;                  // wave tile: matrix-core tiles of 32 x 32
+  static constexpr int NW = (TM / WM) * (TN / WN);          // waves per workgroup
+  static constexpr int STAGE = (TM + TN) * ROW_B;           // bytes
+  static constexpr int PER_CU = (160 * 1024) / (NST * STAGE + 1024);   // workgroups that LDS lets a compute unit hold
+  static constexpr int PER_SIMD = PER_CU * NW / 4;          // their waves on a SIMD
+};
+
+// Workgroup -> tile.  Consecutive workgroup ids go to different XCDs (8 of them, each
+// with its own L2), so ids are first regrouped so that one XCD works on a contiguous
+// range of tiles, and a range is walked in bands of 4 tile rows: the 32 workgroups
+// resident on an XCD then share 4 X tiles and 8 W tiles.
+MOFQ_DEV int regrouped(int id, int total) {
+  const int per_xcd = total / 8;
+  return id < per_xcd * 8 ? (id & 7) * per_xcd + (id >> 3) : id;
+}
+MOFQ_DEV void tile_of(const GemmArgs& a, int t, int& bm, int& bn) {
+  constexpr int BAND = 4;
+  const int band = t / (BAND * a.tiles_n);
+  const int first_m = band * BAND;
+  const int rows_in_band = (a.tiles_m - first_m) < BAND ? (a.tiles_m - first_m) : BAND;
+  const int in_band = t - band * BAND * a.tiles_n;
+  bm = first_m + in_band % rows_in_band;
+  bn = in_band / rows_in_band;
+}
+
+template <typename T, int KIND1, int KIND2, bool WIDE>
+__global__ __launch_bounds__(T::NW * 64) __attribute__((amdgpu_waves_per_eu(T::PER_SIMD, T::PER_SIMD))) void wa_gemm_kernel(const GemmArgs a) {
+  constexpr int TM = T::TM, TN = T::TN, WM = T::WM, WN = T::WN, NW = T::NW;
+  constexpr int TI = WM / 32, TJ = WN / 32;
+  constexpr int STAGE = T::STAGE;
+  constexpr int DEP = STAGE / 1024 / NW;        // deposits per wave per stage
+  constexpr int FIRST = DEP / 4;                // of which the first ones are issued a step ahead
+  constexpr int STEP = NW * 8;                  // rows from one deposit of a wave to the next
+  static_assert(DEP * NW * 1024 == STAGE && TM % STEP == 0 && STEP % 16 == 0, "deposits");
   __shared__ __attribute__((aligned(1024))) unsigned char s_buf[NST * STAGE];
   __shared__ double s_red[3][NW];
 
@@ -126,28 +167,11 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2, 2)))
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int wm = wave >> 1, wn = wave & 1;      // 4 x 2 waves
+  const int wm = wave / (TN / WN), wn = wave % (TN / WN);
   const int r = lane & 31, g = lane >> 5;
 
-  // Workgroup -> tile.  Consecutive workgroup ids go to different XCDs (8 of them, each
-  // with its own L2), so ids are first regrouped so that one XCD works on a contiguous
-  // range of tiles, and a range is walked in bands of 4 tile rows: the 32 workgroups
-  // resident on an XCD then share 4 X tiles and 8 W tiles.
-  int t = blockIdx.x;
-  {
-    const int total = a.tiles_m * a.tiles_n;
-    const int per_xcd = total / 8;
-    if (t < per_xcd * 8) t = (t & 7) * per_xcd + (t >> 3);
-    constexpr int BAND = 4;
-    const int band = t / (BAND * a.tiles_n);
-    const int first_m = band * BAND;
-    const int rows_in_band = (a.tiles_m - first_m) < BAND ? (a.tiles_m - first_m) : BAND;
-    const int in_band = t - band * BAND * a.tiles_n;
-    const int bm_ = first_m + in_band % rows_in_band;
-    const int bn_ = in_band / rows_in_band;
-    t = bm_ * a.tiles_n + bn_;
-  }
-  const int bm = t / a.tiles_n, bn = t - bm * a.tiles_n;
+  int bm, bn;
+  tile_of(a, regrouped(blockIdx.x, gridDim.x), bm, bn);
   const int m0 = bm * TM, n0 = bn * TN;
 
   // LDS byte offsets of this lane's fragment rows inside a stage, and of the chunks it
@@ -163,56 +187,82 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2, 2)))
     ch_f[q] = ((4 * (q >> 1) + 2 * g + (q & 1)) ^ sw) * 16;  // fp8 instruction q/2: 32 bytes per lane, half q%2
   }
 
-  f32x16 acc_r[TI][TJ];
+  // ---- the deposits' position in the sequence of stages ----------------------------------
+  // Deposit d of a stage covers the rows d STEP + 8 wave + lane / 8 (multiples of 16 apart, so the lane fetches the
+  // same chunk of each).  The tile's first row and the stage are in the scalar bases, a lane's row and chunk in `off`:
+  // nothing is computed per deposit (with 64-bit addresses per lane, five vector instructions each, these cases took 4 to
+  // 6 % longer: 2048 x 11008 x 4096, three bf16 products, 535 -> 511 us a call, 2048 x 4096 x 4096 196 -> 184.5).  Rows past the edge repeat the last one (masked later).
+  // The deposits run up to three stages ahead of the matrix instructions, across the ends of the products: what the last
+  // steps of one product fetch are the first stages of the next, so a product does not begin with an empty pipeline
+  // (777 x 3000 x 5056, large tiles: 156 -> 154 us).
+  const int row0 = wave * 8 + (lane >> 3), kc = (lane & 7) ^ swz(row0);
+  using off_t = std::conditional_t<WIDE, uint64_t, uint32_t>;
+  off_t off[DEP];
+  const char* dep_x = nullptr;
+  const char* dep_w = nullptr;
+  int dep_left = 0, dep_half = 0, dep_seg = -1;
+  auto next_segment = [&]() {
+    int s = dep_seg + 1;
+    while (s < N_SEG && a.seg[s].stages == 0) ++s;
+    if (s == N_SEG) {       // past the last stage: it is fetched again, unused
+      dep_x -= ROW_B;
+      dep_w -= ROW_B;
+      dep_left = 1;
+      dep_half = 0;
+      return;
+    }
+    dep_seg = s;
+    const Segment& sg = a.seg[s];
+    dep_x = static_cast<const char*>(sg.x) + m0 * sg.xrow;
+    dep_w = static_cast<const char*>(sg.w) + n0 * sg.wrow;
+    dep_left = sg.stages;
+    dep_half = sg.half;
 #pragma unroll
-  for (int i = 0; i < TI; ++i)
-#pragma unroll
-    for (int j = 0; j < TJ; ++j)
-#pragma unroll
-      for (int e = 0; e < 16; ++e) acc_r[i][j][e] = 0.0f;
-
-  // ---- one product: K loop over its own operand arrays ---------------------------------
-  // KIND selects arrays, element size and matrix instruction; acc is f32x16 or i32x16.
-  auto product = [&](auto kind_c, auto& acc, const void* xq, const void* wq, const int kdim) {
-    constexpr int KIND = decltype(kind_c)::value;
-    constexpr int EB = (KIND == K_REF || KIND == K_GRID) ? 2 : 1;   // bytes per element
-    constexpr int TK = ROW_B / EB;                                  // K elements per stage
-    constexpr int NG = (KIND == K_F8) ? CH / 4 : CH / 2;            // matrix groups per stage (TI*TJ instructions each)
-    const char* xb; const char* wb; int64_t xrow, wrow;
-    if constexpr (KIND == K_REF) { xb = reinterpret_cast<const char*>(a.x); wb = reinterpret_cast<const char*>(a.w); xrow = a.ldx * 2; wrow = a.ldw * 2; }
-    else { xb = static_cast<const char*>(xq); wb = static_cast<const char*>(wq); xrow = wrow = static_cast<int64_t>(static_cast<uint32_t>(kdim) * EB); }
-
-    // This lane's global source of each of its wave's deposits at k = 0 (deposit i of a
-    // stage covers chunk slots 64 i .. 64 i + 63 and is issued by wave i % NW: rows that are multiples of 64
-    // apart, so the lane fetches the same chunk of each).
-    // Rows past the edge repeat the last one (masked later): `more_x`, `more_w` rows exist beyond the lane's first.
-    const int row0 = wave * 8 + (lane >> 3), kc = (lane & 7) ^ swz(row0);
-    const int row_x = m0 + row0 < a.M ? m0 + row0 : a.M - 1, row_w = n0 + row0 < a.N ? n0 + row0 : a.N - 1;
-    const int more_x = a.M - 1 - row_x, more_w = a.N - 1 - row_w;
-    const char* const src_x = xb + static_cast<int64_t>(row_x) * xrow + kc * 16;
-    const char* const src_w = wb + static_cast<int64_t>(row_w) * wrow + kc * 16;
-    auto source = [&](int d) {
-      constexpr int STEP = NW * 8;
+    for (int d = 0; d < DEP; ++d) {
       const bool x = d * STEP < TM;
-      int more = x ? more_x : more_w;
-      asm volatile("" : "+v"(more));   // computed at each use: kept, the DEP sources would take 8 registers more
-      const int e = x ? d * STEP : d * STEP - TM;
-      const uint64_t rows = static_cast<uint32_t>(e < more ? e : more);
-      return (x ? src_x : src_w) + rows * static_cast<uint64_t>(x ? xrow : wrow);
-    };
-    // K is a multiple of 64 elements, so the last stage of an 8-bit product may hold only
-    // half a row (64 bytes).  Its deposits then fetch the valid half twice (addresses stay
-    // inside the row) and the matrix groups of the missing half are skipped.
-    const int KT = (kdim + TK - 1) / TK;
-    const bool half_tail = (EB == 1) && (kdim % TK) != 0;   // 16-bit stages hold 64 elements: never
-    const int back = (EB == 1 && kc >= CH / 2) ? ROW_B / 2 : 0;
-    auto issue = [&](int kt, int buf, int lo, int hi) {   // deposits [lo, hi) of stage kt into the buffer at byte `buf`
-      int64_t kb = static_cast<int64_t>(kt) * ROW_B;
-      if constexpr (EB == 1) kb -= (half_tail && kt == KT - 1) ? back : 0;
+      const int row = row0 + (x ? d * STEP : d * STEP - TM), last = (x ? a.M - m0 : a.N - n0) - 1;
+      off[d] = static_cast<off_t>(row < last ? row : last) * static_cast<off_t>(x ? sg.xrow : sg.wrow) + kc * 16;
+    }
+  };
+  auto next_stage = [&]() {
+    dep_left -= 1;
+    dep_x += ROW_B;
+    dep_w += ROW_B;
+    if (dep_left <= 1) {
+      if (dep_left <= 0) next_segment();
+      // The last stage of an 8-bit product may hold half a line per row: the missing half fetches
+      // the valid one again (addresses stay inside the row) and is not multiplied.
+      if (dep_left == 1 && dep_half) {
 #pragma unroll
-      for (int d = 0; d < DEP; ++d)
-        if (d >= lo && d < hi) lds_deposit(source(d) + kb, lds0 + static_cast<uint32_t>(buf + (wave + NW * d) * 1024));
-    };
+        for (int d = 0; d < DEP; ++d) off[d] -= kc >= CH / 2 ? ROW_B / 2 : 0;
+      }
+    }
+  };
+  auto issue = [&](int buf, int lo, int hi) {   // deposits [lo, hi) of the current stage into the buffer at byte `buf`
+#pragma unroll
+    for (int d = 0; d < DEP; ++d)
+      if (d >= lo && d < hi) lds_deposit(d * STEP < TM ? dep_x : dep_w, off[d], lds0 + static_cast<uint32_t>(buf + (wave + NW * d) * 1024));
+  };
+
+  // Stages 0 and 1 and the first deposits of stage 2.
+  int b0 = 0, b1 = STAGE, b2 = 2 * STAGE;   // buffers of the stages k, k + 1, k + 2
+  static_assert(NST == 3, "three buffers in turn");
+  next_stage();
+  issue(b0, 0, DEP);
+  next_stage();
+  issue(b1, 0, DEP);
+  wait_deposits_and_reads<DEP>();
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" ::: "memory");
+  next_stage();
+  issue(b2, 0, FIRST);
+
+  // ---- one product (or side part): a loop over its stages ---------------------------------
+  // KIND selects element size and matrix instruction; acc is f32x16 or i32x16.
+  auto product = [&](auto kind_c, auto& acc, const int stages, const bool half) {
+    constexpr int KIND = decltype(kind_c)::value;
+    constexpr bool EIGHT = KIND == K_I8 || KIND == K_F8;
+    constexpr int NG = (KIND == K_F8) ? CH / 4 : CH / 2;            // matrix groups per stage (TI*TJ instructions each)
     // Fragments of group gi of a stage: f[0 .. TI) = A tiles, f[TI ..) = B tiles.
     using frag_t = std::conditional_t<KIND == K_F8, i32x8, i32x4>;
     auto load_frag = [&](const unsigned char* row, int gi) {
@@ -229,13 +279,13 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2, 2)))
 #pragma unroll
       for (int j = 0; j < TJ; ++j) f[TI + j] = load_frag(st + row_b + j * 32 * ROW_B, gi);
     };
-    // The matrix instructions of one group, with the deposits [lo, hi) of stage kt_dep
+    // The matrix instructions of one group, with the deposits [lo, hi) of the current stage
     // spread between them: a wave issues in order, so a burst of deposits (each occupies
     // the texture path for ~18 clocks, and all waves share it) would hold back the
     // matrix instructions behind it while the matrix pipe runs dry.
     // `then` (the next group's fragment reads) follows the first instruction: what that one waits for is its own
     // group's fragments alone.
-    auto run_group = [&](const frag_t (&f)[TI + TJ], auto more_c, int kt_dep, int buf, int lo, int hi, auto then) {
+    auto run_group = [&](const frag_t (&f)[TI + TJ], int buf, int lo, int hi, auto then) {
 #pragma unroll
       for (int i = 0; i < TI; ++i)
 #pragma unroll
@@ -243,8 +293,8 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2, 2)))
           {
             const int m = i * TJ + j, n = hi - lo;
             __builtin_amdgcn_sched_barrier(0);
-            if (m == 1) then();
-            if constexpr (decltype(more_c)::value) issue(kt_dep, buf, lo + m * n / (TI * TJ), lo + (m + 1) * n / (TI * TJ));
+            if (m == (TI * TJ > 1 ? 1 : 0)) then();
+            issue(buf, lo + m * n / (TI * TJ), lo + (m + 1) * n / (TI * TJ));
             __builtin_amdgcn_sched_barrier(0);
           }
           if constexpr (KIND == K_REF || KIND == K_GRID) {
@@ -257,30 +307,41 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2, 2)))
           }
         }
     };
-    // One K step.  Its last group is preceded by a barrier that makes stage kt+1 visible to everyone and tells
-    // everyone that stage kt is no longer read (its last fragments are in registers): the fragments of the next step's
+    // One K step.  Its last group is preceded by a barrier that makes stage k+1 visible to everyone and tells
+    // everyone that stage k is no longer read (its last fragments are in registers): the fragments of the next step's
     // first group are requested there, ahead of a whole group of matrix instructions, and the deposits of
-    // stage kt+NST may begin to overwrite stage kt.  So no step starts by waiting for LDS, and up to three
+    // stage k+NST may begin to overwrite stage k.  So no step starts by waiting for LDS, and up to three
     // stages are on their way or unread.  Inside the step the fragments of group g+1 are requested before the matrix
     // instructions of group g are issued, and the deposits are spread over the groups so
     // that the texture path works while the matrix cores do.
-    // (Straight-line code: where the step had branches, the compiler moved matrix instructions down past them.)
+    // (Straight-line code away from the ends: with the ends' branch in every step 2048 x 11008 x 4096 takes 532 us.)
     frag_t f[2][TI + TJ];
-    int b0 = 0, b1 = STAGE, b2 = 2 * STAGE;   // buffers of the stages kt, kt + 1, kt + 2
-    static_assert(NST == 3, "three buffers in turn");
-    auto step = [&](int kt, auto groups_c, auto more2_c, auto more3_c) {   // moreN: there is a stage kt + N
-      constexpr int GROUPS = decltype(groups_c)::value;
+    auto step = [&](auto inside_c, auto last_c, const bool drop) {   // last step, drop: the second half of the stage counts nothing
 #pragma unroll
-      for (int gi = 0; gi < GROUPS; ++gi) {
-        if (gi + 1 < GROUPS) {
-          run_group(f[gi & 1], more2_c, kt + 2, b2, (gi + 1) * DEP / NG, (gi + 2) * DEP / NG, [&] { load_group(s_buf + b0, gi + 1, f[(gi + 1) & 1]); });
+      for (int gi = 0; gi < NG; ++gi) {
+        if constexpr (decltype(last_c)::value && EIGHT) {
+          if (gi >= NG / 2) {
+#pragma unroll
+            for (int i = 0; i < TI; ++i) f[gi & 1][i] = drop ? frag_t{} : f[gi & 1][i];
+          }
+        }
+        if (gi + 1 < NG) {
+          run_group(f[gi & 1], b2, FIRST + gi * (DEP - FIRST) / (NG - 1), FIRST + (gi + 1) * (DEP - FIRST) / (NG - 1),
+                    [&] { load_group(s_buf + b0, gi + 1, f[(gi + 1) & 1]); });
         } else {
-          // this wave's deposits of stage kt+1 have landed, its fragment reads are done; stage kt+2 may stay in flight
-          wait_deposits_and_reads<decltype(more2_c)::value ? DEP : 0>();
+          // this wave's deposits of stage k+1 have landed, its fragment reads are done; stage k+2 may stay in flight
+          wait_deposits_and_reads<DEP>();
           __builtin_amdgcn_s_barrier();
           asm volatile("" ::: "memory");     // LDS reads below must not move above the barrier
-          // (after the last step: whatever the buffer holds, unused; a conditional load would keep f[0] twice)
-          run_group(f[gi & 1], more3_c, kt + 3, b0, 0, DEP / NG, [&] { load_group(s_buf + b1, 0, f[(gi + 1) & 1]); });
+          if constexpr (decltype(inside_c)::value) {
+            dep_left -= 1;
+            dep_x += ROW_B;
+            dep_w += ROW_B;
+          } else {
+            next_stage();
+          }
+          // (behind the last step: the next product's, which it reads again as its own kind)
+          run_group(f[gi & 1], b0, 0, FIRST, [&] { load_group(s_buf + b1, 0, f[(gi + 1) & 1]); });
         }
       }
       const int b = b0;
@@ -288,34 +349,21 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2, 2)))
       b1 = b2;
       b2 = b;
     };
-    // Prologue: stages 0 and 1, and what a step before the first would have issued of stage 2.
-    issue(0, b0, 0, DEP);
-    if (KT > 1) {
-      issue(1, b1, 0, DEP);
-      wait_deposits_and_reads<DEP>();
-    } else {
-      wait_deposits_and_reads<0>();
-    }
-    __builtin_amdgcn_s_barrier();
-    asm volatile("" ::: "memory");
-    if (KT > 2) issue(2, b2, 0, DEP / NG);
-    load_group(s_buf, 0, f[0]);
-    using full = std::integral_constant<int, NG>;
+    load_group(s_buf + b0, 0, f[0]);
     using yes = std::true_type;
     using no = std::false_type;
-    for (int kt = 0; kt < KT - 3; ++kt) step(kt, full{}, yes{}, yes{});
-    if (KT > 2) step(KT - 3, full{}, yes{}, no{});
-    if (KT > 1) step(KT - 2, full{}, no{}, no{});
-    if (EB == 1 && half_tail) step(KT - 1, std::integral_constant<int, NG / 2>{}, no{}, no{});
-    else step(KT - 1, full{}, no{}, no{});
-    // The last step's barrier: all deposits of this product have landed and nobody reads them any more, so the
-    // next product's prologue may overwrite the buffers.
+    int k = EIGHT ? 1 : 0;
+    // the deposits' next stage is inside the product, and not its last
+    for (; k < stages - 4; ++k) step(yes{}, no{}, false);
+    for (; k < stages; ++k) step(no{}, no{}, false);
+    if constexpr (EIGHT) step(no{}, yes{}, half);
   };
 
   // ---- squared differences in fp64.  Accumulator value e of a lane in one 32x32 tile is
   // output (row 8*(e/4) + 4*g + e%4, column lane%32) of that tile; rows and columns past
   // the matrix edge hold repeats of the last row and are skipped.  The first reduction
   // also sums Y^2.
+  f32x16 acc_r[TI][TJ];
   double p = 0.0;
   auto sq_diff = [&](auto with_p_c, const auto& acc_q, const float* sx, const float* sw_) {
     constexpr bool WITH_P = decltype(with_p_c)::value;
@@ -358,7 +406,16 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2, 2)))
     return wave_sum(e_q);
   };
 
-  product(std::integral_constant<int, K_REF>{}, acc_r, nullptr, nullptr, a.K);
+  auto clear = [&](auto& acc) {
+#pragma unroll
+    for (int i = 0; i < TI; ++i)
+#pragma unroll
+      for (int j = 0; j < TJ; ++j)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) acc[i][j][e] = 0;
+  };
+  clear(acc_r);
+  product(std::integral_constant<int, K_REF>{}, acc_r, a.seg[SEG_REF].stages, false);
   double e_q[2] = {0.0, 0.0};
   auto quantized = [&](auto kind_c, auto slot_c) {
     constexpr int KIND = decltype(kind_c)::value;
@@ -366,24 +423,19 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2, 2)))
     if constexpr (KIND != WA_NONE) {
       using acc_t = std::conditional_t<KIND == K_I8, i32x16, f32x16>;
       acc_t acc_q[TI][TJ];
-#pragma unroll
-      for (int i = 0; i < TI; ++i)
-#pragma unroll
-        for (int j = 0; j < TJ; ++j)
-#pragma unroll
-          for (int e = 0; e < 16; ++e) acc_q[i][j][e] = 0;
-      product(kind_c, acc_q, a.q[SLOT].x, a.q[SLOT].w, a.K);
+      clear(acc_q);
+      product(kind_c, acc_q, a.seg[SEG_Q + 2 * SLOT].stages, a.seg[SEG_Q + 2 * SLOT].half != 0);
       // The columns split off from an fp8-unit product: one K step from their grid values on
       // the bf16 matrix cores into the same accumulators (both accumulate in fp32).
-      if constexpr (KIND == K_F8)
-        if (a.q[SLOT].xs) product(std::integral_constant<int, K_GRID>{}, acc_q, a.q[SLOT].xs, a.q[SLOT].ws, SIDE_K);
+      if constexpr (KIND == K_F8) product(std::integral_constant<int, K_GRID>{}, acc_q, a.seg[SEG_SIDE + 2 * SLOT].stages, false);
       // the first reduction also sums Y^2
-      e_q[SLOT] = sq_diff(std::integral_constant<bool, SLOT == 0>{}, acc_q, a.q[SLOT].sx, a.q[SLOT].sw);
+      e_q[SLOT] = sq_diff(std::integral_constant<bool, SLOT == 0>{}, acc_q, a.sx[SLOT], a.sw[SLOT]);
     }
   };
   quantized(std::integral_constant<int, KIND1>{}, std::integral_constant<int, 0>{});
   quantized(std::integral_constant<int, KIND2>{}, std::integral_constant<int, 1>{});
   p = wave_sum(p);
+  wait_deposits_and_reads<0>();   // LDS is given back with the workgroup: the unused deposits have to have landed
   if (lane == 0) { s_red[0][wave] = e_q[0]; s_red[1][wave] = e_q[1]; s_red[2][wave] = p; }
   __syncthreads();
   if (tid == 0) {
@@ -391,44 +443,69 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2, 2)))
     double t[3] = {0.0, 0.0, 0.0};
     for (int q = 0; q < 3; ++q)
       for (int w = 0; w < NW; ++w) t[q] += s_red[q][w];   // fixed order
-    if (a.q[0].part) a.q[0].part[out] = t[0];
-    if (a.q[1].part) a.q[1].part[out] = t[1];
-    a.part_p[out] = t[2];
+    for (int q = 0; q < 3; ++q)
+      if (a.part[q]) a.part[q][out] = t[q];
   }
 }
 
+using Large = Tile<256, 128, 64, 64>;    // one workgroup per compute unit, two waves per SIMD
+using Small = Tile<64, 64, 32, 32>;      // three
+
 }  // namespace
 
-int wa_gemm_blocks(int64_t M, int64_t N) {
-  return static_cast<int>(((M + TM - 1) / TM) * ((N + TN - 1) / TN));
+// Large tiles; small ones for rows so far apart that the offsets of a large tile's rows leave 32 bits.
+WaPlan wa_gemm_plan(int64_t M, int64_t N, int64_t K, int64_t ldx, int64_t ldw) {
+  auto tiles = [&](auto t) { using T = decltype(t); return ((M + T::TM - 1) / T::TM) * ((N + T::TN - 1) / T::TN); };
+  // rows whose offsets fit 32 bits
+  const int64_t rows = ((int64_t{1} << 32) - 1 - 2 * K) / (2 * std::max(std::max(ldx, ldw), K)) + 1;
+  WaPlan p{};
+  p.tile = rows < Large::TM ? WaPlan::kWide : WaPlan::kLarge;
+  p.blocks = static_cast<int>(p.tile == WaPlan::kLarge ? tiles(Large{}) : tiles(Small{}));
+  return p;
 }
 
 int launch_wa_gemm(const WaGemmParams& p, hipStream_t st) {
   if (p.K % 64 != 0) return MOFQ_ERR_UNSUPPORTED;
   if (p.q[0].kind == WA_NONE) return MOFQ_ERR_INVALID_ARG;   // the first slot carries the Y^2 sum
   GemmArgs a{};
-  a.x = static_cast<const uint16_t*>(p.x); a.ldx = p.ldx;
-  a.w = static_cast<const uint16_t*>(p.w); a.ldw = p.ldw;
+  const int32_t lines8 = static_cast<int32_t>((p.K + 127) / 128), lines16 = static_cast<int32_t>(p.K / 64);
+  a.seg[SEG_REF] = Segment{p.x, p.w, p.ldx * 2, p.ldw * 2, lines16, 0};
   for (int i = 0; i < 2; ++i) {
-    if ((p.q[i].xs != nullptr) != (p.q[i].ws != nullptr)) return MOFQ_ERR_INVALID_ARG;
-    if (p.q[i].xs && p.q[i].kind != WA_FP8) return MOFQ_ERR_INVALID_ARG;
-    a.q[i] = QProd{p.q[i].x, p.q[i].w, p.q[i].sx, p.q[i].sw, p.q[i].part, p.q[i].xs, p.q[i].ws};
+    const WaProduct& q = p.q[i];
+    if ((q.xs != nullptr) != (q.ws != nullptr)) return MOFQ_ERR_INVALID_ARG;
+    if (q.xs && q.kind != WA_FP8) return MOFQ_ERR_INVALID_ARG;
+    if (q.kind == WA_NONE) continue;
+    const bool eight = q.kind != WA_GRID_BF16;
+    const int64_t row = eight ? p.K : 2 * p.K;
+    a.seg[SEG_Q + 2 * i] = Segment{q.x, q.w, row, row, eight ? lines8 : lines16, eight && p.K % 128 != 0};
+    if (q.xs) a.seg[SEG_SIDE + 2 * i] = Segment{q.xs, q.ws, 2 * SIDE_K, 2 * SIDE_K, 1, 0};
+    a.sx[i] = q.sx;
+    a.sw[i] = q.sw;
+    a.part[i] = q.part;
   }
   a.w_per_channel = p.w_per_channel;
-  a.M = static_cast<int32_t>(p.M); a.N = static_cast<int32_t>(p.N); a.K = static_cast<int32_t>(p.K);
-  a.tiles_m = static_cast<int32_t>((p.M + TM - 1) / TM);
-  a.tiles_n = static_cast<int32_t>((p.N + TN - 1) / TN);
-  a.part_p = p.part_p;
-  const dim3 grid(static_cast<unsigned>(wa_gemm_blocks(p.M, p.N)));
+  a.M = static_cast<int32_t>(p.M); a.N = static_cast<int32_t>(p.N);
+  a.part[2] = p.part_p;
   const int k1 = p.q[0].kind, k2 = p.q[1].kind;
-  bool launched = false;
+  const WaPlan plan = wa_gemm_plan(p.M, p.N, p.K, p.ldx, p.ldw);
+  auto launch = [&](auto k1_c, auto k2_c) {
+    constexpr int K1 = decltype(k1_c)::value, K2 = decltype(k2_c)::value;
+    auto tiled = [&](auto tile_c, auto kernel) {
+      using T = decltype(tile_c);
+      a.tiles_m = static_cast<int32_t>((p.M + T::TM - 1) / T::TM);
+      a.tiles_n = static_cast<int32_t>((p.N + T::TN - 1) / T::TN);
+      hipLaunchKernelGGL(kernel, dim3(static_cast<unsigned>(plan.blocks)), dim3(T::NW * 64), 0, st, a);
+    };
+    if (plan.tile == WaPlan::kLarge) tiled(Large{}, wa_gemm_kernel<Large, K1, K2, false>);
+    else tiled(Small{}, wa_gemm_kernel<Small, K1, K2, true>);
+    return hip_status(hipGetLastError());
+  };
 #define MOFQ_WA(A, B) \
-  if (k1 == (A) && k2 == (B)) { hipLaunchKernelGGL((wa_gemm_kernel<A, B>), grid, dim3(NW * 64), 0, st, a); launched = true; }
+  if (k1 == (A) && k2 == (B)) return launch(std::integral_constant<int, A>{}, std::integral_constant<int, B>{});
   MOFQ_WA(WA_INT8, WA_GRID_BF16) MOFQ_WA(WA_INT8, WA_FP8) MOFQ_WA(WA_INT8, WA_NONE)
   MOFQ_WA(WA_GRID_BF16, WA_NONE) MOFQ_WA(WA_FP8, WA_NONE) MOFQ_WA(WA_GRID_BF16, WA_GRID_BF16)
 #undef MOFQ_WA
-  if (!launched) return MOFQ_ERR_UNSUPPORTED;
-  return hip_status(hipGetLastError());
+  return MOFQ_ERR_UNSUPPORTED;
 }
 
 }  // namespace mofq
