@@ -292,6 +292,7 @@ struct WaWs {
   uint8_t* xq[2];   // [0] INT8 codes, [1] E4M3 codes (fp8-unit mode) or bf16 grid values
   uint8_t* wq[2];
   double* part[3];  // INT8 error, E4M3 error, reference energy; one value per output tile
+  void* partial;
   int blocks;
   size_t bytes;
 };
@@ -309,7 +310,9 @@ WaWs carve_wa(void* ws, const mofq_tensor_t* w, const mofq_tensor_t* x, int n_ca
     a.xq[f] = c.take<uint8_t>(static_cast<size_t>(x->rows) * x->cols * (f ? 2 : 1));
     a.wq[f] = c.take<uint8_t>(static_cast<size_t>(w->rows) * w->cols * (f ? 2 : 1));
   }
-  a.blocks = wa_plan(w, x).blocks;
+  const WaPlan plan = wa_plan(w, x);
+  a.blocks = plan.blocks;
+  a.partial = c.take<uint8_t>(plan.partial_bytes);
   for (int i = 0; i < 3; ++i) a.part[i] = c.take<double>(a.blocks);
   a.bytes = off + (c.off + kAlign - 1) / kAlign * kAlign;
   return a;
@@ -337,6 +340,7 @@ struct WoOutWs {
   WOnlyWs wrec;
   uint8_t* wg[2];   // grid values of W per candidate, bf16, dense
   double* part[3];  // error per candidate, reference energy; one value per output tile
+  void* partial;
   int blocks;
   size_t bytes;
 };
@@ -349,7 +353,9 @@ WoOutWs carve_wo_output(void* ws, const mofq_tensor_t* w, const mofq_tensor_t* x
   char* base = static_cast<char*>(ws);
   Carver c(base ? base + a.wrec.bytes : nullptr);
   for (int f = 0; f < n_cand; ++f) a.wg[f] = c.take<uint8_t>(static_cast<size_t>(w->rows) * w->cols * 2);
-  a.blocks = wa_plan(w, x).blocks;
+  const WaPlan plan = wa_plan(w, x);
+  a.blocks = plan.blocks;
+  a.partial = c.take<uint8_t>(plan.partial_bytes);
   for (int i = 0; i < 3; ++i) a.part[i] = c.take<double>(a.blocks);
   a.bytes = a.wrec.bytes + (c.off + kAlign - 1) / kAlign * kAlign;
   return a;
@@ -396,6 +402,7 @@ int wo_output_score(const mofq_tensor_t* w, const mofq_tensor_t* x, const int32_
   g.w_per_channel = w_cfg->gran == MOFQ_PER_CHANNEL;
   g.M = x->rows; g.N = w->rows; g.K = w->cols;
   g.part_p = a.part[2];
+  g.partial = a.partial;
   if (ev0 && hipEventRecord(ev0, st) != hipSuccess) return MOFQ_ERR_HIP;
   if ((rc = launch_wa_gemm(g, st))) return rc;
   if (ev1 && hipEventRecord(ev1, st) != hipSuccess) return MOFQ_ERR_HIP;
@@ -500,6 +507,7 @@ int wa_score(const mofq_tensor_t* w, const mofq_tensor_t* x, const int32_t* cand
   g.w_per_channel = w_cfg->gran == MOFQ_PER_CHANNEL;
   g.M = x->rows; g.N = w->rows; g.K = w->cols;
   g.part_p = a.part[2];
+  g.partial = a.partial;
   if (ev0 && hipEventRecord(ev0, st) != hipSuccess) return MOFQ_ERR_HIP;
   if ((rc = launch_wa_gemm(g, st))) return rc;
   if (ev1 && hipEventRecord(ev1, st) != hipSuccess) return MOFQ_ERR_HIP;
@@ -587,6 +595,7 @@ struct WaLayerWs {
   WaFusedTensorWs x, w;
   double* part[3];
   int blocks;     // output tiles: values in each part
+  void* partial;  // the group's, for one matrix kernel after the other
   bool fresh_x;   // false: x is the previous layer's (same descriptor, same group)
 };
 
@@ -614,6 +623,7 @@ bool wa_same_x(const mofq_tensor_t* x, int i) {
 size_t carve_wa_group(void* arena, int i0, int n, const mofq_tensor_t* w, const mofq_tensor_t* x, bool exact,
                       WaLayerWs* out) {
   Carver c(arena);
+  size_t partial_bytes = 0;
   for (int j = 0; j < n; ++j) {
     const int i = i0 + j;
     WaLayerWs l{};
@@ -643,10 +653,14 @@ size_t carve_wa_group(void* arena, int i0, int n, const mofq_tensor_t* w, const 
         }
       }
     }
-    l.blocks = wa_plan(&w[i], &x[i]).blocks;
-    for (int q = 0; q < 3; ++q) l.part[q] = c.take<double>(l.blocks);
+    const WaPlan plan = wa_plan(&w[i], &x[i]);
+    l.blocks = plan.blocks;
+    for (int q = 0; q < 3; ++q) l.part[q] = c.take<double>(plan.blocks);
+    partial_bytes = std::max(partial_bytes, plan.partial_bytes);
     if (out) out[j] = l;
   }
+  uint8_t* const partial = c.take<uint8_t>(partial_bytes);   // the matrix kernels follow each other
+  for (int j = 0; out && j < n; ++j) out[j].partial = partial;
   return (c.off + kAlign - 1) / kAlign * kAlign;
 }
 
@@ -728,6 +742,7 @@ int select_layers_wa(int n_layers, const mofq_tensor_t* w, const mofq_tensor_t* 
       g.w_per_channel = 0;
       g.M = x[i].rows; g.N = w[i].rows; g.K = w[i].cols;
       g.part_p = l[j].part[2];
+      g.partial = l[j].partial;
       if (ev(ev_begin, i) && hipEventRecord(ev(ev_begin, i), st) != hipSuccess) return static_cast<int>(MOFQ_ERR_HIP);
       if ((r = launch_wa_gemm(g, st))) return r;
       if (ev(ev_end, i) && hipEventRecord(ev(ev_end, i), st) != hipSuccess) return static_cast<int>(MOFQ_ERR_HIP);

@@ -184,12 +184,15 @@ struct WaGemmParams {
   int32_t w_per_channel;
   int64_t M, N, K;
   double* part_p;                  // [WaPlan::blocks] sum of Y^2
+  void* partial;                   // scratch, WaPlan::partial_bytes
 };
 // How a layer's products are tiled: by its shape alone (the errors' sums depend on it).
 struct WaPlan {
-  enum : int { kLarge, kWide };
+  enum : int { kLarge, kMedium, kSmall, kWide };
   int tile;
+  int run;                 // > 0: every product is cut into pieces of up to so many stages (64 sixteen-bit elements of K), each a workgroup's
   int blocks;              // output tiles
+  size_t partial_bytes;    // of WaGemmParams::partial
 };
 WaPlan wa_gemm_plan(int64_t M, int64_t N, int64_t K, int64_t ldx, int64_t ldw);
 int launch_wa_gemm(const WaGemmParams& p, hipStream_t stream);

@@ -19,7 +19,7 @@
 // (128 registers for its 64x64 share), so that eight waves, two per SIMD, fit: while
 // one waits at the stage barrier or for its fragments the other keeps the matrix core
 // busy.  The 256x128 workgroup tile needs 25 % fewer operand bytes per flop than
-// 128x128.
+// 128x128.  (That is for grids that fill the chip; wa_gemm_plan has the tiles of smaller ones.)
 //
 // What bounds it on full grids: power.  The part holds 1.73 GHz with the matrix cores busy for 0.67 of the clocks
 // (2048 x 11008 x 4096, three bf16 products, 456 us); four waves of 128 x 64, with a quarter less LDS traffic, run at 1.87 GHz
@@ -63,6 +63,7 @@ typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef int i32x16 __attribute__((ext_vector_type(16)));
 typedef int i32x4 __attribute__((ext_vector_type(4)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef int i32x8 __attribute__((ext_vector_type(8)));
 
 constexpr int SIDE_K = kWaSideCols;             // K extent of a product's optional second part: one 16-bit stage
@@ -82,6 +83,10 @@ struct GemmArgs {
   int32_t w_per_channel;
   int32_t M, N;
   int32_t tiles_m, tiles_n;
+  // products cut into pieces (PIECES): accumulators [piece][tile][wave][TI * TJ * 4][lane][4], and the first piece of
+  // the reference, of each product, and the end
+  float* partial;
+  int32_t piece0[4];
 };
 
 // ---- LDS stage ----------------------------------------------------------------------
@@ -135,7 +140,7 @@ template <int TM_, int TN_, int WM_, int WN_> struct Tile {
 
 // Workgroup -> tile.  Consecutive workgroup ids go to different XCDs (8 of them, each
 // with its own L2), so ids are first regrouped so that one XCD works on a contiguous
-// range of tiles, and a range is walked in bands of 4 tile rows: the 32 workgroups
+// range of tiles (of pieces of tiles), and a range is walked in bands of 4 tile rows: the 32 workgroups
 // resident on an XCD then share 4 X tiles and 8 W tiles.
 MOFQ_DEV int regrouped(int id, int total) {
   const int per_xcd = total / 8;
@@ -151,7 +156,7 @@ MOFQ_DEV void tile_of(const GemmArgs& a, int t, int& bm, int& bn) {
   bn = in_band / rows_in_band;
 }
 
-template <typename T, int KIND1, int KIND2, bool WIDE>
+template <typename T, int KIND1, int KIND2, bool PIECES, bool WIDE>
 __global__ __launch_bounds__(T::NW * 64) __attribute__((amdgpu_waves_per_eu(T::PER_SIMD, T::PER_SIMD))) void wa_gemm_kernel(const GemmArgs a) {
   constexpr int TM = T::TM, TN = T::TN, WM = T::WM, WN = T::WN, NW = T::NW;
   constexpr int TI = WM / 32, TJ = WN / 32;
@@ -170,8 +175,11 @@ __global__ __launch_bounds__(T::NW * 64) __attribute__((amdgpu_waves_per_eu(T::P
   const int wm = wave / (TN / WN), wn = wave % (TN / WN);
   const int r = lane & 31, g = lane >> 5;
 
+  const int tiles = a.tiles_m * a.tiles_n;
+  int t = regrouped(blockIdx.x, gridDim.x), piece = 0;
+  if constexpr (PIECES) { piece = t / tiles; t -= piece * tiles; }
   int bm, bn;
-  tile_of(a, regrouped(blockIdx.x, gridDim.x), bm, bn);
+  tile_of(a, t, bm, bn);
   const int m0 = bm * TM, n0 = bn * TN;
 
   // LDS byte offsets of this lane's fragment rows inside a stage, and of the chunks it
@@ -201,10 +209,23 @@ __global__ __launch_bounds__(T::NW * 64) __attribute__((amdgpu_waves_per_eu(T::P
   const char* dep_x = nullptr;
   const char* dep_w = nullptr;
   int dep_left = 0, dep_half = 0, dep_seg = -1;
+  // A piece: some stages of one product, with the side part behind its last ones.
+  int mine = SEG_REF, first_stage = 0, end_stage = 0;
+  bool last_piece = false;
+  if constexpr (PIECES) {
+    const int q = (piece >= a.piece0[1]) + (piece >= a.piece0[2]);
+    mine = q == 0 ? static_cast<int>(SEG_REF) : SEG_Q + 2 * (q - 1);
+    const int n = a.piece0[q + 1] - a.piece0[q], i = piece - a.piece0[q];
+    first_stage = a.seg[mine].stages * i / n;
+    end_stage = a.seg[mine].stages * (i + 1) / n;
+    last_piece = i == n - 1;
+    dep_seg = mine - 1;
+  }
+  const int end_seg = PIECES ? (mine != SEG_REF && last_piece ? mine + 2 : mine + 1) : static_cast<int>(N_SEG);
   auto next_segment = [&]() {
     int s = dep_seg + 1;
-    while (s < N_SEG && a.seg[s].stages == 0) ++s;
-    if (s == N_SEG) {       // past the last stage: it is fetched again, unused
+    while (s < end_seg && a.seg[s].stages == 0) ++s;
+    if (s == end_seg) {       // past the last stage: it is fetched again, unused
       dep_x -= ROW_B;
       dep_w -= ROW_B;
       dep_left = 1;
@@ -217,6 +238,14 @@ __global__ __launch_bounds__(T::NW * 64) __attribute__((amdgpu_waves_per_eu(T::P
     dep_w = static_cast<const char*>(sg.w) + n0 * sg.wrow;
     dep_left = sg.stages;
     dep_half = sg.half;
+    if constexpr (PIECES) {
+      if (s == mine) {
+        dep_x += first_stage * ROW_B;
+        dep_w += first_stage * ROW_B;
+        dep_left = end_stage - first_stage;
+        dep_half = sg.half && last_piece;
+      }
+    }
 #pragma unroll
     for (int d = 0; d < DEP; ++d) {
       const bool x = d * STEP < TM;
@@ -414,6 +443,42 @@ __global__ __launch_bounds__(T::NW * 64) __attribute__((amdgpu_waves_per_eu(T::P
 #pragma unroll
         for (int e = 0; e < 16; ++e) acc[i][j][e] = 0;
   };
+  if constexpr (PIECES) {
+    auto store = [&](const auto& acc) {
+      f32x4* const to = reinterpret_cast<f32x4*>(a.partial) + ((static_cast<int64_t>(piece) * tiles + bm * a.tiles_n + bn) * NW + wave) * (TI * TJ * 4 * 64) + lane;
+#pragma unroll
+      for (int i = 0; i < TI; ++i)
+#pragma unroll
+        for (int j = 0; j < TJ; ++j)
+#pragma unroll
+          for (int q = 0; q < 4; ++q) {
+            i32x4 v;
+#pragma unroll
+            for (int x = 0; x < 4; ++x) {
+              const auto one = acc[i][j][4 * q + x];
+              v[x] = __builtin_bit_cast(int, one);
+            }
+            to[((i * TJ + j) * 4 + q) * 64] = __builtin_bit_cast(f32x4, v);
+          }
+    };
+    const int stages = end_stage - first_stage;
+    auto run = [&](auto kind_c) {
+      constexpr int KIND = decltype(kind_c)::value;
+      if constexpr (KIND != WA_NONE) {
+        using acc_t = std::conditional_t<KIND == K_I8, i32x16, f32x16>;
+        acc_t acc[TI][TJ];
+        clear(acc);
+        product(kind_c, acc, stages, last_piece && a.seg[mine].half != 0);
+        if constexpr (KIND == K_F8) product(std::integral_constant<int, K_GRID>{}, acc, last_piece ? a.seg[mine + 1].stages : 0, false);
+        store(acc);
+      }
+    };
+    if (mine == SEG_REF) run(std::integral_constant<int, K_REF>{});
+    else if (mine == SEG_Q) run(std::integral_constant<int, KIND1>{});
+    else run(std::integral_constant<int, KIND2>{});
+    wait_deposits_and_reads<0>();   // LDS is given back with the workgroup: the unused deposits have to have landed
+    return;
+  }
   clear(acc_r);
   product(std::integral_constant<int, K_REF>{}, acc_r, a.seg[SEG_REF].stages, false);
   double e_q[2] = {0.0, 0.0};
@@ -448,19 +513,111 @@ __global__ __launch_bounds__(T::NW * 64) __attribute__((amdgpu_waves_per_eu(T::P
   }
 }
 
+// The sums of a tile whose products were cut into pieces: fp32 (int32) partial sums in the order of K, then the
+// squared differences as above.
+template <typename T, int KIND1, int KIND2>
+__global__ __launch_bounds__(T::NW * 64) void wa_pieces_kernel(const GemmArgs a) {
+  constexpr int NW = T::NW, TI = T::WM / 32, TJ = T::WN / 32;
+  __shared__ double s_red[3][NW];
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int bm = blockIdx.x / a.tiles_n, bn = blockIdx.x - bm * a.tiles_n;
+  const int m = bm * T::TM + wave / (T::TN / T::WN) * T::WM + 4 * (lane >> 5), n0 = bn * T::TN + wave % (T::TN / T::WN) * T::WN + (lane & 31);
+  const int64_t piece = static_cast<int64_t>(gridDim.x) * NW * (TI * TJ * 4 * 64);   // f32x4 from piece to piece
+  const f32x4* const from = reinterpret_cast<const f32x4*>(a.partial) + (static_cast<int64_t>(blockIdx.x) * NW + wave) * (TI * TJ * 4 * 64) + lane;
+  double e[2] = {0.0, 0.0}, p = 0.0;
+#pragma unroll
+  for (int j = 0; j < TJ; ++j) {
+    const int n = n0 + j * 32;
+    const bool col_ok = n < a.N;
+    double c[2];
+#pragma unroll
+    for (int s = 0; s < 2; ++s)
+      c[s] = (s == 0 || KIND2 != WA_NONE) ? (a.sx[s] ? static_cast<double>(*a.sx[s]) : 1.0) * static_cast<double>(a.sw[s][a.w_per_channel && col_ok ? n : 0]) : 0.0;
+#pragma unroll
+    for (int i = 0; i < TI; ++i) {
+      const f32x4* const at = from + (i * TJ + j) * 4 * 64;
+      auto sum = [&](auto kind_c, int q, double (&v)[16]) {
+        using vec = std::conditional_t<decltype(kind_c)::value == K_I8, i32x4, f32x4>;
+        vec s[4] = {};
+        for (int k = a.piece0[q]; k < a.piece0[q + 1]; ++k)
+#pragma unroll
+          for (int h = 0; h < 4; ++h) s[h] += __builtin_bit_cast(vec, at[k * piece + h * 64]);
+#pragma unroll
+        for (int x = 0; x < 16; ++x) v[x] = static_cast<double>(s[x / 4][x % 4]);
+      };
+      double y[16], v[16];
+      sum(std::integral_constant<int, K_REF>{}, 0, y);
+      auto add = [&](int s) {
+#pragma unroll
+        for (int x = 0; x < 16; ++x) {
+          const bool ok = col_ok && m + i * 32 + 8 * (x / 4) + x % 4 < a.M;
+          const double d = ok ? __builtin_fma(-c[s], v[x], y[x]) : 0.0;
+          e[s] = __builtin_fma(d, d, e[s]);
+          if (s == 0) p = ok ? __builtin_fma(y[x], y[x], p) : p;
+        }
+      };
+      sum(std::integral_constant<int, KIND1>{}, 1, v);
+      add(0);
+      if constexpr (KIND2 != WA_NONE) {
+        sum(std::integral_constant<int, KIND2>{}, 2, v);
+        add(1);
+      }
+    }
+  }
+  const double w[3] = {wave_sum(e[0]), wave_sum(e[1]), wave_sum(p)};
+  if (lane < 3) s_red[lane][wave] = lane == 0 ? w[0] : (lane == 1 ? w[1] : w[2]);
+  __syncthreads();
+  if (threadIdx.x < 3 && a.part[threadIdx.x]) {
+    double t = 0.0;
+    for (int k = 0; k < NW; ++k) t += s_red[threadIdx.x][k];   // fixed order
+    a.part[threadIdx.x][blockIdx.x] = t;
+  }
+}
+
 using Large = Tile<256, 128, 64, 64>;    // one workgroup per compute unit, two waves per SIMD
+using Medium = Tile<128, 128, 64, 64>;   // one, one wave per SIMD
 using Small = Tile<64, 64, 32, 32>;      // three
 
 }  // namespace
 
-// Large tiles; small ones for rows so far apart that the offsets of a large tile's rows leave 32 bits.
+// The tile by the time a K step takes, in units of one of a full grid of large tiles, on 256 compute units: a round of
+// large tiles 1, of medium ones 0.6, of small ones 0.38, 0.51 and 0.7 with one, two and three on a compute unit.
+// Measured, layer selection with INT8 and exact E4M3 products, us, large / medium / small: tokens x rows x columns
+// 2048 x 4096 x 4096 194 / 212 / 289; 1024 x 4096 x 4096 134 / 127 / 168; 777 x 3000 x 5056 155 / 121 / 159;
+// 512 x 4096 x 4096 128 / 101 / 102; 384 x 4096 x 4096 126 / 99 / 95; 384 x 11008 x 4096 202 / 225 / 233;
+// 1536 x 11008 x 4096 458 / 472 / 611; 1024 x 11008 x 4096 340 / 333 / 418.
+// Up to 256 small tiles leave compute units idle, and a tile's three products follow each other: there the products and,
+// with fewer tiles yet, parts of K are workgroups of their own and a second kernel takes the sums.  Small tiles
+// whole / cut to 40 / to 20 stages: 64 x 1024 x 4096 (16 tiles) 66 / 40 / 38; 64 x 512 x 8192 (8) 96 / 42 / 41;
+// 64 x 4096 x 4096 (64) 76 / 56 / 58; 128 x 4096 x 11008 (128) 217 / 166 / 182; 256 x 4096 x 11008 (256) 227 / 232 / 256,
+// into the products alone 226; 256 x 1024 x 4096 (64) 65 / 42 / 43; 1024 x 1024 x 4096 (256) 71 / 69 / 73.  The second
+// launch costs what short products save: 64 x 1024 x 1024 29.4 / - / 30.2, 128 x 8192 x 1024 40 / 44 / 44.
 WaPlan wa_gemm_plan(int64_t M, int64_t N, int64_t K, int64_t ldx, int64_t ldw) {
   auto tiles = [&](auto t) { using T = decltype(t); return ((M + T::TM - 1) / T::TM) * ((N + T::TN - 1) / T::TN); };
+  const int64_t large = tiles(Large{}), medium = tiles(Medium{}), small = tiles(Small{});
+  const int64_t stages = K / 64;
   // rows whose offsets fit 32 bits
   const int64_t rows = ((int64_t{1} << 32) - 1 - 2 * K) / (2 * std::max(std::max(ldx, ldw), K)) + 1;
   WaPlan p{};
-  p.tile = rows < Large::TM ? WaPlan::kWide : WaPlan::kLarge;
-  p.blocks = static_cast<int>(p.tile == WaPlan::kLarge ? tiles(Large{}) : tiles(Small{}));
+  if (rows < Small::TM) {
+    p.tile = WaPlan::kWide;
+  } else {
+    const int64_t per_cu = (small + 255) / 256;
+    const double t_large = static_cast<double>((large + 255) / 256), t_medium = 0.6 * static_cast<double>((medium + 255) / 256);
+    const double t_small = per_cu == 1 ? 0.38 : (per_cu == 2 ? 0.51 : 0.235 * static_cast<double>(per_cu));
+    p.tile = WaPlan::kSmall;
+    if (rows >= Medium::TM && t_medium < t_small) p.tile = WaPlan::kMedium;
+    if (rows >= Large::TM && t_large <= std::min(t_medium, t_small)) p.tile = WaPlan::kLarge;
+  }
+  p.blocks = static_cast<int>(p.tile == WaPlan::kLarge ? large : (p.tile == WaPlan::kMedium ? medium : small));
+  if (p.tile == WaPlan::kSmall && small <= 256 && stages >= 20) {
+    // (at most 16 or 8 pieces of a product, which bounds the scratch: 40 MB or 64 MB)
+    const int64_t run = small <= 48 ? std::max(std::min<int64_t>(20, (stages + 1) / 2), (stages + 15) / 16)
+                                    : (small <= 160 ? std::max<int64_t>(40, (stages + 7) / 8) : stages);
+    p.run = static_cast<int>(run);
+    p.partial_bytes = static_cast<size_t>(3 * ((stages + run - 1) / run) * small) * (Small::TM * Small::TN * sizeof(float));
+  }
   return p;
 }
 
@@ -494,10 +651,25 @@ int launch_wa_gemm(const WaGemmParams& p, hipStream_t st) {
       using T = decltype(tile_c);
       a.tiles_m = static_cast<int32_t>((p.M + T::TM - 1) / T::TM);
       a.tiles_n = static_cast<int32_t>((p.N + T::TN - 1) / T::TN);
-      hipLaunchKernelGGL(kernel, dim3(static_cast<unsigned>(plan.blocks)), dim3(T::NW * 64), 0, st, a);
+      hipLaunchKernelGGL(kernel, dim3(static_cast<unsigned>(plan.blocks * (plan.run ? a.piece0[3] : 1))), dim3(T::NW * 64), 0, st, a);
     };
-    if (plan.tile == WaPlan::kLarge) tiled(Large{}, wa_gemm_kernel<Large, K1, K2, false>);
-    else tiled(Small{}, wa_gemm_kernel<Small, K1, K2, true>);
+    switch (plan.tile) {
+      case WaPlan::kLarge: tiled(Large{}, wa_gemm_kernel<Large, K1, K2, false, false>); break;
+      case WaPlan::kMedium: tiled(Medium{}, wa_gemm_kernel<Medium, K1, K2, false, false>); break;
+      case WaPlan::kWide: tiled(Small{}, wa_gemm_kernel<Small, K1, K2, false, true>); break;
+      default:
+        if (!plan.run) {
+          tiled(Small{}, wa_gemm_kernel<Small, K1, K2, false, false>);
+        } else {
+          for (int q = 0; q < 3; ++q) {
+            const int stages = q == 0 ? a.seg[SEG_REF].stages : a.seg[SEG_Q + 2 * (q - 1)].stages;
+            a.piece0[q + 1] = a.piece0[q] + (stages + plan.run - 1) / plan.run;
+          }
+          a.partial = static_cast<float*>(p.partial);
+          tiled(Small{}, wa_gemm_kernel<Small, K1, K2, true, false>);
+          hipLaunchKernelGGL((wa_pieces_kernel<Small, K1, K2>), dim3(static_cast<unsigned>(plan.blocks)), dim3(Small::NW * 64), 0, st, a);
+        }
+    }
     return hip_status(hipGetLastError());
   };
 #define MOFQ_WA(A, B) \

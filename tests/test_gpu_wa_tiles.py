@@ -1,15 +1,32 @@
-"""GPU parity of the layer-output products of tensors whose rows lie far apart."""
+"""GPU parity of the layer-output products in every tiling: which one a layer takes depends on its
+sizes alone, and each is compared with the oracle at its ragged edges and K remainders."""
 import numpy as np
 import pytest
 import torch
 
 import mofq_inputs as mi
 from oracle import mofq_oracle as orc
+from tests import test_gpu_w_only_output as wo
+from tests import test_gpu_wa as wa
 
 pytestmark = pytest.mark.gpu
 
 DEV = "cuda:0"
-I8, FP8 = orc.INT8, orc.FP8_E4M3
+I4, FP4, I8, FP8 = orc.INT4, orc.FP4_E2M1, orc.INT8, orc.FP8_E4M3
+
+# tokens, rows, columns: by the number of tiles and the stages of 64 columns (an odd number leaves the last stage of an
+# 8-bit product half full)
+SHAPES = {
+    "small tiles": (65, 63, 192),
+    "small tiles, the last number of stages that is not cut": (130, 190, 64 * 19),
+    "cut to 11 stages": (70, 90, 64 * 21),
+    "cut to 20 stages, one more than divides": (64, 65, 64 * 41),
+    "most pieces of a few tiles": (63, 64, 64 * 331),
+    "more than 48 tiles, cut to 40 stages": (449, 448, 64 * 41),
+    "more than 160 tiles, cut into the products": (833, 832, 64 * 21),
+    "medium tiles": (1601, 1345, 192),
+    "large tiles": (2049, 2049, 128),
+}
 
 
 @pytest.fixture(scope="module")
@@ -19,10 +36,59 @@ def mq():
     return binding
 
 
+def tensors(shape, seed):
+    M, N, K = shape
+    return mi.activations(M, K, seed=seed, device=DEV), mi.llama_like_weight(N, K, seed=seed + 1, dtype=torch.bfloat16, device=DEV)
+
+
+@pytest.mark.parametrize("name", list(SHAPES))
+def test_exact_products(mq, name):
+    x, w = tensors(SHAPES[name], 8100)
+    wa.check_layer(mq, x, w, [I8, FP8], orc.PER_TENSOR, name)          # the fused path
+    wa.check_layer(mq, x, w, [FP8, I8], orc.PER_CHANNEL, name)         # the general one; a product alone
+
+
+@pytest.mark.parametrize("name", list(SHAPES))
+def test_weight_only_products(mq, name):
+    x, w = tensors(SHAPES[name], 8200)
+    wo.check_layer(mq, x, w, [I4, FP4], orc.PER_CHANNEL, mi.clip_ratios(1), name)
+
+
+@pytest.mark.parametrize("name", list(SHAPES))
+def test_fp8_unit_products(mq, name):
+    M, N, K = SHAPES[name]
+    x, w = tensors(SHAPES[name], 8300)
+    cfg = mq.Cfg(mq.PER_TENSOR, mi.clip_ratios(1))
+    out, res = mq.alloc_qbuffers(N, K, 8, cfg, DEV), mq.alloc_result(DEV)
+    ws = torch.empty(mq.workspace_bytes(w, x, 2, mq.ERR_LAYER_OUTPUT_FP8_UNIT, cfg), dtype=torch.uint8, device=DEV)
+    print(f"[case] {name} {SHAPES[name]}", flush=True)
+    mq.select_layer(w, x, [I8, FP8], mq.ERR_LAYER_OUTPUT_FP8_UNIT, cfg, out, None, res, ws)
+    torch.cuda.synchronize()
+    r = mq.read_result(res)
+    ref = orc.select_layer_wa(mi.to_f32_numpy(x), mi.to_f32_numpy(w), [I8, FP8], orc.PER_TENSOR)
+    assert np.isclose(r.err[0], ref.errs[0], rtol=wa.E_RTOL) and np.isclose(r.ref_energy, ref.ref_energy, rtol=wa.E_RTOL)
+    # what the unit's alignment drops: see test_gpu_random_layers.py
+    assert abs(r.err[1] / ref.errs[1] - 1.0) <= wa.FP8_UNIT_RTOL + (1e-3 / np.sqrt(M * N) if M * N < 20000 else 0.0)
+
+
+@pytest.mark.parametrize("name", ["cut to 20 stages, one more than divides", "small tiles"])
+def test_unused_scratch_is_not_read(mq, name):
+    """The pieces' partial sums are written before they are read: scratch full of NaN changes nothing."""
+    x, w = tensors(SHAPES[name], 8400)
+    cfg = mq.Cfg(mq.PER_TENSOR, mi.clip_ratios(1))
+    out, res = mq.alloc_qbuffers(w.shape[0], w.shape[1], 8, cfg, DEV), mq.alloc_result(DEV, 2)
+    n = mq.workspace_bytes(w, x, 2, mq.ERR_LAYER_OUTPUT, cfg)
+    for i, fill in enumerate((0, 0xFF)):
+        ws = torch.full((n,), fill, dtype=torch.uint8, device=DEV)
+        mq.select_layer(w, x, [I8, FP8], mq.ERR_LAYER_OUTPUT, cfg, out, None, res[i], ws)
+    torch.cuda.synchronize()
+    assert torch.equal(res[0], res[1])
+
+
 @pytest.mark.parametrize("rows,ld", [(130, 36 << 20), (300, 9 << 20), (300, 18 << 20)])
 def test_rows_far_apart(mq, rows, ld):
-    """Row strides at which a tile's rows reach beyond 2^32 bytes: of 64 rows
-    and of 256 (64-bit offsets)."""
+    """Row strides at which a tile's rows reach beyond 2^32 bytes: of 64 rows (64-bit offsets), of 256 and of 128
+    (smaller tiles)."""
     K = 128
     if torch.cuda.mem_get_info()[0] < rows * ld * 2 + (1 << 30):
         pytest.skip("needs the memory of the gaps between the rows")
