@@ -4,7 +4,7 @@
 // the error of a candidate follows from the number and the sum of magnitudes of the elements below each of its
 // 7 level boundaries (INT4: 8), and the decision is monotone in the magnitude's bit pattern.  Scoring a group
 // of 128 directly (sweep_group_kernel) costs 9.6 vector instructions per element and candidate for the format
-// pair, 960 wave instructions per group with 50 ratios plus a second pass in fp64; a look-up costs 18,
+// pair, 960 wave instructions per group with 50 ratios plus a second pass in fp64; a look-up costs 16,
 // whatever the group's size.
 //
 // One wave takes 64 / LPG groups, LPG = GROUP / 8 lanes each, and shares nothing with other waves:
@@ -20,9 +20,11 @@
 //      leaves (the difference of sums keeps two digits fewer).  Where a second candidate is too close, or a scale is
 //      out of range (non-finite or nearly exact groups), all candidates of the group are scored that way, in fp64.
 //
-// Bound by vector issue: 1878 instructions per wave of four groups of 128 with 50 ratios (130 of them the winners' own
-// sums; the direct kernel: 4360), 4 waves of 10 KB LDS per SIMD.  Measured, layer selection of the seven linears of a
-// 7B block, fp16 groups of 128, 50 ratios: 3003 us -> 1434 us.
+// Bound by vector issue and latency together: 1615 instructions per wave of four groups of 128 with 50 ratios take 84 % of
+// the clocks (130 of them the winners' own sums; the direct kernel: 4360); 11 KB of LDS leave 3.5 waves per SIMD, so
+// registers are spent on look-ups in flight (with a scheduler that kept to 63 registers for 8 waves per SIMD the same
+// instructions took 1425 us instead of 1230).  Measured, layer selection of the seven linears of a
+// 7B block, fp16 groups of 128, 50 ratios: 3003 us -> 1434 us -> 1230 us.
 #include <algorithm>
 #include <cmath>
 
@@ -55,7 +57,17 @@ template <int FMT> struct Levels {
   }
   static constexpr float over(int b) { return static_cast<float>(thr(b) * (1.0 + 0x1p-21)); }
   static constexpr uint32_t step2(int b) { return static_cast<uint32_t>(2.0f * (mag(b + 1) - mag(b))); }   // an integer
-  static constexpr int dg2q(int b) { return static_cast<int>(4.0f * (mag(b) * mag(b) - mag(b + 1) * mag(b + 1))); }
+  static constexpr uint32_t dg2q(int b) { return static_cast<uint32_t>(4.0f * (mag(b + 1) * mag(b + 1) - mag(b) * mag(b))); }
+  static constexpr float kBelow = 1.0f / (over(6) * (1.0f + 0x1p-20f));    // a scale of amax times this: boundary 6 is below amax
+  static constexpr float kAbove = (1.0f + 0x1p-20f) / over(0);             // of v times this: boundary 0 is not below v
+  // a lane's own boundary, the same numbers: byte tables of 4 (m_q + m_{q+1}) / 2 and of the weights (E2M1 has no
+  // eighth boundary: no weight)
+  MOFQ_DEV static float thr_of(uint32_t q) {
+    const float mid = FMT == MOFQ_INT4 ? static_cast<float>(q) + 0.5f : 0.25f * static_cast<float>(static_cast<uint32_t>(0x14140E0A07050301ull >> (8 * q)) & 0xFFu);
+    return u2f(f2u(mid) - (q & 1u));
+  }
+  MOFQ_DEV static uint32_t step2_of(uint32_t q) { return FMT == MOFQ_INT4 ? 2u : static_cast<uint32_t>(0x0004020201010101ull >> (8 * q)) & 0xFFu; }
+  MOFQ_DEV static uint32_t dg2q_of(uint32_t q) { return FMT == MOFQ_INT4 ? 8 * q + 4 : static_cast<uint32_t>(0x00501C1407050301ull >> (8 * q)) & 0xFFu; }
 };
 
 // count << B | sum
@@ -116,6 +128,19 @@ template <int LPG, typename T, typename Op> MOFQ_DEV T group_reduce(T v, Op op) 
   if constexpr (LPG >= 32) v = op(v, __shfl_xor(v, 16, 64));
   return v;
 }
+// sum over N adjacent lanes (2, 4 or 8)
+template <int N, typename T> MOFQ_DEV T lanes_sum(T v) {
+  auto from = [](T x, auto ctrl_c) {
+    constexpr int CTRL = decltype(ctrl_c)::value;
+    auto half = [](uint32_t h) { return static_cast<uint32_t>(dpp_i32<CTRL>(static_cast<int>(h))); };
+    if constexpr (sizeof(T) == 8) return (static_cast<T>(half(static_cast<uint32_t>(x >> 32))) << 32) | half(static_cast<uint32_t>(x));
+    else return half(x);
+  };
+  v += from(v, std::integral_constant<int, DPP_QUAD_XOR1>{});
+  if constexpr (N >= 4) v += from(v, std::integral_constant<int, DPP_QUAD_XOR2>{});
+  if constexpr (N >= 8) v += from(v, std::integral_constant<int, DPP_ROW_HALF_MIRROR>{});
+  return v;
+}
 // x of the lane that control CTRL names, 0 where there is none or ROW_MASK leaves the row out
 template <int CTRL, int ROW_MASK, typename T> MOFQ_DEV T dpp_or_zero(T x) {
   auto half = [](uint32_t v) { return static_cast<uint32_t>(__builtin_amdgcn_update_dpp(0, static_cast<int>(v), CTRL, ROW_MASK, 0xf, false)); };
@@ -137,21 +162,24 @@ template <int LPG, typename T> MOFQ_DEV T group_excl(T v, int l) {
   return inc - v;
 }
 
-// Bytes of a group: bit words and ranks, then the words of the distinct patterns: one array with both
-// halves (narrow with INT4), or an array each.  Pieces of 16 bytes.
+// LDS of a wave: bit words and ranks of each group, then of each group the words of the distinct patterns: one array with
+// both halves (narrow with INT4), or an array each.  The lanes of a group look at neighbouring candidates and read
+// neighbouring places, about the same ones in every group, so the groups' arrays begin in different banks: the tables
+// 256 / GPW bytes apart modulo 256 (an odd number of entries per lane), and so the words.
 template <int GROUP, bool WIDE, bool TAIL> struct GroupLayout {
-  static constexpr int LPG = GROUP / 8;
+  static constexpr int LPG = GROUP / 8, GPW = 64 / LPG;
   static constexpr bool JOINED = TAIL && !WIDE;
   using store = std::conditional_t<WIDE || JOINED, uint64_t, uint32_t>;
   static constexpr int STRIDE = sizeof(store);
-  static constexpr int CELLS = STRIDE * (GROUP + 16 / STRIDE);   // GROUP + 1 of them are used
+  static constexpr int SHIFT = 256 / GPW;
+  static constexpr int CELLS = (STRIDE * (GROUP + 1) - SHIFT + 255) / 256 * 256 + SHIFT;   // GROUP + 1 of them are used
   static constexpr int entries(int nbin) { return ((nbin / 32 + 1 + LPG - 1) / LPG) | 1; }   // per lane; odd: lanes' pieces in different banks
-  static constexpr int table(int nbin) { return (entries(nbin) * LPG * 8 + 15) / 16 * 16; }
-  static constexpr int bytes(int nbin) { return table(nbin) + CELLS * (TAIL && !JOINED ? 2 : 1); }
+  static constexpr int table(int nbin) { return entries(nbin) * LPG * 8; }
+  static constexpr int bytes(int nbin) { return GPW * (table(nbin) + CELLS * (TAIL && !JOINED ? 2 : 1)); }   // pieces of 16
 };
 
 template <typename In, int FA, int FB, int GROUP, bool WIDE>
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4))) void sweep_group_bits_kernel(const GroupArgs a) {
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4, 4))) void sweep_group_bits_kernel(const GroupArgs a) {
   constexpr int NF = (FB >= 0) ? 2 : 1;
   constexpr int FBX = (FB >= 0) ? FB : FA;
   constexpr int LPG = GROUP / 8, GPW = 64 / LPG;
@@ -167,11 +195,10 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4))) void sw
   const int K = a.n_clip, nbin = a.nbin;
   const int lane = threadIdx.x, l = lane % LPG, g = lane / LPG;
   const int epl = Lay::entries(nbin);
-  unsigned char* const mine = s_dyn + g * Lay::bytes(nbin);
-  u32x2* const tbl = reinterpret_cast<u32x2*>(mine);           // bits, distinct patterns before them
+  u32x2* const tbl = reinterpret_cast<u32x2*>(s_dyn + g * Lay::table(nbin));           // bits, distinct patterns before them
   using store = typename Lay::store;
-  store* const P = reinterpret_cast<store*>(mine + Lay::table(nbin));
-  store* const PN = P + Lay::CELLS / Lay::STRIDE;   // not where they are joined
+  store* const P = reinterpret_cast<store*>(s_dyn + GPW * Lay::table(nbin) + g * Lay::CELLS);
+  store* const PN = P + GPW * Lay::CELLS / Lay::STRIDE;   // not where they are joined
 
   const int64_t gpr = a.cols / GROUP;   // groups per row
   int64_t unit = static_cast<int64_t>(blockIdx.x) * GPW + g;
@@ -190,7 +217,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4))) void sw
   for (int k = lane; k < K; k += 64) s_clip[k] = a.clip[k];
   {
     const u32x4 zero = {0u, 0u, 0u, 0u};
-    for (int i = l; i < Lay::bytes(nbin) / 16; i += LPG) reinterpret_cast<u32x4*>(mine)[i] = zero;
+    for (int i = lane; i < Lay::bytes(nbin) / 16; i += 64) reinterpret_cast<u32x4*>(s_dyn)[i] = zero;
   }
   float x[8], amax = 0.0f;
   raw.widen(x);
@@ -209,13 +236,21 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4))) void sw
 
   // ---- 1. bits ----------------------------------------------------------------------------------------
   wave_fence();
-  int at[8];
+  const uint32_t tbl_at = lds_address(tbl), p_at = lds_address(P), pn_at = Lay::JOINED ? p_at + 4 : lds_address(PN);
+  auto entry_at = [&](uint32_t n) {   // of pattern number n
+    uint32_t e = n >> 5;
+    asm("" : "+v"(e));   // a shift-and-add
+    return (e << 3) + tbl_at;
+  };
+  // (no branches around the LDS operations of the elements below the counted patterns: these set and add nothing)
+  uint32_t at[8];
+  bool counted[8];
 #pragma unroll
   for (int i = 0; i < 8; ++i) {
     const int h = static_cast<int>((i % 2 == 0 ? raw.w[i / 2] : raw.w[i / 2] >> 16) & 0x7FFFu);
-    at[i] = min(h - lo, nbin - 1);   // (a non-finite element: the group's error is non-finite anyway)
-    if (at[i] >= 0)
-      __hip_atomic_fetch_or(reinterpret_cast<uint32_t*>(tbl + (at[i] >> 5)), 1u << (at[i] & 31), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    at[i] = static_cast<uint32_t>(max(min(h - lo, nbin - 1), 0));   // (a non-finite element: the group's error is non-finite anyway)
+    counted[i] = h >= lo;
+    __hip_atomic_fetch_or((lds_u32*)static_cast<uintptr_t>(entry_at(at[i])), (counted[i] ? 1u : 0u) << (at[i] & 31u), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
   }
   wave_fence();
   {
@@ -229,12 +264,10 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4))) void sw
     }
   }
   wave_fence();
-  // distinct patterns among the first n
-  const uint32_t tbl_at = lds_address(tbl), p_at = lds_address(P), pn_at = Lay::JOINED ? p_at + 4 : lds_address(PN);
+  // distinct patterns among the first n 
   auto rank = [&](uint32_t n) {
-    uint32_t e = n >> 5, r;
-    asm("" : "+v"(e));   // a shift-and-add
-    const u32x2 t = *(lds_u32x2*)static_cast<uintptr_t>((e << 3) + tbl_at);
+    uint32_t r;
+    const u32x2 t = *(lds_u32x2*)static_cast<uintptr_t>(entry_at(n));
     asm("v_bcnt_u32_b32 %0, %1, %2" : "=v"(r) : "v"(__builtin_amdgcn_ubfe(t[0], 0u, n)), "v"(t[1]));   // (the width's low 5 bits count)
     return r;
   };
@@ -243,19 +276,20 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4))) void sw
   // ---- 2. count and sum per distinct pattern, prefixes -----------------------------------------------
   constexpr int kUlp = std::is_same<In, F16>::value ? 25 : 134;   // exponent field of the pattern whose ulp is 1
   const int e_lo = exponent_of<In>(lo);
+  uint32_t d[8];
 #pragma unroll
-  for (int i = 0; i < 8; ++i)
-    if (at[i] >= 0) {
-      const uint32_t d = rank(static_cast<uint32_t>(at[i]));
-      const word one = (static_cast<word>(1) << C::B) + static_cast<word>(static_cast<uint32_t>(__builtin_ldexpf(__builtin_fabsf(x[i]), kUlp - e_lo)));
-      const store neg = (f2u(x[i]) >> 31) != 0 ? static_cast<store>(one) : 0;
-      if constexpr (Lay::JOINED) {
-        __hip_atomic_fetch_add(P + d, one | (neg << 32), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-      } else {
-        __hip_atomic_fetch_add(P + d, one, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-        if constexpr (TAIL) __hip_atomic_fetch_add(PN + d, neg, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-      }
+  for (int i = 0; i < 8; ++i) d[i] = rank(at[i]);
+#pragma unroll
+  for (int i = 0; i < 8; ++i) {
+    const word one = counted[i] ? (static_cast<word>(1) << C::B) + static_cast<word>(static_cast<uint32_t>(__builtin_ldexpf(__builtin_fabsf(x[i]), kUlp - e_lo))) : 0;
+    const store neg = (f2u(x[i]) >> 31) != 0 ? static_cast<store>(one) : 0;
+    if constexpr (Lay::JOINED) {
+      __hip_atomic_fetch_add(P + d[i], one | (neg << 32), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    } else {
+      __hip_atomic_fetch_add(P + d[i], one, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+      if constexpr (TAIL) __hip_atomic_fetch_add(PN + d[i], neg, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
     }
+  }
   wave_fence();
   auto prefix = [&](store* cells) {   // (no carry from one half to the other)
     store v[8], sum = 0;
@@ -278,70 +312,118 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4))) void sw
   const word total = cell(p_at, GROUP);
   const word n_total = TAIL ? cell(pn_at, GROUP) : 0;
   const float v_lo = bits_to_float<In>(static_cast<uint32_t>(lo));
-  const double minus_2ulp = -2.0 * static_cast<double>(bits_to_float<In>(static_cast<uint32_t>(lo) + 1) - v_lo);   // ulps at lo
+  const double four_ulp = 4.0 * static_cast<double>(bits_to_float<In>(static_cast<uint32_t>(lo) + 1) - v_lo);   // ulps at lo
+  const double en4 = 4.0 * en;
 
   // ---- 3. candidates -----------------------------------------------------------------------------
   double best[NF], second[NF];
   int bk[NF];
-  bool bad = false;   // the group has to be scored exactly
+  bool bad = !(amax <= 0x1p127f);   // the group has to be scored exactly (here: scales may leave the reciprocal's range)
 #pragma unroll
   for (int f = 0; f < NF; ++f) {
     best[f] = second[f] = __builtin_inf();
     bk[f] = MOFQ_MAX_CLIP;
   }
-  auto candidate = [&](auto fmt_c, int k, int f) {
-    constexpr int FMT = decltype(fmt_c)::value;
+  int before_lo = -lo;
+  asm("" : "+v"(before_lo));   // opaque: pattern, this and the carry of the decision are one addition
+  const float v_max = bits_to_float<In>(static_cast<uint32_t>(hmax));
+  // The candidates kbase + l / PER, PER adjacent lanes to each, which share its boundaries; ALL: there is one for every lane.
+  auto candidate = [&](auto fmt_c, auto per_c, auto all_c, int kbase, int f) {
+    constexpr int FMT = decltype(fmt_c)::value, PER = decltype(per_c)::value;
     using Lv = Levels<FMT>;
-    const float s = search_scale<FMT>(s_clip[k < K ? k : K - 1] * amax, f16);
+    const int k = kbase + l / PER;
+    const bool in = decltype(all_c)::value || k < K;
+    const float s0 = search_scale<FMT>(s_clip[in ? k : K - 1] * amax, f16);
+    // No boundary but the eighth beyond the counted patterns: a scale that rounding to fp16 moved so far sends the group
+    // to the exact pass.  (The patterns span more than the boundaries do, so the lower limit is the smaller one.)
+    const float s = med3(s0, v_lo * Lv::kAbove, v_max * Lv::kBelow);
+    bad |= s != s0;
     const float inv = reciprocal(s);
-    uint32_t r[Lv::N];
     // The largest pattern at or below the boundary (threshold t s): the pattern of t s (1 + 2^-21) rounded toward
     // zero or the one before it, as the exact decision on the first tells; patterns above are beyond t s (1 + 2^-22), those
     // below short of t s (1 - 2^-22), whatever the rounding of 1 / s and of the product.
+    auto distinct = [&](float over, float thr, bool last) {
+      const uint32_t e = pattern_rtz<In>(over * s);
+      const bool at_most = scaled<In>(e, inv) <= thr;
+      uint32_t n = e + static_cast<uint32_t>(before_lo) + (at_most ? 1u : 0u);
+      if (last) n = min(n, static_cast<uint32_t>(nbin));
+      return rank(n);
+    };
+    // Sums in half levels and 4 times the sum of squares, less those of all elements on level 7 (INT4: all its
+    // negative ones on -8, one level further): what is missing below the boundaries.
+    word A = -static_cast<word>(2.0f * Lv::mag(7)) * C::sum(total);
+    uint32_t b4 = -static_cast<uint32_t>(4.0f * Lv::mag(7) * Lv::mag(7)) * static_cast<uint32_t>(C::count(total));
+    if constexpr (FMT == MOFQ_INT4) {
+      A -= 2 * C::sum(n_total);
+      b4 -= 60u * static_cast<uint32_t>(C::count(n_total));
+    }
+    if constexpr (PER > 1)   // once
+      if (l % PER != 0) { A = 0; b4 = 0; }
+    auto add = [&](word p, uint32_t step2, uint32_t dg2q) {
+      if constexpr (WIDE) {
+        A += C::sum(p) * step2;
+        b4 += __umul24(static_cast<uint32_t>(C::count(p)), dg2q);
+      } else {
+        A += __umul24(p, step2);   // the low 24 bits
+        b4 = __builtin_amdgcn_udot4(p, dg2q << 24, b4, false);
+      }
+    };
+    if constexpr (PER == 1) {
+      uint32_t r[Lv::N];
 #pragma unroll
-    for (int q = 0; q < Lv::N; ++q) {
-      const uint32_t e = pattern_rtz<In>(Lv::over(q) * s);
-      const bool at_most = scaled<In>(e, inv) <= Lv::thr(q);
-      const int n = static_cast<int>(e) - lo + (at_most ? 1 : 0);
-      if (q == 0) bad |= k < K && (n < 0 || !(s <= 0x1p125f));   // the smallest threshold: uncounted elements might lie above it
-      r[q] = rank(min(static_cast<uint32_t>(n), static_cast<uint32_t>(nbin)));
-    }
-    // sums in half levels, and 4 times the sum of squares
-    word A = 0;
-    int b4 = static_cast<int>(4.0f * Lv::mag(7) * Lv::mag(7)) * C::count(total);
+      for (int q = 0; q < Lv::N; ++q) r[q] = distinct(Lv::over(q), Lv::thr(q), q == 7);
 #pragma unroll
-    for (int q = 0; q < 7; ++q) {
-      const word p = cell(p_at, r[q]);
-      if constexpr (WIDE) A += C::sum(p) * Lv::step2(q);
-      else asm("v_mad_u32_u24 %0, %1, %2, %0" : "+v"(A) : "v"(p), "n"(Lv::step2(q)));   // the low 24 bits
-      b4 = __mul24(C::count(p), Lv::dg2q(q)) + b4;
+      for (int q = 0; q < Lv::N; ++q) {
+        const word p = cell(q == 7 ? pn_at : p_at, r[q]);
+        if constexpr (WIDE) add(p, Lv::step2(q), Lv::dg2q(q));
+        else {
+          asm("v_mad_u32_u24 %0, %1, %2, %0" : "+v"(A) : "v"(p), "n"(Lv::step2(q)));   // the low 24 bits
+          b4 = __builtin_amdgcn_udot4(p, Lv::dg2q(q) << 24, b4, false);
+        }
+      }
+    } else {
+#pragma unroll
+      for (int i = 0; i < 8 / PER; ++i) {
+        const uint32_t q = static_cast<uint32_t>(l % PER + i * PER);
+        const float thr = Lv::thr_of(q);
+        const uint32_t r = distinct(thr * (1.0f + 0x1p-21f), thr, FMT == MOFQ_INT4 && i == 8 / PER - 1);
+        const word p = cell(FMT == MOFQ_INT4 && i == 8 / PER - 1 && q == 7 ? pn_at : p_at, r);
+        add(p, Lv::step2_of(q), Lv::dg2q_of(q));
+      }
+      A = lanes_sum<PER>(A);
+      b4 = lanes_sum<PER>(b4);
     }
-    A = static_cast<word>(2.0f * Lv::mag(7)) * C::sum(total) - A;
-    if constexpr (FMT == MOFQ_INT4) {   // negative elements beyond the last boundary sit on -8
-      const word t = n_total - cell(pn_at, r[7]);
-      A += 2 * C::sum(t);
-      b4 = __mul24(C::count(t), 4 * (64 - 49)) + b4;
-    }
-    const double h = 0.5 * static_cast<double>(s);   // (exact: half of the smallest scales is subnormal in fp32)
-    const double v = __builtin_fma(h, __builtin_fma(h, static_cast<double>(b4), static_cast<double>(A) * minus_2ulp), en);
-    if (k < K) {
-      const bool better = v < best[f];
-      const double worse = better ? best[f] : v;
-      second[f] = worse < second[f] ? worse : second[f];
-      bk[f] = better ? k : bk[f];
-      best[f] = better ? v : best[f];
+    // 4 (error): exact scaling
+    const double sd = static_cast<double>(s);
+    const double Ad = static_cast<double>(static_cast<std::make_signed_t<word>>(A)), bd = static_cast<double>(static_cast<int>(b4));
+    const double v = __builtin_fma(sd, __builtin_fma(-sd, bd, Ad * four_ulp), en4);
+    if (in) {
+      bk[f] = v < best[f] ? k : bk[f];
+      second[f] = __builtin_fmin(second[f], __builtin_fmax(v, best[f]));
+      best[f] = __builtin_fmin(best[f], v);
     }
   };
-  for (int k0 = 0; k0 < K; k0 += LPG) {
-    candidate(std::integral_constant<int, FA>{}, k0 + l, 0);
-    if constexpr (NF == 2) candidate(std::integral_constant<int, FBX>{}, k0 + l, NF - 1);
+  auto round = [&](auto per_c, auto all_c, int kbase) {
+    candidate(std::integral_constant<int, FA>{}, per_c, all_c, kbase, 0);
+    if constexpr (NF == 2) candidate(std::integral_constant<int, FBX>{}, per_c, all_c, kbase, NF - 1);
+  };
+  int k0 = 0;
+  for (; k0 + LPG <= K; k0 += LPG) round(std::integral_constant<int, 1>{}, std::true_type{}, k0);
+  // The rest of them: several lanes to a candidate where there are enough (50 ratios, groups of 128: the last two take
+  // 143 instructions instead of a round's 242).
+  const int rest = K - k0;   // uniform
+  if (rest > 0) {
+    if (rest * 8 <= LPG) round(std::integral_constant<int, 8>{}, std::false_type{}, k0);
+    else if (rest * 4 <= LPG) round(std::integral_constant<int, 4>{}, std::false_type{}, k0);
+    else if (rest * 2 <= LPG) round(std::integral_constant<int, 2>{}, std::false_type{}, k0);
+    else round(std::integral_constant<int, 1>{}, std::false_type{}, k0);
   }
 
   // ---- 4. winners.  Count and sum are exact and the error takes two roundings (filter_bounds): a candidate that
   // is the smallest by more than the margin is the winner, and its own error is then summed element by element, for
   // en - 2 s A + s^2 B keeps two digits fewer than that sum. -------------------------------------------------
   const bool exact = group_reduce<LPG>(bad ? 1 : 0, [](int p, int q) { return p | q; }) != 0;
-  const double margin = filter_bounds<GROUP, true, 4>(en, 0.0, 0.0, 0.0, 0.0).margin;
+  const double margin = 4.0 * filter_bounds<GROUP, true, 4>(en, 0.0, 0.0, 0.0, 0.0).margin;
   int win[NF];
   bool sure[NF];
 #pragma unroll
@@ -409,10 +491,10 @@ int launch_size(const GroupArgs& a, hipStream_t st) {
   if (bits > 32) return MOFQ_ERR_UNSUPPORTED;
   const dim3 grid(static_cast<unsigned>((a.units + GPW - 1) / GPW));
   if (GROUP <= 128 && bits < 24 && ((GROUP - 1) >> (24 - bits)) == 0) {
-    const size_t lds = GPW * static_cast<size_t>(GroupLayout<GROUP, false, TAIL>::bytes(a.nbin));
+    const size_t lds = static_cast<size_t>(GroupLayout<GROUP, false, TAIL>::bytes(a.nbin));
     hipLaunchKernelGGL((sweep_group_bits_kernel<In, FA, FB, GROUP, false>), grid, dim3(64), lds, st, a);
   } else {
-    const size_t lds = GPW * static_cast<size_t>(GroupLayout<GROUP, true, TAIL>::bytes(a.nbin));
+    const size_t lds = static_cast<size_t>(GroupLayout<GROUP, true, TAIL>::bytes(a.nbin));
     hipLaunchKernelGGL((sweep_group_bits_kernel<In, FA, FB, GROUP, true>), grid, dim3(64), lds, st, a);
   }
   return hip_status(hipGetLastError());

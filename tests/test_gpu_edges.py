@@ -114,6 +114,20 @@ def test_group_pattern_ranks(mq, dtype, group, n_clip, lo_clip, f16, pad):  # no
         check_tensor(mq, w, cands, orc.PER_GROUP, ratios, group, f16, label="group-rank-edge")
 
 
+# the candidates of a last round that does not fill the group's lanes: eight, four, two and one lane to each; with scales
+# in fp16 of groups so small that their rounding moves the scale off the counted patterns
+@pytest.mark.parametrize("dtype", [torch.float16, torch.bfloat16])
+@pytest.mark.parametrize("group,n_clip", [(64, 81), (64, 82), (64, 84), (64, 86), (128, 33), (128, 36), (128, 40), (128, 47), (256, 68), (256, 72),
+                                          (256, 80), (256, 91)])
+def test_group_last_round(mq, dtype, group, n_clip):  # noqa: F811
+    w = _strided(6, 5 * group, 0, n_clip, dtype)
+    w[1, :2 * group] = (w[1, :2 * group].float() * 2.0 ** -15).to(dtype)
+    w[2, group:] = (w[2, group:].float() * 2.0 ** -17).to(dtype)
+    ratios = [0.45 + 0.55 * (i + 1) / n_clip for i in range(n_clip)]
+    for cands in (PAIR4, [orc.INT4], [orc.FP4_E2M1]):
+        check_tensor(mq, w, cands, orc.PER_GROUP, ratios, group, True, label="group-last-round")
+
+
 # ratios so small that a group's largest elements are 2^31 ulps of the first counted pattern and more: the last tables
 # of the rank kernel and, beyond them, the direct kernel (bf16: 128 patterns per binade)
 @pytest.mark.parametrize("lo_clip", [1e-5, 4e-6, 2e-6, 1e-6, 1e-7])
