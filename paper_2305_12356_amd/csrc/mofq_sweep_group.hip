@@ -15,16 +15,18 @@
 //      elements, and of its negative elements for INT4's extra level; prefix sums of both.  Count and
 //      sum share a word of 32 bits where they fit (those of the negative elements in the upper half of 64), else 64;
 //   3. a lane per candidate: the largest pattern below each boundary (an fp32 estimate and one exact decision), its
-//      rank among the distinct patterns (a population count), count and sum up to it: two LDS reads;
+//      rank among the distinct patterns (a population count), count and sum up to it: two LDS reads; long tables that
+//      descend are searched coarsely first, then the gaps that can hold the winner;
 //   4. the smallest error and, for the winner alone, the sum of its residuals element by element: that sum is what
 //      leaves (the difference of sums keeps two digits fewer).  Where a second candidate is too close, or a scale is
 //      out of range (non-finite or nearly exact groups), all candidates of the group are scored that way, in fp64.
 //
-// Bound by vector issue and latency together: 1615 instructions per wave of four groups of 128 with 50 ratios take 84 % of
+// Bound by vector issue and latency together: 1375 instructions per wave of four groups of 128 with 50 ratios take 77 % of
 // the clocks (130 of them the winners' own sums; the direct kernel: 4360); 11 KB of LDS leave 3.5 waves per SIMD, so
 // registers are spent on look-ups in flight (with a scheduler that kept to 63 registers for 8 waves per SIMD the same
 // instructions took 1425 us instead of 1230).  Measured, layer selection of the seven linears of a
-// 7B block, fp16 groups of 128, 50 ratios: 3003 us -> 1434 us -> 1230 us.
+// 7B block, fp16 groups of 128, 50 ratios: 3003 us (direct) -> 1434 -> 1230 (every candidate looked up) -> 1143 us (the gaps
+// searched).  A wave that walks several tiles with the next one's elements requested ahead: 1413 (its share is fixed).
 #include <algorithm>
 #include <cmath>
 
@@ -39,6 +41,7 @@ struct GroupArgs {
   int64_t cols, ld, units;
   int32_t scale_f16, n_clip;
   int32_t nbin;                // patterns with a bit, a multiple of 32
+  int32_t descending;          // the ratios: none larger than the one before
   UnitRecords rec;
   float clip[MOFQ_MAX_CLIP];
 };
@@ -128,6 +131,8 @@ template <int LPG, typename T, typename Op> MOFQ_DEV T group_reduce(T v, Op op) 
   if constexpr (LPG >= 32) v = op(v, __shfl_xor(v, 16, 64));
   return v;
 }
+// of the next lane (0 behind the last)
+MOFQ_DEV float next_lane(float x) { return u2f(static_cast<uint32_t>(__builtin_amdgcn_update_dpp(0, static_cast<int>(f2u(x)), 0x130, 0xf, 0xf, false))); }   // wave_shl:1
 // sum over N adjacent lanes (2, 4 or 8)
 template <int N, typename T> MOFQ_DEV T lanes_sum(T v) {
   auto from = [](T x, auto ctrl_c) {
@@ -176,10 +181,20 @@ template <int GROUP, bool WIDE, bool TAIL> struct GroupLayout {
   static constexpr int entries(int nbin) { return ((nbin / 32 + 1 + LPG - 1) / LPG) | 1; }   // per lane; odd: lanes' pieces in different banks
   static constexpr int table(int nbin) { return entries(nbin) * LPG * 8; }
   static constexpr int bytes(int nbin) { return GPW * (table(nbin) + CELLS * (TAIL && !JOINED ? 2 : 1)); }   // pieces of 16
+  // behind them: the clip ratios, and per format and group the candidates to look at in the gaps
+  static constexpr bool gaps(int K) { return K > 2 * LPG; }
+  static constexpr int lists(int K, int nf) { return gaps(K) ? nf * GPW * (K - LPG) : 0; }
+  static constexpr int all_bytes(int nbin, int K, int nf) { return bytes(nbin) + 4 * K + lists(K, nf); }
 };
 
+// Waves per SIMD that the registers are shared out for.  LDS leaves 3.5 (fp16, groups of 128, 50 ratios): what registers
+// are free then hold look-ups in flight.  bf16 has an eighth of the bits and room for more waves: 4096 x 4096, groups
+// of 128, 50 ratios 95.6 us with 4, 92.0 with 5, 89.8 with 6, 91.4 with 8 (before the gaps were searched, with 8: 107.8);
+// with 64-bit words 4: groups of 256 111 us, with 6 115.
+template <typename In, bool WIDE> constexpr int kWaves = std::is_same<In, BF16>::value && !WIDE ? 6 : 4;
+
 template <typename In, int FA, int FB, int GROUP, bool WIDE>
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4, 4))) void sweep_group_bits_kernel(const GroupArgs a) {
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(kWaves<In, WIDE>, kWaves<In, WIDE>))) void sweep_group_bits_kernel(const GroupArgs a) {
   constexpr int NF = (FB >= 0) ? 2 : 1;
   constexpr int FBX = (FB >= 0) ? FB : FA;
   constexpr int LPG = GROUP / 8, GPW = 64 / LPG;
@@ -191,7 +206,6 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4, 4))) void
   typedef __attribute__((address_space(3))) word lds_word;
 
   extern __shared__ __attribute__((aligned(16))) unsigned char s_dyn[];
-  __shared__ float s_clip[MOFQ_MAX_CLIP];
   const int K = a.n_clip, nbin = a.nbin;
   const int lane = threadIdx.x, l = lane % LPG, g = lane / LPG;
   const int epl = Lay::entries(nbin);
@@ -199,6 +213,8 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4, 4))) void
   using store = typename Lay::store;
   store* const P = reinterpret_cast<store*>(s_dyn + GPW * Lay::table(nbin) + g * Lay::CELLS);
   store* const PN = P + GPW * Lay::CELLS / Lay::STRIDE;   // not where they are joined
+  float* const s_clip = reinterpret_cast<float*>(s_dyn + Lay::bytes(nbin));
+  uint8_t* const list = reinterpret_cast<uint8_t*>(s_clip + K) + g * (K - LPG);   // of format 0; format 1: GPW (K - LPG) further
 
   const int64_t gpr = a.cols / GROUP;   // groups per row
   int64_t unit = static_cast<int64_t>(blockIdx.x) * GPW + g;
@@ -224,7 +240,8 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4, 4))) void
   double en = 0.0;
 #pragma unroll
   for (int i = 0; i < 8; ++i) {
-    amax = __builtin_fmaxf(amax, __builtin_fabsf(x[i]));
+    x[i] = __builtin_fabsf(x[i]);
+    amax = __builtin_fmaxf(amax, x[i]);
     const double xd = static_cast<double>(x[i]);
     en = __builtin_fma(xd, xd, en);
   }
@@ -243,14 +260,22 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4, 4))) void
     return (e << 3) + tbl_at;
   };
   // (no branches around the LDS operations of the elements below the counted patterns: these set and add nothing)
-  uint32_t at[8];
-  bool counted[8];
+  // Pattern numbers of two elements at once, 0 .. nbin - 1 (a non-finite element gets the last: the group's error is
+  // non-finite anyway), and 1 for the counted ones.
+  uint32_t at2[4], in2[4], at[8];   // at: LDS address of the entry
+  const i16x2 lo2 = {static_cast<short>(lo), static_cast<short>(lo)}, last2 = {static_cast<short>(nbin - 1), static_cast<short>(nbin - 1)}, zero2 = {0, 0};
 #pragma unroll
-  for (int i = 0; i < 8; ++i) {
-    const int h = static_cast<int>((i % 2 == 0 ? raw.w[i / 2] : raw.w[i / 2] >> 16) & 0x7FFFu);
-    at[i] = static_cast<uint32_t>(max(min(h - lo, nbin - 1), 0));   // (a non-finite element: the group's error is non-finite anyway)
-    counted[i] = h >= lo;
-    __hip_atomic_fetch_or((lds_u32*)static_cast<uintptr_t>(entry_at(at[i])), (counted[i] ? 1u : 0u) << (at[i] & 31u), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+  for (int j = 0; j < 4; ++j) {
+    const i16x2 n2 = __builtin_elementwise_min(__builtin_bit_cast(i16x2, raw.w[j] & 0x7FFF7FFFu) - lo2, last2);
+    at2[j] = __builtin_bit_cast(uint32_t, __builtin_elementwise_max(n2, zero2));
+    in2[j] = (~__builtin_bit_cast(uint32_t, n2) >> 15) & 0x00010001u;
+    asm("" : "+v"(at2[j]), "+v"(in2[j]));   // opaque: the halves are taken by the instructions that use them
+    uint32_t e0 = __builtin_amdgcn_ubfe(at2[j], 5u, 11u), e1 = at2[j] >> 21;
+    asm("" : "+v"(e0), "+v"(e1));
+    at[2 * j] = (e0 << 3) + tbl_at;
+    at[2 * j + 1] = (e1 << 3) + tbl_at;
+    __hip_atomic_fetch_or((lds_u32*)static_cast<uintptr_t>(at[2 * j]), (in2[j] & 0xFFFFu) << (at2[j] & 31u), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    __hip_atomic_fetch_or((lds_u32*)static_cast<uintptr_t>(at[2 * j + 1]), (in2[j] >> 16) << ((at2[j] >> 16) & 31u), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
   }
   wave_fence();
   {
@@ -265,12 +290,13 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4, 4))) void
   }
   wave_fence();
   // distinct patterns among the first n 
-  auto rank = [&](uint32_t n) {
+  auto rank_at = [&](uint32_t at, uint32_t n) {
     uint32_t r;
-    const u32x2 t = *(lds_u32x2*)static_cast<uintptr_t>(entry_at(n));
+    const u32x2 t = *(lds_u32x2*)static_cast<uintptr_t>(at);
     asm("v_bcnt_u32_b32 %0, %1, %2" : "=v"(r) : "v"(__builtin_amdgcn_ubfe(t[0], 0u, n)), "v"(t[1]));   // (the width's low 5 bits count)
     return r;
   };
+  auto rank = [&](uint32_t n) { return rank_at(entry_at(n), n); };
   auto cell = [](uint32_t at, uint32_t r) { return *(lds_word*)static_cast<uintptr_t>(at + r * Lay::STRIDE); };
 
   // ---- 2. count and sum per distinct pattern, prefixes -----------------------------------------------
@@ -278,11 +304,12 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4, 4))) void
   const int e_lo = exponent_of<In>(lo);
   uint32_t d[8];
 #pragma unroll
-  for (int i = 0; i < 8; ++i) d[i] = rank(at[i]);
+  for (int i = 0; i < 8; ++i) d[i] = rank_at(at[i], i % 2 == 0 ? at2[i / 2] : at2[i / 2] >> 16);
 #pragma unroll
   for (int i = 0; i < 8; ++i) {
-    const word one = counted[i] ? (static_cast<word>(1) << C::B) + static_cast<word>(static_cast<uint32_t>(__builtin_ldexpf(__builtin_fabsf(x[i]), kUlp - e_lo))) : 0;
-    const store neg = (f2u(x[i]) >> 31) != 0 ? static_cast<store>(one) : 0;
+    const bool counted = (in2[i / 2] & (i % 2 == 0 ? 1u : 0x10000u)) != 0;
+    const word one = counted ? (static_cast<word>(1) << C::B) + static_cast<word>(static_cast<uint32_t>(__builtin_ldexpf(x[i], kUlp - e_lo))) : 0;
+    const store neg = (raw.w[i / 2] & (i % 2 == 0 ? 0x8000u : 0x80000000u)) != 0 ? static_cast<store>(one) : 0;
     if constexpr (Lay::JOINED) {
       __hip_atomic_fetch_add(P + d[i], one | (neg << 32), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
     } else {
@@ -317,23 +344,24 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4, 4))) void
 
   // ---- 3. candidates -----------------------------------------------------------------------------
   double best[NF], second[NF];
-  int bk[NF];
   bool bad = !(amax <= 0x1p127f);   // the group has to be scored exactly (here: scales may leave the reciprocal's range)
 #pragma unroll
   for (int f = 0; f < NF; ++f) {
     best[f] = second[f] = __builtin_inf();
-    bk[f] = MOFQ_MAX_CLIP;
   }
   int before_lo = -lo;
   asm("" : "+v"(before_lo));   // opaque: pattern, this and the carry of the decision are one addition
   const float v_max = bits_to_float<In>(static_cast<uint32_t>(hmax));
-  // The candidates kbase + l / PER, PER adjacent lanes to each, which share its boundaries; ALL: there is one for every lane.
-  auto candidate = [&](auto fmt_c, auto per_c, auto all_c, int kbase, int f) {
+  // What the search of the gaps needs of the lane's candidate: 4 (error), 4 (sum of squared levels), scale.
+  struct Coarse {
+    double v;
+    float b4, s;
+  } coarse[NF];
+  // Candidate k (any valid number where there is none, !in), PER adjacent lanes to each, which share its boundaries.
+  auto candidate = [&](auto fmt_c, auto per_c, int k, bool in, int f) {
     constexpr int FMT = decltype(fmt_c)::value, PER = decltype(per_c)::value;
     using Lv = Levels<FMT>;
-    const int k = kbase + l / PER;
-    const bool in = decltype(all_c)::value || k < K;
-    const float s0 = search_scale<FMT>(s_clip[in ? k : K - 1] * amax, f16);
+    const float s0 = search_scale<FMT>(s_clip[k] * amax, f16);
     // No boundary but the eighth beyond the counted patterns: a scale that rounding to fp16 moved so far sends the group
     // to the exact pass.  (The patterns span more than the boundaries do, so the lower limit is the smaller one.)
     const float s = med3(s0, v_lo * Lv::kAbove, v_max * Lv::kBelow);
@@ -396,42 +424,91 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4, 4))) void
     // 4 (error): exact scaling
     const double sd = static_cast<double>(s);
     const double Ad = static_cast<double>(static_cast<std::make_signed_t<word>>(A)), bd = static_cast<double>(static_cast<int>(b4));
-    const double v = __builtin_fma(sd, __builtin_fma(-sd, bd, Ad * four_ulp), en4);
+    // the candidate rides in the lowest bits: 2^-45 of the error, far below the margin
+    const double v0 = __builtin_fma(sd, __builtin_fma(-sd, bd, Ad * four_ulp), en4);
+    const double v = __builtin_bit_cast(double, (__builtin_bit_cast(uint64_t, v0) & ~uint64_t{127}) | static_cast<uint32_t>(k));
     if (in) {
-      bk[f] = v < best[f] ? k : bk[f];
       second[f] = __builtin_fmin(second[f], __builtin_fmax(v, best[f]));
       best[f] = __builtin_fmin(best[f], v);
     }
+    coarse[f] = Coarse{v, -static_cast<float>(bd), s};
   };
-  auto round = [&](auto per_c, auto all_c, int kbase) {
-    candidate(std::integral_constant<int, FA>{}, per_c, all_c, kbase, 0);
-    if constexpr (NF == 2) candidate(std::integral_constant<int, FBX>{}, per_c, all_c, kbase, NF - 1);
+  auto both = [&](auto what) {
+    what(std::integral_constant<int, FA>{}, 0);
+    if constexpr (NF == 2) what(std::integral_constant<int, FBX>{}, NF - 1);
   };
-  int k0 = 0;
-  for (; k0 + LPG <= K; k0 += LPG) round(std::integral_constant<int, 1>{}, std::true_type{}, k0);
-  // The rest of them: several lanes to a candidate where there are enough (50 ratios, groups of 128: the last two take
-  // 143 instructions instead of a round's 242).
-  const int rest = K - k0;   // uniform
-  if (rest > 0) {
-    if (rest * 8 <= LPG) round(std::integral_constant<int, 8>{}, std::false_type{}, k0);
-    else if (rest * 4 <= LPG) round(std::integral_constant<int, 4>{}, std::false_type{}, k0);
-    else if (rest * 2 <= LPG) round(std::integral_constant<int, 2>{}, std::false_type{}, k0);
-    else round(std::integral_constant<int, 1>{}, std::false_type{}, k0);
+  using one_lane = std::integral_constant<int, 1>;
+  const double margin = 4.0 * filter_bounds<GROUP, true, 4>(en, 0.0, 0.0, 0.0, 0.0).margin;
+  if (Lay::gaps(K) && a.descending) {   // uniform
+    // LPG candidates over the whole table first, then the ones in the gaps that can be the winner.  The error of a scale
+    // s is the smallest of |x - s g|^2 over all assignments g of levels, so in a gap s2 < s < s1 it lies above some
+    // parabola of curvature |g|^2 <= B, B that at s2 (a smaller scale, larger levels), which at s1 and s2 is not below the errors E1
+    // and E2 there.  The smallest value of such a parabola is below T only if sqrt(E1 - T) + sqrt(E2 - T) < sqrt(B) (s1 - s2).
+    // T: the smallest error so far, twice the filter's margin, and 2^-18 of the energy: a decision on rounded
+    // numbers assigns an element within 2^-22 of a boundary to the level beyond it, which adds up to 4 x^2 2^-22 to the
+    // error (and takes such elements' levels out of B where the gap is that small).  The rest is rounded in favour of
+    // looking.  On LLaMA-like groups of 128 with 50 ratios 4 and 3 of the 34 candidates in the gaps are left.
+    auto place = [&](int i) { return static_cast<int>(static_cast<uint32_t>(i * (K - 1)) / static_cast<uint32_t>(LPG - 1)); };
+    const int mine = place(l), next = place(l + 1);
+    both([&](auto fmt_c, int f) { candidate(fmt_c, one_lane{}, mine, true, f); });
+    uint32_t left[NF];
+    const int gap = (K - 1 + LPG - 2) / (LPG - 1) - 1;   // the most candidates in one
+    // bf16: magnitudes whose squares leave fp32 are scaled by a power of two
+    const int e = std::is_same<In, F16>::value ? 0 : -__builtin_amdgcn_frexp_expf(amax);
+    both([&](auto, int f) {
+      const Coarse& c = coarse[f];
+      const double m = group_reduce<LPG>(c.v, [](double p, double q) { return __builtin_fmin(p, q); });
+      double above = c.v - (m + 2.0 * margin + 0x1p-18 * en4);
+      float ds = c.s - next_lane(c.s);
+      if constexpr (!std::is_same<In, F16>::value) {
+        above = __builtin_amdgcn_ldexp(above, 2 * e);
+        ds = __builtin_amdgcn_ldexpf(ds, e);
+      }
+      const float root = __builtin_amdgcn_sqrtf(__builtin_fmaxf(static_cast<float>(above), 0.0f));   // of 4 (E - T)
+      const bool look = l < LPG - 1 && !(root + next_lane(root) > __builtin_amdgcn_sqrtf(next_lane(c.b4)) * ds * (1.0f + 0x1p-12f));
+      const uint32_t n = look ? static_cast<uint32_t>(next - mine - 1) : 0u;
+      const uint32_t first = group_excl<LPG>(n, l);
+      left[f] = group_reduce<LPG>(n, [](uint32_t p, uint32_t q) { return p + q; });
+      for (uint32_t j = 0; j < static_cast<uint32_t>(gap); ++j)
+        if (j < n) list[f * GPW * (K - LPG) + first + j] = static_cast<uint8_t>(mine + 1 + j);
+    });
+    wave_fence();
+    both([&](auto fmt_c, int f) {
+      for (uint32_t i = 0; __builtin_amdgcn_ballot_w64(i < left[f]) != 0; i += LPG) {
+        const bool in = i + l < left[f];
+        candidate(fmt_c, one_lane{}, in ? list[f * GPW * (K - LPG) + i + l] : 0, in, f);
+      }
+    });
+  } else {
+    int k0 = 0;
+    for (; k0 + LPG <= K; k0 += LPG) both([&](auto fmt_c, int f) { candidate(fmt_c, one_lane{}, k0 + l, true, f); });
+    // The rest of them: several lanes to a candidate where there are enough (two candidates on 16 lanes take
+    // 143 instructions instead of a round's 242).
+    const int rest = K - k0;   // uniform
+    auto shared = [&](auto per_c) {
+      const int k = k0 + l / decltype(per_c)::value;
+      both([&](auto fmt_c, int f) { candidate(fmt_c, per_c, min(k, K - 1), k < K, f); });
+    };
+    if (rest > 0) {
+      if (rest * 8 <= LPG) shared(std::integral_constant<int, 8>{});
+      else if (rest * 4 <= LPG) shared(std::integral_constant<int, 4>{});
+      else if (rest * 2 <= LPG) shared(std::integral_constant<int, 2>{});
+      else shared(one_lane{});
+    }
   }
 
   // ---- 4. winners.  Count and sum are exact and the error takes two roundings (filter_bounds): a candidate that
   // is the smallest by more than the margin is the winner, and its own error is then summed element by element, for
   // en - 2 s A + s^2 B keeps two digits fewer than that sum. -------------------------------------------------
   const bool exact = group_reduce<LPG>(bad ? 1 : 0, [](int p, int q) { return p | q; }) != 0;
-  const double margin = 4.0 * filter_bounds<GROUP, true, 4>(en, 0.0, 0.0, 0.0, 0.0).margin;
   int win[NF];
   bool sure[NF];
 #pragma unroll
   for (int f = 0; f < NF; ++f) {
     auto least = [](double p, double q) { return __builtin_fmin(p, q); };
     const double m = group_reduce<LPG>(best[f], least);
-    win[f] = group_reduce<LPG>(best[f] == m ? bk[f] : MOFQ_MAX_CLIP, [](int p, int q) { return min(p, q); });
-    const double m2 = group_reduce<LPG>(bk[f] == win[f] ? second[f] : best[f], least);   // candidates of one lane are its own
+    win[f] = static_cast<int>(__builtin_bit_cast(uint64_t, m) & 127u);
+    const double m2 = group_reduce<LPG>(best[f] == m ? second[f] : best[f], least);   // candidates of one lane are its own
     sure[f] = !exact && m2 > m + margin;   // false for a zero or non-finite error
   }
   raw.opaque();
@@ -491,10 +568,10 @@ int launch_size(const GroupArgs& a, hipStream_t st) {
   if (bits > 32) return MOFQ_ERR_UNSUPPORTED;
   const dim3 grid(static_cast<unsigned>((a.units + GPW - 1) / GPW));
   if (GROUP <= 128 && bits < 24 && ((GROUP - 1) >> (24 - bits)) == 0) {
-    const size_t lds = static_cast<size_t>(GroupLayout<GROUP, false, TAIL>::bytes(a.nbin));
+    const size_t lds = static_cast<size_t>(GroupLayout<GROUP, false, TAIL>::all_bytes(a.nbin, a.n_clip, FB >= 0 ? 2 : 1));
     hipLaunchKernelGGL((sweep_group_bits_kernel<In, FA, FB, GROUP, false>), grid, dim3(64), lds, st, a);
   } else {
-    const size_t lds = static_cast<size_t>(GroupLayout<GROUP, true, TAIL>::bytes(a.nbin));
+    const size_t lds = static_cast<size_t>(GroupLayout<GROUP, true, TAIL>::all_bytes(a.nbin, a.n_clip, FB >= 0 ? 2 : 1));
     hipLaunchKernelGGL((sweep_group_bits_kernel<In, FA, FB, GROUP, true>), grid, dim3(64), lds, st, a);
   }
   return hip_status(hipGetLastError());
@@ -519,20 +596,19 @@ int launch_type(const SweepParams& p, const GroupArgs& a, hipStream_t st) {
   return MOFQ_ERR_UNSUPPORTED;
 }
 
-// From how many clip ratios on this kernel is the faster one: building the table costs what scoring that many
-// candidates costs.  The pair shares one table and a format alone has it to itself; INT4's takes the negative elements'
-// words as well (E2M1 alone needs neither them nor their prefixes); bf16 has an eighth of fp16's bits to clear and to
-// walk; a group of 64 has a table of its own like any other; one of 256 takes 64-bit words.  Measured at the lines,
-// layer selection, 4096 x 4096 (11008 x 4096 gives the same lines to within three ratios; below 1000 rows launches hide
-// the difference), us, scored directly / by look-up: INT4 and E2M1, fp16: 64, 29 ratios: 161 / 160; 128, 13: 84 / 83;
-// 256, 21: 117 / 114; bf16: 64, 12: 84 / 83; 128, 9: 66 / 65; 256, 18: 103 / 102.  INT4: fp16 64, 80: 183 / 179; 128,
-// 28: 77 / 76; 256, 40: 103 / 102; bf16 64, 21: 68.4 / 67.5; 128, 20: 60.8 / 60.8; 256, 39: 99 / 97.  E2M1: fp16 64,
-// 38: 115 / 113; 128, 20: 68 / 66; 256, 19: 63 / 63; bf16 64, 13: 56.5 / 55.8; 128, 11: 47.6 / 45.7; 256, 16: 55.8 /
-// 55.5.
+// From how many clip ratios on this kernel is the faster one: building the table costs what scoring that many candidates
+// costs. The pair shares one table and a format alone has it to itself; INT4's takes the negative elements' words as well
+// (E2M1 alone needs neither them nor their prefixes); bf16 has an eighth of fp16's bits to clear and to walk; a group of
+// 64 has a table of its own like any other; one of 256 takes 64-bit words. Measured at the lines, layer selection, 4096 x
+// 4096, type and group, ratios: us scored directly / by look-up: INT4 and E2M1: fp16 64, 23: 133.8 / 131.1; fp16 128, 12:
+// 80.1 / 78.7; fp16 256, 21: 116.8 / 112.6; bf16 64, 10: 76.4 / 75.1; bf16 128, 9: 66.5 / 65.6; bf16 256, 18: 102.8 /
+// 100.7. INT4: fp16 64, 48: 122.0 / 120.4; fp16 128, 25: 73.3 / 72.2; fp16 256, 39: 101.2 / 100.4; bf16 64, 19: 64.1 /
+// 62.4; bf16 128, 19: 59.9 / 59.5; bf16 256, 37: 95.7 / 95.4. E2M1: fp16 64, 28: 91.5 / 90.4; fp16 128, 15: 57.5 / 56.6;
+// fp16 256, 20: 64.9 / 63.4; bf16 64, 13: 56.7 / 53.1; bf16 128, 11: 47.8 / 46.7; bf16 256, 17: 58.6 / 58.2.
 int min_clip(const SweepParams& p) {
   static constexpr int lines[2][3][3] = {   // [fp16, bf16][64, 128, 256][pair, INT4, E2M1]
-      {{29, 80, 38}, {13, 27, 20}, {21, 40, 19}},
-      {{12, 21, 13}, {9, 20, 11}, {18, 39, 16}}};
+      {{23, 48, 28}, {12, 25, 15}, {21, 39, 20}},
+      {{10, 19, 13}, {9, 19, 11}, {18, 37, 17}}};
   const int which = p.n_fmt == 2 ? 0 : (p.fmt[0] == MOFQ_INT4 ? 1 : 2);
   return lines[p.dtype == MOFQ_F16 ? 0 : 1][p.group == 64 ? 0 : (p.group == 128 ? 1 : 2)][which];
 }
@@ -551,10 +627,12 @@ int launch_sweep_group_bits(const SweepParams& p, hipStream_t st) {
   a.n_clip = p.n_clip;
   a.rec = p.rec;
   float r_min = INFINITY;
+  a.descending = 1;
   for (int k = 0; k < p.n_clip; ++k) {
     if (!(p.clip[k] > 0.0f) || !std::isfinite(p.clip[k])) return MOFQ_ERR_UNSUPPORTED;
     r_min = std::fmin(r_min, p.clip[k]);
     a.clip[k] = p.clip[k];
+    if (k > 0 && p.clip[k] > p.clip[k - 1]) a.descending = 0;
   }
   const bool e2m1 = p.fmt[0] == MOFQ_FP4_E2M1 || (p.n_fmt == 2 && p.fmt[1] == MOFQ_FP4_E2M1);
   a.nbin = (hist_bins((e2m1 ? 24.0 : 14.0) / r_min, p.dtype == MOFQ_F16 ? 1024 : 128) + 31) / 32 * 32;

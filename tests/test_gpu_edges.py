@@ -128,6 +128,43 @@ def test_group_last_round(mq, dtype, group, n_clip):  # noqa: F811
         check_tensor(mq, w, cands, orc.PER_GROUP, ratios, group, True, label="group-last-round")
 
 
+# tables that descend and are long enough to be searched coarsely first: one more ratio than that takes, the longest;
+# equal neighbours, neighbours an ulp apart, a wide geometric table, one that ends in a plateau
+def _descending(kind, n):
+    if kind == "even":
+        return [float(r) for r in mi.clip_ratios(n)]
+    if kind == "pairs":
+        return [1.0 - 0.5 * (i // 2) / n for i in range(n)]
+    if kind == "ulps":
+        return [float(np.float32(0.8) - np.float32(2.0 ** -24) * i) for i in range(n)]
+    if kind == "wide":
+        return [0.02 ** (i / (n - 1)) for i in range(n)]
+    return [max(1.0 - 0.9 * i / n, 0.6) for i in range(n)]
+
+
+@pytest.mark.parametrize("dtype", [torch.float16, torch.bfloat16])
+@pytest.mark.parametrize("group,n_clip,kind", [
+    (64, 50, "even"), (64, 128, "wide"), (64, 61, "pairs"), (64, 100, "ulps"), (128, 33, "even"), (128, 50, "even"), (128, 64, "plateau"),
+    (128, 128, "even"), (128, 99, "ulps"), (128, 40, "wide"), (256, 65, "even"), (256, 128, "wide"), (256, 90, "pairs")])
+def test_group_gaps(mq, dtype, group, n_clip, kind):  # noqa: F811
+    w = _strided(14, 6 * group, group, n_clip, dtype)
+    g = torch.Generator(device=DEV).manual_seed(group + n_clip)
+    v = [w[r, (r % 3) * group:(r % 3 + 2) * group] for r in range(14)]
+    v[0][:] = 0.0
+    v[1][:] = 0.75
+    v[2][:] = -v[2].abs()
+    v[3][:] = torch.exp2(torch.randint(-9, 3, (2 * group,), generator=g, device=DEV).float()).to(dtype)
+    v[4][:] = torch.randint(-7, 8, (2 * group,), generator=g, device=DEV).to(dtype)      # nearly on one grid
+    v[5][:] = (torch.randint(0, 8, (2 * group,), generator=g, device=DEV) + 0.5).to(dtype)   # on its boundaries
+    v[6][:] = torch.rand(2 * group, generator=g, device=DEV).to(dtype)
+    v[7][3] = -6.0e4
+    v[8][:] = (v[8].float() * (2.0 ** -14 if dtype == torch.float16 else 2.0 ** 120)).to(dtype)
+    v[9][5:] = 0.0
+    v[10][:] = (v[10].float() * (2.0 ** -9 if dtype == torch.float16 else 2.0 ** -115)).to(dtype)
+    for cands in (PAIR4, [orc.INT4], [orc.FP4_E2M1]):
+        check_tensor(mq, w, cands, orc.PER_GROUP, _descending(kind, n_clip), group, label=f"group-gaps {kind}")
+
+
 # ratios so small that a group's largest elements are 2^31 ulps of the first counted pattern and more: the last tables
 # of the rank kernel and, beyond them, the direct kernel (bf16: 128 patterns per binade)
 @pytest.mark.parametrize("lo_clip", [1e-5, 4e-6, 2e-6, 1e-6, 1e-7])
