@@ -465,7 +465,9 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(kWaves<In, W
         ds = __builtin_amdgcn_ldexpf(ds, e);
       }
       const float root = __builtin_amdgcn_sqrtf(__builtin_fmaxf(static_cast<float>(above), 0.0f));   // of 4 (E - T)
-      const bool look = l < LPG - 1 && !(root + next_lane(root) > __builtin_amdgcn_sqrtf(next_lane(c.b4)) * ds * (1.0f + 0x1p-12f));
+      // (the lanes' values are moved by all of them: one that is switched off has none for its neighbour)
+      const float roots = root + next_lane(root), reach = __builtin_amdgcn_sqrtf(next_lane(c.b4)) * ds * (1.0f + 0x1p-12f);
+      const bool look = l < LPG - 1 && !(roots > reach);
       const uint32_t n = look ? static_cast<uint32_t>(next - mine - 1) : 0u;
       const uint32_t first = group_excl<LPG>(n, l);
       left[f] = group_reduce<LPG>(n, [](uint32_t p, uint32_t q) { return p + q; });

@@ -165,6 +165,19 @@ def test_group_gaps(mq, dtype, group, n_clip, kind):  # noqa: F811
         check_tensor(mq, w, cands, orc.PER_GROUP, _descending(kind, n_clip), group, label=f"group-gaps {kind}")
 
 
+# the best ratio in every part of a table that descends, its last gap included: groups whose one large element is 3 to 9
+# standard deviations of the others
+@pytest.mark.parametrize("group,n_clip", [(64, 50), (128, 50), (128, 77), (256, 66), (256, 120)])
+def test_group_gaps_everywhere(mq, group, n_clip):  # noqa: F811
+    g = torch.Generator(device=DEV).manual_seed(n_clip)
+    w = 0.02 * torch.randn(64, 8 * group, generator=g, device=DEV)
+    large = torch.linspace(3.0, 9.0, 64 * 8, device=DEV).view(64, 8)
+    w.view(64, 8, group)[:, :, 5] = 0.02 * large
+    w = w.to(torch.float16)
+    for cands in (PAIR4, [orc.INT4]):
+        check_tensor(mq, w, cands, orc.PER_GROUP, _descending("even", n_clip), group, label="group-gaps-everywhere")
+
+
 # ratios so small that a group's largest elements are 2^31 ulps of the first counted pattern and more: the last tables
 # of the rank kernel and, beyond them, the direct kernel (bf16: 128 patterns per binade)
 @pytest.mark.parametrize("lo_clip", [1e-5, 4e-6, 2e-6, 1e-6, 1e-7])
