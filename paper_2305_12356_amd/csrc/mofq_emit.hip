@@ -17,13 +17,15 @@ constexpr int kThreads = 256;
 constexpr int kNW = kThreads / 64;
 
 // Sums over the units are taken in two stages of a fixed shape, so that a result depends on the
-// number of values alone and not on the launch: consecutive chunks of values (one workgroup each),
-// then the chunk sums.  Up to kDirectUnits values there is one stage: reading 8 KB per candidate
+// number of values alone and not on the launch: consecutive chunks of kChunkUnits values and more (one workgroup each),
+// then the chunk sums.  Up to kDirectUnits values there is one stage: reading 16 KB per candidate
 // in every emitting workgroup costs less than one more launch (2.5 us of host time, about 2 us on
-// the device); beyond, the first stage leaves at most kDecideBlocks values.
-constexpr int64_t kDirectUnits = 1024;
+// the device); beyond, the first stage leaves at most kDecideBlocks values.  Layer selection, us, one stage up to
+// 1024 / 2048 / 4096 values: fp32 2048 x 1024, one ratio 13.5 / 11.2 / 11.2; bf16 1237 x 5000, 100 ratios 25.3 / 24.3 / 24.3;
+// fp32 4000 x 1024 17.2 / 17.2 / 17.1, 4000 x 4096 34.3 / 34.3 / 35.9.
+constexpr int64_t kDirectUnits = 2048, kChunkUnits = 1024;
 int64_t partial_chunks(int64_t n) {
-  return n <= kDirectUnits ? 0 : std::min<int64_t>(kDecideBlocks, (n + kDirectUnits - 1) / kDirectUnits);
+  return n <= kDirectUnits ? 0 : std::min<int64_t>(kDecideBlocks, (n + kChunkUnits - 1) / kChunkUnits);
 }
 
 // every candidate's error, the energy, the sum of the smallest error of every unit
@@ -39,8 +41,8 @@ struct SumArrays {
 
 // Sums of n values of the first n_arr arrays, and of the per-unit minima if asked for, into s_sum.
 // One wave per array: a wave reads 1024 values with 16 loads in flight per lane, so the whole is
-// one memory latency for the sizes this is called with, and the order is fixed (lane-strided, then
-// the wave sum).  Valid for every thread.
+// one or two memory latencies for the sizes this is called with (32 loads in flight cost every emission registers:
+// fp32 4000 x 1024 17.2 -> 20.7 us), and the order is fixed (lane-strided, then the wave sum).  Valid for every thread.
 MOFQ_DEV void block_sums(const SumArrays& a, int n_arr, int64_t lo, int64_t n, bool mixed, double (&s_sum)[kSums]) {
   constexpr int U = 16;
   const int lane = threadIdx.x & 63;
@@ -579,7 +581,7 @@ int launch_wa_copy(const WaCopyParams* p, int n, hipStream_t st) {
 }
 
 int launch_decide(const DecideParams& p, hipStream_t st) {
-  if (p.units < 1 || p.units > (int64_t{1} << 31) * (two_stages(p) ? kDirectUnits : 1) - 1) return MOFQ_ERR_INVALID_ARG;
+  if (p.units < 1 || p.units > (int64_t{1} << 31) * (two_stages(p) ? kChunkUnits : 1) - 1) return MOFQ_ERR_INVALID_ARG;
   const DecideParams* list[1] = {&p};
   const int rc = launch_partial(list, 1, st);
   if (rc != MOFQ_OK) return rc;

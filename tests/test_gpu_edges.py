@@ -31,7 +31,7 @@ def test_per_tensor_passes(mq, rows, cols, pad, dtype):  # noqa: F811
 
 
 # rows of one chunk; units on both sides of the one-stage limit; segments that end inside rows and groups
-@pytest.mark.parametrize("rows,cols,pad,group", [(700, 8, 0, 0), (1024, 40, 0, 0), (1025, 264, 8, 0), (5, 32768, 0, 0),
+@pytest.mark.parametrize("rows,cols,pad,group", [(700, 8, 0, 0), (1024, 40, 0, 0), (1025, 264, 8, 0), (2048, 24, 0, 0), (2049, 136, 8, 0), (5, 32768, 0, 0),
                                                  (33, 4128, 32, 32), (9, 16640, 0, 256), (70, 640, 64, 64)])
 def test_emission_segments(mq, rows, cols, pad, group):  # noqa: F811
     w = _strided(rows, cols, pad, rows + cols, torch.float16)
