@@ -13,8 +13,10 @@
 // bank conflicts take 55 % of the LDS's cycles).
 // The error that leaves for an 8-bit format is the winner's element-wise sum (finish_row): the look-ups
 // choose it, and their difference of large sums would keep four digits fewer (1e-12 instead of 1e-15 on 5000 elements).
-// Measured, layer selection: INT8 against E4M3, 3001 x 5000, 50 ratios 277 -> 69.5 us (68 without that sum; this
-// kernel 58); 4096 x 11008, 100 ratios 1294 -> 141 us; INT4 against E2M1, 1237 x 5000, 100 ratios: 28.2 -> 25.6 us.
+// The prefixes lie over the counters they are formed from (a thread holds its share in registers meanwhile), so that
+// six workgroups of the 8-bit search fit a compute unit instead of five.
+// Measured, layer selection: INT8 against E4M3, 3001 x 5000, 50 ratios 277 -> 69.8 -> 66.4 us (the last step: prefixes over
+// the counters); 4096 x 11008, 100 ratios 1294 -> 141 us; INT4 against E2M1, 1237 x 5000, 100 ratios: 28.2 -> 25.6 us.
 //
 // INT8's levels are spaced evenly; E4M3's evenly inside runs of 8 codes (a binade; the subnormals are the
 // first run): per run the level sums are d sum_i S_i and d^2 sum_i (2 (base + i) + 1) C_i with d the run's
@@ -88,25 +90,30 @@ template <> struct Runs<MOFQ_FP8_E4M3> {
   MOFQ_DEV static int base(int r) { return r > 0 ? 8 : 0; }
 };
 
-// Exclusive prefixes over the counters in place of P[0 .. nbin], packed count << 48 | sum.  Thread `id` of
-// NW waves takes the counters [id pp, (id + 1) pp), pp even.  NW > 1: by the whole workgroup, with barriers.
-template <int NW>
+// Exclusive prefixes over the counters, P[0 .. nbin], packed count << 48 | sum.  Thread `id` of
+// NW waves takes the counters [id pp, (id + 1) pp), pp even and at most 2 PWMAX.  NW > 1: by the whole workgroup, with
+// barriers; a thread's counters stay in its registers over the first, behind which P may lie over them.
+template <int NW, int PWMAX>
 MOFQ_DEV void packed_prefixes(const uint32_t* counters, uint64_t* P, int lo, int nbin, uint64_t* s_wave) {
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int id = NW > 1 ? tid : lane;
   const int pw = (nbin / 2 + NW * 64 - 1) / (NW * 64);   // words per thread
   const int e_lo = exponent_of<BF16>(lo);
   const int w0 = id * pw, w1 = (w0 + pw < nbin / 2) ? w0 + pw : nbin / 2;
-  uint64_t acc = 0;
-  for (int w = w0; w < w1; ++w) {
-    const uint32_t c2 = counters[w];
+  uint32_t c2[PWMAX];
+#pragma unroll
+  for (int j = 0; j < PWMAX; ++j) c2[j] = j < pw && w0 + j < w1 ? counters[w0 + j] : 0u;
+  auto add = [&](int j, uint64_t& acc, auto between) {
     uint32_t m, shift;
-    mant_shift<BF16>(static_cast<uint32_t>(lo + 2 * w), e_lo, m, shift);   // lo is even: both patterns share the exponent
-    P[2 * w] = acc;
-    acc += static_cast<uint64_t>(m << shift) * (c2 & 0xFFFFu) + (static_cast<uint64_t>(c2 & 0xFFFFu) << 48);
-    P[2 * w + 1] = acc;
-    acc += static_cast<uint64_t>((m + 1) << shift) * (c2 >> 16) + (static_cast<uint64_t>(c2 >> 16) << 48);
-  }
+    mant_shift<BF16>(static_cast<uint32_t>(lo + 2 * (w0 + j)), e_lo, m, shift);   // lo is even: both patterns share the exponent
+    acc += static_cast<uint64_t>(m << shift) * (c2[j] & 0xFFFFu) + (static_cast<uint64_t>(c2[j] & 0xFFFFu) << 48);
+    between();
+    acc += static_cast<uint64_t>((m + 1) << shift) * (c2[j] >> 16) + (static_cast<uint64_t>(c2[j] >> 16) << 48);
+  };
+  uint64_t acc = 0;
+#pragma unroll
+  for (int j = 0; j < PWMAX; ++j)
+    if (j < pw) add(j, acc, [] {});   // uniform; words past the end count nothing
   // exclusive scan over the threads (sums of the two fields do not meet: the sum stays below 2^48)
   uint64_t inc = acc;
 #pragma unroll
@@ -114,17 +121,23 @@ MOFQ_DEV void packed_prefixes(const uint32_t* counters, uint64_t* P, int lo, int
     const uint64_t o = __shfl_up(inc, d, 64);
     if (lane >= d) inc += o;
   }
-  uint64_t base = inc - acc;
+  uint64_t at = inc - acc;
   if constexpr (NW > 1) {
     if (lane == 63) s_wave[wave] = inc;
     __syncthreads();
-    for (int w = 0; w < wave; ++w) base += s_wave[w];
+    for (int w = 0; w < wave; ++w) at += s_wave[w];
   }
-  for (int w = w0; w < w1; ++w) {
-    P[2 * w] += base;
-    P[2 * w + 1] += base;
-  }
-  if (id == NW * 64 - 1) P[nbin] = base + acc;
+#pragma unroll
+  for (int j = 0; j < PWMAX; ++j)
+    if (j < pw) {
+      uint64_t first = at, second = 0;
+      add(j, at, [&] { second = at; });
+      if (w0 + j < w1) {
+        P[2 * (w0 + j)] = first;
+        P[2 * (w0 + j) + 1] = second;
+      }
+    }
+  if (id == NW * 64 - 1) P[nbin] = at;
   if constexpr (NW > 1) __syncthreads();
 }
 
@@ -142,13 +155,13 @@ void sweep_bf16_kernel(const SortedArgs a) {
   constexpr bool ANY_TAIL = TAIL_A || TAIL_B;
   constexpr bool EIGHT = Codec<FA>::BITS == 8;
 
-  // dynamic LDS: [counters | of the negative elements | prefixes | of the negative elements]
+  // dynamic LDS: [prefixes, before them the counters in the same place | of the negative elements | their counters]
   extern __shared__ __attribute__((aligned(16))) unsigned char s_dyn[];
   const int nbin = a.nbin, ntbin = ANY_TAIL ? a.ntbin : 0;   // multiples of 8
-  uint32_t* const counters = reinterpret_cast<uint32_t*>(s_dyn);
-  uint32_t* const tcounters = counters + nbin / 2;
-  uint64_t* const P = reinterpret_cast<uint64_t*>(tcounters + ntbin / 2);
+  uint64_t* const P = reinterpret_cast<uint64_t*>(s_dyn);
   uint64_t* const TP = P + (nbin + 1);
+  uint32_t* const counters = reinterpret_cast<uint32_t*>(s_dyn);
+  uint32_t* const tcounters = reinterpret_cast<uint32_t*>(TP + (ntbin + 1));
 
   __shared__ RowSearch<NF, kNW> sh;
   __shared__ float s_wmax[kNW];
@@ -181,7 +194,8 @@ void sweep_bf16_kernel(const SortedArgs a) {
   if (NF == 2 && T.ahead.codes && wave == kNW - 1) tally = tally_read(T.ahead);
   {
     const u32x4 zero = {0u, 0u, 0u, 0u};
-    for (int i = tid; i < (nbin + ntbin) / 8; i += kThreads) reinterpret_cast<u32x4*>(counters)[i] = zero;
+    for (int i = tid; i < nbin / 8; i += kThreads) reinterpret_cast<u32x4*>(counters)[i] = zero;
+    for (int i = tid; i < ntbin / 8; i += kThreads) reinterpret_cast<u32x4*>(tcounters)[i] = zero;
   }
   float amax = 0.0f;
   double en = 0.0;
@@ -244,8 +258,13 @@ void sweep_bf16_kernel(const SortedArgs a) {
   __syncthreads();
 
   if constexpr (ANY_TAIL)
-    if (wave == kNW - 1) packed_prefixes<1>(tcounters, TP, tlo, ntbin, s_wave);
-  packed_prefixes<kNW>(counters, P, lo, nbin, s_wave);
+    if (wave == kNW - 1) {
+      if (ntbin <= 256) packed_prefixes<1, 2>(tcounters, TP, tlo, ntbin, s_wave);
+      else packed_prefixes<1, kMaxTailBins / 128>(tcounters, TP, tlo, ntbin, s_wave);
+    }
+  // (the short ones of the 4-bit formats in code of their own: 1237 x 5000 took 0.6 us more in the other's)
+  if (nbin <= 4 * kThreads) packed_prefixes<kNW, 2>(counters, P, lo, nbin, s_wave);
+  else packed_prefixes<kNW, kMaxBins / 2 / kThreads>(counters, P, lo, nbin, s_wave);
   const uint64_t total = P[nbin];
   const float v_lo = bits_to_float<BF16>(static_cast<uint32_t>(lo));
   const double unit = static_cast<double>(bits_to_float<BF16>(static_cast<uint32_t>(lo) + 1) - v_lo);   // an ulp at lo
@@ -376,7 +395,7 @@ void sweep_bf16_kernel(const SortedArgs a) {
 
 size_t lds_bytes(const SortedArgs& a) {
   const size_t prefixes = std::max<size_t>(8 * static_cast<size_t>(a.nbin + 1 + a.ntbin + 1), 2 * MOFQ_MAX_CLIP * sizeof(double));
-  return 2 * static_cast<size_t>(a.nbin + a.ntbin) + prefixes;
+  return prefixes + 2 * static_cast<size_t>(a.ntbin);
 }
 
 template <int FA, int FB>

@@ -58,7 +58,7 @@ def test_codes_written_by_the_single_candidate_search(mq, dtype, rows, cols, pad
 # one format and two, ratios that stretch the histogram; rows of zeros, of equal elements, of powers of two
 # over the whole range, and rows so small that the scales or the elements are subnormal
 @pytest.mark.parametrize("cols,n_clip,lo_clip,f16", [
-    (1024, 32, 0.5, False), (2048, 16, 0.3, False), (2056, 64, 0.5, True), (4104, 8, 0.9, False), (5000, 50, 0.5, False),
+    (1024, 32, 0.5, False), (2048, 16, 0.3, False), (2056, 64, 0.5, True), (4104, 8, 0.9, False), (5000, 50, 0.5, False), (3000, 20, 0.115, False), (3000, 20, 0.111, False),
     (6152, 65, 0.5, False), (8200, 100, 0.25, True), (12296, 20, 0.5, False), (24576, 9, 0.05, False),
     # from these on for every list of formats
     (1024, 52, 0.4, False), (2048, 26, 0.5, True), (4104, 13, 0.7, False)])
