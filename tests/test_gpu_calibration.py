@@ -82,3 +82,27 @@ def test_zero_calibration_and_ragged_sizes(mq):
     b = calibrate(mq, [x])
     assert b.item() == x.abs().max().item()
     check_batch(mq, x, [I8, FP8], b)
+
+
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float16, torch.float32])
+@pytest.mark.parametrize("rows,cols,ld", [(1, 8, 8), (255, 8, 8), (1023, 8, 24), (1025, 8, 8), (1, 8200, 8200), (129, 2056, 2072),
+                                          (4096, 2048, 2048), (4099, 2048, 2056)])
+def test_running_maximum_everywhere(mq, rows, cols, ld, dtype):
+    # the largest magnitude in the first, the last and one inner element, at the edges of a workgroup's share (1024
+    # chunks of 8, from 4096 of them on four rounds of 4 per lane): each alone has to raise the value, and a smaller batch has to leave it
+    base = torch.zeros(rows, ld, dtype=dtype, device=DEV)
+    base[:, cols:] = 1000.0                                   # between the rows: not part of the tensor
+    x = base[:, :cols]
+    x.uniform_(-1.0, 1.0)
+    a = torch.zeros(1, dtype=torch.float32, device=DEV)
+    ws = _ws(mq, x, 1)
+    mq.calibrate_absmax(x, a, ws)
+    assert a.item() == x.float().abs().max().item()
+    for i, (r, c) in enumerate([(0, 0), (rows - 1, cols - 1), (rows // 2, cols // 3)]):
+        kept = x[r, c].item()
+        x[r, c] = -2.0 - i
+        mq.calibrate_absmax(x, a, ws)
+        assert a.item() == 2.0 + i, (r, c)
+        x[r, c] = kept
+        mq.calibrate_absmax(x, a, ws)
+        assert a.item() == 2.0 + i
