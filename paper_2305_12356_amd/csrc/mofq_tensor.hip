@@ -8,6 +8,8 @@
 //   calibrated: errors of the candidates | select + codes                          (2)
 //   quantize  : largest magnitude | codes + error | one-unit outputs               (3), or 1 for small tensors
 #include <algorithm>
+#include <atomic>
+#include <chrono>
 
 #include "mofq_codes.h"
 #include "mofq_internal.h"
@@ -274,61 +276,105 @@ __global__ __launch_bounds__(kThreads) void tensor_unit_kernel(const TensorArgs 
   }
 }
 
-// Tensors of up to 65536 elements (a few tokens of an activation): one launch.  Every workgroup
-// reads the whole tensor (128 KB at most, from L2) and finds its magnitude; workgroup 0 then sums the
-// error and leaves the outputs of the one unit, workgroup b > 0 writes the b-th eighth of the codes.
-// Two further launches cost a call 4.5 us whatever its size (10.0 us among others, 21.8 alone, bf16 E4M3),
-// the error in one workgroup grows with it: 5.5 / 16.5 us for 4096 elements, 7.6 / 20.4 for 65536.  With registers
-// for twice as many chunks 65536 elements take 7.9 / 20.8, 81920 9.2 / 22.2 and 98304 10.4 / 23.3: the lines cross
-// at about 80000, and the larger tile is slower for every smaller call (fp32 rows no longer fit registers at all).
-constexpr int kSmallThreads = 1024, kSmallChunks = 8;
+// Tensors of up to 163840 elements (a few tokens of an activation): one launch.  Every workgroup reads the whole
+// tensor (from L2, 8 loads in flight per lane) and finds its magnitude, then writes the codes of its own 8192 elements
+// and sums their error; the workgroup that finds everybody's sums in the scratch adds them up.  Up to 65536 elements
+// the host bounds the call (5.0 us among others, 15.5 alone), beyond that what one compute unit reads and compares.
+// bf16 E4M3, us among others / alone, with all of the error summed by one workgroup -> here: 32768 elements 5.1 / 17.2 ->
+// 5.1 / 16.7, 65536 7.5 / 19.8 -> 5.6 / 18.4; in three launches (9.8 / 21.2 whatever the size) -> here: 81920 6.4 / 19.0,
+// 131072 7.4 / 19.9, 196608 9.2 / 21.6, 262144 10.9 / 23.6; fp32 65536 7.4 / 20.1 -> 5.9 / 18.6, 131072 8.0 / 20.6.
+// In the launches of larger tensors the same meeting would cost more than the third launch: its fence in 1024
+// workgroups takes 20 us.
+//
+// The meeting: workgroup b leaves two words, its sum's bits and the same bits ^ nonce, and reads all of them behind a
+// sequentially consistent fence, so the last one in the order of the fences finds them all (a second one that does writes the same
+// values).  A pair is complete if it xors to the nonce, which the host draws per call, so the scratch needs no
+// clearing; whoever finds all pairs leaves zeros, so that a replay of a captured call, which has the same nonce,
+// starts without them.  Torn pairs: (sum, 0) xors to the sum, which is never the nonce (a negative number);
+// (0, sum ^ nonce) xors to the nonce only if the sum is 0, the value then read.  Nobody waits for anybody.
+constexpr int kSmallThreads = 1024, kSmallLoads = 8, kSmallBlocks = 20;
+static_assert(kSmallBlocks <= 64 && 2 * kSmallBlocks <= kTensorBlocks, "a lane and two words of scratch per workgroup");
 template <typename In, int FMT>
-__global__ __launch_bounds__(kSmallThreads) void tensor_quant_small_kernel(const TensorArgs a) {
+__global__ __launch_bounds__(kSmallThreads) void tensor_quant_small_kernel(const TensorArgs a, const uint64_t nonce) {
   __shared__ float s_tmp[kSmallThreads / 64];
   __shared__ double s_sum[kSmallThreads / 64];
-  Raw8<In> raw[kSmallChunks];
   const int n = static_cast<int>(a.n_chunks), tid = threadIdx.x;
-#pragma unroll
-  for (int j = 0; j < kSmallChunks; ++j) {
-    const int c = j * kSmallThreads + tid;
-    if (j * kSmallThreads < n) load_chunk<In>(a, c < n ? c : 0, raw[j]);   // uniform; past the end: chunk 0 again
-  }
-  float m = 0.0f;
-#pragma unroll
-  for (int j = 0; j < kSmallChunks; ++j)
-    if (j * kSmallThreads < n) {
-      float v[8];
-      raw[j].widen(v);
-#pragma unroll
-      for (int i = 0; i < 8; ++i) m = __builtin_fmaxf(m, __builtin_fabsf(v[i]));
+  const int blocks = gridDim.x, b = blockIdx.x;
+  const uint32_t cpr = static_cast<uint32_t>(a.cpr);   // at most n
+  const auto load = [&](int c, Raw8<In>& raw) {
+    if (a.ld == a.cpr * 8) {   // uniform
+      raw.load(a.w, static_cast<int64_t>(c) * 8, 0);
+    } else {
+      const uint32_t row = static_cast<uint32_t>(c) / cpr;
+      raw.load(a.w, row * a.ld + static_cast<int64_t>(static_cast<uint32_t>(c) - row * cpr) * 8, 0);
     }
+  };
+  float m = 0.0f;
+  const auto widest = [&](const Raw8<In>& raw) {
+    float v[8];
+    raw.widen(v);
+#pragma unroll
+    for (int i = 0; i < 8; ++i) m = __builtin_fmaxf(m, __builtin_fabsf(v[i]));
+  };
+  Raw8<In> own;
+  const int c_own = b * kSmallThreads + tid;
+  load(c_own < n ? c_own : 0, own);   // past the end: chunk 0 again
+  for (int j0 = 1; j0 < blocks; j0 += kSmallLoads) {   // the others' chunks, from the next workgroup's on
+    Raw8<In> raw[kSmallLoads];
+#pragma unroll
+    for (int u = 0; u < kSmallLoads; ++u)
+      if (j0 + u < blocks) {   // uniform
+        const int j = b + j0 + u < blocks ? b + j0 + u : b + j0 + u - blocks;
+        const int c = j * kSmallThreads + tid;
+        load(c < n ? c : 0, raw[u]);
+      }
+#pragma unroll
+    for (int u = 0; u < kSmallLoads; ++u)
+      if (j0 + u < blocks) widest(raw[u]);
+  }
+  widest(own);
   const float s = unit_scale(block_max(m, s_tmp), a.ratio, Codec<FMT>::QMAX, a.scale_f16 != 0);
   const float inv_s = 1.0f / s;
-  if (blockIdx.x > 0) {
-#pragma unroll
-    for (int j = 0; j < kSmallChunks; ++j) {
-      const int c = j * kSmallThreads + tid;
-      if (static_cast<int>(blockIdx.x) - 1 == j && c < n) {
-        float v[8];
-        raw[j].widen(v);
-        store_codes<FMT>(a.out.codes, c, v, inv_s);
-      }
-    }
-    return;
-  }
   const double sd = static_cast<double>(s);
   double e = 0.0;
-  uint32_t carry = 0;
+  if (c_own < n) {
+    uint32_t carry = 0;
+    float v[8];
+    own.widen(v);
 #pragma unroll
-  for (int j = 0; j < kSmallChunks; ++j)
-    if (j * kSmallThreads + tid < n) {
-      float v[8];
-      raw[j].widen(v);
-#pragma unroll
-      for (int i = 0; i < 8; i += 2) score2_f64<FMT>(e, v[i], v[i + 1], inv_s, sd, carry);
-    }
+    for (int i = 0; i < 8; i += 2) score2_f64<FMT>(e, v[i], v[i + 1], inv_s, sd, carry);
+    store_codes<FMT>(a.out.codes, c_own, v, inv_s);
+  }
   e = block_sum(e, s_sum);
+  if (tid >= 64) return;
+  if (blocks > 1) {   // uniform
+    uint64_t* const place = reinterpret_cast<uint64_t*>(a.sse);   // two words per workgroup
+    const auto leave = [&](int i, uint64_t w0, uint64_t w1) {
+      __hip_atomic_store(place + 2 * i, w0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      __hip_atomic_store(place + 2 * i + 1, w1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    };
+    const uint64_t bits = __builtin_bit_cast(uint64_t, e);
+    if (tid == 0) leave(b, bits, bits ^ nonce);
+    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "agent");
+    const int i = tid < blocks ? tid : 0;
+    const uint64_t w0 = __hip_atomic_load(place + 2 * i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    const uint64_t w1 = __hip_atomic_load(place + 2 * i + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (__ballot((w0 ^ w1) != nonce) != 0) return;   // uniform
+    if (tid < blocks) leave(tid, 0, 0);
+    e = wave_sum(tid < blocks ? __builtin_bit_cast(double, w0) : 0.0);
+  }
   if (tid == 0) write_unit(a, s, e);
+}
+
+// A number that no other call of the process has, mixed from a count that starts at the time: the bits of a
+// finite negative double.
+uint64_t next_nonce() {
+  static std::atomic<uint64_t> count{static_cast<uint64_t>(std::chrono::system_clock::now().time_since_epoch().count())};
+  uint64_t z = count.fetch_add(0x9E3779B97F4A7C15ull, std::memory_order_relaxed);
+  z = (z ^ (z >> 30)) * 0xBF58476D1CE4E5B9ull;
+  z = (z ^ (z >> 27)) * 0x94D049BB133111EBull;
+  z ^= z >> 31;
+  return (z | 1ull << 63) & ~(1ull << 62);
 }
 
 // ---- launches ----------------------------------------------------------------------------------------
@@ -421,9 +467,9 @@ template <typename In> int launch_pick(const TensorArgs& a, hipStream_t st) {
 }
 
 template <typename In, int FMT> int launch_quant_fmt(const TensorArgs& a, hipStream_t st) {
-  if (a.n_chunks <= kSmallThreads * kSmallChunks) {
-    const unsigned grid = 1u + static_cast<unsigned>((a.n_chunks + kSmallThreads - 1) / kSmallThreads);
-    hipLaunchKernelGGL((tensor_quant_small_kernel<In, FMT>), dim3(grid), dim3(kSmallThreads), 0, st, a);
+  if (a.n_chunks <= kSmallThreads * kSmallBlocks) {
+    const unsigned grid = static_cast<unsigned>((a.n_chunks + kSmallThreads - 1) / kSmallThreads);
+    hipLaunchKernelGGL((tensor_quant_small_kernel<In, FMT>), dim3(grid), dim3(kSmallThreads), 0, st, a, next_nonce());
     return hip_status(hipGetLastError());
   }
   const int rc = launch_max<In>(a, st);

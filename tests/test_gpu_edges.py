@@ -21,7 +21,7 @@ def _strided(rows, cols, pad, seed, dtype):
     return w[:, :cols]
 
 
-# one launch up to 65536 elements, then three; one chunk; rows that lie apart
+# one launch (one workgroup, several), then three; one chunk; rows that lie apart
 @pytest.mark.parametrize("rows,cols,pad", [(1, 8, 0), (8, 8192, 0), (8, 8200, 0), (3, 1000, 8), (67, 1000, 24), (1025, 2056, 0)])
 @pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
 def test_per_tensor_passes(mq, rows, cols, pad, dtype):  # noqa: F811

@@ -6,6 +6,7 @@ import torch
 
 import mofq_inputs as mi
 from oracle import mofq_oracle as orc
+from tests.gpu_util import ERR_RTOL, unpack_codes
 
 pytestmark = pytest.mark.gpu
 
@@ -84,3 +85,51 @@ def test_weight_activation_call_in_a_graph(mq, metric_name):
     res = mq.alloc_result(DEV, len(ws))
     replays_equal_eager(f"mofq_select_layers_wa ({metric_name})",
                         lambda s: mq.select_layers_wa(batch, CANDS8, metric, cfg, res, wsp, s), w_out + x_out, res)
+
+
+# one workgroup, the smallest and the largest number of them that meet in the scratch, and the first size of three
+# launches; 16-bit and 32-bit elements; rows that lie apart.  The tensor changes between the replays, so
+# that a sum left by the one before would show.
+@pytest.mark.parametrize("dtype,rows,cols,ld", [
+    (torch.bfloat16, 1, 8192, 8192), (torch.bfloat16, 1, 8200, 8200), (torch.bfloat16, 37, 1000, 1008), (torch.bfloat16, 16, 4096, 4096),
+    (torch.bfloat16, 9, 8192, 8192), (torch.float16, 40, 4096, 4096), (torch.bfloat16, 1, 163848, 163848), (torch.float32, 40, 4096, 4104), (torch.float32, 41, 4096, 4096)])
+@pytest.mark.parametrize("fmt", [orc.FP8_E4M3, orc.INT4])
+def test_small_tensor_quantization_in_a_graph(mq, dtype, rows, cols, ld, fmt):
+    print(f"[case] graph capture of mofq_quantize {rows}x{cols}/{ld} {dtype} format {fmt}", flush=True)
+    cfg = mq.Cfg(mq.PER_TENSOR, mi.clip_ratios(1))
+    base = torch.zeros(rows, ld, dtype=dtype, device=DEV)
+    x = base[:, :cols]
+    out = mq.alloc_qbuffers(rows, cols, 4 if fmt == orc.INT4 else 8, cfg, DEV)
+    err = torch.zeros(1, dtype=torch.float64, device=DEV)
+    wsp = torch.empty(mq.workspace_bytes(x, None, 1, mq.ERR_TENSOR, cfg), dtype=torch.uint8, device=DEV)
+
+    def check(seed, launch):
+        x.copy_(mi.llama_like_weight(rows, cols, seed=seed, dtype=dtype, device=DEV, outlier_frac=1e-3))
+        out.codes.zero_(), out.scales.zero_(), out.unit_err.zero_(), err.zero_()
+        torch.cuda.synchronize()
+        launch()
+        torch.cuda.synchronize()
+        ref = orc.quantize(mi.to_f32_numpy(x), fmt, orc.PER_TENSOR, mi.clip_ratios(1))
+        assert out.scales.item() == float(ref.scale[0])
+        assert (unpack_codes(out.codes, rows, cols, orc.bits(fmt)) == ref.codes).all()
+        assert abs(err.item() - ref.err) <= ERR_RTOL * ref.err and out.unit_err.item() == err.item()
+        return err.clone()
+
+    def run():
+        mq.quantize(x, fmt, cfg, out, err, wsp)
+
+    for i, fill in enumerate((0, 255, 63)):         # whatever the scratch holds
+        wsp.fill_(fill)
+        check(9100 + i, run)
+    eager = check(9000, run)
+    s = torch.cuda.Stream()
+    s.wait_stream(torch.cuda.current_stream())
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.stream(s):
+        with torch.cuda.graph(g, stream=s):
+            run()
+    for seed in (9000, 9001, 9000, 9002, 9000):
+        e = check(seed, g.replay)
+        assert seed != 9000 or torch.equal(e, eager)
+    check(9003, run)                                       # an eager call between replays, in the same scratch
+    assert torch.equal(check(9000, g.replay), eager)
