@@ -10,6 +10,8 @@
 // clamp, pick spacing, add/subtract rounding constant; then an fp64 residual and
 // an fp64 fused multiply-add into the error) is plain vector ALU work: with the
 // 100-candidate search the kernel is bound by the vector units, not by HBM.
+#include <algorithm>
+#include <cmath>
 #include <type_traits>
 
 #include "mofq_codes.h"
@@ -37,6 +39,7 @@ struct SweepArgs {
   int32_t emit_f8_as_bf16;
   uint16_t* emit_grid[kMaxFmt];   // per-channel single-candidate pair: grid values as bf16 (see SweepParams)
   AheadCodes ahead;
+  int32_t bisect;            // 4-bit formats: score candidates by bisection of the clip ratios, which descend
   float clip[MOFQ_MAX_CLIP];
 };
 
@@ -90,9 +93,20 @@ constexpr float kTinySum = 0x1p-80f;
 // Per-channel: one workgroup per row; the row lives in registers (CH chunks of 8
 // elements per thread, chunk j of thread t = elements [(j*THREADS + t)*8, +8)).
 //
-// Phase 1 scores every (format, candidate) in fp32; phase 2 re-scores in fp64 the
+// Phase 1 scores the (format, candidate) pairs in fp32; phase 2 re-scores in fp64 the
 // candidates that fp32 cannot separate from the best one and picks the first
 // smallest of those, which is the first smallest of all.
+//
+// Bisection (4-bit formats, bisect_clip): a candidate between two scored ones can be left out where it cannot be the
+// winner.  The error of a scale s is the smallest of |x - s g|^2 over all assignments g of levels.  Let s1 > s > s2, E(s)
+// below the smallest error T so far, and g its assignment: the parabola |x - t g|^2 has curvature |g|^2, is below T at
+// s and not below E1 and E2 at s1 and s2, so sqrt(E1 - T) + sqrt(E2 - T) < |g| (s1 - s2); and s |g| <= |x| + sqrt(T).  A
+// gap for which sqrt(E1 - T) + sqrt(E2 - T) > (|x| + sqrt(T)) (s1 - s2) / s2 is left alone.  E1 and E2 are taken 1e-5
+// smaller and T 1e-5 larger (fp32 sums), and T by 2^-18 of the energy besides: a decision on rounded numbers
+// assigns an element within 2^-22 of a boundary to the level beyond it, which adds up to 4 x^2 2^-22 to the error.
+// 8-bit formats gain nothing by it: their levels are so many that any gap between two ratios can hold anything.
+// Vector issue bounds it: layer selection, INT4 against E2M1, fp32: 4096 x 11008, 100 ratios 1145 -> 248 us; 3001 x 5000,
+// 50 ratios 246 -> 123.
 // ------------------------------------------------------------------------------
 template <typename In, int FA, int FB, int THREADS, int CH>
 __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(CH <= 4 ? 8 : 5))) void sweep_channel_kernel(const SweepArgs a) {
@@ -109,11 +123,12 @@ __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(CH <= 4
   __shared__ float s_tot[NF][MOFQ_MAX_CLIP];
   __shared__ float s_wmax[NW];
   __shared__ double s_wen[NW];
-  __shared__ float s_thr[NF];
   __shared__ int s_list[MAXL];                    // shortlisted (format, candidate) pairs
   __shared__ int s_nlist;
   __shared__ double s_p2[NW];
   __shared__ double s_val[MAXL];                  // fp64 error of the shortlisted pairs
+  __shared__ uint64_t s_done[NF][MOFQ_MAX_CLIP / 64];   // bisection: bit per scored candidate
+  __shared__ int s_new[NF];                             // candidates to score, in s_list at f * MOFQ_MAX_CLIP
 
   const int tid = threadIdx.x;
   const int lane = tid & 63;
@@ -171,57 +186,140 @@ __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(CH <= 4
     live[j] = (static_cast<int64_t>(j) * THREADS + wave * 64) * 8 < a.cols;
 
   uint32_t carry = 0;
-  // ---- phase 1: fp32 error of every candidate (nothing to filter with one candidate) --
-  for (int k = 0; k < K && K > 1; ++k) {
-    const float sA = u2f(__builtin_amdgcn_readfirstlane(f2u(s_scale[0][k])));
-    const float iA = u2f(__builtin_amdgcn_readfirstlane(f2u(s_inv[0][k])));
-    const float sB = u2f(__builtin_amdgcn_readfirstlane(f2u(s_scale[NF - 1][k])));
-    const float iB = u2f(__builtin_amdgcn_readfirstlane(f2u(s_inv[NF - 1][k])));
+  // ---- phase 1: fp32 error of the candidates (nothing to filter with one candidate) --
+  auto score = [&](auto with_a, auto with_b, int kA, int kB) {
+    constexpr bool A = decltype(with_a)::value, B = decltype(with_b)::value;
+    const float sA = u2f(__builtin_amdgcn_readfirstlane(f2u(s_scale[0][kA])));
+    const float iA = u2f(__builtin_amdgcn_readfirstlane(f2u(s_inv[0][kA])));
+    const float sB = u2f(__builtin_amdgcn_readfirstlane(f2u(s_scale[NF - 1][kB])));
+    const float iB = u2f(__builtin_amdgcn_readfirstlane(f2u(s_inv[NF - 1][kB])));
     float accA = 0.0f, accB = 0.0f;
 #pragma unroll
     for (int j = 0; j < CH; ++j) {
       if (live[j]) {
 #pragma unroll
         for (int i = 0; i < 8; i += 2) {
-          score2_f32<FA>(accA, x[j * 8 + i], x[j * 8 + i + 1], iA, sA, carry);
-          if constexpr (NF == 2) score2_f32<FBX>(accB, x[j * 8 + i], x[j * 8 + i + 1], iB, sB, carry);
+          if constexpr (A) score2_f32<FA>(accA, x[j * 8 + i], x[j * 8 + i + 1], iA, sA, carry);
+          if constexpr (B) score2_f32<FBX>(accB, x[j * 8 + i], x[j * 8 + i + 1], iB, sB, carry);
         }
       }
     }
-    accA = wave_sum_f32_hi(accA);
-    if constexpr (NF == 2) accB = wave_sum_f32_hi(accB);
+    if constexpr (A) accA = wave_sum_f32_hi(accA);
+    if constexpr (B) accB = wave_sum_f32_hi(accB);
     if (lane == 63) {
-      s_p1[wave][k][0] = accA;
-      if constexpr (NF == 2) s_p1[wave][k][1] = accB;
+      if constexpr (A) s_p1[wave][kA][0] = accA;
+      if constexpr (B) s_p1[wave][kB][NF - 1] = accB;
     }
-  }
-  __syncthreads();
-
-  for (int idx = tid; idx < NF * K; idx += THREADS) {
-    const int f = idx / K, k = idx - f * K;
+  };
+  using yes = std::true_type;
+  using no = std::false_type;
+  using second = std::integral_constant<bool, NF == 2>;
+  auto total = [&](int f, int k) {
     float t = 0.0f;
-    if (K > 1) {
 #pragma unroll
-      for (int r = 0; r < NW; ++r) t += s_p1[r][k][f];
+    for (int r = 0; r < NW; ++r) t += s_p1[r][k][f];
+    return t;
+  };
+  if (Codec<FA>::BITS == 4 && a.bisect) {   // uniform
+    if constexpr (Codec<FA>::BITS == 4) {
+      // Five candidates over the whole table, then round by round the middle of every gap between scored ones that can
+      // hold the winner; wave f % NW decides for format f.  (Seven or nine to begin with: fewer rounds, more candidates,
+      // 3 to 9 % slower with 100 ratios; gaps of two scored whole: 2 %.)
+      constexpr int START = 5;
+      for (int idx = tid; idx < NF * K; idx += THREADS) s_tot[idx / K][idx % K] = __builtin_inff();   // not scored
+      for (int f = 0; f < NF; ++f)
+        if (wave == f % NW) {
+          if (lane < 2) s_done[f][lane] = 0;
+          __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+          if (lane < START) {
+            const int k = lane * (K - 1) / (START - 1);
+            s_list[f * MOFQ_MAX_CLIP + lane] = k;
+            atomicOr(&s_done[f][k >> 6], 1ull << (k & 63));
+          }
+          if (lane == 0) s_new[f] = START;
+        }
+      const float root_en = static_cast<float>(__builtin_sqrt(en));
+      for (;;) {
+        __syncthreads();
+        const int nA = __builtin_amdgcn_readfirstlane(s_new[0]), nB = NF == 2 ? __builtin_amdgcn_readfirstlane(s_new[NF - 1]) : 0;
+        if (nA + nB == 0) break;   // every round before scored one candidate at least
+        const int n_both = nA < nB ? nA : nB;
+        auto at = [&](int f, int i) { return __builtin_amdgcn_readfirstlane(s_list[f * MOFQ_MAX_CLIP + i]); };
+        if constexpr (NF == 2) {
+          for (int i = 0; i < n_both; ++i) score(yes{}, yes{}, at(0, i), at(1, i));
+          for (int i = n_both; i < nB; ++i) score(no{}, yes{}, at(1, i), at(1, i));
+        }
+        for (int i = n_both; i < nA; ++i) score(yes{}, no{}, at(0, i), at(0, i));
+        __syncthreads();
+        for (int f = 0; f < NF; ++f)
+          if (wave == f % NW) {
+            const int n = f == 0 ? nA : nB;
+            for (int i = lane; i < n; i += 64) {
+              const int k = s_list[f * MOFQ_MAX_CLIP + i];
+              s_tot[f][k] = total(f, k);
+            }
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            float b = __builtin_inff();
+            for (int k = lane; k < K; k += 64) b = __builtin_fminf(b, s_tot[f][k]);
+            b = -wave_max(-b);
+            const bool sums = b >= kTinySum && b < __builtin_inff();   // else every candidate is scored
+            const float limit = __builtin_fmaf(root_en * root_en, 0x1p-18f, b * kShortlistFactor);
+            const float span = (root_en + __builtin_amdgcn_sqrtf(limit)) * (1.0f + 0x1p-10f);
+            const uint64_t done0 = s_done[f][0], done1 = s_done[f][1];
+            int n_new = 0;
+            for (int k0 = 0; k0 < K; k0 += 64) {
+              const int k = k0 + lane;
+              // the next scored candidate
+              const uint64_t low = k < 63 ? done0 >> (k + 1) : 0;
+              const uint64_t high = k < 64 ? done1 : (k < 127 ? done1 >> (k - 63) : 0);
+              const int next = low ? k + 1 + __builtin_ctzll(low) : (high ? (k < 64 ? 64 : k + 1) + __builtin_ctzll(high) : k);
+              bool look = false;
+              if ((((k < 64 ? done0 : done1) >> (k & 63)) & 1) && next > k + 1) {
+                const float s1 = s_scale[f][k], s2 = s_scale[f][next];
+                const float up = __builtin_fmaf(s_tot[f][k], 1.0f - 1.0e-5f, -limit), down = __builtin_fmaf(s_tot[f][next], 1.0f - 1.0e-5f, -limit);
+                const float roots = __builtin_amdgcn_sqrtf(__builtin_fmaxf(up, 0.0f)) + __builtin_amdgcn_sqrtf(__builtin_fmaxf(down, 0.0f));
+                look = !sums || s1 < s2 || !(roots > span * ((s1 - s2) / s2));
+              }
+              const uint64_t lanes = __builtin_amdgcn_ballot_w64(look);
+              const int mid = (k + next) >> 1;
+              if (look) {
+                s_list[f * MOFQ_MAX_CLIP + n_new + __builtin_popcountll(lanes & ((1ull << lane) - 1))] = mid;
+                atomicOr(&s_done[f][mid >> 6], 1ull << (mid & 63));
+              }
+              n_new += __builtin_popcountll(lanes);
+            }
+            if (lane == 0) s_new[f] = n_new;
+          }
+      }
     }
-    s_tot[f][k] = t;   // K == 1: zero, which shortlists the only candidate
+  } else {
+    for (int k = 0; k < K && K > 1; ++k) score(yes{}, second{}, k, k);
+    __syncthreads();
+    for (int idx = tid; idx < NF * K; idx += THREADS) {
+      const int f = idx / K, k = idx - f * K;
+      s_tot[f][k] = K > 1 ? total(f, k) : 0.0f;   // K == 1: zero, which shortlists the only candidate
+    }
+    __syncthreads();
   }
-  __syncthreads();
 
-  // ---- shortlist: candidates fp32 cannot tell from the best ----------------------
-  for (int f = wave; f < NF; f += NW) {
-    float m = __builtin_inff();
-    for (int k = lane; k < K; k += 64) m = __builtin_fminf(m, s_tot[f][k]);
-    m = -wave_max(-m);
-    if (lane == 0) s_thr[f] = (m >= kTinySum && m < __builtin_inff()) ? m * kShortlistFactor : __builtin_inff();
-  }
-  __syncthreads();
-  if (tid == 0) {
+  // ---- shortlist: candidates fp32 cannot tell from the best, in candidate order ----------------------
+  if (wave == 0) {
     int n = 0;
-    for (int f = 0; f < NF; ++f)
-      for (int k = 0; k < K; ++k)
-        if (s_tot[f][k] <= s_thr[f] || !(s_tot[f][k] == s_tot[f][k])) s_list[n++] = f * MOFQ_MAX_CLIP + k;
-    s_nlist = n;
+    for (int f = 0; f < NF; ++f) {
+      float m = __builtin_inff();
+      for (int k = lane; k < K; k += 64) m = __builtin_fminf(m, s_tot[f][k]);
+      m = -wave_max(-m);
+      const float thr = (m >= kTinySum && m < __builtin_inff()) ? m * kShortlistFactor : __builtin_inff();
+      for (int k0 = 0; k0 < K; k0 += 64) {
+        const int k = k0 + lane;
+        const float t = s_tot[f][k < K ? k : 0];
+        const bool in = k < K && !(t > thr);   // NaN too
+        const uint64_t lanes = __builtin_amdgcn_ballot_w64(in);
+        if (in) s_list[n + __builtin_popcountll(lanes & ((1ull << lane) - 1))] = f * MOFQ_MAX_CLIP + k;
+        n += __builtin_popcountll(lanes);
+      }
+    }
+    if (lane == 0) s_nlist = n;
   }
   __syncthreads();
   const int n_list = s_nlist;
@@ -967,6 +1065,18 @@ int launch_gran(const SweepParams& p, const SweepArgs& a, hipStream_t st) {
   return MOFQ_ERR_INVALID_ARG;
 }
 
+// From how many descending clip ratios on bisection scores a 4-bit format's candidates.  It scores 12 of 20, 17 of
+// 50, 19 of 100 of them, but in five dependent rounds, which a row of few elements per wave or a tensor of few workgroups
+// waits for.  Layer selection, us, fp32, all candidates / bisection: 4096 x 4096, 12: 88.8 / 87.4, 16: 105.9 / 96.2; 3001 x
+// 5000, 10: 78.4 / 78.3, 14: 94.5 / 87.9; 2000 x 1024, 28: 31.8 / 32.3, 32: 34.4 / 32.5; few rows: 512 x 8192, 16: 33.9 /
+// 34.2, 20: 38.5 / 37.4; 256 x 16384, 14: 33.6 / 34.5, 18: 38.2 / 37.1; 1000 x 600, 32: 26.0 / 26.9, 40: 30.0 / 29.7; 256 x
+// 1024, 40: 28.0 / 28.8.
+int bisect_clip(const SweepParams& p) {
+  if (p.gran != MOFQ_PER_CHANNEL) return MOFQ_MAX_CLIP + 1;
+  if (p.cols <= 2048) return p.rows >= 1024 ? 32 : 44;
+  return p.rows >= 1024 ? 12 : 18;
+}
+
 template <typename In>
 int launch_fmt(const SweepParams& p, const SweepArgs& a, hipStream_t st) {
   const int fa = p.fmt[0], fb = p.n_fmt == 2 ? p.fmt[1] : -1;
@@ -1019,7 +1129,11 @@ int launch_sweep(const SweepParams& p, hipStream_t st) {
     a.ahead = p.ahead;
   }
   a.units = mofq_num_units(p.rows, p.cols, p.gran, p.group);
-  for (int k = 0; k < p.n_clip; ++k) a.clip[k] = p.clip[k];
+  a.bisect = p.n_clip >= bisect_clip(p);
+  for (int k = 0; k < p.n_clip; ++k) {
+    a.clip[k] = p.clip[k];
+    if (!(p.clip[k] > 0.0f) || !std::isfinite(p.clip[k]) || (k > 0 && p.clip[k] > p.clip[k - 1])) a.bisect = 0;
+  }
   if (a.units <= 0) return MOFQ_ERR_INVALID_ARG;
   // same format twice in one launch is handled as two single launches by the caller
   switch (p.dtype) {

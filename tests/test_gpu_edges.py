@@ -178,6 +178,44 @@ def test_group_gaps_everywhere(mq, group, n_clip):  # noqa: F811
         check_tensor(mq, w, cands, orc.PER_GROUP, _descending("even", n_clip), group, label="group-gaps-everywhere")
 
 
+# rows whose candidates are scored by bisection of the ratios: one wave per row to sixteen, masks of one and two words,
+# even and uneven tables, long runs of equal errors, and a table that does not descend
+@pytest.mark.parametrize("dtype,cols,n_clip,kind,f16", [
+    (torch.float32, 264, 44, "even", False), (torch.float16, 600, 64, "pairs", True), (torch.bfloat16, 1000, 65, "ulps", False),
+    (torch.float32, 2056, 18, "even", False), (torch.float32, 4104, 128, "wide", False), (torch.float32, 5000, 100, "even", True),
+    (torch.float32, 8200, 63, "plateau", False), (torch.float32, 12296, 127, "ulps", False), (torch.float32, 16392, 20, "pairs", False),
+    (torch.float32, 24584, 90, "even", False), (torch.float32, 4104, 50, "ascending", False)])
+def test_row_bisection(mq, dtype, cols, n_clip, kind, f16):  # noqa: F811
+    w = _strided(13, cols, 8, n_clip, dtype)
+    g = torch.Generator(device=DEV).manual_seed(cols + n_clip)
+    w[0] = 0.0
+    w[1] = 0.75
+    w[2] = -w[2].abs()
+    w[3] = torch.exp2(torch.randint(-9, 3, (cols,), generator=g, device=DEV).float()).to(dtype)
+    w[4] = torch.randint(-7, 8, (cols,), generator=g, device=DEV).to(dtype)                # nearly on one grid
+    w[5] = (torch.randint(0, 8, (cols,), generator=g, device=DEV) + 0.5).to(dtype)         # on its boundaries
+    w[6, 3] = -6.0e4
+    w[7] = (w[7].float() * (2.0 ** -14 if dtype == torch.float16 else 2.0 ** 100)).to(dtype)    # squares beyond fp32
+    w[8] = (w[8].float() * (2.0 ** -9 if dtype == torch.float16 else 2.0 ** -115)).to(dtype)    # and below it
+    w[9, 5:] = 0.0
+    # the best ratio in many places of the table
+    for r in (10, 11, 12):
+        w[r] = (0.02 * torch.randn(cols, generator=g, device=DEV)).to(dtype)
+        w[r, 7] = 0.02 * (4.0 + 3.0 * (r - 10))
+    ratios = _descending("even", n_clip)[::-1] if kind == "ascending" else _descending(kind, n_clip)
+    for cands in (PAIR4, [orc.INT4], [orc.FP4_E2M1], [orc.FP4_E2M1_IEEE]):
+        check_tensor(mq, w, cands, orc.PER_CHANNEL, ratios, 0, f16, label=f"row-bisection {kind}")
+
+
+@pytest.mark.parametrize("cols,n_clip", [(520, 50), (4104, 100)])
+def test_row_bisection_everywhere(mq, cols, n_clip):  # noqa: F811
+    g = torch.Generator(device=DEV).manual_seed(n_clip)
+    w = 0.02 * torch.randn(200, cols, generator=g, device=DEV)
+    w[:, 5] = 0.02 * torch.linspace(3.5, 14.0, 200, device=DEV)
+    for cands in (PAIR4, [orc.FP4_E2M1]):
+        check_tensor(mq, w, cands, orc.PER_CHANNEL, _descending("even", n_clip), 0, label="row-bisection-everywhere")
+
+
 # ratios so small that a group's largest elements are 2^31 ulps of the first counted pattern and more: the last tables
 # of the rank kernel and, beyond them, the direct kernel (bf16: 128 patterns per binade)
 @pytest.mark.parametrize("lo_clip", [1e-5, 4e-6, 2e-6, 1e-6, 1e-7])
