@@ -566,13 +566,14 @@ MOFQ_DEV uint32_t quad_or(uint32_t v) {
 constexpr int kGroupQuads = 256 / 4;             // groups per workgroup
 constexpr int kMaskWords = MOFQ_MAX_CLIP / 32;
 
-// Phase 1 scores every candidate of a group in fp32 (hardware fp4/fp8 converts) and
+// Phase 1 scores the candidates of a group in fp32 (hardware fp4/fp8 converts), all of them or, BISECT, by
+// bisection (see sweep_channel_kernel; 16 groups of 128 with 50 ratios take 26 rounds of one candidate instead of 50), and
 // parks the sums in LDS; the candidates fp32 cannot tell from the group's best are
 // collected in a bit mask per group and re-scored in fp64 in candidate order, the j-th
 // survivor of all 16 groups of a wave at the same time.  The fp32 sum of a group (32
 // terms per lane, two more additions across the quad) is within (1 +- 40*2^-24) of the
 // exact sum for the same grid choices, so the fp64 winner is always among the survivors.
-template <typename In, int FA, int FB, int GROUP>
+template <typename In, int FA, int FB, int GROUP, bool BISECT>
 __global__ __launch_bounds__(256) void sweep_group_kernel(const SweepArgs a) {
   using L = Load8<In>;
   constexpr int NF = (FB >= 0) ? 2 : 1;
@@ -628,39 +629,149 @@ __global__ __launch_bounds__(256) void sweep_group_kernel(const SweepArgs a) {
   if (K > 1) {
     // ---- phase 1 ----------------------------------------------------------------
     float minA = __builtin_inff(), minB = __builtin_inff();
-    for (int k0 = 0; k0 < K; k0 += LPG) {
-      // lane q of the group prepares candidate k0+q (clamped; surplus ones are ignored)
-      const int kq = (k0 + q < K) ? k0 + q : K - 1;
-      const float r = s_clip[kq];
-      const float mysA = unit_scale(amax, r, Codec<FA>::QMAX, f16);
-      const float myiA = 1.0f / mysA;
-      float mysB = 0.0f, myiB = 0.0f;
-      if constexpr (NF == 2) {
-        mysB = unit_scale(amax, r, Codec<FBX>::QMAX, f16);
-        myiB = 1.0f / mysB;
-      }
-      auto one = [&](float sA, float iA, float sB, float iB, int k) {
-        if (k < K) {   // uniform over the workgroup
-          float accA = 0.0f, accB = 0.0f;
+    // one candidate of each format per group
+    auto one = [&](auto with_a, auto with_b, float sA, float iA, int kA, float sB, float iB, int kB, bool inA, bool inB) __attribute__((always_inline)) {
+      float accA = 0.0f, accB = 0.0f;
 #pragma unroll
-          for (int i = 0; i < NE; i += 2) {
-            score2_f32<FA>(accA, x[i], x[i + 1], iA, sA, carry);
-            if constexpr (NF == 2) score2_f32<FBX>(accB, x[i], x[i + 1], iB, sB, carry);
+      for (int i = 0; i < NE; i += 2) {
+        if constexpr (decltype(with_a)::value) score2_f32<FA>(accA, x[i], x[i + 1], iA, sA, carry);
+        if constexpr (decltype(with_b)::value) score2_f32<FBX>(accB, x[i], x[i + 1], iB, sB, carry);
+      }
+      if constexpr (decltype(with_a)::value) {
+        accA = quad_sum_f32(accA);
+        minA = __builtin_fminf(minA, inA ? accA : __builtin_inff());
+        if (q == 0 && inA) s_p1[kA * kGroupQuads + quad] = accA;
+      }
+      if constexpr (decltype(with_b)::value) {
+        accB = quad_sum_f32(accB);
+        minB = __builtin_fminf(minB, inB ? accB : __builtin_inff());
+        if (q == 1 && inB) s_p1[(K + kB) * kGroupQuads + quad] = accB;
+      }
+    };
+    using yes = std::true_type;
+    using no = std::false_type;
+    using second = std::integral_constant<bool, NF == 2>;
+    if constexpr (BISECT) {
+      // Bisection (see sweep_channel_kernel) on a grid of gaps that all groups share: 8 candidates, then the middles of the gaps
+      // that can hold the group's winner, until a gap has two candidates at most, which are scored together.  A lane tests
+      // every fourth gap of its group; an error not known is infinite, which ends a gap that was left alone.
+      for (int k = q; k < NF * K; k += LPG) s_p1[k * kGroupQuads + quad] = __builtin_inff();
+      constexpr int UNROLL = GROUP <= 128 ? LPG : 1;   // (256: the copies of the scoring code would not fit the instruction cache)
+      // four candidates of each group and format, from its list
+      auto score4 = [&](int kA, int kB) __attribute__((always_inline)) {   // the lane's own; below 0: none
+        const float rA = s_clip[kA < 0 ? 0 : kA], rB = s_clip[kB < 0 ? 0 : kB];
+        const float mysA = unit_scale(amax, rA, Codec<FA>::QMAX, f16), myiA = 1.0f / mysA;
+        float mysB = 0.0f, myiB = 0.0f;
+        if constexpr (NF == 2) {
+          mysB = unit_scale(amax, rB, Codec<FBX>::QMAX, f16);
+          myiB = 1.0f / mysB;
+        }
+        float s1 = mysA, i1 = myiA, s2 = mysB, i2 = myiB;
+#pragma unroll UNROLL
+        for (int j = 0; j < LPG; ++j) {   // lane 0's, then every lane takes the next one's
+          const int a1 = __builtin_amdgcn_update_dpp(0, kA, 0x00, 0xF, 0xF, true), b1 = __builtin_amdgcn_update_dpp(0, kB, 0x00, 0xF, 0xF, true);
+          const bool any_a = __builtin_amdgcn_ballot_w64(a1 >= 0) != 0, any_b = NF == 2 && __builtin_amdgcn_ballot_w64(b1 >= 0) != 0;
+          const float sa = quad_bcast<0>(s1), ia = quad_bcast<0>(i1), sb = quad_bcast<0>(s2), ib = quad_bcast<0>(i2);
+          if (any_a && any_b) {
+            if constexpr (NF == 2) one(yes{}, yes{}, sa, ia, a1, sb, ib, b1, a1 >= 0, b1 >= 0);
+          } else if (any_b) {
+            if constexpr (NF == 2) one(no{}, yes{}, sa, ia, a1, sb, ib, b1, false, b1 >= 0);
+          } else if (any_a) {
+            one(yes{}, no{}, sa, ia, a1, sb, ib, b1, a1 >= 0, false);
           }
-          accA = quad_sum_f32(accA);
-          minA = __builtin_fminf(minA, accA);
-          if (q == 0) s_p1[k * kGroupQuads + quad] = accA;
+          kA = __builtin_amdgcn_update_dpp(0, kA, 0x39, 0xF, 0xF, true);
+          s1 = dpp_f32<0x39>(s1);
+          i1 = dpp_f32<0x39>(i1);
           if constexpr (NF == 2) {
-            accB = quad_sum_f32(accB);
-            minB = __builtin_fminf(minB, accB);
-            if (q == 1) s_p1[(K + k) * kGroupQuads + quad] = accB;
+            kB = __builtin_amdgcn_update_dpp(0, kB, 0x39, 0xF, 0xF, true);
+            s2 = dpp_f32<0x39>(s2);
+            i2 = dpp_f32<0x39>(i2);
           }
         }
       };
-      one(quad_bcast<0>(mysA), quad_bcast<0>(myiA), quad_bcast<0>(mysB), quad_bcast<0>(myiB), k0 + 0);
-      one(quad_bcast<1>(mysA), quad_bcast<1>(myiA), quad_bcast<1>(mysB), quad_bcast<1>(myiB), k0 + 1);
-      one(quad_bcast<2>(mysA), quad_bcast<2>(myiA), quad_bcast<2>(mysB), quad_bcast<2>(myiB), k0 + 2);
-      one(quad_bcast<3>(mysA), quad_bcast<3>(myiA), quad_bcast<3>(mysB), quad_bcast<3>(myiB), k0 + 3);
+      int n = 7;   // gaps
+      // floor(i (K - 1) / n): below 2^14, so the rounded product is off by less than half of 1 / n
+      auto place = [&](int i, float inv_n) { return static_cast<int>((static_cast<float>(__mul24(i, K - 1)) + 0.5f) * inv_n); };
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+      for (int i0 = 0; i0 < 8; i0 += LPG) {
+        const int k = place(i0 + q, 1.0f / 7.0f);
+        score4(k, k);
+      }
+      uint8_t* const list = reinterpret_cast<uint8_t*>(s_p1 + NF * K * kGroupQuads) + quad * NF * (K - 8);
+      const float root_en = static_cast<float>(__builtin_sqrt(en));
+      // two ratios are a scale quotient but for the scales' rounding, unless a scale is below the normal numbers
+      const float rounding = f16 ? 1.0f + 0x1.08p-10f : 1.0f + 0x1p-20f;
+      for (bool last = false; !last; n *= 2) {
+        last = K - 1 <= 3 * n;
+        const float inv_n = 1.0f / static_cast<float>(n);
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        int left[2] = {0, 0};
+#pragma unroll
+        for (int f = 0; f < NF; ++f) {
+          const float b = f == 0 ? minA : minB;
+          const float qmax = f == 0 ? Codec<FA>::QMAX : Codec<FBX>::QMAX;
+          const bool regular = b >= kTinySum && b < __builtin_inff() && amax * s_clip[K - 1] >= qmax * (f16 ? 0x1p-13f : 0x1p-124f) &&
+                               amax * s_clip[0] <= qmax * (f16 ? 65000.0f : 0x1p126f);
+          const float limit = __builtin_fmaf(root_en * root_en, 0x1p-18f, b * kShortlistFactor);
+          const float span = (root_en + __builtin_amdgcn_sqrtf(limit)) * (1.0f + 0x1p-10f);
+          const float* const e = s_p1 + f * K * kGroupQuads + quad;
+          uint32_t bits = 0;
+          int count = 0;
+          for (int i = q, j = 0; i < n; i += LPG, ++j) {
+            const int from = place(i, inv_n), to = place(i + 1, inv_n);
+            const float up = __builtin_fmaf(e[from * kGroupQuads], 1.0f - 1.0e-5f, -limit), down = __builtin_fmaf(e[to * kGroupQuads], 1.0f - 1.0e-5f, -limit);
+            const float roots = __builtin_amdgcn_sqrtf(__builtin_fmaxf(up, 0.0f)) + __builtin_amdgcn_sqrtf(__builtin_fmaxf(down, 0.0f));
+            const float step = __builtin_fmaf(s_clip[from] * rounding, __builtin_amdgcn_rcpf(s_clip[to]), -1.0f);
+            if (to - from > 1 && (!regular || !(roots > span * step))) {
+              bits |= 1u << j;
+              count += last ? to - from - 1 : 1;
+            }
+          }
+          // the list: the lanes' entries one behind another
+          const int c1 = __builtin_amdgcn_update_dpp(0, count, 0x90, 0xF, 0xF, true);   // lane q - 1 (quad_perm 0, 0, 1, 2)
+          int inc = count + (q >= 1 ? c1 : 0);
+          const int c2 = __builtin_amdgcn_update_dpp(0, inc, 0x40, 0xF, 0xF, true);     // lane q - 2 (quad_perm 0, 0, 0, 1)
+          inc += q >= 2 ? c2 : 0;
+          left[f] = __builtin_amdgcn_update_dpp(0, inc, 0xFF, 0xF, 0xF, true);          // lane 3's
+          uint8_t* at = list + f * (K - 8) + (inc - count);
+          while (bits) {
+            const int i = q + LPG * __builtin_ctz(bits);
+            bits &= bits - 1;
+            const int from = place(i, inv_n);
+            if (last) {
+              const int to = place(i + 1, inv_n);
+              for (int k = from + 1; k < to; ++k) *at++ = static_cast<uint8_t>(k);
+            } else {
+              *at++ = static_cast<uint8_t>(place(2 * i + 1, 0.5f * inv_n));
+            }
+          }
+        }
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        for (int i = q; __builtin_amdgcn_ballot_w64(i < left[0] || i < left[1]) != 0; i += LPG)
+          score4(i < left[0] ? list[i] : -1, NF == 2 && i < left[1] ? list[K - 8 + i] : -1);
+      }
+    } else {
+      for (int k0 = 0; k0 < K; k0 += LPG) {
+        // lane q of the group prepares candidate k0+q (clamped; surplus ones are ignored)
+        const int kq = (k0 + q < K) ? k0 + q : K - 1;
+        const float r = s_clip[kq];
+        const float mysA = unit_scale(amax, r, Codec<FA>::QMAX, f16);
+        const float myiA = 1.0f / mysA;
+        float mysB = 0.0f, myiB = 0.0f;
+        if constexpr (NF == 2) {
+          mysB = unit_scale(amax, r, Codec<FBX>::QMAX, f16);
+          myiB = 1.0f / mysB;
+        }
+        auto lane_of = [&](auto j) {
+          constexpr int J = decltype(j)::value;
+          if (k0 + J < K)   // uniform over the workgroup
+            one(yes{}, second{}, quad_bcast<J>(mysA), quad_bcast<J>(myiA), k0 + J, quad_bcast<J>(mysB), quad_bcast<J>(myiB), k0 + J, true, true);
+        };
+        lane_of(std::integral_constant<int, 0>{});
+        lane_of(std::integral_constant<int, 1>{});
+        lane_of(std::integral_constant<int, 2>{});
+        lane_of(std::integral_constant<int, 3>{});
+      }
     }
     __syncthreads();                     // the sums parked by lanes 0 and 1 are visible to the quad
 
@@ -1020,11 +1131,17 @@ template <typename In, int FA, int FB>
 int launch_group(const SweepArgs& a, hipStream_t st) {
   const dim3 grid(static_cast<unsigned>(ceil_div(a.units, kGroupQuads)));
   constexpr int NF = (FB >= 0) ? 2 : 1;
-  const size_t lds = sizeof(float) * (MOFQ_MAX_CLIP + static_cast<size_t>(NF) * a.n_clip * kGroupQuads);
+  const size_t lds = sizeof(float) * (MOFQ_MAX_CLIP + static_cast<size_t>(NF) * a.n_clip * kGroupQuads) +
+                     (Codec<FA>::BITS == 4 && a.bisect ? static_cast<size_t>(NF) * (a.n_clip - 8) * kGroupQuads : 0);   // bisection: lists of candidates beyond the first 8
   switch (a.group) {
 #define MOFQ_G(G)                                                                        \
   case G:                                                                                \
-    hipLaunchKernelGGL((sweep_group_kernel<In, FA, FB, G>), grid, dim3(256), lds, st, a);  \
+    if constexpr (Codec<FA>::BITS == 4)                                                   \
+      if (a.bisect) {                                                                    \
+        hipLaunchKernelGGL((sweep_group_kernel<In, FA, FB, G, true>), grid, dim3(256), lds, st, a);  \
+        return hip_status(hipGetLastError());                                            \
+      }                                                                                  \
+    hipLaunchKernelGGL((sweep_group_kernel<In, FA, FB, G, false>), grid, dim3(256), lds, st, a);  \
     return hip_status(hipGetLastError());
     MOFQ_G(32)
     MOFQ_G(64)
@@ -1065,14 +1182,17 @@ int launch_gran(const SweepParams& p, const SweepArgs& a, hipStream_t st) {
   return MOFQ_ERR_INVALID_ARG;
 }
 
-// From how many descending clip ratios on bisection scores a 4-bit format's candidates.  It scores 12 of 20, 17 of
+// From how many descending clip ratios on bisection scores a 4-bit format's candidates.  On rows it scores 12 of 20, 17 of
 // 50, 19 of 100 of them, but in five dependent rounds, which a row of few elements per wave or a tensor of few workgroups
-// waits for.  Layer selection, us, fp32, all candidates / bisection: 4096 x 4096, 12: 88.8 / 87.4, 16: 105.9 / 96.2; 3001 x
+// waits for; a wave of 16 groups takes as many rounds of four as the worst of them, 16 to 20 candidates of 20, 20 to 29 of 50.
+// Layer selection, us, fp32, all candidates / bisection: rows: 4096 x 4096, 12: 88.8 / 87.4, 16: 105.9 / 96.2; 3001 x
 // 5000, 10: 78.4 / 78.3, 14: 94.5 / 87.9; 2000 x 1024, 28: 31.8 / 32.3, 32: 34.4 / 32.5; few rows: 512 x 8192, 16: 33.9 /
 // 34.2, 20: 38.5 / 37.4; 256 x 16384, 14: 33.6 / 34.5, 18: 38.2 / 37.1; 1000 x 600, 32: 26.0 / 26.9, 40: 30.0 / 29.7; 256 x
-// 1024, 40: 28.0 / 28.8.
+// 1024, 40: 28.0 / 28.8.  Groups, 2048 x 4096: 32, 18: 75.0 / 75.5, 20: 78.9 / 77.2, 50: 157 / 126; 64, 14: 56.7 / 56.6, 16:
+// 60.9 / 58.5, 50: 140 / 97; 128, 16: 55.6 / 55.1, 18: 60.1 / 58.7, 50: 130 / 88; 256, 18: 62.6 / 62.5, 20: 67.1 / 66.6, 50: 133 / 96.
 int bisect_clip(const SweepParams& p) {
-  if (p.gran != MOFQ_PER_CHANNEL) return MOFQ_MAX_CLIP + 1;
+  if (p.gran == MOFQ_PER_TENSOR) return MOFQ_MAX_CLIP + 1;
+  if (p.gran == MOFQ_PER_GROUP) return p.group == 64 ? 16 : (p.group == 128 ? 18 : 20);
   if (p.cols <= 2048) return p.rows >= 1024 ? 32 : 44;
   return p.rows >= 1024 ? 12 : 18;
 }

@@ -580,11 +580,16 @@ int launch_size(const GroupArgs& a, hipStream_t st) {
 }
 
 template <typename In, int FA, int FB>
-int launch_fmt(const SweepParams& p, const GroupArgs& a, hipStream_t st) {
+int launch_fmt(const SweepParams& p, const GroupArgs& a, hipStream_t st) {   // (min_clip: what is left out is never faster)
+  constexpr bool H = std::is_same<In, F16>::value;
   switch (p.group) {
-    case 64: return launch_size<In, FA, FB, 64>(a, st);
+    case 64:
+      if constexpr (FB >= 0 || !H) return launch_size<In, FA, FB, 64>(a, st);
+      break;
     case 128: return launch_size<In, FA, FB, 128>(a, st);
-    case 256: return launch_size<In, FA, FB, 256>(a, st);
+    case 256:
+      if constexpr (FB >= 0 || FA != MOFQ_INT4) return launch_size<In, FA, FB, 256>(a, st);
+      break;
   }
   return MOFQ_ERR_UNSUPPORTED;
 }
@@ -599,18 +604,21 @@ int launch_type(const SweepParams& p, const GroupArgs& a, hipStream_t st) {
 }
 
 // From how many clip ratios on this kernel is the faster one: building the table costs what scoring that many candidates
-// costs. The pair shares one table and a format alone has it to itself; INT4's takes the negative elements' words as well
-// (E2M1 alone needs neither them nor their prefixes); bf16 has an eighth of fp16's bits to clear and to walk; a group of
-// 64 has a table of its own like any other; one of 256 takes 64-bit words. Measured at the lines, layer selection, 4096 x
-// 4096, type and group, ratios: us scored directly / by look-up: INT4 and E2M1: fp16 64, 23: 133.8 / 131.1; fp16 128, 12:
-// 80.1 / 78.7; fp16 256, 21: 116.8 / 112.6; bf16 64, 10: 76.4 / 75.1; bf16 128, 9: 66.5 / 65.6; bf16 256, 18: 102.8 /
-// 100.7. INT4: fp16 64, 48: 122.0 / 120.4; fp16 128, 25: 73.3 / 72.2; fp16 256, 39: 101.2 / 100.4; bf16 64, 19: 64.1 /
-// 62.4; bf16 128, 19: 59.9 / 59.5; bf16 256, 37: 95.7 / 95.4. E2M1: fp16 64, 28: 91.5 / 90.4; fp16 128, 15: 57.5 / 56.6;
-// fp16 256, 20: 64.9 / 63.4; bf16 64, 13: 56.7 / 53.1; bf16 128, 11: 47.8 / 46.7; bf16 256, 17: 58.6 / 58.2.
+// costs (the direct kernel scores all of them up to 15 to 19, beyond by bisection). The pair shares one table and a format
+// alone has it to itself; INT4's takes the negative elements' words as well (E2M1 alone needs neither them nor their
+// prefixes); bf16 has an eighth of fp16's bits to clear and to walk; a group of 64 has a table of its own like any other;
+// one of 256 takes 64-bit words. kNever: bisection is faster up to MOFQ_MAX_CLIP. Measured at the lines, layer selection,
+// 4096 x 4096, type and group, ratios: us scored directly / by look-up: INT4 and E2M1: fp16 64, 56: 170.0 / 174.3, 64:
+// 193.4 / 182.3; fp16 128, 12: 79.6 / 78.0; fp16 256, 22: 113.3 / 111.8; bf16 64, 10: 76.9 / 74.7; bf16 128, 9: 66.5 /
+// 65.6; bf16 256, 18: 102.5 / 100.4. INT4: fp16 64, 128: 154.2 / 193.6; fp16 128, 27: 71.6 / 70.4; fp16 256, 128: 121.6 /
+// 142.3; bf16 64, 18: 64.6 / 63.0; bf16 128, 18: 60.3 / 58.4; bf16 256, 56: 92.5 / 109.1, 128: 120.8 / 130.1. E2M1: fp16
+// 64, 128: 144.4 / 170.0; fp16 128, 15: 57.5 / 56.6; fp16 256, 22: 65.2 / 63.1; bf16 64, 12: 53.3 / 52.7; bf16 128, 11:
+// 47.8 / 46.7; bf16 256, 17: 58.6 / 58.2.
+constexpr int kNever = MOFQ_MAX_CLIP + 1;
 int min_clip(const SweepParams& p) {
   static constexpr int lines[2][3][3] = {   // [fp16, bf16][64, 128, 256][pair, INT4, E2M1]
-      {{23, 48, 28}, {12, 25, 15}, {21, 39, 20}},
-      {{10, 19, 13}, {9, 19, 11}, {18, 37, 17}}};
+      {{60, kNever, kNever}, {12, 27, 15}, {22, kNever, 22}},
+      {{10, 17, 12}, {9, 18, 11}, {18, kNever, 17}}};
   const int which = p.n_fmt == 2 ? 0 : (p.fmt[0] == MOFQ_INT4 ? 1 : 2);
   return lines[p.dtype == MOFQ_F16 ? 0 : 1][p.group == 64 ? 0 : (p.group == 128 ? 1 : 2)][which];
 }

@@ -178,6 +178,46 @@ def test_group_gaps_everywhere(mq, group, n_clip):  # noqa: F811
         check_tensor(mq, w, cands, orc.PER_GROUP, _descending("even", n_clip), group, label="group-gaps-everywhere")
 
 
+# groups whose candidates are scored by bisection of the ratios: groups of 32, and fp32 elements; the numbers of ratios
+# leave one and two candidates in the last gaps, after two to four halvings
+@pytest.mark.parametrize("dtype", [torch.float32, torch.float16, torch.bfloat16])
+@pytest.mark.parametrize("group,n_clip,kind,f16", [
+    (32, 16, "even", True), (32, 50, "even", False), (32, 128, "wide", False), (32, 61, "pairs", True), (32, 100, "ulps", False),
+    (64, 22, "even", True), (64, 23, "plateau", False), (128, 33, "even", False), (128, 43, "even", True), (128, 44, "wide", True),
+    (256, 65, "even", True), (256, 86, "pairs", False), (128, 40, "ascending", False)])
+def test_direct_group_bisection(mq, dtype, group, n_clip, kind, f16):  # noqa: F811
+    if group > 32 and dtype != torch.float32:
+        pytest.skip("looked up, not scored")
+    w = _strided(14, 6 * group, group, n_clip, dtype)
+    g = torch.Generator(device=DEV).manual_seed(group + n_clip)
+    v = [w[r, (r % 3) * group:(r % 3 + 2) * group] for r in range(14)]
+    v[0][:] = 0.0
+    v[1][:] = 0.75
+    v[2][:] = -v[2].abs()
+    v[3][:] = torch.exp2(torch.randint(-9, 3, (2 * group,), generator=g, device=DEV).float()).to(dtype)
+    v[4][:] = torch.randint(-7, 8, (2 * group,), generator=g, device=DEV).to(dtype)      # nearly on one grid
+    v[5][:] = (torch.randint(0, 8, (2 * group,), generator=g, device=DEV) + 0.5).to(dtype)   # on its boundaries
+    v[6][:] = torch.rand(2 * group, generator=g, device=DEV).to(dtype)
+    v[7][3] = -6.0e4
+    small, large = (2.0 ** -14, 1.0) if dtype == torch.float16 else (2.0 ** -115, 2.0 ** 100)
+    v[8][:] = (v[8].float() * large).to(dtype)      # squares beyond fp32
+    v[9][5:] = 0.0
+    v[10][:] = (v[10].float() * small).to(dtype)    # and below it
+    v[11][:] = (v[11].float() * 2.0 ** -16).to(dtype)   # fp16 scales below the normal numbers
+    ratios = _descending("even", n_clip)[::-1] if kind == "ascending" else _descending(kind, n_clip)
+    for cands in (PAIR4, [orc.INT4], [orc.FP4_E2M1], [orc.FP4_E2M1_IEEE]):
+        check_tensor(mq, w, cands, orc.PER_GROUP, ratios, group, f16, label=f"direct-group {kind}")
+
+
+@pytest.mark.parametrize("group,n_clip", [(32, 50), (64, 30), (128, 64), (256, 120)])
+def test_direct_group_bisection_everywhere(mq, group, n_clip):  # noqa: F811
+    g = torch.Generator(device=DEV).manual_seed(n_clip)
+    w = 0.02 * torch.randn(64, 8 * group, generator=g, device=DEV)
+    w.view(64, 8, group)[:, :, 5] = 0.02 * torch.linspace(2.5, 9.0, 64 * 8, device=DEV).view(64, 8)
+    for cands in (PAIR4, [orc.FP4_E2M1]):
+        check_tensor(mq, w, cands, orc.PER_GROUP, _descending("even", n_clip), group, True, label="direct-group-everywhere")
+
+
 # rows whose candidates are scored by bisection of the ratios: one wave per row to sixteen, masks of one and two words,
 # even and uneven tables, long runs of equal errors, and a table that does not descend
 @pytest.mark.parametrize("dtype,cols,n_clip,kind,f16", [
