@@ -53,9 +53,9 @@ constexpr int kHistMaxTailBins = 2048;  // of INT4's negative elements
 
 // The histogram kernel for arguments with nbin > 0 (mofq_sweep_hist.hip).
 int launch_sweep_hist(const SweepParams& p, const SortedArgs& a, int64_t total_rows, hipStream_t st);
-// The one of bf16 rows (mofq_sweep_bf16.hip), and whether these histograms fit it.
-int launch_sweep_bf16(const SweepParams& p, const SortedArgs& a, int64_t total_rows, hipStream_t st);
-bool bf16_search_fits(const SweepParams& p, int nbin, int ntbin);
+// The one of bf16 rows and of 8-bit formats (mofq_sweep_bf16.hip), and whether these histograms fit it.
+int launch_sweep_pattern(const SweepParams& p, const SortedArgs& a, int64_t total_rows, hipStream_t st);
+bool pattern_search_fits(const SweepParams& p, int nbin, int ntbin);
 
 namespace {
 
@@ -181,6 +181,25 @@ template <typename In> MOFQ_DEV int exponent_of(int p) { const int e = p >> Patt
 typedef __attribute__((address_space(3))) uint32_t lds_u32;
 typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
 
+MOFQ_DEV uint32_t dot2(uint32_t a, uint32_t b, uint32_t c) {   // a.lo b.lo + a.hi b.hi + c
+  return __builtin_amdgcn_udot2(__builtin_bit_cast(u16x2, a), __builtin_bit_cast(u16x2, b), c, false);
+}
+
+// count and index-weighted count of eight counters, two per word.  JOINT: rows of up to 4096 elements, whose
+// weighted count stays below 7 * 2^12 < 2^15: one sum with the weights 2^15 + i (two instructions fewer).
+template <bool JOINT> MOFQ_DEV void count8(const u32x4 w, uint32_t& c, uint32_t& wsum) {
+  constexpr uint32_t base = JOINT ? 0x80008000u : 0u;
+  uint32_t s = 0;
+  c = 0;
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    if constexpr (!JOINT) c = dot2(w[j], 0x00010001u, c);
+    s = dot2(w[j], base + (static_cast<uint32_t>(2 * j) | (static_cast<uint32_t>(2 * j + 1) << 16)), s);
+  }
+  if constexpr (JOINT) c = s >> 15;
+  wsum = JOINT ? s & 0x7FFFu : s;
+}
+
 // One counter (16 bits, two per word) at LDS byte address base + byte_off (a multiple of 4) more: the low half
 // of the word for an even counter number, else the high half.
 MOFQ_DEV void count_at(uint32_t base, uint32_t byte_off, uint32_t parity16, uint32_t one = 1u) {
@@ -188,7 +207,7 @@ MOFQ_DEV void count_at(uint32_t base, uint32_t byte_off, uint32_t parity16, uint
   __hip_atomic_fetch_add((lds_u32*)static_cast<uintptr_t>(base + byte_off), one << (parity16 & 31u), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
 }
 
-// Counters of both halves of a word of counter numbers below 8192 (negative halves: none).
+// Counters of both halves of a word of counter numbers (negative halves: none).
 // `one`: 1 in a register of its own (the half-selecting shift takes no constant).
 MOFQ_DEV void count_pair(uint32_t base, i16x2 b2, uint32_t one) {
   uint32_t off2 = __builtin_bit_cast(uint32_t, b2 << static_cast<short>(1)) & 0xFFFCFFFCu;

@@ -1,4 +1,4 @@
-// Per-channel scale search on bf16 rows, 4-bit and 8-bit formats: the histogram search of
+// Per-channel scale search on bf16 rows, 4-bit and 8-bit formats, and on fp16 rows, 8-bit formats: the histogram search of
 // mofq_sweep_hist.hip with a prefix for every bit pattern.  A bf16 magnitude has 128 patterns per
 // binade, so the patterns between the smallest threshold of any candidate and the row's largest magnitude
 // are few (about 760 for INT4 / E2M1 over ratios in [0.5, 1], about 2600 for E4M3, whose
@@ -18,6 +18,13 @@
 // Measured, layer selection: INT8 against E4M3, 3001 x 5000, 50 ratios 277 -> 69.8 -> 66.4 us (the last step: prefixes over
 // the counters); 4096 x 11008, 100 ratios 1294 -> 141 us; INT4 against E2M1, 1237 x 5000, 100 ratios: 28.2 -> 25.6 us.
 //
+// fp16 rows (8-bit formats) have eight times the patterns, up to 20300 below the largest for E4M3: a prefix per group of
+// 8, packed alike, and a look-up adds the group's first counters, 36 instructions.  Counters and prefixes take 61 KB, so
+// two workgroups of 8 waves to a compute unit, and only the patterns that lie below the row's largest are summed up.
+// Bound by vector issue and, for few ratios, by the steps of a row with so few rows resident.  Layer selection, INT8
+// against E4M3, scored directly -> here: 3001 x 5000, 50 ratios 267 -> 159 us; 4096 x 11008, 100 ratios 1302 -> 280;
+// 300 x 11008, 60 ratios 133 -> 33.
+//
 // INT8's levels are spaced evenly; E4M3's evenly inside runs of 8 codes (a binade; the subnormals are the
 // first run): per run the level sums are d sum_i S_i and d^2 sum_i (2 (base + i) + 1) C_i with d the run's
 // spacing.  Boundaries beyond the largest level count everything (threshold infinity) and cancel against the
@@ -28,8 +35,8 @@ namespace mofq {
 
 namespace {
 
-constexpr int kThreads = 256, kNW = kThreads / 64;
-constexpr int kMaxBins = 4096, kMaxTailBins = 1024;
+constexpr int kMaxBins = 4096, kMaxTailBins = 1024;             // bf16
+constexpr int kMaxHalfBins = 24576, kMaxHalfTailBins = 2048;    // fp16
 constexpr int kRuns = 16;   // runs of 8 boundaries of an 8-bit format
 
 // Decision thresholds of the 8-bit formats' boundaries: level magnitude m_b or below <=> t <= thr; est: a
@@ -141,14 +148,60 @@ MOFQ_DEV void packed_prefixes(const uint32_t* counters, uint64_t* P, int lo, int
   if constexpr (NW > 1) __syncthreads();
 }
 
+// fp16: exclusive prefixes over groups of 8 counters, P[0 .. nbin / 8], packed alike.
+MOFQ_DEV uint64_t packed_group(const u32x4 w, int first, int e_first) {   // of the counters from pattern `first` on, a multiple of 8
+  uint32_t c, weighted, m, shift;
+  count8<false>(w, c, weighted);
+  mant_shift<F16>(static_cast<uint32_t>(first), e_first, m, shift);   // a group shares its exponent
+  return (static_cast<uint64_t>(__umul24(m, c) + weighted) << shift) + (static_cast<uint64_t>(c) << 48);
+}
+template <int NW, int GPMAX>
+MOFQ_DEV void group_prefixes(const uint32_t* counters, uint64_t* P, int lo, int nbin, uint64_t* s_wave) {
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int id = NW > 1 ? tid : lane;
+  const int ng = nbin >> 3, gp = (ng + NW * 64 - 1) / (NW * 64);   // groups per thread
+  const int e_lo = exponent_of<F16>(lo);
+  uint64_t v[GPMAX], acc = 0;
+#pragma unroll
+  for (int i = 0; i < GPMAX; ++i) {
+    const int g = id * gp + i;
+    v[i] = 0;
+    if (i < gp && g < ng) v[i] = packed_group(reinterpret_cast<const u32x4*>(counters)[g], lo + 8 * g, e_lo);
+    acc += v[i];
+  }
+  uint64_t inc = acc;
+#pragma unroll
+  for (int d = 1; d < 64; d <<= 1) {
+    const uint64_t o = __shfl_up(inc, d, 64);
+    if (lane >= d) inc += o;
+  }
+  uint64_t at = inc - acc;
+  if constexpr (NW > 1) {
+    if (lane == 63) s_wave[wave] = inc;
+    __syncthreads();
+    for (int w = 0; w < wave; ++w) at += s_wave[w];
+  }
+#pragma unroll
+  for (int i = 0; i < GPMAX; ++i) {
+    const int g = id * gp + i;
+    if (i < gp && g < ng) P[g] = at;
+    at += v[i];
+  }
+  if (id == NW * 64 - 1) P[ng] = at;
+  if constexpr (NW > 1) __syncthreads();
+}
+
 MOFQ_DEV double sum_of(uint64_t p) {   // the low 48 bits
   return __builtin_fma(static_cast<double>(static_cast<uint32_t>(p >> 32) & 0xFFFFu), 0x1p32, static_cast<double>(static_cast<uint32_t>(p)));
 }
 MOFQ_DEV uint32_t count_of(uint64_t p) { return static_cast<uint32_t>(p >> 48); }
 
-template <int FA, int FB, int CH>
-__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(CH <= 6 ? 5 : 4)))
-void sweep_bf16_kernel(const SortedArgs a) {
+template <typename In> constexpr int kThreadsOf = std::is_same<In, BF16>::value ? 256 : 512;
+template <typename In, int FA, int FB, int CH>
+__global__ __launch_bounds__(kThreadsOf<In>) __attribute__((amdgpu_waves_per_eu(std::is_same<In, BF16>::value && CH <= 6 ? 5 : 4)))
+void sweep_pattern_kernel(const SortedArgs a) {
+  constexpr bool HALF = std::is_same<In, F16>::value;
+  constexpr int kThreads = kThreadsOf<In>, kNW = kThreads / 64;
   constexpr int NF = (FB >= 0) ? 2 : 1;
   constexpr int FBX = (FB >= 0) ? FB : FA;
   constexpr bool TAIL_A = Codec<FA>::IS_INT, TAIL_B = (FB >= 0) && Codec<FBX>::IS_INT;   // the level one beyond the positive ones
@@ -157,11 +210,16 @@ void sweep_bf16_kernel(const SortedArgs a) {
 
   // dynamic LDS: [prefixes, before them the counters in the same place | of the negative elements | their counters]
   extern __shared__ __attribute__((aligned(16))) unsigned char s_dyn[];
-  const int nbin = a.nbin, ntbin = ANY_TAIL ? a.ntbin : 0;   // multiples of 8
+  int nbin = a.nbin;   // multiples of 8
+  const int ntbin = ANY_TAIL ? a.ntbin : 0;
+  // fp16: [prefixes of the groups | of the negative elements' | masks | counters | theirs | 16 bytes]
+  int n_rec = HALF ? nbin >> 3 : nbin;
+  const int n_trec = HALF ? ntbin >> 3 : ntbin;
   uint64_t* const P = reinterpret_cast<uint64_t*>(s_dyn);
-  uint64_t* const TP = P + (nbin + 1);
-  uint32_t* const counters = reinterpret_cast<uint32_t*>(s_dyn);
-  uint32_t* const tcounters = reinterpret_cast<uint32_t*>(TP + (ntbin + 1));
+  uint64_t* const TP = P + (n_rec + 1);
+  u32x4* const keep = reinterpret_cast<u32x4*>(s_dyn + (static_cast<uint32_t>(n_rec + n_trec + 2) * 8 + 15) / 16 * 16);   // fp16: of the first c of 8 counters
+  uint32_t* const counters = HALF ? reinterpret_cast<uint32_t*>(keep + 8) : reinterpret_cast<uint32_t*>(s_dyn);
+  uint32_t* const tcounters = HALF ? counters + nbin / 2 : reinterpret_cast<uint32_t*>(TP + (ntbin + 1));
 
   __shared__ RowSearch<NF, kNW> sh;
   __shared__ float s_wmax[kNW];
@@ -181,7 +239,7 @@ void sweep_bf16_kernel(const SortedArgs a) {
   const int n = static_cast<int>(a.cols);
 
   // ---- load the row, clear the counters; largest magnitude and energy ------------------------------
-  Raw8<BF16> raw[CH];
+  Raw8<In> raw[CH];
 #pragma unroll
   for (int j = 0; j < CH; ++j) {
     const int c = (j * kThreads + tid) * 8;
@@ -196,6 +254,10 @@ void sweep_bf16_kernel(const SortedArgs a) {
     const u32x4 zero = {0u, 0u, 0u, 0u};
     for (int i = tid; i < nbin / 8; i += kThreads) reinterpret_cast<u32x4*>(counters)[i] = zero;
     for (int i = tid; i < ntbin / 8; i += kThreads) reinterpret_cast<u32x4*>(tcounters)[i] = zero;
+    if (HALF && tid < 32) {   // word tid % 4 of the mask of the first tid / 4 counters
+      const int c = tid >> 2, i = tid & 3;
+      reinterpret_cast<uint32_t*>(keep)[tid] = (c >= 2 * i + 2) ? 0xFFFFFFFFu : ((c == 2 * i + 1) ? 0x0000FFFFu : 0u);
+    }
   }
   float amax = 0.0f;
   double en = 0.0;
@@ -230,9 +292,13 @@ void sweep_bf16_kernel(const SortedArgs a) {
 
   // ---- count the nbin patterns up to the largest magnitude's (a non-finite element lands in the last
   // counter: the row's error is non-finite anyway) ---------------------------------------------------
-  const int hmax = __builtin_amdgcn_readfirstlane(static_cast<int>(pattern_rtz<BF16>(__builtin_fminf(amax, 3.4028234e38f))));   // exact for a finite amax
+  const int hmax = __builtin_amdgcn_readfirstlane(static_cast<int>(pattern_rtz<In>(__builtin_fminf(amax, 3.4028234e38f))));   // exact for a finite amax
   const int lo = (((hmax + 1 - nbin) > 0 ? (hmax + 1 - nbin) : 0) + 7) & ~7;
   const int tlo = (((hmax + 1 - ntbin) > 0 ? (hmax + 1 - ntbin) : 0) + 7) & ~7;
+  if constexpr (HALF) {   // fp16 rarely has as many patterns below the largest
+    nbin = min(nbin, (hmax + 1 - lo + 7) & ~7);
+    n_rec = nbin >> 3;
+  }
   {
     const i16x2 lo2 = {static_cast<short>(lo), static_cast<short>(lo)};
     const i16x2 last2 = {static_cast<short>(nbin - 1), static_cast<short>(nbin - 1)};
@@ -257,17 +323,23 @@ void sweep_bf16_kernel(const SortedArgs a) {
   }
   __syncthreads();
 
-  if constexpr (ANY_TAIL)
-    if (wave == kNW - 1) {
-      if (ntbin <= 256) packed_prefixes<1, 2>(tcounters, TP, tlo, ntbin, s_wave);
-      else packed_prefixes<1, kMaxTailBins / 128>(tcounters, TP, tlo, ntbin, s_wave);
-    }
-  // (the short ones of the 4-bit formats in code of their own: 1237 x 5000 took 0.6 us more in the other's)
-  if (nbin <= 4 * kThreads) packed_prefixes<kNW, 2>(counters, P, lo, nbin, s_wave);
-  else packed_prefixes<kNW, kMaxBins / 2 / kThreads>(counters, P, lo, nbin, s_wave);
-  const uint64_t total = P[nbin];
-  const float v_lo = bits_to_float<BF16>(static_cast<uint32_t>(lo));
-  const double unit = static_cast<double>(bits_to_float<BF16>(static_cast<uint32_t>(lo) + 1) - v_lo);   // an ulp at lo
+  if constexpr (HALF) {
+    if constexpr (ANY_TAIL)
+      if (wave == kNW - 1) group_prefixes<1, kMaxHalfTailBins / 8 / 64>(tcounters, TP, tlo, ntbin, s_wave);
+    group_prefixes<kNW, kMaxHalfBins / 8 / kThreads>(counters, P, lo, nbin, s_wave);
+  } else {
+    if constexpr (ANY_TAIL)
+      if (wave == kNW - 1) {
+        if (ntbin <= 256) packed_prefixes<1, 2>(tcounters, TP, tlo, ntbin, s_wave);
+        else packed_prefixes<1, kMaxTailBins / 128>(tcounters, TP, tlo, ntbin, s_wave);
+      }
+    // (the short ones of the 4-bit formats in code of their own: 1237 x 5000 took 0.6 us more in the other's)
+    if (nbin <= 4 * kThreads) packed_prefixes<kNW, 2>(counters, P, lo, nbin, s_wave);
+    else packed_prefixes<kNW, kMaxBins / 2 / kThreads>(counters, P, lo, nbin, s_wave);
+  }
+  const uint64_t total = P[n_rec];
+  const float v_lo = bits_to_float<In>(static_cast<uint32_t>(lo));
+  const double unit = static_cast<double>(bits_to_float<In>(static_cast<uint32_t>(lo) + 1) - v_lo);   // an ulp at lo
   const double s_total = sum_of(total);
   const double c_total = static_cast<double>(count_of(total));
 
@@ -277,9 +349,22 @@ void sweep_bf16_kernel(const SortedArgs a) {
     // est * s rounded toward zero passes, one decision on the next tells.  Returns H - first + 1 as
     // a number of counters; negative numbers are large ones to the unsigned minimum.
     auto counters_below = [](float est, float thr, float s, float inv, int first) {
+      if constexpr (HALF) {
+        const int h = static_cast<int>(pattern_rtz<F16>(est * s));
+        return h + (1 - first) + (scaled<F16>(static_cast<uint32_t>(h + 1), inv) <= thr ? 1 : 0);
+      }
       const uint32_t x1 = f2u(est * s) + 0x10000u;
       const bool above = u2f(x1 & 0xFFFF0000u) * inv <= thr;
       return static_cast<int>(x1 >> 16) - first + (above ? 1 : 0);
+    };
+    // count and sum of the elements in the first n1 counters
+    auto first_counters = [&](const uint64_t* R, const uint32_t* cells, int first, uint32_t n1) {
+      if constexpr (HALF) {
+        const uint32_t g = n1 >> 3;
+        return R[g] + packed_group(reinterpret_cast<const u32x4*>(cells)[g] & keep[n1 & 7], first + 8 * static_cast<int>(g), exponent_of<F16>(first));
+      } else {
+        return R[n1];
+      }
     };
     const int chunks = (K + 63) >> 6;
     // few units: the runs of an 8-bit format are dealt to all waves, whose partial sums meet in LDS
@@ -291,9 +376,9 @@ void sweep_bf16_kernel(const SortedArgs a) {
       // negative elements beyond the last positive level's upper boundary sit one level further
       const int n1 = counters_below(est, thr, s, inv, tlo);
       bad |= n1 < 0;
-      const uint64_t above = TP[ntbin] - TP[min(static_cast<uint32_t>(n1), static_cast<uint32_t>(ntbin))];
-      const float v_tlo = bits_to_float<BF16>(static_cast<uint32_t>(tlo));
-      ca_tail = sum_of(above) * static_cast<double>(bits_to_float<BF16>(static_cast<uint32_t>(tlo) + 1) - v_tlo);
+      const uint64_t above = TP[n_trec] - first_counters(TP, tcounters, tlo, min(static_cast<uint32_t>(n1), static_cast<uint32_t>(ntbin)));
+      const float v_tlo = bits_to_float<In>(static_cast<uint32_t>(tlo));
+      ca_tail = sum_of(above) * static_cast<double>(bits_to_float<In>(static_cast<uint32_t>(tlo) + 1) - v_tlo);
       cb_tail = static_cast<int>(count_of(above)) * (2 * first_level + 1);
     };
     auto finish = [&](const int f, const int k, float s, double last) {
@@ -323,7 +408,7 @@ void sweep_bf16_kernel(const SortedArgs a) {
           const int n1 = counters_below(t.b[r][i].est, t.b[r][i].thr, s, inv, lo);
           // the smallest threshold: nothing uncounted above it, and no subnormal product (too coarse an estimate)
           if (i == 0 && r == 0) bad = n1 < 0 || !(t.b[0][0].est * s >= 0x1p-126f);
-          const uint64_t p = P[min(static_cast<uint32_t>(n1), static_cast<uint32_t>(nbin))];
+          const uint64_t p = first_counters(P, counters, lo, min(static_cast<uint32_t>(n1), static_cast<uint32_t>(nbin)));
           sums += p;      // (the counts overflow out of the word)
           ib += __mul24(static_cast<int>(count_of(p)), base2 + 2 * i);
         }
@@ -347,7 +432,7 @@ void sweep_bf16_kernel(const SortedArgs a) {
       for (int q = 0; q < 7; ++q) {
         const int n1 = counters_below(a.thr_est[f][q], a.thr[f][q], s, inv, lo);
         if (q == 0) bad = n1 < 0;
-        const uint64_t p = P[min(static_cast<uint32_t>(n1), static_cast<uint32_t>(nbin))];
+        const uint64_t p = first_counters(P, counters, lo, min(static_cast<uint32_t>(n1), static_cast<uint32_t>(nbin)));
         A = __builtin_fma(sum_of(p), a.dgd[f][q], A);
         cb4 = __mul24(static_cast<int>(count_of(p)), a.dg2q[f][q]) + cb4;
       }
@@ -389,50 +474,69 @@ void sweep_bf16_kernel(const SortedArgs a) {
   __syncthreads();
 
   // ---- winners (the re-scored values lie over the prefixes, which are no longer needed), codes --------
-  finish_row<BF16, FA, FB, kThreads, CH, true>(sh, reinterpret_cast<double*>(P), src, n, K, en, unit * s_total, a.g_absmax, T.rec, row);
-  if (T.ahead.codes) emit_row_ahead<BF16, FA, FB, kThreads, CH>(sh, T.ahead, tally, src, n, row);   // uniform
+  finish_row<In, FA, FB, kThreads, CH, true>(sh, reinterpret_cast<double*>(P), src, n, K, en, unit * s_total, a.g_absmax, T.rec, row);
+  if (T.ahead.codes) emit_row_ahead<In, FA, FB, kThreads, CH>(sh, T.ahead, tally, src, n, row);   // uniform
 }
 
-size_t lds_bytes(const SortedArgs& a) {
+template <typename In> size_t lds_bytes(const SortedArgs& a) {
+  if (std::is_same<In, F16>::value) return (static_cast<size_t>(a.nbin / 8 + a.ntbin / 8 + 2) * 8 + 15) / 16 * 16 + 128 + 2 * static_cast<size_t>(a.nbin + a.ntbin) + 16;
   const size_t prefixes = std::max<size_t>(8 * static_cast<size_t>(a.nbin + 1 + a.ntbin + 1), 2 * MOFQ_MAX_CLIP * sizeof(double));
   return prefixes + 2 * static_cast<size_t>(a.ntbin);
 }
 
-template <int FA, int FB>
+template <typename In, int FA, int FB>
 int launch_shape(const SortedArgs& a, int64_t total_rows, hipStream_t st) {
+  constexpr int THREADS = kThreadsOf<In>;
   const dim3 grid(static_cast<unsigned>(total_rows));
   const int64_t chunks = a.cols / 8;
-#define MOFQ_BF16(CH)                                                                          \
-  if (chunks <= kThreads * (CH)) {                                                              \
-    hipLaunchKernelGGL((sweep_bf16_kernel<FA, FB, CH>), grid, dim3(kThreads), lds_bytes(a), st, a); \
-    return hip_status(hipGetLastError());                                                      \
+#define MOFQ_PATTERN(CH)                                                                        \
+  if (chunks <= THREADS * (CH)) {                                                               \
+    hipLaunchKernelGGL((sweep_pattern_kernel<In, FA, FB, CH>), grid, dim3(THREADS), lds_bytes<In>(a), st, a); \
+    return hip_status(hipGetLastError());                                                       \
   }
-  MOFQ_BF16(1)   //  2048 columns
-  MOFQ_BF16(2)   //  4096
-  MOFQ_BF16(3)   //  6144
-  MOFQ_BF16(4)   //  8192
-  MOFQ_BF16(6)   // 12288
-  MOFQ_BF16(12)  // 24576
-#undef MOFQ_BF16
+  MOFQ_PATTERN(1)   //  2048 columns of bf16, 4096 of fp16
+  MOFQ_PATTERN(2)   //  4096, 8192
+  MOFQ_PATTERN(3)   //  6144, 12288
+  MOFQ_PATTERN(4)   //  8192, 16384
+  if constexpr (std::is_same<In, BF16>::value) {
+    MOFQ_PATTERN(6)   // 12288
+    MOFQ_PATTERN(12)  // 24576
+  }
+#undef MOFQ_PATTERN
   return MOFQ_ERR_UNSUPPORTED;
 }
 
 }  // namespace
 
-// The packed prefixes hold it: sums below 2^45 units (an element is below 2^(8 + binades); eight prefixes
-// are added up in 48 bits); LDS for three workgroups; room for the partial sums of a divided search.
-bool bf16_search_fits(const SweepParams& p, int nbin, int ntbin) {
+// The packed prefixes hold it: sums below 2^45 units (an element is below 2^(1 + mantissa bits + binades); eight prefixes
+// are added up in 48 bits); LDS for three workgroups (fp16: two); room for the partial sums of a divided search.
+bool pattern_search_fits(const SweepParams& p, int nbin, int ntbin) {
+  const bool eight = p.fmt[0] == MOFQ_INT8 || p.fmt[0] == MOFQ_FP8_E4M3;
+  if (p.dtype == MOFQ_F16) {
+    if (!eight || nbin < 4096 || nbin > kMaxHalfBins || ntbin > kMaxHalfTailBins || p.cols > 16384) return false;
+    const int span = (std::max(nbin, ntbin) + 1023) / 1024;
+    return (p.cols << (11 + span)) <= (int64_t{1} << 45);
+  }
   if (p.dtype != MOFQ_BF16 || nbin <= 0 || nbin > kMaxBins || ntbin > kMaxTailBins) return false;
   const int span = (std::max(nbin, ntbin) + 127) / 128;
-  if ((p.fmt[0] == MOFQ_INT8 || p.fmt[0] == MOFQ_FP8_E4M3) && nbin < 512) return false;
+  if (eight && nbin < 512) return false;
   return span <= 22 && (p.cols << (8 + span)) <= (int64_t{1} << 45) && p.cols <= 24576;
 }
 
-int launch_sweep_bf16(const SweepParams& p, const SortedArgs& a, int64_t total_rows, hipStream_t st) {
-  if (!bf16_search_fits(p, a.nbin, a.ntbin)) return MOFQ_ERR_UNSUPPORTED;
+int launch_sweep_pattern(const SweepParams& p, const SortedArgs& a, int64_t total_rows, hipStream_t st) {
+  if (!pattern_search_fits(p, a.nbin, a.ntbin)) return MOFQ_ERR_UNSUPPORTED;
   const int fa = p.fmt[0], fb = p.n_fmt == 2 ? p.fmt[1] : -1;
+  if (p.dtype == MOFQ_F16) {
 #define MOFQ_F(A, B) \
-  if (fa == (A) && fb == (B)) return launch_shape<A, B>(a, total_rows, st);
+  if (fa == (A) && fb == (B)) return launch_shape<F16, A, B>(a, total_rows, st);
+    MOFQ_F(MOFQ_INT8, MOFQ_FP8_E4M3)
+    MOFQ_F(MOFQ_INT8, -1)
+    MOFQ_F(MOFQ_FP8_E4M3, -1)
+#undef MOFQ_F
+    return MOFQ_ERR_UNSUPPORTED;
+  }
+#define MOFQ_F(A, B) \
+  if (fa == (A) && fb == (B)) return launch_shape<BF16, A, B>(a, total_rows, st);
   MOFQ_F(MOFQ_INT4, MOFQ_FP4_E2M1)
   MOFQ_F(MOFQ_INT4, -1)
   MOFQ_F(MOFQ_FP4_E2M1, -1)

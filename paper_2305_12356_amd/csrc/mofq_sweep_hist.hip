@@ -36,10 +36,6 @@ namespace mofq {
 
 namespace {
 
-MOFQ_DEV uint32_t dot2(uint32_t a, uint32_t b, uint32_t c) {   // a.lo b.lo + a.hi b.hi + c
-  return __builtin_amdgcn_udot2(__builtin_bit_cast(u16x2, a), __builtin_bit_cast(u16x2, b), c, false);
-}
-
 // ---- prefixes -----------------------------------------------------------------------------
 // Exclusive prefix of count and magnitude sum per group of 8 counters, one record per group, the
 // totals in record ng.  A group's patterns share the exponent: pattern lo + 8 g + i has the magnitude
@@ -53,21 +49,6 @@ struct Wide {
   double sum;
   uint32_t cnt, unused;
 };
-
-// count and index-weighted count of eight counters, two per word.  JOINT: rows of up to 4096 elements, whose
-// weighted count stays below 7 * 2^12 < 2^15: one sum with the weights 2^15 + i (two instructions fewer).
-template <bool JOINT> MOFQ_DEV void count8(const u32x4 w, uint32_t& c, uint32_t& wsum) {
-  constexpr uint32_t base = JOINT ? 0x80008000u : 0u;
-  uint32_t s = 0;
-  c = 0;
-#pragma unroll
-  for (int j = 0; j < 4; ++j) {
-    if constexpr (!JOINT) c = dot2(w[j], 0x00010001u, c);
-    s = dot2(w[j], base + (static_cast<uint32_t>(2 * j) | (static_cast<uint32_t>(2 * j + 1) << 16)), s);
-  }
-  if constexpr (JOINT) c = s >> 15;
-  wsum = JOINT ? s & 0x7FFFu : s;
-}
 
 // Count and magnitude sum of the elements in the histogram's first n1 counters, 0 <= n1 <= nbin:
 // the record of group n1 / 8 plus the first n1 % 8 counters of that group (n1 = nbin reads the 16
@@ -439,7 +420,7 @@ int launch_hist_sums(const SortedArgs& a, int64_t total_rows, hipStream_t st) {
 
 int launch_sweep_hist(const SweepParams& p, const SortedArgs& a, int64_t total_rows, hipStream_t st) {
   if (a.nbin <= 0 || (p.dtype != MOFQ_F16 && p.dtype != MOFQ_BF16)) return MOFQ_ERR_UNSUPPORTED;
-  if (bf16_search_fits(p, a.nbin, a.ntbin)) return launch_sweep_bf16(p, a, total_rows, st);
+  if (pattern_search_fits(p, a.nbin, a.ntbin)) return launch_sweep_pattern(p, a, total_rows, st);
   const int fa = p.fmt[0], fb = p.n_fmt == 2 ? p.fmt[1] : -1;
   const bool h = p.dtype == MOFQ_F16;
   if (fa == MOFQ_INT4 && fb == MOFQ_FP4_E2M1)

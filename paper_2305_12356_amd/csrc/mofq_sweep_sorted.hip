@@ -665,7 +665,7 @@ template <typename In>
 int launch_fmt(const SweepParams& p, const SortedArgs& a, int64_t total_rows, hipStream_t st) {
   const int fa = p.fmt[0], fb = p.n_fmt == 2 ? p.fmt[1] : -1;
   const bool hist = a.nbin > 0;
-  if (eight_bit(p)) return hist ? launch_sweep_bf16(p, a, total_rows, st) : MOFQ_ERR_UNSUPPORTED;
+  if (eight_bit(p)) return hist ? launch_sweep_pattern(p, a, total_rows, st) : MOFQ_ERR_UNSUPPORTED;
   if (fa == MOFQ_INT4 && fb == MOFQ_FP4_E2M1)
     return hist ? launch_sweep_hist(p, a, total_rows, st) : launch_shape<In, MOFQ_INT4, MOFQ_FP4_E2M1>(a, total_rows, st);
   if (fa == MOFQ_INT4 && fb == -1)
@@ -693,8 +693,7 @@ void hist_sizes(const SweepParams& p, SortedArgs& a) {
     nbin = std::max(nbin, hist_bins(qmax / (static_cast<double>(a.thr[f][0]) * r_min), ppb));
     if (integer) ntbin = std::max(16, hist_bins(qmax / (static_cast<double>(a.thr[f][7]) * r_min), ppb));
   }
-  if (nbin > kHistMaxBins || ntbin > kHistMaxTailBins) return;
-  if (eight_bit(p) && !bf16_search_fits(p, nbin, ntbin)) return;
+  if (eight_bit(p) ? !pattern_search_fits(p, nbin, ntbin) : nbin > kHistMaxBins || ntbin > kHistMaxTailBins) return;
   a.nbin = nbin;
   a.ntbin = ntbin;
 }
@@ -708,13 +707,20 @@ bool in_domain(const SweepParams& p) {
   if (p.gran != MOFQ_PER_CHANNEL || (p.dtype != MOFQ_F16 && p.dtype != MOFQ_BF16)) return false;
   if (p.n_clip < 8 || p.cols < 1024 || p.cols > 24576) return false;
   if (eight_bit(p)) {
-    // Only bf16 rows have few enough patterns. The histogram costs a row much the same whatever the number of
-    // candidates up to 64, scoring them costs their pairs with its elements. Measured at the line, layer selection of
+    // The histogram costs a row much the same whatever the number of candidates up to 64 and again beyond, scoring them
+    // costs their pairs with its elements. (The number of rows must not enter: tensors of one row length share a launch.)
+    // bf16, measured at the line, layer selection of
     // 4096 rows, us, directly / by histogram: the pair, 1024 columns x 36 ratios 72 / 66, 2048 x 18 70 / 69, 4096 x 9
     // 78 / 80, 5120 x 8 88 / 89; INT8, 1536 x 32 46 / 43, 2048 x 24 45 / 45, 4096 x 14 56 / 56, 5120 x 12 62 / 61;
     // E4M3, 1536 x 28 50 / 49, 2048 x 22 52 / 50, 4096 x 11 59 / 59, 5120 x 9 63 / 64.
-    const int64_t line = p.n_fmt == 2 ? 36864 : (p.fmt[0] == MOFQ_INT8 ? 53248 : 45056);
-    if (p.dtype != MOFQ_BF16 || p.cols * p.n_clip < line) return false;
+    // fp16 has eight times the patterns, in groups. 2048 rows: the pair, 2048 x 64 101 / 92, 4096 x 30 93 / 85, 5000 x 24
+    // 99 / 108, 8192 x 16 107 / 96, 11008 x 12 117 / 112, 1024 x 100 91 / 130; INT8, 2048 x 64 52 / 57, 4096 x 30 47 /
+    // 59, 5000 x 24 52 / 65, 8192 x 20 65 / 69, 11008 x 16 74 / 80; E4M3, 2048 x 64 64 / 65, 4096 x 30 59 / 55, 5000 x 24
+    // 64 / 80, 8192 x 20 81 / 66, 11008 x 12 76 / 81.
+    const bool half = p.dtype == MOFQ_F16, more = p.n_clip > 64;
+    const int64_t line = half ? (p.n_fmt == 2 ? (more ? 180000 : 140000) : (p.fmt[0] == MOFQ_INT8 ? 200000 : (more ? 180000 : 165000)))
+                              : (p.n_fmt == 2 ? 36864 : (p.fmt[0] == MOFQ_INT8 ? 53248 : 45056));
+    if (p.cols * p.n_clip < line) return false;
     return p.n_fmt == 1 || (p.fmt[0] == MOFQ_INT8 && p.fmt[1] == MOFQ_FP8_E4M3);
   }
   for (int f = 0; f < p.n_fmt; ++f)

@@ -178,16 +178,47 @@ def test_group_gaps_everywhere(mq, group, n_clip):  # noqa: F811
         check_tensor(mq, w, cands, orc.PER_GROUP, _descending("even", n_clip), group, label="group-gaps-everywhere")
 
 
-# groups whose candidates are scored by bisection of the ratios: groups of 32, and fp32 elements; the numbers of ratios
-# leave one and two candidates in the last gaps, after two to four halvings
+# fp16 rows and 8-bit formats, looked up by groups of patterns: one to four chunks per thread, one and two groups of 64
+# candidates, tables as far as they reach and, in the last line, beyond (scored directly)
+@pytest.mark.parametrize("cols,n_clip,lo_clip,f16", [
+    (2048, 88, 0.5, True), (4096, 49, 0.7, False), (4104, 128, 0.5, False), (5000, 64, 0.3, True), (8200, 25, 0.5, False),
+    (11008, 65, 0.6, False), (12296, 17, 0.5, True), (16384, 13, 0.5, False), (8192, 25, 0.26, False), (8192, 40, 0.02, False)])
+def test_half_pattern_groups(mq, cols, n_clip, lo_clip, f16):  # noqa: F811
+    w = _strided(15, cols, 8, cols, torch.float16)
+    g = torch.Generator(device=DEV).manual_seed(cols)
+    w[1] = 0.0
+    w[2] = 0.75
+    w[3] = torch.exp2(torch.randint(-24, 3, (cols,), generator=g, device=DEV).float()).to(torch.float16) * w[3].sign()
+    w[4] = (w[4].float() * 2.0 ** -14).to(torch.float16)      # few patterns below the largest
+    w[5] = (w[5].float() * 2.0 ** -19).to(torch.float16)
+    w[6] = torch.where(w[6] > 0, w[6], -w[6] * 3)
+    w[7, 3] = -6e4
+    w[8] = torch.randint(-127, 128, (cols,), generator=g, device=DEV).to(torch.float16)
+    w[9] = (torch.randint(0, 128, (cols,), generator=g, device=DEV) + 0.5).to(torch.float16)
+    w[10] = -w[10].abs()
+    w[11, 9:] = 0.0
+    w[12] = torch.rand(cols, generator=g, device=DEV).to(torch.float16)
+    w[13] = torch.randint(0, 0x7BFF, (cols,), generator=g, device=DEV).to(torch.int16).view(torch.float16)   # every pattern
+    ratios = [lo_clip + (1.0 - lo_clip) * (i + 1) / n_clip for i in range(n_clip)]
+    for cands in (PAIR8[::-1], PAIR8, [orc.INT8], [orc.FP8_E4M3]):
+        check_tensor(mq, w, cands, orc.PER_CHANNEL, ratios, f16=f16, label="half-groups")
+
+
+# enough rows that the search writes the codes itself
+def test_half_pattern_groups_write_codes(mq):  # noqa: F811
+    w = _strided(8200, 4096, 0, 3, torch.float16)
+    w[:50] = (w[:50].float().sign() * 0.02).to(torch.float16)
+    check_tensor(mq, w, PAIR8, orc.PER_CHANNEL, mi.clip_ratios(35), label="half-groups-ahead")
+
+
+# groups whose candidates are scored by bisection of the ratios: groups of 32, and fp32 elements (16-bit ones are looked up,
+# but for some formats alone); the numbers of ratios leave one and two candidates in the last gaps, after two to four halvings
 @pytest.mark.parametrize("dtype", [torch.float32, torch.float16, torch.bfloat16])
 @pytest.mark.parametrize("group,n_clip,kind,f16", [
     (32, 16, "even", True), (32, 50, "even", False), (32, 128, "wide", False), (32, 61, "pairs", True), (32, 100, "ulps", False),
     (64, 22, "even", True), (64, 23, "plateau", False), (128, 33, "even", False), (128, 43, "even", True), (128, 44, "wide", True),
     (256, 65, "even", True), (256, 86, "pairs", False), (128, 40, "ascending", False)])
 def test_direct_group_bisection(mq, dtype, group, n_clip, kind, f16):  # noqa: F811
-    if group > 32 and dtype != torch.float32:
-        pytest.skip("looked up, not scored")
     w = _strided(14, 6 * group, group, n_clip, dtype)
     g = torch.Generator(device=DEV).manual_seed(group + n_clip)
     v = [w[r, (r % 3) * group:(r % 3 + 2) * group] for r in range(14)]
