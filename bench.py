@@ -61,7 +61,7 @@ SEARCH_KERNEL_COUNTERS = {
     "valu_instr_per_wave": 1008.0,                                   # SQ_INSTS_VALU / SQ_WAVES, 4096-column instance
 }
 # sweep_group_bits_kernel, fp16 groups of 128, 50 ratios: a wave takes four groups
-GROUP_KERNEL_COUNTERS = {"from": "profiles/w4_group128_7b_k50_kernel_stats.txt", "valu_instr_per_wave": 1878.0}
+GROUP_KERNEL_COUNTERS = {"from": "profiles/w4_group128_7b_k50_kernel_stats.txt", "valu_instr_per_wave": 1356.0}
 
 
 def parse():

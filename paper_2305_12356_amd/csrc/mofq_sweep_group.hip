@@ -21,7 +21,7 @@
 //      leaves (the difference of sums keeps two digits fewer).  Where a second candidate is too close, or a scale is
 //      out of range (non-finite or nearly exact groups), all candidates of the group are scored that way, in fp64.
 //
-// Bound by vector issue and latency together: 1375 instructions per wave of four groups of 128 with 50 ratios take 77 % of
+// Bound by vector issue and latency together: 1356 instructions per wave of four groups of 128 with 50 ratios take 77 % of
 // the clocks (130 of them the winners' own sums; the direct kernel: 4360); 11 KB of LDS leave 3.5 waves per SIMD, so
 // registers are spent on look-ups in flight (with a scheduler that kept to 63 registers for 8 waves per SIMD the same
 // instructions took 1425 us instead of 1230).  Measured, layer selection of the seven linears of a
