@@ -117,10 +117,18 @@ MOFQ_DEV void packed_prefixes(const uint32_t* counters, uint64_t* P, int lo, int
     between();
     acc += static_cast<uint64_t>((m + 1) << shift) * (c2[j] >> 16) + (static_cast<uint64_t>(c2[j] >> 16) << 48);
   };
+  constexpr bool KEEP = PWMAX <= 2;   // the thread's own prefixes in registers, else formed again behind the scan
+  uint64_t own[KEEP ? 2 * PWMAX : 1];
   uint64_t acc = 0;
 #pragma unroll
-  for (int j = 0; j < PWMAX; ++j)
-    if (j < pw) add(j, acc, [] {});   // uniform; words past the end count nothing
+  for (int j = 0; j < PWMAX; ++j) {
+    if constexpr (KEEP) {
+      own[2 * j] = acc;
+      add(j, acc, [&] { own[2 * j + 1] = acc; });   // (counters past the end are zero)
+    } else if (j < pw) {   // uniform; words past the end count nothing
+      add(j, acc, [] {});
+    }
+  }
   // exclusive scan over the threads (sums of the two fields do not meet: the sum stays below 2^48)
   uint64_t inc = acc;
 #pragma unroll
@@ -138,13 +146,18 @@ MOFQ_DEV void packed_prefixes(const uint32_t* counters, uint64_t* P, int lo, int
   for (int j = 0; j < PWMAX; ++j)
     if (j < pw) {
       uint64_t first = at, second = 0;
-      add(j, at, [&] { second = at; });
+      if constexpr (KEEP) {
+        first += own[2 * j];
+        second = at + own[2 * j + 1];
+      } else {
+        add(j, at, [&] { second = at; });
+      }
       if (w0 + j < w1) {
         P[2 * (w0 + j)] = first;
         P[2 * (w0 + j) + 1] = second;
       }
     }
-  if (id == NW * 64 - 1) P[nbin] = at;
+  if (id == NW * 64 - 1) P[nbin] = KEEP ? at + acc : at;
   if constexpr (NW > 1) __syncthreads();
 }
 
