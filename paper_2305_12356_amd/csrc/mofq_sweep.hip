@@ -1189,10 +1189,19 @@ int launch_gran(const SweepParams& p, const SweepArgs& a, hipStream_t st) {
 // 5000, 10: 78.4 / 78.3, 14: 94.5 / 87.9; 2000 x 1024, 28: 31.8 / 32.3, 32: 34.4 / 32.5; few rows: 512 x 8192, 16: 33.9 /
 // 34.2, 20: 38.5 / 37.4; 256 x 16384, 14: 33.6 / 34.5, 18: 38.2 / 37.1; 1000 x 600, 32: 26.0 / 26.9, 40: 30.0 / 29.7; 256 x
 // 1024, 40: 28.0 / 28.8.  Groups, 2048 x 4096: 32, 18: 75.0 / 75.5, 20: 78.9 / 77.2, 50: 157 / 126; 64, 14: 56.7 / 56.6, 16:
-// 60.9 / 58.5, 50: 140 / 97; 128, 16: 55.6 / 55.1, 18: 60.1 / 58.7, 50: 130 / 88; 256, 18: 62.6 / 62.5, 20: 67.1 / 66.6, 50: 133 / 96.
+// 60.9 / 58.5, 50: 140 / 97; 128, 16: 55.6 / 55.1, 18: 60.1 / 58.7, 50: 130 / 88; 256, 18: 62.6 / 62.5, 20: 67.1 / 66.6, 50:
+// 133 / 96.  Fewer groups than are resident at once: 400 x 2048: 32, 32: 26.3 / 27.1, 40: 29.6 / 28.5; 64, 40: 28.6 / 29.2, 50:
+// 33.0 / 32.7; 128, 28: 31.9 / 32.4, 32: 34.7 / 34.1; 256, 24: 43.2 / 44.0, 28: 48.0 / 46.3; 100 x 1024: 32, 50: 26.4 / 28.5.
 int bisect_clip(const SweepParams& p) {
   if (p.gran == MOFQ_PER_TENSOR) return MOFQ_MAX_CLIP + 1;
-  if (p.gran == MOFQ_PER_GROUP) return p.group == 64 ? 16 : (p.group == 128 ? 18 : 20);
+  if (p.gran == MOFQ_PER_GROUP) {
+    const int64_t groups = mofq_num_units(p.rows, p.cols, p.gran, p.group);
+    const int g = p.group == 32 ? 0 : (p.group == 64 ? 1 : (p.group == 128 ? 2 : 3));
+    static constexpr int64_t resident[4] = {65536, 65536, 49152, 32768};   // groups resident at once
+    static constexpr int many[4] = {20, 16, 18, 20}, few[4] = {40, 40, 32, 28};
+    if (groups >= resident[g]) return many[g];
+    return g == 0 && groups < 16384 ? 64 : few[g];
+  }
   if (p.cols <= 2048) return p.rows >= 1024 ? 32 : 44;
   return p.rows >= 1024 ? 12 : 18;
 }

@@ -580,16 +580,11 @@ int launch_size(const GroupArgs& a, hipStream_t st) {
 }
 
 template <typename In, int FA, int FB>
-int launch_fmt(const SweepParams& p, const GroupArgs& a, hipStream_t st) {   // (min_clip: what is left out is never faster)
-  constexpr bool H = std::is_same<In, F16>::value;
+int launch_fmt(const SweepParams& p, const GroupArgs& a, hipStream_t st) {
   switch (p.group) {
-    case 64:
-      if constexpr (FB >= 0 || !H) return launch_size<In, FA, FB, 64>(a, st);
-      break;
+    case 64: return launch_size<In, FA, FB, 64>(a, st);
     case 128: return launch_size<In, FA, FB, 128>(a, st);
-    case 256:
-      if constexpr (FB >= 0 || FA != MOFQ_INT4) return launch_size<In, FA, FB, 256>(a, st);
-      break;
+    case 256: return launch_size<In, FA, FB, 256>(a, st);
   }
   return MOFQ_ERR_UNSUPPORTED;
 }
@@ -614,13 +609,17 @@ int launch_type(const SweepParams& p, const GroupArgs& a, hipStream_t st) {
 // 142.3; bf16 64, 18: 64.6 / 63.0; bf16 128, 18: 60.3 / 58.4; bf16 256, 56: 92.5 / 109.1, 128: 120.8 / 130.1. E2M1: fp16
 // 64, 128: 144.4 / 170.0; fp16 128, 15: 57.5 / 56.6; fp16 256, 22: 65.2 / 63.1; bf16 64, 12: 53.3 / 52.7; bf16 128, 11:
 // 47.8 / 46.7; bf16 256, 17: 58.6 / 58.2.
+// Tensors of fewer than kFewElements: bisection's rounds wait for each other where few groups are resident, so there the
+// lines are those to scoring all candidates (the pair, fp16 64, layer selection: 400 x 2048, 24: 22.3 / 22.2, 32: 25.6 / 20.7;
+// 500 x 4096, 24: 29.7 / 29.7; 1000 x 4096, 32: 55.0 / 52.1; 2048 x 4096, 30: 75.4 / 88.5).
 constexpr int kNever = MOFQ_MAX_CLIP + 1;
+constexpr int64_t kFewElements = 6 << 20;
 int min_clip(const SweepParams& p) {
-  static constexpr int lines[2][3][3] = {   // [fp16, bf16][64, 128, 256][pair, INT4, E2M1]
-      {{60, kNever, kNever}, {12, 27, 15}, {22, kNever, 22}},
-      {{10, 17, 12}, {9, 18, 11}, {18, kNever, 17}}};
+  static constexpr int lines[2][2][3][3] = {   // [many, few elements][fp16, bf16][64, 128, 256][pair, INT4, E2M1]
+      {{{60, kNever, kNever}, {12, 27, 15}, {22, kNever, 22}}, {{10, 17, 12}, {9, 18, 11}, {18, kNever, 17}}},
+      {{{23, 48, 28}, {12, 25, 15}, {21, 39, 20}}, {{10, 19, 13}, {9, 19, 11}, {18, 37, 17}}}};
   const int which = p.n_fmt == 2 ? 0 : (p.fmt[0] == MOFQ_INT4 ? 1 : 2);
-  return lines[p.dtype == MOFQ_F16 ? 0 : 1][p.group == 64 ? 0 : (p.group == 128 ? 1 : 2)][which];
+  return lines[p.rows * p.cols < kFewElements ? 1 : 0][p.dtype == MOFQ_F16 ? 0 : 1][p.group == 64 ? 0 : (p.group == 128 ? 1 : 2)][which];
 }
 
 }  // namespace

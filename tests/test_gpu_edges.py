@@ -215,8 +215,8 @@ def test_half_pattern_groups_write_codes(mq):  # noqa: F811
 # but for some formats alone); the numbers of ratios leave one and two candidates in the last gaps, after two to four halvings
 @pytest.mark.parametrize("dtype", [torch.float32, torch.float16, torch.bfloat16])
 @pytest.mark.parametrize("group,n_clip,kind,f16", [
-    (32, 16, "even", True), (32, 50, "even", False), (32, 128, "wide", False), (32, 61, "pairs", True), (32, 100, "ulps", False),
-    (64, 22, "even", True), (64, 23, "plateau", False), (128, 33, "even", False), (128, 43, "even", True), (128, 44, "wide", True),
+    (32, 64, "even", True), (32, 65, "even", False), (32, 128, "wide", False), (32, 86, "pairs", True), (32, 100, "ulps", False),
+    (64, 43, "even", True), (64, 44, "plateau", False), (128, 33, "even", False), (128, 43, "even", True), (128, 44, "wide", True),
     (256, 65, "even", True), (256, 86, "pairs", False), (128, 40, "ascending", False)])
 def test_direct_group_bisection(mq, dtype, group, n_clip, kind, f16):  # noqa: F811
     w = _strided(14, 6 * group, group, n_clip, dtype)
@@ -240,13 +240,21 @@ def test_direct_group_bisection(mq, dtype, group, n_clip, kind, f16):  # noqa: F
         check_tensor(mq, w, cands, orc.PER_GROUP, ratios, group, f16, label=f"direct-group {kind}")
 
 
-@pytest.mark.parametrize("group,n_clip", [(32, 50), (64, 30), (128, 64), (256, 120)])
+@pytest.mark.parametrize("group,n_clip", [(32, 64), (64, 40), (128, 64), (256, 120)])
 def test_direct_group_bisection_everywhere(mq, group, n_clip):  # noqa: F811
     g = torch.Generator(device=DEV).manual_seed(n_clip)
     w = 0.02 * torch.randn(64, 8 * group, generator=g, device=DEV)
     w.view(64, 8, group)[:, :, 5] = 0.02 * torch.linspace(2.5, 9.0, 64 * 8, device=DEV).view(64, 8)
     for cands in (PAIR4, [orc.FP4_E2M1]):
         check_tensor(mq, w, cands, orc.PER_GROUP, _descending("even", n_clip), group, True, label="direct-group-everywhere")
+
+
+# as many groups as are resident at once, where bisection starts at fewer ratios
+@pytest.mark.parametrize("dtype,group,rows,n_clip", [(torch.float32, 32, 1024, 20), (torch.float32, 64, 2048, 16), (torch.bfloat16, 32, 1024, 23),
+                                                     (torch.float32, 128, 3072, 18), (torch.float32, 256, 4096, 22), (torch.float16, 64, 3100, 40)])
+def test_direct_group_bisection_many_groups(mq, dtype, group, rows, n_clip):  # noqa: F811
+    w = _strided(rows, 2048, 0, group, dtype)
+    check_tensor(mq, w, PAIR4, orc.PER_GROUP, _descending("even", n_clip), group, True, label="direct-group-many")
 
 
 # rows whose candidates are scored by bisection of the ratios: one wave per row to sixteen, masks of one and two words,
