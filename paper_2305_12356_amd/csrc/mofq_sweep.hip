@@ -104,6 +104,7 @@ constexpr float kTinySum = 0x1p-80f;
 // gap for which sqrt(E1 - T) + sqrt(E2 - T) > (|x| + sqrt(T)) (s1 - s2) / s2 is left alone.  E1 and E2 are taken 1e-5
 // smaller and T 1e-5 larger (fp32 sums), and T by 2^-18 of the energy besides: a decision on rounded numbers
 // assigns an element within 2^-22 of a boundary to the level beyond it, which adds up to 4 x^2 2^-22 to the error.
+// All of it needs the scales of a gap to lie between s1 and s2; a row where a degenerate scale breaks their order is scored whole.
 // 8-bit formats gain nothing by it: their levels are so many that any gap between two ratios can hold anything.
 // Vector issue bounds it: layer selection, INT4 against E2M1, fp32: 4096 x 11008, 100 ratios 1145 -> 248 us; 3001 x 5000,
 // 50 ratios 246 -> 123.
@@ -229,14 +230,20 @@ __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(CH <= 4
       for (int idx = tid; idx < NF * K; idx += THREADS) s_tot[idx / K][idx % K] = __builtin_inff();   // not scored
       for (int f = 0; f < NF; ++f)
         if (wave == f % NW) {
+          // The ratios descend, and so do the scales, but for a step up to the 1 of a degenerate scale from one below 1: the
+          // scales between the ends of a gap across that step do not lie between theirs, so such a row is scored whole.
+          bool up = false;
+          for (int k = lane; k + 1 < K; k += 64) up |= s_scale[f][k] < s_scale[f][k + 1];
+          const bool whole = __builtin_amdgcn_ballot_w64(up) != 0;
+          const int n = whole ? K : START;
           if (lane < 2) s_done[f][lane] = 0;
           __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-          if (lane < START) {
-            const int k = lane * (K - 1) / (START - 1);
-            s_list[f * MOFQ_MAX_CLIP + lane] = k;
+          for (int i = lane; i < n; i += 64) {
+            const int k = whole ? i : i * (K - 1) / (START - 1);
+            s_list[f * MOFQ_MAX_CLIP + i] = k;
             atomicOr(&s_done[f][k >> 6], 1ull << (k & 63));
           }
-          if (lane == 0) s_new[f] = START;
+          if (lane == 0) s_new[f] = n;
         }
       const float root_en = static_cast<float>(__builtin_sqrt(en));
       for (;;) {
@@ -278,7 +285,7 @@ __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(CH <= 4
                 const float s1 = s_scale[f][k], s2 = s_scale[f][next];
                 const float up = __builtin_fmaf(s_tot[f][k], 1.0f - 1.0e-5f, -limit), down = __builtin_fmaf(s_tot[f][next], 1.0f - 1.0e-5f, -limit);
                 const float roots = __builtin_amdgcn_sqrtf(__builtin_fmaxf(up, 0.0f)) + __builtin_amdgcn_sqrtf(__builtin_fmaxf(down, 0.0f));
-                look = !sums || s1 < s2 || !(roots > span * ((s1 - s2) / s2));
+                look = !sums || !(roots > span * ((s1 - s2) / s2));
               }
               const uint64_t lanes = __builtin_amdgcn_ballot_w64(look);
               const int mid = (k + next) >> 1;

@@ -295,6 +295,24 @@ def test_row_bisection_everywhere(mq, cols, n_clip):  # noqa: F811
         check_tensor(mq, w, cands, orc.PER_CHANNEL, _descending("even", n_clip), 0, label="row-bisection-everywhere")
 
 
+# The last ratios are so small that their scales become 1, beside a scale just above 1 (index 31) and the row's best ones
+# below it: the scales of the gap between them are not between its ends.  Rows of an even index that way for INT4, of an odd
+# one for E2M1; the last two with all scales above 1 and with all of them 1.
+@pytest.mark.parametrize("cols", [2056, 8200, 16392])
+@pytest.mark.parametrize("f16,tiny", [(True, 1e-9), (False, 1e-39)])
+def test_row_bisection_degenerate_scales(mq, cols, f16, tiny):  # noqa: F811
+    ratios = [1.0 - 0.9 * i / 39 for i in range(40)] + [tiny] * 24
+    g = torch.Generator(device=DEV).manual_seed(cols)
+    w = 0.5 * torch.randn(26, cols, generator=g, device=DEV)
+    above = torch.linspace(1.0005, 1.02, 13, device=DEV)
+    w[0::2, 0] = orc.qmax(orc.INT4) / ratios[31] * above
+    w[1::2, 0] = orc.qmax(orc.FP4_E2M1) / ratios[31] * above
+    w[24, 0] = 100.0
+    w[25] = w[25] * (2.0 ** -30 if f16 else 2.0 ** -130)
+    for cands in (PAIR4, [orc.INT4], [orc.FP4_E2M1], [orc.FP4_E2M1_IEEE]):
+        check_tensor(mq, w, cands, orc.PER_CHANNEL, ratios, 0, f16, label=f"row-bisection-degenerate {tiny}")
+
+
 # ratios so small that a group's largest elements are 2^31 ulps of the first counted pattern and more: the last tables
 # of the rank kernel and, beyond them, the direct kernel (bf16: 128 patterns per binade)
 @pytest.mark.parametrize("lo_clip", [1e-5, 4e-6, 2e-6, 1e-6, 1e-7])
