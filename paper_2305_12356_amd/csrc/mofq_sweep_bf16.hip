@@ -328,7 +328,7 @@ void sweep_pattern_kernel(const SortedArgs a) {
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
           const uint32_t w = j < CH ? raw[j].w[i] : 0;
-          if (j < CH) count_pair(at, __builtin_elementwise_min(__builtin_bit_cast(i16x2, w & 0x7FFF7FFFu) - lo2, last2), one);   // padding (zero) and whatever lies below every threshold has no counter
+          if (j < CH) count_pair(at, __builtin_elementwise_min(__builtin_bit_cast(i16x2, w & 0x7FFF7FFFu) - lo2, last2), one);   // whatever lies below every threshold has no counter, padding (zero) neither unless they reach that far down (E4M3 on fp16)
           if constexpr (ANY_TAIL) note_negative(noted, w, tlo);
         }
       if constexpr (ANY_TAIL) count_noted<PART * 4>(noted, src, (j0 * kThreads + tid) * 8, kThreads * 8, tlo, ntbin, tat);

@@ -713,13 +713,25 @@ bool in_domain(const SweepParams& p) {
     // 4096 rows, us, directly / by histogram: the pair, 1024 columns x 36 ratios 72 / 66, 2048 x 18 70 / 69, 4096 x 9
     // 78 / 80, 5120 x 8 88 / 89; INT8, 1536 x 32 46 / 43, 2048 x 24 45 / 45, 4096 x 14 56 / 56, 5120 x 12 62 / 61;
     // E4M3, 1536 x 28 50 / 49, 2048 x 22 52 / 50, 4096 x 11 59 / 59, 5120 x 9 63 / 64.
-    // fp16 has eight times the patterns, in groups. 2048 rows: the pair, 2048 x 64 101 / 92, 4096 x 30 93 / 85, 5000 x 24
-    // 99 / 108, 8192 x 16 107 / 96, 11008 x 12 117 / 112, 1024 x 100 91 / 130; INT8, 2048 x 64 52 / 57, 4096 x 30 47 /
-    // 59, 5000 x 24 52 / 65, 8192 x 20 65 / 69, 11008 x 16 74 / 80; E4M3, 2048 x 64 64 / 65, 4096 x 30 59 / 55, 5000 x 24
-    // 64 / 80, 8192 x 20 81 / 66, 11008 x 12 76 / 81.
-    const bool half = p.dtype == MOFQ_F16, more = p.n_clip > 64;
-    const int64_t line = half ? (p.n_fmt == 2 ? (more ? 180000 : 140000) : (p.fmt[0] == MOFQ_INT8 ? 200000 : (more ? 180000 : 165000)))
-                              : (p.n_fmt == 2 ? 36864 : (p.fmt[0] == MOFQ_INT8 ? 53248 : 45056));
+    // fp16 has eight times the patterns, in groups. A row's steps between loads and look-ups take some us more per 4096
+    // columns, and so does a second 64 candidates; the zeros that fill the row's last 4096 columns cost up to a quarter, for
+    // they share one counter where the counters reach down to the pattern of zero (E4M3's do). That part is capped: few rows
+    // are looked up faster than all of this says (300 rows, the pair, 4096 columns x 24 ratios 45 / 28), many are not. 2048
+    // rows, directly / by look-up, on either side of the line: the pair, 1024 columns x 128 ratios 114 / 132, 2048 x 50 83 /
+    // 93, 2048 x 64 102 / 93, 2048 x 65 104 / 127, 2048 x 100 151 / 127, 4096 x 24 79 / 86, 4096 x 28 89 / 86, 4104 x 32 113 /
+    // 114, 4104 x 40 135 / 115, 5000 x 24 100 / 110, 5000 x 28 112 / 110, 8192 x 12 89 / 97, 8192 x 14 99 / 97, 8200 x 16 112 /
+    // 125, 8200 x 20 132 / 125, 11008 x 10 105 / 113, 11008 x 12 117 / 113, 16384 x 8 127 / 122; INT8, 2048 x 64 53 / 58, 2048 x
+    // 128 92 / 76, 3072 x 50 56 / 59, 3072 x 64 67 / 59, 4096 x 32 50 / 59, 4096 x 50 69 / 60, 8192 x 20 66 / 70, 8192 x 24 73 /
+    // 70, 12288 x 16 78 / 81, 12288 x 20 89 / 82; E4M3, 2048 x 64 64 / 66, 4096 x 24 51 / 56, 4096 x 32 62 / 56, 4104 x 40 86 /
+    // 86, 4104 x 50 102 / 85, 5000 x 32 79 / 81, 5000 x 40 92 / 81, 8192 x 14 66 / 67, 8192 x 16 72 / 67, 8200 x 20 84 / 95, 8200
+    // x 28 106 / 95, 11008 x 12 78 / 82, 11008 x 14 85 / 82.
+    const int64_t fill = (p.cols + 4095) / 4096 * 4096 - p.cols;
+    const int more = p.n_clip > 64 ? 1 : 0;
+    int64_t line = p.n_fmt == 2 ? 36864 : (p.fmt[0] == MOFQ_INT8 ? 53248 : 45056);
+    if (p.dtype == MOFQ_F16)
+      line = p.n_fmt == 2 ? std::min<int64_t>(95000 + p.cols + 12 * fill, 140000) + 40000 * more
+                          : (p.fmt[0] == MOFQ_INT8 ? std::min<int64_t>(150000 + 5 * p.cols, 200000) + 40000 * more
+                                                   : std::min<int64_t>(105000 + 2 * p.cols + 16 * fill, 165000) + 35000 * more);
     if (p.cols * p.n_clip < line) return false;
     return p.n_fmt == 1 || (p.fmt[0] == MOFQ_INT8 && p.fmt[1] == MOFQ_FP8_E4M3);
   }

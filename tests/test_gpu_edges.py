@@ -179,10 +179,11 @@ def test_group_gaps_everywhere(mq, group, n_clip):  # noqa: F811
 
 
 # fp16 rows and 8-bit formats, looked up by groups of patterns: one to four chunks per thread, one and two groups of 64
-# candidates, tables as far as they reach and, in the last line, beyond (scored directly)
+# candidates, tables as far as they reach and, in the last case, beyond (scored directly)
 @pytest.mark.parametrize("cols,n_clip,lo_clip,f16", [
     (2048, 88, 0.5, True), (4096, 49, 0.7, False), (4104, 128, 0.5, False), (5000, 64, 0.3, True), (8200, 25, 0.5, False),
-    (11008, 65, 0.6, False), (12296, 17, 0.5, True), (16384, 13, 0.5, False), (8192, 25, 0.26, False), (8192, 40, 0.02, False)])
+    (11008, 65, 0.6, False), (12296, 17, 0.5, True), (16384, 13, 0.5, False), (3072, 38, 0.5, False), (4096, 27, 0.5, True),
+    (1544, 128, 0.6, False), (8192, 25, 0.26, False), (8192, 40, 0.02, False)])
 def test_half_pattern_groups(mq, cols, n_clip, lo_clip, f16):  # noqa: F811
     w = _strided(15, cols, 8, cols, torch.float16)
     g = torch.Generator(device=DEV).manual_seed(cols)
