@@ -10,8 +10,9 @@
  *     (the linear layer A_out = W * A_in of Section 3.2).
  *   - Every pointer is a DEVICE pointer unless the comment says HOST.  The
  *     caller owns all memory; the library allocates none, keeps no pointer
- *     after the call and has no global state (one exception, stated there:
- *     mofq_select_layer_static and its built-in workspace).
+ *     after the call and has no global state (two exceptions, stated there:
+ *     mofq_select_layer_static and its built-in workspace, and the count that
+ *     numbers the calls of mofq_quantize).
  *   - Calls only enqueue work on `stream` (a hipStream_t passed as void*;
  *     NULL = the default stream) and never synchronise: results, including the
  *     chosen format, land in device memory.
@@ -157,6 +158,14 @@ typedef struct {
  * clip ratios per unit, then write codes, scales and (optionally) the chosen
  * indices and unit errors.  `tensor_err` (device, may be NULL) receives the
  * tensor error, the sum of the unit errors.
+ *
+ * A tensor of up to 163840 elements with one scale and one clip ratio takes one
+ * launch whose workgroups hand their error sums over in the workspace, marked with
+ * a number that the host draws per call from a process-wide count (atomic, so any
+ * thread may call).  Calls on one workspace are to be ordered, as everywhere (see
+ * mofq_workspace_bytes); where two such calls overlap on one all the same, the codes
+ * are right, but scale, clip index, unit error and tensor error of either can stay
+ * unwritten, and no error is returned.
  */
 int mofq_quantize(const mofq_tensor_t* t, int32_t format, const mofq_scale_cfg_t* cfg,
                   const mofq_qout_t* out, double* tensor_err,

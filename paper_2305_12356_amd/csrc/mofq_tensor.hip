@@ -288,7 +288,8 @@ __global__ __launch_bounds__(kThreads) void tensor_unit_kernel(const TensorArgs 
 //
 // The meeting: workgroup b leaves two words, its sum's bits and the same bits ^ nonce, and reads all of them behind a
 // sequentially consistent fence, so the last one in the order of the fences finds them all (a second one that does writes the same
-// values).  A pair is complete if it xors to the nonce, which the host draws per call, so the scratch needs no
+// values; two calls at once on one scratch, which the interface excludes, can lose each other's pairs, and then
+// nobody finds all of them).  A pair is complete if it xors to the nonce, which the host draws per call, so the scratch needs no
 // clearing; whoever finds all pairs leaves zeros, so that a replay of a captured call, which has the same nonce,
 // starts without them.  Torn pairs: (sum, 0) xors to the sum, which is never the nonce (a negative number);
 // (0, sum ^ nonce) xors to the nonce only if the sum is 0, the value then read.  Nobody waits for anybody.
@@ -366,8 +367,8 @@ __global__ __launch_bounds__(kSmallThreads) void tensor_quant_small_kernel(const
   if (tid == 0) write_unit(a, s, e);
 }
 
-// A number that no other call of the process has, mixed from a count that starts at the time: the bits of a
-// finite negative double.
+// A number that no other call of the process has, a count that starts at the time mixed as the SplitMix64 generator
+// does (Steele, Lea and Flood 2014; its increment and multipliers): the bits of a finite negative double.
 uint64_t next_nonce() {
   static std::atomic<uint64_t> count{static_cast<uint64_t>(std::chrono::system_clock::now().time_since_epoch().count())};
   uint64_t z = count.fetch_add(0x9E3779B97F4A7C15ull, std::memory_order_relaxed);
