@@ -581,7 +581,9 @@ using Small = Tile<64, 64, 32, 32>;      // three
 
 }  // namespace
 
-// The tile by the time a K step takes, in units of one of a full grid of large tiles, on 256 compute units: a round of
+// The tile by the time a K step takes, in units of one of a full grid of large tiles, on the MI355X's 256 compute units (a
+// number of its own here, not the current device's: the plan sets the size of the workspace and the order of the sums,
+// which are the same wherever and whenever they are asked for): a round of
 // large tiles 1, of medium ones 0.6, of small ones 0.38, 0.51 and 0.7 with one, two and three on a compute unit.
 // Measured, layer selection with INT8 and exact E4M3 products, us, large / medium / small: tokens x rows x columns
 // 2048 x 4096 x 4096 194 / 212 / 289; 1024 x 4096 x 4096 134 / 127 / 168; 777 x 3000 x 5056 155 / 121 / 159;
@@ -593,6 +595,7 @@ using Small = Tile<64, 64, 32, 32>;      // three
 // 64 x 4096 x 4096 (64) 76 / 56 / 58; 128 x 4096 x 11008 (128) 217 / 166 / 182; 256 x 4096 x 11008 (256) 227 / 232 / 256,
 // into the products alone 226; 256 x 1024 x 4096 (64) 65 / 42 / 43; 1024 x 1024 x 4096 (256) 71 / 69 / 73.  The second
 // launch costs what short products save: 64 x 1024 x 1024 29.4 / - / 30.2, 128 x 8192 x 1024 40 / 44 / 44.
+constexpr int64_t kUnits = 256;
 WaPlan wa_gemm_plan(int64_t M, int64_t N, int64_t K, int64_t ldx, int64_t ldw) {
   auto tiles = [&](auto t) { using T = decltype(t); return ((M + T::TM - 1) / T::TM) * ((N + T::TN - 1) / T::TN); };
   const int64_t large = tiles(Large{}), medium = tiles(Medium{}), small = tiles(Small{});
@@ -603,15 +606,15 @@ WaPlan wa_gemm_plan(int64_t M, int64_t N, int64_t K, int64_t ldx, int64_t ldw) {
   if (rows < Small::TM) {
     p.tile = WaPlan::kWide;
   } else {
-    const int64_t per_cu = (small + 255) / 256;
-    const double t_large = static_cast<double>((large + 255) / 256), t_medium = 0.6 * static_cast<double>((medium + 255) / 256);
-    const double t_small = per_cu == 1 ? 0.38 : (per_cu == 2 ? 0.51 : 0.235 * static_cast<double>(per_cu));
+    const auto rounds = [](int64_t n) { return static_cast<double>((n + kUnits - 1) / kUnits); };
+    const double per_cu = rounds(small), t_large = rounds(large), t_medium = 0.6 * rounds(medium);
+    const double t_small = per_cu == 1.0 ? 0.38 : (per_cu == 2.0 ? 0.51 : 0.235 * per_cu);
     p.tile = WaPlan::kSmall;
     if (rows >= Medium::TM && t_medium < t_small) p.tile = WaPlan::kMedium;
     if (rows >= Large::TM && t_large <= std::min(t_medium, t_small)) p.tile = WaPlan::kLarge;
   }
   p.blocks = static_cast<int>(p.tile == WaPlan::kLarge ? large : (p.tile == WaPlan::kMedium ? medium : small));
-  if (p.tile == WaPlan::kSmall && small <= 256 && stages >= 20) {
+  if (p.tile == WaPlan::kSmall && small <= kUnits && stages >= 20) {
     // (at most 16 or 8 pieces of a product, which bounds the scratch: 40 MB or 64 MB)
     const int64_t run = small <= 48 ? std::max(std::min<int64_t>(20, (stages + 1) / 2), (stages + 15) / 16)
                                     : (small <= 160 ? std::max<int64_t>(40, (stages + 7) / 8) : stages);
