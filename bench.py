@@ -60,7 +60,8 @@ SEARCH_KERNEL_COUNTERS = {
     "rows_with_codes": 8192,
     "valu_instr_per_wave": 1008.0,                                   # SQ_INSTS_VALU / SQ_WAVES, 4096-column instance
 }
-# sweep_group_bits_kernel, fp16 groups of 128, 50 ratios: a wave takes four groups
+# sweep_group_bits_kernel, fp16 groups of 128, 50 ratios: a wave takes four groups (a mean over this recipe: how many gaps
+# of the coarse search are looked at depends on the data)
 GROUP_KERNEL_COUNTERS = {"from": "profiles/w4_group128_7b_k50_kernel_stats.txt", "valu_instr_per_wave": 1356.0}
 
 
@@ -295,7 +296,8 @@ def run_w4(args, shapes, dev, weights, group, model, steps, warmup, ceilings=Non
         "kernel": (f"sweep_group_bits_kernel<F16, INT4, FP4_E2M1, {GROUP}, 32-bit words> on {dom_cols}-column rows" if group else
                    f"sweep_hist_kernel<F16, INT4, FP4_E2M1> instance for {dom_cols}-column rows"),
         "limited_by": "vector instruction issue, not bytes: " +
-                      (f"per group a table of its bit patterns, then {n_clip} x {N_FMT} candidates x 7 or 8 boundary look-ups" if group else
+                      (f"per group a table of its bit patterns, then 7 or 8 boundary look-ups for each of the {n_clip} x {N_FMT} candidates that "
+                       f"its coarse search of {GROUP // 8} ratios leaves" if group else
                        f"per row a histogram of its bit patterns, then {n_clip} x {N_FMT} candidates x 7 or 8 boundary look-ups"),
         "avg_launch_ms": dom_time / len(dom) * 1e3, "launches": len(dom),
         "algorithmic_bytes_per_launch": alg_bytes_per_launch,
