@@ -730,8 +730,8 @@ bool in_domain(const SweepParams& p) {
     int64_t line = p.n_fmt == 2 ? 36864 : (p.fmt[0] == MOFQ_INT8 ? 53248 : 45056);
     if (p.dtype == MOFQ_F16)
       line = p.n_fmt == 2 ? std::min<int64_t>(95000 + p.cols + 12 * fill, 140000) + 40000 * more
-                          : (p.fmt[0] == MOFQ_INT8 ? std::min<int64_t>(150000 + 5 * p.cols, 200000) + 40000 * more
-                                                   : std::min<int64_t>(105000 + 2 * p.cols + 16 * fill, 165000) + 35000 * more);
+                          : (p.fmt[0] == MOFQ_INT8 ? std::min<int64_t>(150000 + 5 * p.cols + 40000 * more, 200000)
+                                                   : std::min<int64_t>(105000 + 2 * p.cols + 16 * fill + 35000 * more, 165000 + 15000 * more));
     if (p.cols * p.n_clip < line) return false;
     return p.n_fmt == 1 || (p.fmt[0] == MOFQ_INT8 && p.fmt[1] == MOFQ_FP8_E4M3);
   }
