@@ -19,7 +19,8 @@
 // (128 registers for its 64x64 share), so that eight waves, two per SIMD, fit: while
 // one waits at the stage barrier or for its fragments the other keeps the matrix core
 // busy.  The 256x128 workgroup tile needs 25 % fewer operand bytes per flop than
-// 128x128.  (That is for grids that fill the chip; wa_gemm_plan has the tiles of smaller ones.)
+// 128x128.  (That is for grids that fill the chip; wa_gemm_plan has the tiles of smaller ones.)  The weight-only metric's
+// products have X in common and run side by side instead (wa_gemm_shared_kernel).
 //
 // What bounds it on full grids: power.  The part holds 1.73 GHz with the matrix cores busy for 0.67 of the clocks
 // (2048 x 11008 x 4096, three bf16 products, 456 us); four waves of 128 x 64, with a quarter less LDS traffic, run at 1.87 GHz
@@ -575,9 +576,201 @@ __global__ __launch_bounds__(T::NW * 64) void wa_pieces_kernel(const GemmArgs a)
   }
 }
 
+// ---- three bf16 products that share X (weight-only layer output) ------------------------------------------
+// X W^T, X G1^T and X G2^T in one K loop: a stage holds one line of K of TM rows of X and of TN rows of W, G1 and G2
+// each, so X is deposited and its fragments are read once instead of three times: for a 256x128 tile 640 rows a step of 64
+// of K instead of 1152, and 8 fragments for 12 matrix instructions instead of 12.  A lane of a 64x64 share then holds 192
+// accumulators, 247 registers in all, so two waves still fit a SIMD.  A stage of 80 KB leaves room for two in LDS;
+// as a step lasts three times as long as one of wa_gemm_kernel, a stage has as long to arrive if its deposits are issued early in the
+// step before: over its first third (FIRST, SPREAD; over two thirds of it 2048 x 11008 x 4096 474 us a call instead of 467, 1536 x
+// 11008 x 8192 913 instead of 885).  Measured, layer selection with INT4 and E2M1, us, one product after the other -> here:
+// 2048 x 11008 x 4096 (tokens x rows x columns) 516 -> 467, 1536 x 11008 x 8192 1009 -> 885, 2048 x 4096 x 4096 186 -> 167, 1024 x 11008 x 4096
+// 349 -> 314, 512 x 4096 x 4096 100 -> 82, 777 x 3000 x 5056 118 -> 109, 64 x 4096 x 1024 39.8 -> 35.  Bound by power and LDS as
+// wa_gemm_kernel: 1.41 PFLOP/s at the first of these shapes, 1.19 before.  Medium tiles have eight waves of 64x32 (four of 64x64
+// are 1 % slower).  The sums are those of wa_gemm_kernel bit for bit.
+template <int TM_, int TN_, int WM_, int WN_> struct SharedTile {
+  static constexpr int TM = TM_, TN = TN_, WM = WM_, WN = WN_;
+  static constexpr int NW = (TM / WM) * (TN / WN);
+  static constexpr int STAGE = (TM + 3 * TN) * ROW_B;
+  static constexpr int PER_CU = (160 * 1024) / (2 * STAGE);
+  static constexpr int PER_SIMD = PER_CU * NW / 4;
+};
+
+template <typename T>
+__global__ __launch_bounds__(T::NW * 64) __attribute__((amdgpu_waves_per_eu(T::PER_SIMD, T::PER_SIMD))) void wa_gemm_shared_kernel(const GemmArgs a) {
+  constexpr int TM = T::TM, TN = T::TN, WM = T::WM, WN = T::WN, NW = T::NW;
+  constexpr int TI = WM / 32, TJ = WN / 32, STAGE = T::STAGE, STEP = NW * 8;
+  constexpr int DX = TM / STEP, DW = TN / STEP, DEP = DX + 3 * DW;   // deposits per wave per stage
+  constexpr int NG = CH / 2, NSUB = 3 * NG;                          // groups of 16 of K; a group of one product
+  constexpr int FIRST = DEP / 5, SPREAD = 4;                   // deposits issued behind the barrier; over how many parts the others go
+  static_assert(TM % STEP == 0 && TN % STEP == 0 && STEP % 16 == 0, "deposits");
+  __shared__ __attribute__((aligned(1024))) unsigned char s_buf[2 * STAGE];
+
+  const uint32_t lds0 = static_cast<uint32_t>(reinterpret_cast<uintptr_t>((__attribute__((address_space(3))) unsigned char*)s_buf));
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wm = wave / (TN / WN), wn = wave % (TN / WN);
+  const int r = lane & 31, g = lane >> 5;
+  int bm, bn;
+  tile_of(a, regrouped(blockIdx.x, gridDim.x), bm, bn);
+  const int m0 = bm * TM, n0 = bn * TN;
+
+  const int sw = swz(r);
+  const int row_a = (wm * WM + r) * ROW_B, row_b = (TM + wn * WN + r) * ROW_B;
+  int ch_k[NG];
+#pragma unroll
+  for (int q = 0; q < NG; ++q) ch_k[q] = ((2 * q + g) ^ sw) * 16;
+
+  // deposits: the tile's first row and the stage in scalar bases, a lane's row and chunk in 32-bit offsets
+  const int row0 = wave * 8 + (lane >> 3), kc = (lane & 7) ^ swz(row0);
+  uint32_t off_x[DX], off_w[DW], off_g[DW];
+  const Segment& sr = a.seg[SEG_REF];
+  const Segment& s1 = a.seg[SEG_Q];
+  const Segment& s2 = a.seg[SEG_Q + 2];
+  const auto offset = [&](int row, int last, int64_t pitch) { return static_cast<uint32_t>(row < last ? row : last) * static_cast<uint32_t>(pitch) + kc * 16; };
+#pragma unroll
+  for (int d = 0; d < DX; ++d) off_x[d] = offset(row0 + d * STEP, a.M - m0 - 1, sr.xrow);
+#pragma unroll
+  for (int d = 0; d < DW; ++d) {
+    off_w[d] = offset(row0 + d * STEP, a.N - n0 - 1, sr.wrow);
+    off_g[d] = offset(row0 + d * STEP, a.N - n0 - 1, s1.wrow);
+  }
+  const char* dep_x = static_cast<const char*>(sr.x) + m0 * sr.xrow;
+  const char* dep_w[3] = {static_cast<const char*>(sr.w) + n0 * sr.wrow, static_cast<const char*>(s1.w) + n0 * s1.wrow, static_cast<const char*>(s2.w) + n0 * s2.wrow};
+  const int stages = sr.stages;
+  int dep_left = stages - 1;       // stages behind the one that is being deposited; past the last it is fetched again, unused
+  auto next_stage = [&]() {
+    const int by = dep_left > 0 ? ROW_B : 0;
+    dep_left -= 1;
+    dep_x += by;
+#pragma unroll
+    for (int q = 0; q < 3; ++q) dep_w[q] += by;
+  };
+  auto issue = [&](int buf, int lo, int hi) {
+#pragma unroll
+    for (int d = 0; d < DEP; ++d)
+      if (d >= lo && d < hi) {
+        const uint32_t at = lds0 + static_cast<uint32_t>(buf + (wave + NW * d) * 1024);
+        if (d < DX) lds_deposit(dep_x, off_x[d], at);
+        else if ((d - DX) / DW == 0) lds_deposit(dep_w[0], off_w[(d - DX) % DW], at);
+        else lds_deposit(dep_w[(d - DX) / DW], off_g[(d - DX) % DW], at);
+      }
+  };
+
+  f32x16 acc[3][TI][TJ];
+#pragma unroll
+  for (int q = 0; q < 3; ++q)
+#pragma unroll
+    for (int i = 0; i < TI; ++i)
+#pragma unroll
+      for (int j = 0; j < TJ; ++j)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) acc[q][i][j][e] = 0.0f;
+
+  int b0 = 0, b1 = STAGE;
+  issue(b0, 0, DEP);
+  next_stage();
+  issue(b1, 0, FIRST);
+  wait_deposits_and_reads<FIRST>();
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" ::: "memory");
+
+  i32x4 fa[2][TI], fb[2][TJ];
+  auto load_a = [&](int buf, int gi) {
+#pragma unroll
+    for (int i = 0; i < TI; ++i) fa[gi & 1][i] = *reinterpret_cast<const i32x4*>(s_buf + buf + row_a + ch_k[gi] + i * 32 * ROW_B);
+  };
+  auto load_b = [&](int buf, int sub) {   // sub = 3 * group + product
+#pragma unroll
+    for (int j = 0; j < TJ; ++j) fb[sub & 1][j] = *reinterpret_cast<const i32x4*>(s_buf + buf + row_b + ch_k[sub / 3] + (sub % 3 * TN + j * 32) * ROW_B);
+  };
+  load_a(b0, 0);
+  load_b(b0, 0);
+  for (int k = 0; k < stages; ++k) {
+#pragma unroll
+    for (int sub = 0; sub < NSUB; ++sub) {
+      const int gi = sub / 3, q = sub % 3;
+      int lo = 0, hi = 0, buf = b1;
+      if (sub < SPREAD) {
+        lo = FIRST + sub * (DEP - FIRST) / SPREAD;
+        hi = FIRST + (sub + 1) * (DEP - FIRST) / SPREAD;
+      }
+      if (sub == NSUB - 1) {
+        // the next stage has landed, and nobody reads this one any more: its last fragments are in registers
+        wait_deposits_and_reads<0>();
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+        next_stage();
+        lo = 0;
+        hi = FIRST;
+        buf = b0;
+      }
+#pragma unroll
+      for (int i = 0; i < TI; ++i)
+#pragma unroll
+        for (int j = 0; j < TJ; ++j) {
+          const int m = i * TJ + j, n = hi - lo;
+          __builtin_amdgcn_sched_barrier(0);
+          if (m == (TI * TJ > 1 ? 1 : 0)) {
+            if (sub + 1 < NSUB) {
+              if (q == 2) load_a(b0, gi + 1);
+              load_b(b0, sub + 1);
+            } else {
+              load_a(b1, 0);
+              load_b(b1, 0);
+            }
+          }
+          issue(buf, lo + m * n / (TI * TJ), lo + (m + 1) * n / (TI * TJ));
+          __builtin_amdgcn_sched_barrier(0);
+          acc[q][i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, fa[gi & 1][i]), __builtin_bit_cast(bf16x8, fb[sub & 1][j]), acc[q][i][j], 0, 0, 0);
+        }
+    }
+    const int b = b0;
+    b0 = b1;
+    b1 = b;
+  }
+
+  // squared differences in fp64 (the layout and the order of wa_gemm_kernel's)
+  double e[2] = {0.0, 0.0}, p = 0.0;
+  const int row_lim = a.M - (m0 + wm * WM + 4 * g);
+#pragma unroll
+  for (int j = 0; j < TJ; ++j) {
+    const int n = n0 + wn * WN + j * 32 + r;
+    const bool col_ok = n < a.N;
+    const int ns = a.w_per_channel && col_ok ? n : 0;
+    const double c0 = static_cast<double>(a.sw[0][ns]), c1 = static_cast<double>(a.sw[1][ns]);
+#pragma unroll
+    for (int i = 0; i < TI; ++i)
+#pragma unroll
+      for (int x = 0; x < 16; ++x) {
+        const bool ok = col_ok && (i * 32 + 8 * (x / 4) + (x % 4)) < row_lim;
+        const double y = ok ? static_cast<double>(acc[0][i][j][x]) : 0.0;
+        const double d0 = __builtin_fma(-c0, ok ? static_cast<double>(acc[1][i][j][x]) : 0.0, y);
+        const double d1 = __builtin_fma(-c1, ok ? static_cast<double>(acc[2][i][j][x]) : 0.0, y);
+        e[0] = __builtin_fma(d0, d0, e[0]);
+        e[1] = __builtin_fma(d1, d1, e[1]);
+        p = __builtin_fma(y, y, p);
+      }
+  }
+  const double w[3] = {wave_sum(e[0]), wave_sum(e[1]), wave_sum(p)};
+  wait_deposits_and_reads<0>();   // the unused deposits have landed: the sums lie over the stages
+  __syncthreads();
+  double (*const s_red)[NW] = reinterpret_cast<double (*)[NW]>(s_buf);
+  if (lane < 3) s_red[lane][wave] = lane == 0 ? w[0] : (lane == 1 ? w[1] : w[2]);
+  __syncthreads();
+  if (tid < 3 && a.part[tid]) {
+    double t = 0.0;
+    for (int k = 0; k < NW; ++k) t += s_red[tid][k];   // fixed order
+    a.part[tid][bm * a.tiles_n + bn] = t;
+  }
+}
+
 using Large = Tile<256, 128, 64, 64>;    // one workgroup per compute unit, two waves per SIMD
 using Medium = Tile<128, 128, 64, 64>;   // one, one wave per SIMD
 using Small = Tile<64, 64, 32, 32>;      // three
+using SharedLarge = SharedTile<256, 128, 64, 64>;
+using SharedMedium = SharedTile<128, 128, 64, 32>;
+using SharedSmall = SharedTile<64, 64, 32, 32>;
 
 }  // namespace
 
@@ -595,7 +788,11 @@ using Small = Tile<64, 64, 32, 32>;      // three
 // 64 x 4096 x 4096 (64) 76 / 56 / 58; 128 x 4096 x 11008 (128) 217 / 166 / 182; 256 x 4096 x 11008 (256) 227 / 232 / 256,
 // into the products alone 226; 256 x 1024 x 4096 (64) 65 / 42 / 43; 1024 x 1024 x 4096 (256) 71 / 69 / 73.  The second
 // launch costs what short products save: 64 x 1024 x 1024 29.4 / - / 30.2, 128 x 8192 x 1024 40 / 44 / 44.
-constexpr int64_t kUnits = 256;
+//
+// Products that share X (wa_gemm_shared_kernel) take the same tiles, and are cut up to 160 small tiles only: into the products
+// alone / whole 256 x 4096 x 4096 75.8 / 73.0 us, 300 x 3000 x 2048 45.1 / 43.9, 64 x 11008 x 2560 88.7 / 83.8, but 64 x 10240 x 2560
+// (160 tiles) 77.7 / 81.6, 64 x 4096 x 2048 (64) 35.4 / 42.8.
+constexpr int64_t kUnits = 256, kProductsOnly = 160;
 WaPlan wa_gemm_plan(int64_t M, int64_t N, int64_t K, int64_t ldx, int64_t ldw) {
   auto tiles = [&](auto t) { using T = decltype(t); return ((M + T::TM - 1) / T::TM) * ((N + T::TN - 1) / T::TN); };
   const int64_t large = tiles(Large{}), medium = tiles(Medium{}), small = tiles(Small{});
@@ -617,7 +814,7 @@ WaPlan wa_gemm_plan(int64_t M, int64_t N, int64_t K, int64_t ldx, int64_t ldw) {
   if (p.tile == WaPlan::kSmall && small <= kUnits && stages >= 20) {
     // (at most 16 or 8 pieces of a product, which bounds the scratch: 40 MB or 64 MB)
     const int64_t run = small <= 48 ? std::max(std::min<int64_t>(20, (stages + 1) / 2), (stages + 15) / 16)
-                                    : (small <= 160 ? std::max<int64_t>(40, (stages + 7) / 8) : stages);
+                                    : (small <= kProductsOnly ? std::max<int64_t>(40, (stages + 7) / 8) : stages);
     p.run = static_cast<int>(run);
     p.partial_bytes = static_cast<size_t>(3 * ((stages + run - 1) / run) * small) * (Small::TM * Small::TN * sizeof(float));
   }
@@ -650,28 +847,38 @@ int launch_wa_gemm(const WaGemmParams& p, hipStream_t st) {
   const WaPlan plan = wa_gemm_plan(p.M, p.N, p.K, p.ldx, p.ldw);
   auto launch = [&](auto k1_c, auto k2_c) {
     constexpr int K1 = decltype(k1_c)::value, K2 = decltype(k2_c)::value;
-    auto tiled = [&](auto tile_c, auto kernel) {
+    auto tiled = [&](auto tile_c, auto kernel, int pieces = 1) {
       using T = decltype(tile_c);
       a.tiles_m = static_cast<int32_t>((p.M + T::TM - 1) / T::TM);
       a.tiles_n = static_cast<int32_t>((p.N + T::TN - 1) / T::TN);
-      hipLaunchKernelGGL(kernel, dim3(static_cast<unsigned>(plan.blocks * (plan.run ? a.piece0[3] : 1))), dim3(T::NW * 64), 0, st, a);
+      hipLaunchKernelGGL(kernel, dim3(static_cast<unsigned>(plan.blocks * pieces)), dim3(T::NW * 64), 0, st, a);
     };
-    switch (plan.tile) {
-      case WaPlan::kLarge: tiled(Large{}, wa_gemm_kernel<Large, K1, K2, false, false>); break;
-      case WaPlan::kMedium: tiled(Medium{}, wa_gemm_kernel<Medium, K1, K2, false, false>); break;
-      case WaPlan::kWide: tiled(Small{}, wa_gemm_kernel<Small, K1, K2, false, true>); break;
-      default:
-        if (!plan.run) {
-          tiled(Small{}, wa_gemm_kernel<Small, K1, K2, false, false>);
-        } else {
-          for (int q = 0; q < 3; ++q) {
-            const int stages = q == 0 ? a.seg[SEG_REF].stages : a.seg[SEG_Q + 2 * (q - 1)].stages;
-            a.piece0[q + 1] = a.piece0[q] + (stages + plan.run - 1) / plan.run;
-          }
-          a.partial = static_cast<float*>(p.partial);
-          tiled(Small{}, wa_gemm_kernel<Small, K1, K2, true, false>);
-          hipLaunchKernelGGL((wa_pieces_kernel<Small, K1, K2>), dim3(static_cast<unsigned>(plan.blocks)), dim3(Small::NW * 64), 0, st, a);
-        }
+    constexpr bool SHARED = K1 == WA_GRID_BF16 && K2 == WA_GRID_BF16;
+    if constexpr (SHARED) {   // all three products take the unquantized X
+      if (p.q[0].x != p.x || p.q[1].x != p.x || p.ldx != p.K || p.q[0].sx || p.q[1].sx) return static_cast<int>(MOFQ_ERR_UNSUPPORTED);
+    }
+    if (plan.tile == WaPlan::kWide) {
+      tiled(Small{}, wa_gemm_kernel<Small, K1, K2, false, true>);
+    } else if (plan.run && !(SHARED && plan.blocks > kProductsOnly)) {
+      for (int q = 0; q < 3; ++q) {
+        const int stages = q == 0 ? a.seg[SEG_REF].stages : a.seg[SEG_Q + 2 * (q - 1)].stages;
+        a.piece0[q + 1] = a.piece0[q] + (stages + plan.run - 1) / plan.run;
+      }
+      a.partial = static_cast<float*>(p.partial);
+      tiled(Small{}, wa_gemm_kernel<Small, K1, K2, true, false>, a.piece0[3]);
+      hipLaunchKernelGGL((wa_pieces_kernel<Small, K1, K2>), dim3(static_cast<unsigned>(plan.blocks)), dim3(Small::NW * 64), 0, st, a);
+    } else if constexpr (SHARED) {
+      switch (plan.tile) {
+        case WaPlan::kLarge: tiled(SharedLarge{}, wa_gemm_shared_kernel<SharedLarge>); break;
+        case WaPlan::kMedium: tiled(SharedMedium{}, wa_gemm_shared_kernel<SharedMedium>); break;
+        default: tiled(SharedSmall{}, wa_gemm_shared_kernel<SharedSmall>);
+      }
+    } else {
+      switch (plan.tile) {
+        case WaPlan::kLarge: tiled(Large{}, wa_gemm_kernel<Large, K1, K2, false, false>); break;
+        case WaPlan::kMedium: tiled(Medium{}, wa_gemm_kernel<Medium, K1, K2, false, false>); break;
+        default: tiled(Small{}, wa_gemm_kernel<Small, K1, K2, false, false>);
+      }
     }
     return hip_status(hipGetLastError());
   };

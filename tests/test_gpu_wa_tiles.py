@@ -54,6 +54,16 @@ def test_weight_only_products(mq, name):
     wo.check_layer(mq, x, w, [I4, FP4], orc.PER_CHANNEL, mi.clip_ratios(1), name)
 
 
+# One stage of 64 columns, two, three and an odd number more, in each tile of the products that share X, with rows of W apart.
+@pytest.mark.parametrize("shape", [(65, 63, 64), (65, 63, 128), (1601, 1345, 64), (1601, 1345, 64 * 7), (2049, 2049, 64), (2049, 2049, 192)])
+def test_weight_only_products_share_the_input(mq, shape):
+    M, N, K = shape
+    x, w = tensors(shape, 8250)
+    apart = torch.full((N, K + 72), float("nan"), dtype=torch.bfloat16, device=DEV)[:, :K]
+    apart.copy_(w)
+    wo.check_layer(mq, x, apart, [FP4, I4], orc.PER_CHANNEL, mi.clip_ratios(1), shape)
+
+
 @pytest.mark.parametrize("name", list(SHAPES))
 def test_fp8_unit_products(mq, name):
     M, N, K = SHAPES[name]
