@@ -29,12 +29,22 @@ struct SortedArgs {
   // for b = 0..6.  Entry 7 is INT4's extra boundary (|t| below it: a negative element stays on -7)
   // with the weights of the step from 7 to 8; unused (zero weights) for E2M1.
   float thr[2][8];
-  float thr_est[2][8];   // histogram kernel: a shade below thr (see threshold_pattern)
+  float thr_est[2][8];   // histogram kernels: a shade below thr
+  double thr_edge[2][8]; // histogram kernels: between the last product that rounds to thr and the first beyond (decision_edge)
   double dgd[2][8];   // m_b - m_{b+1};  entry 7: 8 - 7
   int32_t dg2q[2][8]; // 4 (m_b^2 - m_{b+1}^2): an integer for every 4-bit format;  entry 7: 4 (64 - 49)
   float g_last[2];    // m_7
   float g_absmax[2];  // largest |level|
 };
+
+// Where the exact products |x| * inv that round to thr or below end, as a number that none of them is near: half an ulp above
+// thr, which itself rounds to the even neighbour, moved by 2^-40 to the side that the tie belongs to.  A product has 35 bits
+// at most and that midpoint 25, so products other than the tie are 2^-36 and more away from it.
+constexpr double decision_edge(float thr) {
+  const uint32_t u = __builtin_bit_cast(uint32_t, thr);
+  const double mid = 0.5 * (static_cast<double>(thr) + static_cast<double>(__builtin_bit_cast(float, u + 1u)));
+  return mid * (u & 1u ? 1.0 - 0x1p-40 : 1.0 + 0x1p-40);
+}
 
 // How many bit patterns lie between a threshold t = c * amax and amax at most: a pattern is
 // (exponent, mantissa) read as an integer, i.e. PPB * (log2 of the value + a term in [0, 0.0861))
@@ -141,8 +151,45 @@ template <> MOFQ_DEV uint32_t pattern_rtz<F16>(float x) {
 }
 template <> MOFQ_DEV uint32_t pattern_rtz<BF16>(float x) { return f2u(x) >> 16; }
 template <typename In> struct Pattern;
-template <> struct Pattern<F16> { static constexpr int MANT = 10; };
-template <> struct Pattern<BF16> { static constexpr int MANT = 7; };
+template <> struct Pattern<F16> { static constexpr int MANT = 10, BIAS = 15; };
+template <> struct Pattern<BF16> { static constexpr int MANT = 7, BIAS = 127; };
+
+// 4-bit formats: log2 of twice the step from level q to the next, and 4 (m_{q+1}^2 - m_q^2)
+template <int FMT> constexpr int half_steps_log2(int q) { return FMT == MOFQ_INT4 ? 1 : (q < 4 ? 0 : (q < 6 ? 1 : 2)); }
+template <int FMT> constexpr uint32_t quad_step(int q) {
+  constexpr uint32_t e2m1[7] = {1, 3, 5, 7, 20, 28, 80};
+  return FMT == MOFQ_INT4 ? 8u * static_cast<uint32_t>(q) + 4u : (q < 7 ? e2m1[q] : 0u);
+}
+
+// ---- the largest pattern that a decision passes --------------------------------------------------------
+// fl32(|x| * inv) <= thr, inv = fl32(1 / s): the elements that pass are those up to decision_edge(thr) / inv, and
+// 1 / inv = s + s (1 - s inv) to 2^-48 (|1 - s inv| <= 2^-24; both steps are exact but for the last rounding).  The
+// quotient in fp64 is cut off at the input type's mantissa by taking the top of its bits: exponent and mantissa
+// are the pattern but for the difference of the biases.  Three instructions a boundary, against seven for a rounded
+// estimate and the decision itself on the next pattern.  Holds for normal numbers of the input type; a quotient
+// below the smallest one gives a number below its pattern.
+MOFQ_DEV double edge_unit(float s, float inv) {
+  const double sd = static_cast<double>(s);
+  return __builtin_fma(sd, __builtin_fma(-sd, static_cast<double>(inv), 1.0), sd);
+}
+template <typename In> constexpr int kPatternBase = (1023 - Pattern<In>::BIAS) << Pattern<In>::MANT;
+// How many patterns from one on pass; before: pattern_before of that one.
+template <typename In> MOFQ_DEV int pattern_before(int first) {
+  int b = __builtin_amdgcn_readfirstlane(first + kPatternBase<In> - 1);
+  asm("" : "+s"(b));   // opaque: one subtraction
+  return b;
+}
+template <typename In> MOFQ_DEV int pattern_top(double edge, double unit) {
+  return static_cast<int>(static_cast<uint32_t>(__builtin_bit_cast(uint64_t, edge * unit) >> 32) >> (20 - Pattern<In>::MANT));
+}
+template <typename In> MOFQ_DEV int patterns_below(double edge, double unit, int before) { return pattern_top<In>(edge, unit) - before; }
+
+// 1 / s, correctly rounded for s in [2^-126, 2^125] (all of them checked): the hardware's reciprocal and one step of
+// Newton's iteration r + r (1 - s r).
+MOFQ_DEV float reciprocal(float s) {
+  const float r = __builtin_amdgcn_rcpf(s);
+  return __builtin_fmaf(__builtin_fmaf(-s, r, 1.0f), r, r);
+}
 
 // Lexicographic minimum of (value, index) over the wave by data-parallel-primitive moves: the
 // smallest value (no NaN among the inputs), then the smallest index among the lanes that hold it.

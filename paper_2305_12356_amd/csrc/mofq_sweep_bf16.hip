@@ -4,19 +4,18 @@
 // are few (about 760 for INT4 / E2M1 over ratios in [0.5, 1], about 2600 for E4M3, whose
 // subnormals reach 20 binades down) and the count and the sum of magnitudes of the elements below
 // each of them fit in LDS, packed into 64 bits: count << 48 | sum in units of the first counted
-// pattern's ulp.  Both are exact.  A look-up (candidate, level boundary) is then one threshold decision, one
-// 8-byte read and four integer operations, 13 vector instructions in all against 38 of the group
+// pattern's ulp.  Both are exact.  A look-up (candidate, level boundary) is then the boundary's pattern (patterns_below), one
+// 8-byte read and three integer operations, 8 vector instructions in all against 22 of the group
 // records, which makes the 127 boundaries of an 8-bit format cheap: scoring every (element, candidate)
 // pair takes 4.8 instructions per element, candidate and format (240 000 per wave lane for a row of
-// 5000 elements and 50 candidates; here a wave issues 2318 instructions in all, in the 4-bit search with
-// 100 candidates 925).  Bound by vector issue and, at 8 bits, by the LDS reads of the look-ups beside it (their
+// 5000 elements and 50 candidates; here a wave issues 1960 instructions in all).  Bound by vector issue and, at 8 bits, by the LDS reads of the look-ups beside it (their
 // bank conflicts take 41 % of the LDS's cycles).
 // The error that leaves for an 8-bit format is the winner's element-wise sum (finish_row): the look-ups
 // choose it, and their difference of large sums would keep four digits fewer (1e-12 instead of 1e-15 on 5000 elements).
 // The prefixes lie over the counters they are formed from (a thread holds its share in registers meanwhile), so that
 // six workgroups of the 8-bit search fit a compute unit instead of five.
-// Measured, layer selection: INT8 against E4M3, 3001 x 5000, 50 ratios 277 -> 69.8 -> 66.4 us (the last step: prefixes over
-// the counters); 4096 x 11008, 100 ratios 1294 -> 141 us; INT4 against E2M1, 1237 x 5000, 100 ratios: 28.2 -> 25.6 us.
+// Measured, layer selection: INT8 against E4M3, 3001 x 5000, 50 ratios 277 -> 69.8 -> 66.0 (prefixes over
+// the counters) -> 62.0 us (patterns_below, weights of the counts by dot products: 13 -> 8 instructions a look-up); 4096 x 11008, 100 ratios 1294 -> 141 us; INT4 against E2M1, 1237 x 5000, 100 ratios: 28.2 -> 25.6 -> 23.8 us.
 //
 // fp16 rows (8-bit formats) have eight times the patterns, up to 20300 below the largest for E4M3: a prefix per group of
 // 8, packed alike, and a look-up adds the group's first counters, 36 instructions.  Counters and prefixes take 61 KB, so
@@ -39,10 +38,11 @@ constexpr int kMaxBins = 4096, kMaxTailBins = 1024;             // bf16
 constexpr int kMaxHalfBins = 24576, kMaxHalfTailBins = 2048;    // fp16
 constexpr int kRuns = 16;   // runs of 8 boundaries of an 8-bit format
 
-// Decision thresholds of the 8-bit formats' boundaries: level magnitude m_b or below <=> t <= thr; est: a
-// shade below (counters_below).  Run r, boundary i between code 8 r + i and the next; ties to the even code.
+// Decision thresholds of the formats' boundaries: level magnitude m_b or below <=> t <= thr; est: a
+// shade below, edge: decision_edge(thr) (counters_below).  Run r, boundary i between code 8 r + i and the next; ties to the even code.
 struct Boundary {
   float est, thr;
+  double edge;
 };
 struct BoundaryTable {
   Boundary b[kRuns][8];
@@ -52,9 +52,9 @@ constexpr float prev_float(float x) { return __builtin_bit_cast(float, __builtin
 constexpr Boundary boundary(double mid, bool up_is_even) {
   const float m = static_cast<float>(mid);   // exact
   const float thr = up_is_even ? prev_float(m) : m;
-  return Boundary{static_cast<float>(thr * (1.0 - 0x1p-21)), thr};
+  return Boundary{static_cast<float>(thr * (1.0 - 0x1p-21)), thr, decision_edge(thr)};
 }
-constexpr Boundary kBeyond{static_cast<float>(kInfinity), static_cast<float>(kInfinity)};
+constexpr Boundary kBeyond{static_cast<float>(kInfinity), static_cast<float>(kInfinity), kInfinity};
 constexpr BoundaryTable int8_table() {
   BoundaryTable t{};
   for (int r = 0; r < kRuns; ++r)
@@ -96,6 +96,12 @@ template <> struct Runs<MOFQ_FP8_E4M3> {
   MOFQ_DEV static double spacing(int r) { return __builtin_bit_cast(double, static_cast<uint64_t>(1023 - 9 + (r > 0 ? r - 1 : 0)) << 52); }   // 2^(max(r, 1) - 10)
   MOFQ_DEV static int base(int r) { return r > 0 ? 8 : 0; }
 };
+
+MOFQ_DEV int clamped(int x, int lo, int hi) {   // one instruction
+  int r;
+  asm("v_med3_i32 %0, %1, %2, %3" : "=v"(r) : "v"(x), "s"(lo), "v"(hi));
+  return r;
+}
 
 // Exclusive prefixes over the counters, P[0 .. nbin], packed count << 48 | sum.  Thread `id` of
 // NW waves takes the counters [id pp, (id + 1) pp), pp even and at most 2 PWMAX.  NW > 1: by the whole workgroup, with
@@ -358,16 +364,28 @@ void sweep_pattern_kernel(const SortedArgs a) {
 
   // ---- level boundaries: one lane per candidate; a wave takes (format, 64 candidates, part of the runs) ----
   {
-    // H = the largest pattern h with fl32(v(h) * inv) <= thr, as in the histogram kernel: the pattern of
-    // est * s rounded toward zero passes, one decision on the next tells.  Returns H - first + 1 as
-    // a number of counters; negative numbers are large ones to the unsigned minimum.
-    auto counters_below = [](float est, float thr, float s, float inv, int first) {
+    // A candidate's scale, and what its boundaries are looked for with.
+    struct Candidate {
+      float s, inv;
+      double per_edge;
+    };
+    auto candidate = [&](int f, int k) {
+      const float s = sh.scale[f][k < K ? k : K - 1];
+      const float inv = HALF ? reciprocal(s) : 1.0f / s;
+      return Candidate{s, inv, edge_unit(s, inv)};
+    };
+    const int before_lo = pattern_before<In>(lo), before_tlo = pattern_before<In>(tlo);
+    // H = the largest pattern h with fl32(v(h) * inv) <= thr, as in the histogram kernel.  Returns H - first + 1 as
+    // a number of counters; negative numbers are large ones to the unsigned minimum.  Where subnormals are counted: the
+    // pattern of est * s rounded toward zero passes, one decision on the next tells.
+    auto counters_below = [](auto normal_tag, const Boundary& b, const Candidate& c, int first, int before) {
+      if constexpr (decltype(normal_tag)::value) return patterns_below<In>(b.edge, c.per_edge, before);
       if constexpr (HALF) {
-        const int h = static_cast<int>(pattern_rtz<F16>(est * s));
-        return h + (1 - first) + (scaled<F16>(static_cast<uint32_t>(h + 1), inv) <= thr ? 1 : 0);
+        const int h = static_cast<int>(pattern_rtz<F16>(b.est * c.s));
+        return h + (1 - first) + (scaled<F16>(static_cast<uint32_t>(h + 1), c.inv) <= b.thr ? 1 : 0);
       }
-      const uint32_t x1 = f2u(est * s) + 0x10000u;
-      const bool above = u2f(x1 & 0xFFFF0000u) * inv <= thr;
+      const uint32_t x1 = f2u(b.est * c.s) + 0x10000u;
+      const bool above = u2f(x1 & 0xFFFF0000u) * c.inv <= b.thr;
       return static_cast<int>(x1 >> 16) - first + (above ? 1 : 0);
     };
     // count and sum of the elements in the first n1 counters
@@ -379,15 +397,27 @@ void sweep_pattern_kernel(const SortedArgs a) {
         return R[n1];
       }
     };
+    // those in the counters below a boundary of the row; below_first: the boundary lies beneath all of them
+    const uint32_t cells_at = static_cast<uint32_t>(reinterpret_cast<uintptr_t>((__attribute__((address_space(3))) uint64_t*)P)) - 8u * static_cast<uint32_t>(before_lo);
+    auto up_to = [&](auto normal_tag, const Boundary& b, const Candidate& c, bool& below_first) {
+      if constexpr (decltype(normal_tag)::value && !HALF) {   // the difference of the patterns is in the address
+        const int top = pattern_top<In>(b.edge, c.per_edge);
+        below_first = top < before_lo;
+        return *(__attribute__((address_space(3))) uint64_t*)static_cast<uintptr_t>(cells_at + 8u * static_cast<uint32_t>(clamped(top, before_lo, before_lo + nbin)));
+      }
+      const int n1 = counters_below(normal_tag, b, c, lo, before_lo);
+      below_first = n1 < 0;
+      return first_counters(P, counters, lo, min(static_cast<uint32_t>(n1), static_cast<uint32_t>(nbin)));
+    };
     const int chunks = (K + 63) >> 6;
     // few units: the runs of an 8-bit format are dealt to all waves, whose partial sums meet in LDS
     const int parts = EIGHT ? kNW / (NF * chunks) : 1;   // 4, 2 or 1
     double A = 0.0, B = 0.0, ca_tail = 0.0;
     bool bad = false;
     int cb_tail = 0;
-    auto tail = [&](const int first_level, float est, float thr, float s, float inv) {
+    auto tail = [&](auto normal_tag, const int first_level, const Boundary& b, const Candidate& c) {
       // negative elements beyond the last positive level's upper boundary sit one level further
-      const int n1 = counters_below(est, thr, s, inv, tlo);
+      const int n1 = counters_below(normal_tag, b, c, tlo, before_tlo);
       bad |= n1 < 0;
       const uint64_t above = TP[n_trec] - first_counters(TP, tcounters, tlo, min(static_cast<uint32_t>(n1), static_cast<uint32_t>(ntbin)));
       const float v_tlo = bits_to_float<In>(static_cast<uint32_t>(tlo));
@@ -403,10 +433,9 @@ void sweep_pattern_kernel(const SortedArgs a) {
         sh.fast[f][k] = bad ? __builtin_nan("") : v;
       }
     };
-    auto search8 = [&](auto fmt_c, const int f, const int k, const int part) {
+    auto search8 = [&](auto normal_tag, auto fmt_c, const int f, const int k, const int part) {
       constexpr int FMT = decltype(fmt_c)::value;
-      const float s = sh.scale[f][k < K ? k : K - 1];
-      const float inv = 1.0f / s;
+      const Candidate c = candidate(f, k);
       A = B = ca_tail = 0.0;
       bad = false;
       cb_tail = 0;
@@ -414,57 +443,64 @@ void sweep_pattern_kernel(const SortedArgs a) {
       const int runs = kRuns / parts;
       for (int r = part * runs; r < (part + 1) * runs; ++r) {
         uint64_t sums = 0;
-        int ib = 0;
-        const int base2 = 2 * Runs<FMT>::base(r) + 1;
+        uint32_t ib = 0;
+        const uint32_t base2 = 2 * Runs<FMT>::base(r) + 1;
 #pragma unroll
         for (int i = 0; i < 8; ++i) {
-          const int n1 = counters_below(t.b[r][i].est, t.b[r][i].thr, s, inv, lo);
+          bool below_first;
+          const uint64_t p = up_to(normal_tag, t.b[r][i], c, below_first);
           // the smallest threshold: nothing uncounted above it, and no subnormal product (too coarse an estimate)
-          if (i == 0 && r == 0) bad = n1 < 0 || !(t.b[0][0].est * s >= 0x1p-126f);
-          const uint64_t p = first_counters(P, counters, lo, min(static_cast<uint32_t>(n1), static_cast<uint32_t>(nbin)));
+          if (i == 0 && r == 0) bad = below_first || (!decltype(normal_tag)::value && !(t.b[0][0].est * c.s >= 0x1p-126f));
           sums += p;      // (the counts overflow out of the word)
-          ib += __mul24(static_cast<int>(count_of(p)), base2 + 2 * i);
+          ib = dot2(static_cast<uint32_t>(p >> 32), (base2 + 2 * i) << 16, ib);   // the count, in the upper half, times its weight
         }
         const double d = Runs<FMT>::spacing(r);
         A = __builtin_fma(-d, sum_of(sums), A);
-        B = __builtin_fma(-d * d, static_cast<double>(ib), B);
+        B = __builtin_fma(-d * d, static_cast<double>(static_cast<int>(ib)), B);
       }
       if constexpr (Codec<FMT>::IS_INT)
-        if (part == 0) tail(127, static_cast<float>((127.5 - 0x1p-17) * (1.0 - 0x1p-21)), static_cast<float>(127.5 - 0x1p-17), s, inv);
-      if (parts == 1) finish(f, k, s, Runs<FMT>::LAST);
+        if (part == 0) tail(normal_tag, 127, boundary(127.5, true), c);
+      if (parts == 1) finish(f, k, c.s, Runs<FMT>::LAST);
     };
-    auto search4 = [&](auto fmt_c, const int f, const int k) {
+    auto search4 = [&](auto normal_tag, auto fmt_c, const int f, const int k) {
       constexpr int FMT = decltype(fmt_c)::value;
-      const float s = sh.scale[f][k < K ? k : K - 1];
-      const float inv = 1.0f / s;
+      const Candidate c = candidate(f, k);
       A = B = ca_tail = 0.0;
       bad = false;
       cb_tail = 0;
-      int cb4 = 0;       // 4 sum_b (count up to boundary b) (m_b^2 - m_{b+1}^2): an integer below 2^31
+      // In half levels: sum_b (sum up to boundary b) 2 (m_{b+1} - m_b), steps of 1, 2 or 4 (pattern_search_fits: below 2^48),
+      // and sum_b (count up to boundary b) 4 (m_{b+1}^2 - m_b^2)
+      uint64_t sums = 0;
+      uint32_t cb4 = 0;
 #pragma unroll
       for (int q = 0; q < 7; ++q) {
-        const int n1 = counters_below(a.thr_est[f][q], a.thr[f][q], s, inv, lo);
-        if (q == 0) bad = n1 < 0;
-        const uint64_t p = first_counters(P, counters, lo, min(static_cast<uint32_t>(n1), static_cast<uint32_t>(nbin)));
-        A = __builtin_fma(sum_of(p), a.dgd[f][q], A);
-        cb4 = __mul24(static_cast<int>(count_of(p)), a.dg2q[f][q]) + cb4;
+        bool below_first;
+        const uint64_t p = up_to(normal_tag, Boundary{a.thr_est[f][q], a.thr[f][q], a.thr_edge[f][q]}, c, below_first);
+        if (q == 0) bad = below_first;
+        sums += p << half_steps_log2<FMT>(q);
+        cb4 = dot2(static_cast<uint32_t>(p >> 32), static_cast<uint32_t>(-a.dg2q[f][q]) << 16, cb4);
       }
-      B = 0.25 * static_cast<double>(cb4);
-      if constexpr (Codec<FMT>::IS_INT) tail(7, a.thr_est[f][7], a.thr[f][7], s, inv);
-      finish(f, k, s, static_cast<double>(a.g_last[f]));
+      A = -0.5 * sum_of(sums);
+      B = -0.25 * static_cast<double>(static_cast<int>(cb4));
+      if constexpr (Codec<FMT>::IS_INT) tail(normal_tag, 7, Boundary{a.thr_est[f][7], a.thr[f][7], a.thr_edge[f][7]}, c);
+      finish(f, k, c.s, static_cast<double>(a.g_last[f]));
     };
-    for (int u = wave; u < NF * chunks * parts; u += kNW) {   // wave-uniform
-      const int part = u % parts, fc = u / parts;
-      const int f = fc / chunks;
-      const int k = (fc - f * chunks) * 64 + lane;
-      if constexpr (EIGHT) {
-        if (f == 0) search8(std::integral_constant<int, FA>{}, f, k, part);
-        else search8(std::integral_constant<int, FBX>{}, f, k, part);
-      } else {
-        if (f == 0) search4(std::integral_constant<int, FA>{}, f, k);
-        else search4(std::integral_constant<int, FBX>{}, f, k);
+    auto search = [&](auto normal_tag) {
+      for (int u = wave; u < NF * chunks * parts; u += kNW) {   // wave-uniform
+        const int part = u % parts, fc = u / parts;
+        const int f = fc / chunks;
+        const int k = (fc - f * chunks) * 64 + lane;
+        if constexpr (EIGHT) {
+          if (f == 0) search8(normal_tag, std::integral_constant<int, FA>{}, f, k, part);
+          else search8(normal_tag, std::integral_constant<int, FBX>{}, f, k, part);
+        } else {
+          if (f == 0) search4(normal_tag, std::integral_constant<int, FA>{}, f, k);
+          else search4(normal_tag, std::integral_constant<int, FBX>{}, f, k);
+        }
       }
-    }
+    };
+    if (lo >= (1 << Pattern<In>::MANT)) search(std::true_type{});   // no subnormal has a counter
+    else search(std::false_type{});
     if constexpr (EIGHT) {
       if (parts > 1) {   // one unit per wave: its sums are still in its registers
         double* const s_part = reinterpret_cast<double*>(P);   // [wave][64][2], over the prefixes
@@ -522,7 +558,7 @@ int launch_shape(const SortedArgs& a, int64_t total_rows, hipStream_t st) {
 }  // namespace
 
 // The packed prefixes hold it: sums below 2^45 units (an element is below 2^(1 + mantissa bits + binades); eight prefixes
-// are added up in 48 bits); LDS for three workgroups (fp16: two); room for the partial sums of a divided search.
+// are added up in 48 bits, those of a 4-bit format with weights of 14 together); LDS for three workgroups (fp16: two); room for the partial sums of a divided search.
 bool pattern_search_fits(const SweepParams& p, int nbin, int ntbin) {
   const bool eight = p.fmt[0] == MOFQ_INT8 || p.fmt[0] == MOFQ_FP8_E4M3;
   if (p.dtype == MOFQ_F16) {
@@ -533,7 +569,7 @@ bool pattern_search_fits(const SweepParams& p, int nbin, int ntbin) {
   if (p.dtype != MOFQ_BF16 || nbin <= 0 || nbin > kMaxBins || ntbin > kMaxTailBins) return false;
   const int span = (std::max(nbin, ntbin) + 127) / 128;
   if (eight && nbin < 512) return false;
-  return span <= 22 && (p.cols << (8 + span)) <= (int64_t{1} << 45) && p.cols <= 24576;
+  return span <= 22 && (p.cols << (8 + span)) <= (int64_t{1} << (eight ? 45 : 44)) && p.cols <= 24576;
 }
 
 int launch_sweep_pattern(const SweepParams& p, const SortedArgs& a, int64_t total_rows, hipStream_t st) {

@@ -99,13 +99,6 @@ template <int FMT> MOFQ_DEV float search_scale(float ra, bool f16) {
   return s;
 }
 
-// 1 / s, correctly rounded for s in [2^-126, 2^125] (all of them checked): the hardware's reciprocal and one step of
-// Newton's iteration r + r (1 - s r).  A group with a larger scale is scored exactly, with the division.
-MOFQ_DEV float reciprocal(float s) {
-  const float r = __builtin_amdgcn_rcpf(s);
-  return __builtin_fmaf(__builtin_fmaf(-s, r, 1.0f), r, r);
-}
-
 // what a lane of the wave wrote to LDS is there for the others: LDS operations of a wave are in order
 MOFQ_DEV void wave_fence() {
   asm volatile("" ::: "memory");
@@ -366,7 +359,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(kWaves<In, W
     // to the exact pass.  (The patterns span more than the boundaries do, so the lower limit is the smaller one.)
     const float s = med3(s0, v_lo * Lv::kAbove, v_max * Lv::kBelow);
     bad |= s != s0;
-    const float inv = reciprocal(s);
+    const float inv = reciprocal(s);   // (a group with a larger scale than that takes is scored exactly, with the division)
     // The largest pattern at or below the boundary (threshold t s): the pattern of t s (1 + 2^-21) rounded toward
     // zero or the one before it, as the exact decision on the first tells; patterns above are beyond t s (1 + 2^-22), those
     // below short of t s (1 - 2^-22), whatever the rounding of 1 / s and of the product.

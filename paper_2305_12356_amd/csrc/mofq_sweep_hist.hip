@@ -10,7 +10,7 @@
 // counts the elements per pattern (16-bit counters, two per word, LDS adds), forms count and
 // magnitude-sum prefixes over groups of 8 patterns (a group shares its exponent, so its elements'
 // magnitudes are v0 + i ulp and its sum is v0 C + ulp sum i c_i, exact in fp64), finds H from
-// an fp32 estimate and one exact decision, and reads count and sum up to H from the group
+// a product in fp64 (patterns_below), and reads count and sum up to H from the group
 // prefix and one 16-byte read of the group's counters.  Only the patterns between the smallest
 // threshold and the row's largest magnitude get a counter: elements below every threshold sit on
 // level 0 for every candidate and drop out of both level sums.  How many patterns that is
@@ -21,11 +21,13 @@
 // Where the counted patterns span few enough binades, sums of magnitudes are 32-bit integers in units
 // of the first counted pattern's ulp (exact, and a third of the instructions of fp64 sums); else fp64.
 //
-// Bound by vector issue: 1008 instructions per wave on rows of 4096 elements (INT4 / E2M1, 100 ratios, codes
-// included): 200 to count, 180 for the prefixes, 310 for the look-ups; they take 611 000 clocks per SIMD of a
-// launch of 38400 rows and 299 us (85 % of it at 2.4 GHz, all but a twentieth at the 2.1 to 2.25 GHz of such a load).  Two blocks of the 65B shape 2295 -> 2222 us, eight of the 7B shape 3094 -> 2957 us with the
+// Bound by vector issue: 963 instructions per wave on rows of 4096 elements (INT4 / E2M1, 100 ratios, codes
+// included): 245 to count, 160 for the prefixes, 205 for the look-ups; they take 805 000 of the 897 000 clocks per SIMD of a
+// launch of 53500 rows.  Two blocks of the 65B shape 2295 -> 2222 us, eight of the 7B shape 3094 -> 2957 us with the
 // negative elements' counting behind the loop (note_negative), the halves of a word selected by
-// the instructions that use them (count_pair) and one weighted sum per group (count8).
+// the instructions that use them (count_pair) and one weighted sum per group (count8); 2218 -> 2161 and 2953 -> 2845 us
+// with look-ups of 22 instead of 32 instructions (patterns_below instead of an estimate and a decision, weights that are zero
+// where masks were) whose reads are requested one look-up ahead (in a loop, a look-up at a time: 2190 and 2884).
 //
 // Filter, shortlist and exact fp64 re-score are those of the sorting kernel; the re-score reads
 // the row again.  With AheadCodes the row's codes are written at the end, from a further read that
@@ -42,7 +44,7 @@ namespace {
 // (m + i) << shift in units of the ulp of pattern lo (Narrow) or v0 + i ulp (Wide).
 struct Narrow {
   using sum_t = uint32_t;
-  uint32_t sum, word;   // word: count (16 bits) | m (11) | shift (5)
+  uint32_t sum, word;   // word: count (16 bits) | m (11) | shift (5: where a shift takes its amount from)
 };
 struct Wide {
   using sum_t = double;
@@ -53,33 +55,55 @@ struct Wide {
 // Count and magnitude sum of the elements in the histogram's first n1 counters, 0 <= n1 <= nbin:
 // the record of group n1 / 8 plus the first n1 % 8 counters of that group (n1 = nbin reads the 16
 // bytes after the counters, which are inside the workgroup's LDS, and masks them all).
-// keep[c]: masks of the first c of a group's eight counters (a table in LDS: one read instead of
-// sixteen compare-and-select instructions).
-template <typename In, bool JOINT>
-MOFQ_DEV void hist_prefix(const uint32_t* hist, const Narrow* rec, const u32x4* keep, int, uint32_t n1, uint32_t& C, uint32_t& S) {
-  uint32_t g = n1 >> 3;
-  asm("" : "+v"(g));   // opaque: both addresses are one shift-add of g (of n1 they would be a shift, a mask and an addition)
-  const u32x4 w = *reinterpret_cast<const u32x4*>(hist + 4 * g);
-  const u32x4 m = keep[n1 & 7];   // 16-bit masks, two per word
-  const Narrow r = rec[g];
-  uint32_t cin, win;
-  count8<JOINT>(w & m, cin, win);
-  S = r.sum + ((__umul24((r.word >> 16) & 0x7FFu, cin) + win) << (r.word >> 27));
-  C = (r.word & 0xFFFFu) + cin;
+// Eight counters, two per word, of which the first c count: their number and index-weighted number are dot products with
+// weights that are zero for the others, from a table in LDS (Weights: the rows of c).  JOINT: both in one sum (count8).
+struct Weights {
+  uint32_t w[2][8][4];   // [0]: the index (JOINT: 2^15 more); [1], not with JOINT: 1
+};
+template <bool JOINT> MOFQ_DEV void fill_weights(Weights& t, int tid) {   // threads 0 .. 31
+  const int c = tid >> 2, i = tid & 3;
+  const uint32_t mask = (c >= 2 * i + 2) ? 0xFFFFFFFFu : ((c == 2 * i + 1) ? 0x0000FFFFu : 0u);
+  t.w[0][c][i] = ((JOINT ? 0x80008000u : 0u) + static_cast<uint32_t>(2 * i) + (static_cast<uint32_t>(2 * i + 1) << 16)) & mask;
+  if constexpr (!JOINT) t.w[1][c][i] = 0x00010001u & mask;
 }
-template <typename In, bool JOINT>
-MOFQ_DEV void hist_prefix(const uint32_t* hist, const Wide* rec, const u32x4* keep, int lo, uint32_t n1, uint32_t& C, double& S) {
-  const int g = static_cast<int>(n1 >> 3);
-  const u32x4 w = *reinterpret_cast<const u32x4*>(hist + 4 * g);
-  const u32x4 m = keep[n1 & 7];
+// A look-up's reads, and what they come to.
+template <typename Rec, bool JOINT> struct LookUp {
+  u32x4 w, wi, w1;
+  Rec r;
+  uint32_t g;
+  MOFQ_DEV void read(const uint32_t* hist, const Rec* rec, const Weights& t, uint32_t n1) {
+    g = n1 >> 3;
+    asm("" : "+v"(g));   // opaque: both addresses are one shift-add of g (of n1 they would be a shift, a mask and an addition)
+    w = *reinterpret_cast<const u32x4*>(hist + 4 * g);
+    wi = *reinterpret_cast<const u32x4*>(t.w[0][n1 & 7]);
+    if constexpr (!JOINT) w1 = *reinterpret_cast<const u32x4*>(t.w[1][n1 & 7]);
+    r = rec[g];
+  }
+  MOFQ_DEV void counts(uint32_t& cin, uint32_t& win) const {
+    uint32_t s = 0, n = 0;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      s = dot2(w[j], wi[j], s);
+      if constexpr (!JOINT) n = dot2(w[j], w1[j], n);
+    }
+    cin = JOINT ? s >> 15 : n;
+    win = JOINT ? s & 0x7FFFu : s;
+  }
+};
+template <typename In, bool JOINT> MOFQ_DEV void hist_prefix(const LookUp<Narrow, JOINT>& l, int, uint32_t& C, uint32_t& S) {
   uint32_t cin, win;
-  count8<JOINT>(w & m, cin, win);
-  const float v0 = bits_to_float<In>(static_cast<uint32_t>(lo + 8 * g));
-  const float ulp = bits_to_float<In>(static_cast<uint32_t>(lo + 8 * g + 1)) - v0;   // exact
-  double s = rec[g].sum;
-  s = __builtin_fma(static_cast<double>(v0), static_cast<double>(cin), s);
+  l.counts(cin, win);
+  S = l.r.sum + ((__umul24(__builtin_amdgcn_ubfe(l.r.word, 5u, 11u), cin) + win) << (l.r.word & 31u));
+  C = (l.r.word >> 16) + cin;
+}
+template <typename In, bool JOINT> MOFQ_DEV void hist_prefix(const LookUp<Wide, JOINT>& l, int lo, uint32_t& C, double& S) {
+  uint32_t cin, win;
+  l.counts(cin, win);
+  const float v0 = bits_to_float<In>(static_cast<uint32_t>(lo) + 8 * l.g);
+  const float ulp = bits_to_float<In>(static_cast<uint32_t>(lo) + 8 * l.g + 1) - v0;   // exact
+  const double s = __builtin_fma(static_cast<double>(v0), static_cast<double>(cin), l.r.sum);
   S = __builtin_fma(static_cast<double>(ulp), static_cast<double>(win), s);
-  C = rec[g].cnt + cin;
+  C = l.r.cnt + cin;
 }
 
 // One group's own count and sum, and its record.
@@ -88,7 +112,7 @@ template <typename In, bool JOINT> MOFQ_DEV void group_sum(const Narrow*, u32x4 
   count8<JOINT>(w, c, wsum);
   mant_shift<In>(static_cast<uint32_t>(lo + 8 * g), exponent_of<In>(lo), m, shift);
   s = (__umul24(m, c) + wsum) << shift;
-  aux = (m << 16) | (shift << 27);
+  aux = (m << 5) | shift;
 }
 template <typename In, bool JOINT> MOFQ_DEV void group_sum(const Wide*, u32x4 w, int lo, int g, uint32_t& c, double& s, uint32_t& aux) {
   uint32_t wsum;
@@ -98,9 +122,9 @@ template <typename In, bool JOINT> MOFQ_DEV void group_sum(const Wide*, u32x4 w,
   s = __builtin_fma(static_cast<double>(ulp), static_cast<double>(wsum), static_cast<double>(v0) * static_cast<double>(c));
   aux = 0;
 }
-MOFQ_DEV Narrow make_record(const Narrow*, uint32_t c, uint32_t s, uint32_t aux) { return Narrow{s, c | aux}; }
+MOFQ_DEV Narrow make_record(const Narrow*, uint32_t c, uint32_t s, uint32_t aux) { return Narrow{s, (c << 16) | aux}; }
 MOFQ_DEV Wide make_record(const Wide*, uint32_t c, double s, uint32_t) { return Wide{s, c, 0}; }
-MOFQ_DEV uint32_t record_count(const Narrow& r) { return r.word & 0xFFFFu; }
+MOFQ_DEV uint32_t record_count(const Narrow& r) { return r.word >> 16; }
 MOFQ_DEV uint32_t record_count(const Wide& r) { return r.cnt; }
 MOFQ_DEV uint32_t wave_excl_scan(uint32_t v, uint32_t& total) { return wave_excl_scan_u32(v, total); }
 MOFQ_DEV double wave_excl_scan(double v, double& total) { return wave_excl_scan_f64(v, total); }
@@ -158,8 +182,7 @@ void sweep_hist_kernel(const SortedArgs a) {
   constexpr int NF = (FB >= 0) ? 2 : 1;
   constexpr int FBX = (FB >= 0) ? FB : FA;
   constexpr int NW = THREADS / 64;
-  constexpr bool TAIL_A = FA == MOFQ_INT4, TAIL_B = (FB >= 0) && FBX == MOFQ_INT4;
-  constexpr bool ANY_TAIL = TAIL_A || TAIL_B;
+  constexpr bool ANY_TAIL = FA == MOFQ_INT4 || FBX == MOFQ_INT4;
   constexpr int GPMAX = kHistMaxBins / 8 / THREADS;   // groups per thread at most
 
   constexpr bool JOINT = CH <= 2;   // 4096 elements at most
@@ -180,7 +203,7 @@ void sweep_hist_kernel(const SortedArgs a) {
   __shared__ double s_wsum[NW];
   __shared__ uint32_t s_wc[NW];
   __shared__ sum_t s_ws[NW];
-  __shared__ __attribute__((aligned(16))) uint32_t s_keep[8][4];
+  __shared__ __attribute__((aligned(16))) Weights s_weights;
 
   const int tid = threadIdx.x;
   const int lane = tid & 63;
@@ -193,11 +216,7 @@ void sweep_hist_kernel(const SortedArgs a) {
   const typename L::elem* src = static_cast<const typename L::elem*>(T.w) + row * T.ld;
   const int K = a.n_clip;
   const int n = static_cast<int>(a.cols);
-  if (tid < 32) {   // word tid % 4 of the mask of the first tid / 4 counters
-    const int c = tid >> 2, i = tid & 3;
-    s_keep[c][i] = (c >= 2 * i + 2) ? 0xFFFFFFFFu : ((c == 2 * i + 1) ? 0x0000FFFFu : 0u);
-  }
-  const u32x4* const keep = reinterpret_cast<const u32x4*>(&s_keep[0][0]);
+  if (tid < 32) fill_weights<JOINT>(s_weights, tid);
 
   // ---- load the row (it stays in registers until it is counted): absmax, energy; clear the counters ---
   u32x4 rawv[CH];
@@ -306,69 +325,106 @@ void sweep_hist_kernel(const SortedArgs a) {
   // candidates) --------------------------------------------------------------------------------
   {
     const int chunks = (K + 63) >> 6;
-    auto unit = [&](auto tail_tag, const int f, const int k) {
-      constexpr bool TAIL = decltype(tail_tag)::value;
+    const int before_lo = pattern_before<In>(lo), before_tlo = pattern_before<In>(tlo);
+    auto unit = [&](auto normal_tag, auto fmt_c, const int f, const int k) {
+      constexpr int FMT = decltype(fmt_c)::value;
+      constexpr bool NORMAL = decltype(normal_tag)::value, TAIL = FMT == MOFQ_INT4;
       const float s = sh.scale[f][k < K ? k : K - 1];
-      const float inv = 1.0f / s;
-      // H = the largest finite pattern h with fl32(v(h) * inv) <= thr.  inv and the product are each off
-      // by at most 2^-24, so the decision flips between thr s (1 - 2^-22) and thr s (1 + 2^-22); thr_est is
-      // thr (1 - 2^-21) (to 2^-24), so the pattern of thr_est s rounded toward zero passes, and the
-      // second pattern above it, at least 2^-11 larger, does not: one decision, on the first, tells.
-      // Returns H - first + 1.
-      auto counters_below = [&](const int f_, const int q, const int first) {
-        const int est = static_cast<int>(pattern_rtz<In>(a.thr_est[f_][q] * s));
-        const bool above = scaled<In>(static_cast<uint32_t>(est + 1), inv) <= a.thr[f_][q];
+      const float inv = std::is_same<In, F16>::value ? reciprocal(s) : 1.0f / s;
+      // H = the largest pattern h with fl32(v(h) * inv) <= thr; returns H - first + 1.  Where subnormals are
+      // counted: inv and the product are each off by at most 2^-24, so the decision flips between thr s (1 - 2^-22)
+      // and thr s (1 + 2^-22); thr_est is thr (1 - 2^-21) (to 2^-24), so the pattern of thr_est s rounded toward zero passes,
+      // and the second pattern above it, at least 2^-11 larger, does not: one decision, on the first, tells.
+      const double per_edge = edge_unit(s, inv);
+      auto counters_below = [&](const int q, const int first, const int before) {
+        if constexpr (NORMAL) return patterns_below<In>(a.thr_edge[f][q], per_edge, before);
+        const int est = static_cast<int>(pattern_rtz<In>(a.thr_est[f][q] * s));
+        const bool above = scaled<In>(static_cast<uint32_t>(est + 1), inv) <= a.thr[f][q];
         return est + (1 - first) + (above ? 1 : 0);
       };
-      double ca = 0.0;
-      int cb4 = 0;       // 4 sum_b (count up to boundary b) (m_b^2 - m_{b+1}^2): an integer below 2^31
       // counters at or below H, as a number of counters: H - lo + 1 within [0, nbin].  A threshold
       // more than one pattern below the histogram's range sends the candidate to the exact pass:
       // uncounted elements might lie above it.  The first boundary's is the smallest (and a negative
       // number is a large one to the unsigned minimum, so addresses stay inside).
       int fewest = 0;
-      // one boundary at a time (a rolled loop: unrolled, the eight of them cost some 80 registers), the first last
-#pragma unroll 1
-      for (int q = 6; q >= 0; --q) {
-        const int n1 = counters_below(f, q, lo);
+      double ca = 0.0, ca_tail = 0.0;
+      uint32_t cb4 = 0;   // 4 sum_b (count up to boundary b) (m_{b+1}^2 - m_b^2): an integer below 2^31
+      using Look = LookUp<Rec, JOINT>;
+      auto look_up = [&](Look& l, const int q) {
+        const int n1 = counters_below(q, lo, before_lo);
         fewest = n1;
-        uint32_t C;
-        sum_t S;
-        hist_prefix<In, JOINT>(hist, rec, keep, lo, min(static_cast<uint32_t>(n1), static_cast<uint32_t>(nbin)), C, S);
-        ca = __builtin_fma(static_cast<double>(S), a.dgd[f][q], ca);
-        cb4 = __mul24(static_cast<int>(C), a.dg2q[f][q]) + cb4;
-      }
-      double ca_tail = 0.0;
-      if constexpr (TAIL) {
-        // negative elements with a pattern above H: the short histogram's totals less its prefix
-        const int n1 = counters_below(f, 7, tlo);
+        l.read(hist, rec, s_weights, min(static_cast<uint32_t>(n1), static_cast<uint32_t>(nbin)));
+      };
+      auto look_up_tail = [&](Look& l) {
+        const int n1 = counters_below(7, tlo, before_tlo);
         fewest = min(fewest, n1);
+        l.read(thist, trec, s_weights, min(static_cast<uint32_t>(n1), static_cast<uint32_t>(ntbin)));
+      };
+      auto add = [&](const Look& l, const double step, const uint32_t weight) {
         uint32_t C;
         sum_t S;
-        hist_prefix<In, JOINT>(thist, trec, keep, tlo, min(static_cast<uint32_t>(n1), static_cast<uint32_t>(ntbin)), C, S);
-        ca_tail = static_cast<double>(trec[ntg].sum - S) * a.dgd[f][7];
+        hist_prefix<In, JOINT>(l, lo, C, S);
+        ca = __builtin_fma(static_cast<double>(S), -step, ca);
+        cb4 = __umul24(C, weight) + cb4;
+        asm volatile("" : "+v"(ca), "+v"(cb4));   // worked out here and not where the sums are used
+      };
+      auto add_tail = [&](const Look& l) {
+        // negative elements with a pattern above H: the short histogram's totals less its prefix
+        uint32_t C;
+        sum_t S;
+        hist_prefix<In, JOINT>(l, tlo, C, S);
+        ca_tail = static_cast<double>(trec[ntg].sum - S);
         if constexpr (std::is_same<Rec, Narrow>::value) {
           const float v_tlo = bits_to_float<In>(static_cast<uint32_t>(tlo));
           ca_tail *= static_cast<double>(bits_to_float<In>(static_cast<uint32_t>(tlo) + 1) - v_tlo);
         }
-        cb4 = __mul24(static_cast<int>(record_count(trec[ntg]) - C), a.dg2q[f][7]) + cb4;
+        cb4 -= __umul24(record_count(trec[ntg]) - C, quad_step<FMT>(7));
+      };
+      if constexpr (NORMAL) {
+        // one look-up's reads under way while the one before is worked out (all eight at once cost some 80 registers)
+        Look l[2];
+        look_up(l[0], 6);
+#pragma unroll
+        for (int q = 6; q >= 0; --q) {   // the first boundary last
+          __builtin_amdgcn_sched_barrier(0);
+          if (q > 0) look_up(l[(7 - q) & 1], q - 1);
+          else if constexpr (TAIL) look_up_tail(l[1]);
+          __builtin_amdgcn_sched_barrier(0);
+          add(l[(6 - q) & 1], 0.5 * (1 << half_steps_log2<FMT>(q)), quad_step<FMT>(q));
+        }
+        if constexpr (TAIL) add_tail(l[1]);
+      } else {
+#pragma unroll 1
+        for (int q = 6; q >= 0; --q) {
+          Look l;
+          look_up(l, q);
+          add(l, -a.dgd[f][q], static_cast<uint32_t>(-a.dg2q[f][q]));
+        }
+        if constexpr (TAIL) {
+          Look l;
+          look_up_tail(l);
+          add_tail(l);
+        }
       }
       if (k < K) {
         const double gl = static_cast<double>(a.g_last[f]);
         const double A = __builtin_fma(sum_unit, ca + gl * s_total, ca_tail);
-        const double B = 0.25 * static_cast<double>(cb4) + gl * gl * static_cast<double>(c_total);
+        const double B = -0.25 * static_cast<double>(static_cast<int>(cb4)) + gl * gl * static_cast<double>(c_total);
         const double sc = static_cast<double>(s);
         const double v = (en - 2.0 * sc * A) + sc * sc * B;   // filtered error
         sh.fast[f][k] = fewest < 0 ? __builtin_nan("") : v;
       }
     };
-    for (int u = wave; u < NF * chunks; u += NW) {
-      const int f = u / chunks;                         // wave-uniform
-      const int k = (u - f * chunks) * 64 + lane;
-      const bool tail = (f == 0) ? TAIL_A : TAIL_B;
-      if (tail) unit(std::true_type{}, f, k);
-      else unit(std::false_type{}, f, k);
-    }
+    auto units = [&](auto normal_tag) {
+      for (int u = wave; u < NF * chunks; u += NW) {
+        const int f = u / chunks;                         // wave-uniform
+        const int k = (u - f * chunks) * 64 + lane;
+        if (f == 0) unit(normal_tag, std::integral_constant<int, FA>{}, 0, k);
+        else unit(normal_tag, std::integral_constant<int, FBX>{}, NF - 1, k);
+      }
+    };
+    if (lo >= (1 << Pattern<In>::MANT)) units(std::true_type{});   // no subnormal has a counter
+    else units(std::false_type{});
   }
   __syncthreads();
 

@@ -629,6 +629,7 @@ void fill_levels(int fmt, SortedArgs& a, int slot) {
     // tie goes down-> magnitude <= m_b needs t <= mid
     a.thr[slot][b] = up_is_even[b] ? std::nextafterf(mid, -INFINITY) : mid;
     a.thr_est[slot][b] = static_cast<float>(a.thr[slot][b] * (1.0 - 0x1p-21));
+    a.thr_edge[slot][b] = decision_edge(a.thr[slot][b]);
     a.dgd[slot][b] = m[b] - m[b + 1];
     a.dg2q[slot][b] = static_cast<int32_t>(4.0 * (m[b] * m[b] - m[b + 1] * m[b + 1]));   // exact
   }
@@ -636,6 +637,7 @@ void fill_levels(int fmt, SortedArgs& a, int slot) {
     // a negative element stays on -7 while t < 7.5 (the tie goes to the even 8); beyond, it lands on -8
     a.thr[slot][7] = std::nextafterf(7.5f, -INFINITY);
     a.thr_est[slot][7] = static_cast<float>(a.thr[slot][7] * (1.0 - 0x1p-21));
+    a.thr_edge[slot][7] = decision_edge(a.thr[slot][7]);
     a.dgd[slot][7] = m[8] - m[7];
     a.dg2q[slot][7] = static_cast<int32_t>(4.0 * (m[8] * m[8] - m[7] * m[7]));
   }
