@@ -48,30 +48,30 @@ template <int FMT> MOFQ_DEV void score2_f64(double& acc, float x0, float x1, flo
   acc = __builtin_fma(d1, d1, acc);
 }
 
-// Codes of 8 scaled elements.  4-bit: one word, element 2j in the low nibble of byte j;
+// Codes of 8 scaled elements (Raw8::scaled).  4-bit: one word, element 2j in the low nibble of byte j;
 // 8-bit: two words, one byte per element.  The FP formats use the gfx950 pack-convert
 // instructions (round to nearest even, subnormals kept, saturating; the E4M3 convert
 // needs its input clamped to +-448 first), which agree with Codec<>::code on every
 // finite fp32 bit pattern.
 template <int FMT>
-MOFQ_DEV void encode8(const float (&v)[8], float inv_s, uint32_t (&words)[2]) {
+MOFQ_DEV void encode_scaled8(const float (&t)[8], uint32_t (&words)[2]) {
   if constexpr (FMT == MOFQ_FP4_E2M1) {
     uint32_t w = 0;
-    w = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(w, v[0] * inv_s, v[1] * inv_s, 1.0f, 0);
-    w = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(w, v[2] * inv_s, v[3] * inv_s, 1.0f, 1);
-    w = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(w, v[4] * inv_s, v[5] * inv_s, 1.0f, 2);
-    w = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(w, v[6] * inv_s, v[7] * inv_s, 1.0f, 3);
+    w = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(w, t[0], t[1], 1.0f, 0);
+    w = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(w, t[2], t[3], 1.0f, 1);
+    w = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(w, t[4], t[5], 1.0f, 2);
+    w = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(w, t[6], t[7], 1.0f, 3);
     words[0] = w;
     words[1] = 0;
   } else if constexpr (FMT == MOFQ_FP8_E4M3) {
-    float t[8];
+    float c[8];
 #pragma unroll
-    for (int i = 0; i < 8; ++i) t[i] = med3(v[i] * inv_s, -448.0f, 448.0f);
+    for (int i = 0; i < 8; ++i) c[i] = med3(t[i], -448.0f, 448.0f);
     int w0 = 0, w1 = 0;
-    w0 = __builtin_amdgcn_cvt_pk_fp8_f32(t[0], t[1], w0, false);
-    w0 = __builtin_amdgcn_cvt_pk_fp8_f32(t[2], t[3], w0, true);
-    w1 = __builtin_amdgcn_cvt_pk_fp8_f32(t[4], t[5], w1, false);
-    w1 = __builtin_amdgcn_cvt_pk_fp8_f32(t[6], t[7], w1, true);
+    w0 = __builtin_amdgcn_cvt_pk_fp8_f32(c[0], c[1], w0, false);
+    w0 = __builtin_amdgcn_cvt_pk_fp8_f32(c[2], c[3], w0, true);
+    w1 = __builtin_amdgcn_cvt_pk_fp8_f32(c[4], c[5], w1, false);
+    w1 = __builtin_amdgcn_cvt_pk_fp8_f32(c[6], c[7], w1, true);
     words[0] = static_cast<uint32_t>(w0);
     words[1] = static_cast<uint32_t>(w1);
   } else if constexpr (FMT == MOFQ_INT4 || FMT == MOFQ_INT8) {
@@ -80,7 +80,7 @@ MOFQ_DEV void encode8(const float (&v)[8], float inv_s, uint32_t (&words)[2]) {
     constexpr float lo = FMT == MOFQ_INT4 ? -8.0f : -128.0f, hi = FMT == MOFQ_INT4 ? 7.0f : 127.0f;
     uint32_t y[8];
 #pragma unroll
-    for (int i = 0; i < 8; ++i) y[i] = f2u(med3(v[i] * inv_s, lo, hi) + 12582912.0f);
+    for (int i = 0; i < 8; ++i) y[i] = f2u(med3(t[i], lo, hi) + 12582912.0f);
     if constexpr (FMT == MOFQ_INT4) {
       uint32_t b[4];   // two codes in the low byte
 #pragma unroll
@@ -96,19 +96,26 @@ MOFQ_DEV void encode8(const float (&v)[8], float inv_s, uint32_t (&words)[2]) {
   } else if constexpr (Codec<FMT>::BITS == 4) {
     uint32_t w = 0;
 #pragma unroll
-    for (int i = 0; i < 8; ++i) w |= Codec<FMT>::code(v[i] * inv_s) << (4 * i);
+    for (int i = 0; i < 8; ++i) w |= Codec<FMT>::code(t[i]) << (4 * i);
     words[0] = w;
     words[1] = 0;
   } else {
     uint32_t w0 = 0, w1 = 0;
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-      w0 |= Codec<FMT>::code(v[i] * inv_s) << (8 * i);
-      w1 |= Codec<FMT>::code(v[4 + i] * inv_s) << (8 * i);
+      w0 |= Codec<FMT>::code(t[i]) << (8 * i);
+      w1 |= Codec<FMT>::code(t[4 + i]) << (8 * i);
     }
     words[0] = w0;
     words[1] = w1;
   }
+}
+
+template <int FMT> MOFQ_DEV void encode8(const float (&v)[8], float inv_s, uint32_t (&words)[2]) {
+  float t[8];
+#pragma unroll
+  for (int i = 0; i < 8; ++i) t[i] = v[i] * inv_s;
+  encode_scaled8<FMT>(t, words);
 }
 
 // What the finished rows of a tensor favour (AheadCodes): read by one wave (a lane per place; the sum
@@ -148,6 +155,13 @@ template <typename In> struct Raw8 {
       }
     }
   }
+  // fl32(x * inv).  fp16: widening and product are one mixed-precision fused multiply-add, the same single rounding of
+  // the exact product; the addend -0 leaves a zero's sign.
+  MOFQ_DEV void scaled(float inv, float (&t)[8]) const {
+    widen(t);
+#pragma unroll
+    for (int i = 0; i < 8; ++i) t[i] = std::is_same<In, F16>::value ? __builtin_fmaf(t[i], inv, -0.0f) : t[i] * inv;
+  }
 };
 template <> struct Raw8<F32> {
   u32x4 w[2];
@@ -161,6 +175,11 @@ template <> struct Raw8<F32> {
   MOFQ_DEV void widen(float (&v)[8]) const {
 #pragma unroll
     for (int i = 0; i < 4; ++i) { v[i] = u2f(w[0][i]); v[4 + i] = u2f(w[1][i]); }
+  }
+  MOFQ_DEV void scaled(float inv, float (&t)[8]) const {
+    widen(t);
+#pragma unroll
+    for (int i = 0; i < 8; ++i) t[i] *= inv;
   }
 };
 

@@ -285,18 +285,18 @@ template <int FMT> MOFQ_DEV uint32_t grid_pair_bf16(float t0, float t1) {
   return (f2u(Codec<FMT>::grid(t0)) >> 16) | (f2u(Codec<FMT>::grid(t1)) & 0xFFFF0000u);
 }
 
-// One 8-element chunk: quantize with the unit's scale and store.
+// One 8-element chunk, divided by its unit's scale: quantize and store.
 template <int FMT>
-MOFQ_DEV void emit_chunk(const EmitArgs& a, void* codes, int64_t c0, uint32_t l, const float (&v)[8], float inv_s) {   // chunk c0 + l; c0 is uniform
+MOFQ_DEV void emit_chunk(const EmitArgs& a, void* codes, int64_t c0, uint32_t l, const float (&t)[8]) {   // chunk c0 + l; c0 is uniform
   if (a.as_bf16_values) {
     u32x4 o;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) o[i] = grid_pair_bf16<FMT>(v[2 * i] * inv_s, v[2 * i + 1] * inv_s);
+    for (int i = 0; i < 4; ++i) o[i] = grid_pair_bf16<FMT>(t[2 * i], t[2 * i + 1]);
     (static_cast<u32x4*>(codes) + c0)[l] = o;
     return;
   }
   uint32_t words[2];
-  encode8<FMT>(v, inv_s, words);
+  encode_scaled8<FMT>(t, words);
   if constexpr (Codec<FMT>::BITS == 4) {
     (static_cast<uint32_t*>(codes) + c0)[l] = words[0];
   } else {
@@ -357,9 +357,9 @@ __global__ __launch_bounds__(kThreads) void emit_kernel(const EmitArgs a) {
         const float s0 = sc0[u], s1 = sc1[u];
         float s = c == 0 ? s0 : s1;
         if (c > 1) s = t.scale[c][unit0 + unit[u]];
-        float v[8];
-        raw[u].widen(v);
-        emit_chunk<decltype(fmt_c)::value>(a, t.out.codes, c0, static_cast<uint32_t>(l0 + u * kThreads), v, 1.0f / s);   // dense output rows
+        float scaled[8];
+        raw[u].scaled(1.0f / s, scaled);
+        emit_chunk<decltype(fmt_c)::value>(a, t.out.codes, c0, static_cast<uint32_t>(l0 + u * kThreads), scaled);   // dense output rows
       };
       if constexpr (PER_UNIT) {
 #pragma unroll
@@ -452,9 +452,9 @@ __global__ __launch_bounds__(kThreads) void fixup_kernel(const EmitArgs a) {
 #pragma unroll
           for (int u = 0; u < kEmitUnroll; ++u)
             if (l0 + u * kThreads < cpr) {
-              float v[8];
-              raw[u].widen(v);
-              emit_chunk<decltype(fmt_c)::value>(a, t.out.codes, row * t.cpr, static_cast<uint32_t>(l0 + u * kThreads), v, inv_s);
+              float scaled[8];
+              raw[u].scaled(inv_s, scaled);
+              emit_chunk<decltype(fmt_c)::value>(a, t.out.codes, row * t.cpr, static_cast<uint32_t>(l0 + u * kThreads), scaled);
             }
         }
       });

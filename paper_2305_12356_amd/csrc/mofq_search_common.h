@@ -161,6 +161,18 @@ template <int FMT> constexpr uint32_t quad_step(int q) {
   return FMT == MOFQ_INT4 ? 8u * static_cast<uint32_t>(q) + 4u : (q < 7 ? e2m1[q] : 0u);
 }
 
+// unit_scale of a search for a finite absmax: ratio * absmax over QMAX by one multiplication and Markstein's correction, which is the
+// correctly rounded quotient for 7 and 6 (all mantissas checked) wherever it is at least 2^-126; a non-finite
+// unit comes out as 1.
+template <int FMT> MOFQ_DEV float search_scale(float ra, bool f16) {
+  constexpr float d = Codec<FMT>::QMAX, r = 1.0f / d;
+  const float q = ra * r;
+  float s = __builtin_fmaf(__builtin_fmaf(-d, q, ra), r, q);
+  if (f16) s = round_fp16_clamped(s);
+  if (!(s >= 0x1p-126f)) s = 1.0f;
+  return s;
+}
+
 // ---- the largest pattern that a decision passes --------------------------------------------------------
 // fl32(|x| * inv) <= thr, inv = fl32(1 / s): the elements that pass are those up to decision_edge(thr) / inv, and
 // 1 / inv = s + s (1 - s inv) to 2^-48 (|1 - s inv| <= 2^-24; both steps are exact but for the last rounding).  The
@@ -254,40 +266,57 @@ MOFQ_DEV void count_at(uint32_t base, uint32_t byte_off, uint32_t parity16, uint
   __hip_atomic_fetch_add((lds_u32*)static_cast<uintptr_t>(base + byte_off), one << (parity16 & 31u), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
 }
 
-// Counters of both halves of a word of counter numbers (negative halves: none).
-// `one`: 1 in a register of its own (the half-selecting shift takes no constant).
-MOFQ_DEV void count_pair(uint32_t base, i16x2 b2, uint32_t one) {
-  uint32_t off2 = __builtin_bit_cast(uint32_t, b2 << static_cast<short>(1)) & 0xFFFCFFFCu;
-  uint32_t par2 = __builtin_bit_cast(uint32_t, b2 << static_cast<short>(4));
-  // opaque: the halves are then selected by the instructions that use them instead of masked first
-  asm("" : "+v"(off2), "+v"(par2));
-  if (b2[0] >= 0) count_at(base, off2 & 0xFFFFu, par2, one);
-  if (__builtin_bit_cast(int, b2) >= 0) count_at(base, off2 >> 16, par2 >> 16, one);
-}
+// The counters of a row, with kSpare counters before them that nobody reads: an element below the counted patterns goes to
+// one of those, a lane to its own (one for all serialises the additions), which costs one instruction for two elements instead of a
+// comparison and a change of the active lanes for each.
+constexpr int kSpare = 16;
+struct RowCounters {
+  uint32_t at, one;        // LDS byte address of the spare ones; 1 in a register of its own (the half-selecting shift takes no constant)
+  i16x2 first, last, spare;
+  MOFQ_DEV RowCounters(const uint32_t* counters, int lo, int nbin)
+      : at(static_cast<uint32_t>(reinterpret_cast<uintptr_t>((lds_u32*)counters)) - 2 * kSpare), one(1) {
+    const short f = static_cast<short>(lo - kSpare), l = static_cast<short>(nbin - 1 + kSpare), s = static_cast<short>(threadIdx.x & (kSpare - 1));
+    first = i16x2{f, f};
+    last = i16x2{l, l};
+    spare = i16x2{s, s};
+    asm("" : "+v"(one), "+v"(spare));
+  }
+  // both halves of a word of two elements at once: signed 16-bit differences to the first pattern (patterns are below 2^15),
+  // clamped to the last counter (a non-finite element's row has a non-finite error anyway)
+  MOFQ_DEV void count_pair(uint32_t w) const {
+    const i16x2 b2 = __builtin_elementwise_max(__builtin_elementwise_min(__builtin_bit_cast(i16x2, w & 0x7FFF7FFFu) - first, last), spare);
+    uint32_t off2 = __builtin_bit_cast(uint32_t, b2 << static_cast<short>(1)) & 0xFFFCFFFCu;
+    uint32_t par2 = __builtin_bit_cast(uint32_t, b2 << static_cast<short>(4));
+    // opaque: the halves are then selected by the instructions that use them instead of masked first
+    asm("" : "+v"(off2), "+v"(par2));
+    count_at(at, off2 & 0xFFFFu, par2, one);
+    count_at(at, off2 >> 16, par2 >> 16, one);
+  }
+};
 
 // The counters of a row's negative elements at or above pattern tlo, counted apart from the others.  They are
 // few (the boundary lies half way up to the row's largest magnitude), but among the 128 elements of a wave's
 // word there is nearly always one: as a branch of the counting loop they cost every word 15 instructions.
 // So the loop only notes them, 3 instructions per word, and they are read again (they come from
 // L2) once the loop is done: a lane has two at most in most rows.
-// A mask holds the words of four 16-byte chunks: bits 0 and 16 the last word's halves.
-MOFQ_DEV void note_negative(uint32_t& mask, uint32_t w, int tlo) {
+// A mask holds the words of four 16-byte chunks: bits t and 16 + t the halves of word t.
+MOFQ_DEV void note_negative(uint32_t& mask, uint32_t w, int tlo, int t) {
   const unsigned short below = static_cast<unsigned short>(0x8000 + tlo - 1);
   const u16x2 below2 = {below, below}, one = {1, 1};
   uint32_t over = __builtin_bit_cast(uint32_t, __builtin_elementwise_sub_sat(__builtin_bit_cast(u16x2, w), below2));   // sign and magnitude as one number
   asm("" : "+v"(over));   // opaque: else two comparisons and selects
-  mask = (mask << 1) | __builtin_bit_cast(uint32_t, __builtin_elementwise_min(__builtin_bit_cast(u16x2, over), one));
+  mask |= __builtin_bit_cast(uint32_t, __builtin_elementwise_min(__builtin_bit_cast(u16x2, over), one)) << t;
 }
-// chunk0: element number of the lane's first chunk of the mask; its chunks are `stride` elements apart.
-template <int WORDS>
-MOFQ_DEV void count_noted(uint32_t mask, const uint16_t* src, int chunk0, int stride, int tlo, int ntbin, uint32_t at) {
+// chunk0: byte offset of the lane's first chunk of the mask; its chunks are STRIDE bytes apart.
+template <uint32_t STRIDE>
+MOFQ_DEV void count_noted(uint32_t mask, const uint16_t* src, uint32_t chunk0, int tlo, int ntbin, uint32_t at) {
+  static_assert(STRIDE % 4 == 0, "chunks");
   while (mask) {
-    const uint32_t bit = 31u - static_cast<uint32_t>(__builtin_clz(mask));
-    mask &= ~(1u << bit);
-    const uint32_t word = (WORDS - 1) - (bit & 15u);
-    const uint32_t e = static_cast<uint32_t>(chunk0) + __umul24(word >> 2, static_cast<uint32_t>(stride)) + 2 * (word & 3u) + (bit >> 4);
-    const int b = min((src[e] & 0x7FFF) - tlo, ntbin - 1);
-    count_at(at, static_cast<uint32_t>(2 * b) & ~3u, static_cast<uint32_t>(b) << 4);
+    const uint32_t p = static_cast<uint32_t>(__builtin_ctz(mask));
+    mask &= mask - 1;
+    const uint32_t off = (p & 12u) * (STRIDE / 4) + (p & 3u) * 4 + (p >> 4) * 2 + chunk0;
+    const int b = min((*reinterpret_cast<const uint16_t*>(reinterpret_cast<const char*>(src) + off) & 0x7FFF) - tlo, ntbin - 1);
+    count_at(at, (static_cast<uint32_t>(b) >> 1) << 2, static_cast<uint32_t>(b) << 4);
   }
 }
 
@@ -465,10 +494,10 @@ MOFQ_DEV void emit_row_ahead(RowSearch<(FB >= 0 ? 2 : 1), THREADS / 64>& sh, con
 #pragma unroll
     for (int j = 0; j < CH; ++j) {
       const int c = j * THREADS + tid;
-      float v[8];
-      raw[j].widen(v);
+      float t[8];
+      raw[j].scaled(inv, t);
       uint32_t words[2];
-      encode8<FMT>(v, inv, words);
+      encode_scaled8<FMT>(t, words);
       if (c * 8 < n) {
         if constexpr (Codec<FMT>::BITS == 4) {
           (static_cast<uint32_t*>(ahead.codes) + row_chunks)[c] = words[0];

@@ -15,7 +15,7 @@
 // The prefixes lie over the counters they are formed from (a thread holds its share in registers meanwhile), so that
 // six workgroups of the 8-bit search fit a compute unit instead of five.
 // Measured, layer selection: INT8 against E4M3, 3001 x 5000, 50 ratios 277 -> 69.8 -> 66.0 (prefixes over
-// the counters) -> 62.0 us (patterns_below, weights of the counts by dot products: 13 -> 8 instructions a look-up); 4096 x 11008, 100 ratios 1294 -> 141 us; INT4 against E2M1, 1237 x 5000, 100 ratios: 28.2 -> 25.6 -> 23.8 us.
+// the counters) -> 62.0 (patterns_below, weights of the counts by dot products: 13 -> 8 instructions a look-up) -> 60.5 us (RowCounters); 4096 x 11008, 100 ratios 1294 -> 141 us; INT4 against E2M1, 1237 x 5000, 100 ratios: 28.2 -> 25.6 -> 23.4 us.
 //
 // fp16 rows (8-bit formats) have eight times the patterns, up to 20300 below the largest for E4M3: a prefix per group of
 // 8, packed alike, and a look-up adds the group's first counters, 36 instructions.  Counters and prefixes take 61 KB, so
@@ -233,11 +233,11 @@ void sweep_pattern_kernel(const SortedArgs a) {
   const int ntbin = ANY_TAIL ? a.ntbin : 0;
   // fp16: [prefixes of the groups | of the negative elements' | masks | counters | theirs | 16 bytes]
   int n_rec = HALF ? nbin >> 3 : nbin;
-  const int n_trec = HALF ? ntbin >> 3 : ntbin;
+  const int n_trec = HALF ? ntbin >> 3 : ntbin;   // (before the counters the spare ones)
   uint64_t* const P = reinterpret_cast<uint64_t*>(s_dyn);
   uint64_t* const TP = P + (n_rec + 1);
   u32x4* const keep = reinterpret_cast<u32x4*>(s_dyn + (static_cast<uint32_t>(n_rec + n_trec + 2) * 8 + 15) / 16 * 16);   // fp16: of the first c of 8 counters
-  uint32_t* const counters = HALF ? reinterpret_cast<uint32_t*>(keep + 8) : reinterpret_cast<uint32_t*>(s_dyn);
+  uint32_t* const counters = (HALF ? reinterpret_cast<uint32_t*>(keep + 8) : reinterpret_cast<uint32_t*>(s_dyn)) + kSpare / 2;
   uint32_t* const tcounters = HALF ? counters + nbin / 2 : reinterpret_cast<uint32_t*>(TP + (ntbin + 1));
 
   __shared__ RowSearch<NF, kNW> sh;
@@ -319,12 +319,8 @@ void sweep_pattern_kernel(const SortedArgs a) {
     n_rec = nbin >> 3;
   }
   {
-    const i16x2 lo2 = {static_cast<short>(lo), static_cast<short>(lo)};
-    const i16x2 last2 = {static_cast<short>(nbin - 1), static_cast<short>(nbin - 1)};
-    const uint32_t at = static_cast<uint32_t>(reinterpret_cast<uintptr_t>((lds_u32*)counters));
+    const RowCounters row_counters(counters, lo, nbin);
     const uint32_t tat = static_cast<uint32_t>(reinterpret_cast<uintptr_t>((lds_u32*)tcounters));
-    uint32_t one = 1;
-    asm("" : "+v"(one));
 #pragma unroll
     for (int j0 = 0; j0 < CH; j0 += 4) {
       constexpr int PART = CH < 4 ? CH : 4;
@@ -334,10 +330,10 @@ void sweep_pattern_kernel(const SortedArgs a) {
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
           const uint32_t w = j < CH ? raw[j].w[i] : 0;
-          if (j < CH) count_pair(at, __builtin_elementwise_min(__builtin_bit_cast(i16x2, w & 0x7FFF7FFFu) - lo2, last2), one);   // whatever lies below every threshold has no counter, padding (zero) neither unless they reach that far down (E4M3 on fp16)
-          if constexpr (ANY_TAIL) note_negative(noted, w, tlo);
+          if (j < CH) row_counters.count_pair(w);   // whatever lies below every threshold has no counter, padding (zero) neither unless they reach that far down (E4M3 on fp16)
+          if constexpr (ANY_TAIL) note_negative(noted, w, tlo, 4 * (j - j0) + i);
         }
-      if constexpr (ANY_TAIL) count_noted<PART * 4>(noted, src, (j0 * kThreads + tid) * 8, kThreads * 8, tlo, ntbin, tat);
+      if constexpr (ANY_TAIL) count_noted<kThreads * 16>(noted, src, static_cast<uint32_t>(j0 * kThreads + tid) * 16, tlo, ntbin, tat);
     }
   }
   __syncthreads();
@@ -528,7 +524,7 @@ void sweep_pattern_kernel(const SortedArgs a) {
 }
 
 template <typename In> size_t lds_bytes(const SortedArgs& a) {
-  if (std::is_same<In, F16>::value) return (static_cast<size_t>(a.nbin / 8 + a.ntbin / 8 + 2) * 8 + 15) / 16 * 16 + 128 + 2 * static_cast<size_t>(a.nbin + a.ntbin) + 16;
+  if (std::is_same<In, F16>::value) return (static_cast<size_t>(a.nbin / 8 + a.ntbin / 8 + 2) * 8 + 15) / 16 * 16 + 128 + 2 * static_cast<size_t>(kSpare + a.nbin + a.ntbin) + 16;
   const size_t prefixes = std::max<size_t>(8 * static_cast<size_t>(a.nbin + 1 + a.ntbin + 1), 2 * MOFQ_MAX_CLIP * sizeof(double));
   return prefixes + 2 * static_cast<size_t>(a.ntbin);
 }

@@ -87,18 +87,6 @@ template <> struct Cell<true> {
   MOFQ_DEV static int count(word w) { return static_cast<int>(w >> 48); }
 };
 
-// unit_scale of the search: ratio * absmax over QMAX by one multiplication and Markstein's correction, which is the
-// correctly rounded quotient for 7 and 6 (all mantissas checked) wherever it is at least 2^-126; a non-finite
-// group comes out as 1 and is scored exactly later.
-template <int FMT> MOFQ_DEV float search_scale(float ra, bool f16) {
-  constexpr float d = Codec<FMT>::QMAX, r = 1.0f / d;
-  const float q = ra * r;
-  float s = __builtin_fmaf(__builtin_fmaf(-d, q, ra), r, q);
-  if (f16) s = round_fp16_clamped(s);
-  if (!(s >= 0x1p-126f)) s = 1.0f;
-  return s;
-}
-
 // what a lane of the wave wrote to LDS is there for the others: LDS operations of a wave are in order
 MOFQ_DEV void wave_fence() {
   asm volatile("" ::: "memory");
@@ -354,7 +342,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(kWaves<In, W
   auto candidate = [&](auto fmt_c, auto per_c, int k, bool in, int f) {
     constexpr int FMT = decltype(fmt_c)::value, PER = decltype(per_c)::value;
     using Lv = Levels<FMT>;
-    const float s0 = search_scale<FMT>(s_clip[k] * amax, f16);
+    const float s0 = search_scale<FMT>(s_clip[k] * amax, f16);   // (a non-finite group comes out as 1 and is scored exactly later)
     // No boundary but the eighth beyond the counted patterns: a scale that rounding to fp16 moved so far sends the group
     // to the exact pass.  (The patterns span more than the boundaries do, so the lower limit is the smaller one.)
     const float s = med3(s0, v_lo * Lv::kAbove, v_max * Lv::kBelow);

@@ -21,13 +21,14 @@
 // Where the counted patterns span few enough binades, sums of magnitudes are 32-bit integers in units
 // of the first counted pattern's ulp (exact, and a third of the instructions of fp64 sums); else fp64.
 //
-// Bound by vector issue: 963 instructions per wave on rows of 4096 elements (INT4 / E2M1, 100 ratios, codes
-// included): 245 to count, 160 for the prefixes, 205 for the look-ups; they take 805 000 of the 897 000 clocks per SIMD of a
-// launch of 53500 rows.  Two blocks of the 65B shape 2295 -> 2222 us, eight of the 7B shape 3094 -> 2957 us with the
+// Bound by vector issue: 920 instructions per wave on rows of 4096 elements (INT4 / E2M1, 100 ratios, codes
+// included): 215 to count, 160 for the prefixes, 205 for the look-ups; they take nine tenths of the clocks.  Two blocks of the 65B shape 2295 -> 2222 us, eight of the 7B shape 3094 -> 2957 us with the
 // negative elements' counting behind the loop (note_negative), the halves of a word selected by
 // the instructions that use them (count_pair) and one weighted sum per group (count8); 2218 -> 2161 and 2953 -> 2845 us
 // with look-ups of 22 instead of 32 instructions (patterns_below instead of an estimate and a decision, weights that are zero
-// where masks were) whose reads are requested one look-up ahead (in a loop, a look-up at a time: 2190 and 2884).
+// where masks were) whose reads are requested one look-up ahead (in a loop, a look-up at a time: 2190 and 2884); 2120 and 2818 us with
+// spare counters instead of branches (RowCounters), notes that hold the word's place, scales by a multiplication and the codes'
+// widening and product in one instruction.
 //
 // Filter, shortlist and exact fp64 re-score are those of the sorting kernel; the re-score reads
 // the row again.  With AheadCodes the row's codes are written at the end, from a further read that
@@ -189,13 +190,13 @@ void sweep_hist_kernel(const SortedArgs a) {
   static_assert(CH > 2 || CH * THREADS * 8 <= 4096, "count8");
   using sum_t = typename Rec::sum_t;
 
-  // dynamic LDS: [records | the short histogram's | counters | the short histogram's | 16 bytes]
+  // dynamic LDS: [records | the short histogram's | spare counters | counters | the short histogram's | 16 bytes]
   extern __shared__ __attribute__((aligned(16))) unsigned char s_dyn[];
   const int nbin = a.nbin, ntbin = ANY_TAIL ? a.ntbin : 0;   // multiples of 8
   const int ng = nbin >> 3, ntg = ntbin >> 3;
   Rec* const rec = reinterpret_cast<Rec*>(s_dyn);
   Rec* const trec = rec + (ng + 1);
-  uint32_t* const hist = reinterpret_cast<uint32_t*>(s_dyn + (static_cast<size_t>((ng + 1) + (ntg + 1)) * sizeof(Rec) + 15) / 16 * 16);
+  uint32_t* const hist = reinterpret_cast<uint32_t*>(s_dyn + (static_cast<size_t>((ng + 1) + (ntg + 1)) * sizeof(Rec) + 15) / 16 * 16 + 2 * kSpare);
   uint32_t* const thist = hist + (nbin >> 1);   // (counts stay below 2^16: a row has at most 24576 elements)
 
   __shared__ RowSearch<NF, NW> sh;
@@ -269,9 +270,16 @@ void sweep_hist_kernel(const SortedArgs a) {
     en += s_wsum[w];
   }
   if (tid < 2 * MOFQ_MAX_CLIP) {   // thread f * MOFQ_MAX_CLIP + k
-    const int f = tid / MOFQ_MAX_CLIP, k = tid % MOFQ_MAX_CLIP;
+    const int f = __builtin_amdgcn_readfirstlane(tid / MOFQ_MAX_CLIP), k = tid % MOFQ_MAX_CLIP;
     const float qmax = (f == 0) ? Codec<FA>::QMAX : Codec<FBX>::QMAX;
-    if (f < NF && k < K) sh.scale[f][k] = unit_scale(amax, a.clip[k], qmax, a.scale_f16 != 0);
+    if (f < NF && k < K) {
+      if (std::is_same<In, F16>::value && amax <= 65504.0f) {   // uniform
+        const float ra = a.clip[k] * amax;
+        sh.scale[f][k] = f == 0 ? search_scale<FA>(ra, a.scale_f16 != 0) : search_scale<FBX>(ra, a.scale_f16 != 0);
+      } else {
+        sh.scale[f][k] = unit_scale(amax, a.clip[k], qmax, a.scale_f16 != 0);
+      }
+    }
   }
   static_assert(2 * MOFQ_MAX_CLIP <= THREADS, "one thread per (format, candidate)");
 
@@ -281,14 +289,8 @@ void sweep_hist_kernel(const SortedArgs a) {
   const int lo = (((hmax + 1 - nbin) > 0 ? (hmax + 1 - nbin) : 0) + 7) & ~7;
   const int tlo = (((hmax + 1 - ntbin) > 0 ? (hmax + 1 - ntbin) : 0) + 7) & ~7;
   {
-    // both halves of a word at once: signed 16-bit differences to the first counted pattern
-    // (patterns are below 2^15), clamped to the last counter
-    const i16x2 lo2 = {static_cast<short>(lo), static_cast<short>(lo)};
-    const i16x2 last2 = {static_cast<short>(nbin - 1), static_cast<short>(nbin - 1)};
-    const uint32_t hist_at = static_cast<uint32_t>(reinterpret_cast<uintptr_t>((lds_u32*)hist));     // LDS byte addresses, multiples of 16
-    const uint32_t thist_at = static_cast<uint32_t>(reinterpret_cast<uintptr_t>((lds_u32*)thist));
-    uint32_t one = 1;
-    asm("" : "+v"(one));
+    const RowCounters counters(hist, lo, nbin);
+    const uint32_t thist_at = static_cast<uint32_t>(reinterpret_cast<uintptr_t>((lds_u32*)thist));   // LDS byte address, a multiple of 16
 #pragma unroll
     for (int j0 = 0; j0 < CH; j0 += 4) {
       constexpr int PART = CH < 4 ? CH : 4;
@@ -299,10 +301,10 @@ void sweep_hist_kernel(const SortedArgs a) {
         for (int i = 0; i < 4; ++i) {
           const uint32_t w = j < CH ? rawv[j][i] : 0;
           // padding (zero) and whatever lies below every threshold has no counter
-          if (j < CH) count_pair(hist_at, __builtin_elementwise_min(__builtin_bit_cast(i16x2, w & 0x7FFF7FFFu) - lo2, last2), one);
-          if constexpr (ANY_TAIL) note_negative(noted, w, tlo);
+          if (j < CH) counters.count_pair(w);
+          if constexpr (ANY_TAIL) note_negative(noted, w, tlo, 4 * (j - j0) + i);
         }
-      if constexpr (ANY_TAIL) count_noted<PART * 4>(noted, src, (j0 * THREADS + tid) * 8, THREADS * 8, tlo, ntbin, thist_at);
+      if constexpr (ANY_TAIL) count_noted<THREADS * 16>(noted, src, static_cast<uint32_t>(j0 * THREADS + tid) * 16, tlo, ntbin, thist_at);
     }
   }
   __syncthreads();
@@ -445,7 +447,7 @@ int launch_hist_shape(const SortedArgs& a, int64_t total_rows, hipStream_t st) {
   const dim3 grid(static_cast<unsigned>(total_rows));
   const int64_t chunks = a.cols / 8;
   const int ng = a.nbin / 8, ntg = a.ntbin / 8;
-  const size_t lds = std::max<size_t>((static_cast<size_t>((ng + 1) + (ntg + 1)) * sizeof(Rec) + 15) / 16 * 16 + 2 * static_cast<size_t>(a.nbin + a.ntbin) + 16,
+  const size_t lds = std::max<size_t>((static_cast<size_t>((ng + 1) + (ntg + 1)) * sizeof(Rec) + 15) / 16 * 16 + 2 * static_cast<size_t>(kSpare + a.nbin + a.ntbin) + 16,
                                       2 * MOFQ_MAX_CLIP * sizeof(double));   // at least the shortlist's values
 #define MOFQ_HIST(CH)                                                                         \
   if (chunks <= 256 * (CH)) {                                                                  \
