@@ -130,10 +130,16 @@ struct SweepEmit {
   void* grid[2];   // per-channel pair: bf16 grid values of candidate 0 and candidate 1
 };
 
+// Where a search writes codes ahead (AheadCodes; nullptr: it does not), and whether its rows leave tallies.
+struct AheadTo {
+  void* codes;
+  bool tallied;
+};
+
 // Parameters of the launch that scores candidates c0 .. c0 + n - 1 (n = 2: a pair of different
 // formats that share one read of the tensor).  A launch takes at most kMaxFmt formats.
 int sweep_params(const mofq_tensor_t* t, const int32_t* cand, int c0, int n,
-                 const mofq_scale_cfg_t* cfg, const WOnlyWs& w, void* ahead_codes, SweepParams* out) {
+                 const mofq_scale_cfg_t* cfg, const WOnlyWs& w, const AheadTo& ahead, SweepParams* out) {
   if (n < 1 || n > kMaxFmt || c0 < 0 || c0 + n > MOFQ_MAX_CANDIDATES) return MOFQ_ERR_INVALID_ARG;
   SweepParams p{};
   p.w = t->data;
@@ -160,10 +166,10 @@ int sweep_params(const mofq_tensor_t* t, const int32_t* cand, int c0, int n,
   p.absmax_part = w.absmax_part;
   p.sse_part = w.sse_part;
   p.energy_part = w.energy_part;
-  if (ahead_codes) {
-    p.ahead.codes = ahead_codes;
+  if (ahead.codes) {
+    p.ahead.codes = ahead.codes;
     p.ahead.tag = n == 2 ? w.tag : nullptr;
-    p.ahead.tally = n == 2 ? w.tally : nullptr;
+    p.ahead.tally = n == 2 && ahead.tallied ? w.tally : nullptr;
     for (int f = 0; f < n; ++f) p.ahead.cand_of[f] = slot[f];
   }
   *out = p;
@@ -175,16 +181,29 @@ bool one_sweep_launch(const int32_t* cand, int n_cand) {
   return n_cand == 1 || (n_cand == 2 && paired(cand[0], cand[1]));
 }
 
-// Whether the search of these tensors (one launch) should write codes ahead (AheadCodes).  One clip
-// ratio: it saves the second read of the input and costs a launch of 2 us for the tallies plus the
-// rows done twice, so it pays from about 100 MB on (64 MB: even).  Histogram search: from a few times
-// as many rows as are resident at once, so that most of them find a tally.
-constexpr int64_t kAheadBytes = int64_t{128} << 20;
-constexpr int64_t kAheadRows = 8192;
-bool codes_ahead(const mofq_tensor_t* t, const int32_t* cand, int n_cand, const mofq_scale_cfg_t* cfg, int64_t launch_bytes, int64_t launch_rows) {
-  if (cfg->gran != MOFQ_PER_CHANNEL || !one_sweep_launch(cand, n_cand)) return false;
-  if (cfg->n_clip == 1) return launch_bytes >= kAheadBytes && t->cols < (int64_t{1} << 31);
-  if (launch_rows < kAheadRows) return false;
+// Whether the search of these tensors (one launch) should write codes ahead (AheadCodes): it saves the emission's read of
+// the input and costs the codes of a row in the search and the rows that are done twice.  Layer selection, us, emission behind
+// the search -> codes ahead, a row in its own better format (in brackets with half of the rows in either format):
+//   one clip ratio: fp32 1024 x 1024 9.4 -> 8.8 (9.6 -> 9.5), 4096 x 4096 32.6 -> 23.8 (32.6 -> 29.8), 2048 x 11008 39.7 -> 25.7; fp16 4096
+//     x 11008 59.9 -> 45.5 (59.7 -> 56.8); from 128 MB on the rows done twice come from HBM and a tally of the finished rows saves
+//     most of them: fp32 16384 x 16384, new inputs for each call, 243 with a tally, 245 without;
+//   4 bits by histogram: bf16 1237 x 5000, 100 ratios 23.4 -> 20.1, 4096 x 4096, 50 ratios 39.5 -> 37.2 (43.3 -> 42.7), fp16 4096 x 11008
+//     71.2 -> 61.4 (85.2 -> 85.0); from 8192 rows on most rows find a tally, which pays where launches queue up: two 65B blocks
+//     2120 -> 1991, 11008 x 4096 87.3 -> 85.1;
+//   8 bits by histogram: codes of its own format lengthen the rounds of a row by what the emission took: 3001 x 5000, 50 ratios 60.9 ->
+//     62.4 (64.9 -> 61.3), 2500 x 11008 75.4 -> 75.9, 1237 x 5000 34.6 -> 31.6; only with a tally.
+// Fewer than 1024 rows (8 bits, whose rows agree less: 2048): the emission requests its input before the select, rows that are
+// done twice only after it, and few workgroups share them: fp32 64 x 16384, one ratio, 8 bits 10.8 -> 14.0, 1024 x 8192 16.5 -> 19.8,
+// 1500 x 16384 43.9 -> 38.2, bf16 256 x 11008, 4 bits, 50 ratios 15.0 -> 16.2, 1024 x 16384 (37.0 -> 40.4).
+// Beside the searches of a following batch the emission costs nothing that is waited for (mofq_select_layers).
+constexpr int64_t kOwnRows = 1024, kAheadRows = 8192, kTallyBytes = int64_t{128} << 20;
+enum class Ahead { kNo, kOwn, kTallied };
+Ahead codes_ahead(const mofq_tensor_t* t, const int32_t* cand, int n_cand, const mofq_scale_cfg_t* cfg, int64_t launch_rows, int64_t launch_bytes) {
+  if (cfg->gran != MOFQ_PER_CHANNEL || !one_sweep_launch(cand, n_cand)) return Ahead::kNo;
+  if (launch_rows < kOwnRows * (is8(cand[0]) ? 2 : 1)) return Ahead::kNo;
+  if (cfg->n_clip == 1) return launch_bytes >= kTallyBytes ? Ahead::kTallied : Ahead::kOwn;
+  const Ahead how = launch_rows >= kAheadRows ? Ahead::kTallied : Ahead::kOwn;
+  if (how == Ahead::kOwn && n_cand == 2 && is8(cand[0])) return Ahead::kNo;
   SweepParams p{};
   p.dtype = t->dtype;
   p.cols = t->cols;
@@ -193,20 +212,21 @@ bool codes_ahead(const mofq_tensor_t* t, const int32_t* cand, int n_cand, const 
   std::memcpy(p.clip, cfg->clip_ratios, sizeof(float) * cfg->n_clip);
   p.n_fmt = n_cand;
   for (int c = 0; c < n_cand; ++c) p.fmt[c] = cand[c];
-  return sweep_by_histogram(p);
+  return sweep_by_histogram(p) ? how : Ahead::kNo;
 }
+
 int64_t tensor_bytes(const mofq_tensor_t* t) { return t->rows * t->cols * (t->dtype == MOFQ_F32 ? 4 : 2); }
 
 int sweep_candidates(const mofq_tensor_t* t, const int32_t* cand, int n_cand,
                      const mofq_scale_cfg_t* cfg, const WOnlyWs& w, hipStream_t st,
-                     const SweepEmit* em = nullptr, void* ahead_codes = nullptr) {
+                     const SweepEmit* em = nullptr, const AheadTo& ahead = {}) {
   int c0 = 0;
   while (c0 < n_cand) {
     // two different formats share one launch (one read of the tensor); a repeated
     // format is scored on its own
     const int n = (c0 + 1 < n_cand && paired(cand[c0], cand[c0 + 1])) ? 2 : 1;
     SweepParams p{};
-    int rc = sweep_params(t, cand, c0, n, cfg, w, ahead_codes, &p);
+    int rc = sweep_params(t, cand, c0, n, cfg, w, ahead, &p);
     if (rc != MOFQ_OK) return rc;
     if (em) {
       if (n != 2) return MOFQ_ERR_INVALID_ARG;
@@ -363,13 +383,13 @@ WoOutWs carve_wo_output(void* ws, const mofq_tensor_t* w, const mofq_tensor_t* x
 
 int wo_output_score(const mofq_tensor_t* w, const mofq_tensor_t* x, const int32_t* cand, int n_cand,
                     const mofq_scale_cfg_t* w_cfg, const WoOutWs& a, hipStream_t st,
-                    hipEvent_t ev0, hipEvent_t ev1) {
+                    hipEvent_t ev0, hipEvent_t ev1, void* ahead_codes = nullptr) {
   int rc;
   // A pair of different formats with per-channel absmax scales (one clip ratio): the scoring pass
   // holds each row in registers and writes both candidates' grid values itself.
   const bool fused = n_cand == 2 && paired(cand[0], cand[1]) && w_cfg->gran == MOFQ_PER_CHANNEL && w_cfg->n_clip == 1;
   const SweepEmit em{nullptr, nullptr, 0, {a.wg[0], a.wg[1]}};
-  if ((rc = sweep_candidates(w, cand, n_cand, w_cfg, a.wrec, st, fused ? &em : nullptr))) return rc;
+  if ((rc = sweep_candidates(w, cand, n_cand, w_cfg, a.wrec, st, fused ? &em : nullptr, {ahead_codes, false}))) return rc;
   WaGemmParams g{};
   for (int c = 0; c < n_cand; ++c) {
     if (!fused) {
@@ -822,11 +842,12 @@ int select_w_only(const mofq_tensor_t* w, const int32_t* candidates, int n_candi
     if ((rc = record(ev1))) return rc;
     return launch_tensor_pick(p, st);
   }
-  const bool ahead = codes_ahead(w, candidates, n_candidates, w_cfg, tensor_bytes(w), w->rows);
+  const Ahead how = codes_ahead(w, candidates, n_candidates, w_cfg, w->rows, tensor_bytes(w));
+  const bool ahead = how != Ahead::kNo, tallied = how == Ahead::kTallied;
   const bool two = n_candidates == 2;   // else the codes written ahead are final: no tallies, no tags
-  if (ahead && two && (rc = launch_clear(&s.tally, 1, st))) return rc;
+  if (tallied && two && (rc = launch_clear(&s.tally, 1, st))) return rc;
   if ((rc = record(ev0))) return rc;
-  if ((rc = sweep_candidates(w, candidates, n_candidates, w_cfg, s, st, nullptr, ahead ? w_out->codes : nullptr))) return rc;
+  if ((rc = sweep_candidates(w, candidates, n_candidates, w_cfg, s, st, nullptr, {ahead ? w_out->codes : nullptr, tallied}))) return rc;
   if ((rc = record(ev1))) return rc;
   DecideParams d{};
   d.units = units;
@@ -957,8 +978,8 @@ int mofq_quantize(const mofq_tensor_t* t, int32_t format, const mofq_scale_cfg_t
     p.tensor_err = tensor_err;
     return launch_tensor_quantize(p, st);
   }
-  const bool ahead = codes_ahead(t, &format, 1, cfg, tensor_bytes(t), t->rows);
-  if ((rc = sweep_candidates(t, &format, 1, cfg, w, st, nullptr, ahead ? out->codes : nullptr))) return rc;
+  const bool ahead = codes_ahead(t, &format, 1, cfg, t->rows, tensor_bytes(t)) != Ahead::kNo;
+  if ((rc = sweep_candidates(t, &format, 1, cfg, w, st, nullptr, {ahead ? out->codes : nullptr, false}))) return rc;
   EmitParams e{};
   if (tensor_err) {
     e.decide.units = units;
@@ -1200,18 +1221,20 @@ int mofq_select_layers_timed(int32_t n_layers, const mofq_tensor_t* w, const int
     int first[kEmitBatch];
     plan_search_groups(w + i0, nb, candidates, n_candidates, first);
     const bool one_launch = one_sweep_launch(candidates, n_candidates);
-    bool ahead[kEmitBatch];
+    Ahead ahead[kEmitBatch];
     double* tally[kEmitBatch];
-    int n_ahead = 0;
+    int n_tallied = 0;
     for (int j = 0; j < nb; ++j) {
-      int64_t bytes = 0, rows = 0;   // of tensor j's launch
+      int64_t rows = 0, bytes = 0;   // of tensor j's launch
       for (int k = 0; k < nb; ++k)
-        if (first[k] == first[j]) { bytes += tensor_bytes(&w[i0 + k]); rows += w[i0 + k].rows; }
-      ahead[j] = codes_ahead(&w[i0 + j], candidates, n_candidates, w_cfg, bytes, rows);
-      if (ahead[j]) tally[n_ahead++] = slot[j].tally;
+        if (first[k] == first[j]) { rows += w[i0 + k].rows; bytes += tensor_bytes(&w[i0 + k]); }
+      ahead[j] = codes_ahead(&w[i0 + j], candidates, n_candidates, w_cfg, rows, bytes);
+      if (ahead[j] == Ahead::kOwn && sw.two && i0 + nb < n_layers) ahead[j] = Ahead::kNo;   // (eight 7B blocks 2881 -> 2776 us)
+      if (ahead[j] == Ahead::kTallied) tally[n_tallied++] = slot[j].tally;
     }
     const bool two = n_candidates == 2;   // else the codes written ahead are final
-    if (n_ahead && two && (rc = launch_clear(tally, n_ahead, st))) return join(rc);
+    auto ahead_to = [&](int j) { return AheadTo{ahead[j] != Ahead::kNo ? w_out[i0 + j].codes : nullptr, ahead[j] == Ahead::kTallied}; };
+    if (n_tallied && two && (rc = launch_clear(tally, n_tallied, st))) return join(rc);
     for (int j = 0; j < nb; ++j) {
       if (first[j] != j) continue;
       // A launch over several tensors exists only where the whole candidate list is one
@@ -1221,7 +1244,7 @@ int mofq_select_layers_timed(int32_t n_layers, const mofq_tensor_t* w, const int
       int g = 0, last = j;
       for (int k = j; k < nb; ++k)
         if (first[k] == j) {
-          if (one_launch && (rc = sweep_params(&w[i0 + k], candidates, 0, n_candidates, w_cfg, slot[k], ahead[k] ? w_out[i0 + k].codes : nullptr, &sp[g])))
+          if (one_launch && (rc = sweep_params(&w[i0 + k], candidates, 0, n_candidates, w_cfg, slot[k], ahead_to(k), &sp[g])))
             return join(rc);
           ++g;
           last = k;
@@ -1245,7 +1268,7 @@ int mofq_select_layers_timed(int32_t n_layers, const mofq_tensor_t* w, const int
         if (!one_launch) return join(MOFQ_ERR_INVALID_ARG);   // cannot happen: see plan_search_groups
         if ((rc = launch_sweep_group(sp, g, st))) return join(rc);
       } else {
-        if ((rc = sweep_candidates(&w[i0 + j], candidates, n_candidates, w_cfg, slot[j], st, nullptr, ahead[j] ? w_out[i0 + j].codes : nullptr)))
+        if ((rc = sweep_candidates(&w[i0 + j], candidates, n_candidates, w_cfg, slot[j], st, nullptr, ahead_to(j))))
           return join(rc);
       }
       if (ev_end && hipEventRecord(static_cast<hipEvent_t>(ev_end[i0 + last]), st) != hipSuccess) return join(MOFQ_ERR_HIP);
@@ -1265,9 +1288,9 @@ int mofq_select_layers_timed(int32_t n_layers, const mofq_tensor_t* w, const int
       int n = 0, m = 0;
       for (int j = 0; j < nb; ++j)
         if (w[i0 + j].dtype == dtype) {
-          EmitParams& q = ahead[j] ? f[m++] : e[n++];
+          EmitParams& q = ahead[j] != Ahead::kNo ? f[m++] : e[n++];
           q = emit_params(i0 + j, slot[j]);
-          if (ahead[j] && two) q.tag = slot[j].tag;
+          if (ahead[j] != Ahead::kNo && two) q.tag = slot[j].tag;
         }
       if (m && (rc = launch_fixup(f, m, emit_cap, st2))) return join(rc);
       if (n && (rc = launch_emit(e, n, emit_cap, st2))) return join(rc);
@@ -1460,7 +1483,10 @@ int mofq_select_layer_timed(const mofq_tensor_t* w, const mofq_tensor_t* x,
     if ((rc = check_wo_output(w, x, candidates, n_candidates, w_cfg))) return rc;
     const WoOutWs a = carve_wo_output(ws, w, x, n_candidates, w_cfg);
     if (!ws || ws_bytes < a.bytes || !aligned16(ws)) return MOFQ_ERR_WORKSPACE;
-    if ((rc = wo_output_score(w, x, candidates, n_candidates, w_cfg, a, st, ev0, ev1))) return rc;
+    // a row's codes in the format with its smaller tensor error: mostly the one with the smaller layer-output error (2048 x
+    // 11008 x 4096 469 -> 455 us, 512 x 4096 x 4096 85 -> 80; behind a search with 20 ratios no gain: 2048 x 4096 x 4096 204 -> 205)
+    const bool ahead = w_cfg->n_clip == 1 && codes_ahead(w, candidates, n_candidates, w_cfg, w->rows, tensor_bytes(w)) != Ahead::kNo;
+    if ((rc = wo_output_score(w, x, candidates, n_candidates, w_cfg, a, st, ev0, ev1, ahead ? w_out->codes : nullptr))) return rc;
     DecideParams d{};
     d.units = a.blocks;
     d.n_cand = n_candidates;
@@ -1485,8 +1511,9 @@ int mofq_select_layer_timed(const mofq_tensor_t* w, const mofq_tensor_t* x,
       e.err[c] = a.wrec.err[c];
     }
     e.decide = d;
+    e.tag = ahead && n_candidates == 2 ? a.wrec.tag : nullptr;
     e.out = *w_out;
-    return launch_emit(&e, 1, 0, st);
+    return ahead ? launch_fixup(&e, 1, 0, st) : launch_emit(&e, 1, 0, st);
   }
   if (metric != MOFQ_ERR_LAYER_OUTPUT && metric != MOFQ_ERR_LAYER_OUTPUT_FP8_UNIT)
     return MOFQ_ERR_INVALID_ARG;

@@ -257,6 +257,7 @@ struct EmitArgs {
   int32_t fmt[MOFQ_MAX_CANDIDATES];
   int32_t scale_f16_out;
   int32_t as_bf16_values;   // write grid values (bf16, unscaled) instead of codes
+  int32_t fix_rows;         // fixup_kernel: rows a workgroup takes at a time
   EmitTensor t[kEmitBatch];
 };
 
@@ -403,29 +404,41 @@ __global__ __launch_bounds__(kThreads) void emit_kernel(const EmitArgs a) {
 }
 
 // After searches that wrote codes ahead (AheadCodes): select, per-unit outputs, and the codes of the
-// rows that hold another candidate's.  A workgroup takes kFixRows rows at a time: a thread per row for
-// the outputs, then all threads for one row to be done again after the other.
-constexpr int kFixRows = 16;
+// rows that hold another candidate's.  A workgroup takes fix_rows rows at a time: a thread per row for
+// the outputs, then all threads for the chunks of the rows to be done again, as one sequence.  What a row's thread needs of the first two
+// candidates is requested before the select.
+constexpr int kFixRows = 16;   // at most
 template <typename In>
 __global__ __launch_bounds__(kThreads) void fixup_kernel(const EmitArgs a) {
   __shared__ double s_sum[kSums];
-  __shared__ int s_redo[kFixRows];
+  __shared__ int s_redo[kFixRows], s_n;
+  __shared__ float s_inv[kFixRows];
   const int k = tensor_of(a.first_block, static_cast<int>(blockIdx.x));
   const EmitTensor& t = a.t[k];
   const int b = static_cast<int>(blockIdx.x) - a.first_block[k];
   const int nb = (k + 1 < a.n ? a.first_block[k + 1] : static_cast<int>(gridDim.x)) - a.first_block[k];
   const int64_t rows = t.n_chunks / t.cpr;
-  const int tid = threadIdx.x;
-  const int best = t.d.n > 0 ? decide(t.d, b == 0, s_sum) : 0;   // uniform
-  for (int64_t r0 = static_cast<int64_t>(b) * kFixRows; r0 < rows; r0 += static_cast<int64_t>(nb) * kFixRows) {
-    if (tid < kFixRows) {
-      const int64_t o = r0 + tid;
-      int redo = 0;
-      if (o < rows) {
-        redo = t.tag ? t.tag[o] != best : 0;
-        const float s = t.scale[best][o];
-        const int32_t clip = t.clip[best][o];
-        const double err = t.err[best][o];
+  const int tid = threadIdx.x, per = a.fix_rows;
+  int best = -1;
+  for (int64_t r0 = static_cast<int64_t>(b) * per; r0 < rows; r0 += static_cast<int64_t>(nb) * per) {
+    const int64_t o = r0 + tid;
+    const bool mine = tid < per && o < rows;
+    const int64_t at = mine ? o : r0;
+    const float s0 = t.scale[0][at], s1 = t.scale[1][at];
+    const int32_t clip0 = t.clip[0][at], clip1 = t.clip[1][at];
+    const double err0 = t.err[0][at], err1 = t.err[1][at];
+    const int tag = t.tag ? t.tag[at] : 0;
+    if (best < 0) best = t.d.n > 0 ? decide(t.d, b == 0, s_sum) : 0;   // uniform
+    if (tid < per) {
+      bool redo = false;
+      float scale = 1.0f;
+      if (mine) {
+        redo = t.tag && tag != best;
+        float s = best == 0 ? s0 : s1;
+        int32_t clip = best == 0 ? clip0 : clip1;
+        double err = best == 0 ? err0 : err1;
+        if (best > 1) { s = t.scale[best][o]; clip = t.clip[best][o]; err = t.err[best][o]; }
+        scale = s;
         if (t.out.scales) {
           if (a.scale_f16_out)
             static_cast<uint16_t*>(t.out.scales)[o] = __half_as_ushort(__float2half_rn(s));  // exact: s is an fp16 value
@@ -435,26 +448,35 @@ __global__ __launch_bounds__(kThreads) void fixup_kernel(const EmitArgs a) {
         if (t.out.clip_idx) t.out.clip_idx[o] = clip;
         if (t.out.unit_err) t.out.unit_err[o] = err;
       }
-      s_redo[tid] = redo;
+      // the rows to be done again, in any order (per <= 16: one wave)
+      const uint64_t again = __builtin_amdgcn_ballot_w64(redo);
+      if (redo) {
+        const int i = __builtin_popcountll(again & ((uint64_t{1} << tid) - 1));
+        s_redo[i] = tid;
+        s_inv[i] = 1.0f / scale;
+      }
+      if (tid == 0) s_n = __builtin_popcountll(again);
     }
     __syncthreads();
-    for (int i = 0; i < kFixRows; ++i) {
-      if (!s_redo[i]) continue;   // uniform
-      const int64_t row = r0 + i;
-      const float inv_s = 1.0f / t.scale[best][row];
-      const int cpr = static_cast<int>(t.cpr);
+    const uint32_t n = static_cast<uint32_t>(s_n) * t.cpr;   // their chunks, one row behind the other
+    if (n > 0) {   // uniform
       with_format(a.fmt[best], [&](auto fmt_c) {
-        for (int l0 = tid; l0 < cpr; l0 += kThreads * kEmitUnroll) {
+        for (uint32_t l0 = tid; l0 < n; l0 += kThreads * kEmitUnroll) {
           Raw8<In> raw[kEmitUnroll];
+          uint32_t row[kEmitUnroll], chunk[kEmitUnroll];   // the row's place in the list
+#pragma unroll
+          for (int u = 0; u < kEmitUnroll; ++u) {
+            const uint32_t l = l0 + u * kThreads < n ? l0 + u * kThreads : l0;
+            row[u] = t.magic ? __umulhi(l, t.magic) : l / t.cpr;   // l * cpr < 2^32
+            chunk[u] = l - row[u] * t.cpr;
+            raw[u].load(t.w, (r0 + s_redo[row[u]]) * t.ld, chunk[u] * 8);
+          }
 #pragma unroll
           for (int u = 0; u < kEmitUnroll; ++u)
-            raw[u].load(t.w, row * t.ld, static_cast<uint32_t>(l0 + u * kThreads < cpr ? l0 + u * kThreads : l0) * 8);
-#pragma unroll
-          for (int u = 0; u < kEmitUnroll; ++u)
-            if (l0 + u * kThreads < cpr) {
+            if (l0 + u * kThreads < n) {
               float scaled[8];
-              raw[u].scaled(inv_s, scaled);
-              emit_chunk<decltype(fmt_c)::value>(a, t.out.codes, row * t.cpr, static_cast<uint32_t>(l0 + u * kThreads), scaled);
+              raw[u].scaled(s_inv[row[u]], scaled);
+              emit_chunk<decltype(fmt_c)::value>(a, t.out.codes, r0 * t.cpr, static_cast<uint32_t>(s_redo[row[u]]) * t.cpr + chunk[u], scaled);
             }
         }
       });
@@ -635,7 +657,7 @@ int prepare_emit(const EmitParams* p, int n, EmitArgs& a, hipStream_t st) {
       while ((8 << t.group_shift) < q.group) ++t.group_shift;   // segments hold whole groups: 512 chunks and more
     }
     for (int c = 0; c < q.n_cand; ++c) { t.scale[c] = q.scale[c]; t.clip[c] = q.clip[c]; t.err[c] = q.err[c]; }
-    if (q.n_cand < 2) t.scale[1] = q.scale[0];   // requested early, not used
+    if (q.n_cand < 2) { t.scale[1] = q.scale[0]; t.clip[1] = q.clip[0]; t.err[1] = q.err[0]; }   // requested early, not used
     if (q.decide.units > 0) {
       t.d = decision(q.decide, two_stages(q.decide));
       dec[n_dec++] = &q.decide;
@@ -690,8 +712,11 @@ int launch_fixup(const EmitParams* p, int n, int max_blocks, hipStream_t st) {
   EmitArgs a;
   const int rc = prepare_emit(p, n, a, st);
   if (rc != MOFQ_OK) return rc;
-  int64_t want[kEmitBatch];
-  for (int i = 0; i < n; ++i) want[i] = (p[i].rows + kFixRows - 1) / kFixRows;
+  // few rows: fewer at a time, for more workgroups
+  int64_t rows = 0, want[kEmitBatch];
+  for (int i = 0; i < n; ++i) rows += p[i].rows;
+  a.fix_rows = static_cast<int32_t>(std::min<int64_t>(kFixRows, std::max<int64_t>(2, rows / 512)));
+  for (int i = 0; i < n; ++i) want[i] = (p[i].rows + a.fix_rows - 1) / a.fix_rows;
   const dim3 grid(deal_blocks(a, want, max_blocks > 0 ? max_blocks : 256 * 8));
   switch (p[0].dtype) {
     case MOFQ_F32: hipLaunchKernelGGL(fixup_kernel<F32>, grid, dim3(kThreads), 0, st, a); break;

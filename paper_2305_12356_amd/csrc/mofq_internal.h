@@ -23,7 +23,7 @@ struct UnitRecords {
 
 // Codes written by the search itself (per-channel scales, one launch for the whole candidate list):
 // every row is emitted while it is at hand, in the format that the tensor's rows favour so far, so
-// that the tensor is read once; rows whose format turns out not to be the tensor's choice are
+// that the tensor is read once (few rows: each in its own better format); rows whose format turns out not to be the tensor's choice are
 // emitted again afterwards (launch_fixup).  What is favoured is a sum over finished rows that
 // workgroups read and add to as they come: it decides how many rows are done twice, never the result.
 // Every XCD has sums of its own, kTalliesPerXcd of them, so that the traffic stays inside its L2: an
@@ -33,7 +33,8 @@ struct AheadCodes {
   void* codes;              // nullptr: not asked for
   // two formats only (a single one's codes are final):
   uint8_t* tag;             // [rows]: candidate whose codes the row holds
-  double* tally;            // [kTallies][kTallyStride]: sums of (error in slot 0 - error in slot 1); zero before the launch
+  double* tally;            // [kTallies][kTallyStride]: sums of (error in slot 0 - error in slot 1); zero before the launch.
+                            // nullptr: a row takes its own better format
   int32_t cand_of[kMaxFmt]; // launch slot -> candidate index
 };
 

@@ -461,21 +461,29 @@ MOFQ_DEV void finish_row(RowSearch<(FB >= 0 ? 2 : 1), THREADS / 64>& sh, double*
 }
 
 // The row's codes (AheadCodes) after finish_row, in the format that the tensor's rows favour so far.
-// `tally`: what tally_read gave the last wave.
+// `tally`: what tally_read gave the last wave.  Rows of up to kKeptChunks chunks a thread stay in its registers (`kept`) from
+// the first pass on; longer ones are read again, from L2.
+constexpr int kKeptChunks = 3;
 template <typename In, int FA, int FB, int THREADS, int CH>
-MOFQ_DEV void emit_row_ahead(RowSearch<(FB >= 0 ? 2 : 1), THREADS / 64>& sh, const AheadCodes& ahead, double tally, const uint16_t* src, int n, int64_t row) {
+MOFQ_DEV void emit_row_ahead(RowSearch<(FB >= 0 ? 2 : 1), THREADS / 64>& sh, const AheadCodes& ahead, double tally, const Raw8<In> (&kept)[CH],
+                             const uint16_t* src, int n, int64_t row) {
   constexpr int NF = (FB >= 0) ? 2 : 1, FBX = (FB >= 0) ? FB : FA, NW = THREADS / 64;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   if (NF == 2 && wave == NW - 1) {
-    tally = wave_sum(tally);
+    if (ahead.tally) tally = wave_sum(tally);   // uniform
     if (lane == 0) sh.tally = tally;
   }
   Raw8<In> raw[CH];
 #pragma unroll
   for (int j = 0; j < CH; ++j) {
     const int c = (j * THREADS + tid) * 8;
-    raw[j].load(src, 0, static_cast<uint32_t>(c < n ? c : 0));
+    if constexpr (Codec<FA>::BITS == 4 && CH <= kKeptChunks) {
+      raw[j] = kept[j];
+      raw[j].opaque();   // nothing widened from it is kept
+    } else {
+      raw[j].load(src, 0, static_cast<uint32_t>(c < n ? c : 0));
+    }
   }
   __syncthreads();
   int slot = 0;
@@ -483,7 +491,7 @@ MOFQ_DEV void emit_row_ahead(RowSearch<(FB >= 0 ? 2 : 1), THREADS / 64>& sh, con
     const double d = sh.best[0] - sh.best[1];
     slot = __builtin_amdgcn_readfirstlane(sh.tally + d > 0.0 ? 1 : 0);
     if (tid == 0) {
-      tally_add<4>(ahead, d);
+      if (ahead.tally) tally_add<4>(ahead, d);
       ahead.tag[row] = static_cast<uint8_t>(ahead.cand_of[slot]);
     }
   }

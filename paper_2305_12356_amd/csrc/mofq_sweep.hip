@@ -416,7 +416,7 @@ __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(GRID ? 
   // read early, so that its latency is hidden (it may miss the rows of the last microseconds), but behind
   // the row (loads return in order), and by one wave: waves that read it at different times could disagree
   double tally = 0.0;
-  if (NF == 2 && a.ahead.codes && wave == 0) tally = tally_read(a.ahead);
+  if (NF == 2 && a.ahead.tally && wave == 0) tally = tally_read(a.ahead);
   float amax = 0.0f;
   double en = 0.0;
 #pragma unroll
@@ -486,7 +486,7 @@ __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(GRID ? 
   if constexpr (NF == 2) accB = wave_sum(accB);
   if (lane == 0) { s_acc[0][wave] = accA; s_acc[1][wave] = accB; }
   if (NF == 2 && a.ahead.codes && wave == 0) {
-    tally = wave_sum(tally);
+    if (a.ahead.tally) tally = wave_sum(tally);
     if (lane == 0) s_tally = tally;
   }
   __syncthreads();
@@ -499,7 +499,7 @@ __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(GRID ? 
     a.rec.err[tid][row] = t;
     if (tid == 0 && a.rec.energy) a.rec.energy[row] = en;
   }
-  if (!GRID && a.ahead.codes) {   // uniform
+  if (a.ahead.codes) {   // uniform
     int slot = 0;
     if constexpr (NF == 2) {
       double d = 0.0;
@@ -507,7 +507,7 @@ __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(GRID ? 
       for (int w = 0; w < NW; ++w) d += s_acc[0][w] - s_acc[1][w];
       slot = __builtin_amdgcn_readfirstlane(s_tally + d > 0.0 ? 1 : 0);
       if (tid == 0) {
-        tally_add<16>(a.ahead, d);
+        if (a.ahead.tally) tally_add<16>(a.ahead, d);
         a.ahead.tag[row] = static_cast<uint8_t>(a.ahead.cand_of[slot]);
       }
     }
@@ -1261,7 +1261,7 @@ int launch_sweep(const SweepParams& p, hipStream_t st) {
     a.emit_grid[1] = static_cast<uint16_t*>(p.emit_grid[1]);
   }
   if (p.ahead.codes) {
-    if (p.gran != MOFQ_PER_CHANNEL || p.n_clip != 1 || (p.n_fmt == 2 && (!p.ahead.tag || !p.ahead.tally))) return MOFQ_ERR_UNSUPPORTED;
+    if (p.gran != MOFQ_PER_CHANNEL || p.n_clip != 1 || (p.n_fmt == 2 && !p.ahead.tag)) return MOFQ_ERR_UNSUPPORTED;
     a.ahead = p.ahead;
   }
   a.units = mofq_num_units(p.rows, p.cols, p.gran, p.group);

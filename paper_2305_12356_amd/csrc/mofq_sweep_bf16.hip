@@ -268,7 +268,7 @@ void sweep_pattern_kernel(const SortedArgs a) {
   // what the tensor's finished rows favour: behind the row (loads return in order), by one wave (waves that
   // read it at different times could disagree)
   double tally = 0.0;
-  if (NF == 2 && T.ahead.codes && wave == kNW - 1) tally = tally_read(T.ahead);
+  if (NF == 2 && T.ahead.tally && wave == kNW - 1) tally = tally_read(T.ahead);
   {
     const u32x4 zero = {0u, 0u, 0u, 0u};
     for (int i = tid; i < nbin / 8; i += kThreads) reinterpret_cast<u32x4*>(counters)[i] = zero;
@@ -520,7 +520,7 @@ void sweep_pattern_kernel(const SortedArgs a) {
 
   // ---- winners (the re-scored values lie over the prefixes, which are no longer needed), codes --------
   finish_row<In, FA, FB, kThreads, CH, true>(sh, reinterpret_cast<double*>(P), src, n, K, en, unit * s_total, a.g_absmax, T.rec, row);
-  if (T.ahead.codes) emit_row_ahead<In, FA, FB, kThreads, CH>(sh, T.ahead, tally, src, n, row);   // uniform
+  if (T.ahead.codes) emit_row_ahead<In, FA, FB, kThreads, CH>(sh, T.ahead, tally, raw, src, n, row);   // uniform
 }
 
 template <typename In> size_t lds_bytes(const SortedArgs& a) {

@@ -28,10 +28,10 @@
 // with look-ups of 22 instead of 32 instructions (patterns_below instead of an estimate and a decision, weights that are zero
 // where masks were) whose reads are requested one look-up ahead (in a loop, a look-up at a time: 2190 and 2884); 2120 and 2818 us with
 // spare counters instead of branches (RowCounters), notes that hold the word's place, scales by a multiplication and the codes'
-// widening and product in one instruction.
+// widening and product in one instruction; 2725 us on the 7B blocks with rows of up to 4096 columns kept in registers for their codes.
 //
 // Filter, shortlist and exact fp64 re-score are those of the sorting kernel; the re-score reads
-// the row again.  With AheadCodes the row's codes are written at the end, from a further read that
+// the row again.  With AheadCodes the row's codes are written at the end, from registers or a further read that
 // comes from L2.
 #include "mofq_search_common.h"
 
@@ -234,7 +234,7 @@ void sweep_hist_kernel(const SortedArgs a) {
   // what the tensor's finished rows favour: behind the row (loads return in order), by one wave (waves that
   // read it at different times could disagree)
   double tally = 0.0;
-  if (NF == 2 && T.ahead.codes && wave == NW - 1) tally = tally_read(T.ahead);
+  if (NF == 2 && T.ahead.tally && wave == NW - 1) tally = tally_read(T.ahead);
   {
     const u32x4 zero = {0u, 0u, 0u, 0u};
     for (int i = tid; i < ng + ntg; i += THREADS) reinterpret_cast<u32x4*>(hist)[i] = zero;   // hist and thist are adjacent
@@ -437,7 +437,10 @@ void sweep_hist_kernel(const SortedArgs a) {
   // which are no longer needed (the host sizes the dynamic LDS for it).
   static_assert(GPMAX + 6 + NW + 2 <= 16, "depth of the prefix sums");
   finish_row<In, FA, FB, THREADS, CH, std::is_same<Rec, Narrow>::value>(sh, reinterpret_cast<double*>(s_dyn), src, n, K, en, l1, a.g_absmax, T.rec, row);
-  if (T.ahead.codes) emit_row_ahead<In, FA, FB, THREADS, CH>(sh, T.ahead, tally, src, n, row);   // uniform
+  Raw8<In> kept[CH];
+#pragma unroll
+  for (int j = 0; j < CH; ++j) kept[j].w = rawv[j];
+  if (T.ahead.codes) emit_row_ahead<In, FA, FB, THREADS, CH>(sh, T.ahead, tally, kept, src, n, row);   // uniform
 }
 
 // Dynamic LDS: the records and counters of both histograms; the shortlist's re-scored values lie

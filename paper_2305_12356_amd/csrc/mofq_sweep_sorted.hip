@@ -794,7 +794,7 @@ int launch_sweep_sorted_group(const SweepParams* ps, int n, hipStream_t st) {
   for (int k = 0; k < p.n_clip; ++k) a.clip[k] = p.clip[k];
   for (int f = 0; f < p.n_fmt; ++f) fill_levels(p.fmt[f], a, f);
   hist_sizes(p, a);
-  if (p.ahead.codes && (a.nbin <= 0 || (p.n_fmt == 2 && (!p.ahead.tag || !p.ahead.tally)))) return MOFQ_ERR_UNSUPPORTED;
+  if (p.ahead.codes && (a.nbin <= 0 || (p.n_fmt == 2 && !p.ahead.tag))) return MOFQ_ERR_UNSUPPORTED;
   return p.dtype == MOFQ_F16 ? launch_fmt<F16>(p, a, total_rows, st) : launch_fmt<BF16>(p, a, total_rows, st);
 }
 
