@@ -1090,6 +1090,17 @@ int batch_length(int n_layers, const mofq_tensor_t* w, int i0, int cus) {
   return nb;
 }
 
+// Scales per group: every tensor is a search launch of its own, so the last batch is emitted in two parts, the first one's
+// emission beside the second one's searches, which take ten times as long per byte.  The second part holds an eighth of the
+// batch or the last tensor.  A 7B block, groups of 128, 50 ratios 1132 -> 1085 us.
+int first_part(const mofq_tensor_t* w, int nb) {
+  int64_t total = 0, tail = 0;
+  for (int j = 0; j < nb; ++j) total += w[j].rows * w[j].cols;
+  int n = nb;
+  while (n > 1 && 8 * tail < total) { --n; tail += w[n].rows * w[n].cols; }
+  return n;
+}
+
 // Tensors of a batch with one row length and dtype share a search launch (up to
 // kSweepGroupMax of them, adjacent or not: a larger launch fills the device better than
 // several small ones, and nothing orders the searches inside a batch).  first[j] (j < nb)
@@ -1177,7 +1188,9 @@ int mofq_select_layers_timed(int32_t n_layers, const mofq_tensor_t* w, const int
   // compute unit and 18.7 with fewer; 65B-shaped set 123.5 against 140.4 ms, where one per compute
   // unit no longer keeps up with the searches; three to eight per compute unit are no faster).
   const int cus = compute_units();
-  int emit_cap = sw.two ? 2 * cus : 0;
+  // Group searches have waves of their own small workgroups and leave it room (where the streams share a hardware queue, 7B block:
+  // 1185 us with the cap, 1145 without).
+  int emit_cap = sw.two && w_cfg->gran != MOFQ_PER_GROUP ? 2 * cus : 0;
 
   // everything after the search of tensor i: reduce + select, codes and per-unit outputs
   auto emit_params = [&](int i, const WOnlyWs& s) {
@@ -1209,8 +1222,13 @@ int mofq_select_layers_timed(int32_t n_layers, const mofq_tensor_t* w, const int
   };
 
   char* base = static_cast<char*>(ws);
+  int batch_end = 0;
   for (int i0 = 0, nb = 0; i0 < n_layers; i0 += nb) {
-    nb = batch_length(n_layers, w, i0, cus);
+    nb = i0 == batch_end ? batch_length(n_layers, w, i0, cus) : batch_end - i0;
+    if (i0 == batch_end) {
+      batch_end += nb;
+      if (sw.two && w_cfg->gran == MOFQ_PER_GROUP && batch_end == n_layers) nb = first_part(w + i0, nb);
+    }
     WOnlyWs slot[kEmitBatch];
     // 1. the searches, back to back; the tensors of one row length share a launch
     for (int j = 0; j < nb; ++j) {
