@@ -196,11 +196,12 @@ struct WaPlan {
   size_t partial_bytes;    // of WaGemmParams::partial
 };
 WaPlan wa_gemm_plan(int64_t M, int64_t N, int64_t K, int64_t ldx, int64_t ldw);
-int launch_wa_gemm(const WaGemmParams& p, hipStream_t stream);
 
 // The fused weight-activation path (both 8-bit formats as candidates, per-tensor scales)
 // works on groups of up to kWaGroup layers: one launch per step for the whole group.
 constexpr int kWaGroup = 8;
+int launch_wa_gemm(const WaGemmParams& p, hipStream_t stream);
+int launch_wa_gemms(const WaGemmParams* p, int n, hipStream_t stream);   // of a group: the layers may share launches
 
 // Pass 1 + 2 over the inputs of the group's layers (up to 2 * kWaGroup tensors, one launch per
 // pass): largest magnitude, then both quantized copies and the tensor error of each format.

@@ -157,8 +157,19 @@ MOFQ_DEV void tile_of(const GemmArgs& a, int t, int& bm, int& bn) {
   bn = in_band / rows_in_band;
 }
 
-template <typename T, int KIND1, int KIND2, bool PIECES, bool WIDE>
-__global__ __launch_bounds__(T::NW * 64) __attribute__((amdgpu_waves_per_eu(T::PER_SIMD, T::PER_SIMD))) void wa_gemm_kernel(const GemmArgs a) {
+// The layers of a launch.  Layers one launch after the other leave compute units idle in each one's last round (688 tiles of
+// 2048 x 11008 x 4096 are 2.69 rounds); together they have one last round.  The XCDs' ranges are those of each layer by itself.
+template <int N> struct GemmBatch {
+  GemmArgs a[N];
+  int32_t first[N];   // first workgroup of a layer; unused entries: INT_MAX
+};
+
+template <typename T, int KIND1, int KIND2, bool PIECES, bool WIDE, int N>
+__global__ __launch_bounds__(T::NW * 64) __attribute__((amdgpu_waves_per_eu(T::PER_SIMD, T::PER_SIMD))) void wa_gemm_kernel(const GemmBatch<N> batch) {
+  int layer = 0;
+#pragma unroll
+  for (int i = 1; i < N; ++i) layer += static_cast<int>(blockIdx.x) >= batch.first[i] ? 1 : 0;
+  const GemmArgs& a = batch.a[layer];
   constexpr int TM = T::TM, TN = T::TN, WM = T::WM, WN = T::WN, NW = T::NW;
   constexpr int TI = WM / 32, TJ = WN / 32;
   constexpr int STAGE = T::STAGE;
@@ -177,7 +188,7 @@ __global__ __launch_bounds__(T::NW * 64) __attribute__((amdgpu_waves_per_eu(T::P
   const int r = lane & 31, g = lane >> 5;
 
   const int tiles = a.tiles_m * a.tiles_n;
-  int t = regrouped(blockIdx.x, gridDim.x), piece = 0;
+  int t = N > 1 ? regrouped(static_cast<int>(blockIdx.x) - batch.first[layer], tiles) : regrouped(blockIdx.x, gridDim.x), piece = 0;
   if constexpr (PIECES) { piece = t / tiles; t -= piece * tiles; }
   int bm, bn;
   tile_of(a, t, bm, bn);
@@ -821,10 +832,13 @@ WaPlan wa_gemm_plan(int64_t M, int64_t N, int64_t K, int64_t ldx, int64_t ldw) {
   return p;
 }
 
-int launch_wa_gemm(const WaGemmParams& p, hipStream_t st) {
+namespace {
+
+// Kernel arguments of a layer but for its tiles.
+int gemm_args(const WaGemmParams& p, GemmArgs& a) {
   if (p.K % 64 != 0) return MOFQ_ERR_UNSUPPORTED;
   if (p.q[0].kind == WA_NONE) return MOFQ_ERR_INVALID_ARG;   // the first slot carries the Y^2 sum
-  GemmArgs a{};
+  a = GemmArgs{};
   const int32_t lines8 = static_cast<int32_t>((p.K + 127) / 128), lines16 = static_cast<int32_t>(p.K / 64);
   a.seg[SEG_REF] = Segment{p.x, p.w, p.ldx * 2, p.ldw * 2, lines16, 0};
   for (int i = 0; i < 2; ++i) {
@@ -843,41 +857,59 @@ int launch_wa_gemm(const WaGemmParams& p, hipStream_t st) {
   a.w_per_channel = p.w_per_channel;
   a.M = static_cast<int32_t>(p.M); a.N = static_cast<int32_t>(p.N);
   a.part[2] = p.part_p;
+  return MOFQ_OK;
+}
+template <typename T> void set_tiles(const WaGemmParams& p, GemmArgs& a) {
+  a.tiles_m = static_cast<int32_t>((p.M + T::TM - 1) / T::TM);
+  a.tiles_n = static_cast<int32_t>((p.N + T::TN - 1) / T::TN);
+}
+
+}  // namespace
+
+int launch_wa_gemm(const WaGemmParams& p, hipStream_t st) {
+  GemmBatch<1> batch{};
+  GemmArgs& a = batch.a[0];
+  const int rc = gemm_args(p, a);
+  if (rc != MOFQ_OK) return rc;
   const int k1 = p.q[0].kind, k2 = p.q[1].kind;
   const WaPlan plan = wa_gemm_plan(p.M, p.N, p.K, p.ldx, p.ldw);
   auto launch = [&](auto k1_c, auto k2_c) {
     constexpr int K1 = decltype(k1_c)::value, K2 = decltype(k2_c)::value;
     auto tiled = [&](auto tile_c, auto kernel, int pieces = 1) {
       using T = decltype(tile_c);
-      a.tiles_m = static_cast<int32_t>((p.M + T::TM - 1) / T::TM);
-      a.tiles_n = static_cast<int32_t>((p.N + T::TN - 1) / T::TN);
-      hipLaunchKernelGGL(kernel, dim3(static_cast<unsigned>(plan.blocks * pieces)), dim3(T::NW * 64), 0, st, a);
+      set_tiles<T>(p, a);
+      hipLaunchKernelGGL(kernel, dim3(static_cast<unsigned>(plan.blocks * pieces)), dim3(T::NW * 64), 0, st, batch);
+    };
+    auto shared = [&](auto tile_c, auto kernel) {
+      using T = decltype(tile_c);
+      set_tiles<T>(p, a);
+      hipLaunchKernelGGL(kernel, dim3(static_cast<unsigned>(plan.blocks)), dim3(T::NW * 64), 0, st, a);
     };
     constexpr bool SHARED = K1 == WA_GRID_BF16 && K2 == WA_GRID_BF16;
     if constexpr (SHARED) {   // all three products take the unquantized X
       if (p.q[0].x != p.x || p.q[1].x != p.x || p.ldx != p.K || p.q[0].sx || p.q[1].sx) return static_cast<int>(MOFQ_ERR_UNSUPPORTED);
     }
     if (plan.tile == WaPlan::kWide) {
-      tiled(Small{}, wa_gemm_kernel<Small, K1, K2, false, true>);
+      tiled(Small{}, wa_gemm_kernel<Small, K1, K2, false, true, 1>);
     } else if (plan.run && !(SHARED && plan.blocks > kProductsOnly)) {
       for (int q = 0; q < 3; ++q) {
         const int stages = q == 0 ? a.seg[SEG_REF].stages : a.seg[SEG_Q + 2 * (q - 1)].stages;
         a.piece0[q + 1] = a.piece0[q] + (stages + plan.run - 1) / plan.run;
       }
       a.partial = static_cast<float*>(p.partial);
-      tiled(Small{}, wa_gemm_kernel<Small, K1, K2, true, false>, a.piece0[3]);
+      tiled(Small{}, wa_gemm_kernel<Small, K1, K2, true, false, 1>, a.piece0[3]);
       hipLaunchKernelGGL((wa_pieces_kernel<Small, K1, K2>), dim3(static_cast<unsigned>(plan.blocks)), dim3(Small::NW * 64), 0, st, a);
     } else if constexpr (SHARED) {
       switch (plan.tile) {
-        case WaPlan::kLarge: tiled(SharedLarge{}, wa_gemm_shared_kernel<SharedLarge>); break;
-        case WaPlan::kMedium: tiled(SharedMedium{}, wa_gemm_shared_kernel<SharedMedium>); break;
-        default: tiled(SharedSmall{}, wa_gemm_shared_kernel<SharedSmall>);
+        case WaPlan::kLarge: shared(SharedLarge{}, wa_gemm_shared_kernel<SharedLarge>); break;
+        case WaPlan::kMedium: shared(SharedMedium{}, wa_gemm_shared_kernel<SharedMedium>); break;
+        default: shared(SharedSmall{}, wa_gemm_shared_kernel<SharedSmall>);
       }
     } else {
       switch (plan.tile) {
-        case WaPlan::kLarge: tiled(Large{}, wa_gemm_kernel<Large, K1, K2, false, false>); break;
-        case WaPlan::kMedium: tiled(Medium{}, wa_gemm_kernel<Medium, K1, K2, false, false>); break;
-        default: tiled(Small{}, wa_gemm_kernel<Small, K1, K2, false, false>);
+        case WaPlan::kLarge: tiled(Large{}, wa_gemm_kernel<Large, K1, K2, false, false, 1>); break;
+        case WaPlan::kMedium: tiled(Medium{}, wa_gemm_kernel<Medium, K1, K2, false, false, 1>); break;
+        default: tiled(Small{}, wa_gemm_kernel<Small, K1, K2, false, false, 1>);
       }
     }
     return hip_status(hipGetLastError());
@@ -888,6 +920,57 @@ int launch_wa_gemm(const WaGemmParams& p, hipStream_t st) {
   MOFQ_WA(WA_GRID_BF16, WA_NONE) MOFQ_WA(WA_FP8, WA_NONE) MOFQ_WA(WA_GRID_BF16, WA_GRID_BF16)
 #undef MOFQ_WA
   return MOFQ_ERR_UNSUPPORTED;
+}
+
+// Layers of one tile whose products are whole share a launch, the longest loops first; the others have their own.
+int launch_wa_gemms(const WaGemmParams* p, int n, hipStream_t st) {
+  if (!p || n < 1 || n > kWaGroup) return MOFQ_ERR_INVALID_ARG;
+  bool done[kWaGroup] = {};
+  for (const int tile : {WaPlan::kLarge, WaPlan::kMedium, WaPlan::kSmall}) {
+    int list[kWaGroup], m = 0;
+    for (int i = 0; i < n; ++i) {
+      const WaPlan plan = wa_gemm_plan(p[i].M, p[i].N, p[i].K, p[i].ldx, p[i].ldw);
+      const bool pair = p[i].q[0].kind == WA_INT8 && (p[i].q[1].kind == WA_FP8 || p[i].q[1].kind == WA_GRID_BF16) && p[i].q[1].kind == p[0].q[1].kind;
+      if (plan.tile == tile && !plan.run && pair) list[m++] = i;
+    }
+    if (m < 2) continue;
+    std::stable_sort(list, list + m, [&](int i, int j) { return p[i].K > p[j].K; });
+    GemmBatch<kWaGroup> batch{};
+    static_assert(sizeof(batch) <= 4096, "kernel arguments");
+    int64_t blocks = 0;
+    for (int i = 0; i < kWaGroup; ++i) batch.first[i] = INT32_MAX;
+    for (int i = 0; i < m; ++i) {
+      const int rc = gemm_args(p[list[i]], batch.a[i]);
+      if (rc != MOFQ_OK) return rc;
+      switch (tile) {
+        case WaPlan::kLarge: set_tiles<Large>(p[list[i]], batch.a[i]); break;
+        case WaPlan::kMedium: set_tiles<Medium>(p[list[i]], batch.a[i]); break;
+        default: set_tiles<Small>(p[list[i]], batch.a[i]);
+      }
+      batch.first[i] = static_cast<int32_t>(blocks);
+      blocks += static_cast<int64_t>(batch.a[i].tiles_m) * batch.a[i].tiles_n;
+    }
+    if (blocks >= (int64_t{1} << 31)) continue;
+    auto launch = [&](auto k2_c) {
+      constexpr int K2 = decltype(k2_c)::value;
+      const dim3 grid(static_cast<unsigned>(blocks));
+      switch (tile) {
+        case WaPlan::kLarge: hipLaunchKernelGGL((wa_gemm_kernel<Large, WA_INT8, K2, false, false, kWaGroup>), grid, dim3(Large::NW * 64), 0, st, batch); break;
+        case WaPlan::kMedium: hipLaunchKernelGGL((wa_gemm_kernel<Medium, WA_INT8, K2, false, false, kWaGroup>), grid, dim3(Medium::NW * 64), 0, st, batch); break;
+        default: hipLaunchKernelGGL((wa_gemm_kernel<Small, WA_INT8, K2, false, false, kWaGroup>), grid, dim3(Small::NW * 64), 0, st, batch);
+      }
+    };
+    if (p[0].q[1].kind == WA_FP8) launch(std::integral_constant<int, WA_FP8>{});
+    else launch(std::integral_constant<int, WA_GRID_BF16>{});
+    if (hipGetLastError() != hipSuccess) return MOFQ_ERR_HIP;
+    for (int i = 0; i < m; ++i) done[list[i]] = true;
+  }
+  for (int i = 0; i < n; ++i)
+    if (!done[i]) {
+      const int rc = launch_wa_gemm(p[i], st);
+      if (rc != MOFQ_OK) return rc;
+    }
+  return MOFQ_OK;
 }
 
 }  // namespace mofq
