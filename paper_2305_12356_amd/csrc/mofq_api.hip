@@ -615,7 +615,7 @@ struct WaLayerWs {
   WaFusedTensorWs x, w;
   double* part[3];
   int blocks;     // output tiles: values in each part
-  void* partial;  // the group's, for one matrix kernel after the other
+  void* partial;  // products in pieces: their sums
   bool fresh_x;   // false: x is the previous layer's (same descriptor, same group)
 };
 
@@ -643,7 +643,6 @@ bool wa_same_x(const mofq_tensor_t* x, int i) {
 size_t carve_wa_group(void* arena, int i0, int n, const mofq_tensor_t* w, const mofq_tensor_t* x, bool exact,
                       WaLayerWs* out) {
   Carver c(arena);
-  size_t partial_bytes = 0;
   for (int j = 0; j < n; ++j) {
     const int i = i0 + j;
     WaLayerWs l{};
@@ -676,11 +675,9 @@ size_t carve_wa_group(void* arena, int i0, int n, const mofq_tensor_t* w, const 
     const WaPlan plan = wa_plan(&w[i], &x[i]);
     l.blocks = plan.blocks;
     for (int q = 0; q < 3; ++q) l.part[q] = c.take<double>(plan.blocks);
-    partial_bytes = std::max(partial_bytes, plan.partial_bytes);
+    l.partial = c.take<uint8_t>(plan.partial_bytes);
     if (out) out[j] = l;
   }
-  uint8_t* const partial = c.take<uint8_t>(partial_bytes);   // the matrix kernels follow each other
-  for (int j = 0; out && j < n; ++j) out[j].partial = partial;
   return (c.off + kAlign - 1) / kAlign * kAlign;
 }
 

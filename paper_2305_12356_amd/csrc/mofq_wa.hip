@@ -162,13 +162,17 @@ MOFQ_DEV void tile_of(const GemmArgs& a, int t, int& bm, int& bn) {
 template <int N> struct GemmBatch {
   GemmArgs a[N];
   int32_t first[N];   // first workgroup of a layer; unused entries: INT_MAX
+  MOFQ_DEV int layer_of(uint32_t block) const {
+    int layer = 0;
+#pragma unroll
+    for (int i = 1; i < N; ++i) layer += static_cast<int>(block) >= first[i] ? 1 : 0;
+    return layer;
+  }
 };
 
 template <typename T, int KIND1, int KIND2, bool PIECES, bool WIDE, int N>
 __global__ __launch_bounds__(T::NW * 64) __attribute__((amdgpu_waves_per_eu(T::PER_SIMD, T::PER_SIMD))) void wa_gemm_kernel(const GemmBatch<N> batch) {
-  int layer = 0;
-#pragma unroll
-  for (int i = 1; i < N; ++i) layer += static_cast<int>(blockIdx.x) >= batch.first[i] ? 1 : 0;
+  const int layer = batch.layer_of(blockIdx.x);
   const GemmArgs& a = batch.a[layer];
   constexpr int TM = T::TM, TN = T::TN, WM = T::WM, WN = T::WN, NW = T::NW;
   constexpr int TI = WM / 32, TJ = WN / 32;
@@ -188,7 +192,7 @@ __global__ __launch_bounds__(T::NW * 64) __attribute__((amdgpu_waves_per_eu(T::P
   const int r = lane & 31, g = lane >> 5;
 
   const int tiles = a.tiles_m * a.tiles_n;
-  int t = N > 1 ? regrouped(static_cast<int>(blockIdx.x) - batch.first[layer], tiles) : regrouped(blockIdx.x, gridDim.x), piece = 0;
+  int t = regrouped(static_cast<int>(blockIdx.x) - (N > 1 ? batch.first[layer] : 0), PIECES ? tiles * a.piece0[3] : tiles), piece = 0;
   if constexpr (PIECES) { piece = t / tiles; t -= piece * tiles; }
   int bm, bn;
   tile_of(a, t, bm, bn);
@@ -527,16 +531,19 @@ __global__ __launch_bounds__(T::NW * 64) __attribute__((amdgpu_waves_per_eu(T::P
 
 // The sums of a tile whose products were cut into pieces: fp32 (int32) partial sums in the order of K, then the
 // squared differences as above.
-template <typename T, int KIND1, int KIND2>
-__global__ __launch_bounds__(T::NW * 64) void wa_pieces_kernel(const GemmArgs a) {
+template <typename T, int KIND1, int KIND2, int N>
+__global__ __launch_bounds__(T::NW * 64) void wa_pieces_kernel(const GemmBatch<N> batch) {
+  const int layer = batch.layer_of(blockIdx.x);
+  const GemmArgs& a = batch.a[layer];
+  const int tile = static_cast<int>(blockIdx.x) - (N > 1 ? batch.first[layer] : 0);
   constexpr int NW = T::NW, TI = T::WM / 32, TJ = T::WN / 32;
   __shared__ double s_red[3][NW];
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int bm = blockIdx.x / a.tiles_n, bn = blockIdx.x - bm * a.tiles_n;
+  const int bm = tile / a.tiles_n, bn = tile - bm * a.tiles_n;
   const int m = bm * T::TM + wave / (T::TN / T::WN) * T::WM + 4 * (lane >> 5), n0 = bn * T::TN + wave % (T::TN / T::WN) * T::WN + (lane & 31);
-  const int64_t piece = static_cast<int64_t>(gridDim.x) * NW * (TI * TJ * 4 * 64);   // f32x4 from piece to piece
-  const f32x4* const from = reinterpret_cast<const f32x4*>(a.partial) + (static_cast<int64_t>(blockIdx.x) * NW + wave) * (TI * TJ * 4 * 64) + lane;
+  const int64_t piece = static_cast<int64_t>(a.tiles_m * a.tiles_n) * NW * (TI * TJ * 4 * 64);   // f32x4 from piece to piece
+  const f32x4* const from = reinterpret_cast<const f32x4*>(a.partial) + (static_cast<int64_t>(tile) * NW + wave) * (TI * TJ * 4 * 64) + lane;
   double e[2] = {0.0, 0.0}, p = 0.0;
 #pragma unroll
   for (int j = 0; j < TJ; ++j) {
@@ -583,7 +590,7 @@ __global__ __launch_bounds__(T::NW * 64) void wa_pieces_kernel(const GemmArgs a)
   if (threadIdx.x < 3 && a.part[threadIdx.x]) {
     double t = 0.0;
     for (int k = 0; k < NW; ++k) t += s_red[threadIdx.x][k];   // fixed order
-    a.part[threadIdx.x][blockIdx.x] = t;
+    a.part[threadIdx.x][tile] = t;
   }
 }
 
@@ -859,6 +866,15 @@ int gemm_args(const WaGemmParams& p, GemmArgs& a) {
   a.part[2] = p.part_p;
   return MOFQ_OK;
 }
+// Products in pieces of up to `run` stages: returns their number.
+int set_pieces(GemmArgs& a, int run, void* partial) {
+  for (int q = 0; q < 3; ++q) {
+    const int stages = q == 0 ? a.seg[SEG_REF].stages : a.seg[SEG_Q + 2 * (q - 1)].stages;
+    a.piece0[q + 1] = a.piece0[q] + (stages + run - 1) / run;
+  }
+  a.partial = static_cast<float*>(partial);
+  return a.piece0[3];
+}
 template <typename T> void set_tiles(const WaGemmParams& p, GemmArgs& a) {
   a.tiles_m = static_cast<int32_t>((p.M + T::TM - 1) / T::TM);
   a.tiles_n = static_cast<int32_t>((p.N + T::TN - 1) / T::TN);
@@ -892,13 +908,8 @@ int launch_wa_gemm(const WaGemmParams& p, hipStream_t st) {
     if (plan.tile == WaPlan::kWide) {
       tiled(Small{}, wa_gemm_kernel<Small, K1, K2, false, true, 1>);
     } else if (plan.run && !(SHARED && plan.blocks > kProductsOnly)) {
-      for (int q = 0; q < 3; ++q) {
-        const int stages = q == 0 ? a.seg[SEG_REF].stages : a.seg[SEG_Q + 2 * (q - 1)].stages;
-        a.piece0[q + 1] = a.piece0[q] + (stages + plan.run - 1) / plan.run;
-      }
-      a.partial = static_cast<float*>(p.partial);
-      tiled(Small{}, wa_gemm_kernel<Small, K1, K2, true, false, 1>, a.piece0[3]);
-      hipLaunchKernelGGL((wa_pieces_kernel<Small, K1, K2>), dim3(static_cast<unsigned>(plan.blocks)), dim3(Small::NW * 64), 0, st, a);
+      tiled(Small{}, wa_gemm_kernel<Small, K1, K2, true, false, 1>, set_pieces(a, plan.run, p.partial));
+      hipLaunchKernelGGL((wa_pieces_kernel<Small, K1, K2, 1>), dim3(static_cast<unsigned>(plan.blocks)), dim3(Small::NW * 64), 0, st, batch);
     } else if constexpr (SHARED) {
       switch (plan.tile) {
         case WaPlan::kLarge: shared(SharedLarge{}, wa_gemm_shared_kernel<SharedLarge>); break;
@@ -922,38 +933,52 @@ int launch_wa_gemm(const WaGemmParams& p, hipStream_t st) {
   return MOFQ_ERR_UNSUPPORTED;
 }
 
-// Layers of one tile whose products are whole share a launch, the longest loops first; the others have their own.
+// Layers of one tile, with whole products or with pieces, share a launch, the longest loops first.
 int launch_wa_gemms(const WaGemmParams* p, int n, hipStream_t st) {
   if (!p || n < 1 || n > kWaGroup) return MOFQ_ERR_INVALID_ARG;
   bool done[kWaGroup] = {};
-  for (const int tile : {WaPlan::kLarge, WaPlan::kMedium, WaPlan::kSmall}) {
+  for (int kind = 0; kind < 4; ++kind) {
+    const bool pieces = kind == 3;
+    const int tile = kind == 0 ? WaPlan::kLarge : (kind == 1 ? WaPlan::kMedium : WaPlan::kSmall);
     int list[kWaGroup], m = 0;
     for (int i = 0; i < n; ++i) {
       const WaPlan plan = wa_gemm_plan(p[i].M, p[i].N, p[i].K, p[i].ldx, p[i].ldw);
       const bool pair = p[i].q[0].kind == WA_INT8 && (p[i].q[1].kind == WA_FP8 || p[i].q[1].kind == WA_GRID_BF16) && p[i].q[1].kind == p[0].q[1].kind;
-      if (plan.tile == tile && !plan.run && pair) list[m++] = i;
+      if (plan.tile == tile && (plan.run > 0) == pieces && pair) list[m++] = i;
     }
     if (m < 2) continue;
     std::stable_sort(list, list + m, [&](int i, int j) { return p[i].K > p[j].K; });
     GemmBatch<kWaGroup> batch{};
     static_assert(sizeof(batch) <= 4096, "kernel arguments");
-    int64_t blocks = 0;
-    for (int i = 0; i < kWaGroup; ++i) batch.first[i] = INT32_MAX;
+    int64_t blocks = 0, sums = 0;
+    int32_t first_sum[kWaGroup];
+    for (int i = 0; i < kWaGroup; ++i) batch.first[i] = first_sum[i] = INT32_MAX;
     for (int i = 0; i < m; ++i) {
       const int rc = gemm_args(p[list[i]], batch.a[i]);
       if (rc != MOFQ_OK) return rc;
+      const WaGemmParams& q = p[list[i]];
+      const int n_pieces = pieces ? set_pieces(batch.a[i], wa_gemm_plan(q.M, q.N, q.K, q.ldx, q.ldw).run, q.partial) : 1;
       switch (tile) {
         case WaPlan::kLarge: set_tiles<Large>(p[list[i]], batch.a[i]); break;
         case WaPlan::kMedium: set_tiles<Medium>(p[list[i]], batch.a[i]); break;
         default: set_tiles<Small>(p[list[i]], batch.a[i]);
       }
+      const int64_t tiles = static_cast<int64_t>(batch.a[i].tiles_m) * batch.a[i].tiles_n;
       batch.first[i] = static_cast<int32_t>(blocks);
-      blocks += static_cast<int64_t>(batch.a[i].tiles_m) * batch.a[i].tiles_n;
+      first_sum[i] = static_cast<int32_t>(sums);
+      blocks += tiles * n_pieces;
+      sums += tiles;
     }
     if (blocks >= (int64_t{1} << 31)) continue;
     auto launch = [&](auto k2_c) {
       constexpr int K2 = decltype(k2_c)::value;
       const dim3 grid(static_cast<unsigned>(blocks));
+      if (pieces) {
+        hipLaunchKernelGGL((wa_gemm_kernel<Small, WA_INT8, K2, true, false, kWaGroup>), grid, dim3(Small::NW * 64), 0, st, batch);
+        std::copy(first_sum, first_sum + kWaGroup, batch.first);
+        hipLaunchKernelGGL((wa_pieces_kernel<Small, WA_INT8, K2, kWaGroup>), dim3(static_cast<unsigned>(sums)), dim3(Small::NW * 64), 0, st, batch);
+        return;
+      }
       switch (tile) {
         case WaPlan::kLarge: hipLaunchKernelGGL((wa_gemm_kernel<Large, WA_INT8, K2, false, false, kWaGroup>), grid, dim3(Large::NW * 64), 0, st, batch); break;
         case WaPlan::kMedium: hipLaunchKernelGGL((wa_gemm_kernel<Medium, WA_INT8, K2, false, false, kWaGroup>), grid, dim3(Medium::NW * 64), 0, st, batch); break;

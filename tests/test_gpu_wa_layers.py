@@ -319,16 +319,23 @@ def test_degenerate_layers(mq):
         assert float(x_out[0].scales.cpu()[0]) == 1.0 and float(w_out[1].scales.cpu()[0]) == 1.0
 
 
+SHARED_LAUNCHES = {
+    # large tiles: 4100 and 2500 columns; medium: 1200, 1100 and 1300; small: 500
+    "tiles": (2048, [(1200, 128), (4100, 192), (500, 128), (1100, 192), (2500, 64), (1300, 64), (2500, 192)]),
+    # products in pieces (20 stages of 64 columns and more), of different lengths, and one too short for them
+    "pieces": (130, [(100, 1344), (70, 2752), (200, 1280), (130, 1216), (64, 1344), (1000, 2752)]),
+}
+
+
+@pytest.mark.parametrize("name", list(SHARED_LAUNCHES))
 @pytest.mark.parametrize("metric_name", ["ERR_LAYER_OUTPUT", "ERR_LAYER_OUTPUT_FP8_UNIT"])
-def test_layers_that_share_launches_equal_single_calls(mq, metric_name):
-    """Layers of each tile in one group, two and three of one kind sharing a launch (numbers of tiles that are and are not
-    multiples of 8, K loops of different lengths), one kind alone."""
+def test_layers_that_share_launches_equal_single_calls(mq, metric_name, name):
+    """Several layers of one kind sharing a launch (numbers of tiles that are and are not multiples of 8, K loops of
+    different lengths), one kind alone."""
     metric = getattr(mq, metric_name)
     cfg = mq.Cfg(mq.PER_TENSOR, mi.clip_ratios(1))
-    tokens, ks = 2048, (128, 192, 64)
-    acts = {k: mi.activations(tokens, k, seed=k, device=DEV) for k in ks}
-    # large: 4100 and 2500 columns; medium: 1200, 1100 and 1300; small: 500
-    layers = [(1200, 128), (4100, 192), (500, 128), (1100, 192), (2500, 64), (1300, 64), (2500, 192)]
+    tokens, layers = SHARED_LAUNCHES[name]
+    acts = {k: mi.activations(tokens, k, seed=k, device=DEV) for k in {k for _, k in layers}}
     ws = [mi.llama_like_weight(n, k, seed=n + k, dtype=torch.bfloat16, device=DEV) for n, k in layers]
     xs = [acts[k] for _, k in layers]
     cands = [mq.INT8, mq.FP8_E4M3]
