@@ -55,16 +55,21 @@ struct PrepTensor {
 struct PrepArgs {
   PrepTensor t[kMaxTensors];
   int32_t first_block[kMaxTensors + 1];   // workgroups [first_block[k], first_block[k + 1]) walk tensor k
+  int32_t first_side[kMaxTensors + 1];    // quantize pass: behind them, those of the side operands
   int32_t n;
 };
 
 // The workgroup's tensor, its index among the tensor's workgroups and their number.
-MOFQ_DEV const PrepTensor& my_tensor(const PrepArgs& a, int& b, int& nb) {
-  int k = 0;
-  while (k + 1 < a.n && static_cast<int>(blockIdx.x) >= a.first_block[k + 1]) ++k;   // uniform
-  b = static_cast<int>(blockIdx.x) - a.first_block[k];
-  nb = a.first_block[k + 1] - a.first_block[k];
+MOFQ_DEV const PrepTensor& my_tensor(const PrepArgs& a, const int32_t (&first)[kMaxTensors + 1], int& k, int& b, int& nb) {
+  k = 0;
+  while (k + 1 < a.n && static_cast<int>(blockIdx.x) >= first[k + 1]) ++k;   // uniform
+  b = static_cast<int>(blockIdx.x) - first[k];
+  nb = first[k + 1] - first[k];
   return a.t[k];
+}
+MOFQ_DEV const PrepTensor& my_tensor(const PrepArgs& a, int& b, int& nb) {
+  int k;
+  return my_tensor(a, a.first_block, k, b, nb);
 }
 
 // Address of chunk c: rows are dense in the outputs, `ld` apart in the input.
@@ -76,37 +81,6 @@ MOFQ_DEV const uint16_t* chunk_src(const PrepTensor& t, int64_t c) {
 
 constexpr int kInFlight = 8;   // 16-byte loads in flight per lane (largest-magnitude pass)
 constexpr int kQuantInFlight = 2;   // quantize pass: every further chunk in flight costs some 17 registers
-
-__global__ __launch_bounds__(kThreads) void wa_absmax_kernel(const PrepArgs a) {
-  using L = Load8<BF16>;
-  __shared__ float s_wmax[kThreads / 64];
-  int b, nb;
-  const PrepTensor& t = my_tensor(a, b, nb);
-  const int tid = threadIdx.x;
-  const int64_t stride = static_cast<int64_t>(nb) * kThreads;
-  float amax = 0.0f;
-  int64_t c = static_cast<int64_t>(b) * kThreads + tid;
-  for (; c + (kInFlight - 1) * stride < t.n_chunks; c += kInFlight * stride) {
-    float v[kInFlight][8];
-#pragma unroll
-    for (int u = 0; u < kInFlight; ++u) L::load(chunk_src(t, c + u * stride), v[u]);
-#pragma unroll
-    for (int u = 0; u < kInFlight; ++u)
-#pragma unroll
-      for (int i = 0; i < 8; ++i) amax = __builtin_fmaxf(amax, __builtin_fabsf(v[u][i]));
-  }
-  for (; c < t.n_chunks; c += stride) {
-    float v[8];
-    L::load(chunk_src(t, c), v);
-#pragma unroll
-    for (int i = 0; i < 8; ++i) amax = __builtin_fmaxf(amax, __builtin_fabsf(v[i]));
-  }
-  amax = wave_max(amax);
-  if ((tid & 63) == 0) s_wmax[tid >> 6] = amax;
-  __syncthreads();
-  if (tid == 0)
-    t.absmax_part[b] = __builtin_fmaxf(__builtin_fmaxf(s_wmax[0], s_wmax[1]), __builtin_fmaxf(s_wmax[2], s_wmax[3]));
-}
 
 // One chunk in both formats: codes, optional grid values, squared differences.
 MOFQ_DEV void quant_chunk(const PrepTensor& t, int64_t c, const u32x4 raw, float iA, float iB, double sAd,
@@ -215,111 +189,137 @@ __global__ __launch_bounds__(kThreads) void wa_colmax_kernel(const PrepArgs a) {
 // activation.  (Any choice gives the same sum; the choice only decides how much the fp8 unit's
 // alignment can lose.)
 constexpr float kOutlierFactor = 4.0f;
-constexpr int kPickCached = 12288;   // column maxima held in LDS up to this many columns
-__global__ __launch_bounds__(kThreads) void wa_pick_kernel(const PrepArgs a) {
-  __shared__ float s_col[kPickCached];
-  __shared__ __attribute__((aligned(16))) uint8_t s_slot[kPickCached];
+//
+// A few workgroups beside a pass over the weights, so LDS and registers are left to that: the maxima are read from L2 each time, four
+// 16-byte loads in flight per lane.
+MOFQ_DEV void pick_columns(const PrepTensor& t) {
   __shared__ double s_sum[2][kThreads / 64];
   __shared__ uint32_t s_cnt[2][kThreads / 64];
   __shared__ float s_amax[kThreads / 64];
-  const PrepTensor& t = a.t[blockIdx.x];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int K = t.cols_i32;
-  const bool cached = K <= kPickCached;   // uniform
-  if (cached) {
-    // all of a thread's loads are issued before the first is used (K is a multiple of 64)
-    constexpr int NV = kPickCached / (kThreads * 4);
-    u32x4 v[NV];
+  const int K = t.cols_i32, nv = K / 4;   // K is a multiple of 64
+  const u32x4* const col4 = reinterpret_cast<const u32x4*>(t.colmax);
+  // f(vector, its four maxima) for the vectors first, first + step, .. of n
+  auto each = [&](int first, int step, int n, auto f) {
+    for (int i0 = 0; i0 < n; i0 += 4) {
+      u32x4 v[4];
 #pragma unroll
-    for (int u = 0; u < NV; ++u) {
-      const int c = (u * kThreads + tid) * 4;
-      if (c < K) v[u] = *reinterpret_cast<const u32x4*>(t.colmax + c);
-    }
+      for (int u = 0; u < 4; ++u) v[u] = col4[i0 + u < n ? first + (i0 + u) * step : first];
 #pragma unroll
-    for (int u = 0; u < NV; ++u) {
-      const int c = (u * kThreads + tid) * 4;
-      if (c < K) *reinterpret_cast<u32x4*>(&s_col[c]) = v[u];
+      for (int u = 0; u < 4; ++u)
+        if (i0 + u < n) f(first + (i0 + u) * step, v[u]);
     }
-    __syncthreads();
+  };
+  const int strided = tid < nv ? (nv - tid + kThreads - 1) / kThreads : 0;
+  double sum = 0.0;
+  float amax = 0.0f;
+  each(tid, kThreads, strided, [&](int, u32x4 v) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      sum += static_cast<double>(u2f(v[i]));
+      amax = __builtin_fmaxf(amax, u2f(v[i]));
+    }
+  });
+  sum = wave_sum(sum);
+  amax = wave_max(amax);
+  if (lane == 0) { s_sum[0][wave] = sum; s_amax[wave] = amax; }
+  __syncthreads();
+  // the tensor's largest magnitude is the largest column maximum
+  if (tid == 0) t.absmax_part[0] = __builtin_fmaxf(__builtin_fmaxf(s_amax[0], s_amax[1]), __builtin_fmaxf(s_amax[2], s_amax[3]));
+  const float thr0 = kOutlierFactor * static_cast<float>(((s_sum[0][0] + s_sum[0][1]) + (s_sum[0][2] + s_sum[0][3])) / K);
+  double sum1 = 0.0;
+  uint32_t n1 = 0;
+  each(tid, kThreads, strided, [&](int, u32x4 v) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+      if (!(u2f(v[i]) > thr0)) { sum1 += static_cast<double>(u2f(v[i])); ++n1; }
+  });
+  sum1 = wave_sum(sum1);
+#pragma unroll
+  for (int d = 32; d >= 1; d >>= 1) n1 += static_cast<uint32_t>(__shfl_xor(static_cast<int>(n1), d, 64));
+  if (lane == 0) { s_sum[1][wave] = sum1; s_cnt[1][wave] = n1; }
+  __syncthreads();
+  const uint32_t n_typ = (s_cnt[1][0] + s_cnt[1][1]) + (s_cnt[1][2] + s_cnt[1][3]);
+  const double typ = ((s_sum[1][0] + s_sum[1][1]) + (s_sum[1][2] + s_sum[1][3])) / (n_typ > 0 ? n_typ : 1);
+  const float thr = n_typ > 0 ? kOutlierFactor * static_cast<float>(typ) : thr0;
+  // thread t owns the vectors [t * per, (t + 1) * per): count, scan over the threads, assign slots
+  const int per = (nv + kThreads - 1) / kThreads;
+  const int lo = tid * per < nv ? tid * per : 0, own = tid * per < nv ? (nv - tid * per < per ? nv - tid * per : per) : 0;
+  uint32_t n = 0;
+  each(lo, 1, own, [&](int, u32x4 v) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) n += u2f(v[i]) > thr ? 1u : 0u;
+  });
+  uint32_t incl = n;
+#pragma unroll
+  for (int d = 1; d < 64; d <<= 1) {
+    const uint32_t o = static_cast<uint32_t>(__shfl_up(static_cast<int>(incl), d, 64));
+    if (lane >= d) incl += o;
   }
-  // two copies of the rest, so that neither reads through a run-time choice of memory
-  auto rest = [&](auto cached_c) {
-    constexpr bool CACHED = decltype(cached_c)::value;
-    auto col = [&](int c) {
-      if constexpr (CACHED) return s_col[c];
-      else return t.colmax[c];
-    };
-    double sum = 0.0;
-    float amax = 0.0f;
-    for (int c = tid; c < K; c += kThreads) {
-      const float v = col(c);
-      sum += static_cast<double>(v);
-      amax = __builtin_fmaxf(amax, v);
-    }
-    sum = wave_sum(sum);
-    amax = wave_max(amax);
-    if (lane == 0) { s_sum[0][wave] = sum; s_amax[wave] = amax; }
-    __syncthreads();
-    // the tensor's largest magnitude is the largest column maximum: the first pass skips it
-    if (tid == 0) t.absmax_part[0] = __builtin_fmaxf(__builtin_fmaxf(s_amax[0], s_amax[1]), __builtin_fmaxf(s_amax[2], s_amax[3]));
-    const float thr0 = kOutlierFactor * static_cast<float>(((s_sum[0][0] + s_sum[0][1]) + (s_sum[0][2] + s_sum[0][3])) / K);
-    double sum1 = 0.0;
-    uint32_t n1 = 0;
-    for (int c = tid; c < K; c += kThreads) {
-      const float v = col(c);
-      if (!(v > thr0)) { sum1 += static_cast<double>(v); ++n1; }
-    }
-    sum1 = wave_sum(sum1);
+  if (lane == 63) s_cnt[0][wave] = incl;
+  __syncthreads();
+  uint32_t base = incl - n;
+  for (int w = 0; w < wave; ++w) base += s_cnt[0][w];
+  each(lo, 1, own, [&](int c4, u32x4 v) {
+    uint32_t slots = 0;
 #pragma unroll
-    for (int d = 32; d >= 1; d >>= 1) n1 += static_cast<uint32_t>(__shfl_xor(static_cast<int>(n1), d, 64));
-    if (lane == 0) { s_sum[1][wave] = sum1; s_cnt[1][wave] = n1; }
-    __syncthreads();
-    const uint32_t n_typ = (s_cnt[1][0] + s_cnt[1][1]) + (s_cnt[1][2] + s_cnt[1][3]);
-    const double typ = ((s_sum[1][0] + s_sum[1][1]) + (s_sum[1][2] + s_sum[1][3])) / (n_typ > 0 ? n_typ : 1);
-    const float thr = n_typ > 0 ? kOutlierFactor * static_cast<float>(typ) : thr0;
-    // thread t owns the columns [t * per, (t + 1) * per): count, scan over the threads, assign slots
-    const int per = (K + kThreads - 1) / kThreads;
-    const int lo = tid * per, hi = (lo + per < K) ? lo + per : K;
-    uint32_t n = 0;
-    for (int c = lo; c < hi; ++c) n += (col(c) > thr) ? 1u : 0u;
-    uint32_t incl = n;
-#pragma unroll
-    for (int d = 1; d < 64; d <<= 1) {
-      const uint32_t o = static_cast<uint32_t>(__shfl_up(static_cast<int>(incl), d, 64));
-      if (lane >= d) incl += o;
-    }
-    if (lane == 63) s_cnt[0][wave] = incl;
-    __syncthreads();
-    uint32_t base = incl - n;
-    for (int w = 0; w < wave; ++w) base += s_cnt[0][w];
-    for (int c = lo; c < hi; ++c) {
-      uint8_t slot = 0xFFu;
-      if (col(c) > thr) {
-        if (base < static_cast<uint32_t>(kWaSideCols)) { slot = static_cast<uint8_t>(base); t.side_cols[base] = c; }
+    for (int i = 0; i < 4; ++i) {
+      uint32_t slot = 0xFFu;
+      if (u2f(v[i]) > thr) {
+        if (base < static_cast<uint32_t>(kWaSideCols)) { slot = base; t.side_cols[base] = 4 * c4 + i; }
         ++base;
       }
-      if constexpr (CACHED) s_slot[c] = slot;
-      else t.col_slot[c] = slot;
+      slots |= slot << (8 * i);
     }
-    if constexpr (CACHED) {   // the slot bytes leave in 16-byte pieces
-      __syncthreads();
-      for (int c = tid * 16; c < K; c += kThreads * 16)
-        *reinterpret_cast<u32x4*>(t.col_slot + c) = *reinterpret_cast<const u32x4*>(&s_slot[c]);
-    }
-    if (tid == kThreads - 1) t.side_cols[kWaSideCols] = static_cast<int32_t>(base < static_cast<uint32_t>(kWaSideCols) ? base : kWaSideCols);
-  };
-  if (cached) rest(std::true_type{});
-  else rest(std::false_type{});
+    reinterpret_cast<uint32_t*>(t.col_slot)[c4] = slots;
+  });
+  if (tid == kThreads - 1) t.side_cols[kWaSideCols] = static_cast<int32_t>(base < static_cast<uint32_t>(kWaSideCols) ? base : kWaSideCols);
+}
+
+// First pass: largest magnitudes.  The activations of a column split, a workgroup each, come first: their largest magnitude
+// is that of the column maxima.  Picking their columns beside the weights' largest magnitudes instead of before them takes a launch
+// of 15 us out of a 7B block's step.
+__global__ __launch_bounds__(kThreads) void wa_absmax_kernel(const PrepArgs a) {
+  using L = Load8<BF16>;
+  __shared__ float s_wmax[kThreads / 64];
+  int b, nb;
+  const PrepTensor& t = my_tensor(a, b, nb);
+  if (t.is_x && t.side) {   // uniform
+    pick_columns(t);
+    return;
+  }
+  const int tid = threadIdx.x;
+  const int64_t stride = static_cast<int64_t>(nb) * kThreads;
+  float amax = 0.0f;
+  int64_t c = static_cast<int64_t>(b) * kThreads + tid;
+  for (; c + (kInFlight - 1) * stride < t.n_chunks; c += kInFlight * stride) {
+    float v[kInFlight][8];
+#pragma unroll
+    for (int u = 0; u < kInFlight; ++u) L::load(chunk_src(t, c + u * stride), v[u]);
+#pragma unroll
+    for (int u = 0; u < kInFlight; ++u)
+#pragma unroll
+      for (int i = 0; i < 8; ++i) amax = __builtin_fmaxf(amax, __builtin_fabsf(v[u][i]));
+  }
+  for (; c < t.n_chunks; c += stride) {
+    float v[8];
+    L::load(chunk_src(t, c), v);
+#pragma unroll
+    for (int i = 0; i < 8; ++i) amax = __builtin_fmaxf(amax, __builtin_fabsf(v[i]));
+  }
+  amax = wave_max(amax);
+  if ((tid & 63) == 0) s_wmax[tid >> 6] = amax;
+  __syncthreads();
+  if (tid == 0)
+    t.absmax_part[b] = __builtin_fmaxf(__builtin_fmaxf(s_wmax[0], s_wmax[1]), __builtin_fmaxf(s_wmax[2], s_wmax[3]));
 }
 
 // The side operand of a tensor: the E4M3 grid values of its split-off columns as bf16, dense
-// [rows][kWaSideCols], zero in the slots beyond the number of split-off columns.  Runs after the
-// quantize pass (which leaves the E4M3 scale in t.scale[1]).
-__global__ __launch_bounds__(kThreads) void wa_side_kernel(const PrepArgs a) {
-  int b, nb;
-  const PrepTensor& t = my_tensor(a, b, nb);
+// [rows][kWaSideCols], zero in the slots beyond the number of split-off columns.  The last workgroups of the quantize pass;
+// workgroup b of nb.
+MOFQ_DEV void side_operand(const PrepTensor& t, int b, int nb, float scale) {
   const int count = t.side_cols[kWaSideCols];
-  const float inv = 1.0f / t.scale[1];
+  const float inv = 1.0f / scale;
   const int64_t n = static_cast<int64_t>(t.rows_i32) * kWaSideCols;
   for (int64_t e = static_cast<int64_t>(b) * kThreads + threadIdx.x; e < n; e += static_cast<int64_t>(nb) * kThreads) {
     const int slot = static_cast<int>(e % kWaSideCols);
@@ -335,11 +335,16 @@ __global__ __launch_bounds__(kThreads) void wa_side_kernel(const PrepArgs a) {
   }
 }
 
+// SIDE: with the side operands' workgroups behind the others.
+template <bool SIDE>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(5))) void wa_quant_kernel(const PrepArgs a) {
   __shared__ float s_tmp[kThreads / 64];
   __shared__ double s_part[kThreads / 64][2];
-  int b, nb;
-  const PrepTensor& t = my_tensor(a, b, nb);
+  int k, b, nb;
+  const bool side = SIDE && static_cast<int>(blockIdx.x) >= a.first_block[a.n];   // uniform
+  const PrepTensor& t = side ? my_tensor(a, a.first_side, k, b, nb) : my_tensor(a, a.first_block, k, b, nb);
+  const int n_side = nb;
+  if (side) nb = a.first_block[k + 1] - a.first_block[k];
   const int tid = threadIdx.x;
   // the tensor's largest magnitude from the partials of the first pass (same launch shape) or
   // from the one the column pass left
@@ -352,6 +357,10 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(5))) v
   amax = __builtin_fmaxf(__builtin_fmaxf(s_tmp[0], s_tmp[1]), __builtin_fmaxf(s_tmp[2], s_tmp[3]));
   const float sA = unit_scale(amax, t.ratio, Codec<MOFQ_INT8>::QMAX, false);
   const float sB = unit_scale(amax, t.ratio, Codec<MOFQ_FP8_E4M3>::QMAX, false);
+  if (side) {
+    side_operand(t, b, n_side, sB);
+    return;
+  }
   if (b == 0 && tid == 0) { t.scale[0] = sA; t.scale[1] = sB; }
   const float iA = 1.0f / sA, iB = 1.0f / sB;
   const double sAd = static_cast<double>(sA), sBd = static_cast<double>(sB);
@@ -450,38 +459,37 @@ int launch_wa_prep(const WaPrepTensor* p, int n, hipStream_t st) {
     a.first_block[k + 1] = a.first_block[k] + static_cast<int32_t>(nb);
   }
   const int blocks = a.first_block[a.n];
-  // first pass: every tensor but the activations of a column split, whose largest magnitude
-  // comes out of the column maxima
-  PrepArgs am{};
+  // column split: the activations' column maxima come first, the pick beside the largest magnitudes of the other tensors, and
+  // the side operands at the end of the quantize pass (which zeroes the picked columns in the fp8 operand)
+  PrepArgs xs{}, am{};
+  a.first_side[0] = blocks;
   for (int k = 0; k < a.n; ++k) {
-    if (a.t[k].side && a.t[k].is_x) { a.t[k].n_absmax = 1; continue; }
+    const PrepTensor& t = a.t[k];
+    int64_t side = 0;
+    if (t.side) {
+      side = std::min<int64_t>((static_cast<int64_t>(t.rows_i32) * kWaSideCols + kThreads * 4 - 1) / (kThreads * 4), 1024);
+      if (t.is_x) {
+        a.t[k].n_absmax = 1;
+        xs.t[xs.n] = am.t[am.n] = t;
+        xs.first_block[xs.n + 1] = xs.first_block[xs.n] + t.cols_i32 / 64;
+        am.first_block[am.n + 1] = am.first_block[am.n] + 1;
+        ++xs.n;
+        ++am.n;
+      }
+    }
+    a.first_side[k + 1] = a.first_side[k] + static_cast<int32_t>(side);
+  }
+  for (int k = 0; k < a.n; ++k) {
+    if (a.t[k].side && a.t[k].is_x) continue;
     am.t[am.n] = a.t[k];
     am.first_block[am.n + 1] = am.first_block[am.n] + (a.first_block[k + 1] - a.first_block[k]);
     ++am.n;
   }
-  if (am.n) hipLaunchKernelGGL(wa_absmax_kernel, dim3(am.first_block[am.n]), dim3(kThreads), 0, st, am);
-  // column split: the activations' column maxima and the pick come before the quantize pass
-  // (which zeroes the picked columns in the fp8 operand), the side operands after it (they
-  // use the scale it leaves)
-  PrepArgs xs{}, sd{};
-  for (int k = 0; k < a.n; ++k) {
-    if (!a.t[k].side) continue;
-    if (a.t[k].is_x) {
-      xs.t[xs.n] = a.t[k];
-      xs.first_block[xs.n + 1] = xs.first_block[xs.n] + a.t[k].cols_i32 / 64;
-      ++xs.n;
-    }
-    sd.t[sd.n] = a.t[k];
-    const int64_t nb = (static_cast<int64_t>(a.t[k].rows_i32) * kWaSideCols + kThreads * 4 - 1) / (kThreads * 4);
-    sd.first_block[sd.n + 1] = sd.first_block[sd.n] + static_cast<int32_t>(std::min<int64_t>(nb, 1024));
-    ++sd.n;
-  }
-  if (xs.n) {
-    hipLaunchKernelGGL(wa_colmax_kernel, dim3(xs.first_block[xs.n]), dim3(kThreads), 0, st, xs);
-    hipLaunchKernelGGL(wa_pick_kernel, dim3(xs.n), dim3(kThreads), 0, st, xs);
-  }
-  hipLaunchKernelGGL(wa_quant_kernel, dim3(blocks), dim3(kThreads), 0, st, a);
-  if (sd.n) hipLaunchKernelGGL(wa_side_kernel, dim3(sd.first_block[sd.n]), dim3(kThreads), 0, st, sd);
+  static_assert(sizeof(PrepArgs) <= 4096, "kernel arguments");
+  if (xs.n) hipLaunchKernelGGL(wa_colmax_kernel, dim3(xs.first_block[xs.n]), dim3(kThreads), 0, st, xs);
+  hipLaunchKernelGGL(wa_absmax_kernel, dim3(am.first_block[am.n]), dim3(kThreads), 0, st, am);
+  if (a.first_side[a.n] > blocks) hipLaunchKernelGGL(wa_quant_kernel<true>, dim3(a.first_side[a.n]), dim3(kThreads), 0, st, a);
+  else hipLaunchKernelGGL(wa_quant_kernel<false>, dim3(blocks), dim3(kThreads), 0, st, a);
   return hip_status(hipGetLastError());
 }
 
