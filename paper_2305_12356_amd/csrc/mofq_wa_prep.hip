@@ -81,61 +81,83 @@ MOFQ_DEV const uint16_t* chunk_src(const PrepTensor& t, int64_t c) {
 }
 
 constexpr int kInFlight = 8;   // 16-byte loads in flight per lane (largest-magnitude pass)
-constexpr int kQuantInFlight = 2;   // quantize pass: every further chunk in flight costs some 17 registers
 
-// One chunk in both formats: codes, optional grid values, squared differences.
-MOFQ_DEV void quant_chunk(const PrepTensor& t, int64_t c, const u32x4 raw, float iA, float iB, double sAd,
-                          double sBd, double& accA, double& accB) {
-  float v[8];
+// One chunk in both formats: codes, grid values of E4M3 as bf16 (EXACT), squared differences.
+struct QuantChunk {
+  u32x2 i8, f8;
+  u32x4 g;
+};
+template <bool EXACT>
+MOFQ_DEV QuantChunk quant_chunk(const u32x4 raw, float iA, float iB, double sAd, double sBd, double& accA, double& accB) {
+  QuantChunk q;
+  float v[8], y[8];
+  int wf[2] = {0, 0};
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
     v[2 * i] = u2f(raw[i] << 16);           // bf16 is the top half of an fp32
     v[2 * i + 1] = u2f(raw[i] & 0xFFFF0000u);
   }
-  uint32_t wi[2] = {0u, 0u};
-  int wf[2] = {0, 0};
-  u32x4 gb;
+  auto add = [](double& acc, float grid, double s, float x) {
+    const double d = __builtin_fma(-static_cast<double>(grid), s, static_cast<double>(x));
+    acc = __builtin_fma(d, d, acc);
+  };
 #pragma unroll
   for (int i = 0; i < 8; i += 2) {
-    const float q0 = Codec<MOFQ_INT8>::grid(v[i] * iA), q1 = Codec<MOFQ_INT8>::grid(v[i + 1] * iA);
-    wi[i >> 2] |= (static_cast<uint32_t>(static_cast<int>(q0)) & 0xFFu) << (8 * (i & 3));
-    wi[i >> 2] |= (static_cast<uint32_t>(static_cast<int>(q1)) & 0xFFu) << (8 * ((i & 3) + 1));
-    const double d0 = __builtin_fma(-static_cast<double>(q0), sAd, static_cast<double>(v[i]));
-    const double d1 = __builtin_fma(-static_cast<double>(q1), sAd, static_cast<double>(v[i + 1]));
-    accA = __builtin_fma(d0, d0, accA);
-    accA = __builtin_fma(d1, d1, accA);
+    // clamping before rounding gives the same integer; adding 1.5 * 2^23 rounds to nearest even and leaves the
+    // two's-complement integer in the low bits (encode_scaled8)
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      y[i + h] = med3(v[i + h] * iA, -128.0f, 127.0f) + 12582912.0f;
+      add(accA, y[i + h] - 12582912.0f, sAd, v[i + h]);
+    }
     // E4M3 through the pack-convert (round to nearest even, subnormals kept; saturating once
     // the input is clamped), which agrees with the codec on every finite fp32 pattern
-    const int p = __builtin_amdgcn_cvt_pk_fp8_f32(med3(v[i] * iB, -448.0f, 448.0f),
-                                                  med3(v[i + 1] * iB, -448.0f, 448.0f), 0, false);
-    const f32x2 g = __builtin_amdgcn_cvt_pk_f32_fp8(p, false);
-    wf[i >> 2] |= (p & 0xFFFF) << (16 * ((i >> 1) & 1));
-    gb[i >> 1] = (f2u(g[0]) >> 16) | (f2u(g[1]) & 0xFFFF0000u);   // at most 4 significant bits: exact in bf16
-    const double e0 = __builtin_fma(-static_cast<double>(g[0]), sBd, static_cast<double>(v[i]));
-    const double e1 = __builtin_fma(-static_cast<double>(g[1]), sBd, static_cast<double>(v[i + 1]));
-    accB = __builtin_fma(e0, e0, accB);
-    accB = __builtin_fma(e1, e1, accB);
+    const float t0 = med3(v[i] * iB, -448.0f, 448.0f), t1 = med3(v[i + 1] * iB, -448.0f, 448.0f);
+    f32x2 g;
+    if (i % 4 == 0) {
+      wf[i / 4] = __builtin_amdgcn_cvt_pk_fp8_f32(t0, t1, wf[i / 4], false);
+      g = __builtin_amdgcn_cvt_pk_f32_fp8(wf[i / 4], false);
+    } else {
+      wf[i / 4] = __builtin_amdgcn_cvt_pk_fp8_f32(t0, t1, wf[i / 4], true);
+      g = __builtin_amdgcn_cvt_pk_f32_fp8(wf[i / 4], true);
+    }
+    if constexpr (EXACT) q.g[i >> 1] = (f2u(g[0]) >> 16) | (f2u(g[1]) & 0xFFFF0000u);   // at most 4 significant bits: exact in bf16
+    add(accB, g[0], sBd, v[i]);
+    add(accB, g[1], sBd, v[i + 1]);
     // one pair at a time: the two fp64 chains are sequential anyway, and scheduling all eight
     // elements of a chunk together costs some 130 registers
     __builtin_amdgcn_sched_barrier(0);
   }
-  u32x2 oi, of;
-  oi[0] = wi[0];
-  oi[1] = wi[1];
-  of[0] = static_cast<uint32_t>(wf[0]);
-  of[1] = static_cast<uint32_t>(wf[1]);
-  reinterpret_cast<u32x2*>(t.q_i8)[c] = oi;
-  reinterpret_cast<u32x2*>(t.q_f8)[c] = of;
-  if (t.q_g) reinterpret_cast<u32x4*>(t.q_g)[c] = gb;
-  if (t.q_f8_main) {   // uniform: the activation of an fp8-unit product
-    // slot bytes of the chunk's 8 columns: bit 7 set = not split off = keep the code
-    const uint32_t col8 = static_cast<uint32_t>(c) % static_cast<uint32_t>(t.cpr);   // fewer than 2^31 chunks (checked by the host)
-    const u32x2 m = reinterpret_cast<const u32x2*>(t.col_slot)[col8];
-    u32x2 om;
-    om[0] = of[0] & (((m[0] >> 7) & 0x01010101u) * 0xFFu);
-    om[1] = of[1] & (((m[1] >> 7) & 0x01010101u) * 0xFFu);
-    reinterpret_cast<u32x2*>(t.q_f8_main)[c] = om;
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    q.i8[i] = __builtin_amdgcn_perm(__builtin_amdgcn_perm(f2u(y[4 * i + 3]), f2u(y[4 * i + 2]), 0x0C0C0400u),
+                                    __builtin_amdgcn_perm(f2u(y[4 * i + 1]), f2u(y[4 * i]), 0x0C0C0400u), 0x05040100u);
+    q.f8[i] = static_cast<uint32_t>(wf[i]);
   }
+  return q;
+}
+
+// E4M3 codes of chunk c less those of the columns that are split off: bit 7 of a column's slot byte set = keep the code
+MOFQ_DEV u32x2 without_side(const PrepTensor& t, int64_t c, u32x2 f8) {
+  const uint32_t col8 = static_cast<uint32_t>(c) % static_cast<uint32_t>(t.cpr);   // fewer than 2^31 chunks (checked by the host)
+  const u32x2 m = reinterpret_cast<const u32x2*>(t.col_slot)[col8];
+  u32x2 o;
+  o[0] = f8[0] & (((m[0] >> 7) & 0x01010101u) * 0xFFu);
+  o[1] = f8[1] & (((m[1] >> 7) & 0x01010101u) * 0xFFu);
+  return o;
+}
+template <bool EXACT> MOFQ_DEV void store_chunk(const PrepTensor& t, int64_t c, const QuantChunk& q) {
+  reinterpret_cast<u32x2*>(t.q_i8)[c] = q.i8;
+  reinterpret_cast<u32x2*>(t.q_f8)[c] = q.f8;
+  if constexpr (EXACT) reinterpret_cast<u32x4*>(t.q_g)[c] = q.g;
+  else if (t.q_f8_main) reinterpret_cast<u32x2*>(t.q_f8_main)[c] = without_side(t, c, q.f8);   // uniform: an activation
+}
+// Chunks c and c + 1, c even: 16 bytes of codes each
+MOFQ_DEV void store_pair(const PrepTensor& t, int64_t c, const QuantChunk& a, const QuantChunk& b) {
+  auto both = [](u32x2 p, u32x2 q) { return u32x4{p[0], p[1], q[0], q[1]}; };
+  reinterpret_cast<u32x4*>(t.q_i8)[c / 2] = both(a.i8, b.i8);
+  reinterpret_cast<u32x4*>(t.q_f8)[c / 2] = both(a.f8, b.f8);
+  if (t.q_f8_main) reinterpret_cast<u32x4*>(t.q_f8_main)[c / 2] = both(without_side(t, c, a.f8), without_side(t, c + 1, b.f8));
 }
 
 // ---- column split for the fp8-unit product ------------------------------------------------
@@ -278,7 +300,7 @@ MOFQ_DEV void pick_columns(const PrepTensor& t) {
 }
 
 // First pass: largest magnitudes, a workgroup to a segment (a share of 2500 workgroups to a tensor, 1.2 rounds of resident ones, 95 us
-// for the 405 MB of a 7B block's weights, ZZ us so).  The tensors and their segments in descending order: the quantize pass begins
+// for the 405 MB of a 7B block's weights, 84 us so).  The tensors and their segments in descending order: the quantize pass begins
 // with what was read last, which the 256 MB cache still holds.  The activations of a column split, a workgroup each, come first: their largest magnitude
 // is that of the column maxima.  Picking their columns beside the weights' largest magnitudes instead of before them takes a launch
 // of 15 us out of a 7B block's step.
@@ -340,7 +362,7 @@ MOFQ_DEV void side_operand(const PrepTensor& t, int b, int nb, float scale) {
   }
 }
 
-// SIDE: with the side operands' workgroups behind the others.
+// SIDE: the fp8-unit product's inputs, with the side operands' workgroups behind the others; else the exact product's.
 template <bool SIDE>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(5))) void wa_quant_kernel(const PrepArgs a) {
   __shared__ float s_tmp[kThreads / 64];
@@ -374,21 +396,23 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(5))) v
     const int64_t lo = static_cast<int64_t>(seg) * t.seg_chunks;
     const int64_t hi = (lo + t.seg_chunks < t.n_chunks) ? lo + t.seg_chunks : t.n_chunks;
     double accA = 0.0, accB = 0.0;
-    int64_t c = lo + tid;
-    // dense input (uniform): several loads in flight; rows apart: one chunk at a time
-    for (; dense && c + (kQuantInFlight - 1) * kThreads < hi; c += kQuantInFlight * kThreads) {
-      u32x4 raw[kQuantInFlight];
-#pragma unroll
-      for (int u = 0; u < kQuantInFlight; ++u) raw[u] = *reinterpret_cast<const u32x4*>(t.data + (c + u * kThreads) * 8);
-#pragma unroll
-      for (int u = 0; u < kQuantInFlight; ++u) {
-        quant_chunk(t, c + u * kThreads, raw[u], iA, iB, sAd, sBd, accA, accB);
-        __builtin_amdgcn_sched_barrier(0);   // one chunk at a time: keeps the register count low
-      }
+    // Dense input (uniform): two chunks in flight; where only codes leave, neighbouring ones, in 16-byte pieces (with grid values,
+    // whose two pieces would lie apart, 4096 wide, 200 tokens 817 -> 845 us).  Rows apart: one chunk at a time.
+    int64_t c = SIDE && dense ? lo + 2 * tid : lo + tid;
+    constexpr int64_t other = SIDE ? 1 : kThreads;   // the second chunk
+    for (; dense && c + other < hi; c += 2 * kThreads) {
+      const u32x4 raw0 = *reinterpret_cast<const u32x4*>(t.data + c * 8), raw1 = *reinterpret_cast<const u32x4*>(t.data + (c + other) * 8);
+      const QuantChunk q0 = quant_chunk<!SIDE>(raw0, iA, iB, sAd, sBd, accA, accB);
+      if constexpr (!SIDE) store_chunk<true>(t, c, q0);
+      __builtin_amdgcn_sched_barrier(0);   // one chunk at a time: keeps the register count low
+      const QuantChunk q1 = quant_chunk<!SIDE>(raw1, iA, iB, sAd, sBd, accA, accB);
+      if constexpr (SIDE) store_pair(t, c, q0, q1);
+      else store_chunk<true>(t, c + other, q1);
     }
-    for (; c < hi; c += kThreads) {
+    // what is left of a lane's chunks, or all of them
+    for (; c < hi; c += SIDE && dense ? 2 * kThreads : kThreads) {
       const u32x4 raw = *reinterpret_cast<const u32x4*>(chunk_src(t, c));
-      quant_chunk(t, c, raw, iA, iB, sAd, sBd, accA, accB);
+      store_chunk<!SIDE>(t, c, quant_chunk<!SIDE>(raw, iA, iB, sAd, sBd, accA, accB));
     }
     accA = wave_sum(accA);
     accB = wave_sum(accB);
@@ -409,7 +433,7 @@ bool fill(const WaPrepTensor& p, PrepTensor* t) {
   t->n_chunks = p.rows * t->cpr;
   t->ld = p.ld;
   t->n_seg = wa_prep_segments(p.rows, p.cols);
-  t->seg_chunks = static_cast<int32_t>((t->n_chunks + t->n_seg - 1) / t->n_seg);
+  t->seg_chunks = static_cast<int32_t>((t->n_chunks + t->n_seg - 1) / t->n_seg + 1) / 2 * 2;   // even; the last segments may be empty
   t->ratio = p.ratio;
   t->absmax_part = p.absmax_part;
   t->sse_part = p.sse_part;
@@ -455,12 +479,13 @@ int launch_wa_prep(const WaPrepTensor* p, int n, hipStream_t st) {
     ++a.n;
   }
   if (a.n < 1) return MOFQ_OK;
-  // One workgroup per segment while the launch stays within 16 workgroups per compute unit's
-  // worth (4096); beyond that every tensor gets its share and workgroups take several segments.
-  constexpr int64_t kMaxBlocks = 4096;
+  // One workgroup per segment, but for up to twice as many segments as 16 workgroups per compute unit a share of those: short
+  // segments hardly pay for the fold before them.  (Shares for any number: a block of 4096, 200 tokens, exact 824 -> 801 us without,
+  // 3008, 400 tokens 620 -> 608; 1024, 1000 tokens, fp8 unit 163 -> 166.)
+  constexpr int64_t kShares = 4096;
   for (int k = 0; k < a.n; ++k) {
     int64_t nb = a.t[k].n_seg;
-    if (total_seg > kMaxBlocks) nb = std::max<int64_t>(1, nb * kMaxBlocks / total_seg);
+    if (total_seg > kShares && total_seg <= 2 * kShares) nb = std::max<int64_t>(1, nb * kShares / total_seg);
     a.first_block[k + 1] = a.first_block[k] + static_cast<int32_t>(nb);
   }
   const int blocks = a.first_block[a.n];
