@@ -112,7 +112,21 @@ MOFQ_DEV uint32_t wave_excl_scan_u32(uint32_t v, uint32_t& total) {
   total = static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(inc), 63));
   return inc - v;
 }
-// the same for doubles: each step moves the two halves of the running sum separately
+// the same for 64-bit integers: each step moves the two halves of the running sum separately
+template <int CTRL, int ROW_MASK> MOFQ_DEV uint64_t dpp_add_u64(uint64_t x) {
+  const uint32_t lo = static_cast<uint32_t>(__builtin_amdgcn_update_dpp(0, static_cast<int>(static_cast<uint32_t>(x)), CTRL, ROW_MASK, 0xf, false));
+  const uint32_t hi = static_cast<uint32_t>(__builtin_amdgcn_update_dpp(0, static_cast<int>(static_cast<uint32_t>(x >> 32)), CTRL, ROW_MASK, 0xf, false));
+  return x + ((static_cast<uint64_t>(hi) << 32) | lo);
+}
+MOFQ_DEV uint64_t wave_incl_scan_u64(uint64_t v) {
+  v = dpp_add_u64<0x111, 0xf>(v);   // row_shr:1
+  v = dpp_add_u64<0x112, 0xf>(v);   // row_shr:2
+  v = dpp_add_u64<0x114, 0xf>(v);   // row_shr:4
+  v = dpp_add_u64<0x118, 0xf>(v);   // row_shr:8
+  v = dpp_add_u64<0x142, 0xa>(v);   // row_bcast:15 into rows 1 and 3
+  return dpp_add_u64<0x143, 0xc>(v);   // row_bcast:31 into rows 2 and 3
+}
+// and for doubles
 template <int CTRL, int ROW_MASK> MOFQ_DEV double dpp_add_f64(double x) {
   const uint64_t u = __builtin_bit_cast(uint64_t, x);
   const uint32_t lo = static_cast<uint32_t>(__builtin_amdgcn_update_dpp(0, static_cast<int>(static_cast<uint32_t>(u)), CTRL, ROW_MASK, 0xf, false));
@@ -326,7 +340,7 @@ MOFQ_DEV void count_noted(uint32_t mask, const uint16_t* src, uint32_t chunk0, i
 template <int NF, int NW> struct RowSearch {
   float scale[NF][MOFQ_MAX_CLIP];
   double fast[NF][MOFQ_MAX_CLIP];       // filtered errors; NaN: has to be scored exactly
-  double thr[NF], p2[NW], best[NF], tally;
+  double thr[NF], p2[NW], p2b[NW], best[NF], tally;
   float best_scale[NF];
   int direct[NF];                       // the winning candidate where no element-wise pass is needed, else -1
   int nlist;
@@ -405,7 +419,42 @@ MOFQ_DEV void finish_row(RowSearch<(FB >= 0 ? 2 : 1), THREADS / 64>& sh, double*
 
   // exact fp64 re-score of the shortlist, element by element
   uint32_t carry = 0;
-  for (int e = 0; e < n_list; ++e) {
+  // An 8-bit search nearly always has its two winners here: both formats from one read of the row
+  const bool both = Codec<FA>::BITS == 8 && NF == 2 && n_list == 2 && sh.list[0] / MOFQ_MAX_CLIP != sh.list[1] / MOFQ_MAX_CLIP;   // uniform
+  if (both) {
+    const int first = sh.list[0] / MOFQ_MAX_CLIP;   // place of format 0 in the list
+    const float s0 = sh.scale[0][sh.list[first] % MOFQ_MAX_CLIP], s1 = sh.scale[NF - 1][sh.list[1 - first] % MOFQ_MAX_CLIP];
+    const float i0 = 1.0f / s0, i1 = 1.0f / s1;
+    const double d0 = static_cast<double>(s0), d1 = static_cast<double>(s1);
+    double acc0 = 0.0, acc1 = 0.0;
+#pragma unroll
+    for (int j = 0; j < CH; ++j) {
+      const int c = (j * THREADS + tid) * 8;
+      Raw8<In> raw;
+      raw.clear();                   // padding is zero and scores zero
+      if (c < n) raw.load(src, 0, static_cast<uint32_t>(c));
+      float v[8];
+      raw.widen(v);
+#pragma unroll
+      for (int i = 0; i < 8; i += 2) {
+        score2_f64<FA>(acc0, v[i], v[i + 1], i0, d0, carry);
+        score2_f64<FBX>(acc1, v[i], v[i + 1], i1, d1, carry);
+      }
+    }
+    acc0 = wave_sum(acc0);
+    acc1 = wave_sum(acc1);
+    if (lane == 0) { sh.p2[wave] = acc0; sh.p2b[wave] = acc1; }
+    __syncthreads();
+    if (tid < 2) {
+      const double* const p = tid == first ? sh.p2 : sh.p2b;
+      double t = p[0];
+#pragma unroll
+      for (int w = 1; w < NW; ++w) t += p[w];
+      s_val[tid] = t;
+    }
+    __syncthreads();
+  }
+  for (int e = both ? n_list : 0; e < n_list; ++e) {
     const int fk = sh.list[e];
     const int f = __builtin_amdgcn_readfirstlane(fk / MOFQ_MAX_CLIP);
     const int k = __builtin_amdgcn_readfirstlane(fk % MOFQ_MAX_CLIP);

@@ -15,7 +15,8 @@
 // The prefixes lie over the counters they are formed from (a thread holds its share in registers meanwhile), so that
 // six workgroups of the 8-bit search fit a compute unit instead of five.
 // Measured, layer selection: INT8 against E4M3, 3001 x 5000, 50 ratios 277 -> 69.8 -> 66.0 (prefixes over
-// the counters) -> 62.0 (patterns_below, weights of the counts by dot products: 13 -> 8 instructions a look-up) -> 60.5 us (RowCounters); 4096 x 11008, 100 ratios 1294 -> 141 us; INT4 against E2M1, 1237 x 5000, 100 ratios: 28.2 -> 25.6 -> 23.4 us.
+// the counters) -> 62.0 (patterns_below, weights of the counts by dot products: 13 -> 8 instructions a look-up) -> 60.5 (RowCounters) ->
+// 58 us (both winners summed in one pass, a thread's own prefixes in registers, scans by data-parallel-primitive moves); 4096 x 11008, 100 ratios 1294 -> 141 us; INT4 against E2M1, 1237 x 5000, 100 ratios: 28.2 -> 25.6 -> 23.4 us.
 //
 // fp16 rows (8-bit formats) have eight times the patterns, up to 20300 below the largest for E4M3: a prefix per group of
 // 8, packed alike, and a look-up adds the group's first counters, 36 instructions.  Counters and prefixes take 61 KB, so
@@ -123,7 +124,7 @@ MOFQ_DEV void packed_prefixes(const uint32_t* counters, uint64_t* P, int lo, int
     between();
     acc += static_cast<uint64_t>((m + 1) << shift) * (c2[j] >> 16) + (static_cast<uint64_t>(c2[j] >> 16) << 48);
   };
-  constexpr bool KEEP = PWMAX <= 2;   // the thread's own prefixes in registers, else formed again behind the scan
+  constexpr bool KEEP = PWMAX <= 6;   // the thread's own prefixes in registers, else formed again behind the scan
   uint64_t own[KEEP ? 2 * PWMAX : 1];
   uint64_t acc = 0;
 #pragma unroll
@@ -136,12 +137,7 @@ MOFQ_DEV void packed_prefixes(const uint32_t* counters, uint64_t* P, int lo, int
     }
   }
   // exclusive scan over the threads (sums of the two fields do not meet: the sum stays below 2^48)
-  uint64_t inc = acc;
-#pragma unroll
-  for (int d = 1; d < 64; d <<= 1) {
-    const uint64_t o = __shfl_up(inc, d, 64);
-    if (lane >= d) inc += o;
-  }
+  const uint64_t inc = wave_incl_scan_u64(acc);
   uint64_t at = inc - acc;
   if constexpr (NW > 1) {
     if (lane == 63) s_wave[wave] = inc;
@@ -188,12 +184,7 @@ MOFQ_DEV void group_prefixes(const uint32_t* counters, uint64_t* P, int lo, int 
     if (i < gp && g < ng) v[i] = packed_group(reinterpret_cast<const u32x4*>(counters)[g], lo + 8 * g, e_lo);
     acc += v[i];
   }
-  uint64_t inc = acc;
-#pragma unroll
-  for (int d = 1; d < 64; d <<= 1) {
-    const uint64_t o = __shfl_up(inc, d, 64);
-    if (lane >= d) inc += o;
-  }
+  const uint64_t inc = wave_incl_scan_u64(acc);
   uint64_t at = inc - acc;
   if constexpr (NW > 1) {
     if (lane == 63) s_wave[wave] = inc;
@@ -350,6 +341,7 @@ void sweep_pattern_kernel(const SortedArgs a) {
       }
     // (the short ones of the 4-bit formats in code of their own: 1237 x 5000 took 0.6 us more in the other's)
     if (nbin <= 4 * kThreads) packed_prefixes<kNW, 2>(counters, P, lo, nbin, s_wave);
+    else if (nbin <= 12 * kThreads) packed_prefixes<kNW, 6>(counters, P, lo, nbin, s_wave);
     else packed_prefixes<kNW, kMaxBins / 2 / kThreads>(counters, P, lo, nbin, s_wave);
   }
   const uint64_t total = P[n_rec];
