@@ -780,34 +780,19 @@ int select_layers_wa(int n_layers, const mofq_tensor_t* w, const mofq_tensor_t* 
         f[j].t[0].sse_part = l[j].x.sse_part; f[j].t[0].scale = l[j].x.scale;
         f[j].t[0].out_scales = x_out[i].scales; f[j].t[0].out_clip = x_out[i].clip_idx;
         f[j].t[0].out_unit_err = x_out[i].unit_err;
+        f[j].codes[0] = {{l[j].x.i8, l[j].x.f8}, static_cast<uint8_t*>(x_out[i].codes), x[i].rows * x[i].cols};
       }
       f[j].t[1].n_segments = wa_prep_segments(w[i].rows, w[i].cols);
       f[j].t[1].sse_part = l[j].w.sse_part; f[j].t[1].scale = l[j].w.scale;
       f[j].t[1].out_scales = w_out[i].scales; f[j].t[1].out_clip = w_out[i].clip_idx;
       f[j].t[1].out_unit_err = w_out[i].unit_err;
+      uint8_t* const to = static_cast<uint8_t*>(w_out[i].codes);   // the E4M3 codes are there already
+      f[j].codes[1] = {{l[j].w.i8, to}, to, w[i].rows * w[i].cols};
     }
     return launch_wa_finish(f, n, st);
   };
-  auto codes = [&](int i0, int n, const WaLayerWs* l, hipStream_t s) {
-    WaCopyParams p[kWaGroup] = {};
-    for (int j = 0; j < n; ++j) {
-      const int i = i0 + j;
-      p[j].result = &results[i];
-      p[j].n_cand = n_cand;
-      for (int c = 0; c < n_cand; ++c) p[j].fmt_slot[c] = fmt_slot[c];
-      if (x_out) {
-        p[j].t[0].src[0] = l[j].x.i8; p[j].t[0].src[1] = l[j].x.f8;
-        p[j].t[0].dst = static_cast<uint8_t*>(x_out[i].codes);
-        p[j].t[0].bytes = x[i].rows * x[i].cols;
-      }
-      p[j].t[1].src[0] = l[j].w.i8; p[j].t[1].src[1] = static_cast<const uint8_t*>(w_out[i].codes);
-      p[j].t[1].dst = static_cast<uint8_t*>(w_out[i].codes);
-      p[j].t[1].bytes = w[i].rows * w[i].cols;
-    }
-    return launch_wa_copy(p, n, s);
-  };
 
-  // Group by group on the caller's stream: the quantize passes, the matrix kernels, the selects,
+  // Group by group on the caller's stream: the quantize passes, the matrix kernels, the selects with
   // the code copies.  (Running the passes of the next group on a second stream beside the matrix
   // kernels was measured and lost: two waves of 216-240 registers on every SIMD leave no room
   // for a second kernel's waves, so the side work only delays the matrix kernels.)
@@ -817,7 +802,6 @@ int select_layers_wa(int n_layers, const mofq_tensor_t* w, const mofq_tensor_t* 
     carve_wa_group(ws, i0, n, w, x, !fp8_unit, cur);
     if ((rc = prep(i0, n, cur, st))) return rc;
     if ((rc = products(i0, n, cur))) return rc;
-    if ((rc = codes(i0, n, cur, st))) return rc;
   }
   return MOFQ_OK;
 }

@@ -151,9 +151,12 @@ __global__ __launch_bounds__(kThreads) void decide_kernel(const Decision d) {
   decide(d, true, s_sum);
 }
 
-// The weight-activation path after the matrix kernels of a group of layers, one workgroup per
-// layer: select from the per-tile partials, then the one-unit outputs of the chosen format
-// for X and W.
+// The weight-activation path after the matrix kernels of a group of layers: select from the per-tile partials, the one-unit
+// outputs of the chosen format for X and W, and a copy of its codes (16-byte pieces, grid-stride, four in flight per lane).
+// Workgroups are dealt to the tensors in proportion to their sizes; each takes its layer's select anew, as the emission does, and
+// the first of a layer writes what is not codes.  (A launch of the selects before the copies cost a single layer 5 us: 777 x 3000 x
+// 5056 119.8 us, 116.9 so.)
+constexpr int kCopyTensors = 2 * kWaGroup;
 struct WaFinishLayer {
   Decision d;
   int32_t fmt_slot[MOFQ_MAX_CANDIDATES];
@@ -161,62 +164,55 @@ struct WaFinishLayer {
 };
 struct WaFinishArgs {
   WaFinishLayer p[kWaGroup];
-};
-static_assert(sizeof(WaFinishArgs) <= 4096, "kernel arguments");
-__global__ __launch_bounds__(kThreads) void wa_finish_kernel(const WaFinishArgs args) {
-  __shared__ double s_sum[kSums];
-  __shared__ double s_red[kNW];
-  const WaFinishLayer& l = args.p[blockIdx.x];
-  const int f = l.fmt_slot[decide(l.d, true, s_sum)];
-#pragma unroll
-  for (int which = 0; which < 2; ++which) {
-    const WaFinishTensor& t = l.t[which];
-    if (t.n_segments < 1) continue;   // uniform
-    double e = 0.0;
-    if (t.out_unit_err) {
-      for (int i = threadIdx.x; i < t.n_segments; i += kThreads) e += t.sse_part[2 * i + f];
-      e = wave_sum(e);
-      __syncthreads();
-      if ((threadIdx.x & 63) == 0) s_red[threadIdx.x >> 6] = e;
-      __syncthreads();
-      e = (s_red[0] + s_red[1]) + (s_red[2] + s_red[3]);
-    }
-    if (threadIdx.x == 0) {
-      if (t.out_unit_err) *t.out_unit_err = e;
-      if (t.out_scales) *static_cast<float*>(t.out_scales) = t.scale[f];
-      if (t.out_clip) *t.out_clip = 0;
-    }
-  }
-}
-
-// Copy of the chosen format's codes (16-byte pieces, grid-stride, four in flight per lane) for
-// the tensors of a group of layers.  Workgroups are dealt to the tensors in proportion to
-// their sizes.
-constexpr int kCopyTensors = 2 * kWaGroup;
-struct WaCopyArgs {
-  const mofq_result_t* result[kCopyTensors];
-  int32_t n_cand[kCopyTensors];
-  int32_t fmt_slot[kCopyTensors][MOFQ_MAX_CANDIDATES];
-  WaCopyTensor t[kCopyTensors];
+  struct {
+    const uint8_t* src[2];
+    uint8_t* dst;
+    int64_t bytes;
+    int32_t layer, writes;   // writes: its first workgroup leaves the layer's other outputs
+  } t[kCopyTensors];
   int32_t first_block[kCopyTensors + 1];
   int32_t n;
 };
-__global__ __launch_bounds__(256) void wa_copy_kernel(const WaCopyArgs a) {
+static_assert(sizeof(WaFinishArgs) <= 4096, "kernel arguments");
+__global__ __launch_bounds__(kThreads) void wa_finish_kernel(const WaFinishArgs a) {
+  __shared__ double s_sum[kSums];
+  __shared__ double s_red[kNW];
   int k = 0;
   while (k + 1 < a.n && static_cast<int>(blockIdx.x) >= a.first_block[k + 1]) ++k;   // uniform
   const int b = static_cast<int>(blockIdx.x) - a.first_block[k];
   const int nb = a.first_block[k + 1] - a.first_block[k];
-  int best = a.result[k]->best;
-  if (best < 0 || best >= a.n_cand[k]) best = 0;
-  const int f = a.fmt_slot[k][__builtin_amdgcn_readfirstlane(best)];
-  const WaCopyTensor& t = a.t[k];
-  const uint8_t* src = f ? t.src[1] : t.src[0];
-  if (src == t.dst) return;   // uniform: the codes are in place
+  const auto& copy = a.t[k];
+  const WaFinishLayer& l = a.p[copy.layer];
+  const bool write = b == 0 && copy.writes != 0;   // uniform
+  const int f = l.fmt_slot[decide(l.d, write, s_sum)];
+  if (write) {
+#pragma unroll
+    for (int which = 0; which < 2; ++which) {
+      const WaFinishTensor& t = l.t[which];
+      if (t.n_segments < 1) continue;   // uniform
+      double e = 0.0;
+      if (t.out_unit_err) {
+        for (int i = threadIdx.x; i < t.n_segments; i += kThreads) e += t.sse_part[2 * i + f];
+        e = wave_sum(e);
+        __syncthreads();
+        if ((threadIdx.x & 63) == 0) s_red[threadIdx.x >> 6] = e;
+        __syncthreads();
+        e = (s_red[0] + s_red[1]) + (s_red[2] + s_red[3]);
+      }
+      if (threadIdx.x == 0) {
+        if (t.out_unit_err) *t.out_unit_err = e;
+        if (t.out_scales) *static_cast<float*>(t.out_scales) = t.scale[f];
+        if (t.out_clip) *t.out_clip = 0;
+      }
+    }
+  }
+  const uint8_t* const src = f ? copy.src[1] : copy.src[0];
+  if (src == copy.dst) return;   // uniform: the codes are in place
   const u32x4* s4 = reinterpret_cast<const u32x4*>(src);
-  u32x4* d4 = reinterpret_cast<u32x4*>(t.dst);
-  const int64_t n = t.bytes / 16;
-  const int64_t stride = static_cast<int64_t>(nb) * 256;
-  int64_t i = static_cast<int64_t>(b) * 256 + threadIdx.x;
+  u32x4* d4 = reinterpret_cast<u32x4*>(copy.dst);
+  const int64_t n = copy.bytes / 16;
+  const int64_t stride = static_cast<int64_t>(nb) * kThreads;
+  int64_t i = static_cast<int64_t>(b) * kThreads + threadIdx.x;
   for (; i + 3 * stride < n; i += 4 * stride) {
     const u32x4 v0 = s4[i], v1 = s4[i + stride], v2 = s4[i + 2 * stride], v3 = s4[i + 3 * stride];
     d4[i] = v0; d4[i + stride] = v1; d4[i + 2 * stride] = v2; d4[i + 3 * stride] = v3;
@@ -557,9 +553,11 @@ int launch_partial(const DecideParams* const* p, int n, hipStream_t st) {
 int launch_wa_finish(const WaFinishParams* p, int n, hipStream_t st) {
   if (!p || n < 1 || n > kWaGroup) return MOFQ_ERR_INVALID_ARG;
   WaFinishArgs a{};
+  int64_t want[kCopyTensors];
+  int64_t total = 0;
   for (int i = 0; i < n; ++i) {
     const DecideParams& d = p[i].d;
-    if (d.units < 1 || d.n_cand < 1 || d.n_cand > MOFQ_MAX_CANDIDATES || !d.result) return MOFQ_ERR_INVALID_ARG;
+    if (d.units < 1 || d.n_cand < 1 || d.n_cand > MOFQ_MAX_CANDIDATES || !d.result || !p[i].codes[1].dst) return MOFQ_ERR_INVALID_ARG;
     for (int c = 0; c < d.n_cand; ++c) {
       if (!d.err[c] || p[i].fmt_slot[c] < 0 || p[i].fmt_slot[c] > 1) return MOFQ_ERR_INVALID_ARG;
       a.p[i].fmt_slot[c] = p[i].fmt_slot[c];
@@ -567,38 +565,22 @@ int launch_wa_finish(const WaFinishParams* p, int n, hipStream_t st) {
     a.p[i].d = decision(d, false);
     a.p[i].t[0] = p[i].t[0];
     a.p[i].t[1] = p[i].t[1];
-  }
-  hipLaunchKernelGGL(wa_finish_kernel, dim3(static_cast<unsigned>(n)), dim3(kThreads), 0, st, a);
-  return hip_status(hipGetLastError());
-}
-
-int launch_wa_copy(const WaCopyParams* p, int n, hipStream_t st) {
-  if (!p || n < 1 || n > kWaGroup) return MOFQ_ERR_INVALID_ARG;
-  WaCopyArgs a{};
-  int64_t want[kCopyTensors];
-  int64_t total = 0;
-  for (int i = 0; i < n; ++i) {
-    if (!p[i].result || p[i].n_cand < 1 || p[i].n_cand > MOFQ_MAX_CANDIDATES) return MOFQ_ERR_INVALID_ARG;
     for (int which = 0; which < 2; ++which) {
-      const WaCopyTensor& t = p[i].t[which];
+      const WaCopyTensor& t = p[i].codes[which];
       if (!t.dst) continue;
       if (t.bytes < 16 || t.bytes % 16 != 0 || !t.src[0] || !t.src[1]) return MOFQ_ERR_INVALID_ARG;
       const int k = a.n++;
-      a.result[k] = p[i].result;
-      a.n_cand[k] = p[i].n_cand;
-      for (int c = 0; c < MOFQ_MAX_CANDIDATES; ++c) a.fmt_slot[k][c] = p[i].fmt_slot[c];
-      a.t[k] = t;
-      want[k] = (t.bytes / 16 + 256 * 4 - 1) / (256 * 4);
+      a.t[k] = {{t.src[0], t.src[1]}, t.dst, t.bytes, i, which};
+      want[k] = (t.bytes / 16 + kThreads * 4 - 1) / (kThreads * 4);
       total += want[k];
     }
   }
-  if (a.n < 1) return MOFQ_OK;
   const int64_t cap = 256 * 8;
   for (int k = 0; k < a.n; ++k) {
     const int64_t nb = total <= cap ? want[k] : std::max<int64_t>(1, want[k] * cap / total);
     a.first_block[k + 1] = a.first_block[k] + static_cast<int32_t>(nb);
   }
-  hipLaunchKernelGGL(wa_copy_kernel, dim3(static_cast<unsigned>(a.first_block[a.n])), dim3(256), 0, st, a);
+  hipLaunchKernelGGL(wa_finish_kernel, dim3(static_cast<unsigned>(a.first_block[a.n])), dim3(kThreads), 0, st, a);
   return hip_status(hipGetLastError());
 }
 

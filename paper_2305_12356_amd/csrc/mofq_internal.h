@@ -237,9 +237,10 @@ struct WaPrepTensor {
 int wa_prep_segments(int64_t rows, int64_t cols);
 int launch_wa_prep(const WaPrepTensor* t, int n, hipStream_t stream);
 
-// After the matrix kernels of a group: per layer (one workgroup each) the fixed-order sums of
-// its per-tile partials, Algorithm 1's select, the result record, and the one-unit outputs
-// (scale, clip index 0, tensor error) of the chosen format for both tensors.
+// After the matrix kernels of a group, one launch: per layer the fixed-order sums of its per-tile partials, Algorithm 1's
+// select, the result record, the one-unit outputs (scale, clip index 0, tensor error) of the chosen format for both tensors, and
+// its codes into the caller's buffers: a copy of the quantized operand the matrix kernel used (no second quantization).
+// Where the chosen format's codes already sit in the destination (src == dst) nothing is moved.
 struct WaFinishTensor {
   int32_t n_segments;        // 0: no outputs for this tensor
   const double* sse_part;    // as written by launch_wa_prep
@@ -248,28 +249,18 @@ struct WaFinishTensor {
   int32_t* out_clip;         // may be nullptr
   double* out_unit_err;      // may be nullptr
 };
+struct WaCopyTensor {
+  const uint8_t* src[2];     // INT8 codes, E4M3 codes
+  uint8_t* dst;              // nullptr: nothing to do (X only)
+  int64_t bytes;             // multiple of 16
+};
 struct WaFinishParams {
   DecideParams d;                          // err[c] = the tile partials of candidate c's format
   int32_t fmt_slot[MOFQ_MAX_CANDIDATES];   // per candidate: 0 INT8, 1 E4M3
   WaFinishTensor t[2];                     // X, W
+  WaCopyTensor codes[2];
 };
 int launch_wa_finish(const WaFinishParams* p, int n, hipStream_t stream);
-
-// Codes of the chosen format into the caller's buffers, for the layers of a group in one
-// launch: a copy of the quantized operand the matrix kernel used (no second quantization).
-// Where the chosen format's codes already sit in the destination (src == dst) nothing is moved.
-struct WaCopyTensor {
-  const uint8_t* src[2];     // INT8 codes, E4M3 codes
-  uint8_t* dst;              // nullptr: nothing to do
-  int64_t bytes;             // multiple of 16
-};
-struct WaCopyParams {
-  const mofq_result_t* result;
-  int32_t n_cand;
-  int32_t fmt_slot[MOFQ_MAX_CANDIDATES];
-  WaCopyTensor t[2];
-};
-int launch_wa_copy(const WaCopyParams* p, int n, hipStream_t stream);
 
 inline int hip_status(hipError_t e) { return e == hipSuccess ? MOFQ_OK : MOFQ_ERR_HIP; }
 
