@@ -598,7 +598,6 @@ bool wa_fused(const int32_t* cand, int n_cand, const mofq_scale_cfg_t* w_cfg) {
 struct WaFusedTensorWs {
   uint8_t* i8;
   uint8_t* f8;
-  uint8_t* g;
   float* absmax_part;
   double* sse_part;
   float* scale;
@@ -634,6 +633,18 @@ int wa_group_length(int n_layers, const mofq_tensor_t* w, int i0) {
   return n;
 }
 
+// Whether the code buffers of a group's weights share no byte: then the E4M3 codes are the product's operand where they are
+// wanted in the end.  (A caller who is after the choices alone may hand over one buffer for all layers.)
+bool codes_apart(const mofq_tensor_t* w, const mofq_qout_t* out, int n) {
+  for (int i = 0; i < n; ++i)
+    for (int j = 0; j < i; ++j) {
+      const char* const a = static_cast<const char*>(out[i].codes);
+      const char* const b = static_cast<const char*>(out[j].codes);
+      if (a < b + w[j].rows * w[j].cols && b < a + w[i].rows * w[i].cols) return false;
+    }
+  return true;
+}
+
 bool wa_same_x(const mofq_tensor_t* x, int i) {
   return x[i].data == x[i - 1].data && x[i].rows == x[i - 1].rows && x[i].cols == x[i - 1].cols &&
          x[i].ld == x[i - 1].ld;
@@ -655,8 +666,7 @@ size_t carve_wa_group(void* arena, int i0, int n, const mofq_tensor_t* w, const 
       }
       const size_t e = static_cast<size_t>(which ? w[i].rows * w[i].cols : x[i].rows * x[i].cols);
       t.i8 = c.take<uint8_t>(e);
-      t.f8 = which ? nullptr : c.take<uint8_t>(e);   // the weight's live in the caller's code buffer
-      t.g = exact ? c.take<uint8_t>(2 * e) : nullptr;
+      t.f8 = which && !exact ? nullptr : c.take<uint8_t>(e);   // the weight's mostly live in the caller's code buffer instead (codes_apart)
       t.absmax_part = c.take<float>(kTensorBlocks);
       t.sse_part = c.take<double>(2 * kTensorBlocks);
       t.scale = c.take<float>(2);
@@ -722,7 +732,7 @@ int select_layers_wa(int n_layers, const mofq_tensor_t* w, const mofq_tensor_t* 
         px.data = x[i].data; px.rows = x[i].rows; px.cols = x[i].cols; px.ld = x[i].ld;
         px.ratio = 1.0f;   // activations: per tensor at the full range (Section 3.2)
         px.absmax_part = l[j].x.absmax_part; px.sse_part = l[j].x.sse_part;
-        px.q_i8 = l[j].x.i8; px.q_f8 = l[j].x.f8; px.q_g = l[j].x.g; px.scale = l[j].x.scale;
+        px.q_i8 = l[j].x.i8; px.q_f8 = l[j].x.f8; px.scale = l[j].x.scale;
         px.is_x = 1;
         px.colmax = l[j].x.colmax; px.col_slot = l[j].x.col_slot; px.side_cols = l[j].x.side_cols;
         px.q_f8_main = l[j].x.f8_main; px.side = l[j].x.side;
@@ -730,7 +740,7 @@ int select_layers_wa(int n_layers, const mofq_tensor_t* w, const mofq_tensor_t* 
       pw.data = w[i].data; pw.rows = w[i].rows; pw.cols = w[i].cols; pw.ld = w[i].ld;
       pw.ratio = w_cfg->clip_ratios[0];
       pw.absmax_part = l[j].w.absmax_part; pw.sse_part = l[j].w.sse_part;
-      pw.q_i8 = l[j].w.i8; pw.q_f8 = static_cast<uint8_t*>(w_out[i].codes); pw.q_g = l[j].w.g;
+      pw.q_i8 = l[j].w.i8; pw.q_f8 = l[j].w.f8;
       pw.scale = l[j].w.scale;
       // the weight's side operand follows its activation's pick of columns
       pw.is_x = 0;
@@ -748,11 +758,11 @@ int select_layers_wa(int n_layers, const mofq_tensor_t* w, const mofq_tensor_t* 
       g.q[0].x = l[j].x.i8; g.q[0].w = l[j].w.i8;
       g.q[0].sx = l[j].x.scale; g.q[0].sw = l[j].w.scale;
       g.q[0].part = l[j].part[0];
-      g.q[1].kind = fp8_unit ? WA_FP8 : WA_GRID_BF16;
-      g.q[1].x = fp8_unit ? l[j].x.f8_main : l[j].x.g;
+      g.q[1].kind = fp8_unit ? WA_FP8 : WA_GRID_FP8;
+      g.q[1].x = fp8_unit ? l[j].x.f8_main : l[j].x.f8;
       g.q[1].xs = fp8_unit ? l[j].x.side : nullptr;
       g.q[1].ws = fp8_unit ? l[j].w.side : nullptr;
-      g.q[1].w = fp8_unit ? static_cast<const uint8_t*>(w_out[i].codes) : l[j].w.g;
+      g.q[1].w = l[j].w.f8;
       g.q[1].sx = l[j].x.scale + 1; g.q[1].sw = l[j].w.scale + 1;
       g.q[1].part = l[j].part[1];
       g.x = x[i].data; g.ldx = x[i].ld;
@@ -786,8 +796,7 @@ int select_layers_wa(int n_layers, const mofq_tensor_t* w, const mofq_tensor_t* 
       f[j].t[1].sse_part = l[j].w.sse_part; f[j].t[1].scale = l[j].w.scale;
       f[j].t[1].out_scales = w_out[i].scales; f[j].t[1].out_clip = w_out[i].clip_idx;
       f[j].t[1].out_unit_err = w_out[i].unit_err;
-      uint8_t* const to = static_cast<uint8_t*>(w_out[i].codes);   // the E4M3 codes are there already
-      f[j].codes[1] = {{l[j].w.i8, to}, to, w[i].rows * w[i].cols};
+      f[j].codes[1] = {{l[j].w.i8, l[j].w.f8}, static_cast<uint8_t*>(w_out[i].codes), w[i].rows * w[i].cols};   // E4M3's may be there already
     }
     return launch_wa_finish(f, n, st);
   };
@@ -800,6 +809,8 @@ int select_layers_wa(int n_layers, const mofq_tensor_t* w, const mofq_tensor_t* 
   for (int i0 = 0, n = 0; i0 < n_layers; i0 += n) {
     n = wa_group_length(n_layers, w, i0);
     carve_wa_group(ws, i0, n, w, x, !fp8_unit, cur);
+    if (fp8_unit || codes_apart(&w[i0], &w_out[i0], n))
+      for (int j = 0; j < n; ++j) cur[j].w.f8 = static_cast<uint8_t*>(w_out[i0 + j].codes);
     if ((rc = prep(i0, n, cur, st))) return rc;
     if ((rc = products(i0, n, cur))) return rc;
   }

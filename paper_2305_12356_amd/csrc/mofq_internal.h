@@ -167,6 +167,7 @@ enum WaKind : int32_t {
   WA_GRID_BF16 = 1,   // grid values stored as bf16 (exact), bf16 matrix cores
   WA_INT8 = 2,        // int8 codes, int8 matrix cores
   WA_FP8 = 3,         // e4m3 codes, fp8 matrix cores
+  WA_GRID_FP8 = 4,    // e4m3 codes, widened to bf16 on the way to the bf16 matrix cores (exact)
 };
 struct WaProduct {
   int32_t kind;
@@ -224,7 +225,6 @@ struct WaPrepTensor {
   double* sse_part;          // [wa_prep_segments(rows, cols)][2]: INT8, E4M3
   uint8_t* q_i8;             // [rows][cols] int8 codes, dense
   uint8_t* q_f8;             // [rows][cols] e4m3 codes, dense
-  uint8_t* q_g;              // [rows][cols] e4m3 grid values as bf16, dense; or nullptr
   float* scale;              // [2]: INT8 scale, E4M3 scale
   // column split for the fp8-unit product (all null otherwise)
   int32_t is_x;              // activation: picks the columns; weight: uses its activation's pick

@@ -29,13 +29,19 @@
 //
 // Exactness: bf16 x bf16 products are exact in fp32 and are accumulated in fp32;
 // int8 products are accumulated exactly in int32 (|sum| <= 32768*127*127 < 2^31).
-// A quantized product is one of three kinds:
+// A quantized product is one of four kinds:
 //   WA_INT8      : int8 codes on the int8 matrix cores (exact);
 //   WA_GRID_BF16 : grid values stored as bf16 (exact for 4-bit and 8-bit grids) on the
-//                  bf16 matrix cores, products exact, fp32 accumulation -- the E4M3
-//                  product that meets the 1e-5 tolerance on the error sum, and the
-//                  4-bit products of the weight-only layer-output metric, where the
-//                  "quantized" input is the 16-bit input itself (scale 1);
+//                  bf16 matrix cores, products exact, fp32 accumulation -- the products
+//                  of the weight-only layer-output metric, where the "quantized" input is
+//                  the 16-bit input itself (scale 1), and of scales per channel;
+//   WA_GRID_FP8  : the same product from e4m3 codes, widened in registers: half the bytes
+//                  deposited, kept in LDS and read as fragments, and no bf16 copies of the
+//                  operands to write.  It meets the 1e-5 tolerance on the error sum, which
+//                  the fp8 matrix cores by themselves do not.  The three products of a layer, with their
+//                  inputs' passes, from the stored bf16 values and so: 2048 x 11008 x 4096
+//                  469 -> 436 us, 1024 x 4096 x 4096 117 -> 111, 64 x 4096 x 4096 53 -> 47;
+//                  a block of 4096 x 10624 at 2048 tokens 2099 -> 1923;
 //   WA_FP8       : e4m3 codes on the fp8 matrix cores (the low-bit matmul units the WA
 //                  case of Algorithm 1 targets).  Measured on the part with single
 //                  instructions: the 8 products of each group of 8 consecutive k are
@@ -61,6 +67,7 @@ namespace mofq {
 namespace {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef int i32x16 __attribute__((ext_vector_type(16)));
 typedef int i32x4 __attribute__((ext_vector_type(4)));
@@ -128,7 +135,7 @@ template <int N> MOFQ_DEV void wait_deposits_and_reads() {
   __builtin_amdgcn_s_waitcnt((N & 15) | (7 << 4) | (0 << 8) | ((N >> 4) << 14));
 }
 
-enum : int { K_REF = 100, K_GRID = WA_GRID_BF16, K_I8 = WA_INT8, K_F8 = WA_FP8 };   // K_REF: the 16-bit inputs themselves
+enum : int { K_REF = 100, K_GRID = WA_GRID_BF16, K_I8 = WA_INT8, K_F8 = WA_FP8, K_G8 = WA_GRID_FP8 };   // K_REF: the 16-bit inputs themselves
 
 template <int TM_, int TN_, int WM_, int WN_> struct Tile {
   static constexpr int TM = TM_, TN = TN_;                  // workgroup tile
@@ -306,7 +313,7 @@ __global__ __launch_bounds__(T::NW * 64) __attribute__((amdgpu_waves_per_eu(T::P
   // KIND selects element size and matrix instruction; acc is f32x16 or i32x16.
   auto product = [&](auto kind_c, auto& acc, const int stages, const bool half) {
     constexpr int KIND = decltype(kind_c)::value;
-    constexpr bool EIGHT = KIND == K_I8 || KIND == K_F8;
+    constexpr bool WIDENED = KIND == K_G8, EIGHT = KIND == K_I8 || KIND == K_F8 || WIDENED;
     constexpr int NG = (KIND == K_F8) ? CH / 4 : CH / 2;            // matrix groups per stage (TI*TJ instructions each)
     // Fragments of group gi of a stage: f[0 .. TI) = A tiles, f[TI ..) = B tiles.
     using frag_t = std::conditional_t<KIND == K_F8, i32x8, i32x4>;
@@ -324,33 +331,66 @@ __global__ __launch_bounds__(T::NW * 64) __attribute__((amdgpu_waves_per_eu(T::P
 #pragma unroll
       for (int j = 0; j < TJ; ++j) f[TI + j] = load_frag(st + row_b + j * 32 * ROW_B, gi);
     };
+    // E4M3 codes for the bf16 matrix cores (grid values have 4 significant bits: the same operands as if they had been stored as
+    // bf16).  A lane's 16 codes of a fragment are the operands of two instructions, 8 each, the same k of A and B.  They are
+    // widened (4 conversions to 8 codes) between the matrix instructions before: the second half of a group's during its first half,
+    // the next group's first half (of `next`) during its second.
+    bf16x8 wide[2][TI + TJ];
+    auto widen = [](const auto& v, int h) {
+      bf16x8 o;
+#pragma unroll
+      for (int d = 0; d < 2; ++d)
+#pragma unroll
+        for (int e = 0; e < 2; ++e) {
+          const bf16x2 p = e ? __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(v[2 * h + d], 1.0f, true) : __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(v[2 * h + d], 1.0f, false);
+          o[4 * d + 2 * e] = p[0];
+          o[4 * d + 2 * e + 1] = p[1];
+        }
+      return o;
+    };
     // The matrix instructions of one group, with the deposits [lo, hi) of the current stage
     // spread between them: a wave issues in order, so a burst of deposits (each occupies
     // the texture path for ~18 clocks, and all waves share it) would hold back the
     // matrix instructions behind it while the matrix pipe runs dry.
     // `then` (the next group's fragment reads) follows the first instruction: what that one waits for is its own
     // group's fragments alone.
-    auto run_group = [&](const frag_t (&f)[TI + TJ], int buf, int lo, int hi, auto then) {
+    auto run_group = [&](const frag_t (&f)[TI + TJ], const frag_t (&next)[TI + TJ], int buf, int lo, int hi, auto then) {
+      if constexpr (WIDENED) {
+        constexpr int PER = TI * TJ;
 #pragma unroll
-      for (int i = 0; i < TI; ++i)
+        for (int m = 0; m < 2 * PER; ++m) {
+          const int h = m / PER, i = m % PER / TJ, j = m % TJ, n = hi - lo;
+          __builtin_amdgcn_sched_barrier(0);
+          if (m == (PER > 1 ? 1 : 0)) then();
+          issue(buf, lo + m * n / (2 * PER), lo + (m + 1) * n / (2 * PER));
 #pragma unroll
-        for (int j = 0; j < TJ; ++j) {
-          {
-            const int m = i * TJ + j, n = hi - lo;
-            __builtin_amdgcn_sched_barrier(0);
-            if (m == (TI * TJ > 1 ? 1 : 0)) then();
-            issue(buf, lo + m * n / (TI * TJ), lo + (m + 1) * n / (TI * TJ));
-            __builtin_amdgcn_sched_barrier(0);
-          }
-          if constexpr (KIND == K_REF || KIND == K_GRID) {
-            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, f[i]), __builtin_bit_cast(bf16x8, f[TI + j]), acc[i][j], 0, 0, 0);
-          } else if constexpr (KIND == K_I8) {
-            acc[i][j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(f[i], f[TI + j], acc[i][j], 0, 0, 0);
-          } else {
-            // format selectors 0 = E4M3 for both operands; block scales 2^0 (exponent byte 127)
-            acc[i][j] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(f[i], f[TI + j], acc[i][j], 0, 0, 0, 127, 0, 127);
-          }
+          for (int q = 0; q < TI + TJ; ++q)
+            if (q >= (m % PER) * (TI + TJ) / PER && q < (m % PER + 1) * (TI + TJ) / PER) wide[1 - h][q] = h == 0 ? widen(f[q], 1) : widen(next[q], 0);
+          __builtin_amdgcn_sched_barrier(0);
+          acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wide[h][i], wide[h][TI + j], acc[i][j], 0, 0, 0);
         }
+      } else {
+#pragma unroll
+        for (int i = 0; i < TI; ++i)
+#pragma unroll
+          for (int j = 0; j < TJ; ++j) {
+            {
+              const int m = i * TJ + j, n = hi - lo;
+              __builtin_amdgcn_sched_barrier(0);
+              if (m == (TI * TJ > 1 ? 1 : 0)) then();
+              issue(buf, lo + m * n / (TI * TJ), lo + (m + 1) * n / (TI * TJ));
+              __builtin_amdgcn_sched_barrier(0);
+            }
+            if constexpr (KIND == K_REF || KIND == K_GRID) {
+              acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, f[i]), __builtin_bit_cast(bf16x8, f[TI + j]), acc[i][j], 0, 0, 0);
+            } else if constexpr (KIND == K_I8) {
+              acc[i][j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(f[i], f[TI + j], acc[i][j], 0, 0, 0);
+            } else {
+              // format selectors 0 = E4M3 for both operands; block scales 2^0 (exponent byte 127)
+              acc[i][j] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(f[i], f[TI + j], acc[i][j], 0, 0, 0, 127, 0, 127);
+            }
+          }
+      }
     };
     // One K step.  Its last group is preceded by a barrier that makes stage k+1 visible to everyone and tells
     // everyone that stage k is no longer read (its last fragments are in registers): the fragments of the next step's
@@ -367,11 +407,14 @@ __global__ __launch_bounds__(T::NW * 64) __attribute__((amdgpu_waves_per_eu(T::P
         if constexpr (decltype(last_c)::value && EIGHT) {
           if (gi >= NG / 2) {
 #pragma unroll
-            for (int i = 0; i < TI; ++i) f[gi & 1][i] = drop ? frag_t{} : f[gi & 1][i];
+            for (int i = 0; i < TI; ++i) {
+              f[gi & 1][i] = drop ? frag_t{} : f[gi & 1][i];
+              if constexpr (WIDENED) wide[0][i] = drop ? bf16x8{} : wide[0][i];
+            }
           }
         }
         if (gi + 1 < NG) {
-          run_group(f[gi & 1], b2, FIRST + gi * (DEP - FIRST) / (NG - 1), FIRST + (gi + 1) * (DEP - FIRST) / (NG - 1),
+          run_group(f[gi & 1], f[(gi + 1) & 1], b2, FIRST + gi * (DEP - FIRST) / (NG - 1), FIRST + (gi + 1) * (DEP - FIRST) / (NG - 1),
                     [&] { load_group(s_buf + b0, gi + 1, f[(gi + 1) & 1]); });
         } else {
           // this wave's deposits of stage k+1 have landed, its fragment reads are done; stage k+2 may stay in flight
@@ -386,7 +429,7 @@ __global__ __launch_bounds__(T::NW * 64) __attribute__((amdgpu_waves_per_eu(T::P
             next_stage();
           }
           // (behind the last step: the next product's, which it reads again as its own kind)
-          run_group(f[gi & 1], b0, 0, FIRST, [&] { load_group(s_buf + b1, 0, f[(gi + 1) & 1]); });
+          run_group(f[gi & 1], f[(gi + 1) & 1], b0, 0, FIRST, [&] { load_group(s_buf + b1, 0, f[(gi + 1) & 1]); });
         }
       }
       const int b = b0;
@@ -395,6 +438,10 @@ __global__ __launch_bounds__(T::NW * 64) __attribute__((amdgpu_waves_per_eu(T::P
       b2 = b;
     };
     load_group(s_buf + b0, 0, f[0]);
+    if constexpr (WIDENED) {
+#pragma unroll
+      for (int q = 0; q < TI + TJ; ++q) wide[0][q] = widen(f[0][q], 0);
+    }
     using yes = std::true_type;
     using no = std::false_type;
     int k = EIGHT ? 1 : 0;
@@ -927,7 +974,7 @@ int launch_wa_gemm(const WaGemmParams& p, hipStream_t st) {
   };
 #define MOFQ_WA(A, B) \
   if (k1 == (A) && k2 == (B)) return launch(std::integral_constant<int, A>{}, std::integral_constant<int, B>{});
-  MOFQ_WA(WA_INT8, WA_GRID_BF16) MOFQ_WA(WA_INT8, WA_FP8) MOFQ_WA(WA_INT8, WA_NONE)
+  MOFQ_WA(WA_INT8, WA_GRID_BF16) MOFQ_WA(WA_INT8, WA_GRID_FP8) MOFQ_WA(WA_INT8, WA_FP8) MOFQ_WA(WA_INT8, WA_NONE)
   MOFQ_WA(WA_GRID_BF16, WA_NONE) MOFQ_WA(WA_FP8, WA_NONE) MOFQ_WA(WA_GRID_BF16, WA_GRID_BF16)
 #undef MOFQ_WA
   return MOFQ_ERR_UNSUPPORTED;
@@ -943,7 +990,7 @@ int launch_wa_gemms(const WaGemmParams* p, int n, hipStream_t st) {
     int list[kWaGroup], m = 0;
     for (int i = 0; i < n; ++i) {
       const WaPlan plan = wa_gemm_plan(p[i].M, p[i].N, p[i].K, p[i].ldx, p[i].ldw);
-      const bool pair = p[i].q[0].kind == WA_INT8 && (p[i].q[1].kind == WA_FP8 || p[i].q[1].kind == WA_GRID_BF16) && p[i].q[1].kind == p[0].q[1].kind;
+      const bool pair = p[i].q[0].kind == WA_INT8 && (p[i].q[1].kind == WA_FP8 || p[i].q[1].kind == WA_GRID_FP8) && p[i].q[1].kind == p[0].q[1].kind;
       if (plan.tile == tile && (plan.run > 0) == pieces && pair) list[m++] = i;
     }
     if (m < 2) continue;
@@ -986,7 +1033,7 @@ int launch_wa_gemms(const WaGemmParams* p, int n, hipStream_t st) {
       }
     };
     if (p[0].q[1].kind == WA_FP8) launch(std::integral_constant<int, WA_FP8>{});
-    else launch(std::integral_constant<int, WA_GRID_BF16>{});
+    else launch(std::integral_constant<int, WA_GRID_FP8>{});
     if (hipGetLastError() != hipSuccess) return MOFQ_ERR_HIP;
     for (int i = 0; i < m; ++i) done[list[i]] = true;
   }

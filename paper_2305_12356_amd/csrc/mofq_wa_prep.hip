@@ -4,9 +4,8 @@
 // group of layers go through every pass together, one launch per pass:
 //
 //   1. largest magnitude of each tensor (per-workgroup partial maxima);
-//   2. both formats at once: the INT8 codes, the E4M3 codes and, where the exact E4M3
-//      product is wanted, the E4M3 grid values as bf16, all from one read of the tensor,
-//      with the tensor error of each format as partial sums in fp64.
+//   2. both formats at once: the INT8 and the E4M3 codes from one read of the tensor, with
+//      the tensor error of each format as partial sums in fp64.
 //
 // The small dependent steps (folding the partial maxima, the two scales) are redone by every
 // workgroup of pass 2 from the partials, so no one-workgroup kernel sits between the passes.
@@ -41,7 +40,6 @@ struct PrepTensor {
   double* sse_part;
   uint8_t* q_i8;
   uint8_t* q_f8;
-  uint8_t* q_g;
   float* scale;
   // column split (fp8-unit product); null / 0 otherwise
   int32_t is_x;
@@ -82,12 +80,10 @@ MOFQ_DEV const uint16_t* chunk_src(const PrepTensor& t, int64_t c) {
 
 constexpr int kInFlight = 8;   // 16-byte loads in flight per lane (largest-magnitude pass)
 
-// One chunk in both formats: codes, grid values of E4M3 as bf16 (EXACT), squared differences.
+// One chunk in both formats: codes and squared differences.
 struct QuantChunk {
   u32x2 i8, f8;
-  u32x4 g;
 };
-template <bool EXACT>
 MOFQ_DEV QuantChunk quant_chunk(const u32x4 raw, float iA, float iB, double sAd, double sBd, double& accA, double& accB) {
   QuantChunk q;
   float v[8], y[8];
@@ -121,7 +117,6 @@ MOFQ_DEV QuantChunk quant_chunk(const u32x4 raw, float iA, float iB, double sAd,
       wf[i / 4] = __builtin_amdgcn_cvt_pk_fp8_f32(t0, t1, wf[i / 4], true);
       g = __builtin_amdgcn_cvt_pk_f32_fp8(wf[i / 4], true);
     }
-    if constexpr (EXACT) q.g[i >> 1] = (f2u(g[0]) >> 16) | (f2u(g[1]) & 0xFFFF0000u);   // at most 4 significant bits: exact in bf16
     add(accB, g[0], sBd, v[i]);
     add(accB, g[1], sBd, v[i + 1]);
     // one pair at a time: the two fp64 chains are sequential anyway, and scheduling all eight
@@ -146,11 +141,10 @@ MOFQ_DEV u32x2 without_side(const PrepTensor& t, int64_t c, u32x2 f8) {
   o[1] = f8[1] & (((m[1] >> 7) & 0x01010101u) * 0xFFu);
   return o;
 }
-template <bool EXACT> MOFQ_DEV void store_chunk(const PrepTensor& t, int64_t c, const QuantChunk& q) {
+MOFQ_DEV void store_chunk(const PrepTensor& t, int64_t c, const QuantChunk& q) {
   reinterpret_cast<u32x2*>(t.q_i8)[c] = q.i8;
   reinterpret_cast<u32x2*>(t.q_f8)[c] = q.f8;
-  if constexpr (EXACT) reinterpret_cast<u32x4*>(t.q_g)[c] = q.g;
-  else if (t.q_f8_main) reinterpret_cast<u32x2*>(t.q_f8_main)[c] = without_side(t, c, q.f8);   // uniform: an activation
+  if (t.q_f8_main) reinterpret_cast<u32x2*>(t.q_f8_main)[c] = without_side(t, c, q.f8);   // uniform: an activation
 }
 // Chunks c and c + 1, c even: 16 bytes of codes each
 MOFQ_DEV void store_pair(const PrepTensor& t, int64_t c, const QuantChunk& a, const QuantChunk& b) {
@@ -396,23 +390,22 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(5))) v
     const int64_t lo = static_cast<int64_t>(seg) * t.seg_chunks;
     const int64_t hi = (lo + t.seg_chunks < t.n_chunks) ? lo + t.seg_chunks : t.n_chunks;
     double accA = 0.0, accB = 0.0;
-    // Dense input (uniform): two chunks in flight; where only codes leave, neighbouring ones, in 16-byte pieces (with grid values,
-    // whose two pieces would lie apart, 4096 wide, 200 tokens 817 -> 845 us).  Rows apart: one chunk at a time.
-    int64_t c = SIDE && dense ? lo + 2 * tid : lo + tid;
-    constexpr int64_t other = SIDE ? 1 : kThreads;   // the second chunk
-    for (; dense && c + other < hi; c += 2 * kThreads) {
-      const u32x4 raw0 = *reinterpret_cast<const u32x4*>(t.data + c * 8), raw1 = *reinterpret_cast<const u32x4*>(t.data + (c + other) * 8);
-      const QuantChunk q0 = quant_chunk<!SIDE>(raw0, iA, iB, sAd, sBd, accA, accB);
-      if constexpr (!SIDE) store_chunk<true>(t, c, q0);
+    // dense input (uniform): two neighbouring chunks at a time, so that the codes leave in 16-byte pieces; one where rows are apart or
+    // two would leave threads without work (28.95 and 28.64 us for a whole select of 512 x 1024 x 1024)
+    const bool pairs = dense && hi - lo >= 4 * kThreads;
+    int64_t c = pairs ? lo + 2 * tid : lo + tid;
+    for (; pairs && c + 1 < hi; c += 2 * kThreads) {
+      const u32x4* const src = reinterpret_cast<const u32x4*>(t.data + c * 8);
+      const u32x4 raw0 = src[0], raw1 = src[1];
+      const QuantChunk q0 = quant_chunk(raw0, iA, iB, sAd, sBd, accA, accB);
       __builtin_amdgcn_sched_barrier(0);   // one chunk at a time: keeps the register count low
-      const QuantChunk q1 = quant_chunk<!SIDE>(raw1, iA, iB, sAd, sBd, accA, accB);
-      if constexpr (SIDE) store_pair(t, c, q0, q1);
-      else store_chunk<true>(t, c + other, q1);
+      const QuantChunk q1 = quant_chunk(raw1, iA, iB, sAd, sBd, accA, accB);
+      store_pair(t, c, q0, q1);
     }
-    // what is left of a lane's chunks, or all of them
-    for (; c < hi; c += SIDE && dense ? 2 * kThreads : kThreads) {
+    // an odd last chunk, or all of them
+    for (; c < hi; c += pairs ? 2 * kThreads : kThreads) {
       const u32x4 raw = *reinterpret_cast<const u32x4*>(chunk_src(t, c));
-      store_chunk<!SIDE>(t, c, quant_chunk<!SIDE>(raw, iA, iB, sAd, sBd, accA, accB));
+      store_chunk(t, c, quant_chunk(raw, iA, iB, sAd, sBd, accA, accB));
     }
     accA = wave_sum(accA);
     accB = wave_sum(accB);
@@ -439,7 +432,6 @@ bool fill(const WaPrepTensor& p, PrepTensor* t) {
   t->sse_part = p.sse_part;
   t->q_i8 = p.q_i8;
   t->q_f8 = p.q_f8;
-  t->q_g = p.q_g;
   t->scale = p.scale;
   if (p.side) {
     if (!p.col_slot || !p.side_cols || p.cols % 64 != 0 || p.rows > (1 << 30) || p.cols > (1 << 20) ||

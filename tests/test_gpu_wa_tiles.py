@@ -8,6 +8,7 @@ import mofq_inputs as mi
 from oracle import mofq_oracle as orc
 from tests import test_gpu_w_only_output as wo
 from tests import test_gpu_wa as wa
+from tests import test_gpu_wa_layers as layers
 
 pytestmark = pytest.mark.gpu
 
@@ -46,6 +47,46 @@ def test_exact_products(mq, name):
     x, w = tensors(SHAPES[name], 8100)
     wa.check_layer(mq, x, w, [I8, FP8], orc.PER_TENSOR, name)          # the fused path
     wa.check_layer(mq, x, w, [FP8, I8], orc.PER_CHANNEL, name)         # the general one; a product alone
+
+
+@pytest.mark.parametrize("shape", [(70, 300, 320), (64, 256, 64 * 41), (1601, 1345, 320), (2049, 2049, 256)])
+def test_exact_products_widen_every_code(mq, shape):
+    """Operands on E4M3's grid (scale 1), every finite code of it, one weight to a row: each output is a single product of
+    two grid values, exact in fp32, so the E4M3 error is 0 in every tiling."""
+    M, N, K = shape
+    g = torch.Generator().manual_seed(K)
+    grid = torch.arange(256, dtype=torch.uint8).view(torch.float8_e4m3fn).float()
+    grid = grid[grid.isfinite()]
+    x = grid[torch.randint(len(grid), (M, K), generator=g)]
+    w = torch.zeros(N, K)
+    w[torch.arange(N), torch.arange(N) % K] = grid[torch.arange(N) % len(grid)]
+    x[0, 0] = w[0, 0] = 448.0
+    x, w = x.to(torch.bfloat16).to(DEV), w.to(torch.bfloat16).to(DEV)
+    cfg = mq.Cfg(mq.PER_TENSOR, mi.clip_ratios(1))
+    r, w_out, _ = layers.run_single(mq, [w], [x], [I8, FP8], mq.ERR_LAYER_OUTPUT, cfg)
+    assert r[0].err[1] == 0.0 and r[0].err[0] > 0.0 and r[0].best == 1
+    assert torch.equal(w_out[0].codes.view(-1), w.cpu().float().to(torch.float8_e4m3fn).view(torch.uint8).view(-1).to(DEV))
+
+
+@pytest.mark.parametrize("apart", [0, 64])
+def test_layers_with_one_code_buffer(mq, apart):
+    """Layers whose weights' codes go to the same memory, or to memory that overlaps: what is written there is not
+    defined, the errors and choices are those of separate buffers."""
+    ws = [mi.llama_like_weight(n, 320, seed=n, dtype=torch.bfloat16, device=DEV) for n in (200, 260, 130)]
+    xs = [mi.activations(150, 320, seed=7, device=DEV)] * 3
+    cfg = mq.Cfg(mq.PER_TENSOR, mi.clip_ratios(1))
+    want, _, _ = layers.run_batched(mq, ws, xs, [I8, FP8], mq.ERR_LAYER_OUTPUT, cfg)
+    w_out, x_out = layers.alloc_outs(mq, ws, xs, cfg)
+    memory = torch.empty(260 * 320 + 128, dtype=torch.uint8, device=DEV)
+    for i, o in enumerate(w_out):
+        o.codes = memory[i * apart:i * apart + ws[i].numel()]
+    batch = mq.WaLayerBatch(ws, xs, w_out, x_out)
+    wsp = torch.empty(batch.workspace_bytes(2, mq.ERR_LAYER_OUTPUT, cfg), dtype=torch.uint8, device=DEV)
+    res = mq.alloc_result(DEV, 3)
+    mq.select_layers_wa(batch, [I8, FP8], mq.ERR_LAYER_OUTPUT, cfg, res, wsp)
+    torch.cuda.synchronize()
+    for a, b in zip(mq.read_results(res), want):
+        assert a.best == b.best and list(a.err)[:2] == list(b.err)[:2] and a.ref_energy == b.ref_energy
 
 
 @pytest.mark.parametrize("name", list(SHAPES))
