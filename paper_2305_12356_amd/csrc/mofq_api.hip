@@ -127,7 +127,8 @@ struct SweepEmit {
   uint8_t* i8;
   void* f8;
   int f8_as_bf16;
-  void* grid[2];   // per-channel pair: bf16 grid values of candidate 0 and candidate 1
+  void* grid[2];   // per-channel pair: grid values of candidate 0 and candidate 1
+  int grid_fp8;    // (SweepParams::emit_grid_fp8)
 };
 
 // Where a search writes codes ahead (AheadCodes; nullptr: it does not), and whether its rows leave tallies.
@@ -237,6 +238,7 @@ int sweep_candidates(const mofq_tensor_t* t, const int32_t* cand, int n_cand,
       const bool swapped = p.fmt[0] != cand[c0];
       p.emit_grid[0] = em->grid[swapped ? 1 : 0];
       p.emit_grid[1] = em->grid[swapped ? 0 : 1];
+      p.emit_grid_fp8 = em->grid_fp8;
     }
     rc = launch_sweep(p, st);
     if (rc != MOFQ_OK) return rc;
@@ -358,7 +360,7 @@ int check_wo_output(const mofq_tensor_t* w, const mofq_tensor_t* x, const int32_
 
 struct WoOutWs {
   WOnlyWs wrec;
-  uint8_t* wg[2];   // grid values of W per candidate, bf16, dense
+  uint8_t* wg[2];   // grid values of W per candidate, bf16, dense; or in the first both candidates' as e4m3 codes
   double* part[3];  // error per candidate, reference energy; one value per output tile
   void* partial;
   int blocks;
@@ -381,6 +383,8 @@ WoOutWs carve_wo_output(void* ws, const mofq_tensor_t* w, const mofq_tensor_t* x
   return a;
 }
 
+bool four_bits(int32_t format) { return format == MOFQ_INT4 || format == MOFQ_FP4_E2M1 || format == MOFQ_FP4_E2M1_IEEE; }
+
 int wo_output_score(const mofq_tensor_t* w, const mofq_tensor_t* x, const int32_t* cand, int n_cand,
                     const mofq_scale_cfg_t* w_cfg, const WoOutWs& a, hipStream_t st,
                     hipEvent_t ev0, hipEvent_t ev1, void* ahead_codes = nullptr) {
@@ -388,7 +392,9 @@ int wo_output_score(const mofq_tensor_t* w, const mofq_tensor_t* x, const int32_
   // A pair of different formats with per-channel absmax scales (one clip ratio): the scoring pass
   // holds each row in registers and writes both candidates' grid values itself.
   const bool fused = n_cand == 2 && paired(cand[0], cand[1]) && w_cfg->gran == MOFQ_PER_CHANNEL && w_cfg->n_clip == 1;
-  const SweepEmit em{nullptr, nullptr, 0, {a.wg[0], a.wg[1]}};
+  // Products side by side read the two 4-bit formats' values from one array of e4m3 codes, half the bytes of bf16.
+  const bool pair = fused && wa_plan(w, x).shared && four_bits(cand[0]) && four_bits(cand[1]);
+  const SweepEmit em{nullptr, nullptr, 0, {a.wg[0], pair ? a.wg[0] + 64 : a.wg[1]}, pair};
   if ((rc = sweep_candidates(w, cand, n_cand, w_cfg, a.wrec, st, fused ? &em : nullptr, {ahead_codes, false}))) return rc;
   WaGemmParams g{};
   for (int c = 0; c < n_cand; ++c) {
@@ -410,9 +416,9 @@ int wo_output_score(const mofq_tensor_t* w, const mofq_tensor_t* x, const int32_
       e.as_bf16_values = 1;
       if ((rc = launch_emit(&e, 1, 0, st))) return rc;
     }
-    g.q[c].kind = WA_GRID_BF16;
+    g.q[c].kind = pair ? WA_PAIR_FP8 : WA_GRID_BF16;
     g.q[c].x = x->data;          // the unquantized input, scale 1
-    g.q[c].w = a.wg[c];
+    g.q[c].w = a.wg[pair ? 0 : c];
     g.q[c].sx = nullptr;
     g.q[c].sw = a.wrec.scale[c];
     g.q[c].part = a.part[c];
@@ -482,7 +488,7 @@ int wa_score(const mofq_tensor_t* w, const mofq_tensor_t* x, const int32_t* cand
   if (n_cand == 2)
     both = (cand[0] == MOFQ_INT8 && cand[1] == MOFQ_FP8_E4M3) || (cand[0] == MOFQ_FP8_E4M3 && cand[1] == MOFQ_INT8);
   const bool fused_x = both, fused_w = both && w_cfg->gran == MOFQ_PER_TENSOR;
-  const SweepEmit ex{a.xq[0], a.xq[1], fp8_unit ? 0 : 1, {nullptr, nullptr}}, ew{a.wq[0], a.wq[1], fp8_unit ? 0 : 1, {nullptr, nullptr}};
+  const SweepEmit ex{a.xq[0], a.xq[1], fp8_unit ? 0 : 1, {nullptr, nullptr}, 0}, ew{a.wq[0], a.wq[1], fp8_unit ? 0 : 1, {nullptr, nullptr}, 0};
   if ((rc = sweep_candidates(x, cand, n_cand, &xc, a.xrec, st, fused_x ? &ex : nullptr))) return rc;
   if ((rc = sweep_candidates(w, cand, n_cand, w_cfg, a.wrec, st, fused_w ? &ew : nullptr))) return rc;
   WaGemmParams g{};

@@ -63,9 +63,18 @@ struct SweepParams {
   int32_t emit_f8_as_bf16;
   // per-channel pair of two different formats (bf16 input) with one clip ratio only: the pass
   // also writes the grid values of format slot f as bf16, dense [rows][cols], to emit_grid[f]
+  // (emit_grid_fp8, 4-bit formats: as e4m3 codes, a byte each, at grid_fp8_at() in rows of 2 * cols bytes; emit_grid[f] is the
+  // first row's first byte of slot f)
   void* emit_grid[kMaxFmt];
+  int32_t emit_grid_fp8;
   AheadCodes ahead;
 };
+
+// The grid values of two 4-bit formats as one operand (WA_PAIR_FP8): 128 bytes of a row hold 64 of its columns, the e4m3 codes of the
+// first format and then of the second, so that one line of LDS is one step of K.  Pieces of 8 codes; in every second 16 rows the
+// two of a 16-byte piece are exchanged: the matrix kernel's reads of 8 bytes by 32 rows then meet no bank twice.
+// Byte of a row at which piece c of the first format begins (the second's: 64 further):
+constexpr uint32_t grid_fp8_at(uint32_t row, uint32_t c) { return c / 8 * 128 + ((c % 8) ^ (row >> 4 & 1)) * 8; }
 
 constexpr int kTensorBlocks = 1024;  // partial results of per-tensor passes
 
@@ -167,6 +176,7 @@ enum WaKind : int32_t {
   WA_GRID_BF16 = 1,   // grid values stored as bf16 (exact), bf16 matrix cores
   WA_INT8 = 2,        // int8 codes, int8 matrix cores
   WA_FP8 = 3,         // e4m3 codes, fp8 matrix cores
+  WA_PAIR_FP8 = 5,    // both products' w: e4m3 codes of two 4-bit formats in one array (grid_fp8_at), widened as WA_GRID_FP8
   WA_GRID_FP8 = 4,    // e4m3 codes, widened to bf16 on the way to the bf16 matrix cores (exact)
 };
 struct WaProduct {
@@ -192,6 +202,7 @@ struct WaGemmParams {
 struct WaPlan {
   enum : int { kLarge, kMedium, kSmall, kWide };
   int tile;
+  bool shared;             // three bf16 products with one X run side by side (wa_gemm_shared_kernel)
   int run;                 // > 0: every product is cut into pieces of up to so many stages (64 sixteen-bit elements of K), each a workgroup's
   int blocks;              // output tiles
   size_t partial_bytes;    // of WaGemmParams::partial

@@ -37,7 +37,8 @@ struct SweepArgs {
   uint8_t* emit_i8;          // per-tensor 8-bit pair: also write the codes (see SweepParams)
   void* emit_f8;
   int32_t emit_f8_as_bf16;
-  uint16_t* emit_grid[kMaxFmt];   // per-channel single-candidate pair: grid values as bf16 (see SweepParams)
+  uint16_t* emit_grid[kMaxFmt];   // per-channel single-candidate pair: grid values as bf16 or e4m3 codes (see SweepParams)
+  int32_t emit_grid_fp8;
   AheadCodes ahead;
   int32_t bisect;            // 4-bit formats: score candidates by bisection of the clip ratios, which descend
   float clip[MOFQ_MAX_CLIP];
@@ -386,11 +387,11 @@ __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(CH <= 4
 // keeps the fp64 image of the whole row across the barrier (128 registers and spills for 4 chunks
 // per thread, 72 without).
 //
-// GRID: the pass also writes the grid values of both formats as bf16 (dense rows), the operands
-// of the weight-only layer-output products, so that they cost no further read of the tensor.
+// GRID: the pass also writes the grid values of both formats, the operands of the weight-only layer-output products, so that
+// they cost no further read of the tensor: 1 as bf16 (dense rows), 2 as e4m3 codes in one array.
 // With a.ahead the row's codes leave from the same registers.
 // ------------------------------------------------------------------------------
-template <typename In, int FA, int FB, int THREADS, int CH, bool GRID = false>
+template <typename In, int FA, int FB, int THREADS, int CH, int GRID = 0>
 __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(GRID ? 2 : 4))) void sweep_channel_single_kernel(const SweepArgs a) {
   constexpr int NF = (FB >= 0) ? 2 : 1;
   constexpr int FBX = (FB >= 0) ? FB : FA;
@@ -450,16 +451,26 @@ __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(GRID ? 
     raw[j].opaque();
     float v[8];
     raw[j].widen(v);
-    if constexpr (GRID) {
-      // grid values have at most 7 significant bits: exact in bf16 (the top half of an fp32)
+    if constexpr (GRID != 0) {
+      // grid values have at most 7 significant bits: exact in bf16 (the top half of an fp32); 4-bit formats' at most 3, and the
+      // smallest is 1/2: exact in e4m3
       u32x4 ga, gb;
+      int pa[2] = {0, 0}, pb[2] = {0, 0};
 #pragma unroll
       for (int i = 0; i < 8; i += 2) {
         const float x0 = v[i], x1 = v[i + 1];
         const f32x2 qa = grid2<FA>(x0 * iA, x1 * iA, carry);
         const f32x2 qb = grid2<FBX>(x0 * iB, x1 * iB, carry);
-        ga[i >> 1] = (f2u(qa[0]) >> 16) | (f2u(qa[1]) & 0xFFFF0000u);
-        gb[i >> 1] = (f2u(qb[0]) >> 16) | (f2u(qb[1]) & 0xFFFF0000u);
+        if constexpr (GRID == 1) {
+          ga[i >> 1] = (f2u(qa[0]) >> 16) | (f2u(qa[1]) & 0xFFFF0000u);
+          gb[i >> 1] = (f2u(qb[0]) >> 16) | (f2u(qb[1]) & 0xFFFF0000u);
+        } else if (i % 4 == 0) {
+          pa[i / 4] = __builtin_amdgcn_cvt_pk_fp8_f32(qa[0], qa[1], pa[i / 4], false);
+          pb[i / 4] = __builtin_amdgcn_cvt_pk_fp8_f32(qb[0], qb[1], pb[i / 4], false);
+        } else {
+          pa[i / 4] = __builtin_amdgcn_cvt_pk_fp8_f32(qa[0], qa[1], pa[i / 4], true);
+          pb[i / 4] = __builtin_amdgcn_cvt_pk_fp8_f32(qb[0], qb[1], pb[i / 4], true);
+        }
         const double a0 = __builtin_fma(-static_cast<double>(qa[0]), sAd, static_cast<double>(x0));
         const double a1 = __builtin_fma(-static_cast<double>(qa[1]), sAd, static_cast<double>(x1));
         accA = __builtin_fma(a0, a0, accA);
@@ -471,8 +482,14 @@ __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(GRID ? 
       }
       const int c = j * THREADS + tid;
       if (c < cpr) {
-        reinterpret_cast<u32x4*>(a.emit_grid[0])[row * cpr + c] = ga;
-        reinterpret_cast<u32x4*>(a.emit_grid[1])[row * cpr + c] = gb;
+        if constexpr (GRID == 1) {
+          reinterpret_cast<u32x4*>(a.emit_grid[0])[row * cpr + c] = ga;
+          reinterpret_cast<u32x4*>(a.emit_grid[1])[row * cpr + c] = gb;
+        } else {
+          const int64_t at = row * (2 * a.cols) + grid_fp8_at(static_cast<uint32_t>(row), static_cast<uint32_t>(c));
+          *reinterpret_cast<u32x2*>(reinterpret_cast<char*>(a.emit_grid[0]) + at) = u32x2{static_cast<uint32_t>(pa[0]), static_cast<uint32_t>(pa[1])};
+          *reinterpret_cast<u32x2*>(reinterpret_cast<char*>(a.emit_grid[1]) + at) = u32x2{static_cast<uint32_t>(pb[0]), static_cast<uint32_t>(pb[1])};
+        }
       }
     } else {
 #pragma unroll
@@ -1110,7 +1127,12 @@ int launch_channel(const SweepArgs& a, hipStream_t st) {
     if (a.emit_grid[0]) {                                                                \
       if constexpr (std::is_same<In, BF16>::value && FB >= 0) {                          \
         if (a.n_clip != 1 || !a.emit_grid[1]) return MOFQ_ERR_UNSUPPORTED;               \
-        hipLaunchKernelGGL((sweep_channel_single_kernel<In, FA, FB, THREADS, CH, true>), grid, dim3(THREADS), 0, st, a); \
+        if (!a.emit_grid_fp8)                                                            \
+          hipLaunchKernelGGL((sweep_channel_single_kernel<In, FA, FB, THREADS, CH, 1>), grid, dim3(THREADS), 0, st, a); \
+        else if constexpr (Codec<FA>::BITS == 4 && Codec<(FB >= 0 ? FB : FA)>::BITS == 4) \
+          hipLaunchKernelGGL((sweep_channel_single_kernel<In, FA, FB, THREADS, CH, 2>), grid, dim3(THREADS), 0, st, a); \
+        else                                                                             \
+          return MOFQ_ERR_UNSUPPORTED;                                                   \
       } else {                                                                           \
         return MOFQ_ERR_UNSUPPORTED;                                                     \
       }                                                                                  \
@@ -1259,6 +1281,8 @@ int launch_sweep(const SweepParams& p, hipStream_t st) {
     if (p.gran != MOFQ_PER_CHANNEL || p.n_clip != 1 || p.n_fmt != 2) return MOFQ_ERR_UNSUPPORTED;
     a.emit_grid[0] = static_cast<uint16_t*>(p.emit_grid[0]);
     a.emit_grid[1] = static_cast<uint16_t*>(p.emit_grid[1]);
+    a.emit_grid_fp8 = p.emit_grid_fp8;
+    if (p.emit_grid_fp8 && p.cols % 64 != 0) return MOFQ_ERR_UNSUPPORTED;
   }
   if (p.ahead.codes) {
     if (p.gran != MOFQ_PER_CHANNEL || p.n_clip != 1 || (p.n_fmt == 2 && !p.ahead.tag)) return MOFQ_ERR_UNSUPPORTED;

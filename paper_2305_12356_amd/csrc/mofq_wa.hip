@@ -67,9 +67,9 @@ namespace mofq {
 namespace {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef int i32x16 __attribute__((ext_vector_type(16)));
+typedef int i32x2 __attribute__((ext_vector_type(2)));
 typedef int i32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef int i32x8 __attribute__((ext_vector_type(8)));
@@ -133,6 +133,17 @@ MOFQ_DEV void lds_deposit(const char* base, uint32_t off, uint32_t lds_addr) {
 // s_waitcnt: all LDS reads done, at most N vector-memory operations in flight (6 bits, split field).
 template <int N> MOFQ_DEV void wait_deposits_and_reads() {
   __builtin_amdgcn_s_waitcnt((N & 15) | (7 << 4) | (0 << 8) | ((N >> 4) << 14));
+}
+
+// 8 e4m3 codes as bf16 (exact)
+MOFQ_DEV i32x4 widened(int lo, int hi) {
+  i32x4 o;
+#pragma unroll
+  for (int d = 0; d < 2; ++d) {
+    o[2 * d] = __builtin_bit_cast(int, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(d ? hi : lo, 1.0f, false));
+    o[2 * d + 1] = __builtin_bit_cast(int, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(d ? hi : lo, 1.0f, true));
+  }
+  return o;
 }
 
 enum : int { K_REF = 100, K_GRID = WA_GRID_BF16, K_I8 = WA_INT8, K_F8 = WA_FP8, K_G8 = WA_GRID_FP8 };   // K_REF: the 16-bit inputs themselves
@@ -336,18 +347,7 @@ __global__ __launch_bounds__(T::NW * 64) __attribute__((amdgpu_waves_per_eu(T::P
     // widened (4 conversions to 8 codes) between the matrix instructions before: the second half of a group's during its first half,
     // the next group's first half (of `next`) during its second.
     bf16x8 wide[2][TI + TJ];
-    auto widen = [](const auto& v, int h) {
-      bf16x8 o;
-#pragma unroll
-      for (int d = 0; d < 2; ++d)
-#pragma unroll
-        for (int e = 0; e < 2; ++e) {
-          const bf16x2 p = e ? __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(v[2 * h + d], 1.0f, true) : __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(v[2 * h + d], 1.0f, false);
-          o[4 * d + 2 * e] = p[0];
-          o[4 * d + 2 * e + 1] = p[1];
-        }
-      return o;
-    };
+    auto widen = [](const auto& v, int h) { return __builtin_bit_cast(bf16x8, widened(v[2 * h], v[2 * h + 1])); };
     // The matrix instructions of one group, with the deposits [lo, hi) of the current stage
     // spread between them: a wave issues in order, so a burst of deposits (each occupies
     // the texture path for ~18 clocks, and all waves share it) would hold back the
@@ -651,12 +651,21 @@ __global__ __launch_bounds__(T::NW * 64) void wa_pieces_kernel(const GemmBatch<N
 // 11008 x 8192 913 instead of 885).  Measured, layer selection with INT4 and E2M1, us, one product after the other -> here:
 // 2048 x 11008 x 4096 (tokens x rows x columns) 516 -> 467, 1536 x 11008 x 8192 1009 -> 885, 2048 x 4096 x 4096 186 -> 167, 1024 x 11008 x 4096
 // 349 -> 314, 512 x 4096 x 4096 100 -> 82, 777 x 3000 x 5056 118 -> 109, 64 x 4096 x 1024 39.8 -> 35.  Bound by power and LDS as
-// wa_gemm_kernel: 1.41 PFLOP/s at the first of these shapes, 1.19 before.  Medium tiles have eight waves of 64x32 (four of 64x64
-// are 1 % slower).  The sums are those of wa_gemm_kernel bit for bit.
-template <int TM_, int TN_, int WM_, int WN_> struct SharedTile {
+// wa_gemm_kernel.  Medium tiles have eight waves of 64x32 (four of 64x64 are 1 % slower).  The sums are those of
+// wa_gemm_kernel bit for bit.
+//
+// PAIR: two 4-bit formats' grid values come as e4m3 codes in one array (grid_fp8_at) and are widened to bf16, exactly, while the product
+// before runs: 512 rows a step instead of 640, fragments of 6 x 16 bytes for 12 matrix instructions instead of 8, and half the
+// bytes for the scoring pass to write.  A lane holds one format's codes of a group at a time (both formats' take more registers than
+// two waves of a SIMD have: 5 spilled, 458 us for the first shape).  As bf16 -> so, us: 2048 x 11008 x 4096 443 -> 426 (1.50 PFLOP/s in
+// the kernel), 1536 x 11008 x 8192 840 -> 797, 2048 x 4096 x 4096 161 -> 159, 1024 x 11008 x 4096 299 -> 250, 512 x 4096 x 4096 77 -> 71, 777 x 3000 x
+// 5056 106 -> 97, 64 x 4096 x 1024 34.2 -> 30.4.  The bf16 form serves 8-bit formats and scales with several ratios, whose
+// values leave the emission pass.
+template <int TM_, int TN_, int WM_, int WN_, bool PAIR_> struct SharedTile {
+  static constexpr bool PAIR = PAIR_;   // operands of the quantized products: one array of e4m3 codes, else two of bf16
   static constexpr int TM = TM_, TN = TN_, WM = WM_, WN = WN_;
   static constexpr int NW = (TM / WM) * (TN / WN);
-  static constexpr int STAGE = (TM + 3 * TN) * ROW_B;
+  static constexpr int STAGE = (TM + (PAIR ? 2 : 3) * TN) * ROW_B;
   static constexpr int PER_CU = (160 * 1024) / (2 * STAGE);
   static constexpr int PER_SIMD = PER_CU * NW / 4;
 };
@@ -665,9 +674,11 @@ template <typename T>
 __global__ __launch_bounds__(T::NW * 64) __attribute__((amdgpu_waves_per_eu(T::PER_SIMD, T::PER_SIMD))) void wa_gemm_shared_kernel(const GemmArgs a) {
   constexpr int TM = T::TM, TN = T::TN, WM = T::WM, WN = T::WN, NW = T::NW;
   constexpr int TI = WM / 32, TJ = WN / 32, STAGE = T::STAGE, STEP = NW * 8;
-  constexpr int DX = TM / STEP, DW = TN / STEP, DEP = DX + 3 * DW;   // deposits per wave per stage
+  constexpr bool PAIR = T::PAIR;
+  constexpr int NB = PAIR ? 2 : 3;                             // arrays beside X
+  constexpr int DX = TM / STEP, DW = TN / STEP, DEP = DX + NB * DW;   // deposits per wave per stage
   constexpr int NG = CH / 2, NSUB = 3 * NG;                          // groups of 16 of K; a group of one product
-  constexpr int FIRST = DEP / 5, SPREAD = 4;                   // deposits issued behind the barrier; over how many parts the others go
+  constexpr int FIRST = PAIR ? DEP / 4 : DEP / 5, SPREAD = 4;                   // deposits issued behind the barrier; over how many parts the others go
   static_assert(TM % STEP == 0 && TN % STEP == 0 && STEP % 16 == 0, "deposits");
   __shared__ __attribute__((aligned(1024))) unsigned char s_buf[2 * STAGE];
 
@@ -709,7 +720,7 @@ __global__ __launch_bounds__(T::NW * 64) __attribute__((amdgpu_waves_per_eu(T::P
     dep_left -= 1;
     dep_x += by;
 #pragma unroll
-    for (int q = 0; q < 3; ++q) dep_w[q] += by;
+    for (int q = 0; q < NB; ++q) dep_w[q] += by;
   };
   auto issue = [&](int buf, int lo, int hi) {
 #pragma unroll
@@ -749,8 +760,16 @@ __global__ __launch_bounds__(T::NW * 64) __attribute__((amdgpu_waves_per_eu(T::P
 #pragma unroll
     for (int j = 0; j < TJ; ++j) fb[sub & 1][j] = *reinterpret_cast<const i32x4*>(s_buf + buf + row_b + ch_k[sub / 3] + (sub % 3 * TN + j * 32) * ROW_B);
   };
+  // PAIR: a group's 8 codes of each format, widened into fb while the product before runs
+  const int row_q = (TM + TN + wn * WN + r) * ROW_B, half_q = ((g ^ (r >> 4)) & 1) * 8;
+  i32x2 fq[TJ];
+  auto load_q = [&](int buf, int gi, int f) {
+#pragma unroll
+    for (int j = 0; j < TJ; ++j) fq[j] = *reinterpret_cast<const i32x2*>(s_buf + buf + row_q + ((4 * f + gi) ^ sw) * 16 + half_q + j * 32 * ROW_B);
+  };
   load_a(b0, 0);
   load_b(b0, 0);
+  if constexpr (PAIR) load_q(b0, 0, 0);
   for (int k = 0; k < stages; ++k) {
 #pragma unroll
     for (int sub = 0; sub < NSUB; ++sub) {
@@ -779,11 +798,19 @@ __global__ __launch_bounds__(T::NW * 64) __attribute__((amdgpu_waves_per_eu(T::P
           if (m == (TI * TJ > 1 ? 1 : 0)) {
             if (sub + 1 < NSUB) {
               if (q == 2) load_a(b0, gi + 1);
-              load_b(b0, sub + 1);
+              if (!PAIR || q == 2) load_b(b0, sub + 1);
+              if (PAIR && q == 2) load_q(b0, gi + 1, 0);
             } else {
               load_a(b1, 0);
               load_b(b1, 0);
+              if (PAIR) load_q(b1, 0, 0);
             }
+          }
+          if (PAIR && q < 2) {
+#pragma unroll
+            for (int t = 0; t < TJ; ++t)
+              if (m == (t + 1 < TI * TJ ? t + 1 : TI * TJ - 1)) fb[(sub + 1) & 1][t] = widened(fq[t][0], fq[t][1]);
+            if (q == 0 && m == (TJ < TI * TJ ? TJ : TI * TJ - 1)) load_q(b0, gi, 1);
           }
           issue(buf, lo + m * n / (TI * TJ), lo + (m + 1) * n / (TI * TJ));
           __builtin_amdgcn_sched_barrier(0);
@@ -833,9 +860,9 @@ __global__ __launch_bounds__(T::NW * 64) __attribute__((amdgpu_waves_per_eu(T::P
 using Large = Tile<256, 128, 64, 64>;    // one workgroup per compute unit, two waves per SIMD
 using Medium = Tile<128, 128, 64, 64>;   // one, one wave per SIMD
 using Small = Tile<64, 64, 32, 32>;      // three
-using SharedLarge = SharedTile<256, 128, 64, 64>;
-using SharedMedium = SharedTile<128, 128, 64, 32>;
-using SharedSmall = SharedTile<64, 64, 32, 32>;
+template <bool PAIR> using SharedLarge = SharedTile<256, 128, 64, 64, PAIR>;
+template <bool PAIR> using SharedMedium = SharedTile<128, 128, 64, 32, PAIR>;
+template <bool PAIR> using SharedSmall = SharedTile<64, 64, 32, 32, PAIR>;
 
 }  // namespace
 
@@ -883,6 +910,7 @@ WaPlan wa_gemm_plan(int64_t M, int64_t N, int64_t K, int64_t ldx, int64_t ldw) {
     p.run = static_cast<int>(run);
     p.partial_bytes = static_cast<size_t>(3 * ((stages + run - 1) / run) * small) * (Small::TM * Small::TN * sizeof(float));
   }
+  p.shared = p.tile != WaPlan::kWide && (p.run == 0 || p.blocks > kProductsOnly);
   return p;
 }
 
@@ -900,7 +928,7 @@ int gemm_args(const WaGemmParams& p, GemmArgs& a) {
     if ((q.xs != nullptr) != (q.ws != nullptr)) return MOFQ_ERR_INVALID_ARG;
     if (q.xs && q.kind != WA_FP8) return MOFQ_ERR_INVALID_ARG;
     if (q.kind == WA_NONE) continue;
-    const bool eight = q.kind != WA_GRID_BF16;
+    const bool eight = q.kind != WA_GRID_BF16 && q.kind != WA_PAIR_FP8;   // (a pair: two bytes a column)
     const int64_t row = eight ? p.K : 2 * p.K;
     a.seg[SEG_Q + 2 * i] = Segment{q.x, q.w, row, row, eight ? lines8 : lines16, eight && p.K % 128 != 0};
     if (q.xs) a.seg[SEG_SIDE + 2 * i] = Segment{q.xs, q.ws, 2 * SIDE_K, 2 * SIDE_K, 1, 0};
@@ -948,26 +976,31 @@ int launch_wa_gemm(const WaGemmParams& p, hipStream_t st) {
       set_tiles<T>(p, a);
       hipLaunchKernelGGL(kernel, dim3(static_cast<unsigned>(plan.blocks)), dim3(T::NW * 64), 0, st, a);
     };
-    constexpr bool SHARED = K1 == WA_GRID_BF16 && K2 == WA_GRID_BF16;
+    constexpr bool PAIR = K1 == WA_PAIR_FP8, SHARED = (K1 == WA_GRID_BF16 && K2 == WA_GRID_BF16) || PAIR;
     if constexpr (SHARED) {   // all three products take the unquantized X
       if (p.q[0].x != p.x || p.q[1].x != p.x || p.ldx != p.K || p.q[0].sx || p.q[1].sx) return static_cast<int>(MOFQ_ERR_UNSUPPORTED);
-    }
-    if (plan.tile == WaPlan::kWide) {
-      tiled(Small{}, wa_gemm_kernel<Small, K1, K2, false, true, 1>);
-    } else if (plan.run && !(SHARED && plan.blocks > kProductsOnly)) {
-      tiled(Small{}, wa_gemm_kernel<Small, K1, K2, true, false, 1>, set_pieces(a, plan.run, p.partial));
-      hipLaunchKernelGGL((wa_pieces_kernel<Small, K1, K2, 1>), dim3(static_cast<unsigned>(plan.blocks)), dim3(Small::NW * 64), 0, st, batch);
-    } else if constexpr (SHARED) {
-      switch (plan.tile) {
-        case WaPlan::kLarge: shared(SharedLarge{}, wa_gemm_shared_kernel<SharedLarge>); break;
-        case WaPlan::kMedium: shared(SharedMedium{}, wa_gemm_shared_kernel<SharedMedium>); break;
-        default: shared(SharedSmall{}, wa_gemm_shared_kernel<SharedSmall>);
+      if (PAIR && (!plan.shared || p.q[0].w != p.q[1].w)) return static_cast<int>(MOFQ_ERR_UNSUPPORTED);
+      if (plan.shared) {
+        switch (plan.tile) {
+          case WaPlan::kLarge: shared(SharedLarge<PAIR>{}, wa_gemm_shared_kernel<SharedLarge<PAIR>>); break;
+          case WaPlan::kMedium: shared(SharedMedium<PAIR>{}, wa_gemm_shared_kernel<SharedMedium<PAIR>>); break;
+          default: shared(SharedSmall<PAIR>{}, wa_gemm_shared_kernel<SharedSmall<PAIR>>);
+        }
+        return hip_status(hipGetLastError());
       }
-    } else {
-      switch (plan.tile) {
-        case WaPlan::kLarge: tiled(Large{}, wa_gemm_kernel<Large, K1, K2, false, false, 1>); break;
-        case WaPlan::kMedium: tiled(Medium{}, wa_gemm_kernel<Medium, K1, K2, false, false, 1>); break;
-        default: tiled(Small{}, wa_gemm_kernel<Small, K1, K2, false, false, 1>);
+    }
+    if constexpr (!PAIR) {
+      if (plan.tile == WaPlan::kWide) {
+        tiled(Small{}, wa_gemm_kernel<Small, K1, K2, false, true, 1>);
+      } else if (plan.run) {
+        tiled(Small{}, wa_gemm_kernel<Small, K1, K2, true, false, 1>, set_pieces(a, plan.run, p.partial));
+        hipLaunchKernelGGL((wa_pieces_kernel<Small, K1, K2, 1>), dim3(static_cast<unsigned>(plan.blocks)), dim3(Small::NW * 64), 0, st, batch);
+      } else if constexpr (!SHARED) {
+        switch (plan.tile) {
+          case WaPlan::kLarge: tiled(Large{}, wa_gemm_kernel<Large, K1, K2, false, false, 1>); break;
+          case WaPlan::kMedium: tiled(Medium{}, wa_gemm_kernel<Medium, K1, K2, false, false, 1>); break;
+          default: tiled(Small{}, wa_gemm_kernel<Small, K1, K2, false, false, 1>);
+        }
       }
     }
     return hip_status(hipGetLastError());
@@ -976,6 +1009,7 @@ int launch_wa_gemm(const WaGemmParams& p, hipStream_t st) {
   if (k1 == (A) && k2 == (B)) return launch(std::integral_constant<int, A>{}, std::integral_constant<int, B>{});
   MOFQ_WA(WA_INT8, WA_GRID_BF16) MOFQ_WA(WA_INT8, WA_GRID_FP8) MOFQ_WA(WA_INT8, WA_FP8) MOFQ_WA(WA_INT8, WA_NONE)
   MOFQ_WA(WA_GRID_BF16, WA_NONE) MOFQ_WA(WA_FP8, WA_NONE) MOFQ_WA(WA_GRID_BF16, WA_GRID_BF16)
+  MOFQ_WA(WA_PAIR_FP8, WA_PAIR_FP8)
 #undef MOFQ_WA
   return MOFQ_ERR_UNSUPPORTED;
 }

@@ -95,6 +95,14 @@ def test_weight_only_products(mq, name):
     wo.check_layer(mq, x, w, [I4, FP4], orc.PER_CHANNEL, mi.clip_ratios(1), name)
 
 
+# Both candidates' 4-bit values in one operand, in either order, and what goes on as two operands, in each tile.
+@pytest.mark.parametrize("cands,ratios", [([FP4, I4], 1), ([I4, orc.FP4_E2M1_IEEE], 1), ([I8, FP8], 1), ([I4, FP4], 3)])
+@pytest.mark.parametrize("shape", [(449, 1040, 192), (65, 63, 64), (1601, 1345, 64), (2049, 2049, 128)])
+def test_weight_only_operands(mq, shape, cands, ratios):
+    x, w = tensors(shape, 8300)
+    wo.check_layer(mq, x, w, cands, orc.PER_CHANNEL, mi.clip_ratios(ratios), f"{shape} {cands}")
+
+
 # One stage of 64 columns, two, three and an odd number more, in each tile of the products that share X, with rows of W apart.
 @pytest.mark.parametrize("shape", [(65, 63, 64), (65, 63, 128), (1601, 1345, 64), (1601, 1345, 64 * 7), (2049, 2049, 64), (2049, 2049, 192)])
 def test_weight_only_products_share_the_input(mq, shape):
