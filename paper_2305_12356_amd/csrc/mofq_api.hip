@@ -676,16 +676,18 @@ size_t carve_wa_group(void* arena, int i0, int n, const mofq_tensor_t* w, const 
       t.absmax_part = c.take<float>(kTensorBlocks);
       t.sse_part = c.take<double>(2 * kTensorBlocks);
       t.scale = c.take<float>(2);
-      if (!exact) {
-        const size_t rows = static_cast<size_t>(which ? w[i].rows : x[i].rows);
-        t.side = c.take<uint16_t>(rows * kWaSideCols);
-        if (!which) {
-          const size_t cols = static_cast<size_t>(x[i].cols);
-          t.f8_main = c.take<uint8_t>(e);
-          t.colmax = c.take<float>(cols);
-          t.col_slot = c.take<uint8_t>(cols);
-          t.side_cols = c.take<int32_t>(kWaSideCols + 1);
-        }
+      // The column split's part (the exact product takes it too, unused: its workspace is the larger one, so that a caller can
+      // size one buffer for both metrics by it).
+      const size_t rows = static_cast<size_t>(which ? w[i].rows : x[i].rows);
+      uint16_t* const side = c.take<uint16_t>(rows * kWaSideCols);
+      if (!exact) t.side = side;
+      if (!which) {
+        const size_t cols = static_cast<size_t>(x[i].cols);
+        uint8_t* const f8_main = c.take<uint8_t>(e);
+        float* const colmax = c.take<float>(cols);
+        uint8_t* const col_slot = c.take<uint8_t>(cols);
+        int32_t* const side_cols = c.take<int32_t>(kWaSideCols + 1);
+        if (!exact) { t.f8_main = f8_main; t.colmax = colmax; t.col_slot = col_slot; t.side_cols = side_cols; }
       }
     }
     const WaPlan plan = wa_plan(&w[i], &x[i]);

@@ -8,7 +8,7 @@
 // 8-byte read and three integer operations, 8 vector instructions in all against 22 of the group
 // records, which makes the 127 boundaries of an 8-bit format cheap: scoring every (element, candidate)
 // pair takes 4.8 instructions per element, candidate and format (240 000 per wave lane for a row of
-// 5000 elements and 50 candidates; here a wave issues 1960 instructions in all).  Bound by vector issue and, at 8 bits, by the LDS reads of the look-ups beside it (their
+// 5000 elements and 50 candidates; here a wave issues 1780 instructions in all).  Bound by vector issue and, at 8 bits, by the LDS reads of the look-ups beside it (their
 // bank conflicts take 41 % of the LDS's cycles).
 // The error that leaves for an 8-bit format is the winner's element-wise sum (finish_row): the look-ups
 // choose it, and their difference of large sums would keep four digits fewer (1e-12 instead of 1e-15 on 5000 elements).

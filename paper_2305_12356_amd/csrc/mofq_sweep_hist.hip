@@ -21,7 +21,7 @@
 // Where the counted patterns span few enough binades, sums of magnitudes are 32-bit integers in units
 // of the first counted pattern's ulp (exact, and a third of the instructions of fp64 sums); else fp64.
 //
-// Bound by vector issue: 920 instructions per wave on rows of 4096 elements (INT4 / E2M1, 100 ratios, codes
+// Bound by vector issue: 904 instructions per wave on rows of 4096 elements (INT4 / E2M1, 100 ratios, codes
 // included): 215 to count, 160 for the prefixes, 205 for the look-ups; they take nine tenths of the clocks.  Two blocks of the 65B shape 2295 -> 2222 us, eight of the 7B shape 3094 -> 2957 us with the
 // negative elements' counting behind the loop (note_negative), the halves of a word selected by
 // the instructions that use them (count_pair) and one weighted sum per group (count8); 2218 -> 2161 and 2953 -> 2845 us

@@ -645,7 +645,7 @@ __global__ __launch_bounds__(T::NW * 64) void wa_pieces_kernel(const GemmBatch<N
 // X W^T, X G1^T and X G2^T in one K loop: a stage holds one line of K of TM rows of X and of TN rows of W, G1 and G2
 // each, so X is deposited and its fragments are read once instead of three times: for a 256x128 tile 640 rows a step of 64
 // of K instead of 1152, and 8 fragments for 12 matrix instructions instead of 12.  A lane of a 64x64 share then holds 192
-// accumulators, 247 registers in all, so two waves still fit a SIMD.  A stage of 80 KB leaves room for two in LDS;
+// accumulators, 247 registers in all, so two waves still fit a SIMD.  A stage of 80 KB (PAIR: 64) leaves room for two in LDS;
 // as a step lasts three times as long as one of wa_gemm_kernel, a stage has as long to arrive if its deposits are issued early in the
 // step before: over its first third (FIRST, SPREAD; over two thirds of it 2048 x 11008 x 4096 474 us a call instead of 467, 1536 x
 // 11008 x 8192 913 instead of 885).  Measured, layer selection with INT4 and E2M1, us, one product after the other -> here:
