@@ -253,8 +253,9 @@ struct EmitArgs {
   int32_t fmt[MOFQ_MAX_CANDIDATES];
   int32_t scale_f16_out;
   int32_t as_bf16_values;   // write grid values (bf16, unscaled) instead of codes
-  int32_t fix_rows;         // fixup_kernel: rows a workgroup takes at a time
   EmitTensor t[kEmitBatch];
+  int32_t fix_rows;         // fixup_kernel: rows a workgroup takes at a time (behind the tensors: in front of them it puts what a single
+                            // one's workgroups load first on one cache line more, 0.35 us of a launch)
 };
 
 // row, counted from the segment's first, of the chunk `off` chunks behind that row's start

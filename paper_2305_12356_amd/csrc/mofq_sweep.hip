@@ -37,8 +37,8 @@ struct SweepArgs {
   uint8_t* emit_i8;          // per-tensor 8-bit pair: also write the codes (see SweepParams)
   void* emit_f8;
   int32_t emit_f8_as_bf16;
-  uint16_t* emit_grid[kMaxFmt];   // per-channel single-candidate pair: grid values as bf16 or e4m3 codes (see SweepParams)
   int32_t emit_grid_fp8;
+  uint16_t* emit_grid[kMaxFmt];   // per-channel single-candidate pair: grid values as bf16 or e4m3 codes (see SweepParams)
   AheadCodes ahead;
   int32_t bisect;            // 4-bit formats: score candidates by bisection of the clip ratios, which descend
   float clip[MOFQ_MAX_CLIP];
