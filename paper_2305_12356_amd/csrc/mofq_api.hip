@@ -125,8 +125,7 @@ WOnlyWs carve_w_only(void* ws, int64_t units, int n_cand, int gran, int n_clip) 
 // Optional outputs of the scoring pass itself (per-tensor (INT8, FP8-E4M3) pair only).
 struct SweepEmit {
   uint8_t* i8;
-  void* f8;
-  int f8_as_bf16;
+  uint8_t* f8;
   void* grid[2];   // per-channel pair: grid values of candidate 0 and candidate 1
   int grid_fp8;    // (SweepParams::emit_grid_fp8)
 };
@@ -233,7 +232,6 @@ int sweep_candidates(const mofq_tensor_t* t, const int32_t* cand, int n_cand,
       if (n != 2) return MOFQ_ERR_INVALID_ARG;
       p.emit_i8 = em->i8;
       p.emit_f8 = em->f8;
-      p.emit_f8_as_bf16 = em->f8_as_bf16;
       // launch slots are in (INT, FP) order whatever the candidates' order
       const bool swapped = p.fmt[0] != cand[c0];
       p.emit_grid[0] = em->grid[swapped ? 1 : 0];
@@ -311,7 +309,7 @@ WaPlan wa_plan(const mofq_tensor_t* w, const mofq_tensor_t* x) { return wa_gemm_
 
 struct WaWs {
   WOnlyWs xrec, wrec;
-  uint8_t* xq[2];   // [0] INT8 codes, [1] E4M3 codes (fp8-unit mode) or bf16 grid values
+  uint8_t* xq[2];   // [0] INT8 codes, [1] E4M3 codes
   uint8_t* wq[2];
   double* part[3];  // INT8 error, E4M3 error, reference energy; one value per output tile
   void* partial;
@@ -329,8 +327,8 @@ WaWs carve_wa(void* ws, const mofq_tensor_t* w, const mofq_tensor_t* x, int n_ca
   off += a.wrec.bytes;
   Carver c(base ? base + off : nullptr);
   for (int f = 0; f < 2; ++f) {
-    a.xq[f] = c.take<uint8_t>(static_cast<size_t>(x->rows) * x->cols * (f ? 2 : 1));
-    a.wq[f] = c.take<uint8_t>(static_cast<size_t>(w->rows) * w->cols * (f ? 2 : 1));
+    a.xq[f] = c.take<uint8_t>(static_cast<size_t>(x->rows) * x->cols);
+    a.wq[f] = c.take<uint8_t>(static_cast<size_t>(w->rows) * w->cols);
   }
   const WaPlan plan = wa_plan(w, x);
   a.blocks = plan.blocks;
@@ -394,7 +392,7 @@ int wo_output_score(const mofq_tensor_t* w, const mofq_tensor_t* x, const int32_
   const bool fused = n_cand == 2 && paired(cand[0], cand[1]) && w_cfg->gran == MOFQ_PER_CHANNEL && w_cfg->n_clip == 1;
   // Products side by side read the two 4-bit formats' values from one array of e4m3 codes, half the bytes of bf16.
   const bool pair = fused && wa_plan(w, x).shared && four_bits(cand[0]) && four_bits(cand[1]);
-  const SweepEmit em{nullptr, nullptr, 0, {a.wg[0], pair ? a.wg[0] + 64 : a.wg[1]}, pair};
+  const SweepEmit em{nullptr, nullptr, {a.wg[0], pair ? a.wg[0] + 64 : a.wg[1]}, pair};
   if ((rc = sweep_candidates(w, cand, n_cand, w_cfg, a.wrec, st, fused ? &em : nullptr, {ahead_codes, false}))) return rc;
   WaGemmParams g{};
   for (int c = 0; c < n_cand; ++c) {
@@ -488,7 +486,7 @@ int wa_score(const mofq_tensor_t* w, const mofq_tensor_t* x, const int32_t* cand
   if (n_cand == 2)
     both = (cand[0] == MOFQ_INT8 && cand[1] == MOFQ_FP8_E4M3) || (cand[0] == MOFQ_FP8_E4M3 && cand[1] == MOFQ_INT8);
   const bool fused_x = both, fused_w = both && w_cfg->gran == MOFQ_PER_TENSOR;
-  const SweepEmit ex{a.xq[0], a.xq[1], fp8_unit ? 0 : 1, {nullptr, nullptr}, 0}, ew{a.wq[0], a.wq[1], fp8_unit ? 0 : 1, {nullptr, nullptr}, 0};
+  const SweepEmit ex{a.xq[0], a.xq[1], {nullptr, nullptr}, 0}, ew{a.wq[0], a.wq[1], {nullptr, nullptr}, 0};
   if ((rc = sweep_candidates(x, cand, n_cand, &xc, a.xrec, st, fused_x ? &ex : nullptr))) return rc;
   if ((rc = sweep_candidates(w, cand, n_cand, w_cfg, a.wrec, st, fused_w ? &ew : nullptr))) return rc;
   WaGemmParams g{};
@@ -517,11 +515,10 @@ int wa_score(const mofq_tensor_t* w, const mofq_tensor_t* x, const int32_t* cand
       e.clip[0] = rec.clip[slot];
       e.err[0] = rec.err[slot];
       e.out.codes = which ? a.wq[f] : a.xq[f];
-      e.as_bf16_values = (f == 1 && !fp8_unit);
       if ((rc = launch_emit(&e, 1, 0, st))) return rc;
     }
     WaProduct& q = g.q[n_q++];
-    q.kind = f == 0 ? WA_INT8 : (fp8_unit ? WA_FP8 : WA_GRID_BF16);
+    q.kind = f == 0 ? WA_INT8 : (fp8_unit ? WA_FP8 : WA_GRID_FP8);
     q.x = a.xq[f];
     q.w = a.wq[f];
     q.sx = a.xrec.scale[slot];

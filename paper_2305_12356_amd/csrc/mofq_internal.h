@@ -59,8 +59,7 @@ struct SweepParams {
   // per-tensor (INT8, FP8-E4M3) pair with one clip ratio only: the scoring pass also writes
   // the quantized tensor in both formats (dense rows), saving two further reads of the input
   uint8_t* emit_i8;         // int8 codes, or nullptr
-  void* emit_f8;            // e4m3 codes (1 byte) or grid values as bf16 (2 bytes)
-  int32_t emit_f8_as_bf16;
+  uint8_t* emit_f8;         // e4m3 codes
   // per-channel pair of two different formats (bf16 input) with one clip ratio only: the pass
   // also writes the grid values of format slot f as bf16, dense [rows][cols], to emit_grid[f]
   // (emit_grid_fp8, 4-bit formats: as e4m3 codes, a byte each, at grid_fp8_at() in rows of 2 * cols bytes; emit_grid[f] is the

@@ -35,8 +35,7 @@ struct SweepArgs {
   int32_t n_blocks;  // per-tensor: blocks of the partial passes
   int32_t k0;                // per-tensor: first clip candidate of this scoring pass
   uint8_t* emit_i8;          // per-tensor 8-bit pair: also write the codes (see SweepParams)
-  void* emit_f8;
-  int32_t emit_f8_as_bf16;
+  uint8_t* emit_f8;
   int32_t emit_grid_fp8;
   uint16_t* emit_grid[kMaxFmt];   // per-channel single-candidate pair: grid values as bf16 or e4m3 codes (see SweepParams)
   AheadCodes ahead;
@@ -991,7 +990,7 @@ __global__ __launch_bounds__(256) void tensor_score_kernel(const SweepArgs a) {
 
 // Per-tensor (INT8, FP8-E4M3) pair at one clip ratio, as the weight-activation path uses
 // it: the same partial errors as tensor_score_kernel, and in the same pass the int8 codes
-// and the E4M3 codes (or their grid values as bf16) of every element, so that the operands
+// and the E4M3 codes of every element, so that the operands
 // of the layer-output products cost one read of the tensor instead of three.
 template <typename In>
 __global__ __launch_bounds__(256) void tensor_score_emit8_kernel(const SweepArgs a) {
@@ -1014,7 +1013,6 @@ __global__ __launch_bounds__(256) void tensor_score_emit8_kernel(const SweepArgs
     L::load(static_cast<const typename L::elem*>(a.w) + row * a.ld + col, v);
     uint32_t wi[2] = {0u, 0u};
     int wf[2] = {0, 0};
-    u32x4 gb;
 #pragma unroll
     for (int i = 0; i < 8; i += 2) {
       // INT8
@@ -1030,7 +1028,6 @@ __global__ __launch_bounds__(256) void tensor_score_emit8_kernel(const SweepArgs
                                                     med3(v[i + 1] * iB, -448.0f, 448.0f), 0, false);
       const f32x2 g = __builtin_amdgcn_cvt_pk_f32_fp8(p, false);
       wf[i >> 2] |= (p & 0xFFFF) << (16 * ((i >> 1) & 1));
-      gb[i >> 1] = (f2u(g[0]) >> 16) | (f2u(g[1]) & 0xFFFF0000u);
       const double e0 = __builtin_fma(-static_cast<double>(g[0]), sBd, static_cast<double>(v[i]));
       const double e1 = __builtin_fma(-static_cast<double>(g[1]), sBd, static_cast<double>(v[i + 1]));
       accB = __builtin_fma(e0, e0, accB);
@@ -1041,14 +1038,10 @@ __global__ __launch_bounds__(256) void tensor_score_emit8_kernel(const SweepArgs
     oi[0] = wi[0];
     oi[1] = wi[1];
     reinterpret_cast<u32x2*>(a.emit_i8)[e8] = oi;
-    if (a.emit_f8_as_bf16) {
-      reinterpret_cast<u32x4*>(a.emit_f8)[e8] = gb;
-    } else {
-      u32x2 of;
-      of[0] = static_cast<uint32_t>(wf[0]);
-      of[1] = static_cast<uint32_t>(wf[1]);
-      reinterpret_cast<u32x2*>(a.emit_f8)[e8] = of;
-    }
+    u32x2 of;
+    of[0] = static_cast<uint32_t>(wf[0]);
+    of[1] = static_cast<uint32_t>(wf[1]);
+    reinterpret_cast<u32x2*>(a.emit_f8)[e8] = of;
   }
   accA = wave_sum(accA);
   accB = wave_sum(accB);
@@ -1275,7 +1268,6 @@ int launch_sweep(const SweepParams& p, hipStream_t st) {
     if (p.gran != MOFQ_PER_TENSOR) return MOFQ_ERR_UNSUPPORTED;
     a.emit_i8 = p.emit_i8;
     a.emit_f8 = p.emit_f8;
-    a.emit_f8_as_bf16 = p.emit_f8_as_bf16;
   }
   if (p.emit_grid[0] || p.emit_grid[1]) {
     if (p.gran != MOFQ_PER_CHANNEL || p.n_clip != 1 || p.n_fmt != 2) return MOFQ_ERR_UNSUPPORTED;

@@ -34,7 +34,7 @@
 //   WA_GRID_BF16 : grid values stored as bf16 (exact for 4-bit and 8-bit grids) on the
 //                  bf16 matrix cores, products exact, fp32 accumulation -- the products
 //                  of the weight-only layer-output metric, where the "quantized" input is
-//                  the 16-bit input itself (scale 1), and of scales per channel;
+//                  the 16-bit input itself (scale 1);
 //   WA_GRID_FP8  : the same product from e4m3 codes, widened in registers: half the bytes
 //                  deposited, kept in LDS and read as fragments, and no bf16 copies of the
 //                  operands to write.  It meets the 1e-5 tolerance on the error sum, which
@@ -222,10 +222,11 @@ __global__ __launch_bounds__(T::NW * 64) __attribute__((amdgpu_waves_per_eu(T::P
   const int sw = swz(r);                                   // same for all of the lane's rows (multiples of 32 apart)
   const int row_a = (wm * WM + r) * ROW_B;                 // + i * 32 * ROW_B
   const int row_b = (TM + wn * WN + r) * ROW_B;            // + j * 32 * ROW_B
-  int ch_k[CH / 2], ch_f[CH / 2];
+  int ch_k[CH / 2], ch_h[CH / 2], ch_f[CH / 2];
 #pragma unroll
   for (int q = 0; q < CH / 2; ++q) {
     ch_k[q] = ((2 * q + g) ^ sw) * 16;                       // K slice q of a stage, 16 bytes per lane
+    ch_h[q] = ((4 * (q / 2) + 2 * g + q % 2) ^ sw) * 16;     // 16-bit elements: the columns that half a slice of widened codes holds
     ch_f[q] = ((4 * (q >> 1) + 2 * g + (q & 1)) ^ sw) * 16;  // fp8 instruction q/2: 32 bytes per lane, half q%2
   }
 
@@ -243,16 +244,20 @@ __global__ __launch_bounds__(T::NW * 64) __attribute__((amdgpu_waves_per_eu(T::P
   const char* dep_x = nullptr;
   const char* dep_w = nullptr;
   int dep_left = 0, dep_half = 0, dep_seg = -1;
-  // A piece: some stages of one product, with the side part behind its last ones.
-  int mine = SEG_REF, first_stage = 0, end_stage = 0;
+  // A piece: some stages of one product, with the side part behind its last ones.  (Widened codes': the columns of the reference
+  // product's piece, which may begin and end at half a line.)
+  int mine = SEG_REF, piece_byte = 0, piece_stages = 0, piece_half = 0;
   bool last_piece = false;
   if constexpr (PIECES) {
     const int q = (piece >= a.piece0[1]) + (piece >= a.piece0[2]);
     mine = q == 0 ? static_cast<int>(SEG_REF) : SEG_Q + 2 * (q - 1);
     const int n = a.piece0[q + 1] - a.piece0[q], i = piece - a.piece0[q];
-    first_stage = a.seg[mine].stages * i / n;
-    end_stage = a.seg[mine].stages * (i + 1) / n;
     last_piece = i == n - 1;
+    const bool widened_codes = (KIND1 == K_G8 && q == 1) || (KIND2 == K_G8 && q == 2);
+    const int total = a.seg[widened_codes ? static_cast<int>(SEG_REF) : mine].stages, first = total * i / n, count = total * (i + 1) / n - first;
+    piece_byte = first * (widened_codes ? ROW_B / 2 : ROW_B);
+    piece_stages = widened_codes ? (count + 1) / 2 : count;
+    piece_half = widened_codes ? count % 2 : a.seg[mine].half && last_piece;
     dep_seg = mine - 1;
   }
   const int end_seg = PIECES ? (mine != SEG_REF && last_piece ? mine + 2 : mine + 1) : static_cast<int>(N_SEG);
@@ -274,10 +279,10 @@ __global__ __launch_bounds__(T::NW * 64) __attribute__((amdgpu_waves_per_eu(T::P
     dep_half = sg.half;
     if constexpr (PIECES) {
       if (s == mine) {
-        dep_x += first_stage * ROW_B;
-        dep_w += first_stage * ROW_B;
-        dep_left = end_stage - first_stage;
-        dep_half = sg.half && last_piece;
+        dep_x += piece_byte;
+        dep_w += piece_byte;
+        dep_left = piece_stages;
+        dep_half = piece_half;
       }
     }
 #pragma unroll
@@ -333,7 +338,7 @@ __global__ __launch_bounds__(T::NW * 64) __attribute__((amdgpu_waves_per_eu(T::P
         const i32x4 lo = *reinterpret_cast<const i32x4*>(row + ch_f[2 * gi]), hi = *reinterpret_cast<const i32x4*>(row + ch_f[2 * gi + 1]);
         return __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
       } else {
-        return *reinterpret_cast<const i32x4*>(row + ch_k[gi]);
+        return *reinterpret_cast<const i32x4*>(row + (EIGHT ? ch_k[gi] : ch_h[gi]));
       }
     };
     auto load_group = [&](const unsigned char* st, int gi, frag_t (&f)[TI + TJ]) {
@@ -343,9 +348,10 @@ __global__ __launch_bounds__(T::NW * 64) __attribute__((amdgpu_waves_per_eu(T::P
       for (int j = 0; j < TJ; ++j) f[TI + j] = load_frag(st + row_b + j * 32 * ROW_B, gi);
     };
     // E4M3 codes for the bf16 matrix cores (grid values have 4 significant bits: the same operands as if they had been stored as
-    // bf16).  A lane's 16 codes of a fragment are the operands of two instructions, 8 each, the same k of A and B.  They are
-    // widened (4 conversions to 8 codes) between the matrix instructions before: the second half of a group's during its first half,
-    // the next group's first half (of `next`) during its second.
+    // bf16).  A lane's 16 codes of a fragment are the operands of two instructions, 8 each; the 16-bit products take their columns in the
+    // same order (ch_h), so that values on the grid leave an error of exactly 0.  (Exchanging codes between lanes for the other
+    // order costs 2 to 4 % of a call.)  They are widened (4 conversions to 8 codes) between the matrix instructions before: the second
+    // half of a group's during its first half, the next group's first half (of `next`) during its second.
     bf16x8 wide[2][TI + TJ];
     auto widen = [](const auto& v, int h) { return __builtin_bit_cast(bf16x8, widened(v[2 * h], v[2 * h + 1])); };
     // The matrix instructions of one group, with the deposits [lo, hi) of the current stage
@@ -524,14 +530,13 @@ __global__ __launch_bounds__(T::NW * 64) __attribute__((amdgpu_waves_per_eu(T::P
             to[((i * TJ + j) * 4 + q) * 64] = __builtin_bit_cast(f32x4, v);
           }
     };
-    const int stages = end_stage - first_stage;
     auto run = [&](auto kind_c) {
       constexpr int KIND = decltype(kind_c)::value;
       if constexpr (KIND != WA_NONE) {
         using acc_t = std::conditional_t<KIND == K_I8, i32x16, f32x16>;
         acc_t acc[TI][TJ];
         clear(acc);
-        product(kind_c, acc, stages, last_piece && a.seg[mine].half != 0);
+        product(kind_c, acc, piece_stages, piece_half != 0);
         if constexpr (KIND == K_F8) product(std::integral_constant<int, K_GRID>{}, acc, last_piece ? a.seg[mine + 1].stages : 0, false);
         store(acc);
       }
@@ -651,8 +656,7 @@ __global__ __launch_bounds__(T::NW * 64) void wa_pieces_kernel(const GemmBatch<N
 // 11008 x 8192 913 instead of 885).  Measured, layer selection with INT4 and E2M1, us, one product after the other -> here:
 // 2048 x 11008 x 4096 (tokens x rows x columns) 516 -> 467, 1536 x 11008 x 8192 1009 -> 885, 2048 x 4096 x 4096 186 -> 167, 1024 x 11008 x 4096
 // 349 -> 314, 512 x 4096 x 4096 100 -> 82, 777 x 3000 x 5056 118 -> 109, 64 x 4096 x 1024 39.8 -> 35.  Bound by power and LDS as
-// wa_gemm_kernel.  Medium tiles have eight waves of 64x32 (four of 64x64 are 1 % slower).  The sums are those of
-// wa_gemm_kernel bit for bit.
+// wa_gemm_kernel.  Medium tiles have eight waves of 64x32 (four of 64x64 are 1 % slower).
 //
 // PAIR: two 4-bit formats' grid values come as e4m3 codes in one array (grid_fp8_at) and are widened to bf16, exactly, while the product
 // before runs: 512 rows a step instead of 640, fragments of 6 x 16 bytes for 12 matrix instructions instead of 8, and half the
@@ -941,13 +945,13 @@ int gemm_args(const WaGemmParams& p, GemmArgs& a) {
   a.part[2] = p.part_p;
   return MOFQ_OK;
 }
-// Products in pieces of up to `run` stages: returns their number.
-int set_pieces(GemmArgs& a, int run, void* partial) {
+// Products in pieces of up to `run` stages (of widened codes as many as the reference product's): returns their number.
+int set_pieces(const WaGemmParams& p, GemmArgs& a, int run) {
   for (int q = 0; q < 3; ++q) {
-    const int stages = q == 0 ? a.seg[SEG_REF].stages : a.seg[SEG_Q + 2 * (q - 1)].stages;
+    const int stages = q == 0 || p.q[q - 1].kind == WA_GRID_FP8 ? a.seg[SEG_REF].stages : a.seg[SEG_Q + 2 * (q - 1)].stages;
     a.piece0[q + 1] = a.piece0[q] + (stages + run - 1) / run;
   }
-  a.partial = static_cast<float*>(partial);
+  a.partial = static_cast<float*>(p.partial);
   return a.piece0[3];
 }
 template <typename T> void set_tiles(const WaGemmParams& p, GemmArgs& a) {
@@ -993,7 +997,7 @@ int launch_wa_gemm(const WaGemmParams& p, hipStream_t st) {
       if (plan.tile == WaPlan::kWide) {
         tiled(Small{}, wa_gemm_kernel<Small, K1, K2, false, true, 1>);
       } else if (plan.run) {
-        tiled(Small{}, wa_gemm_kernel<Small, K1, K2, true, false, 1>, set_pieces(a, plan.run, p.partial));
+        tiled(Small{}, wa_gemm_kernel<Small, K1, K2, true, false, 1>, set_pieces(p, a, plan.run));
         hipLaunchKernelGGL((wa_pieces_kernel<Small, K1, K2, 1>), dim3(static_cast<unsigned>(plan.blocks)), dim3(Small::NW * 64), 0, st, batch);
       } else if constexpr (!SHARED) {
         switch (plan.tile) {
@@ -1007,8 +1011,8 @@ int launch_wa_gemm(const WaGemmParams& p, hipStream_t st) {
   };
 #define MOFQ_WA(A, B) \
   if (k1 == (A) && k2 == (B)) return launch(std::integral_constant<int, A>{}, std::integral_constant<int, B>{});
-  MOFQ_WA(WA_INT8, WA_GRID_BF16) MOFQ_WA(WA_INT8, WA_GRID_FP8) MOFQ_WA(WA_INT8, WA_FP8) MOFQ_WA(WA_INT8, WA_NONE)
-  MOFQ_WA(WA_GRID_BF16, WA_NONE) MOFQ_WA(WA_FP8, WA_NONE) MOFQ_WA(WA_GRID_BF16, WA_GRID_BF16)
+  MOFQ_WA(WA_INT8, WA_GRID_FP8) MOFQ_WA(WA_INT8, WA_FP8) MOFQ_WA(WA_INT8, WA_NONE)
+  MOFQ_WA(WA_GRID_BF16, WA_NONE) MOFQ_WA(WA_GRID_FP8, WA_NONE) MOFQ_WA(WA_FP8, WA_NONE) MOFQ_WA(WA_GRID_BF16, WA_GRID_BF16)
   MOFQ_WA(WA_PAIR_FP8, WA_PAIR_FP8)
 #undef MOFQ_WA
   return MOFQ_ERR_UNSUPPORTED;
@@ -1038,7 +1042,7 @@ int launch_wa_gemms(const WaGemmParams* p, int n, hipStream_t st) {
       const int rc = gemm_args(p[list[i]], batch.a[i]);
       if (rc != MOFQ_OK) return rc;
       const WaGemmParams& q = p[list[i]];
-      const int n_pieces = pieces ? set_pieces(batch.a[i], wa_gemm_plan(q.M, q.N, q.K, q.ldx, q.ldw).run, q.partial) : 1;
+      const int n_pieces = pieces ? set_pieces(q, batch.a[i], wa_gemm_plan(q.M, q.N, q.K, q.ldx, q.ldw).run) : 1;
       switch (tile) {
         case WaPlan::kLarge: set_tiles<Large>(p[list[i]], batch.a[i]); break;
         case WaPlan::kMedium: set_tiles<Medium>(p[list[i]], batch.a[i]); break;

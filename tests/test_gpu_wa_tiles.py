@@ -68,6 +68,21 @@ def test_exact_products_widen_every_code(mq, shape):
     assert torch.equal(w_out[0].codes.view(-1), w.cpu().float().to(torch.float8_e4m3fn).view(torch.uint8).view(-1).to(DEV))
 
 
+@pytest.mark.parametrize("name", list(SHAPES))
+def test_exact_products_of_grid_values_have_no_error(mq, name):
+    """Dense operands on E4M3's grid: the reference and the E4M3 product add up the same numbers in the same order in every
+    tiling and piece, so the error is exactly 0 and an earlier candidate without error stays the choice."""
+    M, N, K = SHAPES[name]
+    g = torch.Generator().manual_seed(K + 1)
+    grid = torch.arange(256, dtype=torch.uint8).view(torch.float8_e4m3fn).float()
+    grid = grid[grid.isfinite()]
+    x, w = grid[torch.randint(len(grid), (M, K), generator=g)], grid[torch.randint(len(grid), (N, K), generator=g)]
+    x[0, 0] = w[0, 0] = 448.0
+    x, w = x.to(torch.bfloat16).to(DEV), w.to(torch.bfloat16).to(DEV)
+    r, _, _ = layers.run_single(mq, [w], [x], [I8, FP8], mq.ERR_LAYER_OUTPUT, mq.Cfg(mq.PER_TENSOR, mi.clip_ratios(1)))
+    assert r[0].err[1] == 0.0 and r[0].err[0] > 0.0 and r[0].best == 1
+
+
 @pytest.mark.parametrize("apart", [0, 64])
 def test_layers_with_one_code_buffer(mq, apart):
     """Layers whose weights' codes go to the same memory, or to memory that overlaps: what is written there is not
