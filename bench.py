@@ -58,7 +58,7 @@ SEARCH_KERNEL_COUNTERS = {
     "write_bytes_per_row": 896.0 * 1024 / 4096,                      # WRITE_SIZE: records alone
     "write_bytes_per_row_with_codes": 104104.0 * 1024 / 46592,
     "rows_with_codes": 8192,
-    "valu_instr_per_wave": 1008.0,                                   # SQ_INSTS_VALU / SQ_WAVES, 4096-column instance
+    "valu_instr_per_wave": 904.0,                                    # SQ_INSTS_VALU / SQ_WAVES, 4096-column instance
 }
 # sweep_group_bits_kernel, fp16 groups of 128, 50 ratios: a wave takes four groups (a mean over this recipe: how many gaps
 # of the coarse search are looked at depends on the data)
