@@ -1090,17 +1090,6 @@ int batch_length(int n_layers, const mofq_tensor_t* w, int i0, int cus) {
   return nb;
 }
 
-// Scales per group: every tensor is a search launch of its own, so the last batch is emitted in two parts, the first one's
-// emission beside the second one's searches, which take ten times as long per byte.  The second part holds an eighth of the
-// batch or the last tensor.  A 7B block, groups of 128, 50 ratios 1132 -> 1085 us.
-int first_part(const mofq_tensor_t* w, int nb) {
-  int64_t total = 0, tail = 0;
-  for (int j = 0; j < nb; ++j) total += w[j].rows * w[j].cols;
-  int n = nb;
-  while (n > 1 && 8 * tail < total) { --n; tail += w[n].rows * w[n].cols; }
-  return n;
-}
-
 // Tensors of a batch with one row length and dtype share a search launch (up to
 // kSweepGroupMax of them, adjacent or not: a larger launch fills the device better than
 // several small ones, and nothing orders the searches inside a batch).  first[j] (j < nb)
@@ -1118,6 +1107,17 @@ void plan_search_groups(const mofq_tensor_t* w, int nb, const int32_t* cand, int
         ++n;
       }
   }
+}
+
+// Scales per group: every tensor is a search launch of its own, so the last batch is emitted in two parts, the first one's
+// emission beside the second one's searches, which take ten times as long per byte.  The second part holds an eighth of the
+// batch or the last tensor, in the order of the searches (`order`: places in w).  A 7B block, groups of 128, 50 ratios 1132 -> 1085 us.
+int first_part(const mofq_tensor_t* w, const int* order, int nb) {
+  int64_t total = 0, tail = 0;
+  for (int j = 0; j < nb; ++j) total += w[j].rows * w[j].cols;
+  int n = nb;
+  while (n > 1 && 8 * tail < total) { --n; tail += w[order[n]].rows * w[order[n]].cols; }
+  return n;
 }
 
 }  // namespace
@@ -1222,15 +1222,9 @@ int mofq_select_layers_timed(int32_t n_layers, const mofq_tensor_t* w, const int
   };
 
   char* base = static_cast<char*>(ws);
-  int batch_end = 0;
   for (int i0 = 0, nb = 0; i0 < n_layers; i0 += nb) {
-    nb = i0 == batch_end ? batch_length(n_layers, w, i0, cus) : batch_end - i0;
-    if (i0 == batch_end) {
-      batch_end += nb;
-      if (sw.two && w_cfg->gran == MOFQ_PER_GROUP && batch_end == n_layers) nb = first_part(w + i0, nb);
-    }
+    nb = batch_length(n_layers, w, i0, cus);
     WOnlyWs slot[kEmitBatch];
-    // 1. the searches, back to back; the tensors of one row length share a launch
     for (int j = 0; j < nb; ++j) {
       const int64_t units = mofq_num_units(w[i0 + j].rows, w[i0 + j].cols, w_cfg->gran, w_cfg->group_size);
       slot[j] = carve_w_only(base, units, n_candidates, w_cfg->gran, w_cfg->n_clip);
@@ -1238,6 +1232,10 @@ int mofq_select_layers_timed(int32_t n_layers, const mofq_tensor_t* w, const int
     }
     int first[kEmitBatch];
     plan_search_groups(w + i0, nb, candidates, n_candidates, first);
+    int order[kEmitBatch], n_order = 0;   // of the searches: group by group
+    for (int j = 0; j < nb; ++j)
+      for (int k = j; first[j] == j && k < nb; ++k)
+        if (first[k] == j) order[n_order++] = k;
     const bool one_launch = one_sweep_launch(candidates, n_candidates);
     Ahead ahead[kEmitBatch];
     double* tally[kEmitBatch];
@@ -1253,65 +1251,68 @@ int mofq_select_layers_timed(int32_t n_layers, const mofq_tensor_t* w, const int
     const bool two = n_candidates == 2;   // else the codes written ahead are final
     auto ahead_to = [&](int j) { return AheadTo{ahead[j] != Ahead::kNo ? w_out[i0 + j].codes : nullptr, ahead[j] == Ahead::kTallied}; };
     if (n_tallied && two && (rc = launch_clear(tally, n_tallied, st))) return join(rc);
-    for (int j = 0; j < nb; ++j) {
-      if (first[j] != j) continue;
-      // A launch over several tensors exists only where the whole candidate list is one
-      // launch (plan_search_groups joins nothing otherwise); longer lists go tensor by tensor
-      // through sweep_candidates, which splits them into launches of at most two formats.
-      SweepParams sp[kSweepGroupMax];
-      int g = 0, last = j;
-      for (int k = j; k < nb; ++k)
-        if (first[k] == j) {
-          if (one_launch && (rc = sweep_params(&w[i0 + k], candidates, 0, n_candidates, w_cfg, slot[k], ahead_to(k), &sp[g])))
+    const int head = sw.two && w_cfg->gran == MOFQ_PER_GROUP && i0 + nb == n_layers ? first_part(w + i0, order, nb) : nb;
+    for (int o0 = 0, o1 = head; o0 < nb; o0 = o1, o1 = nb) {   // the batch, or its two parts
+      // 1. the searches, back to back; the tensors of one row length share a launch
+      for (int o = o0, end = 0; o < o1; o = end) {
+        // order[o .. end): one group's, all of them but where the group lies in both parts (whose tensors are launches of their own)
+        const int j = first[order[o]];
+        for (end = o + 1; end < o1 && first[order[end]] == j;) ++end;
+        const bool begins = order[o] == j, ends = end == nb || first[order[end]] != j;
+        // A launch over several tensors exists only where the whole candidate list is one
+        // launch (plan_search_groups joins nothing otherwise); longer lists go tensor by tensor
+        // through sweep_candidates, which splits them into launches of at most two formats.
+        SweepParams sp[kSweepGroupMax];
+        const int g = end - o;
+        for (int k = 0; one_launch && k < g; ++k)
+          if ((rc = sweep_params(&w[i0 + order[o + k]], candidates, 0, n_candidates, w_cfg, slot[order[o + k]], ahead_to(order[o + k]), &sp[k])))
             return join(rc);
-          ++g;
-          last = k;
+        if (begins && ev_begin && hipEventRecord(static_cast<hipEvent_t>(ev_begin[i0 + j]), st) != hipSuccess) return join(MOFQ_ERR_HIP);
+        // one scale per tensor: nothing to share, the whole of mofq_select_layer per tensor (its codes while its
+        // elements may still be in cache, unless events ask for the scoring alone)
+        auto tensor = [&](int k) {
+          TensorParams p = tensor_params(&w[i0 + k], candidates, n_candidates, w_cfg, slot[k]);
+          p.out = w_out[i0 + k];
+          p.result = &results[i0 + k];
+          return p;
+        };
+        if (one_scale(w_cfg)) {
+          for (int k = o; k < end; ++k) {
+            if ((rc = launch_tensor_scores(tensor(order[k]), st))) return join(rc);
+            if (!ev_end && (rc = launch_tensor_pick(tensor(order[k]), st))) return join(rc);
+          }
+        } else if (g > 1) {
+          if (!one_launch) return join(MOFQ_ERR_INVALID_ARG);   // cannot happen: see plan_search_groups
+          if ((rc = launch_sweep_group(sp, g, st))) return join(rc);
+        } else {
+          if ((rc = sweep_candidates(&w[i0 + order[o]], candidates, n_candidates, w_cfg, slot[order[o]], st, nullptr, ahead_to(order[o]))))
+            return join(rc);
         }
-      if (ev_begin && hipEventRecord(static_cast<hipEvent_t>(ev_begin[i0 + j]), st) != hipSuccess) return join(MOFQ_ERR_HIP);
-      // one scale per tensor: nothing to share, the whole of mofq_select_layer per tensor (its codes while its
-      // elements may still be in cache, unless events ask for the scoring alone)
-      auto tensor = [&](int k) {
-        TensorParams p = tensor_params(&w[i0 + k], candidates, n_candidates, w_cfg, slot[k]);
-        p.out = w_out[i0 + k];
-        p.result = &results[i0 + k];
-        return p;
-      };
-      if (one_scale(w_cfg)) {
-        for (int k = j; k <= last; ++k) {
-          if (first[k] != j) continue;
-          if ((rc = launch_tensor_scores(tensor(k), st))) return join(rc);
-          if (!ev_end && (rc = launch_tensor_pick(tensor(k), st))) return join(rc);
-        }
-      } else if (g > 1) {
-        if (!one_launch) return join(MOFQ_ERR_INVALID_ARG);   // cannot happen: see plan_search_groups
-        if ((rc = launch_sweep_group(sp, g, st))) return join(rc);
-      } else {
-        if ((rc = sweep_candidates(&w[i0 + j], candidates, n_candidates, w_cfg, slot[j], st, nullptr, ahead_to(j))))
-          return join(rc);
+        if (ends && ev_end && hipEventRecord(static_cast<hipEvent_t>(ev_end[i0 + order[end - 1]]), st) != hipSuccess) return join(MOFQ_ERR_HIP);
+        if (ev_end && one_scale(w_cfg))
+          for (int k = o; k < end; ++k)
+            if ((rc = launch_tensor_pick(tensor(order[k]), st))) return join(rc);
       }
-      if (ev_end && hipEventRecord(static_cast<hipEvent_t>(ev_end[i0 + last]), st) != hipSuccess) return join(MOFQ_ERR_HIP);
-      if (ev_end && one_scale(w_cfg))
-        for (int k = j; k <= last; ++k)
-          if (first[k] == j && (rc = launch_tensor_pick(tensor(k), st))) return join(rc);
-    }
-    if (i0 + nb >= n_layers) emit_cap = 0;   // nothing runs beside the last batch's emission
-    // 2. on the second stream, once the batch's searches are done: reduce + select, the codes of
-    //    the winners and the per-unit outputs, one launch for the tensors of one dtype.  The next
-    //    batch's searches follow on the caller's stream meanwhile; every tensor has its own
-    //    workspace.
-    if (one_scale(w_cfg)) continue;
-    if ((rc = sw.fork())) return join(rc);
-    for (int dtype : {MOFQ_F32, MOFQ_F16, MOFQ_BF16}) {
-      EmitParams e[kEmitBatch], f[kEmitBatch];
-      int n = 0, m = 0;
-      for (int j = 0; j < nb; ++j)
-        if (w[i0 + j].dtype == dtype) {
+      if (i0 + nb >= n_layers) emit_cap = 0;   // nothing runs beside the last emission
+      // 2. on the second stream, once the searches are done: reduce + select, the codes of
+      //    the winners and the per-unit outputs, one launch for the tensors of one dtype.  The next
+      //    searches follow on the caller's stream meanwhile; every tensor has its own
+      //    workspace.
+      if (one_scale(w_cfg)) continue;
+      if ((rc = sw.fork())) return join(rc);
+      for (int dtype : {MOFQ_F32, MOFQ_F16, MOFQ_BF16}) {
+        EmitParams e[kEmitBatch], f[kEmitBatch];
+        int n = 0, m = 0;
+        for (int o = o0; o < o1; ++o) {
+          const int j = order[o];
+          if (w[i0 + j].dtype != dtype) continue;
           EmitParams& q = ahead[j] != Ahead::kNo ? f[m++] : e[n++];
           q = emit_params(i0 + j, slot[j]);
           if (ahead[j] != Ahead::kNo && two) q.tag = slot[j].tag;
         }
-      if (m && (rc = launch_fixup(f, m, emit_cap, st2))) return join(rc);
-      if (n && (rc = launch_emit(e, n, emit_cap, st2))) return join(rc);
+        if (m && (rc = launch_fixup(f, m, emit_cap, st2))) return join(rc);
+        if (n && (rc = launch_emit(e, n, emit_cap, st2))) return join(rc);
+      }
     }
   }
   return join(MOFQ_OK);

@@ -1,6 +1,8 @@
 """The batched weight-only select (mofq_select_layers) must give, tensor by tensor, exactly
 what mofq_select_layer gives (which the other tests hold to the oracle), and is also
 compared with the oracle directly on a few tensors."""
+import ctypes as C
+
 import numpy as np
 import pytest
 import torch
@@ -179,6 +181,37 @@ def test_events_enclose_the_scoring_alone(mq):
     assert torch.equal(res, plain)
     for o, q in zip(outs, want):
         assert torch.equal(o.codes, q.codes) and torch.equal(o.scales, q.scales) and torch.equal(o.unit_err, q.unit_err)
+
+
+@pytest.mark.parametrize("gran,group", [(orc.PER_GROUP, 128), (orc.PER_CHANNEL, 0)])
+@pytest.mark.parametrize("shapes", [
+    [(256, 1024)] * 4,                                          # one group, emitted in two parts
+    [(64, 1024), (100, 2048), (64, 1024), (200, 2048), (30, 1024)],   # groups that interleave
+])
+def test_only_the_events_of_the_search_groups(mq, gran, group, shapes):
+    """ev_begin of a group's first tensor and ev_end of its last one are recorded; the others may be NULL."""
+    ws_ = [mi.llama_like_weight(r, c, seed=40 + i, device=DEV) for i, (r, c) in enumerate(shapes)]
+    cands, cfg = [mq.INT4, mq.FP4_E2M1], mq.Cfg(gran, mi.clip_ratios(12), group, True)
+    outs = [mq.alloc_qbuffers(r, c, 4, cfg, DEV) for r, c in shapes]
+    batch = mq.LayerBatch(ws_, outs)
+    first = batch.search_groups(cands)
+    last = {f: i for i, f in enumerate(first)}
+    e0 = {f: torch.cuda.Event(enable_timing=True) for f in last}
+    e1 = {f: torch.cuda.Event(enable_timing=True) for f in last}
+    handles = lambda at: (C.c_void_p * batch.n)(*[mq._event_handle(at[i]).value if i in at else None for i in range(batch.n)])  # noqa: E731
+    results = mq.alloc_result(DEV, len(shapes))
+    ws = torch.empty(batch.workspace_bytes(2, cfg), dtype=torch.uint8, device=DEV)
+    side = torch.cuda.Stream()
+    print(f"[case] events of the groups alone, {gran} {shapes}", flush=True)
+    rc = mq._lib.mofq_select_layers_timed(batch.n, batch.w, (C.c_int32 * 2)(*cands), 2, C.byref(cfg.c), batch.out, mq._ptr(results), mq._ptr(ws),
+                                          ws.nbytes, mq._stream_handle(None), side.cuda_stream, handles(e0), handles({last[f]: e for f, e in e1.items()}))
+    assert rc == 0
+    torch.cuda.synchronize()
+    assert len(last) < len(shapes) and all(e0[f].elapsed_time(e1[f]) > 0.0 for f in last)
+    for r, o, w in zip(mq.read_results(results), outs, ws_):
+        ref_out, ref = _single(mq, w, cands, cfg, 4)
+        assert r.best == ref.best and list(r.err) == list(ref.err)
+        assert torch.equal(o.codes, ref_out.codes) and torch.equal(o.scales, ref_out.scales) and torch.equal(o.unit_err, ref_out.unit_err)
 
 
 def test_current_stream_handle(mq, monkeypatch):
