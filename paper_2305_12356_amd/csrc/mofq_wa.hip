@@ -226,7 +226,8 @@ __global__ __launch_bounds__(T::NW * 64) __attribute__((amdgpu_waves_per_eu(T::P
 #pragma unroll
   for (int q = 0; q < CH / 2; ++q) {
     ch_k[q] = ((2 * q + g) ^ sw) * 16;                       // K slice q of a stage, 16 bytes per lane
-    ch_h[q] = ((4 * (q / 2) + 2 * g + q % 2) ^ sw) * 16;     // 16-bit elements: the columns that half a slice of widened codes holds
+    // 16-bit elements: the columns that half a slice of widened codes holds; in the weight-only metric's products as wa_gemm_shared_kernel
+    ch_h[q] = KIND1 == K_GRID ? ch_k[q] : ((4 * (q / 2) + 2 * g + q % 2) ^ sw) * 16;
     ch_f[q] = ((4 * (q >> 1) + 2 * g + (q & 1)) ^ sw) * 16;  // fp8 instruction q/2: 32 bytes per lane, half q%2
   }
 
@@ -646,9 +647,9 @@ __global__ __launch_bounds__(T::NW * 64) void wa_pieces_kernel(const GemmBatch<N
   }
 }
 
-// ---- three bf16 products that share X (weight-only layer output) ------------------------------------------
-// X W^T, X G1^T and X G2^T in one K loop: a stage holds one line of K of TM rows of X and of TN rows of W, G1 and G2
-// each, so X is deposited and its fragments are read once instead of three times: for a 256x128 tile 640 rows a step of 64
+// ---- bf16 products that share X (weight-only layer output) -------------------------------------------------
+// X W^T, X G1^T and X G2^T (of a format alone, NQ = 1, the first two) in one K loop: a stage holds one line of K of TM rows of X
+// and of TN rows of W, G1 and G2 each, so X is deposited and its fragments are read once instead of three times: for a 256x128 tile 640 rows a step of 64
 // of K instead of 1152, and 8 fragments for 12 matrix instructions instead of 12.  A lane of a 64x64 share then holds 192
 // accumulators, 247 registers in all, so two waves still fit a SIMD.  A stage of 80 KB (PAIR: 64) leaves room for two in LDS;
 // as a step lasts three times as long as one of wa_gemm_kernel, a stage has as long to arrive if its deposits are issued early in the
@@ -665,11 +666,17 @@ __global__ __launch_bounds__(T::NW * 64) void wa_pieces_kernel(const GemmBatch<N
 // the kernel), 1536 x 11008 x 8192 840 -> 797, 2048 x 4096 x 4096 161 -> 159, 1024 x 11008 x 4096 299 -> 250, 512 x 4096 x 4096 77 -> 71, 777 x 3000 x
 // 5056 106 -> 97, 64 x 4096 x 1024 34.2 -> 30.4.  The bf16 form serves 8-bit formats and scales with several ratios, whose
 // values leave the emission pass.
-template <int TM_, int TN_, int WM_, int WN_, bool PAIR_> struct SharedTile {
-  static constexpr bool PAIR = PAIR_;   // operands of the quantized products: one array of e4m3 codes, else two of bf16
+//
+// All forms add up a product in one order (wa_gemm_kernel's pieces of one too) and divide a tile among the same waves: a format's error
+// is the same number, bit for bit, with another candidate beside it and alone.  Alone (mofq_score), us, wa_gemm_kernel -> here: 2048 x
+// 11008 x 4096 354 -> 331, 2048 x 4096 x 4096 136 -> 127, 777 x 3000 x 5056 90.2 -> 92.4, 512 x 4096 x 4096 73.6 -> 67.4.
+template <int TM_, int TN_, int WM_, int WN_, int NQ_, bool PAIR_> struct SharedTile {
+  static constexpr int NQ = NQ_;        // quantized products
+  static constexpr bool PAIR = PAIR_;   // their operands: one array of e4m3 codes, else bf16
+  static constexpr int NB = PAIR_ ? 2 : 1 + NQ_;   // arrays beside X
   static constexpr int TM = TM_, TN = TN_, WM = WM_, WN = WN_;
   static constexpr int NW = (TM / WM) * (TN / WN);
-  static constexpr int STAGE = (TM + (PAIR ? 2 : 3) * TN) * ROW_B;
+  static constexpr int STAGE = (TM + NB * TN) * ROW_B;
   static constexpr int PER_CU = (160 * 1024) / (2 * STAGE);
   static constexpr int PER_SIMD = PER_CU * NW / 4;
 };
@@ -679,11 +686,12 @@ __global__ __launch_bounds__(T::NW * 64) __attribute__((amdgpu_waves_per_eu(T::P
   constexpr int TM = T::TM, TN = T::TN, WM = T::WM, WN = T::WN, NW = T::NW;
   constexpr int TI = WM / 32, TJ = WN / 32, STAGE = T::STAGE, STEP = NW * 8;
   constexpr bool PAIR = T::PAIR;
-  constexpr int NB = PAIR ? 2 : 3;                             // arrays beside X
+  constexpr int NB = T::NB, NP = 1 + T::NQ;                    // products
   constexpr int DX = TM / STEP, DW = TN / STEP, DEP = DX + NB * DW;   // deposits per wave per stage
-  constexpr int NG = CH / 2, NSUB = 3 * NG;                          // groups of 16 of K; a group of one product
-  constexpr int FIRST = PAIR ? DEP / 4 : DEP / 5, SPREAD = 4;                   // deposits issued behind the barrier; over how many parts the others go
+  constexpr int NG = CH / 2, NSUB = NP * NG;                         // groups of 16 of K; a group of one product
+  constexpr int FIRST = NB == 2 ? DEP / 4 : DEP / 5, SPREAD = 4;                   // deposits issued behind the barrier; over how many parts the others go
   static_assert(TM % STEP == 0 && TN % STEP == 0 && STEP % 16 == 0, "deposits");
+  static_assert(SPREAD < NSUB && (!PAIR || NP == 3), "parts of a step");
   __shared__ __attribute__((aligned(1024))) unsigned char s_buf[2 * STAGE];
 
   const uint32_t lds0 = static_cast<uint32_t>(reinterpret_cast<uintptr_t>((__attribute__((address_space(3))) unsigned char*)s_buf));
@@ -737,9 +745,9 @@ __global__ __launch_bounds__(T::NW * 64) __attribute__((amdgpu_waves_per_eu(T::P
       }
   };
 
-  f32x16 acc[3][TI][TJ];
+  f32x16 acc[NP][TI][TJ];
 #pragma unroll
-  for (int q = 0; q < 3; ++q)
+  for (int q = 0; q < NP; ++q)
 #pragma unroll
     for (int i = 0; i < TI; ++i)
 #pragma unroll
@@ -760,9 +768,9 @@ __global__ __launch_bounds__(T::NW * 64) __attribute__((amdgpu_waves_per_eu(T::P
 #pragma unroll
     for (int i = 0; i < TI; ++i) fa[gi & 1][i] = *reinterpret_cast<const i32x4*>(s_buf + buf + row_a + ch_k[gi] + i * 32 * ROW_B);
   };
-  auto load_b = [&](int buf, int sub) {   // sub = 3 * group + product
+  auto load_b = [&](int buf, int sub) {   // sub = NP * group + product
 #pragma unroll
-    for (int j = 0; j < TJ; ++j) fb[sub & 1][j] = *reinterpret_cast<const i32x4*>(s_buf + buf + row_b + ch_k[sub / 3] + (sub % 3 * TN + j * 32) * ROW_B);
+    for (int j = 0; j < TJ; ++j) fb[sub & 1][j] = *reinterpret_cast<const i32x4*>(s_buf + buf + row_b + ch_k[sub / NP] + (sub % NP * TN + j * 32) * ROW_B);
   };
   // PAIR: a group's 8 codes of each format, widened into fb while the product before runs
   const int row_q = (TM + TN + wn * WN + r) * ROW_B, half_q = ((g ^ (r >> 4)) & 1) * 8;
@@ -777,7 +785,7 @@ __global__ __launch_bounds__(T::NW * 64) __attribute__((amdgpu_waves_per_eu(T::P
   for (int k = 0; k < stages; ++k) {
 #pragma unroll
     for (int sub = 0; sub < NSUB; ++sub) {
-      const int gi = sub / 3, q = sub % 3;
+      const int gi = sub / NP, q = sub % NP;
       int lo = 0, hi = 0, buf = b1;
       if (sub < SPREAD) {
         lo = FIRST + sub * (DEP - FIRST) / SPREAD;
@@ -801,9 +809,9 @@ __global__ __launch_bounds__(T::NW * 64) __attribute__((amdgpu_waves_per_eu(T::P
           __builtin_amdgcn_sched_barrier(0);
           if (m == (TI * TJ > 1 ? 1 : 0)) {
             if (sub + 1 < NSUB) {
-              if (q == 2) load_a(b0, gi + 1);
-              if (!PAIR || q == 2) load_b(b0, sub + 1);
-              if (PAIR && q == 2) load_q(b0, gi + 1, 0);
+              if (q == NP - 1) load_a(b0, gi + 1);
+              if (!PAIR || q == NP - 1) load_b(b0, sub + 1);
+              if (PAIR && q == NP - 1) load_q(b0, gi + 1, 0);
             } else {
               load_a(b1, 0);
               load_b(b1, 0);
@@ -834,7 +842,7 @@ __global__ __launch_bounds__(T::NW * 64) __attribute__((amdgpu_waves_per_eu(T::P
     const int n = n0 + wn * WN + j * 32 + r;
     const bool col_ok = n < a.N;
     const int ns = a.w_per_channel && col_ok ? n : 0;
-    const double c0 = static_cast<double>(a.sw[0][ns]), c1 = static_cast<double>(a.sw[1][ns]);
+    const double c0 = static_cast<double>(a.sw[0][ns]), c1 = NP == 3 ? static_cast<double>(a.sw[1][ns]) : 0.0;
 #pragma unroll
     for (int i = 0; i < TI; ++i)
 #pragma unroll
@@ -842,9 +850,11 @@ __global__ __launch_bounds__(T::NW * 64) __attribute__((amdgpu_waves_per_eu(T::P
         const bool ok = col_ok && (i * 32 + 8 * (x / 4) + (x % 4)) < row_lim;
         const double y = ok ? static_cast<double>(acc[0][i][j][x]) : 0.0;
         const double d0 = __builtin_fma(-c0, ok ? static_cast<double>(acc[1][i][j][x]) : 0.0, y);
-        const double d1 = __builtin_fma(-c1, ok ? static_cast<double>(acc[2][i][j][x]) : 0.0, y);
         e[0] = __builtin_fma(d0, d0, e[0]);
-        e[1] = __builtin_fma(d1, d1, e[1]);
+        if constexpr (NP == 3) {
+          const double d1 = __builtin_fma(-c1, ok ? static_cast<double>(acc[2][i][j][x]) : 0.0, y);
+          e[1] = __builtin_fma(d1, d1, e[1]);
+        }
         p = __builtin_fma(y, y, p);
       }
   }
@@ -864,9 +874,9 @@ __global__ __launch_bounds__(T::NW * 64) __attribute__((amdgpu_waves_per_eu(T::P
 using Large = Tile<256, 128, 64, 64>;    // one workgroup per compute unit, two waves per SIMD
 using Medium = Tile<128, 128, 64, 64>;   // one, one wave per SIMD
 using Small = Tile<64, 64, 32, 32>;      // three
-template <bool PAIR> using SharedLarge = SharedTile<256, 128, 64, 64, PAIR>;
-template <bool PAIR> using SharedMedium = SharedTile<128, 128, 64, 32, PAIR>;
-template <bool PAIR> using SharedSmall = SharedTile<64, 64, 32, 32, PAIR>;
+template <int NQ, bool PAIR> using SharedLarge = SharedTile<256, 128, 64, 64, NQ, PAIR>;
+template <int NQ, bool PAIR> using SharedMedium = SharedTile<128, 128, 64, 32, NQ, PAIR>;
+template <int NQ, bool PAIR> using SharedSmall = SharedTile<64, 64, 32, 32, NQ, PAIR>;
 
 }  // namespace
 
@@ -980,15 +990,20 @@ int launch_wa_gemm(const WaGemmParams& p, hipStream_t st) {
       set_tiles<T>(p, a);
       hipLaunchKernelGGL(kernel, dim3(static_cast<unsigned>(plan.blocks)), dim3(T::NW * 64), 0, st, a);
     };
-    constexpr bool PAIR = K1 == WA_PAIR_FP8, SHARED = (K1 == WA_GRID_BF16 && K2 == WA_GRID_BF16) || PAIR;
-    if constexpr (SHARED) {   // all three products take the unquantized X
-      if (p.q[0].x != p.x || p.q[1].x != p.x || p.ldx != p.K || p.q[0].sx || p.q[1].sx) return static_cast<int>(MOFQ_ERR_UNSUPPORTED);
+    constexpr bool PAIR = K1 == WA_PAIR_FP8, SHARED = K1 == WA_GRID_BF16 || PAIR;
+    if constexpr (SHARED) {   // all products take the unquantized X
+      constexpr int NQ = K2 == WA_NONE ? 1 : 2;
+      for (int i = 0; i < NQ; ++i)
+        if (p.q[i].x != p.x || p.q[i].sx) return static_cast<int>(MOFQ_ERR_UNSUPPORTED);
+      if (p.ldx != p.K) return static_cast<int>(MOFQ_ERR_UNSUPPORTED);
       if (PAIR && (!plan.shared || p.q[0].w != p.q[1].w)) return static_cast<int>(MOFQ_ERR_UNSUPPORTED);
-      if (plan.shared) {
+      // (a single format where products are workgroups of their own, each a whole one: there the sums are the same, and
+      // 256 x 4096 x 4096 takes 55.5 us instead of 63.4)
+      if (NQ == 2 ? plan.shared : plan.shared && plan.run == 0) {
         switch (plan.tile) {
-          case WaPlan::kLarge: shared(SharedLarge<PAIR>{}, wa_gemm_shared_kernel<SharedLarge<PAIR>>); break;
-          case WaPlan::kMedium: shared(SharedMedium<PAIR>{}, wa_gemm_shared_kernel<SharedMedium<PAIR>>); break;
-          default: shared(SharedSmall<PAIR>{}, wa_gemm_shared_kernel<SharedSmall<PAIR>>);
+          case WaPlan::kLarge: shared(SharedLarge<NQ, PAIR>{}, wa_gemm_shared_kernel<SharedLarge<NQ, PAIR>>); break;
+          case WaPlan::kMedium: shared(SharedMedium<NQ, PAIR>{}, wa_gemm_shared_kernel<SharedMedium<NQ, PAIR>>); break;
+          default: shared(SharedSmall<NQ, PAIR>{}, wa_gemm_shared_kernel<SharedSmall<NQ, PAIR>>);
         }
         return hip_status(hipGetLastError());
       }

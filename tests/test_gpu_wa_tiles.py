@@ -110,6 +110,51 @@ def test_weight_only_products(mq, name):
     wo.check_layer(mq, x, w, [I4, FP4], orc.PER_CHANNEL, mi.clip_ratios(1), name)
 
 
+@pytest.mark.parametrize("cands,gran,ratios", [([I4, FP4], orc.PER_CHANNEL, 1), ([FP4, I4], orc.PER_TENSOR, 1), ([I8, FP8], orc.PER_CHANNEL, 1),
+                                               ([I4, FP4], orc.PER_CHANNEL, 3)])
+@pytest.mark.parametrize("name", list(SHAPES))
+def test_weight_only_error_of_a_format_alone(mq, name, cands, gran, ratios):
+    """mofq_score's error and energy are the select's, bit for bit: Algorithm 1 put together from scores chooses alike."""
+    x, w = tensors(SHAPES[name], 8600)
+    r, _ = wo.run_select(mq, x, w, cands, gran, mi.clip_ratios(ratios))
+    for c, fmt in enumerate(cands):
+        assert wo.run_score(mq, x, w, fmt, gran, mi.clip_ratios(ratios)) == (r.err[c], r.ref_energy)
+
+
+@pytest.mark.parametrize("cands,gran", [([I8, FP8], orc.PER_CHANNEL), ([FP8, I8], orc.PER_TENSOR)])
+@pytest.mark.parametrize("name", list(SHAPES))
+def test_exact_error_of_a_format_alone(mq, name, cands, gran):
+    """The same with the activation quantized too, in the general path and the fused one."""
+    x, w = tensors(SHAPES[name], 8650)
+    cfg = mq.Cfg(gran, mi.clip_ratios(1))
+    r, _, _ = layers.run_single(mq, [w], [x], cands, mq.ERR_LAYER_OUTPUT, cfg)
+    for c, fmt in enumerate(cands):
+        err, en = (torch.zeros(1, dtype=torch.float64, device=DEV) for _ in range(2))
+        ws = torch.empty(mq.workspace_bytes(w, x, 1, mq.ERR_LAYER_OUTPUT, cfg), dtype=torch.uint8, device=DEV)
+        mq.score(w, x, fmt, mq.ERR_LAYER_OUTPUT, cfg, err, en, ws)
+        assert (err.item(), en.item()) == (r[0].err[c], r[0].ref_energy)
+
+
+@pytest.mark.parametrize("cands", [[I4, FP4], [FP4, I4], [I8, FP8]])
+@pytest.mark.parametrize("name", list(SHAPES))
+def test_weight_only_products_of_grid_values_have_no_error(mq, name, cands):
+    """Weights on a format's grid (scale 1): the reference and that format's product add up the same numbers in the same
+    order in every tiling and piece and from either kind of operand, so its error is exactly 0."""
+    M, N, K = SHAPES[name]
+    g = torch.Generator().manual_seed(K + 2)
+    x = mi.activations(M, K, seed=8700, device=DEV)
+    for fmt, levels in ((I4, torch.arange(-7.0, 8)), (FP4, torch.tensor([0.0, 0.5, 1, 1.5, 2, 3, 4, 6])), (I8, torch.arange(-127.0, 128))):
+        if fmt not in cands:
+            continue
+        w = levels[torch.randint(len(levels), (N, K), generator=g)] * (torch.randint(2, (N, K), generator=g) * 2 - 1)
+        w[:, 0] = levels.max()
+        w = w.to(torch.bfloat16).to(DEV)
+        c = cands.index(fmt)
+        r, _ = wo.run_select(mq, x, w, cands, orc.PER_CHANNEL, mi.clip_ratios(1))
+        assert r.err[c] == 0.0 and r.err[1 - c] > 0.0 and r.best == c
+        assert wo.run_score(mq, x, w, fmt, orc.PER_CHANNEL, mi.clip_ratios(1)) == (0.0, r.ref_energy)
+
+
 # Both candidates' 4-bit values in one operand, in either order, and what goes on as two operands, in each tile.
 @pytest.mark.parametrize("cands,ratios", [([FP4, I4], 1), ([I4, orc.FP4_E2M1_IEEE], 1), ([I8, FP8], 1), ([I4, FP4], 3)])
 @pytest.mark.parametrize("shape", [(449, 1040, 192), (65, 63, 64), (1601, 1345, 64), (2049, 2049, 128)])
