@@ -50,5 +50,15 @@ def build(jobs: int = 8) -> str:
     return LIB
 
 
+def build_library(src: str, lib: str) -> str:
+    """Compile one HIP source into a shared library of its own (what the tests run of the headers' functions)."""
+    tmp = lib + f".tmp{os.getpid()}"
+    r = subprocess.run([HIPCC, *FLAGS, "-shared", src, "-o", tmp], capture_output=True, text=True)
+    if r.returncode != 0:
+        raise RuntimeError(f"hipcc failed on {src}:\n{r.stderr}")
+    os.replace(tmp, lib)
+    return lib
+
+
 if __name__ == "__main__":
     print(build())

@@ -15,6 +15,7 @@
 namespace mofq {
 
 #define MOFQ_DEV __device__ __forceinline__
+#define MOFQ_BOTH __host__ __device__ __forceinline__   // also run on the host, by the tests
 
 MOFQ_DEV uint32_t f2u(float f) { return __builtin_bit_cast(uint32_t, f); }
 MOFQ_DEV float u2f(uint32_t u) { return __builtin_bit_cast(float, u); }

@@ -175,13 +175,16 @@ template <int FMT> constexpr uint32_t quad_step(int q) {
   return FMT == MOFQ_INT4 ? 8u * static_cast<uint32_t>(q) + 4u : (q < 7 ? e2m1[q] : 0u);
 }
 
-// unit_scale of a search for a finite absmax: ratio * absmax over QMAX by one multiplication and Markstein's correction, which is the
-// correctly rounded quotient for 7 and 6 (all mantissas checked) wherever it is at least 2^-126; a non-finite
-// unit comes out as 1.
-template <int FMT> MOFQ_DEV float search_scale(float ra, bool f16) {
+// ra / QMAX by one multiplication and Markstein's correction: the correctly rounded quotient for 7 and 6 (all mantissas
+// checked) wherever it is at least 2^-126.
+template <int FMT> MOFQ_BOTH float over_qmax(float ra) {
   constexpr float d = Codec<FMT>::QMAX, r = 1.0f / d;
   const float q = ra * r;
-  float s = __builtin_fmaf(__builtin_fmaf(-d, q, ra), r, q);
+  return __builtin_fmaf(__builtin_fmaf(-d, q, ra), r, q);
+}
+// unit_scale of a search for a finite absmax, ra = ratio * absmax; a non-finite unit comes out as 1.
+template <int FMT> MOFQ_DEV float search_scale(float ra, bool f16) {
+  float s = over_qmax<FMT>(ra);
   if (f16) s = round_fp16_clamped(s);
   if (!(s >= 0x1p-126f)) s = 1.0f;
   return s;
@@ -194,7 +197,7 @@ template <int FMT> MOFQ_DEV float search_scale(float ra, bool f16) {
 // are the pattern but for the difference of the biases.  Three instructions a boundary, against seven for a rounded
 // estimate and the decision itself on the next pattern.  Holds for normal numbers of the input type; a quotient
 // below the smallest one gives a number below its pattern.
-MOFQ_DEV double edge_unit(float s, float inv) {
+MOFQ_BOTH double edge_unit(float s, float inv) {
   const double sd = static_cast<double>(s);
   return __builtin_fma(sd, __builtin_fma(-sd, static_cast<double>(inv), 1.0), sd);
 }
@@ -205,7 +208,7 @@ template <typename In> MOFQ_DEV int pattern_before(int first) {
   asm("" : "+s"(b));   // opaque: one subtraction
   return b;
 }
-template <typename In> MOFQ_DEV int pattern_top(double edge, double unit) {
+template <typename In> MOFQ_BOTH int pattern_top(double edge, double unit) {
   return static_cast<int>(static_cast<uint32_t>(__builtin_bit_cast(uint64_t, edge * unit) >> 32) >> (20 - Pattern<In>::MANT));
 }
 template <typename In> MOFQ_DEV int patterns_below(double edge, double unit, int before) { return pattern_top<In>(edge, unit) - before; }
