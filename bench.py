@@ -452,7 +452,8 @@ def run_w8a8(args, shapes, dev, weights, w_only, fp8_unit, steps, warmup, ceilin
     roofline = {
         "bound": "mfma", "achieved": achieved, "peak": peak, "unit": "TFLOP/s",
         "frac": achieved / peak, "traffic": None,
-        "kernel": "wa_gemm_kernel (reference, INT8-code and E4M3 products of one linear)",
+        "kernel": ("wa_gemm_shared_kernel (reference, INT4 and E2M1 products of one linear, which share X)" if w_only else
+                   "wa_gemm_kernel (reference, INT8-code and E4M3 products of one linear)"),
         "note": "three products per launch, " + " + ".join(kinds) + "; peak is the rate at which the "
                 "three would finish if each ran at the published dense peak of its own type "
                 "(bf16 2.5, int8 5.0, fp8 5.0 PFLOP/s)",

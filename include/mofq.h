@@ -292,15 +292,17 @@ int mofq_select_layers_search_groups(int32_t n_layers, const mofq_tensor_t* w, c
  *              recorded on `stream` immediately before and after each layer's matrix kernel.
  * With candidates {MOFQ_INT8, MOFQ_FP8_E4M3} (either order) and per-tensor weight scales the
  * layers take a fused path in groups of up to 8 consecutive layers (a decoder block): the X
- * and W of a group go through the two quantize passes together (two launches), then one matrix
- * kernel per layer, one small kernel for the selects and the one-unit outputs of the group,
- * and one copy of the chosen codes; a layer whose activation descriptor equals the previous
- * layer's (the q/k/v or gate/up projections of a block given the same x) reuses its quantized
- * activation.  During the call w_out[i].codes holds W's E4M3 codes before the select; the
- * chosen format's codes are in place when the call's work has finished.  Other candidate lists
- * and per-channel weight scales go layer by layer through the general path of
- * mofq_select_layer.
- * Workspace: mofq_select_layers_wa_workspace_bytes (one group's operands, not n_layers').
+ * and W of a group go through the quantize passes together (two launches; with the fp8 unit a
+ * third before them), then the matrix kernels, in which layers of one tile share a launch (two
+ * launches where products are cut into pieces; in the _timed variant with events every layer
+ * has its own), then one launch for the selects, the one-unit outputs and the copies of the
+ * chosen codes; a layer whose activation descriptor equals the previous layer's (the q/k/v or
+ * gate/up projections of a block given the same x) reuses its quantized activation.  During the
+ * call w_out[i].codes holds W's E4M3 codes before the select; the chosen format's codes are in
+ * place when the call's work has finished.  Other candidate lists and per-channel weight scales
+ * go layer by layer through the general path of mofq_select_layer.
+ * Workspace: mofq_select_layers_wa_workspace_bytes (one group's operands and, where products
+ * are cut into pieces, every layer's partial sums, up to 64 MB a layer; not n_layers').
  * Everything is enqueued on `stream`; the library creates no events and keeps no state.
  */
 int mofq_select_layers_wa(int32_t n_layers, const mofq_tensor_t* w, const mofq_tensor_t* x,
@@ -368,7 +370,8 @@ int mofq_select_calibrated(const mofq_tensor_t* x, const int32_t* candidates, in
  * kernels (the scale search for the tensor metric, the matrix products for the
  * layer-output metric), so that a harness can time the dominant kernel inside its
  * own timed region.  Everything else is identical: where a per-channel search writes the
- * codes as well (one kernel; large tensors), the events enclose that too.
+ * codes as well (one kernel; from 1024 rows on, 8-bit formats from 2048, and as candidates with
+ * several clip ratios from 8192), the events enclose that too.
  */
 int mofq_select_layer_timed(const mofq_tensor_t* w, const mofq_tensor_t* x,
                             const int32_t* candidates, int32_t n_candidates, int32_t metric,
