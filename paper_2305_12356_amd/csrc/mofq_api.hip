@@ -183,19 +183,25 @@ bool one_sweep_launch(const int32_t* cand, int n_cand) {
 
 // Whether the search of these tensors (one launch) should write codes ahead (AheadCodes): it saves the emission's read of
 // the input and costs the codes of a row in the search and the rows that are done twice.  Layer selection, us, emission behind
-// the search -> codes ahead, a row in its own better format (in brackets with half of the rows in either format):
-//   one clip ratio: fp32 1024 x 1024 9.4 -> 8.8 (9.6 -> 9.5), 4096 x 4096 32.6 -> 23.8 (32.6 -> 29.8), 2048 x 11008 39.7 -> 25.7; fp16 4096
-//     x 11008 59.9 -> 45.5 (59.7 -> 56.8); from 128 MB on the rows done twice come from HBM and a tally of the finished rows saves
-//     most of them: fp32 16384 x 16384, new inputs for each call, 243 with a tally, 245 without;
-//   4 bits by histogram: bf16 1237 x 5000, 100 ratios 23.4 -> 20.1, 4096 x 4096, 50 ratios 39.5 -> 37.2 (43.3 -> 42.7), fp16 4096 x 11008
-//     71.2 -> 61.4 (85.2 -> 85.0); from 8192 rows on most rows find a tally, which pays where launches queue up: two 65B blocks
-//     2120 -> 1991, 11008 x 4096 87.3 -> 85.1;
+// the search -> codes ahead, for rows that all favour the tensor's choice (in brackets: every second row does; one row in 32 does, whose
+// errors outweigh the others'):
+//   one clip ratio, a row in its own better format: fp32 1024 x 1024 10.7 -> 10.0 (10.7 -> 10.7; 10.9 -> 10.9), 4096 x 4096 36.0 -> 27.0 (35.9
+//     -> 33.2; 36.0 -> 37.6), 2048 x 11008 42.9 -> 28.9 (43.1 -> 37.6; 43.7 -> 44.0), 8 bits 4096 x 4096 38.3 -> 29.1 (38.3 -> 35.5; 38.4 -> 40.6);
+//     fp16 4096 x 11008 60.7 -> 46.2 (60.7 -> 58.4; 61.5 -> 68.8); from 128 MB on the rows done twice come from HBM and a tally of the finished
+//     rows saves most of them: fp32 16384 x 16384 394 -> 241 (405 -> 356; 392 -> 447), without the tally 232 (351; 424) on one
+//     tensor again and again and the same 246 as with it on two in turn;
+//   4 bits by histogram, a row in its own better format: bf16 1237 x 5000, 100 ratios 23.3 -> 18.9 (25.6 -> 22.6; 25.3 -> 23.8), 4096 x 4096, 50
+//     ratios 38.6 -> 34.3 (43.5 -> 42.6; 42.9 -> 45.3), fp16 4096 x 11008 74.7 -> 60.7 (90.5 -> 90.4; 89.3 -> 98.1); from 8192 rows on most
+//     rows find a tally, which pays where launches queue up: eight 7B blocks 2857 (behind), 2820 (own format), 2704 (tally), two 65B
+//     blocks 2195, 2126, 1984; alone it does not, 11008 x 4096 96.1 -> 81.9 with the own format, 83.7 with a tally (108 -> 105, 107; 108
+//     -> 113, 115);
 //   8 bits by histogram: codes of its own format lengthen the rounds of a row by what the emission took: 3001 x 5000, 50 ratios 60.9 ->
-//     62.4 (64.9 -> 61.3), 2500 x 11008 75.4 -> 75.9, 1237 x 5000 34.6 -> 31.6; only with a tally.
-// Fewer than 1024 rows (8 bits, whose rows agree less: 2048): the emission requests its input before the select, rows that are
-// done twice only after it, and few workgroups share them: fp32 64 x 16384, one ratio, 8 bits 10.8 -> 14.0, 1024 x 8192 16.5 -> 19.8,
-// 1500 x 16384 43.9 -> 38.2, bf16 256 x 11008, 4 bits, 50 ratios 15.0 -> 16.2, 1024 x 16384 (37.0 -> 40.4).
-// Beside the searches of a following batch the emission costs nothing that is waited for (mofq_select_layers).
+//     62.4, 2500 x 11008 75.4 -> 75.9, 1237 x 5000 34.6 -> 31.6; only with a tally: 8192 x 4096 114 -> 105 (122 -> 125; 121 -> 128).
+// So it gains 7 to 39 % where the rows agree and up to 18 % where half of them do, and loses up to a seventh where a few rows
+// decide against nearly all others.  Wide tensors of just 1024 rows lose with half of them too: 1024 x 8192 fp32 18.4 -> 16.3 (18.4 -> 19.5; 18.8 ->
+// 21.7), bf16 1024 x 16384, 50 ratios 31.4 -> 28.4 (37.8 -> 39.9; 36.9 -> 42.1); but fp32 1300 x 8192 28.9 -> 19.9 (28.9 -> 23.8; 29.2 -> 26.2).  Fewer than 1024 rows (8 bits, whose rows agree less: 2048): the emission requests its input before the select, rows that are
+// done twice only after it, and few workgroups share them: fp32 64 x 16384, one ratio, 8 bits 10.8 -> 14.0, bf16 256 x 11008, 4 bits, 50
+// ratios 15.0 -> 16.2.  Beside the searches of a following batch the emission costs nothing that is waited for (mofq_select_layers).
 constexpr int64_t kOwnRows = 1024, kAheadRows = 8192, kTallyBytes = int64_t{128} << 20;
 enum class Ahead { kNo, kOwn, kTallied };
 Ahead codes_ahead(const mofq_tensor_t* t, const int32_t* cand, int n_cand, const mofq_scale_cfg_t* cfg, int64_t launch_rows, int64_t launch_bytes) {
@@ -586,9 +592,9 @@ int select_wa_general(const mofq_tensor_t* w, const mofq_tensor_t* x, const int3
 
 // ---- the fused weight-activation path ----------------------------------------------------
 // INT8 against FP8-E4M3 with per-tensor weight scales (the configuration of Section 5's
-// W8A8 experiments).  Per layer: the two quantize passes over X and W together
-// (launch_wa_prep), the matrix kernel, one small kernel for select + one-unit outputs, and a
-// copy of the chosen codes.  The weight's E4M3 codes are written straight into the caller's
+// W8A8 experiments).  Per group of layers: the quantize passes over all X and W together
+// (launch_wa_prep), the matrix kernels (launch_wa_gemms: layers of one tile share a launch), and
+// one launch for the selects, the one-unit outputs and the copies of the chosen codes (launch_wa_finish).  The weight's E4M3 codes are written straight into the caller's
 // code buffer by the quantize pass (they are an operand of the fp8-unit product, and the
 // output itself if E4M3 is chosen); if INT8 is chosen its codes are copied over them.  An
 // activation that the previous layer of the call already used (same descriptor: the q/k/v
@@ -1111,7 +1117,7 @@ void plan_search_groups(const mofq_tensor_t* w, int nb, const int32_t* cand, int
 
 // Scales per group: every tensor is a search launch of its own, so the last batch is emitted in two parts, the first one's
 // emission beside the second one's searches, which take ten times as long per byte.  The second part holds an eighth of the
-// batch or the last tensor, in the order of the searches (`order`: places in w).  A 7B block, groups of 128, 50 ratios 1132 -> 1085 us.
+// batch or the last tensor, in the order of the searches (`order`: places in w).  A 7B block, groups of 128, 50 ratios 1131 -> 1108 us.
 int first_part(const mofq_tensor_t* w, const int* order, int nb) {
   int64_t total = 0, tail = 0;
   for (int j = 0; j < nb; ++j) total += w[j].rows * w[j].cols;

@@ -711,22 +711,21 @@ bool in_domain(const SweepParams& p) {
   if (eight_bit(p)) {
     // The histogram costs a row much the same whatever the number of candidates up to 64 and again beyond, scoring them
     // costs their pairs with its elements. (The number of rows must not enter: tensors of one row length share a launch.)
-    // bf16, measured at the line, layer selection of
-    // 4096 rows, us, directly / by histogram: the pair, 1024 columns x 36 ratios 72 / 66, 2048 x 18 70 / 69, 4096 x 9
-    // 78 / 80, 5120 x 8 88 / 89; INT8, 1536 x 32 46 / 43, 2048 x 24 45 / 45, 4096 x 14 56 / 56, 5120 x 12 62 / 61;
-    // E4M3, 1536 x 28 50 / 49, 2048 x 22 52 / 50, 4096 x 11 59 / 59, 5120 x 9 63 / 64.
+    // bf16: the lines lie where the times crossed while a look-up took 13 instructions; it takes 8 now and they cross lower, at about 25000 (the
+    // pair and E4M3) and 37000 (INT8).  Layer selection of 4096 rows, us, directly / by histogram: the pair, 1024 columns x 24 ratios 52 /
+    // 52, 1024 x 32 63 / 52, 2048 x 12 53 / 54, 2048 x 16 63 / 54, 4096 x 9 77 / 64, 5120 x 8 87 / 72; INT8, 1536 x 24 38 / 38, 1536 x 32 44 /
+    // 38, 2048 x 20 41 / 38, 4096 x 10 48 / 44, 4096 x 14 56 / 44; E4M3, 1536 x 20 41 / 36, 2048 x 14 40 / 36, 4096 x 8 51 / 42, 4096 x 11 59
+    // / 41.
     // fp16 has eight times the patterns, in groups. A row's steps between loads and look-ups take some us more per 4096
     // columns, and so does a second 64 candidates; the zeros that fill the row's last 4096 columns cost up to a quarter, for
     // they share one counter where the counters reach down to the pattern of zero (E4M3's do). That part is capped: few rows
     // are looked up faster than all of this says (300 rows, the pair, 4096 columns x 24 ratios 45 / 28), many are not. 2048
-    // rows, directly / by look-up, on either side of the line: the pair, 1024 columns x 128 ratios 114 / 132, 2048 x 50 83 /
-    // 93, 2048 x 64 102 / 93, 2048 x 65 104 / 127, 2048 x 100 151 / 127, 4096 x 24 79 / 86, 4096 x 28 89 / 86, 4104 x 32 113 /
-    // 114, 4104 x 40 135 / 115, 5000 x 24 100 / 110, 5000 x 28 112 / 110, 8192 x 12 89 / 97, 8192 x 14 99 / 97, 8200 x 16 112 /
-    // 125, 8200 x 20 132 / 125, 11008 x 10 105 / 113, 11008 x 12 117 / 113, 16384 x 8 127 / 122; INT8, 2048 x 64 53 / 58, 2048 x
-    // 128 92 / 76, 3072 x 50 56 / 59, 3072 x 64 67 / 59, 4096 x 32 50 / 59, 4096 x 50 69 / 60, 8192 x 20 66 / 70, 8192 x 24 73 /
-    // 70, 12288 x 16 78 / 81, 12288 x 20 89 / 82; E4M3, 2048 x 64 64 / 66, 4096 x 24 51 / 56, 4096 x 32 62 / 56, 4104 x 40 86 /
-    // 86, 4104 x 50 102 / 85, 5000 x 32 79 / 81, 5000 x 40 92 / 81, 8192 x 14 66 / 67, 8192 x 16 72 / 67, 8200 x 20 84 / 95, 8200
-    // x 28 106 / 95, 11008 x 12 78 / 82, 11008 x 14 85 / 82.
+    // rows, directly / by look-up: the pair, 1024 columns x 128 ratios 113 / 124, 2048 x 50 84 / 89, 2048 x 64 103 / 89, 2048 x 65 105 /
+    // 119, 2048 x 100 151 / 120, 4096 x 24 80 / 82, 4096 x 28 90 / 82, 5000 x 24 99 / 105, 5000 x 28 111 / 105, 8192 x 12 89 / 92, 8192 x 14
+    // 98 / 92, 11008 x 10 105 / 110, 11008 x 12 116 / 110, 16384 x 8 128 / 116; INT8, 2048 x 64 53 / 53, 2048 x 128 92 / 68, 3072 x 50 56 /
+    // 54, 4096 x 32 51 / 54, 4096 x 50 69 / 54, 8192 x 20 65 / 61, 8192 x 24 73 / 61; E4M3, 2048 x 64 65 / 62, 4096 x 24 52 / 52, 4096 x 32
+    // 63 / 52, 5000 x 32 78 / 76, 8192 x 14 65 / 58, 8200 x 28 106 / 87, 11008 x 12 77 / 71.  (INT8 and E4M3 alone cross up to a fifth below their
+    // lines, which are as old as bf16's.)
     const int64_t fill = (p.cols + 4095) / 4096 * 4096 - p.cols;
     const int more = p.n_clip > 64 ? 1 : 0;
     int64_t line = p.n_fmt == 2 ? 36864 : (p.fmt[0] == MOFQ_INT8 ? 53248 : 45056);

@@ -295,7 +295,7 @@ MOFQ_DEV void pick_columns(const PrepTensor& t) {
 
 // First pass: largest magnitudes, a workgroup to a segment (a share of 2500 workgroups to a tensor, 1.2 rounds of resident ones, 95 us
 // for the 405 MB of a 7B block's weights, 84 us so).  The tensors and their segments in descending order: the quantize pass begins
-// with what was read last, which the 256 MB cache still holds.  The activations of a column split, a workgroup each, come first: their largest magnitude
+// with what was read last (a block of 4096, 200 tokens 711 -> 704 us, 3008, 400 tokens 519 -> 512; smaller ones and a layer alone even).  The activations of a column split, a workgroup each, come first: their largest magnitude
 // is that of the column maxima.  Picking their columns beside the weights' largest magnitudes instead of before them takes a launch
 // of 15 us out of a 7B block's step.
 __global__ __launch_bounds__(kThreads) void wa_absmax_kernel(const PrepArgs a) {
@@ -472,8 +472,9 @@ int launch_wa_prep(const WaPrepTensor* p, int n, hipStream_t st) {
   }
   if (a.n < 1) return MOFQ_OK;
   // One workgroup per segment, but for up to twice as many segments as 16 workgroups per compute unit a share of those: short
-  // segments hardly pay for the fold before them.  (Shares for any number: a block of 4096, 200 tokens, exact 824 -> 801 us without,
-  // 3008, 400 tokens 620 -> 608; 1024, 1000 tokens, fp8 unit 163 -> 166.)
+  // segments hardly pay for the fold before them.  Exact / fp8 unit, us, without shares -> with: a block of 1024, 1000 tokens 157.7 ->
+  // 156.7 / 160.7 -> 158.4, 2048, 64 tokens 130.2 -> 130.1 / 133.3 -> 130.7; but 4096, 64 tokens, whose segments are four times as long, 441 -> 454 /
+  // 446 -> 448.  Beyond that number they lose for all: 4096, 200 tokens, exact 801 -> 824, 3008, 400 tokens 608 -> 620.
   constexpr int64_t kShares = 4096;
   for (int k = 0; k < a.n; ++k) {
     int64_t nb = a.t[k].n_seg;
